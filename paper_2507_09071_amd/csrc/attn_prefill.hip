@@ -36,6 +36,8 @@
 #include <type_traits>
 #include <vector>
 
+#include "attn_common.h"
+#include "attn_rows.h"
 #include "device_map.h"
 #include "tilemap_internal.h"
 
@@ -64,13 +66,7 @@ struct KernelArgs {
         const int32_t *__restrict__ map_free_before, const int2 *__restrict__ map_span_free
 #define BS_MAP_ARGS(d) (d)->code, (d)->text_bits, (d)->sink_bits, (d)->span_range, (d)->row_ptr, (d)->ranges, (d)->work, (d)->head_class, (d)->row_order, (d)->key_order, (d)->free_before, (d)->span_free
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kBlockM = 128, kBlockN = 64, kThreads = 256;
+constexpr int kThreads = 256;
 
 // Walks the key tiles of one (class, query tile): ranges of [begin, end) with a FULL flag.
 struct TileWalker {
@@ -208,19 +204,6 @@ __device__ inline void apply_mask_tight(const floatx16 (&s)[2], floatx16 (&ms)[2
                 : "v"(w[kb]), "n"(8 * (v / 4) + (v % 4)), "v"(s[kb][v]), "v"(ninf));
             ms[kb][v] = r;
         }
-}
-
-__device__ inline float max_across_halves(float x)
-{
-    // r[0] = (x.lo, x.lo), r[1] = (x.hi, x.hi): both halves see both values
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ inline float sum_across_halves(float x)
-{
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // Online-softmax update (running max m, running sum l, rescale factor alpha; App. kernel
@@ -1152,6 +1135,7 @@ int device_setup(int dev, void **scratch_out, int *n_cus_out)
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs::attn_prefill_f32<128>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bs::f32_lds_bytes<128>());
+        if (e == hipSuccess) e = bs::rows_device_setup();
         if (e != hipSuccess) return bs::fail_hip(e, "hipFuncSetAttribute");
         int cus = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1230,7 +1214,7 @@ size_t bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
 extern "C" int bs_tilemap_upload(bs_tilemap *tm)
 {
     if (!tm) return BS_EINVAL;
-    if (tm->dev) return BS_OK;
+    if (tm->dev && tm->dev->blob) return BS_OK;
     const int rc = bs::upload_prompt_part(tm, nullptr);
     if (rc != BS_OK) return rc;
     const hipError_t e = hipStreamSynchronize(nullptr);   // this entry point promises a finished upload
@@ -1273,7 +1257,7 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
     int rc = check_call(q, k, v, out, tm, dtype, n_q_heads, gqa_group, head_dim, scale);
     if (rc != BS_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
+    if ((rc = bs::ensure_device_map(tm, st)) != BS_OK) return rc;
     DeviceMap *d = tm->dev;
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -1282,20 +1266,34 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
     int n_cus = 0;
     if ((rc = device_setup(dev, nullptr, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
-    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, st);
-    if (rc != BS_OK) return rc;
+    const bs::RowsPlan rows = bs::plan_rows(tm, dtype, gqa_group, head_dim, n_cus);
+    if (!rows.use || rows.need_bits)
+        if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
+    if (!rows.use) {
+        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, st);
+        if (rc != BS_OK) return rc;
+    }
 
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
-    if (dtype == BS_BF16) {
-        // workspace of the pre-pass: packed K tiles, then packed V^T tiles (owned by the map)
+    // workspace of the call, owned by the map
+    auto workspace = [&](size_t bytes) {
+        if (d->vt_bytes >= bytes) return BS_OK;
+        bs::pool_release(dev, d->vt_buf, d->vt_bytes, d->last_use);
+        d->vt_buf = nullptr; d->vt_bytes = 0;
+        e = bs::pool_acquire(dev, bytes, st, &d->vt_buf, &d->vt_bytes);
+        if (e == hipSuccess) return BS_OK;
+        d->vt_buf = nullptr; d->vt_bytes = 0;
+        return bs::fail_hip(e, "hipMalloc(workspace)");
+    };
+    if (rows.use) {
+        if ((rc = workspace(rows.workspace)) != BS_OK) return rc;
+        if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
+        bs::launch_rows(rows, q, k, v, out, tm, d, d->vt_buf, gqa_group, head_dim, scale, st);
+    } else if (dtype == BS_BF16) {
+        // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
         const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
-        if (d->vt_bytes < 2 * pack_bytes) {
-            bs::pool_release(dev, d->vt_buf, d->vt_bytes, d->last_use);
-            d->vt_buf = nullptr; d->vt_bytes = 0;
-            e = bs::pool_acquire(dev, 2 * pack_bytes, st, &d->vt_buf, &d->vt_bytes);
-            if (e != hipSuccess) { d->vt_buf = nullptr; d->vt_bytes = 0; return bs::fail_hip(e, "hipMalloc(K / V^T workspace)"); }
-        }
+        if ((rc = workspace(2 * pack_bytes)) != BS_OK) return rc;
         if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, st, ev_main_start);
         else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, st, ev_main_start);
     } else {
@@ -1327,12 +1325,6 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
                                        "(after every bs_tilemap_rebind); this entry point uploads and allocates nothing");
     const int n_kv_heads = n_q_heads / gqa_group;
     const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
-    if (2 * pack_bytes > kStaticScratchBytes) {
-        snprintf(bs::g_last_error, sizeof bs::g_last_error,
-                 "bs_attn_prefill_static: packed K / V^T tiles need %zu bytes, the static scratch holds %zu "
-                 "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", 2 * pack_bytes, kStaticScratchBytes);
-        return BS_EUNSUPPORTED;
-    }
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return bs::fail_hip(e, "hipGetDevice");
@@ -1340,12 +1332,20 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     void *ws = nullptr;
     int n_cus = 0;
     if ((rc = device_setup(dev, &ws, &n_cus)) != BS_OK) return rc;   // looks the address up on the first call per device
+    const bs::RowsPlan rows = bs::plan_rows(tm, BS_BF16, gqa_group, head_dim, n_cus);
+    if ((rows.use ? rows.workspace : 2 * pack_bytes) > kStaticScratchBytes) {
+        snprintf(bs::g_last_error, sizeof bs::g_last_error,
+                 "bs_attn_prefill_static: packed K / V^T tiles need %zu bytes, the static scratch holds %zu "
+                 "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", 2 * pack_bytes, kStaticScratchBytes);
+        return BS_EUNSUPPORTED;
+    }
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
-    // the pre-pass writes every slot of every tile it covers (keys, or zeros): nothing of the
-    // previous call's contents is read
-    if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, st, nullptr);
+    // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
+    // call's contents is
+    if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, st, nullptr);
     else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");

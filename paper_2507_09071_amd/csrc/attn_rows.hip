@@ -1,0 +1,470 @@
+// Few query rows against a long KV cache: a decoding step (one row per head) or a handful of draft tokens.
+//
+// The 128-row query tiles of the prefill kernel are the wrong shape here.  The work is reading K and V once,
+// so the bound is HBM, and what the prefill path does around it (a packed copy of K and V, one workgroup per
+// two heads walking the whole cache) cost many times the read.  Measured, one row: 28 heads over 39.5K keys of
+// 4 KV heads (81 MB) 893 us there, 18.5 + 5 us here (4.4 TB/s in the first kernel); 32 heads over 302K keys of
+// 16 KV heads (2.5 GB) 7460 us there, 413 + 4 us here (6.0 TB/s; a large copy reaches 4.7).  How:
+//  * the query rows of ALL heads of a GQA group are stacked (head-major) into blocks of 32 rows, the free
+//    dimension of a 32x32x16 MFMA, so K and V of a KV head are read once for the whole group;
+//  * the keys are split over the chip: grid (parts, KV heads, row groups), about one workgroup per CU; its
+//    four waves take every fourth block of 32 keys and run on their own: no barrier in the loop;
+//  * K and V blocks go global -> LDS straight from the caller's arrays with 16-byte LDS-direct loads, whole
+//    rows at a time, two blocks deep: 32-64 KB in flight per wave, which is what covers the latency of HBM.
+//    The 16-byte chunks of a row are exchanged (XOR with the row) so that column reads are free of conflicts;
+//  * V^T comes out of LDS through the transposing 64-bit read; scores and softmax are as in the prefill kernel;
+//  * the four waves merge through LDS, the parts through a second, small kernel.
+// Masks: the rows see keys of the prompt in position order, every allowed pair once; a mask word is formed per
+// row and block from the row's bounds, its image and (image rows of sparse heads only) the text / sink bits.
+#include "attn_rows.h"
+
+#include <algorithm>
+#include <climits>
+#include <type_traits>
+#include <cmath>
+
+#include "attn_common.h"
+#include "device_map.h"
+
+namespace bs {
+
+constexpr int kRowsWaves = 4, kRowsThreads = 64 * kRowsWaves, kRowsKeys = 32;
+constexpr int kRowsMaxRows = 32, kRowsMaxHeads = 512;
+
+// What one query row sees, whatever the head's class: keys first .. last, and for an image row its image.
+struct RowBounds {
+    int32_t first, last;
+    int32_t img_lo, img_hi;   // own image, empty for a text row
+};
+
+struct RowsArgs {
+    const void *q, *k, *v;
+    void *out;
+    float *part_o;       // [KV head][row group][part][row][D]
+    float2 *part_ml;     // [KV head][row group][part][row]: reference point and row sum of a part
+    const uint64_t *text_bits, *sink_bits;
+    int32_t L, R, G;
+    int32_t k0, n_blocks;
+    float scale_log2e;
+    RowBounds rows[kRowsMaxRows];
+    uint32_t classes[kRowsMaxHeads / 16];   // two bits per head
+};
+
+template <int D>
+struct RowsTraits {
+    static constexpr int kRowBytes = D * 2;
+    static constexpr int kBlock = kRowsKeys * kRowBytes;    // one block of K or V
+    static constexpr int kLoads = kBlock / 1024;            // LDS-direct instructions per block
+    static constexpr int kWave = 4 * kBlock;                // two stages of K and V
+    static constexpr int kRing = kRowsWaves * kWave;
+    static constexpr int kLds = kRing + kRowsWaves * 64 * 8;
+    static constexpr int kPerCu = D == 64 ? 2 : 1;          // workgroups per CU
+    // exchange of the 16-byte chunks of row r: rows that share their banks get different chunks
+    __device__ static int swizzle(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
+};
+
+__device__ inline uint32_t mask_below(int x)   // bits [0, x) of 32
+{
+    return x >= 32 ? ~0u : (x <= 0 ? 0u : (1u << x) - 1u);
+}
+
+template <int D, int NRB>
+__global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void attn_rows_bf16(const RowsArgs a)
+{
+    using TR = RowsTraits<D>;
+    constexpr int NT = D / 16, NDB = D / 32, ROWB = TR::kRowBytes, BLK = TR::kBlock, NI = TR::kLoads;
+    extern __shared__ __align__(1024) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int part = blockIdx.x, kvh = blockIdx.y, grp = blockIdx.z, n_parts = gridDim.x;
+    const int S = a.G * a.R;   // stacked rows of a KV head
+
+    // ---- the rows of this lane (column `col` of every row block)
+    bf16x8 q[NRB][NT];
+    int first[NRB], last[NRB], own_lo[NRB], own_hi[NRB];
+    bool sees_all[NRB], sinks[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const int s = min((grp * NRB + rb) * 32 + col, S - 1);   // a slot without a row works on a copy, never stored
+        const int g = s / a.R, r = s - g * a.R, head = kvh * a.G + g;
+        const __bf16 *qr = static_cast<const __bf16 *>(a.q) + ((size_t)head * a.R + r) * D;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) q[rb][t] = *reinterpret_cast<const bf16x8 *>(qr + 16 * t + 8 * hl);
+        const RowBounds b = a.rows[r];
+        const int cls = (a.classes[head >> 4] >> (2 * (head & 15))) & 3;
+        first[rb] = b.first;
+        last[rb] = b.last;
+        sees_all[rb] = cls == BS_DENSE || b.img_hi == b.img_lo;
+        sinks[rb] = cls & 1;
+        own_lo[rb] = (cls & 2) ? b.img_lo : 0;
+        own_hi[rb] = (cls & 2) ? b.img_hi : 0;
+    }
+    // The query rows must be here before the loop: the compiler would wait for them inside it, and with them for
+    // the LDS-direct loads, which it does not know.
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(q[rb][t]));
+    bool all_see_all = true;
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) all_see_all = all_see_all && __all(sees_all[rb]);
+
+    floatx16 o[NRB][NDB];
+    float m_run[NRB], l_run[NRB];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        m_run[rb] = -INFINITY;
+        l_run[rb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[rb][db][i] = 0.f;
+    }
+
+    // ---- key blocks of this wave
+    const int b_begin = (int)((int64_t)a.n_blocks * part / n_parts);
+    const int b_end = (int)((int64_t)a.n_blocks * (part + 1) / n_parts);
+    const int n_steps = b_end - b_begin > wave ? (b_end - b_begin - wave + kRowsWaves - 1) / kRowsWaves : 0;
+    const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * a.L * ROWB;
+    const char *vh = static_cast<const char *>(a.v) + (size_t)kvh * a.L * ROWB;
+    auto block_of = [&](int i) { return a.k0 + b_begin + wave + kRowsWaves * i; };
+
+    // LDS-direct loads of a block: instruction j moves 1 KB, i.e. 1024 / ROWB whole rows; a lane picks the chunk
+    // of its row that belongs at its place.
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const uint32_t ring = (uint32_t)(uintptr_t)(lds_ptr)lds + wave * TR::kWave;
+    uint32_t voff[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int r = j * (1024 / ROWB) + lane / (ROWB / 16), p = lane % (ROWB / 16);
+        voff[j] = r * ROWB + ((p ^ TR::swizzle(r)) << 4);
+    }
+    auto issue = [&](const char *base, int blk, uint32_t dst) __attribute__((always_inline)) {
+        const char *src = base + (size_t)blk * BLK;
+        const int rows_left = a.L - blk * kRowsKeys;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            uint32_t off = voff[j];
+            if (rows_left < kRowsKeys) {   // the last block of the cache: rows past its end repeat the last one (masked)
+                const int r = j * (1024 / ROWB) + lane / (ROWB / 16);
+                off = off % ROWB + min(r, rows_left - 1) * ROWB;
+            }
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                         :
+                         : "v"(off), "s"(src), "s"(dst + j * 1024)
+                         : "memory", "m0");
+        }
+    };
+    // at most `kNewer` blocks issued after the one that is waited for
+    auto wait_loads = [&](auto newer) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(newer)::value * NI) : "memory");
+    };
+    auto reads_done = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+    using N0 = std::integral_constant<int, 0>;
+    using N1 = std::integral_constant<int, 1>;
+    using N2 = std::integral_constant<int, 2>;
+    using N3 = std::integral_constant<int, 3>;
+
+    const uint32_t k_read = wave * TR::kWave + col * ROWB + ((hl ^ TR::swizzle(col)) << 4);
+    uint32_t v_read[2];
+    {
+        const int i = lane & 15, half = (lane >> 4) & 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = 8 * h + 4 * hl + (i >> 2);
+            v_read[h] = wave * TR::kWave + BLK + r * ROWB + (((2 * half + ((i >> 1) & 1)) ^ TR::swizzle(r)) << 4) + (i & 1) * 8;
+        }
+    }
+
+    if (n_steps > 0) {
+        issue(kh, block_of(0), ring);
+        issue(vh, block_of(0), ring + BLK);
+    }
+    if (n_steps > 1) {
+        issue(kh, block_of(1), ring + 2 * BLK);
+        issue(vh, block_of(1), ring + 3 * BLK);
+    }
+    for (int i = 0; i < n_steps; ++i) {
+        const int stage = (i & 1) * 2 * BLK;
+        const int blk = block_of(i);
+        const bool more = i + 1 < n_steps, more2 = i + 2 < n_steps;
+
+        // ---- S^T = K Q^T
+        if (more) wait_loads(N3{}); else wait_loads(N1{});
+        floatx16 s[NRB];
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[rb][e] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const bf16x8 f = *reinterpret_cast<const bf16x8 *>(lds + ((k_read + stage) ^ (t << 5)));
+#pragma unroll
+            for (int rb = 0; rb < NRB; ++rb) s[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, q[rb][t], s[rb], 0, 0, 0);
+        }
+        reads_done();
+        if (more2) issue(kh, block_of(i + 2), ring + stage);
+
+        // ---- mask and online softmax (lane: 16 keys 8 (e / 4) + 4 hl + e % 4 of one row per block)
+        bf16x8 p[NRB][2];
+        const int n0 = blk * kRowsKeys;
+        uint32_t tb = 0, sb = 0;
+        if (!all_see_all) {
+            // scalar loads: a vector load would be waited for together with the LDS-direct loads in flight
+            typedef const __attribute__((address_space(4))) uint32_t *scalar_words;
+            tb = ((scalar_words)(uintptr_t)a.text_bits)[blk];
+            sb = ((scalar_words)(uintptr_t)a.sink_bits)[blk];
+        }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            uint32_t allowed = ~0u;
+            if (!sees_all[rb])
+                allowed = tb | (sinks[rb] ? sb : 0u) | (mask_below(own_hi[rb] - n0) & ~mask_below(own_lo[rb] - n0));
+            allowed &= mask_below(last[rb] + 1 - n0) & ~mask_below(first[rb] - n0);
+            if (!__all(allowed == ~0u)) {
+                const uint32_t w = allowed >> (4 * hl);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) s[rb][e] = (w & (1u << (8 * (e / 4) + e % 4))) ? s[rb][e] : -INFINITY;
+            }
+            float mx = s[rb][0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[rb][e]);
+            mx = max_across_halves(mx);
+            // the reference point moves only when the block's maximum exceeds it by 2^8 (any reference gives the
+            // same quotient), so the accumulators are rescaled a few times per row and not once per block
+            const float c = a.scale_log2e;
+            const bool grow = fmaf(mx, c, -(m_run[rb] * c)) > 8.f;
+            const float m_new = grow ? mx : m_run[rb];
+            const float off = m_new == -INFINITY ? 0.f : -(m_new * c);   // no key so far: p = 0
+            const float alpha = grow ? __builtin_amdgcn_exp2f(fmaf(m_run[rb], c, off)) : 1.f;
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float pv = __builtin_amdgcn_exp2f(fmaf(s[rb][e], c, off));
+                sum += pv;
+                p[rb][e >> 3][e & 7] = (__bf16)pv;
+            }
+            l_run[rb] = fmaf(l_run[rb], alpha, sum);
+            m_run[rb] = m_new;
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[rb][db][e] *= alpha;
+            }
+        }
+
+        // ---- O^T += V^T P^T
+        if (more2) wait_loads(N3{}); else if (more) wait_loads(N2{}); else wait_loads(N0{});
+        typedef __attribute__((address_space(3))) bf16x4 *lds_bf16x4;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+                bf16x8 f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bf16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                        (lds_bf16x4)(lds + ((v_read[h] + stage + t * 16 * ROWB) ^ (db << 6))));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[4 * h + e] = x[e];
+                }
+#pragma unroll
+                for (int rb = 0; rb < NRB; ++rb)
+                    o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, p[rb][t], o[rb][db], 0, 0, 0);
+            }
+        reads_done();
+        if (more2) issue(vh, block_of(i + 2), ring + stage + BLK);
+    }
+
+    // ---- merge of the four waves, through LDS (the ring is free after the barrier)
+    constexpr int ROWS = NRB * 32, CH4 = D / 4;
+    float2 *ml = reinterpret_cast<float2 *>(lds + TR::kRing);   // [wave][row]
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const float l = sum_across_halves(l_run[rb]);
+        if (hl == 0) ml[wave * ROWS + rb * 32 + col] = make_float2(m_run[rb], l);
+    }
+    __syncthreads();
+    const int n_rows = min(ROWS, S - grp * ROWS);
+    float4 *stage = reinterpret_cast<float4 *>(lds);
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const int row = rb * 32 + col;
+        float m = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kRowsWaves; ++w) m = fmaxf(m, ml[w * ROWS + row].x);
+        const float f = m_run[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[rb] - m) * a.scale_log2e);
+        if (row < n_rows)
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    stage[(wave * ROWS + row) * CH4 + ((db * 8 + 2 * g + hl) ^ (col & (CH4 - 1)))] =
+                        make_float4(o[rb][db][4 * g] * f, o[rb][db][4 * g + 1] * f, o[rb][db][4 * g + 2] * f, o[rb][db][4 * g + 3] * f);
+    }
+    __syncthreads();
+    const size_t slot = ((size_t)(kvh * gridDim.z + grp) * n_parts + part) * ROWS;
+    for (int idx = tid; idx < n_rows * CH4; idx += kRowsThreads) {
+        const int row = idx / CH4, ch = idx % CH4;
+        float m = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < kRowsWaves; ++w) m = fmaxf(m, ml[w * ROWS + row].x);
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < kRowsWaves; ++w) {
+            const float2 x = ml[w * ROWS + row];
+            l += x.x == -INFINITY ? 0.f : x.y * __builtin_amdgcn_exp2f((x.x - m) * a.scale_log2e);
+            const float4 y = stage[(w * ROWS + row) * CH4 + (ch ^ (row & 31 & (CH4 - 1)))];
+            sum.x += y.x; sum.y += y.y; sum.z += y.z; sum.w += y.w;
+        }
+        if (n_parts == 1) {
+            const float inv = l > 0.f ? 1.f / l : 0.f;
+            const int s = grp * ROWS + row, g = s / a.R, r = s - g * a.R;
+            bf16x4 w;
+            w[0] = (__bf16)(sum.x * inv); w[1] = (__bf16)(sum.y * inv); w[2] = (__bf16)(sum.z * inv); w[3] = (__bf16)(sum.w * inv);
+            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + ((size_t)(kvh * a.G + g) * a.R + r) * D + 4 * ch) = w;
+        } else {
+            *reinterpret_cast<float4 *>(a.part_o + (slot + row) * D + 4 * ch) = sum;
+            if (ch == 0) a.part_ml[slot + row] = make_float2(m, l);
+        }
+    }
+}
+
+// Merges the parts: one workgroup per (head, row); its threads are D / 4 channel quads times the parts in flight.
+template <int D>
+__global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
+                                                  __bf16 *__restrict__ out, int R, int G, int groups, int rows_per_group,
+                                                  int n_parts, float scale_log2e)
+{
+    constexpr int CH4 = D / 4, LANES = 256 / CH4;   // parts handled side by side
+    __shared__ float4 acc[LANES][CH4];
+    __shared__ float m_wave[4], l_wave[4];
+    const int head = blockIdx.x / R, r = blockIdx.x % R;
+    const int kvh = head / G, s = (head % G) * R + r;
+    const int grp = s / rows_per_group, row = s % rows_per_group;
+    const size_t base = (size_t)(kvh * groups + grp) * n_parts * rows_per_group + row;
+    const int tid = threadIdx.x;
+
+    float m = -INFINITY;
+    for (int p = tid; p < n_parts; p += 256) m = fmaxf(m, part_ml[base + (size_t)p * rows_per_group].x);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    if ((tid & 63) == 0) m_wave[tid >> 6] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(m_wave[0], m_wave[1]), fmaxf(m_wave[2], m_wave[3]));
+
+    const int ch = tid % CH4;
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    float l = 0.f;
+#pragma unroll 8
+    for (int p = tid / CH4; p < n_parts; p += LANES) {
+        const size_t at = base + (size_t)p * rows_per_group;
+        const float2 x = part_ml[at];
+        const float4 y = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
+        const float f = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m) * scale_log2e);
+        l += x.y * f;
+        sum.x += y.x * f; sum.y += y.y * f; sum.z += y.z * f; sum.w += y.w * f;
+    }
+    acc[tid / CH4][ch] = sum;
+    float l_lane = ch == 0 ? l : 0.f;   // every channel lane of a part holds the same l
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l_lane += __shfl_xor(l_lane, off, 64);
+    if ((tid & 63) == 0) l_wave[tid >> 6] = l_lane;
+    __syncthreads();
+    if (tid < CH4) {
+        const float l_tot = (l_wave[0] + l_wave[1]) + (l_wave[2] + l_wave[3]);
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        float4 t = acc[0][tid];
+#pragma unroll
+        for (int i = 1; i < LANES; ++i) {
+            const float4 y = acc[i][tid];
+            t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
+        }
+        bf16x4 w;
+        w[0] = (__bf16)(t.x * inv); w[1] = (__bf16)(t.y * inv); w[2] = (__bf16)(t.z * inv); w[3] = (__bf16)(t.w * inv);
+        *reinterpret_cast<bf16x4 *>(out + (size_t)blockIdx.x * D + 4 * tid) = w;
+    }
+}
+
+RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32_t head_dim, int32_t n_cus)
+{
+    RowsPlan p;
+    const int32_t L = tm->L, R = L - tm->q_begin, n_kv = tm->n_q_heads / gqa_group;
+    if (dtype != BS_BF16 || R > kRowsMaxRows || tm->n_q_heads > kRowsMaxHeads) return p;
+    if (n_kv > 65535 || (int64_t)L * head_dim * 2 >= INT32_MAX) return p;
+    // Up to 32 rows: with 28 / 4 heads this kernel then takes 20 / 26 / 54 / 144 us at 1K / 8K / 39.5K / 140K keys,
+    // the prefill kernel 40 / 200 / 893 / 3125 (other head counts alike).
+    // Every block of keys is read for every head.  That is the work when a text row or a Dense head is there (both
+    // see every earlier key); rows of images under sparse heads only keep the tile lists of the prefill kernel.
+    bool any_dense = false, all_dense = true, any_text = false, any_image = false;
+    for (uint8_t c : tm->head_class) (c == BS_DENSE ? any_dense : all_dense) = c == BS_DENSE;
+    int32_t first = L, last = -1;
+    for (int32_t i = tm->q_begin; i < L; ++i) {
+        int32_t lo, hi, img_lo, img_hi;
+        row_bounds(tm, i, &lo, &hi, &img_lo, &img_hi);
+        (img_hi > img_lo ? any_image : any_text) = true;
+        first = std::min(first, lo);
+        last = std::max(last, hi);
+    }
+    if (!any_text && !any_dense) return p;
+    p.use = true;
+    p.need_bits = any_image && !all_dense;
+    p.k0 = first / kRowsKeys;
+    p.k1 = last / kRowsKeys + 1;
+    const int32_t S = gqa_group * R;
+    p.row_blocks = S > 32 ? 2 : 1;
+    p.groups = (S + 32 * p.row_blocks - 1) / (32 * p.row_blocks);
+    // One workgroup per CU (two at head dimension 64, whose ring takes half the LDS), but no wave without a block.
+    const int32_t wgs = n_cus * (head_dim == 64 ? 2 : 1);
+    const int32_t n_blocks = p.k1 - p.k0;
+    p.parts = std::max(1, std::min(wgs / std::max(1, n_kv * p.groups), (n_blocks + kRowsWaves - 1) / kRowsWaves));
+    if (p.parts > 1) p.workspace = (size_t)n_kv * p.groups * p.parts * p.row_blocks * 32 * (head_dim + 2) * sizeof(float);
+    return p;
+}
+
+template <int D>
+static void launch_rows_dim(const RowsPlan &plan, const RowsArgs &a, int n_kv, hipStream_t st)
+{
+    const dim3 grid((unsigned)plan.parts, (unsigned)n_kv, (unsigned)plan.groups), block(kRowsThreads);
+    if (plan.row_blocks == 1)
+        hipLaunchKernelGGL((attn_rows_bf16<D, 1>), grid, block, RowsTraits<D>::kLds, st, a);
+    else
+        hipLaunchKernelGGL((attn_rows_bf16<D, 2>), grid, block, RowsTraits<D>::kLds, st, a);
+    if (plan.parts > 1)
+        hipLaunchKernelGGL(merge_rows<D>, dim3((unsigned)(n_kv * a.G * a.R)), dim3(256), 0, st, a.part_o, a.part_ml,
+                           static_cast<__bf16 *>(a.out), a.R, a.G, plan.groups, plan.row_blocks * 32, plan.parts, a.scale_log2e);
+}
+
+void launch_rows(const RowsPlan &plan, const void *q, const void *k, const void *v, void *out, const bs_tilemap *tm,
+                 const DeviceMap *d, void *workspace, int32_t gqa_group, int32_t head_dim, float scale, hipStream_t st)
+{
+    const int32_t n_kv = tm->n_q_heads / gqa_group;
+    RowsArgs a{};
+    a.q = q; a.k = k; a.v = v; a.out = out;
+    a.part_o = static_cast<float *>(workspace);
+    a.part_ml = reinterpret_cast<float2 *>(a.part_o + (size_t)n_kv * plan.groups * plan.parts * plan.row_blocks * 32 * head_dim);
+    if (plan.need_bits) { a.text_bits = d->text_bits; a.sink_bits = d->sink_bits; }
+    a.L = tm->L; a.R = tm->L - tm->q_begin; a.G = gqa_group;
+    a.k0 = plan.k0; a.n_blocks = plan.k1 - plan.k0;
+    a.scale_log2e = scale * 1.4426950408889634f;
+    for (int32_t i = 0; i < a.R; ++i)
+        row_bounds(tm, tm->q_begin + i, &a.rows[i].first, &a.rows[i].last, &a.rows[i].img_lo, &a.rows[i].img_hi);
+    for (int32_t h = 0; h < tm->n_q_heads; ++h) a.classes[h >> 4] |= (uint32_t)tm->head_class[h] << (2 * (h & 15));
+    if (head_dim == 128) launch_rows_dim<128>(plan, a, n_kv, st);
+    else launch_rows_dim<64>(plan, a, n_kv, st);
+}
+
+hipError_t rows_device_setup()
+{
+    const void *const k128[] = {reinterpret_cast<const void *>(attn_rows_bf16<128, 1>), reinterpret_cast<const void *>(attn_rows_bf16<128, 2>)};
+    const void *const k64[] = {reinterpret_cast<const void *>(attn_rows_bf16<64, 1>), reinterpret_cast<const void *>(attn_rows_bf16<64, 2>)};
+    for (int i = 0; i < 2; ++i) {
+        hipError_t e = hipFuncSetAttribute(k128[i], hipFuncAttributeMaxDynamicSharedMemorySize, RowsTraits<128>::kLds);
+        if (e == hipSuccess) e = hipFuncSetAttribute(k64[i], hipFuncAttributeMaxDynamicSharedMemorySize, RowsTraits<64>::kLds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace bs

@@ -60,7 +60,7 @@ struct DeviceMap {
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
-    // ---- bf16 workspace: packed K tiles, then packed V^T tiles, of the last call
+    // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
     void *vt_buf = nullptr;
     size_t vt_bytes = 0;
     hipStream_t last_stream = nullptr;    // stream of the most recent upload / launch (compared, never used)
@@ -84,6 +84,8 @@ hipError_t staging_begin(size_t bytes, Staging *out);
 hipError_t staging_commit(const Staging &s, void *dst, size_t bytes, hipStream_t st);
 void staging_abandon(const Staging &s);
 
+// The map's device side without any upload: the device it lives on, its last-use event (once per map).
+int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Upload the prompt part (once per map) / the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
 int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, hipStream_t st);

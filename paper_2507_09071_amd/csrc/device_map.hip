@@ -197,14 +197,41 @@ namespace {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 }
 
-int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
+int ensure_device_map(bs_tilemap *tm, hipStream_t st)
 {
     if (!tm) return BS_EINVAL;
     if (tm->dev) return BS_OK;
-    if (tm->bn > 64) return BS_EUNSUPPORTED;  // the per-tile key bit masks are 64 wide
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
+    DeviceMap *d = new (std::nothrow) DeviceMap();
+    std::shared_ptr<EventHolder> holder;
+    try {
+        holder = std::make_shared<EventHolder>();
+    } catch (const std::bad_alloc &) {
+    }
+    if (!d || !holder) { delete d; return BS_ENOMEM; }
+    e = hipEventCreateWithFlags(&holder->ev, hipEventDisableTiming);
+    if (e != hipSuccess) { delete d; return fail_hip(e, "hipEventCreate"); }
+    d->device = dev;
+    d->last_stream = st;
+    d->last_use = holder;
+    tm->dev = d;
+    tm->dev_free = free_device_map;
+    return BS_OK;
+}
+
+int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
+{
+    if (!tm) return BS_EINVAL;
+    if (tm->dev && tm->dev->blob) return BS_OK;
+    if (tm->bn > 64) return BS_EUNSUPPORTED;  // the per-tile key bit masks are 64 wide
+    int rc = ensure_device_map(tm, st);
+    if (rc != BS_OK) return rc;
+    DeviceMap *d = tm->dev;
+    if ((rc = order_after_last_use(d, st)) != BS_OK) return rc;
+    const int dev = d->device;
+    hipError_t e;
 
     const int64_t M1 = (int64_t)tm->M + 1;
     int64_t total_ranges = 0;
@@ -224,16 +251,9 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     const size_t off_ranges = align256(off_rowptr + (size_t)(4 * M1) * 4);
     const size_t bytes = align256(off_ranges + (size_t)std::max<int64_t>(total_ranges, 1) * 8);
 
-    DeviceMap *d = new (std::nothrow) DeviceMap();
-    std::shared_ptr<EventHolder> holder;
-    try {
-        holder = std::make_shared<EventHolder>();
-    } catch (const std::bad_alloc &) {
-    }
-    if (!d || !holder) { delete d; return BS_ENOMEM; }
     Staging sg;
     e = staging_begin(bytes, &sg);
-    if (e != hipSuccess) { delete d; return fail_hip(e, "pinned staging buffer"); }
+    if (e != hipSuccess) return fail_hip(e, "pinned staging buffer");
     unsigned char *host = static_cast<unsigned char *>(sg.host);
     std::memcpy(host + off_code, tm->code.data(), (size_t)tm->L * 4);
     std::memcpy(host + off_rows, tm->row_order.data(), tm->row_order.size() * 4);
@@ -264,23 +284,17 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     e = pool_acquire(dev, bytes, st, &blob, &blob_cap);
     if (e != hipSuccess) {
         staging_abandon(sg);
-        delete d;
         return fail_hip(e, "hipMalloc(tile map)");
     }
     e = staging_commit(sg, blob, bytes, st);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&holder->ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(holder->ev, st);
+    if (e == hipSuccess) e = hipEventRecord(d->last_use->ev, st);
     if (e != hipSuccess) {
         (void)hipFree(blob);
-        delete d;
         return fail_hip(e, "hipMemcpyAsync(tile map)");
     }
     unsigned char *b = static_cast<unsigned char *>(blob);
-    d->device = dev;
     d->blob = blob;
     d->blob_cap = blob_cap;
-    d->last_stream = st;
-    d->last_use = holder;
     d->code = reinterpret_cast<const uint32_t *>(b + off_code);
     d->row_order = reinterpret_cast<const int32_t *>(b + off_rows);
     d->key_order = reinterpret_cast<const int32_t *>(b + off_keys);
@@ -291,8 +305,6 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     d->span_range = reinterpret_cast<const int2 *>(b + off_spans);
     d->row_ptr = reinterpret_cast<const int32_t *>(b + off_rowptr);
     d->ranges = reinterpret_cast<const int2 *>(b + off_ranges);
-    tm->dev = d;
-    tm->dev_free = free_device_map;
     return BS_OK;
 }
 

@@ -663,6 +663,22 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     return BS_OK;
 }
 
+void bs::row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, int32_t *img_lo, int32_t *img_hi)
+{
+    *first = tm->window > 0 ? std::max(0, i - tm->window + 1) : 0;
+    *last = i;
+    *img_lo = *img_hi = 0;
+    const auto &sp = tm->spans;
+    const auto it = std::upper_bound(sp.begin(), sp.end(), i, [](int32_t t, const bs_span &s) { return t < s.end; });
+    if (it == sp.end() || i < it->start) return;
+    *img_lo = it->start;
+    *img_hi = it->end;
+    if (tm->bidir) {   // the whole own image, also beyond a window
+        *last = it->end - 1;
+        *first = std::min(*first, it->start);
+    }
+}
+
 // Work list of the fp32 kernel: heaviest (head, query tile) first so the tail of the launch is
 // short; ties keep one KV group's heads of a query tile next to each other.
 void bs_plan_work(bs_tilemap *tm)

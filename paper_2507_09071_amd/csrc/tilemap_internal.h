@@ -56,6 +56,9 @@ struct PairPlan {
 
 struct DeviceMap;  // defined by the HIP side
 
+// What the query at position i sees apart from its head's class: keys *first .. *last; its image (empty for text).
+void row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, int32_t *img_lo, int32_t *img_hi);
+
 }  // namespace bs
 
 // Pair up the work items for KV-sharing workgroups (host only; see PairItem).
