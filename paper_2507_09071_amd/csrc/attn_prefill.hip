@@ -467,6 +467,11 @@ struct PairWalker {
     __device__ int state(int grp) const { return grp ? (states & 3) : (states >> 2); }  // 0 skip 1 partial 2 full
 };
 
+// Results of a part of a cut unit: per item the output accumulators in register order (wave, channel block, quad,
+// lane), then reference point and row sum of its 128 rows.
+template <int D>
+constexpr int kCutSlotFloats = 2 * (kBlockM * D + 2 * kBlockM);
+
 // One workgroup = two groups of four waves = one work unit: two (head, query tile) items that
 // read the same KV head and walk one merged key-tile list (heads of a GQA group with the same
 // class, or two neighbouring query tiles of one head), so each K / V^T tile is fetched ONCE for
@@ -486,7 +491,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     const int32_t *__restrict__ map_free_before, const int2 *__restrict__ map_span_free,
     const int4 *__restrict__ pair_items,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
-    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off)
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
 {
     constexpr int ROW = D * 2;            // bytes per K row in LDS
     constexpr int TILE = kBlockN * ROW;   // bytes per K or V^T tile
@@ -506,6 +512,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // ---- state of the work unit in progress (a workgroup takes units from its XCD's queue until
     // ---- the queues are empty; see the unit loop below)
     int head = 0, m = 0, T = 0, n_steps = 1, cls = 0;
+    int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
     int row = 0;                    // the query position of this lane's row
     const char *kph = nullptr, *vth = nullptr;   // packed K / V^T tiles of the unit's KV head
@@ -522,6 +529,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         list_begin = __builtin_amdgcn_readfirstlane(it1.x);
         list_end = __builtin_amdgcn_readfirstlane(it1.y);
         const int hsafe = max(head, 0);
+        slot_id = __builtin_amdgcn_readfirstlane(it1.w >> 16);
         cls = __builtin_amdgcn_readfirstlane((grp ? it1.w >> 8 : it1.w) & 3);   // head classes travel with the unit
         const int kvh = __builtin_amdgcn_readfirstlane(it0.x / a.G);            // both items share it
         // a tile slot without a row behaves like a row past the end of the prompt (computed on a
@@ -856,10 +864,21 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     auto ticket_wait = [&](int &ticket) __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(0)" : "+v"(ticket)::"memory");
     };
+    // Equal shares (few units; planned by the host): workgroup b first walks the parts of its share, then helps with
+    // what the queues hold.  Workgroups go round-robin over the XCDs, so the shares of an XCD are neighbours and
+    // meet in its L2.
+    int share_next = 0, share_end = 0;
+    if (share_off) {
+        const int n = gridDim.x, per = n >> 3, b = blockIdx.x;
+        const int share = (n & 7) == 0 ? (b & 7) * per + (b >> 3) : b;
+        share_next = share_off[share];
+        share_end = share_off[share + 1];
+    }
     if (wave8 == 0) {
-        const int first = claim_from(xcc, __builtin_amdgcn_readfirstlane(take_ticket()));
+        const int first = share_next < share_end ? share_next : claim_from(xcc, __builtin_amdgcn_readfirstlane(take_ticket()));
         if (lane == 0) mailbox[0] = first;
     }
+    ++share_next;
     __syncthreads();
     int unit = __builtin_amdgcn_readfirstlane(mailbox[0]);
 
@@ -906,7 +925,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         if (grp == 0) {
             const int k_claim = max(n_steps - 2, 0);
             for (int k = 0, slot = 0; k < n_steps; ++k) {
-                if (wave8 == 0 && k == k_claim) next_ticket = take_ticket_async();   // consumed after the loop
+                if (wave8 == 0 && k == k_claim && share_next >= share_end) next_ticket = take_ticket_async();   // consumed after the loop
                 phase_x(slot, k > 0, std::false_type{});
                 __builtin_amdgcn_s_barrier();
                 issue_refill();   // under the second group's head reads, before its chain starts
@@ -926,12 +945,13 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // reading the ring.  The ticket has returned by then as well.
         ticket_wait(next_ticket);            // vmcnt(0)
         if (wave8 == 0) {
-            const int nxt = claim_from(xcc, __builtin_amdgcn_readfirstlane(next_ticket));
+            const int nxt = share_next < share_end ? share_next : claim_from(xcc, __builtin_amdgcn_readfirstlane(next_ticket));
             if (lane == 0) mailbox[0] = nxt;
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the mailbox write is in LDS before the barrier
         }
         __builtin_amdgcn_s_barrier();
         const int next_unit = __builtin_amdgcn_readfirstlane(mailbox[0]);
+        ++share_next;
 
         // epilogue: divide by the running sum, round, store.  Empty rows (l = 0) give zeros.  A lane holds
         // four channels of one row at a time (O^T accumulators), which would make every store instruction
@@ -940,7 +960,22 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // of 128-byte row segments.
         const float l_tot = sum_across_halves(l_run);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        {
+        if (slot_id > 0) {
+            // a part of a cut unit: accumulators, reference point and row sum as they are, 1 KB per instruction
+            float *slot = cut_results + (size_t)(slot_id - 1) * kCutSlotFloats<D> + grp * (kCutSlotFloats<D> / 2);
+            if (have_item) {
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        floatx4 w;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) w[r] = o[db][4 * g + r];
+                        *reinterpret_cast<floatx4 *>(slot + (((wave * NDB + db) * 4 + g) * 64 + lane) * 4) = w;
+                    }
+                if (hl == 0) *reinterpret_cast<float2 *>(slot + kBlockM * D + (wave * 32 + col) * 2) = make_float2(m_run, l_tot);
+            }
+        } else {
             constexpr int kStageRow = 128 + 16;                 // 64 channels, then the row's position
             unsigned char *stage = lds + wave8 * (32 * kStageRow);
             if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kStageRow + 128) = row;
@@ -977,6 +1012,70 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         unit = next_unit;
+    }
+}
+
+// Merges the parts of the cut items: one wave per (cut item, 32 rows, 32 channels), so that some hundred cut items
+// keep a thousand waves reading; rows leave through LDS as in the epilogue above.
+template <int D>
+__global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *__restrict__ cut_items,
+                                                      const int32_t *__restrict__ map_row_order,
+                                                      const float *__restrict__ cut_results)
+{
+    constexpr int NDB = D / 32, kStageRow = 64 + 16;   // 32 channels, then the row's position
+    __shared__ __align__(16) unsigned char stage[32 * kStageRow];
+    const int4 it = cut_items[blockIdx.x];
+    const int head = it.x, m = it.y, n_parts = it.w >> 1, item = it.w & 1, wave = blockIdx.y, db = blockIdx.z;
+    const int lane = threadIdx.x, hl = lane >> 5, col = lane & 31;
+    const int R = a.L - a.q_begin;
+    const float *slot = cut_results + (size_t)it.z * kCutSlotFloats<D> + item * (kCutSlotFloats<D> / 2);
+    const float2 *ml = reinterpret_cast<const float2 *>(slot + kBlockM * D) + wave * 32 + col;
+    const floatx4 *src = reinterpret_cast<const floatx4 *>(slot) + (wave * NDB + db) * 256 + lane;
+    constexpr size_t kNext = kCutSlotFloats<D>;
+    if (hl == 0) {
+        const int row_slot = map_row_order[m * kBlockM + wave * 32 + col];
+        *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = row_slot < 0 ? a.L : row_slot;
+    }
+
+    // one pass over the parts, with the reference point moving as in the attention loop
+    float mx = -INFINITY, l = 0.f;
+    floatx4 acc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int p = 0; p < n_parts; ++p) {
+        const float2 x = ml[p * (kNext / 2)];
+        floatx4 y[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) y[g] = src[p * (kNext / 4) + g * 64];
+        const float m_new = fmaxf(mx, x.x);
+        const float old = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mx - m_new) * a.scale_log2e);
+        const float f = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m_new) * a.scale_log2e);
+        mx = m_new;
+        l = fmaf(l, old, x.y * f);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[g][r] = fmaf(acc[g][r], old, y[g][r] * f);
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        bf16x4 w;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = (__bf16)(acc[g][r] * inv);
+        *reinterpret_cast<bf16x4 *>(stage + col * kStageRow + (8 * g + 4 * hl) * 2) = w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int r = 16 * j + (lane >> 2), chunk = lane & 3;
+        const uint4 piece = *reinterpret_cast<const uint4 *>(stage + r * kStageRow + chunk * 16);
+        const int32_t pos = *reinterpret_cast<const int32_t *>(stage + r * kStageRow + 64);
+        if (pos < a.L) {
+            __bf16 *orow = reinterpret_cast<__bf16 *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D;
+            *reinterpret_cast<uint4 *>(orow + 32 * db + chunk * 8) = piece;
+        }
     }
 }
 
@@ -1189,19 +1288,30 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.
 template <int D>
 void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t pack_bytes,
-                 int n_kv_heads, int n_cus, hipStream_t st, void *ev_main_start)
+                 int n_kv_heads, int n_cus, bool shares, hipStream_t st, void *ev_main_start)
 {
     __bf16 *kp = static_cast<__bf16 *>(workspace);
+    float *cut_results = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * pack_bytes);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + pack_bytes);
     const dim3 tgrid((unsigned)tm->N, (unsigned)n_kv_heads, 2);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
-    const dim3 pgrid((unsigned)std::min(d->n_pairs, n_cus)), pblock(bs::kPingPongThreads);
+    const dim3 pgrid((unsigned)(shares ? d->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
                        static_cast<const __bf16 *>(a.v), kp, vt, d->key_order, tm->L, tm->N, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->code, d->text_bits,
-                       d->sink_bits, d->span_range, d->row_order, d->free_before, d->span_free, d->pair_items,
-                       d->pair_ranges, kp, vt, tm->N, d->queue_ctr, d->queue_off);
+                       d->sink_bits, d->span_range, d->row_order, d->free_before, d->span_free,
+                       shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
+                       d->queue_ctr, shares ? d->share_queue_off : d->queue_off, shares ? d->share_off : nullptr, cut_results);
+    if (shares && d->n_cut > 0)
+        hipLaunchKernelGGL(bs::merge_cut_items<D>, dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
+                           d->row_order, cut_results);
+}
+
+// Bytes of the results of cut units (0 without equal shares).
+size_t cut_bytes(const DeviceMap *d, int head_dim)
+{
+    return (size_t)d->n_slots * 4 * (head_dim == 128 ? bs::kCutSlotFloats<128> : bs::kCutSlotFloats<64>);
 }
 
 size_t bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
@@ -1235,9 +1345,10 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
     if (e != hipSuccess) return bs::fail_hip(e, "hipGetDevice");
     if (dev != d->device) return BS_EINVAL;  // the map lives on another device
     void *unused = nullptr;
-    if ((rc = device_setup(dev, &unused, nullptr)) != BS_OK) return rc;
+    int n_cus = 0;
+    if ((rc = device_setup(dev, &unused, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
-    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, st);
+    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, n_cus, st);
     if (rc != BS_OK) return rc;
     e = hipEventRecord(d->last_use->ev, st);
     return e == hipSuccess ? BS_OK : bs::fail_hip(e, "hipEventRecord");
@@ -1270,7 +1381,7 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
     if (!rows.use || rows.need_bits)
         if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
     if (!rows.use) {
-        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, st);
+        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, n_cus, st);
         if (rc != BS_OK) return rc;
     }
 
@@ -1293,9 +1404,10 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
         // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
         const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
-        if ((rc = workspace(2 * pack_bytes)) != BS_OK) return rc;
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, st, ev_main_start);
+        const bool shares = d->n_shares > 0;
+        if ((rc = workspace(2 * pack_bytes + cut_bytes(d, head_dim))) != BS_OK) return rc;
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
     } else {
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         const dim3 grid((unsigned)d->n_work), block(bs::kThreads);
@@ -1342,11 +1454,13 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
+    // units are cut only if their partial results fit behind the packed tiles
+    const bool shares = d->n_shares > 0 && 2 * pack_bytes + cut_bytes(d, head_dim) <= kStaticScratchBytes;
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, st, nullptr);
+    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

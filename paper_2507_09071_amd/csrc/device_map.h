@@ -59,6 +59,12 @@ struct DeviceMap {
     const int2 *pair_ranges = nullptr;
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])
+    const int4 *share_items = nullptr;    // equal shares instead of the queues (null: not worth it): the parts, ...
+    const int2 *share_ranges = nullptr;
+    const int32_t *share_off = nullptr;   // ... [n_shares + 1] the parts of each workgroup, ...
+    const int32_t *share_queue_off = nullptr;   // ... [9] the parts for whoever is done first, ...
+    const int4 *cut_items = nullptr;      // ... [n_cut] the items whose results come in parts
+    int32_t n_shares = 0, n_cut = 0, n_slots = 0;
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
     void *vt_buf = nullptr;
@@ -88,7 +94,7 @@ void staging_abandon(const Staging &s);
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Upload the prompt part (once per map) / the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, hipStream_t st);
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cus, hipStream_t st);
 // Order work queued on `st` after the map's previous use if that was on another stream.
 int order_after_last_use(DeviceMap *d, hipStream_t st);
 

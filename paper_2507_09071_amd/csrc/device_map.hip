@@ -323,14 +323,14 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, hipStream_t st)
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cus, hipStream_t st)
 {
     DeviceMap *d = tm->dev;
     if (!d) return BS_EINVAL;
     if (kind == kBindWorkList) gqa_group = 0;   // the work list does not depend on it
     if (d->bind_kind == kind && d->bind_G == gqa_group && d->bind_epoch == tm->class_epoch) return BS_OK;
     try {
-        if (kind == kBindPairPlan) bs_plan_pairs(tm, gqa_group);
+        if (kind == kBindPairPlan) bs_plan_shares(tm, gqa_group, n_cus);   // and the pair plan it is made from
         else bs_plan_work(tm);
     } catch (const std::bad_alloc &) {
         return BS_ENOMEM;
@@ -344,12 +344,27 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, hipStream_t 
     const size_t off_b = align256(off_a + a_bytes);        // ranges of the work units
     const size_t b_bytes = kind == kBindPairPlan ? std::max<size_t>(plan.ranges.size(), 1) * sizeof(PairRange) : 0;
     const size_t off_q = align256(off_b + b_bytes);        // queue offsets [9], then queue counters [8]
-    const size_t bytes = align256(off_q + 256);
+    const SharePlan &shares = tm->shares;
+    const bool shared = kind == kBindPairPlan && !shares.share_off.empty();
+    const size_t off_si = align256(off_q + 256);           // equal shares: parts, their ranges, share offsets, cut items
+    const size_t off_sr = align256(off_si + (shared ? shares.parts.size() * sizeof(PairItem) : 0));
+    const size_t off_so = align256(off_sr + (shared ? shares.ranges.size() * sizeof(PairRange) : 0));
+    const size_t off_sq = align256(off_so + (shared ? shares.share_off.size() * 4 : 0));
+    const size_t off_sc = align256(off_sq + (shared ? sizeof shares.queue_off : 0));
+    const size_t bytes = align256(off_sc + (shared ? shares.cut.size() * sizeof(CutItem) : 0));
 
     Staging sg;
     hipError_t e = staging_begin(bytes, &sg);
     if (e != hipSuccess) return fail_hip(e, "pinned staging buffer");
     unsigned char *host = static_cast<unsigned char *>(sg.host);
+    if (shared) {
+        static_assert(sizeof(CutItem) == sizeof(int4), "copied as it is");
+        std::memcpy(host + off_si, shares.parts.data(), shares.parts.size() * sizeof(PairItem));
+        std::memcpy(host + off_sr, shares.ranges.data(), shares.ranges.size() * sizeof(PairRange));
+        std::memcpy(host + off_so, shares.share_off.data(), shares.share_off.size() * 4);
+        std::memcpy(host + off_sq, shares.queue_off, sizeof shares.queue_off);
+        if (!shares.cut.empty()) std::memcpy(host + off_sc, shares.cut.data(), shares.cut.size() * sizeof(CutItem));
+    }
     std::memcpy(host + off_class, tm->head_class.data(), n_heads);
     if (kind == kBindPairPlan) {
         static_assert(sizeof(PairItem) == 2 * sizeof(int4) && sizeof(PairRange) == sizeof(int2), "copied as they are");
@@ -393,6 +408,14 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, hipStream_t 
     d->pair_ranges = kind == kBindPairPlan ? reinterpret_cast<const int2 *>(b + off_b) : nullptr;
     d->n_pairs = kind == kBindPairPlan ? (int32_t)plan.items.size() : 0;
     d->queue_off = kind == kBindPairPlan ? reinterpret_cast<const int32_t *>(b + off_q) : nullptr;
+    d->share_items = shared ? reinterpret_cast<const int4 *>(b + off_si) : nullptr;
+    d->share_ranges = shared ? reinterpret_cast<const int2 *>(b + off_sr) : nullptr;
+    d->share_off = shared ? reinterpret_cast<const int32_t *>(b + off_so) : nullptr;
+    d->share_queue_off = shared ? reinterpret_cast<const int32_t *>(b + off_sq) : nullptr;
+    d->cut_items = shared ? reinterpret_cast<const int4 *>(b + off_sc) : nullptr;
+    d->n_shares = shared ? (int32_t)shares.share_off.size() - 1 : 0;
+    d->n_cut = shared ? (int32_t)shares.cut.size() : 0;
+    d->n_slots = shared ? shares.n_slots : 0;
     d->queue_ctr = kind == kBindPairPlan ? reinterpret_cast<int32_t *>(b + off_q + 64) : nullptr;
     return BS_OK;
 }

@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <functional>
 #include <new>
 
 #include "tilemap_internal.h"
@@ -864,7 +865,8 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     // grows with the square of the head count (measured: 16 KV heads at 300K tokens gain 2-3 % from 512-
     // 1024 tiles, 8 KV heads at 140K 0.3-1 % from 256-1024, 4 KV heads lose 0.2-0.5 % with anything above
     // 32), but never so wide that the heaviest-first order loses its grip on the tail (a workgroup's
-    // share of the steps / 64).
+    // share of the steps / 64; below 32 tiles on prompts of less than some 20K tokens, whose K and V the caches
+    // hold anyway).
     constexpr int32_t kXcds = 8;
     int32_t cost_bucket = 32;
     {
@@ -873,7 +875,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         const int64_t n_kv = std::max<int64_t>(1, (int64_t)tm->head_class.size() / std::max(G, 1));
         const int64_t for_locality = 32 * std::max<int64_t>(1, n_kv / 4) * std::max<int64_t>(1, n_kv / 4);
         const int64_t for_balance = total / 256 / 64;                     // 256 workgroups
-        cost_bucket = (int32_t)std::max<int64_t>(32, std::min(for_locality, for_balance) / 32 * 32);
+        cost_bucket = (int32_t)std::max<int64_t>(1, for_balance < 32 ? for_balance : std::min(for_locality, for_balance) / 32 * 32);
     }
     const int32_t kXcdBlock = std::min<int64_t>(16, std::max<int64_t>(8, (int64_t)plan.items.size() / 2048));
     std::stable_sort(plan.items.begin(), plan.items.end(), [G, cost_bucket](const bs::PairItem &a, const bs::PairItem &b) {
@@ -898,6 +900,145 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         it.classes = tm->head_class[it.head_a] | (it.head_b >= 0 ? tm->head_class[it.head_b] << 8 : 0);
     plan.gqa_group = G;
     plan.epoch = tm->class_epoch;
+}
+
+// Equal shares.  The queues balance a launch as long as there are many units per workgroup and none is long; with
+// few units -- a short prompt, a chunk of a few hundred rows behind a long cache -- most of the chip waits for the
+// longest one.  Here every workgroup gets units up to an equal share of the steps: first whole ones, longest first
+// (neighbours in that order walk the same tiles side by side and share them in L2), then the room that is left is
+// filled with parts of the units that found no place, cut along their key tiles.  A cut unit leaves partial results
+// (unnormalised output, reference point, row sum) that a second kernel merges.  The time per step differs by up to
+// 15 % between workgroups (which tiles they find in L2, partial tiles), so long shares keep back a part of the steps
+// as short pieces that go to the queues, for whoever is done first.
+// Costs are in key-tile steps: a unit or part costs its steps and kUnitCost around them (prologue and epilogue,
+// 8 us against 1.3-1.7 us per step by time stamps), the merge kMergeCost for the launch.
+void bs_plan_shares(bs_tilemap *tm, int32_t G, int32_t n_wgs)
+{
+    bs::SharePlan &sp = tm->shares;
+    if (sp.gqa_group == G && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
+    bs_plan_pairs(tm, G);
+    const bs::PairPlan &plan = tm->pairs;
+    sp.parts.clear(); sp.ranges.clear(); sp.share_off.clear(); sp.cut.clear();
+    sp.n_slots = 0;
+    std::fill(sp.queue_off, sp.queue_off + 9, 0);
+    sp.gqa_group = G; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
+    constexpr int64_t kUnitCost = 6, kMergeCost = 6, kMinPart = 4, kMaxUnitsPerWg = 3;
+    const int32_t n_units = (int32_t)std::min<size_t>(plan.items.size(), INT32_MAX);
+    if (n_units > kMaxUnitsPerWg * n_wgs || n_wgs > 4096) return;
+    int64_t total = 0, longest = 0;
+    for (const bs::PairItem &it : plan.items) {
+        total += it.n_tiles + kUnitCost;
+        longest = std::max<int64_t>(longest, it.n_tiles + kUnitCost);
+    }
+    // a fresh share always takes a part: it is longer than two of the shortest
+    const int64_t least = std::max<int64_t>((total + n_wgs - 1) / n_wgs, 2 * kMinPart + kUnitCost);
+    if (n_units <= n_wgs && longest <= least + kMergeCost) return;
+
+    // longest first, in buckets of an eighth of a share inside which the units of a KV head stay together
+    const int64_t bucket = std::max<int64_t>(1, least / 8);
+    std::vector<std::pair<int64_t, int32_t>> order(n_units);
+    for (int32_t u = 0; u < n_units; ++u)
+        order[u] = {(-(plan.items[u].n_tiles / bucket) << 32) + plan.items[u].head_a / G, u};
+    std::sort(order.begin(), order.end());
+    using Load = std::pair<int64_t, int32_t>;   // steps given to a workgroup, the workgroup
+    // what the queues need: heaviest first onto the workgroup that is free first
+    int64_t queued = longest;
+    std::vector<Load> heap(n_wgs);
+    auto deal = [&](auto &&accept) {   // units in order to the least loaded workgroup; the loads end up in `heap`
+        for (int32_t w = 0; w < n_wgs; ++w) heap[w] = {0, w};
+        for (const auto &o : order) {
+            const int64_t x = plan.items[o.second].n_tiles + kUnitCost;
+            std::pop_heap(heap.begin(), heap.end(), std::greater<Load>());
+            if (accept(o.second, heap.back(), x)) heap.back().first += x;
+            std::push_heap(heap.begin(), heap.end(), std::greater<Load>());
+        }
+    };
+    if (n_units > n_wgs) {
+        deal([](int32_t, const Load &, int64_t) { return true; });
+        for (const Load &l : heap) queued = std::max(queued, l.first);
+    }
+
+    struct Piece { int32_t wg, unit, begin, steps; };
+    std::vector<Piece> pieces;
+    std::vector<int32_t> homeless;
+    std::vector<int64_t> load(n_wgs);
+    constexpr int64_t kQueuedFrom = 600;   // shares from here on hand a sixth of the steps to the queues ...
+    auto fill = [&](int64_t share) {       // false: units are left over
+        const int64_t fixed = share >= kQueuedFrom ? share - share / 6 : share;
+        const int64_t queue_piece = share / 24;   // ... in pieces of four to that sixth
+        pieces.clear();
+        homeless.clear();
+        deal([&](int32_t u, const Load &l, int64_t x) {
+            if (l.first + x > fixed) { homeless.push_back(u); return false; }
+            pieces.push_back({l.second, u, 0, plan.items[u].n_tiles});
+            return true;
+        });
+        for (const Load &l : heap) load[l.second] = l.first;
+        int32_t w = 0;
+        for (int32_t u : homeless) {
+            int32_t done = 0;
+            for (int32_t left = plan.items[u].n_tiles; left > 0;) {
+                if (w == n_wgs && fixed == share) return false;
+                const int64_t room = w == n_wgs ? queue_piece : fixed - load[w] - kUnitCost;
+                // the rest of the unit, or a part as long as the room; neither it nor the rest too short
+                const int64_t take = left <= room ? left : std::min<int64_t>(room, left - kMinPart);
+                if (take >= std::min<int64_t>(left, kMinPart)) {
+                    pieces.push_back({w, u, done, (int32_t)take});
+                    if (w < n_wgs) load[w] += take + kUnitCost;
+                    done += (int32_t)take;
+                    left -= (int32_t)take;
+                }
+                if (left > 0 && w < n_wgs) ++w;
+            }
+        }
+        return true;
+    };
+    int64_t share = least + kUnitCost;   // a cut costs another unit's worth
+    while (share + kMergeCost < queued && !fill(share)) share += std::max<int64_t>(1, share / 32);
+    if (share + kMergeCost >= queued) return;   // no gain over the queues
+    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &b) { return a.wg < b.wg; });
+    std::vector<int32_t> off(n_wgs + 2, 0);   // (the queued pieces count as those of workgroup n_wgs)
+    for (const Piece &p : pieces) ++off[p.wg + 1];
+    for (int32_t w = 0; w <= n_wgs; ++w) off[w + 1] += off[w];
+    off.pop_back();
+    for (int q = 0; q <= 8; ++q) sp.queue_off[q] = (int32_t)(off[n_wgs] + (pieces.size() - off[n_wgs]) * q / 8);
+
+    std::vector<int32_t> n_parts(n_units, 0), made(n_units, 0), slot0(n_units, -1);
+    for (const Piece &p : pieces) ++n_parts[p.unit];
+    for (const Piece &p : pieces) {
+        const bs::PairItem &it = plan.items[p.unit];
+        bs::PairItem part = it;
+        int32_t slot = 0;
+        if (n_parts[p.unit] > 1) {
+            if (slot0[p.unit] < 0) {
+                slot0[p.unit] = sp.n_slots;
+                sp.n_slots += n_parts[p.unit];
+                sp.cut.push_back({it.head_a, it.tile_a, slot0[p.unit], n_parts[p.unit] << 1});
+                if (it.head_b >= 0) sp.cut.push_back({it.head_b, it.tile_b, slot0[p.unit], n_parts[p.unit] << 1 | 1});
+            }
+            slot = slot0[p.unit] + made[p.unit]++ + 1;
+        }
+        part.list_begin = (int32_t)sp.ranges.size();
+        part.n_tiles = p.steps;
+        int32_t skip = p.begin, left = p.steps;
+        for (int32_t r = it.list_begin; r < it.list_end && left > 0; ++r) {
+            const bs::PairRange &rg = plan.ranges[r];
+            const int32_t len = (rg.end_states >> 4) - rg.begin;
+            if (skip >= len) { skip -= len; continue; }
+            const int32_t b = rg.begin + skip, e = std::min(rg.end_states >> 4, b + left);
+            sp.ranges.push_back({b, (e << 4) | (rg.end_states & 15)});
+            left -= e - b;
+            skip = 0;
+        }
+        part.list_end = (int32_t)sp.ranges.size();
+        part.classes = it.classes | slot << 16;
+        sp.parts.push_back(part);
+    }
+    sp.share_off = off;
+    if (sp.n_slots >= 32767) {   // the slot has 15 bits next to the classes
+        sp.parts.clear(); sp.ranges.clear(); sp.share_off.clear(); sp.cut.clear();
+        sp.n_slots = 0;
+    }
 }
 
 extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *n_units, int64_t *unit_tiles,

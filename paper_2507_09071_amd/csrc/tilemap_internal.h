@@ -54,6 +54,22 @@ struct PairPlan {
     int32_t queue_off[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // queue x = items[queue_off[x] .. queue_off[x + 1])
 };
 
+// One item of a unit that was cut: its partial results lie in slots first_slot .. first_slot + n_parts - 1.
+struct CutItem { int32_t head, tile, first_slot, n_parts_item; };   // n_parts_item: parts << 1 | item of the unit (0 A, 1 B)
+
+// The units of a PairPlan in equal shares, one per workgroup, with units cut along their key tiles where a share
+// ends (see bs_plan_shares).
+struct SharePlan {
+    int32_t gqa_group = 0, n_wgs = 0;     // made for these ...
+    uint64_t epoch = 0;                   // ... and for this class vector
+    std::vector<PairItem> parts;          // PairItem::classes carries slot + 1 in its upper half for a part of a cut unit
+    std::vector<PairRange> ranges;        // the parts' lists
+    std::vector<int32_t> share_off;       // workgroup w takes parts[share_off[w] .. share_off[w + 1]); empty: not worth it
+    int32_t queue_off[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // parts for whoever is done, in eight queues behind the shares
+    std::vector<CutItem> cut;
+    int32_t n_slots = 0;
+};
+
 struct DeviceMap;  // defined by the HIP side
 
 // What the query at position i sees apart from its head's class: keys *first .. *last; its image (empty for text).
@@ -63,6 +79,8 @@ void row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, 
 
 // Pair up the work items for KV-sharing workgroups (host only; see PairItem).
 void bs_plan_pairs(bs_tilemap *tm, int32_t gqa_group);
+// Cut the units of the pair plan into equal shares for n_wgs workgroups, if that pays (host only; see SharePlan).
+void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs);
 // The plain work list of the fp32 kernel: every (head, query tile), heaviest first (host only).
 void bs_plan_work(bs_tilemap *tm);
 
@@ -91,6 +109,7 @@ struct bs_tilemap {
     std::vector<bs::WorkItem> work;        // n_q_heads * M items, heaviest first; built on first use (work_epoch)
     uint64_t work_epoch = 0;
     bs::PairPlan pairs;                    // built on first use for a given gqa_group and class vector
+    bs::SharePlan shares;
     bs::DeviceMap *dev = nullptr;          // created lazily by bs_tilemap_upload
     void (*dev_free)(bs::DeviceMap *) = nullptr;
 };
