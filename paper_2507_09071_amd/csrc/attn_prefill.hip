@@ -37,150 +37,13 @@
 #include <vector>
 
 #include "attn_common.h"
+#include "attn_f32.h"
 #include "attn_rows.h"
+#include "cut_merge.h"
 #include "device_map.h"
 #include "tilemap_internal.h"
 
 namespace bs {
-
-// Read-only tile-map arrays; passed as separate __restrict__ kernel parameters so that loads
-// with wave-uniform addresses go through the scalar cache (they then never wait on the vector
-// memory counter that tracks the in-flight LDS-direct loads).
-struct KernelArgs {
-    const void *q, *k, *v;
-    void *out;
-    int32_t L, M, G;
-    float scale_log2e;  // scale * log2(e): softmax runs in the exp2 domain
-    int32_t n_prompt_tiles;   // key tiles that are the prompt in position order (compact tiles follow)
-    int32_t packed, intra_compact;
-    int32_t bidir;            // tokens of one image also see the later tokens of that image
-    int32_t window;           // > 0: keys more than window - 1 positions before the query are masked
-    int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
-};
-#define BS_MAP_PARAMS                                                                              \
-    const uint32_t *__restrict__ map_code, const uint64_t *__restrict__ map_text_bits,             \
-        const uint64_t *__restrict__ map_sink_bits, const int2 *__restrict__ map_span_range,       \
-        const int32_t *__restrict__ map_row_ptr, const int2 *__restrict__ map_ranges,              \
-        const int2 *__restrict__ map_work, const uint8_t *__restrict__ map_head_class,             \
-        const int32_t *__restrict__ map_row_order, const int32_t *__restrict__ map_key_order,      \
-        const int32_t *__restrict__ map_free_before, const int2 *__restrict__ map_span_free
-#define BS_MAP_ARGS(d) (d)->code, (d)->text_bits, (d)->sink_bits, (d)->span_range, (d)->row_ptr, (d)->ranges, (d)->work, (d)->head_class, (d)->row_order, (d)->key_order, (d)->free_before, (d)->span_free
-
-constexpr int kThreads = 256;
-
-// Walks the key tiles of one (class, query tile): ranges of [begin, end) with a FULL flag.
-struct TileWalker {
-    const int2 *__restrict__ rg;
-    int p, p_end, n, n_end;
-    bool full;
-    __device__ void load()
-    {
-        if (p < p_end) {
-            // wave-uniform by construction; say so, so the loads go through the scalar cache
-            const int2 r = rg[__builtin_amdgcn_readfirstlane(p)];
-            n = __builtin_amdgcn_readfirstlane(r.x);
-            n_end = __builtin_amdgcn_readfirstlane(r.y) >> 1;
-            full = __builtin_amdgcn_readfirstlane(r.y) & 1;
-        }
-    }
-    __device__ void init(const int2 *__restrict__ ranges, int begin, int end)
-    {
-        rg = ranges;
-        n = 0; n_end = 0; full = false;
-        p = __builtin_amdgcn_readfirstlane(begin);
-        p_end = __builtin_amdgcn_readfirstlane(end);
-        load();
-    }
-    __device__ bool valid() const { return p < p_end; }
-    __device__ void next()
-    {
-        if (++n == n_end) { ++p; load(); }
-    }
-};
-
-// What the lane's query may see (paper Sec. 3.2), in a form that is cheap to apply per tile.
-// With packed keys (see the tile-map builder) an image query of a sparse class reads the free
-// keys -- text and sink keys -- from compact tiles and only own-image keys from the prompt's
-// tiles, so that every allowed pair is counted once.
-struct QueryView {
-    int32_t row;       // last visible position: the query's own (causal), the end of its image (bidirectional images)
-    int32_t first;     // first visible position: 0, or the start of the query's sliding window
-    int32_t own_lo;    // own image [own_lo, own_hi) if the class attends inside images, else empty
-    int32_t own_hi;
-    int32_t free_bound;  // packed: free keys at positions <= i (the visible compact slots are [0, free_bound))
-    int32_t cfree_lo;    // packed, Intra-Image+Sink: compact slots of the free keys inside the own image
-    int32_t cfree_hi;
-    bool sees_all;     // text query or Dense head: every earlier key
-    bool own_only;     // packed: in the prompt's tiles only own-image keys count for this query
-    __device__ void init(const uint32_t *__restrict__ code, const int2 *__restrict__ span_range,
-                         const int32_t *__restrict__ free_before, const int2 *__restrict__ span_free,
-                         int L, int cls, int32_t i, bool packed, bool intra_compact, bool bidir, int32_t window)
-    {
-        row = i;
-        first = window > 0 ? max(0, i - window + 1) : 0;
-        const uint32_t qcode = i < L ? code[i] : kCodeText;
-        sees_all = (qcode & kCodeText) || cls == BS_DENSE;
-        own_lo = own_hi = 0;
-        free_bound = cfree_lo = cfree_hi = 0;
-        own_only = false;
-        if (!(qcode & kCodeText) && (bidir || (cls & 2))) {
-            const int2 sp = span_range[qcode & kCodeImgMask];
-            // an image query that sees its whole image behaves, for every class, like the
-            // image's last query under the causal mask; its image stays visible beyond a window
-            if (bidir) { row = sp.y - 1; first = min(first, sp.x); }
-            if (!sees_all && (cls & 2)) { own_lo = sp.x; own_hi = sp.y; }
-        }
-        if (packed && !sees_all && (cls != BS_INTRA || intra_compact)) {
-            free_bound = free_before[row + 1];
-            own_only = true;
-            if (cls == BS_INTRA_SINK) {
-                const int2 cr = span_free[qcode & kCodeImgMask];
-                cfree_lo = cr.x; cfree_hi = cr.y;
-            }
-        }
-    }
-};
-
-__device__ inline uint64_t bits_below(int x)  // bits [0, x), x in [0, 64]
-{
-    return x >= 64 ? ~0ull : ((1ull << x) - 1ull);
-}
-__device__ inline uint64_t bits_between(int lo, int hi)  // bits [lo, hi) clipped to [0, 64)
-{
-    return bits_below(min(max(hi, 0), 64)) & ~bits_below(min(max(lo, 0), 64));
-}
-
-// Bit b set <=> the key in slot b of key tile n is allowed for this lane's query.  tbits / sbits:
-// text keys and sink keys of the tile; n_prompt: number of key tiles that are the prompt in
-// position order (the tiles after them are compact tiles of free keys).
-__device__ inline uint64_t allowed_keys(const QueryView &qv, int cls, uint64_t tbits, uint64_t sbits, int n, int n_prompt)
-{
-    if (n < n_prompt) {
-        const int n0 = n * kBlockN;
-        const uint64_t base = qv.sees_all ? ~0ull : (qv.own_only ? 0ull : (tbits | ((cls & 1) ? sbits : 0ull)));
-        const uint64_t own = bits_between(qv.own_lo - n0, qv.own_hi - n0);
-        return (base | own) & bits_between(qv.first - n0, qv.row - n0 + 1);   // keys first .. row
-    }
-    // compact tile: slots are free keys in position order, visible up to the row's bound
-    const int s0 = (n - n_prompt) * kBlockN;
-    const uint64_t base = qv.sees_all ? 0ull : ((cls & 1) ? ~0ull : tbits);   // Intra-Image: text keys only
-    const uint64_t excl = bits_between(qv.cfree_lo - s0, qv.cfree_hi - s0);   // counted with the own image
-    return base & ~excl & bits_below(min(max(qv.free_bound - s0, 0), 64));
-}
-
-// Score block layout (two 32x32 MFMA C tiles): lane (hl = lane/32, col = lane%32) holds, for
-// query col, keys 32*kb + 8*(v/4) + 4*hl + v%4, v = 0..15.
-__device__ inline void apply_mask(floatx16 (&s)[2], uint64_t allowed, int hl)
-{
-    const uint32_t w[2] = {(uint32_t)allowed >> (4 * hl), (uint32_t)(allowed >> 32) >> (4 * hl)};
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t bit = 1u << (8 * (v / 4) + (v % 4));
-            s[kb][v] = (w[kb] & bit) ? s[kb][v] : -INFINITY;
-        }
-}
 
 // The same masking in two instructions per score, kept together so that the scheduler cannot
 // hoist the 32 bit tests in front of the 32 selects (32 registers of pressure in a kernel that
@@ -204,35 +67,6 @@ __device__ inline void apply_mask_tight(const floatx16 (&s)[2], floatx16 (&ms)[2
                 : "v"(w[kb]), "n"(8 * (v / 4) + (v % 4)), "v"(s[kb][v]), "v"(ninf));
             ms[kb][v] = r;
         }
-}
-
-// Online-softmax update (running max m, running sum l, rescale factor alpha; App. kernel
-// Alg. 4) in the exp2 domain: p = exp2(s*c - m*c).  l is the lane's partial sum (its 32 keys);
-// the halves are added once, in the epilogue.  MAY_BE_EMPTY guards rows with no allowed key
-// so far (m = -inf), which only PARTIAL tiles can produce.
-template <bool MAY_BE_EMPTY>
-__device__ inline void softmax_block(floatx16 (&s)[2], float &m_run, float &l_run, float &alpha, float c)
-{
-    float mx = fmaxf(s[0][0], s[0][1]);
-#pragma unroll
-    for (int v = 2; v < 16; v += 2) mx = fmaxf(fmaxf(mx, s[0][v]), s[0][v + 1]);
-#pragma unroll
-    for (int v = 0; v < 16; v += 2) mx = fmaxf(fmaxf(mx, s[1][v]), s[1][v + 1]);
-    mx = max_across_halves(mx);
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = (MAY_BE_EMPTY && m_new == -INFINITY) ? 0.f : m_new;
-    const float mc = m_use * c;
-    alpha = __builtin_amdgcn_exp2f(fmaf(m_run, c, -mc));  // m_run = -inf -> 0
-    float sum0 = 0.f, sum1 = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[0][v], c, -mc));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[1][v], c, -mc));
-        s[0][v] = p0; s[1][v] = p1;
-        sum0 += p0; sum1 += p1;
-    }
-    l_run = fmaf(l_run, alpha, sum0 + sum1);
-    m_run = m_new;
 }
 
 // Same update as softmax_block, but the scores are only read and the probabilities go straight
@@ -437,40 +271,6 @@ struct NoBatch { static constexpr int kind = 0, idx = 0; static constexpr bool f
 constexpr int kRing = 4;   // K slots = V^T slots of the LDS ring
 template <int D>
 constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + 64; }   // ring, then the unit mailbox
-
-// Walks the merged key-tile list of a work unit: runs of [begin, end) with a state per item.
-struct PairWalker {
-    const int2 *__restrict__ rg;
-    int p, p_end, n, n_end, states;
-    __device__ void load()
-    {
-        if (p < p_end) {
-            const int2 r = rg[__builtin_amdgcn_readfirstlane(p)];
-            n = __builtin_amdgcn_readfirstlane(r.x);
-            n_end = __builtin_amdgcn_readfirstlane(r.y) >> 4;
-            states = __builtin_amdgcn_readfirstlane(r.y) & 15;
-        }
-    }
-    __device__ void init(const int2 *__restrict__ ranges, int begin, int end)
-    {
-        rg = ranges;
-        n = 0; n_end = 0; states = 0;
-        p = __builtin_amdgcn_readfirstlane(begin);
-        p_end = __builtin_amdgcn_readfirstlane(end);
-        load();
-    }
-    __device__ bool valid() const { return p < p_end; }
-    __device__ void next()
-    {
-        if (++n == n_end) { ++p; load(); }
-    }
-    __device__ int state(int grp) const { return grp ? (states & 3) : (states >> 2); }  // 0 skip 1 partial 2 full
-};
-
-// Results of a part of a cut unit: per item the output accumulators in register order (wave, channel block, quad,
-// lane), then reference point and row sum of its 128 rows.
-template <int D>
-constexpr int kCutSlotFloats = 2 * (kBlockM * D + 2 * kBlockM);
 
 // One workgroup = two groups of four waves = one work unit: two (head, query tile) items that
 // read the same KV head and walk one merged key-tile list (heads of a GQA group with the same
@@ -961,20 +761,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         const float l_tot = sum_across_halves(l_run);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         if (slot_id > 0) {
-            // a part of a cut unit: accumulators, reference point and row sum as they are, 1 KB per instruction
-            float *slot = cut_results + (size_t)(slot_id - 1) * kCutSlotFloats<D> + grp * (kCutSlotFloats<D> / 2);
-            if (have_item) {
-#pragma unroll
-                for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        floatx4 w;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) w[r] = o[db][4 * g + r];
-                        *reinterpret_cast<floatx4 *>(slot + (((wave * NDB + db) * 4 + g) * 64 + lane) * 4) = w;
-                    }
-                if (hl == 0) *reinterpret_cast<float2 *>(slot + kBlockM * D + (wave * 32 + col) * 2) = make_float2(m_run, l_tot);
-            }
+            // a part of a cut unit: accumulators, reference point and row sum as they are
+            if (have_item) store_cut_item<D>(cut_results + ((size_t)(slot_id - 1) * 2 + grp) * kCutItemFloats<D>, o, m_run, l_tot, wave, lane);
         } else {
             constexpr int kStageRow = 128 + 16;                 // 64 channels, then the row's position
             unsigned char *stage = lds + wave8 * (32 * kStageRow);
@@ -1015,188 +803,6 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     }
 }
 
-// Merges the parts of the cut items: one wave per (cut item, 32 rows, 32 channels), so that some hundred cut items
-// keep a thousand waves reading; rows leave through LDS as in the epilogue above.
-template <int D>
-__global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *__restrict__ cut_items,
-                                                      const int32_t *__restrict__ map_row_order,
-                                                      const float *__restrict__ cut_results)
-{
-    constexpr int NDB = D / 32, kStageRow = 64 + 16;   // 32 channels, then the row's position
-    __shared__ __align__(16) unsigned char stage[32 * kStageRow];
-    const int4 it = cut_items[blockIdx.x];
-    const int head = it.x, m = it.y, n_parts = it.w >> 1, item = it.w & 1, wave = blockIdx.y, db = blockIdx.z;
-    const int lane = threadIdx.x, hl = lane >> 5, col = lane & 31;
-    const int R = a.L - a.q_begin;
-    const float *slot = cut_results + (size_t)it.z * kCutSlotFloats<D> + item * (kCutSlotFloats<D> / 2);
-    const float2 *ml = reinterpret_cast<const float2 *>(slot + kBlockM * D) + wave * 32 + col;
-    const floatx4 *src = reinterpret_cast<const floatx4 *>(slot) + (wave * NDB + db) * 256 + lane;
-    constexpr size_t kNext = kCutSlotFloats<D>;
-    if (hl == 0) {
-        const int row_slot = map_row_order[m * kBlockM + wave * 32 + col];
-        *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = row_slot < 0 ? a.L : row_slot;
-    }
-
-    // one pass over the parts, with the reference point moving as in the attention loop
-    float mx = -INFINITY, l = 0.f;
-    floatx4 acc[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int p = 0; p < n_parts; ++p) {
-        const float2 x = ml[p * (kNext / 2)];
-        floatx4 y[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) y[g] = src[p * (kNext / 4) + g * 64];
-        const float m_new = fmaxf(mx, x.x);
-        const float old = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mx - m_new) * a.scale_log2e);
-        const float f = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m_new) * a.scale_log2e);
-        mx = m_new;
-        l = fmaf(l, old, x.y * f);
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[g][r] = fmaf(acc[g][r], old, y[g][r] * f);
-    }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        bf16x4 w;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = (__bf16)(acc[g][r] * inv);
-        *reinterpret_cast<bf16x4 *>(stage + col * kStageRow + (8 * g + 4 * hl) * 2) = w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int r = 16 * j + (lane >> 2), chunk = lane & 3;
-        const uint4 piece = *reinterpret_cast<const uint4 *>(stage + r * kStageRow + chunk * 16);
-        const int32_t pos = *reinterpret_cast<const int32_t *>(stage + r * kStageRow + 64);
-        if (pos < a.L) {
-            __bf16 *orow = reinterpret_cast<__bf16 *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D;
-            *reinterpret_cast<uint4 *>(orow + 32 * db + chunk * 8) = piece;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------ fp32
-// Same structure with fp32 MFMA (32x32x2) end to end; P stays fp32.  Parity path for fp32
-// inputs, not tuned: K / V tiles are gathered from the caller's arrays through key_order (no
-// pre-pass).  Dynamic LDS: K[64][D+1] floats, V[64][D+8] floats.
-
-template <int D>
-__global__ __launch_bounds__(kThreads, 1) void attn_prefill_f32(KernelArgs a, BS_MAP_PARAMS)
-{
-    constexpr int KS = D + 1, VS = D + 8;
-    extern __shared__ __align__(16) unsigned char smem[];
-    float *lds_k = reinterpret_cast<float *>(smem);
-    float *lds_v = lds_k + kBlockN * KS;
-
-    const int2 item = map_work[blockIdx.x];
-    const int head = item.x, m = item.y;
-    const int cls = map_head_class[head];
-    const int kvh = head / a.G;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hl = lane >> 5, col = lane & 31;
-    const int L = a.L;
-    const int row_slot = map_row_order[m * kBlockM + wave * 32 + col];
-    const int row = row_slot < 0 ? L : row_slot;
-
-    const int R = L - a.q_begin;   // query rows per head
-    const float *qh = reinterpret_cast<const float *>(a.q) + (size_t)head * R * D;
-    const float *kh = reinterpret_cast<const float *>(a.k) + (size_t)kvh * L * D;
-    const float *vh = reinterpret_cast<const float *>(a.v) + (size_t)kvh * L * D;
-
-    float qreg[D / 2];  // Q[row][2t + hl]
-    {
-        const int qrow = min(row, L - 1) - a.q_begin;
-#pragma unroll
-        for (int t = 0; t < D / 2; ++t) qreg[t] = qh[(size_t)qrow * D + 2 * t + hl];
-    }
-    QueryView qv;
-    qv.init(map_code, map_span_range, map_free_before, map_span_free, a.L, cls, row, a.packed != 0, a.intra_compact != 0,
-            a.bidir != 0, a.window);
-
-    floatx16 o[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-
-    TileWalker tw;
-    tw.init(map_ranges, map_row_ptr[cls * (a.M + 1) + m], map_row_ptr[cls * (a.M + 1) + m + 1]);
-
-    for (; tw.valid(); tw.next()) {
-        __syncthreads();
-        for (int idx = tid; idx < kBlockN * (D / 4); idx += kThreads) {
-            const int key = idx / (D / 4), ch = idx % (D / 4);
-            // the key this slot of the tile holds (a compact tile of a packed map gathers free keys);
-            // a slot without a key is masked below, any finite values will do for it
-            const int grow = max(map_key_order[tw.n * kBlockN + key], 0);
-            const floatx4 kk = *reinterpret_cast<const floatx4 *>(kh + (size_t)grow * D + ch * 4);
-            const floatx4 vv = *reinterpret_cast<const floatx4 *>(vh + (size_t)grow * D + ch * 4);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                lds_k[key * KS + ch * 4 + r] = kk[r];
-                lds_v[key * VS + ch * 4 + r] = vv[r];
-            }
-        }
-        __syncthreads();
-
-        floatx16 s[2];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
-#pragma unroll
-            for (int t = 0; t < D / 2; ++t)
-                s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(lds_k[(32 * kb + col) * KS + 2 * t + hl], qreg[t], s[kb], 0, 0, 0);
-        }
-        float alpha;
-        if (tw.full) {
-            softmax_block<false>(s, m_run, l_run, alpha, a.scale_log2e);
-        } else {
-            const uint64_t tb = map_text_bits[tw.n];
-            const uint64_t sb = map_sink_bits[tw.n];
-            apply_mask(s, allowed_keys(qv, cls, tb, sb, tw.n, a.n_prompt_tiles), hl);
-            softmax_block<true>(s, m_run, l_run, alpha, a.scale_log2e);
-        }
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-
-        // contraction slot hl of MFMA (kb, v) is key 32kb + 8(v/4) + 4hl + v%4
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int key = 32 * kb + 8 * (v / 4) + 4 * hl + (v % 4);
-                    o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(lds_v[key * VS + 32 * db + col], s[kb][v], o[db], 0, 0, 0);
-                }
-    }
-
-    const float l_tot = sum_across_halves(l_run);
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    if (row < L) {
-        float *orow = reinterpret_cast<float *>(a.out) + ((size_t)head * R + (row - a.q_begin)) * D;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                floatx4 w;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) w[r] = o[db][4 * g + r] * inv;
-                *reinterpret_cast<floatx4 *>(orow + 32 * db + 8 * g + 4 * hl) = w;
-            }
-    }
-}
-
-template <int D>
-constexpr size_t f32_lds_bytes() { return (size_t)kBlockN * (D + 1) * 4 + (size_t)kBlockN * (D + 8) * 4; }
-
 }  // namespace bs
 
 using bs::DeviceMap;
@@ -1231,9 +837,7 @@ int device_setup(int dev, void **scratch_out, int *n_cus_out)
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs::attn_prefill_bf16<64>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, bs::bf16_lds_bytes<64>());
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs::attn_prefill_f32<128>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bs::f32_lds_bytes<128>());
+        if (e == hipSuccess) e = bs::f32_device_setup();
         if (e == hipSuccess) e = bs::rows_device_setup();
         if (e != hipSuccess) return bs::fail_hip(e, "hipFuncSetAttribute");
         int cus = 0;
@@ -1304,14 +908,14 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
                        shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
                        d->queue_ctr, shares ? d->share_queue_off : d->queue_off, shares ? d->share_off : nullptr, cut_results);
     if (shares && d->n_cut > 0)
-        hipLaunchKernelGGL(bs::merge_cut_items<D>, dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
+        hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
                            d->row_order, cut_results);
 }
 
 // Bytes of the results of cut units (0 without equal shares).
 size_t cut_bytes(const DeviceMap *d, int head_dim)
 {
-    return (size_t)d->n_slots * 4 * (head_dim == 128 ? bs::kCutSlotFloats<128> : bs::kCutSlotFloats<64>);
+    return (size_t)d->n_slots * 2 * 4 * (head_dim == 128 ? bs::kCutItemFloats<128> : bs::kCutItemFloats<64>);
 }
 
 size_t bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
@@ -1348,7 +952,7 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
     int n_cus = 0;
     if ((rc = device_setup(dev, &unused, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
-    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, n_cus, st);
+    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_cus, st);   // (fp32: head dimension 128)
     if (rc != BS_OK) return rc;
     e = hipEventRecord(d->last_use->ev, st);
     return e == hipSuccess ? BS_OK : bs::fail_hip(e, "hipEventRecord");
@@ -1381,7 +985,8 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
     if (!rows.use || rows.need_bits)
         if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
     if (!rows.use) {
-        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindWorkList, gqa_group, n_cus, st);
+        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group,
+                                dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim), st);
         if (rc != BS_OK) return rc;
     }
 
@@ -1409,12 +1014,9 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
         if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
         else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
     } else {
+        if ((rc = workspace(bs::f32_workspace(d, head_dim))) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
-        const dim3 grid((unsigned)d->n_work), block(bs::kThreads);
-        if (head_dim == 128)
-            hipLaunchKernelGGL(bs::attn_prefill_f32<128>, grid, block, bs::f32_lds_bytes<128>(), st, a, BS_MAP_ARGS(d));
-        else
-            hipLaunchKernelGGL(bs::attn_prefill_f32<64>, grid, block, bs::f32_lds_bytes<64>(), st, a, BS_MAP_ARGS(d));
+        bs::launch_f32(a, d, d->vt_buf, head_dim, st);
     }
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");

@@ -3,8 +3,7 @@
 // A map has two parts on the device.  The PROMPT part depends on the span table and the map
 // options only (token codes, row and key order, key bit masks, the four per-class range lists):
 // it is uploaded once and serves every layer of the model.  The BINDING part depends on the class
-// vector the map is bound to (and, for the bf16 kernel, on the GQA group size): the head classes
-// and the work list or work units.  bs_tilemap_rebind only invalidates the binding part.
+// vector the map is bound to (and, for the bf16 kernel, on the GQA group size): the work units.  bs_tilemap_rebind only invalidates the binding part.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,7 +28,7 @@ struct EventHolder {
     ~EventHolder() { if (ev) (void)hipEventDestroy(ev); }
 };
 
-enum BindingKind : int32_t { kBindNone = 0, kBindWorkList = 1, kBindPairPlan = 2 };
+enum BindingKind : int32_t { kBindNone = 0, kBindSolo = 1, kBindPairPlan = 2 };
 
 struct DeviceMap {
     int device = -1;
@@ -52,10 +51,8 @@ struct DeviceMap {
     int32_t bind_kind = kBindNone;
     int32_t bind_G = 0;
     uint64_t bind_epoch = 0;              // class_epoch of the map the binding was made for
-    const uint8_t *head_class = nullptr;  // [Hq]
-    const int2 *work = nullptr;           // fp32 kernel: [n_work] (head, query tile)
-    int32_t n_work = 0;
-    const int4 *pair_items = nullptr;     // bf16 kernel: work units, two int4 each
+    int32_t bind_wgs = 0;                 // workgroups the shares were cut for
+    const int4 *pair_items = nullptr;     // work units, two int4 each
     const int2 *pair_ranges = nullptr;
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])
@@ -94,7 +91,7 @@ void staging_abandon(const Staging &s);
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Upload the prompt part (once per map) / the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cus, hipStream_t st);
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, hipStream_t st);
 // Order work queued on `st` after the map's previous use if that was on another stream.
 int order_after_last_use(DeviceMap *d, hipStream_t st);
 

@@ -323,59 +323,49 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cus, hipStream_t st)
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, hipStream_t st)
 {
     DeviceMap *d = tm->dev;
     if (!d) return BS_EINVAL;
-    if (kind == kBindWorkList) gqa_group = 0;   // the work list does not depend on it
-    if (d->bind_kind == kind && d->bind_G == gqa_group && d->bind_epoch == tm->class_epoch) return BS_OK;
+    if (kind == kBindSolo) gqa_group = 0;   // its units do not depend on it
+    if (d->bind_kind == kind && d->bind_G == gqa_group && d->bind_wgs == n_wgs && d->bind_epoch == tm->class_epoch) return BS_OK;
     try {
-        if (kind == kBindPairPlan) bs_plan_shares(tm, gqa_group, n_cus);   // and the pair plan it is made from
-        else bs_plan_work(tm);
+        bs_plan_shares(tm, gqa_group, n_wgs);   // and the pair or solo plan it is made from
     } catch (const std::bad_alloc &) {
         return BS_ENOMEM;
     }
-    const PairPlan &plan = tm->pairs;
-    if (kind == kBindPairPlan && plan.ranges.size() >= (size_t)INT32_MAX) return BS_EUNSUPPORTED;
-    const size_t n_heads = tm->head_class.size();
-    const size_t off_class = 0;
-    const size_t off_a = align256(off_class + n_heads);    // work list, or work units
-    const size_t a_bytes = kind == kBindPairPlan ? plan.items.size() * sizeof(PairItem) : tm->work.size() * sizeof(WorkItem);
-    const size_t off_b = align256(off_a + a_bytes);        // ranges of the work units
-    const size_t b_bytes = kind == kBindPairPlan ? std::max<size_t>(plan.ranges.size(), 1) * sizeof(PairRange) : 0;
-    const size_t off_q = align256(off_b + b_bytes);        // queue offsets [9], then queue counters [8]
+    const PairPlan &plan = kind == kBindPairPlan ? tm->pairs : tm->solo;
+    if (plan.ranges.size() >= (size_t)INT32_MAX) return BS_EUNSUPPORTED;
     const SharePlan &shares = tm->shares;
-    const bool shared = kind == kBindPairPlan && !shares.share_off.empty();
-    const size_t off_si = align256(off_q + 256);           // equal shares: parts, their ranges, share offsets, cut items
-    const size_t off_sr = align256(off_si + (shared ? shares.parts.size() * sizeof(PairItem) : 0));
-    const size_t off_so = align256(off_sr + (shared ? shares.ranges.size() * sizeof(PairRange) : 0));
-    const size_t off_sq = align256(off_so + (shared ? shares.share_off.size() * 4 : 0));
-    const size_t off_sc = align256(off_sq + (shared ? sizeof shares.queue_off : 0));
-    const size_t bytes = align256(off_sc + (shared ? shares.cut.size() * sizeof(CutItem) : 0));
+    const bool shared = !shares.share_off.empty();
+    // the parts of the block, one after the other: units, their ranges, queue offsets [9] and counters [8 at + 64 B]; then
+    // equal shares: parts, their ranges, share offsets, queue offsets, cut items
+    size_t bytes = 0;
+    auto section = [&](size_t n) { const size_t at = bytes; bytes = align256(bytes + n); return at; };
+    const size_t off_a = section(plan.items.size() * sizeof(PairItem));
+    const size_t off_b = section(std::max<size_t>(plan.ranges.size(), 1) * sizeof(PairRange));
+    const size_t off_q = section(256);
+    const size_t off_si = section(shares.parts.size() * sizeof(PairItem));
+    const size_t off_sr = section(shares.ranges.size() * sizeof(PairRange));
+    const size_t off_so = section(shares.share_off.size() * 4);
+    const size_t off_sq = section(sizeof shares.queue_off);
+    const size_t off_sc = section(shares.cut.size() * sizeof(CutItem));
 
     Staging sg;
     hipError_t e = staging_begin(bytes, &sg);
     if (e != hipSuccess) return fail_hip(e, "pinned staging buffer");
     unsigned char *host = static_cast<unsigned char *>(sg.host);
-    if (shared) {
-        static_assert(sizeof(CutItem) == sizeof(int4), "copied as it is");
-        std::memcpy(host + off_si, shares.parts.data(), shares.parts.size() * sizeof(PairItem));
-        std::memcpy(host + off_sr, shares.ranges.data(), shares.ranges.size() * sizeof(PairRange));
-        std::memcpy(host + off_so, shares.share_off.data(), shares.share_off.size() * 4);
-        std::memcpy(host + off_sq, shares.queue_off, sizeof shares.queue_off);
-        if (!shares.cut.empty()) std::memcpy(host + off_sc, shares.cut.data(), shares.cut.size() * sizeof(CutItem));
-    }
-    std::memcpy(host + off_class, tm->head_class.data(), n_heads);
-    if (kind == kBindPairPlan) {
-        static_assert(sizeof(PairItem) == 2 * sizeof(int4) && sizeof(PairRange) == sizeof(int2), "copied as they are");
-        std::memcpy(host + off_a, plan.items.data(), a_bytes);
-        if (!plan.ranges.empty()) std::memcpy(host + off_b, plan.ranges.data(), plan.ranges.size() * sizeof(PairRange));
-        std::memset(host + off_q, 0, 256);
-        std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
-    } else {
-        static_assert(sizeof(WorkItem) == sizeof(int2), "copied as it is");
-        std::memcpy(host + off_a, tm->work.data(), a_bytes);
-    }
+    static_assert(sizeof(PairItem) == 2 * sizeof(int4) && sizeof(PairRange) == sizeof(int2) && sizeof(CutItem) == sizeof(int4), "copied as they are");
+    auto put = [&](size_t at, const auto &v) { if (!v.empty()) std::memcpy(host + at, v.data(), v.size() * sizeof(v[0])); };
+    put(off_a, plan.items);
+    put(off_b, plan.ranges);
+    std::memset(host + off_q, 0, 256);
+    std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
+    put(off_si, shares.parts);
+    put(off_sr, shares.ranges);
+    put(off_so, shares.share_off);
+    std::memcpy(host + off_sq, shares.queue_off, sizeof shares.queue_off);
+    put(off_sc, shares.cut);
     // a fresh block every time: kernels of an earlier binding may still be reading the old one,
     // which goes back to the cache behind the map's last-use event
     void *blob = nullptr;
@@ -388,7 +378,7 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cu
     e = staging_commit(sg, blob, bytes, st);
     if (e != hipSuccess) {
         (void)hipFree(blob);
-        return fail_hip(e, "hipMemcpyAsync(work units)");
+        return fail_hip(e, "copy of the work units");
     }
     if (d->bind_blob) {
         // the event object is shared with the cached block, and recorded again by later launches
@@ -400,23 +390,21 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_cu
     d->bind_cap = cap;
     d->bind_kind = kind;
     d->bind_G = gqa_group;
+    d->bind_wgs = n_wgs;
     d->bind_epoch = tm->class_epoch;
-    d->head_class = b + off_class;
-    d->work = kind == kBindWorkList ? reinterpret_cast<const int2 *>(b + off_a) : nullptr;
-    d->n_work = kind == kBindWorkList ? (int32_t)tm->work.size() : 0;
-    d->pair_items = kind == kBindPairPlan ? reinterpret_cast<const int4 *>(b + off_a) : nullptr;
-    d->pair_ranges = kind == kBindPairPlan ? reinterpret_cast<const int2 *>(b + off_b) : nullptr;
-    d->n_pairs = kind == kBindPairPlan ? (int32_t)plan.items.size() : 0;
-    d->queue_off = kind == kBindPairPlan ? reinterpret_cast<const int32_t *>(b + off_q) : nullptr;
-    d->share_items = shared ? reinterpret_cast<const int4 *>(b + off_si) : nullptr;
-    d->share_ranges = shared ? reinterpret_cast<const int2 *>(b + off_sr) : nullptr;
-    d->share_off = shared ? reinterpret_cast<const int32_t *>(b + off_so) : nullptr;
-    d->share_queue_off = shared ? reinterpret_cast<const int32_t *>(b + off_sq) : nullptr;
-    d->cut_items = shared ? reinterpret_cast<const int4 *>(b + off_sc) : nullptr;
+    d->pair_items = reinterpret_cast<const int4 *>(b + off_a);
+    d->pair_ranges = reinterpret_cast<const int2 *>(b + off_b);
+    d->n_pairs = (int32_t)plan.items.size();
+    d->queue_off = reinterpret_cast<const int32_t *>(b + off_q);
+    d->queue_ctr = reinterpret_cast<int32_t *>(b + off_q + 64);
+    d->share_items = reinterpret_cast<const int4 *>(b + off_si);
+    d->share_ranges = reinterpret_cast<const int2 *>(b + off_sr);
+    d->share_off = reinterpret_cast<const int32_t *>(b + off_so);
+    d->share_queue_off = reinterpret_cast<const int32_t *>(b + off_sq);
+    d->cut_items = reinterpret_cast<const int4 *>(b + off_sc);
     d->n_shares = shared ? (int32_t)shares.share_off.size() - 1 : 0;
-    d->n_cut = shared ? (int32_t)shares.cut.size() : 0;
-    d->n_slots = shared ? shares.n_slots : 0;
-    d->queue_ctr = kind == kBindPairPlan ? reinterpret_cast<int32_t *>(b + off_q + 64) : nullptr;
+    d->n_cut = (int32_t)shares.cut.size();
+    d->n_slots = shares.n_slots;
     return BS_OK;
 }
 

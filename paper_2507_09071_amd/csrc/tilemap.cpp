@@ -680,25 +680,35 @@ void bs::row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *la
     }
 }
 
-// Work list of the fp32 kernel: heaviest (head, query tile) first so the tail of the launch is
-// short; ties keep one KV group's heads of a query tile next to each other.
-void bs_plan_work(bs_tilemap *tm)
+// Units of the fp32 kernel: every (head, query tile) on its own, heaviest first so the tail of the launch is short;
+// ties keep one KV group's heads of a query tile next to each other.
+void bs_plan_solo(bs_tilemap *tm)
 {
-    if (tm->work_epoch == tm->class_epoch) return;
-    const int32_t H = tm->n_q_heads;
-    tm->work.resize((size_t)H * tm->M);
-    size_t w = 0;
-    for (int32_t h = 0; h < H; ++h)
-        for (int32_t m = 0; m < tm->M; ++m) tm->work[w++] = {h, m};
-    const bs_tilemap *t = tm;
-    std::stable_sort(tm->work.begin(), tm->work.end(), [t](const bs::WorkItem &a, const bs::WorkItem &b) {
-        int32_t ca = t->cls[t->head_class[a.head]].row_tiles[a.q_tile];
-        int32_t cb = t->cls[t->head_class[b.head]].row_tiles[b.q_tile];
-        if (ca != cb) return ca > cb;
-        if (a.q_tile != b.q_tile) return a.q_tile > b.q_tile;
-        return a.head < b.head;
+    bs::PairPlan &plan = tm->solo;
+    if (plan.epoch == tm->class_epoch) return;
+    plan.ranges.clear();
+    plan.items.clear();
+    const int32_t H = tm->n_q_heads, M = tm->M;
+    int32_t base[4];   // the class's lists in plan.ranges
+    for (int c = 0; c < 4; ++c) {
+        base[c] = -1;
+        if (std::find(tm->head_class.begin(), tm->head_class.end(), (uint8_t)c) == tm->head_class.end()) continue;
+        base[c] = (int32_t)plan.ranges.size();
+        for (const TileRange &r : tm->cls[c].ranges) plan.ranges.push_back({r.begin, (r.end() << 4) | ((r.full() ? 2 : 1) << 2)});
+    }
+    plan.items.reserve((size_t)H * M);
+    for (int32_t h = 0; h < H; ++h) {
+        const int c = tm->head_class[h];
+        const ClassLists &cl = tm->cls[c];
+        for (int32_t m = 0; m < M; ++m)
+            plan.items.push_back({h, m, -1, 0, base[c] + (int32_t)cl.row_ptr[m], base[c] + (int32_t)cl.row_ptr[m + 1], cl.row_tiles[m], c});
+    }
+    std::sort(plan.items.begin(), plan.items.end(), [](const bs::PairItem &a, const bs::PairItem &b) {
+        if (a.n_tiles != b.n_tiles) return a.n_tiles > b.n_tiles;
+        if (a.tile_a != b.tile_a) return a.tile_a > b.tile_a;
+        return a.head_a < b.head_a;
     });
-    tm->work_epoch = tm->class_epoch;
+    plan.epoch = tm->class_epoch;
 }
 
 extern "C" int bs_tilemap_rebind(bs_tilemap *tm, const uint8_t *head_class, int32_t n_q_heads)
@@ -912,17 +922,22 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
 // as short pieces that go to the queues, for whoever is done first.
 // Costs are in key-tile steps: a unit or part costs its steps and kUnitCost around them (prologue and epilogue,
 // 8 us against 1.3-1.7 us per step by time stamps), the merge kMergeCost for the launch.
-void bs_plan_shares(bs_tilemap *tm, int32_t G, int32_t n_wgs)
+void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
 {
     bs::SharePlan &sp = tm->shares;
-    if (sp.gqa_group == G && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
-    bs_plan_pairs(tm, G);
-    const bs::PairPlan &plan = tm->pairs;
+    if (sp.gqa_group == gqa_group && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
+    const bool solo = gqa_group == 0;
+    if (solo) bs_plan_solo(tm);
+    else bs_plan_pairs(tm, gqa_group);
+    const bs::PairPlan &plan = solo ? tm->solo : tm->pairs;
+    const int32_t G = std::max(gqa_group, 1);
     sp.parts.clear(); sp.ranges.clear(); sp.share_off.clear(); sp.cut.clear();
     sp.n_slots = 0;
     std::fill(sp.queue_off, sp.queue_off + 9, 0);
-    sp.gqa_group = G; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
-    constexpr int64_t kUnitCost = 6, kMergeCost = 6, kMinPart = 4, kMaxUnitsPerWg = 3;
+    sp.gqa_group = gqa_group; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
+    // the fp32 kernel's steps take 3.5-7 us
+    const int64_t kUnitCost = solo ? 1 : 6, kMergeCost = solo ? 1 : 6, kMinPart = solo ? 1 : 4;
+    constexpr int64_t kMaxUnitsPerWg = 3;
     const int32_t n_units = (int32_t)std::min<size_t>(plan.items.size(), INT32_MAX);
     if (n_units > kMaxUnitsPerWg * n_wgs || n_wgs > 4096) return;
     int64_t total = 0, longest = 0;
@@ -962,7 +977,7 @@ void bs_plan_shares(bs_tilemap *tm, int32_t G, int32_t n_wgs)
     std::vector<Piece> pieces;
     std::vector<int32_t> homeless;
     std::vector<int64_t> load(n_wgs);
-    constexpr int64_t kQueuedFrom = 600;   // shares from here on hand a sixth of the steps to the queues ...
+    const int64_t kQueuedFrom = solo ? INT64_MAX : 600;   // shares from here on hand a sixth of the steps to the queues ...
     auto fill = [&](int64_t share) {       // false: units are left over
         const int64_t fixed = share >= kQueuedFrom ? share - share / 6 : share;
         const int64_t queue_piece = share / 24;   // ... in pieces of four to that sixth

@@ -28,8 +28,6 @@ struct ClassLists {
     int64_t visited = 0, full = 0, partial = 0, allowed_pairs = 0, empty_rows = 0;
 };
 
-struct WorkItem { int32_t head, q_tile; };
-
 // Work unit of the bf16 kernel: two (head, query tile) items that read the SAME KV head and walk
 // one merged key-tile list, so a workgroup streams each K / V tile once for both.
 //   item B is absent when head_b < 0.
@@ -79,10 +77,11 @@ void row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, 
 
 // Pair up the work items for KV-sharing workgroups (host only; see PairItem).
 void bs_plan_pairs(bs_tilemap *tm, int32_t gqa_group);
-// Cut the units of the pair plan into equal shares for n_wgs workgroups, if that pays (host only; see SharePlan).
+// The units of the fp32 kernel: every (head, query tile) on its own, heaviest first (host only).
+void bs_plan_solo(bs_tilemap *tm);
+// Cut the units of the pair plan (of the solo plan if gqa_group is 0) into equal shares for n_wgs workgroups, if that
+// pays (host only; see SharePlan).
 void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs);
-// The plain work list of the fp32 kernel: every (head, query tile), heaviest first (host only).
-void bs_plan_work(bs_tilemap *tm);
 
 struct bs_tilemap {
     int32_t L = 0, bm = 0, bn = 0, M = 0, N = 0, n_q_heads = 0, sink_len = 0;
@@ -105,10 +104,9 @@ struct bs_tilemap {
     std::vector<uint64_t> text_bits;       // N: bit b of entry n = key n*bn + b is a text key (bn <= 64 only)
     std::vector<uint64_t> sink_bits;       // N: same for sink keys
     bs::ClassLists cls[4];
-    uint64_t class_epoch = 1;              // bumped by bs_tilemap_rebind: work list, work units and their device copies are stale
-    std::vector<bs::WorkItem> work;        // n_q_heads * M items, heaviest first; built on first use (work_epoch)
-    uint64_t work_epoch = 0;
+    uint64_t class_epoch = 1;              // bumped by bs_tilemap_rebind: work units and their device copies are stale
     bs::PairPlan pairs;                    // built on first use for a given gqa_group and class vector
+    bs::PairPlan solo;                     // one item per unit; built on first use
     bs::SharePlan shares;
     bs::DeviceMap *dev = nullptr;          // created lazily by bs_tilemap_upload
     void (*dev_free)(bs::DeviceMap *) = nullptr;
