@@ -33,12 +33,10 @@ __device__ inline float sum_across_halves(float x)
 struct KernelArgs {
     const void *q, *k, *v;
     void *out;
-    int32_t L, M, G;
+    int32_t L, G;
     float scale_log2e;  // scale * log2(e): softmax runs in the exp2 domain
     int32_t n_prompt_tiles;   // key tiles that are the prompt in position order (compact tiles follow)
     int32_t packed, intra_compact;
-    int32_t bidir;            // tokens of one image also see the later tokens of that image
-    int32_t window;           // > 0: keys more than window - 1 positions before the query are masked
     int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
 };
 // What the lane's query may see (paper Sec. 3.2), in a form that is cheap to apply per tile.
@@ -55,31 +53,21 @@ struct QueryView {
     int32_t cfree_hi;
     bool sees_all;     // text query or Dense head: every earlier key
     bool own_only;     // packed: in the prompt's tiles only own-image keys count for this query
-    __device__ void init(const uint32_t *__restrict__ code, const int2 *__restrict__ span_range,
-                         const int32_t *__restrict__ free_before, const int2 *__restrict__ span_free,
-                         int L, int cls, int32_t i, bool packed, bool intra_compact, bool bidir, int32_t window)
+    // From the row's record in the map's device copy (two int4, see RowRecord).
+    __device__ void init(const int4 &r0, const int4 &r1, int cls, bool packed, bool intra_compact)
     {
-        row = i;
-        first = window > 0 ? max(0, i - window + 1) : 0;
-        const uint32_t qcode = i < L ? code[i] : kCodeText;
-        sees_all = (qcode & kCodeText) || cls == BS_DENSE;
+        first = r0.y;
+        row = r0.z;
+        const bool image = r1.x > r0.w;
+        sees_all = !image || cls == BS_DENSE;
         own_lo = own_hi = 0;
         free_bound = cfree_lo = cfree_hi = 0;
         own_only = false;
-        if (!(qcode & kCodeText) && (bidir || (cls & 2))) {
-            const int2 sp = span_range[qcode & kCodeImgMask];
-            // an image query that sees its whole image behaves, for every class, like the
-            // image's last query under the causal mask; its image stays visible beyond a window
-            if (bidir) { row = sp.y - 1; first = min(first, sp.x); }
-            if (!sees_all && (cls & 2)) { own_lo = sp.x; own_hi = sp.y; }
-        }
+        if (!sees_all && (cls & 2)) { own_lo = r0.w; own_hi = r1.x; }
         if (packed && !sees_all && (cls != BS_INTRA || intra_compact)) {
-            free_bound = free_before[row + 1];
+            free_bound = r1.y;
             own_only = true;
-            if (cls == BS_INTRA_SINK) {
-                const int2 cr = span_free[qcode & kCodeImgMask];
-                cfree_lo = cr.x; cfree_hi = cr.y;
-            }
+            if (cls == BS_INTRA_SINK) { cfree_lo = r1.z; cfree_hi = r1.w; }
         }
     }
 };

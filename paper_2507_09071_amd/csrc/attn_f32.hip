@@ -4,7 +4,7 @@
 // Bound: the fp32 matrix pipe (157 TFLOP/s; a 64-key tile is 8,192 cycles of it per wave at head dimension 64, 16,384 at
 // 128), on short prompts the number of tiles a wave walks one after the other.  A workgroup is four waves of 32 rows of one
 // (head, query tile) item.  K and V tiles go global -> LDS straight from the caller's arrays with LDS-direct loads, one
-// tile ahead of the one that is computed, with one barrier per tile; keys of compact tiles are gathered through key_order
+// tile ahead of the one that is computed, with one barrier per tile; keys of compact tiles are gathered
 // by the lanes' addresses.  K rows exchange their 16-byte chunks (XOR with the row), so a column read of four channels per
 // lane is free of conflicts and feeds four MFMAs; V is read a row at a time.  Few items are cut along their key tiles into
 // equal shares for the whole chip, as in the bf16 kernel, and merged by merge_cut_items.
@@ -69,10 +69,8 @@ __device__ inline void softmax_block(floatx16 (&s)[2], float &m_run, float &l_ru
 
 template <int D>
 __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32(
-    KernelArgs a, const uint32_t *__restrict__ map_code, const uint64_t *__restrict__ map_text_bits,
-    const uint64_t *__restrict__ map_sink_bits, const int2 *__restrict__ map_span_range, const int32_t *__restrict__ map_row_order,
-    const int32_t *__restrict__ map_key_order, const int32_t *__restrict__ map_free_before, const int2 *__restrict__ map_span_free,
-    const int4 *__restrict__ items, const int2 *__restrict__ item_ranges, const int32_t *__restrict__ share_off,
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const int32_t *__restrict__ compact_keys, const int4 *__restrict__ items, const int2 *__restrict__ item_ranges, const int32_t *__restrict__ share_off,
     float *__restrict__ cut_results)
 {
     constexpr int ROWB = D * 4, TILE = kBlockN * ROWB, NDB = D / 32;
@@ -101,9 +99,12 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
         uint32_t row_off[NI];
 #pragma unroll
         for (int j = 0; j < NI; ++j) row_off[j] = (ld_row + j * (64 / CHUNKS)) * ROWB;
-        if (!whole) {   // a compact tile, or the last keys: positions from the key order; a slot without a key is masked
+        if (!whole) {   // the last keys, or a compact tile, whose slots name the keys; a slot without a key is masked
 #pragma unroll
-            for (int j = 0; j < NI; ++j) row_off[j] = (uint32_t)max(map_key_order[n * kBlockN + ld_row + j * (64 / CHUNKS)], 0) * ROWB;
+            for (int j = 0; j < NI; ++j) {
+                const int s = n * kBlockN + ld_row + j * (64 / CHUNKS);
+                row_off[j] = (uint32_t)(n < a.n_prompt_tiles ? min(s, L - 1) : max(compact_keys[s - a.n_prompt_tiles * kBlockN], 0)) * ROWB;
+            }
         }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
@@ -126,8 +127,8 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
         w_next = w;
         if (T > 0) issue_tile(kh, vh, w.n, 0);
 
-        const int row_slot = map_row_order[m * kBlockM + wave * 32 + col];
-        const int row = row_slot < 0 ? L : row_slot;
+        const int4 r0 = map_rows[2 * (m * kBlockM + wave * 32 + col)], r1 = map_rows[2 * (m * kBlockM + wave * 32 + col) + 1];
+        const int row = r0.x;   // L: no row here, computed on a copy of the last one and not stored
         floatx4 q[D / 8];   // Q[row][8j + 4hl .. +4)
         {
             const float *qr = static_cast<const float *>(a.q) + ((size_t)head * R + min(row, L - 1) - a.q_begin) * D;
@@ -135,8 +136,7 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
             for (int j = 0; j < D / 8; ++j) q[j] = *reinterpret_cast<const floatx4 *>(qr + 8 * j + 4 * hl);
         }
         QueryView qv;
-        qv.init(map_code, map_span_range, map_free_before, map_span_free, L, cls, row, a.packed != 0, a.intra_compact != 0,
-                a.bidir != 0, a.window);
+        qv.init(r0, r1, cls, a.packed != 0, a.intra_compact != 0);
         // What was loaded for the rows must be here before the loop: the compiler would wait for it inside, and with it
         // for the LDS-direct loads, which it does not know.
 #pragma unroll
@@ -235,12 +235,12 @@ static void launch_f32_dim(const KernelArgs &a, const DeviceMap *d, void *worksp
     const bool shares = d->n_shares > 0;
     float *cut_results = static_cast<float *>(workspace);
     hipLaunchKernelGGL(attn_prefill_f32<D>, dim3((unsigned)(shares ? d->n_shares : d->n_pairs)), dim3(kF32Threads), f32_lds_bytes<D>(), st,
-                       a, d->code, d->text_bits, d->sink_bits, d->span_range, d->row_order, d->key_order, d->free_before, d->span_free,
+                       a, d->text_bits, d->sink_bits, d->rows, d->compact_keys,
                        shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges,
                        shares ? d->share_off : nullptr, cut_results);
     if (shares && d->n_cut > 0)
         hipLaunchKernelGGL((merge_cut_items<D, 1, float>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
-                           d->row_order, cut_results);
+                           d->rows, cut_results);
 }
 
 void launch_f32(const KernelArgs &a, const DeviceMap *d, void *workspace, int32_t head_dim, hipStream_t st)

@@ -199,18 +199,24 @@ __device__ inline void mfma_drain(floatx16 &c0, floatx16 &c1)
 //            as two halves h holding keys 16g + {4h..4h+3, 8+4h..8+4h+3} (the contraction slots
 //            of lane half h), stored at half h ^ ((channel >> 3) & 1)
 // A 128-bit read of 16 consecutive keys (channels) then touches every bank exactly once.
-// The key of every tile slot comes from the map's key order (the prompt in position order, then
-// the compact tiles of a packed map); slots without a key are zero-filled.
+// The prompt's tiles hold its keys in position order, the compact tiles of a packed map the keys their slots
+// name; slots without a key are zero-filled.
+__device__ inline int slot_key(const int32_t *__restrict__ compact_keys, int n, int key, int L, int N0)   // -1: no key
+{
+    const int s = n * kBlockN + key;
+    return n < N0 ? (s < L ? s : -1) : compact_keys[s - N0 * kBlockN];
+}
+
 template <int D>
 __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__restrict__ vt,
-                                    const int32_t *__restrict__ key_order, int L, int N, __bf16 *tile)
+                                    const int32_t *__restrict__ compact_keys, int L, int N, int N0, __bf16 *tile)
 {
     constexpr int PAD = D + 2;  // odd word stride: the column gathers below spread over banks
     const int n = blockIdx.x, kvh = blockIdx.y, tid = threadIdx.x;
     const __bf16 *src = v + (size_t)kvh * L * D;
     for (int idx = tid; idx < kBlockN * (D / 8); idx += 256) {
         const int key = idx / (D / 8), ch = idx % (D / 8);
-        const int pos = key_order[n * kBlockN + key];   // -1: the slot holds no key
+        const int pos = slot_key(compact_keys, n, key, L, N0);
         bf16x8 val;
 #pragma unroll
         for (int e = 0; e < 8; ++e) val[e] = (__bf16)0.f;
@@ -232,7 +238,7 @@ __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__rest
 
 template <int D>
 __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restrict__ kp,
-                                   const int32_t *__restrict__ key_order, int L, int N)
+                                   const int32_t *__restrict__ compact_keys, int L, int N, int N0)
 {
     const int n = blockIdx.x, kvh = blockIdx.y;
     const __bf16 *src = k + (size_t)kvh * L * D;
@@ -240,7 +246,7 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     for (int idx = threadIdx.x; idx < kBlockN * (D / 8); idx += 256) {   // one 16-byte half per iteration
         const int hp = idx & 1, key = (idx >> 1) % kBlockN, t = idx / (2 * kBlockN);
         const int h = hp ^ ((key >> 3) & 1);
-        const int pos = key_order[n * kBlockN + key];   // -1: the slot holds no key
+        const int pos = slot_key(compact_keys, n, key, L, N0);
         uint4 val = make_uint4(0, 0, 0, 0);
         if (pos >= 0) val = *reinterpret_cast<const uint4 *>(src + (size_t)pos * D + 16 * t + 8 * h);
         *reinterpret_cast<uint4 *>(dst + (size_t)idx * 8) = val;
@@ -251,14 +257,14 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
 template <int D>
 __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                                      __bf16 *__restrict__ kp, __bf16 *__restrict__ vt,
-                                                     const int32_t *__restrict__ key_order, int L, int N,
+                                                     const int32_t *__restrict__ compact_keys, int L, int N, int N0,
                                                      int32_t *__restrict__ queue_ctr)
 {
     __shared__ __bf16 tile[kBlockN * (D + 2)];
     // the attention kernel that follows starts on fresh unit queues
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
-    if (blockIdx.z == 0) pack_k_tile<D>(k, kp, key_order, L, N);
-    else pack_vt_tile<D>(v, vt, key_order, L, N, tile);
+    if (blockIdx.z == 0) pack_k_tile<D>(k, kp, compact_keys, L, N, N0);
+    else pack_vt_tile<D>(v, vt, compact_keys, L, N, N0, tile);
 }
 
 constexpr int kPingPongThreads = 512;
@@ -285,11 +291,8 @@ constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + 64; }   //
 // of the two waves queueing for the same unit.
 template <int D>
 __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
-    KernelArgs a, const uint32_t *__restrict__ map_code, const uint64_t *__restrict__ map_text_bits,
-    const uint64_t *__restrict__ map_sink_bits, const int2 *__restrict__ map_span_range,
-    const int32_t *__restrict__ map_row_order,
-    const int32_t *__restrict__ map_free_before, const int2 *__restrict__ map_span_free,
-    const int4 *__restrict__ pair_items,
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const int4 *__restrict__ pair_items,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
     int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
@@ -334,8 +337,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         const int kvh = __builtin_amdgcn_readfirstlane(it0.x / a.G);            // both items share it
         // a tile slot without a row behaves like a row past the end of the prompt (computed on a
         // copy of the last row, never stored)
-        const int row_slot = map_row_order[max(m, 0) * kBlockM + wave * 32 + col];
-        row = row_slot < 0 ? L : row_slot;
+        const int slot = max(m, 0) * kBlockM + wave * 32 + col;
+        const int4 r0 = map_rows[2 * slot], r1 = map_rows[2 * slot + 1];
+        row = r0.x;
         const __bf16 *qh = reinterpret_cast<const __bf16 *>(a.q) + (size_t)hsafe * R * D;
         // one TILE-byte block per key tile
         kph = reinterpret_cast<const char *>(kp + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
@@ -344,8 +348,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             qreg[t] = *reinterpret_cast<const bf16x8 *>(qh + (size_t)qrow * D + 16 * t + 8 * hl);
-        qv.init(map_code, map_span_range, map_free_before, map_span_free, L, cls, row, a.packed != 0, a.intra_compact != 0,
-                a.bidir != 0, a.window);
+        qv.init(r0, r1, cls, a.packed != 0, a.intra_compact != 0);
     };
 
     // LDS byte address of this lane's MFMA operand fragments inside a K / V^T tile (see the
@@ -878,13 +881,11 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
 {
     bs::KernelArgs a;
     a.q = q; a.k = k; a.v = v; a.out = out;
-    a.L = tm->L; a.M = tm->M; a.G = gqa_group;
+    a.L = tm->L; a.G = gqa_group;
     a.scale_log2e = scale * 1.4426950408889634f;
     a.n_prompt_tiles = tm->N0;
     a.packed = tm->packed;
     a.intra_compact = tm->intra_compact;
-    a.bidir = tm->bidir;
-    a.window = tm->window;
     a.q_begin = tm->q_begin;
     return a;
 }
@@ -901,15 +902,14 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(shares ? d->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                       static_cast<const __bf16 *>(a.v), kp, vt, d->key_order, tm->L, tm->N, d->queue_ctr);
+                       static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
-    hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->code, d->text_bits,
-                       d->sink_bits, d->span_range, d->row_order, d->free_before, d->span_free,
-                       shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
+    hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
+                       d->sink_bits, d->rows, shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
                        d->queue_ctr, shares ? d->share_queue_off : d->queue_off, shares ? d->share_off : nullptr, cut_results);
     if (shares && d->n_cut > 0)
         hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
-                           d->row_order, cut_results);
+                           d->rows, cut_results);
 }
 
 // Bytes of the results of cut units (0 without equal shares).

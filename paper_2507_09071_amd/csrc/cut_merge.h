@@ -30,7 +30,7 @@ __device__ inline void store_cut_item(float *item, const floatx16 (&o)[D / 32], 
 // keep a thousand waves reading; bf16 rows leave through LDS as 16-byte pieces.
 template <int D, int ITEMS, typename OUT>
 __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *__restrict__ cut_items,
-                                                      const int32_t *__restrict__ map_row_order,
+                                                      const int4 *__restrict__ map_rows,
                                                       const float *__restrict__ cut_results)
 {
     constexpr int NDB = D / 32, kStageRow = 64 + 16;   // 32 channels, then the row's position
@@ -44,8 +44,7 @@ __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *
     const floatx4 *src = reinterpret_cast<const floatx4 *>(slot) + (wave * NDB + db) * 256 + lane;
     constexpr size_t kNext = (size_t)ITEMS * kCutItemFloats<D>;
     if constexpr (std::is_same<OUT, __bf16>::value) if (hl == 0) {
-        const int row_slot = map_row_order[m * kBlockM + wave * 32 + col];
-        *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = row_slot < 0 ? a.L : row_slot;
+        *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = map_rows[2 * (m * kBlockM + wave * 32 + col)].x;
     }
 
     // one pass over the parts, with the reference point moving as in the attention loop
@@ -71,8 +70,8 @@ __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if constexpr (!std::is_same<OUT, __bf16>::value) {
-        const int pos = map_row_order[m * kBlockM + wave * 32 + col];
-        if (pos >= 0)
+        const int pos = map_rows[2 * (m * kBlockM + wave * 32 + col)].x;
+        if (pos < a.L)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 *reinterpret_cast<floatx4 *>(static_cast<float *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D + 32 * db + 8 * g + 4 * hl) = acc[g] * inv;

@@ -1,8 +1,8 @@
 // Device-side copy of a tile map and the memory plumbing around it (internal to the library).
 //
 // A map has two parts on the device.  The PROMPT part depends on the span table and the map
-// options only (token codes, row and key order, key bit masks, the four per-class range lists):
-// it is uploaded once and serves every layer of the model.  The BINDING part depends on the class
+// options only (what each query row may see, key order, key bit masks): a kernel makes it from the span
+// table, once per map, and it serves every layer of the model.  The BINDING part depends on the class
 // vector the map is bound to (and, for the bf16 kernel, on the GQA group size): the work units.  bs_tilemap_rebind only invalidates the binding part.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -30,21 +30,24 @@ struct EventHolder {
 
 enum BindingKind : int32_t { kBindNone = 0, kBindSolo = 1, kBindPairPlan = 2 };
 
+// A query-tile slot: two int4.  pos = first = last = L-like values for a slot without a row (see expand_map).
+struct RowRecord {
+    int32_t pos;                  // position of the row; L: no row
+    int32_t first, last;          // first and last visible position (window, own image under bidirectional images)
+    int32_t img_lo, img_hi;       // own image; empty for a text row
+    int32_t free_bound;           // free keys at positions <= last
+    int32_t cfree_lo, cfree_hi;   // compact slots of the free keys inside the own image
+};
+
 struct DeviceMap {
     int device = -1;
     // ---- prompt part: one block, uploaded once
     void *blob = nullptr;
     size_t blob_cap = 0;
-    const uint32_t *code = nullptr;       // [L] per-token code
-    const int32_t *row_order = nullptr;   // [M * 128] position of each query-tile row, -1 = none
-    const int32_t *key_order = nullptr;   // [N * 64] position of each key-tile slot, -1 = none
-    const int32_t *free_before = nullptr; // packed: [L + 1]
-    const int2 *span_free = nullptr;      // packed: [G + 1] compact slots of the free keys inside each image
+    const int4 *rows = nullptr;           // [M * 128][2] what the query in each query-tile slot may see (RowRecord)
+    const int32_t *compact_keys = nullptr;   // packed: [(N - N0) * 64] position of each compact slot, -1 = none
     const uint64_t *text_bits = nullptr;  // [N] text keys of each key tile
     const uint64_t *sink_bits = nullptr;  // [N] sink keys of each key tile
-    const int2 *span_range = nullptr;     // [G + 1] (start, end) by imgid; entry 0 unused
-    const int32_t *row_ptr = nullptr;     // [4][M + 1] offsets into ranges
-    const int2 *ranges = nullptr;         // concatenated over classes
     // ---- binding part: one block, uploaded again after a rebind / for another kind or group size
     void *bind_blob = nullptr;
     size_t bind_cap = 0;
@@ -89,7 +92,7 @@ void staging_abandon(const Staging &s);
 
 // The map's device side without any upload: the device it lives on, its last-use event (once per map).
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
-// Upload the prompt part (once per map) / the binding part (when stale) on `st`; no host-side wait.
+// Make the prompt part (once per map) / upload the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
 int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, hipStream_t st);
 // Order work queued on `st` after the map's previous use if that was on another stream.

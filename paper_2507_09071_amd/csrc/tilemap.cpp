@@ -11,6 +11,7 @@
 #include <climits>
 #include <cstring>
 #include <functional>
+#include <mutex>
 #include <new>
 
 #include "tilemap_internal.h"
@@ -25,33 +26,33 @@ using bs::TileRange;
 // every row of image g sees up to the image's last token, as if it were that token's query.
 struct Segment { int32_t g, a, b, ea, eb; };
 
-struct Geometry {
-    int32_t L, bm, bn, M, N;
-    const std::vector<bs_span> *spans;
-    std::vector<int32_t> n_text;       // L+1: text tokens in [0, t)
-    std::vector<int32_t> n_free_sink;  // L+1: tokens in [0, t) that are text or sink
-    std::vector<int32_t> last_text;    // L: largest text position <= t, or -1
-    std::vector<int32_t> next_text;    // L+1: smallest text position >= t, or L
-    std::vector<int32_t> next_free_sink;  // L+1: smallest (text or sink) position >= t, or L
-    // per key tile, for classes without / with the sink bit: smallest n' >= n whose keys are
-    // all free (text, or text/sink) and which is a complete tile; N if none
-    std::vector<int32_t> next_allfree_tile[2];  // N+1 each
-    // packed keys: compact tiles N .. N + Nc - 1 hold the free keys (text or sink) in position order
-    bool packed = false, intra_compact = false;
-    bool bidir = false;                // tokens of one image also see the later tokens of that image
-    int32_t window = 0;                // > 0: a query at position i sees no key before i - window + 1
-    int32_t Nc = 0, n_free = 0;
-    // first key position a query at position i may see: the start of its window; with bidirectional
-    // images the query's own image stays visible at any distance, so for an image token it is the
-    // smaller of the window's start and the image's start (the visible keys stay one interval, and the
-    // bound still grows with the position)
-    std::vector<int32_t> first_visible;   // L entries when window > 0
-    int32_t lo(int32_t i) const { return window > 0 ? first_visible[i] : 0; }
-    std::vector<int32_t> ctext;        // n_free + 1: text keys among compact slots [0, s)
+using bs::PromptGeometry;
 
-    const std::vector<int32_t> &free_count(int cls) const { return (cls & 1) ? n_free_sink : n_text; }
-    const std::vector<int32_t> &next_free(int cls) const { return (cls & 1) ? next_free_sink : next_text; }
-    const std::vector<int32_t> &next_allfree(int cls) const { return next_allfree_tile[cls & 1]; }
+// What the list builders need on top of the prompt's geometry (per-tile tables, no per-token ones).
+struct Geometry : PromptGeometry {
+    explicit Geometry(const PromptGeometry &g) : PromptGeometry(g) {}
+    // per key tile, for classes without / with the sink bit: smallest n' >= n whose keys are
+    // all free (text, or text/sink) and which is a complete tile; N0 if none.  Filled on first use.
+    mutable std::vector<int32_t> next_allfree_tile[2];  // N0 + 1 each
+    bool packed = false, intra_compact = false;
+    int32_t Nc = 0;
+    std::vector<int32_t> ctext;            // packed: text keys in the compact tiles before tile c (Nc + 1)
+    std::vector<TileRange> ctext_runs;     // runs of complete compact tiles by their text keys: FULL all, PARTIAL some
+
+    int32_t lo(int32_t i) const { return window > 0 ? first_visible(i) : 0; }
+    const std::vector<int32_t> &next_allfree(int cls) const
+    {
+        std::vector<int32_t> &t = next_allfree_tile[cls & 1];
+        if (t.empty()) {
+            t.assign(N0 + 1, N0);
+            for (int32_t n = N0 - 1; n >= 0; --n) {
+                const int32_t c0 = n * bn, c1 = std::min(c0 + bn, L);
+                const bool allfree = c1 - c0 == bn && free_count(cls, c1) - free_count(cls, c0) == bn;
+                t[n] = allfree ? n : t[n + 1];
+            }
+        }
+        return t;
+    }
 };
 
 struct QueryTile {
@@ -70,16 +71,13 @@ void describe_query_rows(const Geometry &G, int32_t r0, int32_t r1, bool ragged,
     qt.r0 = r0;
     qt.r1 = r1;
     qt.ragged = ragged;
-    int32_t lt = G.last_text[qt.r1 - 1];
+    int32_t lt = G.last_text(qt.r1 - 1);
     qt.last_text = (lt >= qt.r0) ? lt : -1;
     qt.segs.clear();
-    const auto &sp = *G.spans;
-    // first span whose end lies beyond r0
-    size_t lo = std::upper_bound(sp.begin(), sp.end(), qt.r0,
-                                 [](int32_t r, const bs_span &s) { return r < s.end; }) - sp.begin();
-    for (size_t g = lo; g < sp.size() && sp[g].start < qt.r1; ++g) {
+    const bs::SpanInfo *sp = G.spans.data();
+    for (int32_t g = G.span_at(qt.r0); g < G.n_spans && sp[g].start < qt.r1; ++g) {
         const int32_t a = std::max(sp[g].start, qt.r0), b = std::min(sp[g].end, qt.r1);
-        qt.segs.push_back({(int32_t)g, a, b, G.bidir ? sp[g].end - 1 : a, G.bidir ? sp[g].end : b});
+        qt.segs.push_back({g, a, b, G.bidir ? sp[g].end - 1 : a, G.bidir ? sp[g].end : b});
     }
     // the visible range grows with the row position, so the first / last row bound the tile
     qt.e0 = (!qt.segs.empty() && qt.segs.front().a == qt.r0) ? qt.segs.front().ea : qt.r0;
@@ -92,8 +90,8 @@ int tile_state(const Geometry &G, const QueryTile &qt, int cls, int32_t n)
     const int32_t c0 = n * G.bn, c1 = std::min(c0 + G.bn, G.L);
     if (c0 > qt.e1 - 1) return 0;  // beyond what the last row sees
     if (c1 - 1 < G.lo(qt.r0)) return 0;  // before the first row's window (and every later row's)
-    const auto &sp = *G.spans;
-    const auto &freec = G.free_count(cls);
+    const bs::SpanInfo *sp = G.spans.data();
+    auto freec = [&](int32_t t) { return G.free_count(cls, t); };
 
     // Every row i sees the keys of its class pattern inside [lo(i), e(i)]; both ends grow with i, so
     // the rows of a run together see [lo(first), e(last)] and share [lo(last), e(first)].
@@ -102,13 +100,13 @@ int tile_state(const Geometry &G, const QueryTile &qt, int cls, int32_t n)
         any = true;
     } else {
         // a text row at or after the tile's first key, close enough to see the tile's last key
-        const int32_t t = G.next_text[std::max(qt.r0, c0)];
+        const int32_t t = G.next_text(std::max(qt.r0, c0));
         if (t < qt.r1 && G.lo(t) <= c1 - 1) any = true;
         for (const Segment &s : qt.segs) {
             if (any) break;
             const int32_t lo = std::max(c0, G.lo(s.a)), hi = std::min(c1, s.eb);  // keys the segment's rows may see
             if (hi <= lo) continue;
-            if (freec[hi] - freec[lo] > 0) { any = true; break; }
+            if (freec(hi) - freec(lo) > 0) { any = true; break; }
             if (cls & 2) {
                 int32_t lo2 = std::max(lo, sp[s.g].start), hi2 = std::min(hi, sp[s.g].end);
                 if (hi2 > lo2) { any = true; break; }
@@ -123,15 +121,15 @@ int tile_state(const Geometry &G, const QueryTile &qt, int cls, int32_t n)
     } else if (cls == BS_DENSE || qt.segs.empty()) {
         all = true;
     } else {
-        int32_t nonfree = G.bn - (freec[c1] - freec[c0]);
+        int32_t nonfree = G.bn - (freec(c1) - freec(c0));
         if (nonfree == 0) {
             all = true;
         } else if (!(cls & 2) || qt.segs.size() > 1) {
             all = false;  // a masked image key, or two images that cannot both own it
         } else {
-            const bs_span &own = sp[qt.segs[0].g];
+            const bs::SpanInfo &own = sp[qt.segs[0].g];
             int32_t lo2 = std::max(c0, own.start), hi2 = std::min(c1, own.end);
-            int32_t nonfree_own = (hi2 > lo2) ? (hi2 - lo2) - (freec[hi2] - freec[lo2]) : 0;
+            int32_t nonfree_own = (hi2 > lo2) ? (hi2 - lo2) - (freec(hi2) - freec(lo2)) : 0;
             all = (nonfree_own == nonfree);
         }
     }
@@ -149,9 +147,8 @@ void candidate_tiles(const Geometry &G, const QueryTile &qt, int cls, std::vecto
         return;
     }
     // image-only query tile of a sparse class: tiles with a free key (text / enabled sink) ...
-    const auto &nf = G.next_free(cls);
     for (int32_t pos = 0; pos < qt.e1;) {
-        int32_t j = nf[pos];
+        int32_t j = G.next_free(cls, pos);
         if (j >= qt.e1) break;
         int32_t n = j / G.bn;
         cand.push_back(n);
@@ -160,7 +157,7 @@ void candidate_tiles(const Geometry &G, const QueryTile &qt, int cls, std::vecto
     }
     // ... and tiles overlapping the part of an own image that lies at or before the tile's rows
     if (cls & 2) {
-        const auto &sp = *G.spans;
+        const bs::SpanInfo *sp = G.spans.data();
         for (const Segment &s : qt.segs)
             for (int32_t n = sp[s.g].start / G.bn; n <= (s.eb - 1) / G.bn; ++n) cand.push_back(n);
         std::sort(cand.begin(), cand.end());
@@ -210,7 +207,7 @@ void build_run(const Geometry &G, int cls, const QueryTile &qt, std::vector<int3
         cand.clear();
         const auto &naf = G.next_allfree(cls);
         for (int32_t n = naf[0]; n < n_full_limit; n = naf[n + 1]) cand.push_back(n);
-        const auto &sp = *G.spans;
+        const bs::SpanInfo *sp = G.spans.data();
         for (const Segment &sg : qt.segs)
             for (int32_t n = sp[sg.g].start / G.bn; n <= (sg.eb - 1) / G.bn && n < n_full_limit; ++n) cand.push_back(n);
         for (int32_t n = qt.last_text / G.bn + 1; n <= n_last; ++n) cand.push_back(n);
@@ -262,34 +259,40 @@ void build_run_packed(const Geometry &G, int cls, int32_t g, int32_t a, int32_t 
             run_begin = bg; run_end = en; run_state = st;
         }
     };
-    const auto &sp = *G.spans;
-    const auto &nfs = G.n_free_sink;
+    const bs::SpanInfo &own = G.spans[g];
     if (cls & 2) {
-        const int32_t s0 = sp[g].start;
-        for (int32_t n = s0 / G.bn; n <= (b - 1) / G.bn; ++n) {
-            const int32_t c0 = n * G.bn, c1 = c0 + G.bn;
-            const bool full = !ragged && c0 >= s0 && c1 - 1 <= a && c1 <= G.L;
-            emit(n, n + 1, full ? 2 : 1);
-        }
+        const int32_t s0 = own.start, n0 = s0 / G.bn, n1 = (b - 1) / G.bn + 1;
+        // FULL: tiles inside the image, visible to the first row
+        const int32_t f0 = std::min(n1, (s0 + G.bn - 1) / G.bn);
+        const int32_t f1 = ragged ? f0 : std::max(f0, std::min((a + 1) / G.bn, G.L / G.bn));
+        emit(n0, f0, 1);
+        emit(f0, f1, 2);
+        emit(f1, n1, 1);
     }
-    const int32_t fb_min = nfs[a + 1], fb_max = nfs[b];   // visible free keys of the first / last row
-    const int32_t own_lo = nfs[sp[g].start], own_hi = nfs[sp[g].end];
+    const int32_t fb_min = G.n_free(a + 1), fb_max = G.n_free(b);   // visible free keys of the first / last row
     const int32_t c_end = (fb_max + G.bn - 1) / G.bn;
-    for (int32_t c = 0; c < c_end; ++c) {
-        const int32_t s0 = c * G.bn, s1 = s0 + G.bn, vis = std::min(s1, fb_max);   // slots [s0, vis) are visible to the last row
-        const bool below_all = !ragged && s1 <= fb_min;   // every slot visible to every row (implies a complete tile)
-        int st;
-        if (cls == BS_SINK) {
-            st = below_all ? 2 : 1;
-        } else if (cls == BS_INTRA) {
-            const int32_t t = G.ctext[vis] - G.ctext[s0];
-            st = t == 0 ? 0 : ((below_all && t == G.bn) ? 2 : 1);
-        } else {
-            const int32_t lo = std::max(s0, own_lo), hi = std::min(vis, own_hi);
-            const int32_t own = hi > lo ? hi - lo : 0;
-            st = own == vis - s0 ? 0 : ((below_all && own == 0) ? 2 : 1);
+    const int32_t c_all = ragged ? 0 : fb_min / G.bn;               // tiles before it: every slot visible to every row
+    if (cls == BS_SINK) {
+        emit(G.N0, G.N0 + c_all, 2);
+        emit(G.N0 + c_all, G.N0 + c_end, 1);
+    } else if (cls == BS_INTRA) {
+        for (const TileRange &r : G.ctext_runs) {
+            if (r.begin >= c_all) break;
+            emit(G.N0 + r.begin, G.N0 + std::min(r.end(), c_all), r.full() ? 2 : 1);
         }
-        emit(G.N + c, G.N + c + 1, st);
+        for (int32_t c = c_all; c < c_end; ++c) {   // (the free keys before row b's bound: the text before it counts)
+            const int32_t text = ((c + 1) * G.bn <= fb_max ? G.ctext[c + 1] : G.n_text(b)) - G.ctext[c];
+            emit(G.N0 + c, G.N0 + c + 1, text > 0 ? 1 : 0);
+        }
+    } else {
+        const int32_t own_lo = own.free_before, own_hi = own_lo + G.sinks_in(g, own.end - own.start);
+        const int32_t c_own = std::min(c_all, own_lo / G.bn);
+        emit(G.N0, G.N0 + c_own, 2);
+        for (int32_t c = c_own; c < c_end; ++c) {
+            const int32_t s0 = c * G.bn, vis = std::min(s0 + G.bn, fb_max);   // slots [s0, vis) are visible to the last row
+            const int32_t own_slots = std::max(0, std::min(vis, own_hi) - std::max(s0, own_lo));
+            emit(G.N0 + c, G.N0 + c + 1, own_slots == vis - s0 ? 0 : (c < c_all && own_slots == 0 ? 2 : 1));
+        }
     }
     flush();
 }
@@ -327,7 +330,7 @@ void combine_runs(const std::vector<TileRange> &a, const std::vector<TileRange> 
     }
 }
 
-void build_class(const Geometry &G, int cls, const std::vector<int32_t> &row_order, ClassLists &out)
+void build_class(const Geometry &G, int cls, ClassLists &out)
 {
     out.row_ptr.assign(G.M + 1, 0);
     out.row_tiles.assign(G.M, 0);
@@ -335,18 +338,14 @@ void build_class(const Geometry &G, int cls, const std::vector<int32_t> &row_ord
     QueryTile qt;
     std::vector<int32_t> cand;
     std::vector<TileRange> run, seg_run, acc, tmp;
+    std::vector<std::pair<int32_t, int32_t>> runs;
     for (int32_t m = 0; m < G.M; ++m) {
         // the tile's rows as runs of consecutive positions (one run in the natural order)
-        const int32_t *rows = row_order.data() + (size_t)m * G.bm;
-        int32_t n_rows = 0;
-        while (n_rows < G.bm && rows[n_rows] >= 0) ++n_rows;
-        const bool ragged = n_rows < G.bm;
+        const bool ragged = G.tile_runs(m, runs) < G.bm;
         acc.clear();
         bool first = true;
-        for (int32_t i = 0; i < n_rows;) {
-            int32_t j = i + 1;
-            while (j < n_rows && rows[j] == rows[j - 1] + 1) ++j;
-            describe_query_rows(G, rows[i], rows[j - 1] + 1, ragged, qt);
+        for (const auto &rr : runs) {
+            describe_query_rows(G, rr.first, rr.second, ragged, qt);
             if (G.packed && cls != BS_DENSE && (cls != BS_INTRA || G.intra_compact) && qt.last_text < 0 && !qt.segs.empty()) {
                 // image rows of a sparse class: one packed list per image the run touches
                 // (two images can be adjacent without a text token between them)
@@ -369,7 +368,6 @@ void build_class(const Geometry &G, int cls, const std::vector<int32_t> &row_ord
                 combine_runs(acc, run, tmp);
                 acc.swap(tmp);
             }
-            i = j;
         }
         for (const TileRange &r : acc) {
             const int32_t len = r.end() - r.begin;
@@ -383,25 +381,25 @@ void build_class(const Geometry &G, int cls, const std::vector<int32_t> &row_ord
 }
 
 // Allowed pairs and empty rows per class, from prefix counts (no pair enumeration).
-void count_pairs(const Geometry &G, const std::vector<uint32_t> &code, int32_t q_begin, ClassLists lists[4])
+void count_pairs(const PromptGeometry &G, ClassLists lists[4])
 {
-    const auto &sp = *G.spans;
     int64_t pairs[4] = {0, 0, 0, 0}, empty[4] = {0, 0, 0, 0};
-    size_t g = 0;
-    for (int32_t i = q_begin; i < G.L; ++i) {
-        const int32_t lo = G.lo(i);   // first key position the row may see
-        if (code[i] & bs::kCodeText) {
+    for (int32_t i = G.q_begin, g = G.span_at(i); i < G.L; ++i) {
+        while (g < G.n_spans && G.spans[g].end <= i) ++g;
+        const bool image = g < G.n_spans && G.spans[g].start <= i;
+        const int32_t lo = G.window > 0 ? G.first_visible(i) : 0;   // first key position the row may see
+        if (!image) {
             for (int c = 0; c < 4; ++c) pairs[c] += i + 1 - lo;
             continue;
         }
-        while (sp[g].end <= i) ++g;
-        const int32_t e = G.bidir ? sp[g].end - 1 : i;   // last key position the row may see
-        const int32_t s0 = std::max(sp[g].start, lo);    // first own-image key it may see
-        const int64_t text = G.n_text[e + 1] - G.n_text[lo];
-        const int64_t sink_img = G.n_free_sink[e + 1] - G.n_free_sink[lo] - text;  // image tokens that are sinks, in [lo, e]
+        const bs::SpanInfo &sp = G.spans[g];
+        const int32_t e = G.bidir ? sp.end - 1 : i;   // last key position the row may see
+        const int32_t s0 = std::max(sp.start, lo);    // first own-image key it may see
+        const int64_t text = sp.text_before - G.n_text(lo);
+        const int64_t free = sp.free_before + G.sinks_in(g, e + 1 - sp.start) - G.n_free(lo);   // text or sink, in [lo, e]
         const int64_t own = e - s0 + 1;
-        const int64_t own_sink = (G.n_free_sink[e + 1] - G.n_free_sink[s0]) - (G.n_text[e + 1] - G.n_text[s0]);
-        const int64_t row[4] = {e + 1 - lo, text + sink_img, text + own, text + sink_img + own - own_sink};
+        const int64_t own_sink = G.sinks_in(g, e + 1 - sp.start) - G.sinks_in(g, s0 - sp.start);
+        const int64_t row[4] = {e + 1 - lo, free, text + own, free + own - own_sink};
         for (int c = 0; c < 4; ++c) {
             pairs[c] += row[c];
             if (row[c] == 0) ++empty[c];
@@ -470,7 +468,7 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     if (!out || !head_class || n_q_heads <= 0 || seq_len <= 0 || n_spans < 0) return BS_EINVAL;
     if (n_spans > 0 && !spans) return BS_EINVAL;
     if (sink_len < 0 || sink_len > seq_len || block_m <= 0 || block_n <= 0) return BS_EINVAL;
-    if ((int64_t)n_spans >= (int64_t)bs::kCodeImgMask) return BS_EINVAL;
+    if ((int64_t)n_spans >= (int64_t)bs::kMaxSpans) return BS_EINVAL;
     for (int32_t h = 0; h < n_q_heads; ++h)
         if (head_class[h] > 3) return BS_EINVAL;
     if (!spans_valid(spans, n_spans, seq_len)) return BS_EINVAL;
@@ -479,183 +477,104 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     try {
         tm = new bs_tilemap();
         const int32_t L = seq_len;
-        tm->L = L; tm->bm = block_m; tm->bn = block_n; tm->sink_len = sink_len;
+        tm->L = L; tm->bm = block_m; tm->bn = block_n;
         tm->q_begin = q_begin;
         tm->N0 = tm->N = (L + block_n - 1) / block_n;
         tm->n_q_heads = n_q_heads;
-        tm->spans.assign(spans, spans + n_spans);
         tm->head_class.assign(head_class, head_class + n_q_heads);
-
-        // per-token codes
-        tm->code.assign(L, bs::kCodeText);
-        for (int32_t t = 0; t < sink_len; ++t) tm->code[t] |= bs::kCodeSink;
-        for (int32_t g = 0; g < n_spans; ++g)
-            for (int32_t t = spans[g].start; t < spans[g].end; ++t) {
-                uint32_t c = (uint32_t)(g + 1);
-                if (t - spans[g].start < spans[g].sink || t < sink_len) c |= bs::kCodeSink;
-                tm->code[t] = c;
-            }
-        for (int32_t g = 0; g < n_spans; ++g)   // sinks at fixed offsets inside every image
-            for (int32_t o = 0; o < n_sink_offsets; ++o)
-                if (sink_offsets[o] < spans[g].end - spans[g].start) tm->code[spans[g].start + sink_offsets[o]] |= bs::kCodeSink;
         tm->bidir = (flags & BS_MAP_BIDIR_IMAGES) != 0 && n_spans > 0;
+        tm->window = window;
+        bs::PromptGeometry &P = tm->geo;
+        P.init(spans, n_spans, L, sink_len, sink_offsets, n_sink_offsets);
+        P.bm = block_m; P.bn = block_n; P.N0 = tm->N0;
+        P.bidir = tm->bidir; P.window = window; P.q_begin = q_begin;
 
         // Key tiles: the prompt's keys in position order, then (packed) compact tiles with the
         // free keys -- text keys and sink keys, what an image query of a sparse class may see
         // outside its own image -- in position order.  The paper's kernel permutes K / V so that
         // these keys are contiguous (App. kernel, "Attention Sink Subroutine"); here they are a
         // second copy, because text queries and Dense heads keep walking the original order.
-        std::vector<int32_t> free_pos;
-        if (flags & BS_MAP_PACK_KEYS) {
-            bool any_image = false;
-            for (int32_t t = 0; t < L; ++t) {
-                if (tm->code[t] & (bs::kCodeText | bs::kCodeSink)) free_pos.push_back(t);
-                if (!(tm->code[t] & bs::kCodeText)) any_image = true;
-            }
-            if (any_image && !free_pos.empty() && free_pos.size() < (size_t)L) {
-                tm->packed = true;
-                tm->N = tm->N0 + (int32_t)((free_pos.size() + block_n - 1) / block_n);
-            }
-        }
-        tm->key_order.assign((size_t)tm->N * block_n, -1);
-        for (int32_t t = 0; t < L; ++t) tm->key_order[t] = t;
-        if (tm->packed) std::copy(free_pos.begin(), free_pos.end(), tm->key_order.begin() + (size_t)tm->N0 * block_n);
-
-        // per-key-tile bit masks for the kernel's 64-wide element predicate
-        if (block_n <= 64) {
-            tm->text_bits.assign(tm->N, 0);
-            tm->sink_bits.assign(tm->N, 0);
-            for (size_t slot = 0; slot < tm->key_order.size(); ++slot) {
-                const int32_t t = tm->key_order[slot];
-                if (t < 0) continue;
-                const uint64_t bit = 1ull << (slot % block_n);
-                if (tm->code[t] & bs::kCodeText) tm->text_bits[slot / block_n] |= bit;
-                if (tm->code[t] & bs::kCodeSink) tm->sink_bits[slot / block_n] |= bit;
-            }
+        const int32_t n_free = P.n_free(L);
+        if ((flags & BS_MAP_PACK_KEYS) && n_spans > 0 && n_free > 0 && n_free < L) {
+            tm->packed = true;
+            tm->N = tm->N0 + (n_free + block_n - 1) / block_n;
         }
 
         // Order of the query rows.  Natural: tile m holds rows m*bm ... .  Regrouped: the image
         // rows first, then the text rows, each group in position order and padded to whole
-        // tiles (-1).  A text row attends to every earlier token, so a tile that holds even one
+        // tiles.  A text row attends to every earlier token, so a tile that holds even one
         // walks every causal key tile for every class; gathered into tiles of their own, the
         // text rows stop costing the image rows of the sparse classes their skipped tiles.
         {
-            const int64_t bm = block_m;
-            const int64_t R = L - q_begin;                 // the query rows are positions q_begin .. L - 1
-            std::vector<int32_t> img_rows, txt_rows;
-            if (flags & BS_MAP_REGROUP_ROWS) {
-                for (int32_t t = q_begin; t < L; ++t) ((tm->code[t] & bs::kCodeText) ? txt_rows : img_rows).push_back(t);
-            }
-            if (img_rows.empty() || txt_rows.empty()) {   // natural order (also: nothing to separate)
-                tm->M = (int32_t)((R + bm - 1) / bm);
-                tm->row_order.assign((size_t)tm->M * bm, -1);
-                for (int64_t r = 0; r < R; ++r) tm->row_order[r] = (int32_t)(q_begin + r);
+            const int32_t n_txt = P.n_text(L) - P.n_text(q_begin), n_img = L - q_begin - n_txt;
+            if ((flags & BS_MAP_REGROUP_ROWS) && n_txt > 0 && n_img > 0) {   // else nothing to separate
+                P.regrouped = tm->regrouped = true;
+                P.n_img_rows = n_img;
+                P.m_img = (n_img + block_m - 1) / block_m;
+                tm->M = P.m_img + (n_txt + block_m - 1) / block_m;
             } else {
-                const int64_t m_img = ((int64_t)img_rows.size() + bm - 1) / bm, m_txt = ((int64_t)txt_rows.size() + bm - 1) / bm;
-                tm->M = (int32_t)(m_img + m_txt);
-                tm->row_order.assign((size_t)tm->M * bm, -1);
-                std::copy(img_rows.begin(), img_rows.end(), tm->row_order.begin());
-                std::copy(txt_rows.begin(), txt_rows.end(), tm->row_order.begin() + m_img * bm);
-                tm->regrouped = true;
+                tm->M = (L - q_begin + block_m - 1) / block_m;
             }
         }
 
-        Geometry G;
-        G.L = L; G.bm = block_m; G.bn = block_n; G.M = tm->M; G.N = tm->N0; G.spans = &tm->spans;
-        G.bidir = tm->bidir;
-        G.window = tm->window = window;
-        if (window > 0) {
-            G.first_visible.resize(L);
-            for (int32_t t = 0; t < L; ++t) G.first_visible[t] = std::max(0, t - window + 1);
-            if (tm->bidir)
-                for (int32_t g = 0; g < n_spans; ++g)
-                    for (int32_t t = spans[g].start; t < spans[g].end; ++t)
-                        G.first_visible[t] = std::min(G.first_visible[t], spans[g].start);
-        }
-        G.n_text.assign(L + 1, 0);
-        G.n_free_sink.assign(L + 1, 0);
-        G.last_text.assign(L, -1);
-        G.next_text.assign(L + 1, L);
-        G.next_free_sink.assign(L + 1, L);
-        for (int32_t t = 0; t < L; ++t) {
-            const bool text = tm->code[t] & bs::kCodeText;
-            const bool fs = text || (tm->code[t] & bs::kCodeSink);
-            G.n_text[t + 1] = G.n_text[t] + text;
-            G.n_free_sink[t + 1] = G.n_free_sink[t] + fs;
-            G.last_text[t] = text ? t : (t ? G.last_text[t - 1] : -1);
-        }
-        for (int32_t t = L - 1; t >= 0; --t) {
-            const bool text = tm->code[t] & bs::kCodeText;
-            const bool fs = text || (tm->code[t] & bs::kCodeSink);
-            G.next_text[t] = text ? t : G.next_text[t + 1];
-            G.next_free_sink[t] = fs ? t : G.next_free_sink[t + 1];
-        }
-
-        for (int b = 0; b < 2; ++b) {
-            const std::vector<int32_t> &fc = b ? G.n_free_sink : G.n_text;
-            G.next_allfree_tile[b].assign(tm->N0 + 1, tm->N0);
-            for (int32_t n = tm->N0 - 1; n >= 0; --n) {
-                const int32_t c0 = n * block_n, c1 = std::min(c0 + block_n, L);
-                const bool allfree = (c1 - c0 == block_n) && (fc[c1] - fc[c0] == block_n);
-                G.next_allfree_tile[b][n] = allfree ? n : G.next_allfree_tile[b][n + 1];
-            }
-        }
-        if (tm->packed) {
-            G.packed = true;
-            G.n_free = (int32_t)free_pos.size();
-            G.Nc = tm->N - tm->N0;
-            G.ctext.assign(free_pos.size() + 1, 0);
-            for (size_t s2 = 0; s2 < free_pos.size(); ++s2)
-                G.ctext[s2 + 1] = G.ctext[s2] + ((tm->code[free_pos[s2]] & bs::kCodeText) ? 1 : 0);
-            // what the kernel needs per row / per image: free keys before a position, and the
-            // compact slots of the free keys that lie inside each image
-            tm->free_before = G.n_free_sink;
-            tm->span_free_range.assign(2 * ((size_t)n_spans + 1), 0);
-            for (int32_t g = 0; g < n_spans; ++g) {
-                tm->span_free_range[2 * (g + 1)] = G.n_free_sink[spans[g].start];
-                tm->span_free_range[2 * (g + 1) + 1] = G.n_free_sink[spans[g].end];
-            }
-        }
+        P.M = tm->M;
+        Geometry G(P);
         bool intra_close_call = false;
         if (tm->packed) {
+            G.packed = true;
+            G.Nc = tm->N - tm->N0;
+            // text keys before every compact tile
+            G.ctext.assign(G.Nc + 1, 0);
+            for (int32_t c = 0; c < G.Nc; ++c) G.ctext[c] = P.n_text(P.free_position(c * block_n));
+            G.ctext[G.Nc] = P.n_text(L);
+            for (int32_t c = 0; c < G.Nc; ++c) {
+                const int32_t text = G.ctext[c + 1] - G.ctext[c];
+                const bool full = text == block_n;
+                if (text == 0) continue;
+                if (!G.ctext_runs.empty() && G.ctext_runs.back().end() == c && G.ctext_runs.back().full() == full)
+                    G.ctext_runs.back().end_state = ((c + 1) << 1) | (int32_t)full;
+                else
+                    G.ctext_runs.push_back({c, ((c + 1) << 1) | (int32_t)full});
+            }
             // Intra-Image rows need the text keys only.  Among the compact tiles they are mixed
             // with the sink keys; where text is rare (a few long images) the prompt's own tiles
             // hold it in fewer tiles.  Both lists are exact, so the choice is a matter of cost
             // only: count, for the last row of every image, the tiles with a text key either
             // way (prefix counts over the two tile spaces) and take the smaller total; a close
             // call is settled below by building both.
-            std::vector<int32_t> prompt_tiles(tm->N0 + 1, 0), compact_tiles(G.Nc + 1, 0);
-            for (int32_t n = 0; n < tm->N0; ++n) {
-                const int32_t c0 = n * block_n, c1 = std::min(c0 + block_n, L);
-                prompt_tiles[n + 1] = prompt_tiles[n] + (G.n_text[c1] - G.n_text[c0] > 0);
-            }
-            for (int32_t c = 0; c < G.Nc; ++c) {
-                const int32_t s0 = c * block_n, s1 = std::min(s0 + block_n, G.n_free);
-                compact_tiles[c + 1] = compact_tiles[c] + (G.ctext[s1] - G.ctext[s0] > 0);
-            }
+            std::vector<int32_t> compact_tiles(G.Nc + 1, 0);
+            for (int32_t c = 0; c < G.Nc; ++c) compact_tiles[c + 1] = compact_tiles[c] + (G.ctext[c + 1] > G.ctext[c]);
             int64_t cost_prompt = 0, cost_compact = 0;
+            int32_t text_tiles = 0, counted = 0, text_from = 0;   // prompt tiles with a text key before tile `counted`
             for (int32_t g = 0; g < n_spans; ++g) {
-                const int64_t rows = spans[g].end - spans[g].start;
-                cost_prompt += rows * prompt_tiles[(spans[g].end - 1) / block_n + 1];
-                cost_compact += rows * compact_tiles[(G.n_free_sink[spans[g].end] + block_n - 1) / block_n];
+                const bs::SpanInfo &s = P.spans[g];
+                if (s.start > text_from) {                         // the text before image g
+                    const int32_t n0 = std::max(counted, text_from / block_n), n1 = (s.start - 1) / block_n + 1;
+                    text_tiles += std::max(0, n1 - n0);
+                    counted = std::max(counted, n1);
+                }
+                text_from = s.end;
+                // (the tile of the image's last token counts if it holds a text key behind the image)
+                const int32_t n_last = (s.end - 1) / block_n;
+                const bool tail = n_last >= counted && P.n_text(std::min((n_last + 1) * block_n, L)) > P.n_text(s.end);
+                const int64_t rows = s.end - s.start;
+                cost_prompt += rows * (text_tiles + tail);
+                cost_compact += rows * compact_tiles[(s.free_before + P.sinks_in(g, s.end - s.start) + block_n - 1) / block_n];
             }
             G.intra_compact = tm->intra_compact = cost_compact < cost_prompt;
             intra_close_call = cost_compact * 4 >= cost_prompt * 3 && cost_prompt * 4 >= cost_compact * 3;
         }
-        for (int c = 0; c < 4; ++c) build_class(G, c, tm->row_order, tm->cls[c]);
+        for (int c = 0; c < 4; ++c) build_class(G, c, tm->cls[c]);
         if (intra_close_call) {
             // the estimate is within a quarter: build the other variant as well and keep the shorter list
             ClassLists alt;
             G.intra_compact = !G.intra_compact;
-            build_class(G, BS_INTRA, tm->row_order, alt);
+            build_class(G, BS_INTRA, alt);
             if (alt.visited < tm->cls[BS_INTRA].visited) {
                 tm->cls[BS_INTRA] = std::move(alt);
                 tm->intra_compact = G.intra_compact;
             }
-            G.intra_compact = tm->intra_compact;
         }
-        count_pairs(G, tm->code, q_begin, tm->cls);
-
     } catch (const std::bad_alloc &) {
         delete tm;
         return BS_ENOMEM;
@@ -664,19 +583,110 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     return BS_OK;
 }
 
+void bs::PromptGeometry::init(const bs_span *sp, int32_t n, int32_t seq_len, int32_t sink_prefix, const int32_t *offs, int32_t n_offs)
+{
+    L = seq_len;
+    n_spans = n;
+    sink_len = sink_prefix;
+    offsets.assign(offs, offs + n_offs);
+    std::sort(offsets.begin(), offsets.end());
+    offsets.erase(std::unique(offsets.begin(), offsets.end()), offsets.end());
+    spans.resize((size_t)n + 1);
+    int32_t text = 0, free = 0, pos = 0, last = -1;   // of everything before `pos`
+    for (int32_t g = 0; g < n; ++g) {
+        if (sp[g].start > pos) last = sp[g].start - 1;
+        text += sp[g].start - pos;
+        free += sp[g].start - pos;
+        const int32_t len = sp[g].end - sp[g].start;
+        spans[g] = {sp[g].start, sp[g].end, std::max(sp[g].sink, std::min(len, std::max(0, sink_len - sp[g].start))), text, free, last, L, 0};
+        free += sinks_in(g, len);
+        pos = sp[g].end;
+    }
+    if (L > pos) last = L - 1;
+    spans[n] = {L, INT32_MAX, 0, text + L - pos, free + L - pos, last, L, 0};   // sentinel behind the last token
+    for (int32_t g = n - 1; g >= 0; --g)
+        spans[g].next_text = spans[g].end < spans[g + 1].start ? spans[g].end : (g + 1 < n ? spans[g + 1].next_text : L);
+    block_first.resize((size_t)(L >> 6) + 1);
+    for (int32_t b = 0, g = 0; b < (int32_t)block_first.size(); ++b) {
+        while (g < n && spans[g].end <= b << 6) ++g;
+        block_first[b] = g;
+    }
+}
+
+int32_t bs::PromptGeometry::next_free(int cls, int32_t t) const
+{
+    if (!(cls & 1)) return next_text(t);
+    for (int32_t g = span_at(t); g < n_spans; ++g) {
+        const SpanInfo &s = spans[g];
+        if (t < s.start) return t;                      // text
+        const int32_t o = t - s.start;
+        if (o < s.prefix) return t;
+        const auto it = std::lower_bound(offsets.begin(), offsets.end(), o);
+        if (it != offsets.end() && *it < s.end - s.start) return s.start + *it;
+        t = s.end;
+    }
+    return t;   // text behind the last image, or L
+}
+
+int32_t bs::PromptGeometry::free_position(int32_t slot) const
+{
+    // the last image that begins at or before the slot, then its sinks and the text behind it
+    const auto it = std::upper_bound(spans.begin(), spans.begin() + n_spans, slot, [](int32_t s, const SpanInfo &x) { return s < x.free_before; });
+    if (it == spans.begin()) return slot;
+    const SpanInfo &s = *(it - 1);
+    const int32_t r = slot - s.free_before, sinks = sinks_in((int32_t)(it - 1 - spans.begin()), s.end - s.start);
+    if (r >= sinks) return s.end + (r - sinks);
+    return s.start + (r < s.prefix ? r : offsets[offsets_below(s.prefix) + (r - s.prefix)]);
+}
+
+int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, int32_t>> &runs) const
+{
+    runs.clear();
+    if (!regrouped) {
+        const int64_t r0 = q_begin + (int64_t)m * bm, r1 = std::min<int64_t>(r0 + bm, L);
+        runs.push_back({(int32_t)r0, (int32_t)r1});
+        return (int32_t)(r1 - r0);
+    }
+    auto add = [&](int32_t a, int32_t b) {
+        if (b <= a) return;
+        if (!runs.empty() && runs.back().second == a) runs.back().second = b;
+        else runs.push_back({a, b});
+    };
+    const int32_t text0 = n_text(q_begin), img0 = q_begin - text0;   // text / image tokens before the first row
+    if (m < m_img) {   // image rows j0 .. j1 - 1 of all image tokens
+        const int32_t j0 = img0 + m * bm, j1 = img0 + std::min((m + 1) * bm, n_img_rows);
+        auto it = std::upper_bound(spans.begin(), spans.begin() + n_spans, j0, [](int32_t j, const SpanInfo &s) { return j < s.start - s.text_before; }) - 1;
+        for (int32_t j = j0; j < j1; ++it) {
+            const int32_t a = it->start + (j - (it->start - it->text_before)), b = std::min(it->end, a + (j1 - j));
+            add(a, b);
+            j += b - a;
+        }
+        return j1 - j0;
+    }
+    const int32_t t0 = text0 + (m - m_img) * bm, t1 = std::min(t0 + bm, spans[n_spans].text_before);
+    auto it = std::upper_bound(spans.begin(), spans.end(), t0, [](int32_t t, const SpanInfo &s) { return t < s.text_before; });
+    for (int32_t t = t0; t < t1; ++it) {   // the text before *it
+        if (it->text_before <= t) continue;
+        const int32_t a = it->start - (it->text_before - t), b = std::min(it->start, a + (t1 - t));
+        add(a, b);
+        t += b - a;
+    }
+    return t1 - t0;
+}
+
 void bs::row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, int32_t *img_lo, int32_t *img_hi)
 {
     *first = tm->window > 0 ? std::max(0, i - tm->window + 1) : 0;
     *last = i;
     *img_lo = *img_hi = 0;
-    const auto &sp = tm->spans;
-    const auto it = std::upper_bound(sp.begin(), sp.end(), i, [](int32_t t, const bs_span &s) { return t < s.end; });
-    if (it == sp.end() || i < it->start) return;
-    *img_lo = it->start;
-    *img_hi = it->end;
+    const PromptGeometry &P = tm->geo;
+    const int32_t g = P.span_at(i);
+    if (g >= P.n_spans || i < P.spans[g].start) return;
+    *img_lo = P.spans[g].start;
+    *img_hi = P.spans[g].end;
     if (tm->bidir) {   // the whole own image, also beyond a window
-        *last = it->end - 1;
-        *first = std::min(*first, it->start);
+        *last = P.spans[g].end - 1;
+        *first = std::min(*first, P.spans[g].start);
     }
 }
 
@@ -1126,7 +1136,18 @@ extern "C" int bs_tilemap_dims(const bs_tilemap *tm, int32_t *seq_len, int32_t *
 extern "C" int bs_tilemap_row_order(const bs_tilemap *tm, int32_t *rows)
 {
     if (!tm || !rows) return BS_EINVAL;
-    std::memcpy(rows, tm->row_order.data(), tm->row_order.size() * sizeof(int32_t));
+    std::vector<std::pair<int32_t, int32_t>> runs;
+    try {
+        for (int32_t m = 0; m < tm->M; ++m) {
+            int32_t *r = rows + (size_t)m * tm->bm, *end = r + tm->bm;
+            tm->geo.tile_runs(m, runs);
+            for (const auto &x : runs)
+                for (int32_t t = x.first; t < x.second; ++t) *r++ = t;
+            std::fill(r, end, -1);
+        }
+    } catch (const std::bad_alloc &) {
+        return BS_ENOMEM;
+    }
     return BS_OK;
 }
 
@@ -1142,7 +1163,12 @@ extern "C" int bs_tilemap_layout(const bs_tilemap *tm, int32_t *regrouped, int32
 extern "C" int bs_tilemap_key_order(const bs_tilemap *tm, int32_t *keys, int32_t *n_prompt_tiles)
 {
     if (!tm) return BS_EINVAL;
-    if (keys) std::memcpy(keys, tm->key_order.data(), tm->key_order.size() * sizeof(int32_t));
+    if (keys) {
+        for (int32_t s = 0; s < tm->N0 * tm->bn; ++s) keys[s] = s < tm->L ? s : -1;
+        const int32_t n_free = tm->geo.n_free(tm->L);
+        for (int32_t s = 0; s < (tm->N - tm->N0) * tm->bn; ++s)
+            keys[(size_t)tm->N0 * tm->bn + s] = s < n_free ? tm->geo.free_position(s) : -1;
+    }
     if (n_prompt_tiles) *n_prompt_tiles = tm->N0;
     return BS_OK;
 }
@@ -1171,6 +1197,11 @@ extern "C" int bs_tilemap_stats(const bs_tilemap *tm, int32_t cls, int64_t *visi
 {
     if (!tm || cls < 0 || cls > 3) return BS_EINVAL;
     const ClassLists &cl = tm->cls[cls];
+    if (allowed_pairs || empty_rows) {   // counted when first asked for; the lists do not need them
+        std::lock_guard<std::mutex> lock(tm->count_mutex);
+        if (!tm->counted) count_pairs(tm->geo, tm->cls);
+        tm->counted = true;
+    }
     if (visited) *visited = cl.visited;
     if (full) *full = cl.full;
     if (partial) *partial = cl.partial;

@@ -1,17 +1,98 @@
 // Internal layout of bs_tilemap, shared by the host builder and the HIP launcher.
 #pragma once
 #include <cstdint>
+#include <mutex>
+#include <utility>
 #include <vector>
 
 #include "blindsight.h"
 
 namespace bs {
 
-// Per-token code consumed by the kernel's element predicate:
-//   bits 0..29  imgid (0 = text), bit 30 = sink key, bit 31 = text key.
-constexpr uint32_t kCodeImgMask = 0x3fffffffu;
-constexpr uint32_t kCodeSink = 1u << 30;
-constexpr uint32_t kCodeText = 1u << 31;
+constexpr int32_t kMaxSpans = 0x3fffffff;
+
+// One image span and the prompt up to it.
+struct SpanInfo {
+    int32_t start, end;
+    int32_t prefix;        // leading sink tokens: the span's own sink count, or the prompt's sink prefix if that reaches further
+    int32_t text_before;   // text tokens at positions < start
+    int32_t free_before;   // text or sink tokens at positions < start
+    int32_t last_text;     // last text position < start, or -1
+    int32_t next_text;     // first text position >= end, or L
+    int32_t pad;
+};
+
+// The prompt as its span table: everything the builders, the introspection calls and the device copy need is a closed
+// form of it, so no array over the tokens exists on the host.
+struct PromptGeometry {
+    int32_t L = 0, bm = 0, bn = 0, M = 0, N0 = 0, n_spans = 0, sink_len = 0, q_begin = 0, window = 0;
+    bool bidir = false;                 // tokens of one image also see the later tokens of that image
+    bool regrouped = false;             // query rows: image rows first, then text rows
+    int32_t n_img_rows = 0, m_img = 0;  // regrouped: image rows and the tiles that hold them
+    std::vector<SpanInfo> spans;        // n_spans + 1: a sentinel that starts at L
+    std::vector<int32_t> offsets;       // sorted in-image offsets that are sinks in every image
+    std::vector<int32_t> block_first;   // first span that ends behind position 64 b
+
+    void init(const bs_span *sp, int32_t n, int32_t seq_len, int32_t sink_prefix, const int32_t *offs, int32_t n_offs);
+    // first span with end > t (n_spans if none), 0 <= t <= L
+    int32_t span_at(int32_t t) const
+    {
+        int32_t g = block_first[t >> 6];
+        while (g < n_spans && spans[g].end <= t) ++g;
+        return g;
+    }
+    int32_t offsets_below(int32_t x) const
+    {
+        int32_t i = 0;
+        if (!offsets.empty() && offsets.back() < x) return (int32_t)offsets.size();
+        for (int32_t n = (int32_t)offsets.size(); n > 0;) {   // lower bound
+            const int32_t half = n / 2;
+            if (offsets[i + half] < x) { i += half + 1; n -= half + 1; } else n = half;
+        }
+        return i;
+    }
+    // sink tokens among the first x of image g
+    int32_t sinks_in(int32_t g, int32_t x) const
+    {
+        const int32_t p = x < spans[g].prefix ? x : spans[g].prefix;
+        return offsets.empty() ? p : p + offsets_below(x) - offsets_below(p);
+    }
+    // text tokens / text or sink tokens at positions < t
+    int32_t n_text(int32_t t) const
+    {
+        const SpanInfo &s = spans[span_at(t)];
+        return t > s.start ? s.text_before : s.text_before - (s.start - t);
+    }
+    int32_t n_free(int32_t t) const
+    {
+        const int32_t g = span_at(t);
+        const SpanInfo &s = spans[g];
+        return t > s.start ? s.free_before + sinks_in(g, t - s.start) : s.free_before - (s.start - t);
+    }
+    // free keys for a class: text, with the sink bit also sinks
+    int32_t free_count(int cls, int32_t t) const { return (cls & 1) ? n_free(t) : n_text(t); }
+    int32_t last_text(int32_t t) const   // largest text position <= t, or -1 (t < L)
+    {
+        const SpanInfo &s = spans[span_at(t)];
+        return t >= s.start ? s.last_text : t;
+    }
+    int32_t next_text(int32_t t) const   // smallest text position >= t, or L
+    {
+        const SpanInfo &s = spans[span_at(t)];
+        return t >= s.start ? s.next_text : t;
+    }
+    int32_t next_free(int cls, int32_t t) const;       // smallest free position >= t, or L
+    int32_t free_position(int32_t slot) const;         // position of the slot-th free token
+    int32_t first_visible(int32_t i) const             // first position a query at i may see (window > 0)
+    {
+        const int32_t w = i >= window ? i - window + 1 : 0;
+        if (!bidir) return w;
+        const SpanInfo &s = spans[span_at(i)];
+        return i >= s.start && s.start < w ? s.start : w;
+    }
+    // the rows of query tile m as runs [first, second) of positions; returns how many rows
+    int32_t tile_runs(int32_t m, std::vector<std::pair<int32_t, int32_t>> &runs) const;
+};
 
 // Half-open run of key tiles [begin, end) that all share one state.
 struct TileRange {
@@ -84,7 +165,7 @@ void bs_plan_solo(bs_tilemap *tm);
 void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs);
 
 struct bs_tilemap {
-    int32_t L = 0, bm = 0, bn = 0, M = 0, N = 0, n_q_heads = 0, sink_len = 0;
+    int32_t L = 0, bm = 0, bn = 0, M = 0, N = 0, n_q_heads = 0;
     // Key tiles: ids [0, N0) are the prompt's keys in position order; with packed keys, ids
     // [N0, N) are compact tiles holding the free keys (text and sink keys) in position order.
     int32_t N0 = 0;
@@ -93,17 +174,12 @@ struct bs_tilemap {
     int32_t window = 0;                    // > 0: sliding window, keys with i - j >= window are masked
     int32_t q_begin = 0;                   // the query rows are positions q_begin .. L - 1 (q / out hold L - q_begin rows per head)
     bool intra_compact = false;            // packed: Intra-Image rows take their text keys from the compact tiles
-    std::vector<int32_t> key_order;        // N * bn: position of each key-tile slot, -1 = none
-    std::vector<int32_t> free_before;      // packed: L + 1, free keys at positions < t
-    std::vector<int32_t> span_free_range;  // packed: 2 * (G + 1), compact slots [lo, hi) of the free keys inside span g (1-based)
-    std::vector<bs_span> spans;
+    bool regrouped = false;                // the query rows are not in the natural order
+    bs::PromptGeometry geo;
     std::vector<uint8_t> head_class;
-    std::vector<int32_t> row_order;        // M * bm: position of each query-tile row, -1 = no row
-    bool regrouped = false;                // row_order is not the natural order
-    std::vector<uint32_t> code;            // L
-    std::vector<uint64_t> text_bits;       // N: bit b of entry n = key n*bn + b is a text key (bn <= 64 only)
-    std::vector<uint64_t> sink_bits;       // N: same for sink keys
-    bs::ClassLists cls[4];
+    mutable std::mutex count_mutex;        // allowed_pairs, empty_rows of cls: counted when first asked for
+    mutable bool counted = false;
+    mutable bs::ClassLists cls[4];
     uint64_t class_epoch = 1;              // bumped by bs_tilemap_rebind: work units and their device copies are stale
     bs::PairPlan pairs;                    // built on first use for a given gqa_group and class vector
     bs::PairPlan solo;                     // one item per unit; built on first use
