@@ -21,6 +21,7 @@ def hipcc() -> str:
 
 def command(out: str = LIB, extra=()):
     return [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+            "-falign-loops=64",   # the step loops of the attention kernels: d = 64 prompt of 9K tokens 972 -> 963 us a pass
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wall", "-Wno-unused-command-line-argument",
             "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra, *os.environ.get("BS_EXTRA_HIPCC_FLAGS", "").split(),

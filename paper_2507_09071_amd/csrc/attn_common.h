@@ -99,6 +99,17 @@ __device__ inline uint64_t allowed_keys(const QueryView &qv, int cls, uint64_t t
     return base & ~excl & bits_below(min(max(qv.free_bound - s0, 0), 64));
 }
 
+// A load from memory that no kernel in flight writes, at a wave-uniform address: through the scalar cache, whatever the
+// compiler can prove (a vector load is waited for together with the LDS-direct loads in flight).
+template <typename T, typename U>
+__device__ inline T scalar_load(const U *p)
+{
+    static_assert(sizeof(T) == sizeof(U), "");
+    return *(const __attribute__((address_space(4))) T *)(uintptr_t)p;
+}
+typedef int intx2 __attribute__((ext_vector_type(2)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+
 // Walks the merged key-tile list of a work unit: runs of [begin, end) with a state per item.
 struct PairWalker {
     const int2 *__restrict__ rg;
@@ -106,7 +117,7 @@ struct PairWalker {
     __device__ void load()
     {
         if (p < p_end) {
-            const int2 r = rg[__builtin_amdgcn_readfirstlane(p)];
+            const intx2 r = scalar_load<intx2>(rg + __builtin_amdgcn_readfirstlane(p));
             n = __builtin_amdgcn_readfirstlane(r.x);
             n_end = __builtin_amdgcn_readfirstlane(r.y) >> 4;
             states = __builtin_amdgcn_readfirstlane(r.y) & 15;

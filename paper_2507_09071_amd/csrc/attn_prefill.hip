@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // ---- state of the work unit in progress (a workgroup takes units from its XCD's queue until
     // ---- the queues are empty; see the unit loop below)
-    int head = 0, m = 0, T = 0, n_steps = 1, cls = 0;
+    int head = 0, m = 0, T = 0, cls = 0;
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
     int row = 0;                    // the query position of this lane's row
@@ -323,12 +323,11 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     QueryView qv;
     int list_begin = 0, list_end = 0;
     auto load_unit = [&](int unit) __attribute__((always_inline)) {
-        const int4 it0 = pair_items[2 * unit], it1 = pair_items[2 * unit + 1];
+        const intx4 it0 = scalar_load<intx4>(pair_items + 2 * unit), it1 = scalar_load<intx4>(pair_items + 2 * unit + 1);
         head = __builtin_amdgcn_readfirstlane(grp ? it0.z : it0.x);
         m = __builtin_amdgcn_readfirstlane(grp ? it0.w : it0.y);
         have_item = head >= 0;
         T = __builtin_amdgcn_readfirstlane(it1.z);            // key tiles in the merged list
-        n_steps = T + 1;                                      // the last step only adds P(T-1) V(T-1)
         list_begin = __builtin_amdgcn_readfirstlane(it1.x);
         list_end = __builtin_amdgcn_readfirstlane(it1.y);
         const int hsafe = max(head, 0);
@@ -456,8 +455,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         __builtin_amdgcn_sched_barrier(0);
         w0.next();
         const int nn = min(__builtin_amdgcn_readfirstlane(w0.n), n_k_tiles - 1);
-        tb_cur = map_text_bits[nn];
-        sb_cur = map_sink_bits[nn];
+        tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
+        sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
         __builtin_amdgcn_sched_barrier(0);
     };
     const char *ksrc = nullptr, *vsrc = nullptr;   // tiles of the coming refill
@@ -560,45 +559,63 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DMA_PER_WAVE));
     };
 
-    // Phase Y of step k: mask (PARTIAL tiles), online softmax, rescale O, round P to bf16.
-    auto phase_y = [&](int k) __attribute__((always_inline)) {
-        if (k < T) {
-            // state of the tile for this group's item: 0 skip (only the other item wants the
-            // tile), 1 partial, 2 full.  A skipped tile goes through the row-uniform path with
-            // every row dropped (P = 0, running max and sum unchanged): rare, and one straight
-            // code path keeps the register allocation of the loop simple.
-            const int st = have_item ? w0.state(grp) : 0;
-            float alpha;
-            bool rescale;
-            if (st == 2) {
-                rescale = softmax_pack<0>(s, pf, m_run, l_run, alpha, a.scale_log2e, false);
-            } else {
-                const int nu = __builtin_amdgcn_readfirstlane(w0.n);
-                uint64_t allowed = allowed_keys(qv, cls, tb_cur, sb_cur, nu, a.n_prompt_tiles);
-                if (st == 0) allowed = 0ull;
-                if (__all(allowed == 0ull || allowed == ~0ull)) {
-                    // every query of the wave sees all 64 keys or none (e.g. a text row and an
-                    // image row over keys of another image): no per-score work
-                    rescale = softmax_pack<1>(s, pf, m_run, l_run, alpha, a.scale_log2e, allowed == 0ull);
-                } else {
-                    floatx16 ms[2];
-                    apply_mask_tight(s, ms, allowed, hl);
-                    rescale = softmax_pack<2>(ms, pf, m_run, l_run, alpha, a.scale_log2e, false);
-                }
-            }
-            if (rescale && __any(alpha != 1.f)) {
+    // The last step: O += P(T-1) V(T-1), nothing else.
+    auto phase_last = [&](int S) __attribute__((always_inline)) {
+        vbase = kaddr0 + (kRing + (S == 0 ? kRing - 1 : S - 1)) * TILE;
+        bf16x8 fa[4], fb[4], fc[4];
+        if constexpr (NDB < 4) {
 #pragma unroll
-                for (int db = 0; db < NDB; ++db)
+            for (int i = NDB; i < 4; ++i)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-            }
+                for (int e = 0; e < 8; ++e) { fa[i][e] = (__bf16)0.f; fb[i][e] = (__bf16)0.f; fc[i][e] = (__bf16)0.f; }
+        }
+        auto read_batch = [&](auto tag, bf16x8 (&f)[4]) __attribute__((always_inline)) {
+            read_one(tag, I0{}, f[0]); read_one(tag, I1{}, f[1]);
+            read_one(tag, I2{}, f[2]); read_one(tag, I3{}, f[3]);
+        };
+        auto mul_batch = [&](auto tag, bf16x8 (&f)[4]) __attribute__((always_inline)) {
+            mul_one(tag, I0{}, f[0]); mul_one(tag, I1{}, f[1]);
+            mul_one(tag, I2{}, f[2]); mul_one(tag, I3{}, f[3]);
+        };
+        read_batch(PvBatch<0>{}, fa); read_batch(PvBatch<1>{}, fb); read_batch(PvBatch<2>{}, fc);
+        lds_wait<2 * NDB>(fa); mul_batch(PvBatch<0>{}, fa); read_batch(PvBatch<3>{}, fa);
+        lds_wait<2 * NDB>(fb); mul_batch(PvBatch<1>{}, fb);
+        lds_wait<NDB>(fc); mul_batch(PvBatch<2>{}, fc);
+        lds_wait<0>(fa); mul_batch(PvBatch<3>{}, fa);
+        mfma_drain(o[0], o[1]);
+        if constexpr (NDB > 2) asm volatile("" : "+v"(o[2]), "+v"(o[3]));
+    };
+
+    // Phase Y of a step: mask (PARTIAL tiles), online softmax, rescale O, round P to bf16.
+    auto phase_y = [&]() __attribute__((always_inline)) {
+        // state of the tile for this group's item: 0 skip (only the other item wants the
+        // tile), 1 partial, 2 full.  A skipped tile goes through the row-uniform path with
+        // every row dropped (P = 0, running max and sum unchanged): rare, and one straight
+        // code path keeps the register allocation of the loop simple.
+        const int st = have_item ? w0.state(grp) : 0;
+        float alpha;
+        bool rescale;
+        if (st == 2) {
+            rescale = softmax_pack<0>(s, pf, m_run, l_run, alpha, a.scale_log2e, false);
         } else {
-            // past the last tile: the final phase X adds P(T-1) V(T-1); steps after it (none
-            // today) must add nothing
+            const int nu = __builtin_amdgcn_readfirstlane(w0.n);
+            uint64_t allowed = allowed_keys(qv, cls, tb_cur, sb_cur, nu, a.n_prompt_tiles);
+            if (st == 0) allowed = 0ull;
+            if (__all(allowed == 0ull || allowed == ~0ull)) {
+                // every query of the wave sees all 64 keys or none (e.g. a text row and an
+                // image row over keys of another image): no per-score work
+                rescale = softmax_pack<1>(s, pf, m_run, l_run, alpha, a.scale_log2e, allowed == 0ull);
+            } else {
+                floatx16 ms[2];
+                apply_mask_tight(s, ms, allowed, hl);
+                rescale = softmax_pack<2>(ms, pf, m_run, l_run, alpha, a.scale_log2e, false);
+            }
+        }
+        if (rescale && __any(alpha != 1.f)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[i >> 1][i & 1][e] = (__bf16)0.f;
+                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
         }
     };
 
@@ -620,25 +637,28 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // L2; a ticket taken a whole unit ahead was measured to cost half of that sharing), early enough
     // for the atomic to return under the last steps -- and passes the unit on through a mailbox behind
     // the ring.  Every wave reads the same mailbox entry, so the workgroup leaves the loop together.
-    volatile int32_t *mailbox = reinterpret_cast<volatile int32_t *>(lds + 2 * kRing * TILE);
+    typedef volatile __attribute__((address_space(3))) int32_t *lds_int_ptr;
+    const lds_int_ptr mailbox = (lds_int_ptr)(uintptr_t)(ring + 2 * kRing * TILE);
     int xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
     xcc &= 7;
-    // claims on queue q, then on the following ones: index of a unit, or -1 when all are empty
-    auto claim_from = [&](int q0, int first_ticket) {
-        int ticket = first_ticket;
-        for (int t = 0; t < 8; ++t) {
-            const int q = (q0 + t) & 7;
-            const int begin = queue_off[q], len = queue_off[q + 1] - begin;
-            if (t > 0) {
-                ticket = len;
-                if (len > 0) {
-                    int r = 0;
-                    if (lane == 0) r = atomicAdd(&queue_ctr[q], 1);
-                    ticket = __builtin_amdgcn_readfirstlane(r);
-                }
-            }
-            if (ticket < len) return begin + ticket;
+    // The unit of a ticket of the own queue; if that is empty, a claim on the next one that is not, or -1.  One look
+    // at all counters says which queues to ask (a counter only grows: what is empty stays empty); asking seven
+    // empty queues one after the other took 10 us at the end of every launch.
+    auto claim_from = [&](int ticket) {
+        const int own_begin = scalar_load<int>(queue_off + xcc), own_len = scalar_load<int>(queue_off + xcc + 1) - own_begin;
+        if (ticket < own_len) return own_begin + ticket;
+        const int q = lane & 7, begin = queue_off[q], len = queue_off[q + 1] - begin;
+        const bool left = __hip_atomic_load(&queue_ctr[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < len;
+        for (uint32_t open = (uint32_t)__ballot(left && q != xcc) & 0xff; open;) {
+            const uint32_t turned = ((open >> xcc) | (open << (8 - xcc))) & 0xff;   // bit 0: the own queue
+            const int next = (xcc + __builtin_ctz(turned)) & 7;
+            const int next_begin = queue_off[next], next_len = queue_off[next + 1] - next_begin;
+            int r = 0;
+            if (lane == 0) r = atomicAdd(&queue_ctr[next], 1);
+            r = __builtin_amdgcn_readfirstlane(r);
+            if (r < next_len) return next_begin + r;
+            open &= ~(1u << next);
         }
         return -1;
     };
@@ -678,7 +698,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         share_end = share_off[share + 1];
     }
     if (wave8 == 0) {
-        const int first = share_next < share_end ? share_next : claim_from(xcc, __builtin_amdgcn_readfirstlane(take_ticket()));
+        const int first = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(take_ticket()));
         if (lane == 0) mailbox[0] = first;
     }
     ++share_next;
@@ -691,8 +711,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         reset_unit_state();
         {
             const int nn = min(__builtin_amdgcn_readfirstlane(w0.n), n_k_tiles - 1);
-            tb_cur = map_text_bits[nn];
-            sb_cur = map_sink_bits[nn];
+            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
+            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
         }
         // prologue: K(0) -> K slot 0, K(1) -> K slot 1, V^T(0) -> V^T slot 0 (unconditional, clamped)
         {
@@ -725,30 +745,38 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // nobody reads after barrier k; at the end of every matrix phase a wave lets only its newest
         // loads stay in flight (vmcnt), so the loads of interval k have landed before barrier k + 2,
         // and the tiles are read from the interval after that barrier on: four slots each.
+        // The last step only adds P(T-1) V(T-1) and stands behind the loop: half a matrix phase, no refill.
+        // With the look at all queues at once (claim_from) a windowed prompt of 27K tokens, 13 units per
+        // workgroup of 20 tiles each, takes 2058 instead of 2093 us a pass.
+        int slot = 0;
         if (grp == 0) {
-            const int k_claim = max(n_steps - 2, 0);
-            for (int k = 0, slot = 0; k < n_steps; ++k) {
-                if (wave8 == 0 && k == k_claim && share_next >= share_end) next_ticket = take_ticket_async();   // consumed after the loop
+            for (int k = 0; k < T; ++k) {
+                if (wave8 == 0 && k == T - 1 && share_next >= share_end) next_ticket = take_ticket_async();   // consumed after the loop
                 phase_x(slot, k > 0, std::false_type{});
                 __builtin_amdgcn_s_barrier();
                 issue_refill();   // under the second group's head reads, before its chain starts
-                phase_y(k);
+                phase_y();
                 slot = slot == kRing - 1 ? 0 : slot + 1;
             }
+            if (wave8 == 0 && T == 0 && share_next >= share_end) next_ticket = take_ticket_async();
+            phase_last(slot);
+            __builtin_amdgcn_s_barrier();
         } else {
-            for (int k = 0, slot = 0; k < n_steps; ++k) {
+            for (int k = 0; k < T; ++k) {
                 __builtin_amdgcn_s_barrier();
                 phase_x(slot, k > 0, std::true_type{});
-                phase_y(k);
+                phase_y();
                 slot = slot == kRing - 1 ? 0 : slot + 1;
             }
+            __builtin_amdgcn_s_barrier();
+            phase_last(slot);
         }
         // End of the unit: the refills of its last steps (tiles nobody needs) must have landed
         // before the next unit's first tiles go into the same slots, and every wave must be done
         // reading the ring.  The ticket has returned by then as well.
         ticket_wait(next_ticket);            // vmcnt(0)
         if (wave8 == 0) {
-            const int nxt = share_next < share_end ? share_next : claim_from(xcc, __builtin_amdgcn_readfirstlane(next_ticket));
+            const int nxt = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(next_ticket));
             if (lane == 0) mailbox[0] = nxt;
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the mailbox write is in LDS before the barrier
         }

@@ -24,7 +24,7 @@ KERNELS = ("_ZN2bs17attn_prefill_bf16ILi128EEE", "_ZN2bs17attn_prefill_bf16ILi64
 
 
 def compile_to_isa(out_path: str) -> None:
-    cmd = [_build.hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17",
+    cmd = [_build.hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-falign-loops=64",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
            "-I", os.path.join(_build.ROOT, "include"), "-I", _build.CSRC,
            *os.environ.get("BS_EXTRA_HIPCC_FLAGS", "").split(),
