@@ -918,10 +918,11 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
     return a;
 }
 
-// Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.
+// Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
+// holds these tiles already and the binding was just uploaded, its queue counters at zero.
 template <int D>
 void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t pack_bytes,
-                 int n_kv_heads, int n_cus, bool shares, hipStream_t st, void *ev_main_start)
+                 int n_kv_heads, int n_cus, bool shares, bool kv_packed, hipStream_t st, void *ev_main_start)
 {
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     float *cut_results = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * pack_bytes);
@@ -929,8 +930,9 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
     const dim3 tgrid((unsigned)tm->N, (unsigned)n_kv_heads, 2);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(shares ? d->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
-    hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                       static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, d->queue_ctr);
+    if (!kv_packed)
+        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
+                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
                        d->sink_bits, d->rows, shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
@@ -997,6 +999,13 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
                                   int32_t dtype, int32_t n_q_heads, int32_t gqa_group, int32_t head_dim,
                                   float scale, void *stream, void *ev_main_start, void *ev_main_stop)
 {
+    return bs::attn_prefill(q, k, v, out, tm, dtype, n_q_heads, gqa_group, head_dim, scale, stream, ev_main_start, ev_main_stop, nullptr);
+}
+
+int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_tilemap *tm, int32_t dtype,
+                     int32_t n_q_heads, int32_t gqa_group, int32_t head_dim, float scale, void *stream,
+                     void *ev_main_start, void *ev_main_stop, bool *kv_packed)
+{
     int rc = check_call(q, k, v, out, tm, dtype, n_q_heads, gqa_group, head_dim, scale);
     if (rc != BS_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1010,6 +1019,7 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
     if ((rc = device_setup(dev, nullptr, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::RowsPlan rows = bs::plan_rows(tm, dtype, gqa_group, head_dim, n_cus);
+    const uint64_t bound = d->bind_epoch;
     if (!rows.use || rows.need_bits)
         if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
     if (!rows.use) {
@@ -1038,14 +1048,17 @@ extern "C" int bs_attn_prefill_ex(const void *q, const void *k, const void *v, v
         const int n_kv_heads = n_q_heads / gqa_group;
         const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
         const bool shares = d->n_shares > 0;
+        const void *const old_workspace = d->vt_buf;
         if ((rc = workspace(2 * pack_bytes + cut_bytes(d, head_dim))) != BS_OK) return rc;
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, st, ev_main_start);
+        const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
     } else {
         if ((rc = workspace(bs::f32_workspace(d, head_dim))) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         bs::launch_f32(a, d, d->vt_buf, head_dim, st);
     }
+    if (kv_packed) *kv_packed = !rows.use && dtype == BS_BF16;
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     if (ev_main_stop) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_stop), st);
@@ -1089,8 +1102,8 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, false, st, nullptr);
+    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, false, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

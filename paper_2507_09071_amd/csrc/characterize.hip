@@ -17,6 +17,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -26,7 +27,10 @@
 namespace bs {
 
 constexpr int kNmseThreads = 256;
-constexpr int kNmseChunks = 256;   // workgroups per head
+// Workgroups per launch, about (a head has its share of them): four per CU.  With 256 for every head a
+// workgroup of the 28-head, 16K-token case read four 4 KB pieces of each array and spent as long on its reduction:
+// 98 us (2.3 TB/s), now 46 (5.0 TB/s).
+constexpr int kNmseWorkgroups = 1024;
 
 __device__ inline void widen8(const uint4 &raw, float (&f)[8])
 {
@@ -45,7 +49,7 @@ __device__ inline double wave_sum(double x)
     return x;
 }
 
-// sums[head] += (sum (a - r)^2, sum r^2) over the head's `n` elements; grid (kNmseChunks, heads).
+// sums[head] += (sum (a - r)^2, sum r^2) over the head's `n` elements; grid (chunks, heads).
 // Differences of two bf16 (or fp32) values are formed in fp32 (fp64 for fp32 inputs) and squared
 // and accumulated in fp64, so the result is the fp64 sum up to the order of the additions.
 template <typename T>
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(kNmseThreads) void head_sq_error(const T *__restric
     const T *ah = a + (int64_t)head * n;
     const T *rh = r + (int64_t)head * n;
     const int64_t n_vec = n / kVec;
-    const int64_t per_chunk = (n_vec + kNmseChunks - 1) / kNmseChunks;
+    const int64_t per_chunk = (n_vec + gridDim.x - 1) / gridDim.x;
     const int64_t v0 = (int64_t)blockIdx.x * per_chunk;
     const int64_t v1 = v0 + per_chunk < n_vec ? v0 + per_chunk : n_vec;
     double err = 0.0, ref = 0.0;
@@ -86,7 +90,7 @@ __global__ __launch_bounds__(kNmseThreads) void head_sq_error(const T *__restric
             }
         }
     }
-    if (blockIdx.x == kNmseChunks - 1) {   // ragged tail (n not a multiple of the vector width)
+    if (blockIdx.x == gridDim.x - 1) {   // ragged tail (n not a multiple of the vector width)
         for (int64_t i = n_vec * kVec + threadIdx.x; i < n; i += kNmseThreads) {
             double fa, fr;
             if constexpr (sizeof(T) == 2) {
@@ -145,7 +149,7 @@ __global__ void select_head_type(const double *__restrict__ sums, int heads, dou
 static int launch_sq_error(const void *a, const void *r, int dtype, int heads, int64_t n, double *sums,
                            hipStream_t st)
 {
-    const dim3 grid(kNmseChunks, heads);
+    const dim3 grid((unsigned)std::max(1, (kNmseWorkgroups + heads - 1) / heads), heads);
     if (dtype == BS_BF16)
         hipLaunchKernelGGL(head_sq_error<uint16_t>, grid, dim3(kNmseThreads), 0, st,
                            (const uint16_t *)a, (const uint16_t *)r, n, sums);
@@ -203,7 +207,7 @@ extern "C" int bs_characterize_prompt(const void *q, const void *k, const void *
     Buffers b;
     hipError_t e;
     if ((e = hipGetDevice(&b.device)) != hipSuccess) return fail_hip(e, "hipGetDevice");
-    const size_t small_bytes = sizeof(double) * 9 * (size_t)n_q_heads + (size_t)n_q_heads;
+    const size_t result_bytes = (sizeof(double) * 3 + 1) * (size_t)n_q_heads, small_bytes = sizeof(double) * 6 * (size_t)n_q_heads + result_bytes;
     if ((e = pool_acquire(b.device, out_bytes, st, &b.ref, &b.ref_cap)) != hipSuccess) return fail_hip(e, "hipMalloc(reference output)");
     if ((e = pool_acquire(b.device, out_bytes, st, &b.cand, &b.cand_cap)) != hipSuccess) return fail_hip(e, "hipMalloc(masked output)");
     if ((e = pool_acquire(b.device, small_bytes, st, &b.small, &b.small_cap)) != hipSuccess) return fail_hip(e, "hipMalloc(sums)");
@@ -212,9 +216,10 @@ extern "C" int bs_characterize_prompt(const void *q, const void *k, const void *
 
     int rc = BS_OK;
     hipLaunchKernelGGL(fill_zero, dim3((6 * n_q_heads + 255) / 256), dim3(256), 0, st, sums, 6 * n_q_heads);
-    std::vector<uint8_t> cls;
+    std::vector<uint8_t> cls, result;
     try {
         cls.assign(n_q_heads, (uint8_t)BS_DENSE);
+        result.resize(result_bytes);
     } catch (const std::bad_alloc &) {
         rc = BS_ENOMEM;
     }
@@ -223,11 +228,12 @@ extern "C" int bs_characterize_prompt(const void *q, const void *k, const void *
     if (rc == BS_OK)
         rc = bs_build_tilemap_model(spans, n_spans, seq_len, cls.data(), n_q_heads, sink_len, 128, 64, map_flags,
                                     sink_offsets, n_sink_offsets, window, &tm);
+    bool kv_packed = false;
     for (int c = 0; c < 4 && rc == BS_OK; ++c) {   // Dense reference, then Sink, Intra-Image, Intra-Image+Sink
         std::fill(cls.begin(), cls.end(), (uint8_t)c);
         rc = bs_tilemap_rebind(tm, cls.data(), n_q_heads);
-        if (rc == BS_OK)
-            rc = bs_attn_prefill(q, k, v, c == 0 ? b.ref : b.cand, tm, dtype, n_q_heads, gqa_group, head_dim, scale, st);
+        if (rc == BS_OK)   // the packed tiles of K and V are those of the first run
+            rc = attn_prefill(q, k, v, c == 0 ? b.ref : b.cand, tm, dtype, n_q_heads, gqa_group, head_dim, scale, st, nullptr, nullptr, &kv_packed);
         if (rc == BS_OK && c > 0)
             rc = launch_sq_error(b.cand, b.ref, dtype, n_q_heads, per_head, sums + (size_t)(c - 1) * 2 * n_q_heads, st);
     }
@@ -240,9 +246,10 @@ extern "C" int bs_characterize_prompt(const void *q, const void *k, const void *
     // the buffers are about to be handed back: wait for the queued work on every way out
     if ((e = hipStreamSynchronize(st)) != hipSuccess && rc == BS_OK) rc = fail_hip(e, "hipStreamSynchronize");
     if (rc != BS_OK) return rc;
-    if ((e = hipMemcpy(head_type, type_dev, n_q_heads, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy(head_type)");
-    if (nmse && (e = hipMemcpy(nmse, nmse_dev, sizeof(double) * 3 * n_q_heads, hipMemcpyDeviceToHost)) != hipSuccess)
-        return fail_hip(e, "hipMemcpy(nmse)");
+    if ((e = hipMemcpy(result.data(), nmse_dev, result_bytes, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy(nmse, head_type)");
+    const size_t nmse_bytes = sizeof(double) * 3 * (size_t)n_q_heads;
+    if (nmse) std::memcpy(nmse, result.data(), nmse_bytes);
+    std::memcpy(head_type, result.data() + nmse_bytes, n_q_heads);
     return BS_OK;
 }
 

@@ -100,4 +100,11 @@ int order_after_last_use(DeviceMap *d, hipStream_t st);
 
 void free_device_map(DeviceMap *d);
 
+// bs_attn_prefill_ex for a caller that runs several bindings of one map over the same K and V: *kv_packed says in that
+// the map's workspace holds the packed tiles of this K and V (its previous call was this one's predecessor), out
+// that it holds them now.
+int attn_prefill(const void *q, const void *k, const void *v, void *out, bs_tilemap *tm, int32_t dtype, int32_t n_q_heads,
+                 int32_t gqa_group, int32_t head_dim, float scale, void *stream, void *ev_main_start, void *ev_main_stop,
+                 bool *kv_packed);
+
 }  // namespace bs
