@@ -3,8 +3,9 @@
 // The 128-row query tiles of the prefill kernel are the wrong shape here.  The work is reading K and V once,
 // so the bound is HBM, and what the prefill path does around it (a packed copy of K and V, one workgroup per
 // two heads walking the whole cache) cost many times the read.  Measured, one row: 28 heads over 39.5K keys of
-// 4 KV heads (81 MB) 893 us there, 18.5 + 5 us here (4.4 TB/s in the first kernel); 32 heads over 302K keys of
-// 16 KV heads (2.5 GB) 7460 us there, 413 + 4 us here (6.0 TB/s; a large copy reaches 4.7).  How:
+// 4 KV heads (81 MB) 893 us there, 17.4 + 4.1 us here (4.7 TB/s in the first kernel; 18.5 + 5 with the query rows and
+// the rows' bounds loaded before the first keys were requested, and the merge waiting for memory twice); 32 heads over
+// 302K keys of 16 KV heads (2.5 GB) 7460 us there, 413 + 4 us here (6.0 TB/s; a large copy reaches 4.7).  How:
 //  * the query rows of ALL heads of a GQA group are stacked (head-major) into blocks of 32 rows, the free
 //    dimension of a 32x32x16 MFMA, so K and V of a KV head are read once for the whole group;
 //  * the keys are split over the chip: grid (parts, KV heads, row groups), about one workgroup per CU; its
@@ -44,7 +45,7 @@ struct RowsArgs {
     float2 *part_ml;     // [KV head][row group][part][row]: reference point and row sum of a part
     const uint64_t *text_bits, *sink_bits;
     int32_t L, R, G;
-    int32_t k0, n_blocks;
+    int32_t k0, blocks_each, blocks_more;   // a part has blocks_each key blocks, the first blocks_more parts one more
     float scale_log2e;
     RowBounds rows[kRowsMaxRows];
     uint32_t classes[kRowsMaxHeads / 16];   // two bits per head
@@ -57,7 +58,8 @@ struct RowsTraits {
     static constexpr int kLoads = kBlock / 1024;            // LDS-direct instructions per block
     static constexpr int kWave = 4 * kBlock;                // two stages of K and V
     static constexpr int kRing = kRowsWaves * kWave;
-    static constexpr int kLds = kRing + kRowsWaves * 64 * 8;
+    static constexpr int kQuery = kRing + kRowsWaves * 64 * 8;   // the query rows, at most 64
+    static constexpr int kLds = kQuery + 64 * kRowBytes;
     static constexpr int kPerCu = D == 64 ? 2 : 1;          // workgroups per CU
     // exchange of the 16-byte chunks of row r: rows that share their banks get different chunks
     __device__ static int swizzle(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
@@ -79,32 +81,45 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     const int part = blockIdx.x, kvh = blockIdx.y, grp = blockIdx.z, n_parts = gridDim.x;
     const int S = a.G * a.R;   // stacked rows of a KV head
 
-    // ---- the rows of this lane (column `col` of every row block)
-    bf16x8 q[NRB][NT];
+    // ---- what the rows of this lane see (column `col` of every row block; a slot without a row works on a copy of the
+    // last one, never stored).  A vector load here would be waited for together with the LDS-direct loads, which the
+    // compiler does not know, so what a decoding step needs comes through scalar loads, and the rest is here before
+    // the first of them goes out.
+    constexpr int ROWS = NRB * 32;
     int first[NRB], last[NRB], own_lo[NRB], own_hi[NRB];
     bool sees_all[NRB], sinks[NRB];
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        const int s = min((grp * NRB + rb) * 32 + col, S - 1);   // a slot without a row works on a copy, never stored
-        const int g = s / a.R, r = s - g * a.R, head = kvh * a.G + g;
-        const __bf16 *qr = static_cast<const __bf16 *>(a.q) + ((size_t)head * a.R + r) * D;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) q[rb][t] = *reinterpret_cast<const bf16x8 *>(qr + 16 * t + 8 * hl);
-        const RowBounds b = a.rows[r];
-        const int cls = (a.classes[head >> 4] >> (2 * (head & 15))) & 3;
+    auto view = [&](int rb, RowBounds b, int cls) __attribute__((always_inline)) {
         first[rb] = b.first;
         last[rb] = b.last;
         sees_all[rb] = cls == BS_DENSE || b.img_hi == b.img_lo;
         sinks[rb] = cls & 1;
         own_lo[rb] = (cls & 2) ? b.img_lo : 0;
         own_hi[rb] = (cls & 2) ? b.img_hi : 0;
+    };
+    if (a.R == 1) {
+        const int head0 = kvh * a.G + grp * ROWS, word0 = head0 >> 4;   // the classes of ROWS heads: ROWS / 16 + 1 words
+        uint32_t words[ROWS / 16 + 1];
+#pragma unroll
+        for (int i = 0; i < ROWS / 16 + 1; ++i) words[i] = __builtin_amdgcn_readfirstlane(a.classes[min(word0 + i, kRowsMaxHeads / 16 - 1)]);
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            const int head = kvh * a.G + min((grp * NRB + rb) * 32 + col, S - 1);
+            uint32_t w = words[0];
+#pragma unroll
+            for (int i = 1; i < ROWS / 16 + 1; ++i) w = (head >> 4) - word0 == i ? words[i] : w;
+            view(rb, a.rows[0], (w >> (2 * (head & 15))) & 3);
+        }
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            const int s = min((grp * NRB + rb) * 32 + col, S - 1), g = s / a.R, head = kvh * a.G + g;
+            view(rb, a.rows[s - g * a.R], (a.classes[head >> 4] >> (2 * (head & 15))) & 3);
+            int all = sees_all[rb], snk = sinks[rb];
+            asm volatile("" : "+v"(first[rb]), "+v"(last[rb]), "+v"(own_lo[rb]), "+v"(own_hi[rb]), "+v"(all), "+v"(snk));
+            sees_all[rb] = all;
+            sinks[rb] = snk;
+        }
     }
-    // The query rows must be here before the loop: the compiler would wait for them inside it, and with them for
-    // the LDS-direct loads, which it does not know.
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(q[rb][t]));
     bool all_see_all = true;
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) all_see_all = all_see_all && __all(sees_all[rb]);
@@ -122,8 +137,8 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     }
 
     // ---- key blocks of this wave
-    const int b_begin = (int)((int64_t)a.n_blocks * part / n_parts);
-    const int b_end = (int)((int64_t)a.n_blocks * (part + 1) / n_parts);
+    const int b_begin = part * a.blocks_each + min(part, a.blocks_more);
+    const int b_end = b_begin + a.blocks_each + (part < a.blocks_more ? 1 : 0);
     const int n_steps = b_end - b_begin > wave ? (b_end - b_begin - wave + kRowsWaves - 1) / kRowsWaves : 0;
     const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * a.L * ROWB;
     const char *vh = static_cast<const char *>(a.v) + (size_t)kvh * a.L * ROWB;
@@ -176,6 +191,19 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
         }
     }
 
+    // The query rows go to LDS (all waves work on the same ones) in the layout of a K block, ahead of the first blocks of
+    // keys and with them on the way: stacked rows of a KV head lie one behind the other.
+    {
+        const char *qh = static_cast<const char *>(a.q) + (size_t)kvh * S * ROWB;
+        constexpr int kPerWave = ROWS * ROWB / 1024 / kRowsWaves;
+#pragma unroll
+        for (int j = 0; j < kPerWave; ++j) {
+            const int i = wave * kPerWave + j, r = i * (1024 / ROWB) + lane / (ROWB / 16), p = lane % (ROWB / 16);
+            const uint32_t off = min(grp * ROWS + r, S - 1) * ROWB + ((p ^ TR::swizzle(r & 31)) << 4);
+            const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr)lds + TR::kQuery + i * 1024;
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(qh), "s"(dst) : "memory", "m0");
+        }
+    }
     if (n_steps > 0) {
         issue(kh, block_of(0), ring);
         issue(vh, block_of(0), ring + BLK);
@@ -184,6 +212,18 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
         issue(kh, block_of(1), ring + 2 * BLK);
         issue(vh, block_of(1), ring + 3 * BLK);
     }
+    if (n_steps > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NI) : "memory");
+    else if (n_steps > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    bf16x8 q[NRB][NT];
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            q[rb][t] = *reinterpret_cast<const bf16x8 *>(lds + TR::kQuery + rb * 32 * ROWB + ((col * ROWB + ((hl ^ TR::swizzle(col)) << 4)) ^ (t << 5)));
+
     for (int i = 0; i < n_steps; ++i) {
         const int stage = (i & 1) * 2 * BLK;
         const int blk = block_of(i);
@@ -278,7 +318,7 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     }
 
     // ---- merge of the four waves, through LDS (the ring is free after the barrier)
-    constexpr int ROWS = NRB * 32, CH4 = D / 4;
+    constexpr int CH4 = D / 4;
     float2 *ml = reinterpret_cast<float2 *>(lds + TR::kRing);   // [wave][row]
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
@@ -320,10 +360,9 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
         }
         if (n_parts == 1) {
             const float inv = l > 0.f ? 1.f / l : 0.f;
-            const int s = grp * ROWS + row, g = s / a.R, r = s - g * a.R;
             bf16x4 w;
             w[0] = (__bf16)(sum.x * inv); w[1] = (__bf16)(sum.y * inv); w[2] = (__bf16)(sum.z * inv); w[3] = (__bf16)(sum.w * inv);
-            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + ((size_t)(kvh * a.G + g) * a.R + r) * D + 4 * ch) = w;
+            *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + ((size_t)kvh * S + grp * ROWS + row) * D + 4 * ch) = w;
         } else {
             *reinterpret_cast<float4 *>(a.part_o + (slot + row) * D + 4 * ch) = sum;
             if (ch == 0) a.part_ml[slot + row] = make_float2(m, l);
@@ -346,25 +385,41 @@ __global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part
     const size_t base = (size_t)(kvh * groups + grp) * n_parts * rows_per_group + row;
     const int tid = threadIdx.x;
 
+    // The first kAtOnce parts of a lane are requested before the reference point is known (64 parts at D = 128, 128 at
+    // D = 64: all there are for four KV heads on 256 CUs), so a decoding step waits for memory once here, not twice.
+    constexpr int kAtOnce = 8;
+    const int ch = tid % CH4, p0 = tid / CH4;
+    float2 x[kAtOnce];
+    float4 y[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+        const size_t at = base + (size_t)min(p0 + i * LANES, n_parts - 1) * rows_per_group;
+        x[i] = part_ml[at];
+        y[i] = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
+    }
     float m = -INFINITY;
-    for (int p = tid; p < n_parts; p += 256) m = fmaxf(m, part_ml[base + (size_t)p * rows_per_group].x);
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) m = fmaxf(m, x[i].x);
+    for (int p = kAtOnce * LANES + tid; p < n_parts; p += 256) m = fmaxf(m, part_ml[base + (size_t)p * rows_per_group].x);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     if ((tid & 63) == 0) m_wave[tid >> 6] = m;
     __syncthreads();
     m = fmaxf(fmaxf(m_wave[0], m_wave[1]), fmaxf(m_wave[2], m_wave[3]));
 
-    const int ch = tid % CH4;
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
     float l = 0.f;
-#pragma unroll 8
-    for (int p = tid / CH4; p < n_parts; p += LANES) {
-        const size_t at = base + (size_t)p * rows_per_group;
-        const float2 x = part_ml[at];
-        const float4 y = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
+    auto add = [&](const float2 &x, const float4 &y) {
         const float f = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m) * scale_log2e);
         l += x.y * f;
         sum.x += y.x * f; sum.y += y.y * f; sum.z += y.z * f; sum.w += y.w * f;
+    };
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i)
+        if (p0 + i * LANES < n_parts) add(x[i], y[i]);
+    for (int p = p0 + kAtOnce * LANES; p < n_parts; p += LANES) {
+        const size_t at = base + (size_t)p * rows_per_group;
+        add(part_ml[at], *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch));
     }
     acc[tid / CH4][ch] = sum;
     float l_lane = ch == 0 ? l : 0.f;   // every channel lane of a part holds the same l
@@ -446,7 +501,9 @@ void launch_rows(const RowsPlan &plan, const void *q, const void *k, const void 
     a.part_ml = reinterpret_cast<float2 *>(a.part_o + (size_t)n_kv * plan.groups * plan.parts * plan.row_blocks * 32 * head_dim);
     if (plan.need_bits) { a.text_bits = d->text_bits; a.sink_bits = d->sink_bits; }
     a.L = tm->L; a.R = tm->L - tm->q_begin; a.G = gqa_group;
-    a.k0 = plan.k0; a.n_blocks = plan.k1 - plan.k0;
+    a.k0 = plan.k0;
+    a.blocks_each = (plan.k1 - plan.k0) / plan.parts;
+    a.blocks_more = (plan.k1 - plan.k0) % plan.parts;
     a.scale_log2e = scale * 1.4426950408889634f;
     for (int32_t i = 0; i < a.R; ++i)
         row_bounds(tm, tm->q_begin + i, &a.rows[i].first, &a.rows[i].last, &a.rows[i].img_lo, &a.rows[i].img_hi);
