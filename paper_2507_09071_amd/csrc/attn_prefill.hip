@@ -236,34 +236,40 @@ __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__rest
     }
 }
 
+// K tiles before `in_place` are not packed: the attention kernel reads them where the caller has them.  The others -- the
+// ragged last tile of the prompt and the compact tiles -- then hold their rows one behind the other as well; without
+// tiles read in place (in_place = 0) all are packed in the layout above.
 template <int D>
 __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restrict__ kp,
-                                   const int32_t *__restrict__ compact_keys, int L, int N, int N0)
+                                   const int32_t *__restrict__ compact_keys, int L, int n, int N, int N0, int in_place)
 {
-    const int n = blockIdx.x, kvh = blockIdx.y;
+    const int kvh = blockIdx.y;
     const __bf16 *src = k + (size_t)kvh * L * D;
-    __bf16 *dst = kp + ((size_t)kvh * N + n) * (size_t)(D * kBlockN);
-    for (int idx = threadIdx.x; idx < kBlockN * (D / 8); idx += 256) {   // one 16-byte half per iteration
-        const int hp = idx & 1, key = (idx >> 1) % kBlockN, t = idx / (2 * kBlockN);
-        const int h = hp ^ ((key >> 3) & 1);
+    __bf16 *dst = kp + ((size_t)kvh * (N - in_place) + n - in_place) * (size_t)(D * kBlockN);
+    for (int idx = threadIdx.x; idx < kBlockN * (D / 8); idx += 256) {   // 16 bytes per iteration
+        int key = idx / (D / 8), ch = idx % (D / 8);
+        if (in_place == 0) {
+            key = (idx >> 1) % kBlockN;
+            ch = idx / (2 * kBlockN) * 2 + ((idx & 1) ^ ((key >> 3) & 1));
+        }
         const int pos = slot_key(compact_keys, n, key, L, N0);
         uint4 val = make_uint4(0, 0, 0, 0);
-        if (pos >= 0) val = *reinterpret_cast<const uint4 *>(src + (size_t)pos * D + 16 * t + 8 * h);
+        if (pos >= 0) val = *reinterpret_cast<const uint4 *>(src + (size_t)pos * D + ch * 8);
         *reinterpret_cast<uint4 *>(dst + (size_t)idx * 8) = val;
     }
 }
 
-// The pre-pass of a bf16 call, one launch: grid (key tiles, KV heads, 2); z = 0 packs K, z = 1 packs V^T.
+// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place; KV heads).
 template <int D>
 __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                                      __bf16 *__restrict__ kp, __bf16 *__restrict__ vt,
-                                                     const int32_t *__restrict__ compact_keys, int L, int N, int N0,
+                                                     const int32_t *__restrict__ compact_keys, int L, int N, int N0, int in_place,
                                                      int32_t *__restrict__ queue_ctr)
 {
     __shared__ __bf16 tile[kBlockN * (D + 2)];
     // the attention kernel that follows starts on fresh unit queues
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
-    if (blockIdx.z == 0) pack_k_tile<D>(k, kp, compact_keys, L, N, N0);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
+    if ((int)blockIdx.x >= N) pack_k_tile<D>(k, kp, compact_keys, L, in_place + (int)blockIdx.x - N, N, N0, in_place);
     else pack_vt_tile<D>(v, vt, compact_keys, L, N, N0, tile);
 }
 
@@ -294,7 +300,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const int4 *__restrict__ pair_items,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
-    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    int32_t n_k_tiles, int32_t in_place, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
 {
     constexpr int ROW = D * 2;            // bytes per K row in LDS
@@ -318,7 +324,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
     int row = 0;                    // the query position of this lane's row
-    const char *kph = nullptr, *vth = nullptr;   // packed K / V^T tiles of the unit's KV head
+    const char *kph = nullptr, *vth = nullptr;   // K / packed V^T tiles of the unit's KV head
+    const char *kpackh = nullptr;                // its packed K tiles, as if those before `in_place` were, too
     bf16x8 qreg[NT];                // Q^T operand: Q[row][16t + 8hl .. +8] for every 16-wide slice t
     QueryView qv;
     int list_begin = 0, list_end = 0;
@@ -341,7 +348,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         row = r0.x;
         const __bf16 *qh = reinterpret_cast<const __bf16 *>(a.q) + (size_t)hsafe * R * D;
         // one TILE-byte block per key tile
-        kph = reinterpret_cast<const char *>(kp + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
+        kph = reinterpret_cast<const char *>(a.k) + (size_t)kvh * L * ROW;
+        kpackh = reinterpret_cast<const char *>(kp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
         vth = reinterpret_cast<const char *>(vt + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
         const int qrow = min(row, L - 1) - a.q_begin;  // rows past the end compute on a copy and are not stored
 #pragma unroll
@@ -407,6 +415,24 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     auto tile_ptr = [&](const char *base, int n) {
         return base + (size_t)min(n, n_k_tiles - 1) * TILE;  // a walker past its end names no tile
     };
+    auto k_ptr = [&](int n) {
+        n = min(n, n_k_tiles - 1);
+        return (n < in_place ? kph : kpackh) + (size_t)n * TILE;
+    };
+    // The same for a K tile.  If some are read in place their rows lie one behind the other: a lane picks the 16 bytes
+    // that belong at its place, 32 bytes of 32 rows per instruction (the other waves read the rest of the 128-byte
+    // lines at the same time), and the next instruction's slices are 128 bytes further.
+    const uint32_t kdma_key = (wave8 & 1) * 32 + (lane >> 1);
+    const uint32_t kdma_lane_off = in_place ? kdma_key * ROW + (wave8 >> 1) * 32 + (((lane & 1) ^ ((kdma_key >> 3) & 1)) << 4) : dma_lane_off;
+    const int kdma_stride = in_place ? 128 : 8 * 1024;
+    auto kdma = [&](int r, const char *tile, int slot_byte) __attribute__((always_inline)) {
+        const uint32_t dst = ring + slot_byte + wave8 * 1024 + r * 8 * 1024;
+        const char *src = tile + r * kdma_stride;
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(kdma_lane_off), "s"(src), "s"(dst)
+                     : "memory", "m0");
+    };
 
     // ---- phase X building blocks (step k reads K slot k mod 4 and V^T slot (k - 1) mod 4) ----
     // A batch is four 128-bit operand reads feeding four MFMAs:
@@ -464,7 +490,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     auto issue_refill = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, ksrc, Sk_dst * TILE);
+        for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, ksrc, Sk_dst * TILE);
 #pragma unroll
         for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * TILE);
         __builtin_amdgcn_sched_barrier(0);
@@ -506,7 +532,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // Refill addresses: computed while the first operand reads are in flight.
         auto refill_prepare = [&]() __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
-            ksrc = tile_ptr(kph, w2.n);
+            ksrc = k_ptr(w2.n);
             vsrc = tile_ptr(vth, w1.n);
             w1.next();
             w2.next();
@@ -716,17 +742,17 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         }
         // prologue: K(0) -> K slot 0, K(1) -> K slot 1, V^T(0) -> V^T slot 0 (unconditional, clamped)
         {
-            const char *k0 = tile_ptr(kph, w0.n), *k1 = tile_ptr(kph, wt1.n), *v0 = tile_ptr(vth, w0.n);
+            const char *k0 = k_ptr(w0.n), *k1 = k_ptr(wt1.n), *v0 = tile_ptr(vth, w0.n);
 #pragma unroll
-            for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, k0, 0);
+            for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k0, 0);
 #pragma unroll
-            for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, k1, TILE);
+            for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k1, TILE);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v0, kRing * TILE);
             {
-                const char *k2 = tile_ptr(kph, wt2.n), *v1 = tile_ptr(vth, wt1.n);
+                const char *k2 = k_ptr(wt2.n), *v1 = tile_ptr(vth, wt1.n);
 #pragma unroll
-                for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, k2, 2 * TILE);
+                for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k2, 2 * TILE);
 #pragma unroll
                 for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v1, (kRing + 1) * TILE);
             }
@@ -927,19 +953,31 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     float *cut_results = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * pack_bytes);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + pack_bytes);
-    const dim3 tgrid((unsigned)tm->N, (unsigned)n_kv_heads, 2);
+    const int32_t in_place = d->k_in_place;
+    const dim3 tgrid((unsigned)(2 * tm->N - in_place), (unsigned)n_kv_heads);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(shares ? d->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     if (!kv_packed)
         hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, d->queue_ctr);
+                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, in_place, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                       d->sink_bits, d->rows, shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N,
+                       d->sink_bits, d->rows, shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N, in_place,
                        d->queue_ctr, shares ? d->share_queue_off : d->queue_off, shares ? d->share_off : nullptr, cut_results);
     if (shares && d->n_cut > 0)
         hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
                            d->rows, cut_results);
+}
+
+// How many key tiles of K the attention kernel reads where the caller has them.  Packing one costs a read and a write of the
+// tile, reading it in place 32-byte pieces on every fetch: 1-1.6 % of the kernel's time on long prompts, which fetch a
+// tile hundreds of times, against 3-10 % of a launch that fetches it ten times (a window, a chunk behind a long cache).
+// Fetches per tile and time saved, d = 128: window of 1024: 11, 3 %; 517-row chunk of 36K: 9-18, 3.5 %; 2048 of 141K:
+// 10-43, 2.2 %; 8K tokens: 59-108, -0.9 to 0.3; 36K: 182-492, -0.2 %; 302K: 377, -1.6 %; d = 64, 9K tokens: 34-66, -0.5 to 0.2.
+int32_t tiles_in_place(const bs_tilemap *tm, const DeviceMap *d, int n_kv_heads, int32_t head_dim)
+{
+    const int64_t fetches = head_dim == 128 ? 48 : 32;   // (a tile of d = 64 is half as much to pack)
+    return d->n_steps < fetches * n_kv_heads * tm->N ? tm->L / bs::kBlockN : 0;
 }
 
 // Bytes of the results of cut units (0 without equal shares).
@@ -1051,6 +1089,7 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         const void *const old_workspace = d->vt_buf;
         if ((rc = workspace(2 * pack_bytes + cut_bytes(d, head_dim))) != BS_OK) return rc;
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
+        if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
         if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
         else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
     } else {
@@ -1099,6 +1138,7 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
     // units are cut only if their partial results fit behind the packed tiles
     const bool shares = d->n_shares > 0 && 2 * pack_bytes + cut_bytes(d, head_dim) <= kStaticScratchBytes;
+    d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);

@@ -65,10 +65,12 @@ struct DeviceMap {
     const int32_t *share_queue_off = nullptr;   // ... [9] the parts for whoever is done first, ...
     const int4 *cut_items = nullptr;      // ... [n_cut] the items whose results come in parts
     int32_t n_shares = 0, n_cut = 0, n_slots = 0;
+    int64_t n_steps = 0;                  // key-tile steps of the work units
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
     void *vt_buf = nullptr;
     size_t vt_bytes = 0;
+    int32_t k_in_place = 0;               // key tiles of K that the last call read in place (see pack_k_tile)
     hipStream_t last_stream = nullptr;    // stream of the most recent upload / launch (compared, never used)
     std::shared_ptr<EventHolder> last_use;   // recorded after the most recent upload / launch
 };

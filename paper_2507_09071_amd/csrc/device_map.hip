@@ -505,6 +505,8 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     d->pair_items = reinterpret_cast<const int4 *>(b + off_a);
     d->pair_ranges = reinterpret_cast<const int2 *>(b + off_b);
     d->n_pairs = (int32_t)plan.items.size();
+    d->n_steps = 0;
+    for (const PairItem &it : plan.items) d->n_steps += it.n_tiles;
     d->queue_off = reinterpret_cast<const int32_t *>(b + off_q);
     d->queue_ctr = reinterpret_cast<int32_t *>(b + off_q + 64);
     d->share_items = reinterpret_cast<const int4 *>(b + off_si);
