@@ -18,7 +18,7 @@
 //    holds 16 keys of ONE query per 32-key block: row max / row sum are in-lane reductions plus
 //    one exchange with the lane 32 apart (v_permlane32_swap);
 //  * O^T = V^T P^T reuses the probabilities, rounded to bf16, as the B operand; V^T comes from a
-//    pre-pass that writes K and V^T per key tile in exactly the layout the LDS reads want;
+//    pre-pass that writes K (where it is fetched often) and V^T per key tile in exactly the layout the LDS reads want;
 //  * K and V^T tiles travel global -> LDS with 16-byte LDS-direct loads (no VGPR staging) into a
 //    ring of 4 K + 4 V^T slots shared by the two groups; ONE barrier per key tile, placed so that
 //    on every SIMD one wave runs its matrix phase while the other runs its vector phase;
@@ -189,8 +189,8 @@ __device__ inline void mfma_drain(floatx16 &c0, floatx16 &c1)
 }
 
 
-// LDS tile layouts of the bf16 kernel (written by the pre-pass below, copied verbatim by the
-// kernel's LDS-direct loads).  Both are "slice-major": everything an MFMA operand read selects
+// LDS tile layouts of the bf16 kernel (written by the pre-pass below and copied verbatim by the
+// kernel's LDS-direct loads; a K tile read in place gets there piece by piece).  Both are "slice-major": everything an MFMA operand read selects
 // at compile time (head-dim slice, key block, key group, channel block) is an immediate offset,
 // and one per-lane base address serves all reads of a tile.
 //   K tile   [D/16 slices t][64 keys][32 B]   32 B = channels 16t..16t+15 of one key, as two

@@ -29,7 +29,7 @@ namespace bs {
 constexpr int kNmseThreads = 256;
 // Workgroups per launch, about (a head has its share of them): four per CU.  With 256 for every head a
 // workgroup of the 28-head, 16K-token case read four 4 KB pieces of each array and spent as long on its reduction:
-// 98 us (2.3 TB/s), now 46 (5.0 TB/s).
+// 98 us (2.3 TB/s), now 40 (5.7 TB/s; 46 with eight workgroups per CU).
 constexpr int kNmseWorkgroups = 1024;
 
 __device__ inline void widen8(const uint4 &raw, float (&f)[8])
