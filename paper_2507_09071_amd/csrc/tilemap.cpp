@@ -971,6 +971,14 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
     std::vector<Load> heap(n_wgs);
     auto deal = [&](auto &&accept) {   // units in order to the least loaded workgroup; the loads end up in `heap`
         for (int32_t w = 0; w < n_wgs; ++w) heap[w] = {0, w};
+        if (n_units <= n_wgs) {        // each to the next workgroup that has nothing yet
+            int32_t w = 0;
+            for (const auto &o : order) {
+                const int64_t x = plan.items[o.second].n_tiles + kUnitCost;
+                if (accept(o.second, heap[w], x)) heap[w++].first = x;
+            }
+            return;
+        }
         for (const auto &o : order) {
             const int64_t x = plan.items[o.second].n_tiles + kUnitCost;
             std::pop_heap(heap.begin(), heap.end(), std::greater<Load>());
@@ -1018,8 +1026,17 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
         }
         return true;
     };
-    int64_t share = least + kUnitCost;   // a cut costs another unit's worth
-    while (share + kMergeCost < queued && !fill(share)) share += std::max<int64_t>(1, share / 32);
+    // The first share with room for every unit and the cuts it takes (a part costs a unit's worth again); starting a
+    // unit's worth above the mean instead left 20-40 of 256 workgroups without work on short prompts (28 heads, 1.3K
+    // tokens: longest workgroup 15 steps, now 11; 243 -> 235 us a pass of four layers).
+    auto has_room = [&](int64_t share) {
+        int64_t need = 0;
+        for (const bs::PairItem &it : plan.items)
+            need += it.n_tiles + kUnitCost * std::max<int64_t>(1, (it.n_tiles + share - kUnitCost - 1) / (share - kUnitCost));
+        return need <= share * n_wgs;
+    };
+    int64_t share = least;
+    while (share + kMergeCost < queued && !(has_room(share) && fill(share))) share += std::max<int64_t>(1, share / 32);
     if (share + kMergeCost >= queued) return;   // no gain over the queues
     std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &b) { return a.wg < b.wg; });
     std::vector<int32_t> off(n_wgs + 2, 0);   // (the queued pieces count as those of workgroup n_wgs)
