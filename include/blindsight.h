@@ -217,6 +217,17 @@ int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *n_units, in
                          int64_t *skip_steps);
 
 /*
+ * Plan (and check) how those units are cut into equal shares for `n_wgs` workgroups (one per compute unit in
+ * bs_attn_prefill), where a launch has too few units for the queues to balance it; gqa_group 0: the units of the fp32
+ * kernel, one (head, query tile) item each.  Returns BS_OK only if every unit has a part, the parts of a unit walk each
+ * of its key tiles once, each part is in one share or one queue, and the list of cut items names every part's slot.
+ * Outputs (may be NULL): parts (0: the units stay in the queues), units that were cut, parts left to the queues.
+ * Host only, for tests and accounting.
+ */
+int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs, int64_t *n_parts, int64_t *n_cut_units,
+                          int64_t *n_queued);
+
+/*
  * Bind a built map to another class vector (paper Sec. 4: every layer of a model has its own offline-assigned
  * head classes, while the mask metadata depends on the prompt alone, Sec. 5): the four per-class tile lists,
  * token codes, row and key order -- everything bs_build_tilemap derived from the span table -- are kept,

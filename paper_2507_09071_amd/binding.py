@@ -18,7 +18,7 @@ BS_BF16, BS_F32 = 0, 1
 DENSE, SINK, INTRA, INTRA_SINK = 0, 1, 2, 3
 
 EXPORTS = ("bs_build_tilemap", "bs_build_tilemap_ex", "bs_build_tilemap_model", "bs_build_tilemap_suffix", "bs_tilemap_destroy", "bs_tilemap_dims", "bs_tilemap_row_order", "bs_tilemap_layout", "bs_tilemap_key_order", "bs_tilemap_tile_states",
-           "bs_tilemap_stats", "bs_tilemap_pair_plan", "bs_tilemap_upload", "bs_tilemap_rebind", "bs_tilemap_prepare",
+           "bs_tilemap_stats", "bs_tilemap_pair_plan", "bs_tilemap_share_plan", "bs_tilemap_upload", "bs_tilemap_rebind", "bs_tilemap_prepare",
            "bs_attn_prefill", "bs_attn_prefill_ex", "bs_attn_prefill_static", "bs_static_scratch_bytes",
            "bs_characterize_prompt", "bs_head_sq_error", "bs_aggregate_head_type", "bs_aggregate_layer", "bs_alpha_layer", "bs_strerror",
            "bs_last_error")
@@ -94,6 +94,8 @@ def load_library():
     lib.bs_tilemap_stats.restype = ctypes.c_int
     lib.bs_tilemap_pair_plan.argtypes = [vp, i32, i64p, i64p, i64p]
     lib.bs_tilemap_pair_plan.restype = ctypes.c_int
+    lib.bs_tilemap_share_plan.argtypes = [vp, i32, i32, i64p, i64p, i64p]
+    lib.bs_tilemap_share_plan.restype = ctypes.c_int
     lib.bs_tilemap_upload.argtypes = [vp]
     lib.bs_tilemap_upload.restype = ctypes.c_int
     lib.bs_tilemap_rebind.argtypes = [vp, u8p, i32]
@@ -194,6 +196,12 @@ class TileMap:
         _check(load_library().bs_tilemap_pair_plan(self._h, int(gqa_group), *[ctypes.byref(x) for x in v]),
                "bs_tilemap_pair_plan")
         return {n: int(x.value) for n, x in zip(("n_units", "unit_tiles", "skip_steps"), v)}
+
+    def share_plan(self, gqa_group: int, n_wgs: int) -> dict:
+        v = [ctypes.c_int64() for _ in range(3)]
+        _check(load_library().bs_tilemap_share_plan(self._h, int(gqa_group), int(n_wgs), *[ctypes.byref(x) for x in v]),
+               "bs_tilemap_share_plan")
+        return {n: int(x.value) for n, x in zip(("n_parts", "n_cut_units", "n_queued"), v)}
 
     def upload(self):
         _check(load_library().bs_tilemap_upload(self._h), "bs_tilemap_upload")

@@ -1010,7 +1010,8 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
         int32_t w = 0;
         for (int32_t u : homeless) {
             int32_t done = 0;
-            for (int32_t left = plan.items[u].n_tiles; left > 0;) {
+            bool placed = false;   // (a unit without a key tile is a piece of its own: its rows are zeros, and somebody has to write them)
+            for (int32_t left = plan.items[u].n_tiles; left > 0 || !placed;) {
                 if (w == n_wgs && fixed == share) return false;
                 const int64_t room = w == n_wgs ? queue_piece : fixed - load[w] - kUnitCost;
                 // the rest of the unit, or a part as long as the room; neither it nor the rest too short
@@ -1020,8 +1021,9 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
                     if (w < n_wgs) load[w] += take + kUnitCost;
                     done += (int32_t)take;
                     left -= (int32_t)take;
+                    placed = true;
                 }
-                if (left > 0 && w < n_wgs) ++w;
+                if ((left > 0 || !placed) && w < n_wgs) ++w;
             }
         }
         return true;
@@ -1126,6 +1128,102 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
         if (n_units) *n_units = (int64_t)plan.items.size();
         if (unit_tiles) *unit_tiles = tiles;
         if (skip_steps) *skip_steps = skips;
+    } catch (const std::bad_alloc &) {
+        return BS_ENOMEM;
+    }
+    return BS_OK;
+}
+
+extern "C" int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs, int64_t *n_parts, int64_t *n_cut_units,
+                                     int64_t *n_queued)
+{
+    if (!tm || gqa_group < 0 || (gqa_group > 0 && tm->n_q_heads % gqa_group != 0) || n_wgs <= 0) return BS_EINVAL;
+    try {
+        bs_plan_shares(tm, gqa_group, n_wgs);
+        const bs::PairPlan &plan = gqa_group == 0 ? tm->solo : tm->pairs;
+        const bs::SharePlan &sp = tm->shares;
+        const size_t n_units = plan.items.size();
+        int64_t cut_units = 0;
+        if (sp.share_off.empty()) {
+            if (!sp.parts.empty() || !sp.cut.empty() || sp.n_slots != 0) return BS_EINVAL;
+        } else {
+            // every part is in the share of one workgroup or in one queue
+            if (sp.share_off.size() != (size_t)n_wgs + 1 || sp.share_off[0] != 0 || sp.share_off[n_wgs] != sp.queue_off[0]) return BS_EINVAL;
+            for (int32_t w = 0; w < n_wgs; ++w)
+                if (sp.share_off[w + 1] < sp.share_off[w]) return BS_EINVAL;
+            for (int q = 0; q < 8; ++q)
+                if (sp.queue_off[q + 1] < sp.queue_off[q]) return BS_EINVAL;
+            if ((size_t)sp.queue_off[8] != sp.parts.size()) return BS_EINVAL;
+
+            // the parts of every unit
+            std::vector<int32_t> unit_of((size_t)tm->n_q_heads * tm->M, -1);
+            for (size_t u = 0; u < n_units; ++u) unit_of[(size_t)plan.items[u].head_a * tm->M + plan.items[u].tile_a] = (int32_t)u;
+            std::vector<std::vector<int32_t>> parts_of(n_units);
+            for (size_t i = 0; i < sp.parts.size(); ++i) {
+                const bs::PairItem &p = sp.parts[i];
+                if (p.head_a < 0 || p.head_a >= tm->n_q_heads || p.tile_a < 0 || p.tile_a >= tm->M) return BS_EINVAL;
+                const int32_t u = unit_of[(size_t)p.head_a * tm->M + p.tile_a];
+                if (u < 0) return BS_EINVAL;
+                const bs::PairItem &it = plan.items[u];
+                if (p.head_b != it.head_b || p.tile_b != it.tile_b || (p.classes & 0xffff) != it.classes) return BS_EINVAL;
+                parts_of[u].push_back((int32_t)i);
+            }
+            std::vector<uint8_t> want(tm->N), got(tm->N), slot_used(sp.n_slots, 0);
+            std::vector<bs::CutItem> cut;
+            for (size_t u = 0; u < n_units; ++u) {
+                const bs::PairItem &it = plan.items[u];
+                if (parts_of[u].empty()) return BS_EINVAL;   // its rows would never be written
+                const int32_t n = (int32_t)parts_of[u].size();
+                // together the parts walk each of the unit's tiles once, in the unit's states
+                std::fill(want.begin(), want.end(), 0);
+                std::fill(got.begin(), got.end(), 0);
+                for (int32_t r = it.list_begin; r < it.list_end; ++r)
+                    for (int32_t t = plan.ranges[r].begin; t < plan.ranges[r].end_states >> 4; ++t)
+                        want[t] = (uint8_t)(plan.ranges[r].end_states & 15);
+                int32_t first_slot = INT32_MAX, last_slot = -1;
+                for (int32_t i : parts_of[u]) {
+                    const bs::PairItem &p = sp.parts[i];
+                    int32_t steps = 0;
+                    if (p.list_begin < 0 || p.list_end < p.list_begin || (size_t)p.list_end > sp.ranges.size()) return BS_EINVAL;
+                    for (int32_t r = p.list_begin; r < p.list_end; ++r) {
+                        const int32_t b = sp.ranges[r].begin, e = sp.ranges[r].end_states >> 4;
+                        if (b < 0 || e <= b || e > tm->N) return BS_EINVAL;
+                        for (int32_t t = b; t < e; ++t) {
+                            if (got[t] != 0) return BS_EINVAL;
+                            got[t] = (uint8_t)(sp.ranges[r].end_states & 15);
+                        }
+                        steps += e - b;
+                    }
+                    if (steps != p.n_tiles) return BS_EINVAL;
+                    const int32_t slot = p.classes >> 16;   // slot + 1, 0: not a part
+                    if ((slot > 0) != (n > 1) || slot > sp.n_slots) return BS_EINVAL;
+                    if (slot > 0) {
+                        if (slot_used[slot - 1]) return BS_EINVAL;
+                        slot_used[slot - 1] = 1;
+                        first_slot = std::min(first_slot, slot - 1);
+                        last_slot = std::max(last_slot, slot - 1);
+                    }
+                }
+                if (want != got) return BS_EINVAL;
+                if (n > 1) {
+                    if (last_slot - first_slot != n - 1) return BS_EINVAL;   // one behind the other: the merge walks them
+                    ++cut_units;
+                    cut.push_back({it.head_a, it.tile_a, first_slot, n << 1});
+                    if (it.head_b >= 0) cut.push_back({it.head_b, it.tile_b, first_slot, n << 1 | 1});
+                }
+            }
+            auto less = [](const bs::CutItem &a, const bs::CutItem &b) { return a.head != b.head ? a.head < b.head : a.tile < b.tile; };
+            std::vector<bs::CutItem> have = sp.cut;
+            std::sort(have.begin(), have.end(), less);
+            std::sort(cut.begin(), cut.end(), less);
+            if (have.size() != cut.size() || std::find(slot_used.begin(), slot_used.end(), 0) != slot_used.end()) return BS_EINVAL;
+            for (size_t i = 0; i < cut.size(); ++i)
+                if (have[i].head != cut[i].head || have[i].tile != cut[i].tile || have[i].first_slot != cut[i].first_slot ||
+                    have[i].n_parts_item != cut[i].n_parts_item) return BS_EINVAL;
+        }
+        if (n_parts) *n_parts = (int64_t)sp.parts.size();
+        if (n_cut_units) *n_cut_units = cut_units;
+        if (n_queued) *n_queued = sp.share_off.empty() ? 0 : sp.queue_off[8] - sp.queue_off[0];
     } catch (const std::bad_alloc &) {
         return BS_ENOMEM;
     }
