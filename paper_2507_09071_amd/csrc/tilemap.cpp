@@ -963,7 +963,7 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
     const int64_t bucket = std::max<int64_t>(1, least / 8);
     std::vector<std::pair<int64_t, int32_t>> order(n_units);
     for (int32_t u = 0; u < n_units; ++u)
-        order[u] = {(-(plan.items[u].n_tiles / bucket) << 32) + plan.items[u].head_a / G, u};
+        order[u] = {-(plan.items[u].n_tiles / bucket) * ((int64_t)1 << 32) + plan.items[u].head_a / G, u};
     std::sort(order.begin(), order.end());
     using Load = std::pair<int64_t, int32_t>;   // steps given to a workgroup, the workgroup
     // what the queues need: heaviest first onto the workgroup that is free first
