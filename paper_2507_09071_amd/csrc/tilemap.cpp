@@ -497,7 +497,7 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
         const int32_t n_free = P.n_free(L);
         if ((flags & BS_MAP_PACK_KEYS) && n_spans > 0 && n_free > 0 && n_free < L) {
             tm->packed = true;
-            tm->N = tm->N0 + (n_free + block_n - 1) / block_n;
+            tm->N = tm->N0 + (int32_t)(((int64_t)n_free + block_n - 1) / block_n);
         }
 
         // Order of the query rows.  Natural: tile m holds rows m*bm ... .  Regrouped: the image
@@ -507,13 +507,14 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
         // text rows stop costing the image rows of the sparse classes their skipped tiles.
         {
             const int32_t n_txt = P.n_text(L) - P.n_text(q_begin), n_img = L - q_begin - n_txt;
+            auto tiles = [&](int32_t rows) { return (int32_t)(((int64_t)rows + block_m - 1) / block_m); };   // (any block_m fits)
             if ((flags & BS_MAP_REGROUP_ROWS) && n_txt > 0 && n_img > 0) {   // else nothing to separate
                 P.regrouped = tm->regrouped = true;
                 P.n_img_rows = n_img;
-                P.m_img = (n_img + block_m - 1) / block_m;
-                tm->M = P.m_img + (n_txt + block_m - 1) / block_m;
+                P.m_img = tiles(n_img);
+                tm->M = P.m_img + tiles(n_txt);
             } else {
-                tm->M = (L - q_begin + block_m - 1) / block_m;
+                tm->M = tiles(L - q_begin);
             }
         }
 
@@ -654,7 +655,7 @@ int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, 
     };
     const int32_t text0 = n_text(q_begin), img0 = q_begin - text0;   // text / image tokens before the first row
     if (m < m_img) {   // image rows j0 .. j1 - 1 of all image tokens
-        const int32_t j0 = img0 + m * bm, j1 = img0 + std::min((m + 1) * bm, n_img_rows);
+        const int32_t j0 = img0 + m * bm, j1 = img0 + (int32_t)std::min<int64_t>((int64_t)(m + 1) * bm, n_img_rows);
         auto it = std::upper_bound(spans.begin(), spans.begin() + n_spans, j0, [](int32_t j, const SpanInfo &s) { return j < s.start - s.text_before; }) - 1;
         for (int32_t j = j0; j < j1; ++it) {
             const int32_t a = it->start + (j - (it->start - it->text_before)), b = std::min(it->end, a + (j1 - j));
@@ -663,7 +664,7 @@ int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, 
         }
         return j1 - j0;
     }
-    const int32_t t0 = text0 + (m - m_img) * bm, t1 = std::min(t0 + bm, spans[n_spans].text_before);
+    const int32_t t0 = text0 + (m - m_img) * bm, t1 = (int32_t)std::min<int64_t>((int64_t)t0 + bm, spans[n_spans].text_before);
     auto it = std::upper_bound(spans.begin(), spans.end(), t0, [](int32_t t, const SpanInfo &s) { return t < s.text_before; });
     for (int32_t t = t0; t < t1; ++it) {   // the text before *it
         if (it->text_before <= t) continue;
@@ -1279,10 +1280,10 @@ extern "C" int bs_tilemap_key_order(const bs_tilemap *tm, int32_t *keys, int32_t
 {
     if (!tm) return BS_EINVAL;
     if (keys) {
-        for (int32_t s = 0; s < tm->N0 * tm->bn; ++s) keys[s] = s < tm->L ? s : -1;
+        const int64_t n_slots = (int64_t)tm->N0 * tm->bn, n_compact = (int64_t)(tm->N - tm->N0) * tm->bn;
+        for (int64_t s = 0; s < n_slots; ++s) keys[s] = s < tm->L ? (int32_t)s : -1;
         const int32_t n_free = tm->geo.n_free(tm->L);
-        for (int32_t s = 0; s < (tm->N - tm->N0) * tm->bn; ++s)
-            keys[(size_t)tm->N0 * tm->bn + s] = s < n_free ? tm->geo.free_position(s) : -1;
+        for (int64_t s = 0; s < n_compact; ++s) keys[n_slots + s] = s < n_free ? tm->geo.free_position((int32_t)s) : -1;
     }
     if (n_prompt_tiles) *n_prompt_tiles = tm->N0;
     return BS_OK;
