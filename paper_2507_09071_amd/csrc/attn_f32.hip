@@ -92,25 +92,35 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
     auto load16 = [&](const char *src, uint32_t off, uint32_t dst) __attribute__((always_inline)) {
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(src), "s"(dst) : "memory", "m0");
     };
+    auto load16_at = [&](const char *src, uint32_t dst) __attribute__((always_inline)) {
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(dst) : "memory", "m0");
+    };
     auto issue_tile = [&](const char *kh, const char *vh, int n, int stage) __attribute__((always_inline)) {
         const uint32_t dst = lds_base + stage * 2 * TILE + wave * NI * 1024;
-        const bool whole = n * kBlockN + kBlockN <= L && n < a.n_prompt_tiles;
-        const char *kt = whole ? kh + (size_t)n * TILE : kh, *vt = whole ? vh + (size_t)n * TILE : vh;
-        uint32_t row_off[NI];
-#pragma unroll
-        for (int j = 0; j < NI; ++j) row_off[j] = (ld_row + j * (64 / CHUNKS)) * ROWB;
-        if (!whole) {   // the last keys, or a compact tile, whose slots name the keys; a slot without a key is masked
+        if (n * kBlockN + kBlockN <= L && n < a.n_prompt_tiles) {
+            const char *kt = kh + (size_t)n * TILE, *vt = vh + (size_t)n * TILE;
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
-                const int s = n * kBlockN + ld_row + j * (64 / CHUNKS);
-                row_off[j] = (uint32_t)(n < a.n_prompt_tiles ? min(s, L - 1) : max(compact_keys[s - a.n_prompt_tiles * kBlockN], 0)) * ROWB;
+                const int r = ld_row + j * (64 / CHUNKS);
+                load16(kt, r * ROWB + ((ld_chunk ^ (r & 15)) << 4), dst + j * 1024);
+                load16(vt, r * ROWB + (ld_chunk << 4), dst + TILE + j * 1024);
             }
+            return;
+        }
+        // the last keys, or a compact tile, whose slots name the keys (a slot without a key is masked): an address of its own
+        // for every lane, in 64 bits, since a key may lie anywhere in the KV head
+        int key[NI];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int s = n * kBlockN + ld_row + j * (64 / CHUNKS);
+            key[j] = n < a.n_prompt_tiles ? min(s, L - 1) : max(compact_keys[s - a.n_prompt_tiles * kBlockN], 0);
         }
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int r = ld_row + j * (64 / CHUNKS);
-            load16(kt, row_off[j] + ((ld_chunk ^ (r & 15)) << 4), dst + j * 1024);
-            load16(vt, row_off[j] + (ld_chunk << 4), dst + TILE + j * 1024);
+            const size_t at = (size_t)key[j] * ROWB;
+            load16_at(kh + at + ((ld_chunk ^ (r & 15)) << 4), dst + j * 1024);
+            load16_at(vh + at + (ld_chunk << 4), dst + TILE + j * 1024);
         }
     };
 
