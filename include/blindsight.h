@@ -243,10 +243,11 @@ int bs_tilemap_rebind(bs_tilemap *tm, const uint8_t *head_class, int32_t n_q_hea
 /*
  * Do, ahead of time, everything bs_attn_prefill would do on the first call with this map and these
  * arguments except the kernels: upload the prompt part (once per map), plan and upload the work list
- * (BS_F32) or the work units for `gqa_group` (BS_BF16) of the current class vector, raise the kernels'
- * dynamic-LDS limits and look up the address of the static scratch on the current device.  Enqueues
- * copies on `stream`, does not wait.  May allocate (block cache / hipMalloc, pinned staging).  After it,
- * bs_attn_prefill_static with the same map, class vector and gqa_group allocates nothing.
+ * (BS_F32, for either head dimension, with the workspace of the call) or the work units for `gqa_group`
+ * (BS_BF16) of the current class vector, raise the kernels' dynamic-LDS limits and look up the address
+ * of the static scratch on the current device.  Enqueues copies on `stream`, does not wait.  May allocate
+ * (block cache / hipMalloc, pinned staging).  After it, an fp32 call and, with the same map, class vector and
+ * gqa_group, bs_attn_prefill_static allocate nothing.
  * Errors: BS_EINVAL, BS_EUNSUPPORTED, BS_ENOMEM, BS_EHIP.
  */
 int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_group, void *stream);

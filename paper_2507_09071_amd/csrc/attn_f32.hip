@@ -234,29 +234,29 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
     }
 }
 
-size_t f32_workspace(const DeviceMap *d, int32_t head_dim)
+size_t f32_workspace(const ShareSet &shares, int32_t head_dim)
 {
-    return (size_t)d->n_slots * 4 * (head_dim == 128 ? kCutItemFloats<128> : kCutItemFloats<64>);
+    return (size_t)shares.n_slots * 4 * (head_dim == 128 ? kCutItemFloats<128> : kCutItemFloats<64>);
 }
 
 template <int D>
-static void launch_f32_dim(const KernelArgs &a, const DeviceMap *d, void *workspace, hipStream_t st)
+static void launch_f32_dim(const KernelArgs &a, const DeviceMap *d, const ShareSet &sh, void *workspace, hipStream_t st)
 {
-    const bool shares = d->n_shares > 0;
+    const bool shares = sh.n_shares > 0;
     float *cut_results = static_cast<float *>(workspace);
-    hipLaunchKernelGGL(attn_prefill_f32<D>, dim3((unsigned)(shares ? d->n_shares : d->n_pairs)), dim3(kF32Threads), f32_lds_bytes<D>(), st,
+    hipLaunchKernelGGL(attn_prefill_f32<D>, dim3((unsigned)(shares ? sh.n_shares : d->n_pairs)), dim3(kF32Threads), f32_lds_bytes<D>(), st,
                        a, d->text_bits, d->sink_bits, d->rows, d->compact_keys,
-                       shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges,
-                       shares ? d->share_off : nullptr, cut_results);
-    if (shares && d->n_cut > 0)
-        hipLaunchKernelGGL((merge_cut_items<D, 1, float>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
+                       shares ? sh.items : d->pair_items, shares ? sh.ranges : d->pair_ranges,
+                       shares ? sh.off : nullptr, cut_results);
+    if (shares && sh.n_cut > 0)
+        hipLaunchKernelGGL((merge_cut_items<D, 1, float>), dim3((unsigned)sh.n_cut, 4, D / 32), dim3(64), 0, st, a, sh.cut_items,
                            d->rows, cut_results);
 }
 
-void launch_f32(const KernelArgs &a, const DeviceMap *d, void *workspace, int32_t head_dim, hipStream_t st)
+void launch_f32(const KernelArgs &a, const DeviceMap *d, const ShareSet &shares, void *workspace, int32_t head_dim, hipStream_t st)
 {
-    if (head_dim == 128) launch_f32_dim<128>(a, d, workspace, st);
-    else launch_f32_dim<64>(a, d, workspace, st);
+    if (head_dim == 128) launch_f32_dim<128>(a, d, shares, workspace, st);
+    else launch_f32_dim<64>(a, d, shares, workspace, st);
 }
 
 hipError_t f32_device_setup()

@@ -945,10 +945,10 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
 }
 
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
-// holds these tiles already and the binding was just uploaded, its queue counters at zero.
+// holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.
 template <int D>
 void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t pack_bytes,
-                 int n_kv_heads, int n_cus, bool shares, bool kv_packed, hipStream_t st, void *ev_main_start)
+                 int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
 {
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     float *cut_results = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * pack_bytes);
@@ -956,16 +956,16 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
     const int32_t in_place = d->k_in_place;
     const dim3 tgrid((unsigned)(2 * tm->N - in_place), (unsigned)n_kv_heads);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
-    const dim3 pgrid((unsigned)(shares ? d->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
+    const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     if (!kv_packed)
         hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
                            static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, in_place, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                       d->sink_bits, d->rows, shares ? d->share_items : d->pair_items, shares ? d->share_ranges : d->pair_ranges, kp, vt, tm->N, in_place,
-                       d->queue_ctr, shares ? d->share_queue_off : d->queue_off, shares ? d->share_off : nullptr, cut_results);
-    if (shares && d->n_cut > 0)
-        hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)d->n_cut, 4, D / 32), dim3(64), 0, st, a, d->cut_items,
+                       d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->N, in_place,
+                       d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
+    if (sh && sh->n_cut > 0)
+        hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
                            d->rows, cut_results);
 }
 
@@ -981,9 +981,21 @@ int32_t tiles_in_place(const bs_tilemap *tm, const DeviceMap *d, int n_kv_heads,
 }
 
 // Bytes of the results of cut units (0 without equal shares).
-size_t cut_bytes(const DeviceMap *d, int head_dim)
+size_t cut_bytes(const bs::ShareSet &shares, int head_dim)
 {
-    return (size_t)d->n_slots * 2 * 4 * (head_dim == 128 ? bs::kCutItemFloats<128> : bs::kCutItemFloats<64>);
+    return (size_t)shares.n_slots * 2 * 4 * (head_dim == 128 ? bs::kCutItemFloats<128> : bs::kCutItemFloats<64>);
+}
+
+// The workspace of the map's calls, owned by the map: at least `bytes`, for work queued on `st` after this.
+int take_workspace(DeviceMap *d, size_t bytes, hipStream_t st)
+{
+    if (d->vt_bytes >= bytes) return BS_OK;
+    bs::pool_release(d->device, d->vt_buf, d->vt_bytes, d->last_use);
+    d->vt_buf = nullptr; d->vt_bytes = 0;
+    const hipError_t e = bs::pool_acquire(d->device, bytes, st, &d->vt_buf, &d->vt_bytes);
+    if (e == hipSuccess) return BS_OK;
+    d->vt_buf = nullptr; d->vt_bytes = 0;
+    return bs::fail_hip(e, "hipMalloc(workspace)");
 }
 
 size_t bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
@@ -1020,7 +1032,14 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
     int n_cus = 0;
     if ((rc = device_setup(dev, &unused, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
-    rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_cus, st);   // (fp32: head dimension 128)
+    if (dtype == BS_BF16) {
+        rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_cus, 0, st);
+    } else {   // for either head dimension, and the workspace of the larger plan
+        const int32_t wgs128 = n_cus * bs::f32_wgs_per_cu(128), wgs64 = n_cus * bs::f32_wgs_per_cu(64);
+        rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, wgs128, wgs64, st);
+        if (rc == BS_OK)
+            rc = take_workspace(d, std::max(bs::f32_workspace(*d->shares_for(wgs128), 128), bs::f32_workspace(*d->shares_for(wgs64), 64)), st);
+    }
     if (rc != BS_OK) return rc;
     e = hipEventRecord(d->last_use->ev, st);
     return e == hipSuccess ? BS_OK : bs::fail_hip(e, "hipEventRecord");
@@ -1060,42 +1079,32 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
     const uint64_t bound = d->bind_epoch;
     if (!rows.use || rows.need_bits)
         if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
-    if (!rows.use) {
-        rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group,
-                                dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim), st);
-        if (rc != BS_OK) return rc;
-    }
+    const int32_t n_wgs = dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim);
+    if (!rows.use)
+        if ((rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_wgs, 0, st)) != BS_OK) return rc;
 
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
-    // workspace of the call, owned by the map
-    auto workspace = [&](size_t bytes) {
-        if (d->vt_bytes >= bytes) return BS_OK;
-        bs::pool_release(dev, d->vt_buf, d->vt_bytes, d->last_use);
-        d->vt_buf = nullptr; d->vt_bytes = 0;
-        e = bs::pool_acquire(dev, bytes, st, &d->vt_buf, &d->vt_bytes);
-        if (e == hipSuccess) return BS_OK;
-        d->vt_buf = nullptr; d->vt_bytes = 0;
-        return bs::fail_hip(e, "hipMalloc(workspace)");
-    };
     if (rows.use) {
-        if ((rc = workspace(rows.workspace)) != BS_OK) return rc;
+        if ((rc = take_workspace(d, rows.workspace, st)) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         bs::launch_rows(rows, q, k, v, out, tm, d, d->vt_buf, gqa_group, head_dim, scale, st);
     } else if (dtype == BS_BF16) {
         // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
         const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
-        const bool shares = d->n_shares > 0;
+        const bs::ShareSet &shares = *d->shares_for(n_wgs);
+        const bs::ShareSet *const sh = shares.n_shares > 0 ? &shares : nullptr;
         const void *const old_workspace = d->vt_buf;
-        if ((rc = workspace(2 * pack_bytes + cut_bytes(d, head_dim))) != BS_OK) return rc;
+        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) return rc;
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
         if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, shares, packed, st, ev_main_start);
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
     } else {
-        if ((rc = workspace(bs::f32_workspace(d, head_dim))) != BS_OK) return rc;
+        const bs::ShareSet &shares = *d->shares_for(n_wgs);
+        if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
-        bs::launch_f32(a, d, d->vt_buf, head_dim, st);
+        bs::launch_f32(a, d, shares, d->vt_buf, head_dim, st);
     }
     if (kv_packed) *kv_packed = !rows.use && dtype == BS_BF16;
     e = hipGetLastError();
@@ -1137,13 +1146,14 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
     // units are cut only if their partial results fit behind the packed tiles
-    const bool shares = d->n_shares > 0 && 2 * pack_bytes + cut_bytes(d, head_dim) <= kStaticScratchBytes;
+    const bs::ShareSet *sh = d->shares_for(n_cus);
+    if (sh && (sh->n_shares == 0 || 2 * pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes)) sh = nullptr;
     d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, false, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, shares, false, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, sh, false, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

@@ -39,6 +39,18 @@ struct RowRecord {
     int32_t cfree_lo, cfree_hi;   // compact slots of the free keys inside the own image
 };
 
+// Equal shares of the bound units for `n_wgs` workgroups, instead of the queues.
+struct ShareSet {
+    int32_t n_wgs = 0;                    // 0: not made
+    int32_t n_shares = 0;                 // 0: not worth it
+    int32_t n_cut = 0, n_slots = 0;
+    const int4 *items = nullptr;          // the parts, ...
+    const int2 *ranges = nullptr;
+    const int32_t *off = nullptr;         // ... [n_shares + 1] the parts of each workgroup, ...
+    const int32_t *queue_off = nullptr;   // ... [9] the parts for whoever is done first, ...
+    const int4 *cut_items = nullptr;      // ... [n_cut] the items whose results come in parts
+};
+
 struct DeviceMap {
     int device = -1;
     // ---- prompt part: one block, uploaded once
@@ -54,17 +66,11 @@ struct DeviceMap {
     int32_t bind_kind = kBindNone;
     int32_t bind_G = 0;
     uint64_t bind_epoch = 0;              // class_epoch of the map the binding was made for
-    int32_t bind_wgs = 0;                 // workgroups the shares were cut for
     const int4 *pair_items = nullptr;     // work units, two int4 each
     const int2 *pair_ranges = nullptr;
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])
-    const int4 *share_items = nullptr;    // equal shares instead of the queues (null: not worth it): the parts, ...
-    const int2 *share_ranges = nullptr;
-    const int32_t *share_off = nullptr;   // ... [n_shares + 1] the parts of each workgroup, ...
-    const int32_t *share_queue_off = nullptr;   // ... [9] the parts for whoever is done first, ...
-    const int4 *cut_items = nullptr;      // ... [n_cut] the items whose results come in parts
-    int32_t n_shares = 0, n_cut = 0, n_slots = 0;
+    ShareSet shares[2];                   // the second for an fp32 map that was prepared, whose head dimension is not known yet
     int64_t n_steps = 0;                  // key-tile steps of the work units
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
@@ -73,6 +79,13 @@ struct DeviceMap {
     int32_t k_in_place = 0;               // key tiles of K that the last call read in place (see pack_k_tile)
     hipStream_t last_stream = nullptr;    // stream of the most recent upload / launch (compared, never used)
     std::shared_ptr<EventHolder> last_use;   // recorded after the most recent upload / launch
+
+    const ShareSet *shares_for(int32_t n_wgs) const   // null: not made for so many workgroups
+    {
+        for (const ShareSet &s : shares)
+            if (s.n_wgs == n_wgs) return &s;
+        return nullptr;
+    }
 };
 
 // A device block of at least `bytes`, safe to use in work queued on `st` after this call.  Blocks
@@ -96,7 +109,8 @@ void staging_abandon(const Staging &s);
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Make the prompt part (once per map) / upload the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, hipStream_t st);
+// The shares are cut for n_wgs workgroups, and for n_wgs_too if that is not 0.
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st);
 // Order work queued on `st` after the map's previous use if that was on another stream.
 int order_after_last_use(DeviceMap *d, hipStream_t st);
 

@@ -433,21 +433,26 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, hipStream_t st)
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st)
 {
     DeviceMap *d = tm->dev;
     if (!d) return BS_EINVAL;
     if (kind == kBindSolo) gqa_group = 0;   // its units do not depend on it
-    if (d->bind_kind == kind && d->bind_G == gqa_group && d->bind_wgs == n_wgs && d->bind_epoch == tm->class_epoch) return BS_OK;
+    if (d->bind_kind == kind && d->bind_G == gqa_group && d->bind_epoch == tm->class_epoch && d->shares_for(n_wgs) &&
+        (n_wgs_too == 0 || d->shares_for(n_wgs_too))) return BS_OK;
+    SharePlan too;   // the plan for n_wgs_too
     try {
+        if (n_wgs_too != 0) {
+            bs_plan_shares(tm, gqa_group, n_wgs_too);
+            too = tm->shares;
+        }
         bs_plan_shares(tm, gqa_group, n_wgs);   // and the pair or solo plan it is made from
     } catch (const std::bad_alloc &) {
         return BS_ENOMEM;
     }
     const PairPlan &plan = kind == kBindPairPlan ? tm->pairs : tm->solo;
     if (plan.ranges.size() >= (size_t)INT32_MAX) return BS_EUNSUPPORTED;
-    const SharePlan &shares = tm->shares;
-    const bool shared = !shares.share_off.empty();
+    const SharePlan *const share_plans[2] = {&tm->shares, &too};
     // the parts of the block, one after the other: units, their ranges, queue offsets [9] and counters [8 at + 64 B]; then
     // equal shares: parts, their ranges, share offsets, queue offsets, cut items
     size_t bytes = 0;
@@ -455,11 +460,15 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     const size_t off_a = section(plan.items.size() * sizeof(PairItem));
     const size_t off_b = section(std::max<size_t>(plan.ranges.size(), 1) * sizeof(PairRange));
     const size_t off_q = section(256);
-    const size_t off_si = section(shares.parts.size() * sizeof(PairItem));
-    const size_t off_sr = section(shares.ranges.size() * sizeof(PairRange));
-    const size_t off_so = section(shares.share_off.size() * 4);
-    const size_t off_sq = section(sizeof shares.queue_off);
-    const size_t off_sc = section(shares.cut.size() * sizeof(CutItem));
+    size_t off_s[2][5];
+    for (int i = 0; i < 2; ++i) {
+        const SharePlan &s = *share_plans[i];
+        off_s[i][0] = section(s.parts.size() * sizeof(PairItem));
+        off_s[i][1] = section(s.ranges.size() * sizeof(PairRange));
+        off_s[i][2] = section(s.share_off.size() * 4);
+        off_s[i][3] = section(s.share_off.empty() ? 0 : sizeof s.queue_off);
+        off_s[i][4] = section(s.cut.size() * sizeof(CutItem));
+    }
 
     Staging sg;
     hipError_t e = staging_begin(bytes, &sg);
@@ -471,11 +480,14 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     put(off_b, plan.ranges);
     std::memset(host + off_q, 0, 256);
     std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
-    put(off_si, shares.parts);
-    put(off_sr, shares.ranges);
-    put(off_so, shares.share_off);
-    std::memcpy(host + off_sq, shares.queue_off, sizeof shares.queue_off);
-    put(off_sc, shares.cut);
+    for (int i = 0; i < 2; ++i) {
+        const SharePlan &s = *share_plans[i];
+        put(off_s[i][0], s.parts);
+        put(off_s[i][1], s.ranges);
+        put(off_s[i][2], s.share_off);
+        if (!s.share_off.empty()) std::memcpy(host + off_s[i][3], s.queue_off, sizeof s.queue_off);
+        put(off_s[i][4], s.cut);
+    }
     // a fresh block every time: kernels of an earlier binding may still be reading the old one,
     // which goes back to the cache behind the map's last-use event
     void *blob = nullptr;
@@ -500,7 +512,6 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     d->bind_cap = cap;
     d->bind_kind = kind;
     d->bind_G = gqa_group;
-    d->bind_wgs = n_wgs;
     d->bind_epoch = tm->class_epoch;
     d->pair_items = reinterpret_cast<const int4 *>(b + off_a);
     d->pair_ranges = reinterpret_cast<const int2 *>(b + off_b);
@@ -509,14 +520,19 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     for (const PairItem &it : plan.items) d->n_steps += it.n_tiles;
     d->queue_off = reinterpret_cast<const int32_t *>(b + off_q);
     d->queue_ctr = reinterpret_cast<int32_t *>(b + off_q + 64);
-    d->share_items = reinterpret_cast<const int4 *>(b + off_si);
-    d->share_ranges = reinterpret_cast<const int2 *>(b + off_sr);
-    d->share_off = reinterpret_cast<const int32_t *>(b + off_so);
-    d->share_queue_off = reinterpret_cast<const int32_t *>(b + off_sq);
-    d->cut_items = reinterpret_cast<const int4 *>(b + off_sc);
-    d->n_shares = shared ? (int32_t)shares.share_off.size() - 1 : 0;
-    d->n_cut = (int32_t)shares.cut.size();
-    d->n_slots = shares.n_slots;
+    for (int i = 0; i < 2; ++i) {
+        const SharePlan &s = *share_plans[i];
+        ShareSet &to = d->shares[i];
+        to.n_wgs = i == 0 ? n_wgs : n_wgs_too;
+        to.n_shares = s.share_off.empty() ? 0 : (int32_t)s.share_off.size() - 1;
+        to.n_cut = (int32_t)s.cut.size();
+        to.n_slots = s.n_slots;
+        to.items = reinterpret_cast<const int4 *>(b + off_s[i][0]);
+        to.ranges = reinterpret_cast<const int2 *>(b + off_s[i][1]);
+        to.off = reinterpret_cast<const int32_t *>(b + off_s[i][2]);
+        to.queue_off = reinterpret_cast<const int32_t *>(b + off_s[i][3]);
+        to.cut_items = reinterpret_cast<const int4 *>(b + off_s[i][4]);
+    }
     return BS_OK;
 }
 
