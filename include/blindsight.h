@@ -307,7 +307,9 @@ int bs_attn_prefill_ex(const void *q, const void *k, const void *v, void *out, b
  *            after every bs_tilemap_rebind; BS_EINVAL otherwise (bs_last_error says so)
  *   limit    n_kv_heads * n_k_tiles * head_dim * 256 bytes (packed K plus packed V^T) must fit the scratch:
  *            BS_EUNSUPPORTED otherwise, nothing launched (96 MiB hold 4 KV heads x 768 key tiles of d = 128:
- *            a 40K-token prompt with its compact tiles)
+ *            a 40K-token prompt with its compact tiles).  Partial results of work units that are cut (few rows
+ *            behind many keys) go behind the packed tiles or, if there is no room, to a workspace that
+ *            bs_tilemap_prepare takes
  * Every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU (two streams, two
  * threads) race on it; calls queued on one stream are safe.  The pre-pass rewrites every tile slot it
  * uses, so nothing needs clearing between calls.

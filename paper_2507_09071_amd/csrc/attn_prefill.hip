@@ -948,10 +948,9 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.
 template <int D>
 void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t pack_bytes,
-                 int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
+                 float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
 {
     __bf16 *kp = static_cast<__bf16 *>(workspace);
-    float *cut_results = reinterpret_cast<float *>(static_cast<char *>(workspace) + 2 * pack_bytes);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + pack_bytes);
     const int32_t in_place = d->k_in_place;
     const dim3 tgrid((unsigned)(2 * tm->N - in_place), (unsigned)n_kv_heads);
@@ -1034,6 +1033,12 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     if (dtype == BS_BF16) {
         rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_cus, 0, st);
+        if (rc == BS_OK) {   // results of cut units that have no room in the static scratch (the head dimension is not known yet)
+            const int n_kv_heads = tm->n_q_heads / gqa_group;
+            const size_t cut = cut_bytes(*d->shares_for(n_cus), 128);
+            if (2 * bf16_pack_bytes(tm, n_kv_heads, 64) <= kStaticScratchBytes &&
+                2 * bf16_pack_bytes(tm, n_kv_heads, 128) + cut > kStaticScratchBytes) rc = take_workspace(d, cut, st);
+        }
     } else {   // for either head dimension, and the workspace of the larger plan
         const int32_t wgs128 = n_cus * bs::f32_wgs_per_cu(128), wgs64 = n_cus * bs::f32_wgs_per_cu(64);
         rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, wgs128, wgs64, st);
@@ -1098,8 +1103,9 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) return rc;
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
         if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
@@ -1145,15 +1151,21 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
-    // units are cut only if their partial results fit behind the packed tiles
+    // the results of cut units go behind the packed tiles or, if they do not fit there, to the workspace that
+    // bs_tilemap_prepare took (too small only if a call at head dimension 64 made the binding: then nothing is cut)
     const bs::ShareSet *sh = d->shares_for(n_cus);
-    if (sh && (sh->n_shares == 0 || 2 * pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes)) sh = nullptr;
+    if (sh && sh->n_shares == 0) sh = nullptr;
+    float *cut = reinterpret_cast<float *>(static_cast<char *>(ws) + 2 * pack_bytes);
+    if (sh && 2 * pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes) {
+        cut = static_cast<float *>(d->vt_buf);
+        if (cut_bytes(*sh, head_dim) > d->vt_bytes) sh = nullptr;
+    }
     d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, sh, false, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, pack_bytes, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else launch_bf16<64>(a, tm, d, ws, pack_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);
