@@ -1142,7 +1142,8 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     int n_cus = 0;
     if ((rc = device_setup(dev, &ws, &n_cus)) != BS_OK) return rc;   // looks the address up on the first call per device
     const bs::RowsPlan rows = bs::plan_rows(tm, BS_BF16, gqa_group, head_dim, n_cus);
-    if ((rows.use ? rows.workspace : 2 * pack_bytes) > kStaticScratchBytes) {
+    // (one limit for all calls, although the few-row kernel would need less)
+    if (std::max(rows.workspace, 2 * pack_bytes) > kStaticScratchBytes) {
         snprintf(bs::g_last_error, sizeof bs::g_last_error,
                  "bs_attn_prefill_static: packed K / V^T tiles need %zu bytes, the static scratch holds %zu "
                  "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", 2 * pack_bytes, kStaticScratchBytes);
