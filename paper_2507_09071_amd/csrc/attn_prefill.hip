@@ -1093,6 +1093,8 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         if ((rc = take_workspace(d, rows.workspace, st)) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         bs::launch_rows(rows, q, k, v, out, tm, d, d->vt_buf, gqa_group, head_dim, scale, st);
+        d->rows_epoch = tm->class_epoch;
+        d->rows_G = gqa_group;
     } else if (dtype == BS_BF16) {
         // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
@@ -1129,9 +1131,14 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     int rc = check_call(q, k, v, out, tm, BS_BF16, n_q_heads, gqa_group, head_dim, scale);
     if (rc != BS_OK) return rc;
     DeviceMap *d = tm->dev;
-    if (!d || d->bind_kind != bs::kBindPairPlan || d->bind_G != gqa_group || d->bind_epoch != tm->class_epoch)
+    const auto not_prepared = [] {
         return bs::fail_msg(BS_EINVAL, "bs_attn_prefill_static: call bs_tilemap_prepare(tm, BS_BF16, gqa_group, stream) first "
                                        "(after every bs_tilemap_rebind); this entry point uploads and allocates nothing");
+    };
+    if (!d) return not_prepared();
+    const bool units_bound = d->bind_kind == bs::kBindPairPlan && d->bind_G == gqa_group && d->bind_epoch == tm->class_epoch;
+    const bool rows_bound = d->rows_G == gqa_group && d->rows_epoch == tm->class_epoch;
+    if (!units_bound && !rows_bound) return not_prepared();
     const int n_kv_heads = n_q_heads / gqa_group;
     const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
     int dev = -1;
@@ -1142,6 +1149,7 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     int n_cus = 0;
     if ((rc = device_setup(dev, &ws, &n_cus)) != BS_OK) return rc;   // looks the address up on the first call per device
     const bs::RowsPlan rows = bs::plan_rows(tm, BS_BF16, gqa_group, head_dim, n_cus);
+    if (!units_bound && !rows.use) return not_prepared();
     // (one limit for all calls, although the few-row kernel would need less)
     if (std::max(rows.workspace, 2 * pack_bytes) > kStaticScratchBytes) {
         snprintf(bs::g_last_error, sizeof bs::g_last_error,

@@ -71,6 +71,8 @@ struct DeviceMap {
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])
     ShareSet shares[2];                   // the second for an fp32 map that was prepared, whose head dimension is not known yet
+    uint64_t rows_epoch = 0;              // class_epoch and group size of the last call that the few-row kernel took: it needs
+    int32_t rows_G = 0;                   // no units, and prepares the map for the static entry as the upload of units does
     int64_t n_steps = 0;                  // key-tile steps of the work units
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
