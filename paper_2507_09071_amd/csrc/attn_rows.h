@@ -13,11 +13,12 @@ struct DeviceMap;
 struct RowsPlan {
     bool use = false;       // the few-row kernel takes the call
     bool need_bits = false; // some row needs the per-tile text / sink bit masks (the map's device copy)
+    bool check = false;     // rows may be handed keys that their tile lists skip (see merge_rows_checked)
     int32_t groups = 1;     // row groups per KV head
     int32_t row_blocks = 1; // 32-row blocks of a group (1 or 2)
     int32_t parts = 1;      // key ranges per (KV head, row group)
     int32_t k0 = 0, k1 = 0; // blocks of 32 keys that the rows see between them
-    size_t workspace = 0;   // bytes of partial results (0: one part, results go straight to `out`)
+    size_t workspace = 0;   // bytes of partial results (0: one part and no check, results go straight to `out`)
 };
 
 // dtype / head_dim / gqa_group as in bs_attn_prefill, already checked; n_cus: compute units of the device.

@@ -16,7 +16,9 @@
 //  * V^T comes out of LDS through the transposing 64-bit read; scores and softmax are as in the prefill kernel;
 //  * the four waves merge through LDS, the parts through a second, small kernel.
 // Masks: the rows see keys of the prompt in position order, every allowed pair once; a mask word is formed per
-// row and block from the row's bounds, its image and (image rows of sparse heads only) the text / sink bits.
+// row and block from the row's bounds, its image and (image rows of sparse heads only) the text / sink bits.  The values of
+// every key are multiplied, masked ones by zero: where a tile list would have skipped some, the merge looks for results
+// that are not finite (merge_rows_checked).
 #include "attn_rows.h"
 
 #include <algorithm>
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
             const float4 y = stage[(w * ROWS + row) * CH4 + (ch ^ (row & 31 & (CH4 - 1)))];
             sum.x += y.x; sum.y += y.y; sum.z += y.z; sum.w += y.w;
         }
-        if (n_parts == 1) {
+        if (a.part_o == nullptr) {   // one part, and nothing to check
             const float inv = l > 0.f ? 1.f / l : 0.f;
             bf16x4 w;
             w[0] = (__bf16)(sum.x * inv); w[1] = (__bf16)(sum.y * inv); w[2] = (__bf16)(sum.z * inv); w[3] = (__bf16)(sum.w * inv);
@@ -370,15 +372,20 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     }
 }
 
-// Merges the parts: one workgroup per (head, row); its threads are D / 4 channel quads times the parts in flight.
+// Merges the parts of a (head, row): one workgroup; its threads are D / 4 channel quads times the parts in flight.  The
+// result is in the first D / 4 threads.
 template <int D>
-__global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
-                                                  __bf16 *__restrict__ out, int R, int G, int groups, int rows_per_group,
-                                                  int n_parts, float scale_log2e)
+struct MergeLds {
+    static constexpr int CH4 = D / 4, LANES = 256 / CH4;   // parts handled side by side
+    float4 acc[LANES][CH4];
+    float m_wave[4], l_wave[4];
+};
+
+template <int D>
+__device__ inline bf16x4 merge_parts(MergeLds<D> &lds, const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
+                                     int R, int G, int groups, int rows_per_group, int n_parts, float scale_log2e)
 {
-    constexpr int CH4 = D / 4, LANES = 256 / CH4;   // parts handled side by side
-    __shared__ float4 acc[LANES][CH4];
-    __shared__ float m_wave[4], l_wave[4];
+    constexpr int CH4 = MergeLds<D>::CH4, LANES = MergeLds<D>::LANES;
     const int head = blockIdx.x / R, r = blockIdx.x % R;
     const int kvh = head / G, s = (head % G) * R + r;
     const int grp = s / rows_per_group, row = s % rows_per_group;
@@ -403,9 +410,9 @@ __global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part
     for (int p = kAtOnce * LANES + tid; p < n_parts; p += 256) m = fmaxf(m, part_ml[base + (size_t)p * rows_per_group].x);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((tid & 63) == 0) m_wave[tid >> 6] = m;
+    if ((tid & 63) == 0) lds.m_wave[tid >> 6] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(m_wave[0], m_wave[1]), fmaxf(m_wave[2], m_wave[3]));
+    m = fmaxf(fmaxf(lds.m_wave[0], lds.m_wave[1]), fmaxf(lds.m_wave[2], lds.m_wave[3]));
 
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
     float l = 0.f;
@@ -421,25 +428,121 @@ __global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part
         const size_t at = base + (size_t)p * rows_per_group;
         add(part_ml[at], *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch));
     }
-    acc[tid / CH4][ch] = sum;
+    lds.acc[tid / CH4][ch] = sum;
     float l_lane = ch == 0 ? l : 0.f;   // every channel lane of a part holds the same l
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) l_lane += __shfl_xor(l_lane, off, 64);
-    if ((tid & 63) == 0) l_wave[tid >> 6] = l_lane;
+    if ((tid & 63) == 0) lds.l_wave[tid >> 6] = l_lane;
     __syncthreads();
+    bf16x4 w;
+    w[0] = w[1] = w[2] = w[3] = (__bf16)0.f;
     if (tid < CH4) {
-        const float l_tot = (l_wave[0] + l_wave[1]) + (l_wave[2] + l_wave[3]);
+        const float l_tot = (lds.l_wave[0] + lds.l_wave[1]) + (lds.l_wave[2] + lds.l_wave[3]);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        float4 t = acc[0][tid];
+        float4 t = lds.acc[0][tid];
 #pragma unroll
         for (int i = 1; i < LANES; ++i) {
-            const float4 y = acc[i][tid];
+            const float4 y = lds.acc[i][tid];
             t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
         }
-        bf16x4 w;
         w[0] = (__bf16)(t.x * inv); w[1] = (__bf16)(t.y * inv); w[2] = (__bf16)(t.z * inv); w[3] = (__bf16)(t.w * inv);
-        *reinterpret_cast<bf16x4 *>(out + (size_t)blockIdx.x * D + 4 * tid) = w;
     }
+    return w;
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
+                                                  __bf16 *__restrict__ out, int R, int G, int groups, int rows_per_group,
+                                                  int n_parts, float scale_log2e)
+{
+    __shared__ MergeLds<D> lds;
+    const bf16x4 w = merge_parts<D>(lds, part_o, part_ml, R, G, groups, rows_per_group, n_parts, scale_log2e);
+    if (threadIdx.x < D / 4) *reinterpret_cast<bf16x4 *>(out + (size_t)blockIdx.x * D + 4 * threadIdx.x) = w;
+}
+
+// The same where rows are handed keys that their head's tile lists skip (see plan_rows).  The attention kernel multiplies
+// the values of such a key by a probability of zero, and an infinity or a NaN there is a NaN in the result.  A row whose
+// result is not finite is computed again here, a key at a time, from the keys that it sees and nothing else: rare, so
+// what counts is that the usual row pays one vote for it (20 rows under 28 heads behind 1K / 39.5K keys: 18.4 / 51.6 us,
+// unchecked 18.1 / 51.0; up to 128 keys, one part, take this launch on top: 12.9 -> 17.9, the prefill kernel 20.6).
+template <int D>
+__global__ __launch_bounds__(256) void merge_rows_checked(const RowsArgs a, int groups, int rows_per_group, int n_parts)
+{
+    constexpr int CH4 = MergeLds<D>::CH4, LANES = MergeLds<D>::LANES;
+    __shared__ MergeLds<D> lds;
+    __shared__ float p_key[256];   // probabilities of 256 keys, negative: not seen
+    const int tid = threadIdx.x;
+    bf16x4 w = merge_parts<D>(lds, a.part_o, a.part_ml, a.R, a.G, groups, rows_per_group, n_parts, a.scale_log2e);
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad = bad || !(fabsf((float)w[e]) < INFINITY);
+    if (__syncthreads_or(bad)) {
+        const int head = blockIdx.x / a.R;
+        const RowBounds b = a.rows[blockIdx.x % a.R];
+        const int cls = (a.classes[head >> 4] >> (2 * (head & 15))) & 3;
+        const bool sees_all = cls == BS_DENSE || b.img_hi == b.img_lo;
+        const __bf16 *q = static_cast<const __bf16 *>(a.q) + (size_t)blockIdx.x * D;
+        const __bf16 *k = static_cast<const __bf16 *>(a.k) + (size_t)(head / a.G) * a.L * D;
+        const __bf16 *v = static_cast<const __bf16 *>(a.v) + (size_t)(head / a.G) * a.L * D;
+        const int ch = tid % CH4;
+        float m = -INFINITY, l = 0.f;
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int n0 = b.first; n0 <= b.last; n0 += 256) {
+            const int n = n0 + tid;
+            bool seen = n <= b.last;
+            if (seen && !sees_all) {
+                const bool own = (cls & 2) && n >= b.img_lo && n < b.img_hi;
+                const uint64_t free_keys = a.text_bits[n >> 6] | ((cls & 1) ? a.sink_bits[n >> 6] : 0ull);
+                seen = own || ((free_keys >> (n & 63)) & 1);
+            }
+            float s = -INFINITY;
+            if (seen) {
+                s = 0.f;
+                for (int c = 0; c < D; c += 8) {
+                    const bf16x8 x = *reinterpret_cast<const bf16x8 *>(q + c), y = *reinterpret_cast<const bf16x8 *>(k + (size_t)n * D + c);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s = fmaf((float)x[e], (float)y[e], s);
+                }
+            }
+            float m_new = s;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m_new = fmaxf(m_new, __shfl_xor(m_new, off, 64));
+            if ((tid & 63) == 0) lds.m_wave[tid >> 6] = m_new;
+            __syncthreads();   // (and the probabilities of the last 256 keys have been read)
+            m_new = fmaxf(fmaxf(fmaxf(lds.m_wave[0], lds.m_wave[1]), fmaxf(lds.m_wave[2], lds.m_wave[3])), m);
+            const float ref = m_new == -INFINITY ? 0.f : m_new;   // no key so far, or none with a number for a score
+            p_key[tid] = seen ? __builtin_amdgcn_exp2f((s - ref) * a.scale_log2e) : -1.f;
+            const float alpha = __builtin_amdgcn_exp2f((m - ref) * a.scale_log2e);
+            m = m_new;
+            l *= alpha;
+            sum.x *= alpha; sum.y *= alpha; sum.z *= alpha; sum.w *= alpha;
+            __syncthreads();
+            for (int i = tid / CH4; i < 256; i += LANES) {
+                const float p = p_key[i];
+                if (p < 0.f) continue;
+                const bf16x4 y = *reinterpret_cast<const bf16x4 *>(v + (size_t)(n0 + i) * D + 4 * ch);
+                l += p;
+                sum.x = fmaf(p, (float)y[0], sum.x); sum.y = fmaf(p, (float)y[1], sum.y);
+                sum.z = fmaf(p, (float)y[2], sum.z); sum.w = fmaf(p, (float)y[3], sum.w);
+            }
+        }
+        __syncthreads();
+        lds.acc[tid / CH4][ch] = sum;
+        if (ch == 0) p_key[tid / CH4] = l;   // the channel lanes of a key hold the same sum
+        __syncthreads();
+        if (tid < CH4) {
+            float4 t = lds.acc[0][tid];
+            float l_tot = p_key[0];
+            for (int i = 1; i < LANES; ++i) {
+                const float4 y = lds.acc[i][tid];
+                t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
+                l_tot += p_key[i];
+            }
+            const float inv = l_tot > 0.f ? 1.f / l_tot : (l_tot == 0.f ? 0.f : l_tot);   // (a NaN stays one)
+            w[0] = (__bf16)(t.x * inv); w[1] = (__bf16)(t.y * inv); w[2] = (__bf16)(t.z * inv); w[3] = (__bf16)(t.w * inv);
+        }
+    }
+    if (tid < CH4) *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + (size_t)blockIdx.x * D + 4 * tid) = w;
 }
 
 RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32_t head_dim, int32_t n_cus)
@@ -474,7 +577,10 @@ RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32
     const int32_t wgs = n_cus * (head_dim == 64 ? 2 : 1);
     const int32_t n_blocks = p.k1 - p.k0;
     p.parts = std::max(1, std::min(wgs / std::max(1, n_kv * p.groups), (n_blocks + kRowsWaves - 1) / kRowsWaves));
-    if (p.parts > 1) p.workspace = (size_t)n_kv * p.groups * p.parts * p.row_blocks * 32 * (head_dim + 2) * sizeof(float);
+    // A row of an image may be handed keys here that no tile list of its head names: those of other images under a sparse
+    // head, those in front of its window or behind it that other rows see.
+    p.check = any_image;
+    if (p.parts > 1 || p.check) p.workspace = (size_t)n_kv * p.groups * p.parts * p.row_blocks * 32 * (head_dim + 2) * sizeof(float);
     return p;
 }
 
@@ -486,7 +592,10 @@ static void launch_rows_dim(const RowsPlan &plan, const RowsArgs &a, int n_kv, h
         hipLaunchKernelGGL((attn_rows_bf16<D, 1>), grid, block, RowsTraits<D>::kLds, st, a);
     else
         hipLaunchKernelGGL((attn_rows_bf16<D, 2>), grid, block, RowsTraits<D>::kLds, st, a);
-    if (plan.parts > 1)
+    if (plan.check)
+        hipLaunchKernelGGL(merge_rows_checked<D>, dim3((unsigned)(n_kv * a.G * a.R)), dim3(256), 0, st, a, plan.groups,
+                           plan.row_blocks * 32, plan.parts);
+    else if (plan.parts > 1)
         hipLaunchKernelGGL(merge_rows<D>, dim3((unsigned)(n_kv * a.G * a.R)), dim3(256), 0, st, a.part_o, a.part_ml,
                            static_cast<__bf16 *>(a.out), a.R, a.G, plan.groups, plan.row_blocks * 32, plan.parts, a.scale_log2e);
 }
@@ -497,8 +606,10 @@ void launch_rows(const RowsPlan &plan, const void *q, const void *k, const void 
     const int32_t n_kv = tm->n_q_heads / gqa_group;
     RowsArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out;
-    a.part_o = static_cast<float *>(workspace);
-    a.part_ml = reinterpret_cast<float2 *>(a.part_o + (size_t)n_kv * plan.groups * plan.parts * plan.row_blocks * 32 * head_dim);
+    if (plan.workspace > 0) {
+        a.part_o = static_cast<float *>(workspace);
+        a.part_ml = reinterpret_cast<float2 *>(a.part_o + (size_t)n_kv * plan.groups * plan.parts * plan.row_blocks * 32 * head_dim);
+    }
     if (plan.need_bits) { a.text_bits = d->text_bits; a.sink_bits = d->sink_bits; }
     a.L = tm->L; a.R = tm->L - tm->q_begin; a.G = gqa_group;
     a.k0 = plan.k0;
