@@ -127,8 +127,8 @@ int bs_build_tilemap_ex(const bs_span *spans, int32_t n_spans, int32_t seq_len,
  * (text queries too) and every class, only the keys with i - j < window (paper App. kernel, "Dense
  * Attention Subroutine": text queries follow the model's own dense mask, which is causal or a sliding
  * window depending on the model; the sparse masks live inside the dense mask).  0 = no window; a window of seq_len or
- * more is no window.  With a window BS_MAP_PACK_KEYS acts as BS_MAP_REGROUP_ROWS (a windowed query tile
- * visits a handful of key tiles: there is nothing to pack).  Together with BS_MAP_BIDIR_IMAGES the keys of
+ * more is no window.  With a window BS_MAP_PACK_KEYS acts as BS_MAP_REGROUP_ROWS (packed lists are not built
+ * for windows).  Together with BS_MAP_BIDIR_IMAGES the keys of
  * the query's own image stay visible at any distance, also for images longer than the window: an image
  * query then sees its class pattern inside [min(window start, image start), image end).
  * Errors: as bs_build_tilemap_ex; BS_EINVAL for a negative offset, count or window.
@@ -272,9 +272,11 @@ int bs_tilemap_upload(bs_tilemap *tm);
  *   scale    finite and > 0 (1/sqrt(d_k) in the paper)
  *   stream   hipStream_t (NULL = default stream).  The call only enqueues work; the caller
  *            owns q/k/v/out and keeps them alive until the stream has drained.
- * bf16 path: a pre-pass first packs K and V into per-key-tile blocks (V transposed) in a
- * workspace the map owns (2 x the size of K, taken from the library's block cache or hipMalloc
- * on first use).  Calls that share a map share that workspace: the library orders a call after
+ * bf16 path: a pre-pass first packs V (transposed) and, where a launch fetches it often, K into per-key-tile
+ * blocks in a workspace the map owns (2 x the size of K, and the partial results of work units that are
+ * cut; taken from the library's block cache or hipMalloc on first use).  Calls with a few rows that see the
+ * whole cache read K and V where they are; they and the fp32 path use the workspace for partial results.
+ * Calls that share a map share that workspace: the library orders a call after
  * the map's previous call when the stream changes, but two threads must not call with one map
  * at the same time.
  * The first call on a map uploads it: the arrays are staged through pinned host buffers and

@@ -1,11 +1,12 @@
 // Few query rows against a long KV cache: a decoding step (one row per head) or a handful of draft tokens.
 //
 // The 128-row query tiles of the prefill kernel are the wrong shape here.  The work is reading K and V once,
-// so the bound is HBM, and what the prefill path does around it (a packed copy of K and V, one workgroup per
-// two heads walking the whole cache) cost many times the read.  Measured, one row: 28 heads over 39.5K keys of
-// 4 KV heads (81 MB) 893 us there, 17.4 + 4.1 us here (4.7 TB/s in the first kernel; 18.5 + 5 with the query rows and
-// the rows' bounds loaded before the first keys were requested, and the merge waiting for memory twice); 32 heads over
-// 302K keys of 16 KV heads (2.5 GB) 7460 us there, 413 + 4 us here (6.0 TB/s; a large copy reaches 4.7).  How:
+// so the bound is HBM, and what the prefill path does around it (a packed copy of V, a K and V tile per two heads, units
+// cut over the chip and merged) costs a multiple of the read.  Measured, one row: 28 heads over 39.5K keys of
+// 4 KV heads (81 MB) 103 us there, 17.4 + 4.1 us here (4.7 TB/s in the first kernel, a kernel that only reads reaches 5.3
+// on so little; 18.5 + 5 with the query rows and the rows' bounds loaded before the first keys were requested, and the
+// merge waiting for memory twice); 32 heads over 302K keys of 16 KV heads (2.5 GB) 1060 us there, 413 + 4 us here (6.0
+// TB/s; a kernel that only reads reaches 6.2).  How:
 //  * the query rows of ALL heads of a GQA group are stacked (head-major) into blocks of 32 rows, the free
 //    dimension of a 32x32x16 MFMA, so K and V of a KV head are read once for the whole group;
 //  * the keys are split over the chip: grid (parts, KV heads, row groups), about one workgroup per CU; its
@@ -551,8 +552,10 @@ RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32
     const int32_t L = tm->L, R = L - tm->q_begin, n_kv = tm->n_q_heads / gqa_group;
     if (dtype != BS_BF16 || R > kRowsMaxRows || tm->n_q_heads > kRowsMaxHeads) return p;
     if (n_kv > 65535 || (int64_t)L * head_dim * 2 >= INT32_MAX) return p;
-    // Up to 32 rows: with 28 / 4 heads this kernel then takes 20 / 26 / 54 / 144 us at 1K / 8K / 39.5K / 140K keys,
-    // the prefill kernel 40 / 200 / 893 / 3125 (other head counts alike).
+    // Up to 32 rows: with 28 / 4 heads and 32 rows a call takes 19 / 26 / 54 / 141 us at 1K / 8K / 39.5K / 141K keys, through
+    // the prefill kernel 34 / 42 / 101 / 321; with 32 / 16 heads at 302K 428 and 1074, with 32 / 8 of d = 64 at 9K 22 and 37.
+    // (One row: 12 / 12 / 23 / 52 and 36 / 43 / 103 / 315.)  The limit is what the kernel's arguments hold of
+    // the rows' bounds, not where the two meet, which is further up.
     // Every block of keys is read for every head.  That is the work when a text row or a Dense head is there (both
     // see every earlier key); rows of images under sparse heads only keep the tile lists of the prefill kernel.
     bool any_dense = false, all_dense = true, any_text = false, any_image = false;
@@ -574,7 +577,7 @@ RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32
     p.row_blocks = S > 32 ? 2 : 1;
     p.groups = (S + 32 * p.row_blocks - 1) / (32 * p.row_blocks);
     // One workgroup per CU (two at head dimension 64, whose ring takes half the LDS), but no wave without a block.
-    const int32_t wgs = n_cus * (head_dim == 64 ? 2 : 1);
+    const int32_t wgs = n_cus * (head_dim == 64 ? RowsTraits<64>::kPerCu : RowsTraits<128>::kPerCu);
     const int32_t n_blocks = p.k1 - p.k0;
     p.parts = std::max(1, std::min(wgs / std::max(1, n_kv * p.groups), (n_blocks + kRowsWaves - 1) / kRowsWaves));
     // A row of an image may be handed keys here that no tile list of its head names: those of other images under a sparse

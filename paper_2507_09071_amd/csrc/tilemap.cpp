@@ -458,7 +458,7 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     if (window < 0) return BS_EINVAL;
     if (window >= seq_len) window = 0;   // every earlier key is inside the window
     if (window > 0 && (flags & BS_MAP_PACK_KEYS)) {
-        // a windowed query tile visits a few key tiles only: nothing to pack; the rows stay regrouped
+        // packed lists are not built for windows (they would have to be cut at both ends); the rows stay regrouped
         flags = (flags & ~(uint32_t)BS_MAP_PACK_KEYS) | BS_MAP_REGROUP_ROWS;
     }
     if (n_sink_offsets < 0 || (n_sink_offsets > 0 && !sink_offsets)) return BS_EINVAL;
@@ -948,6 +948,10 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
     sp.gqa_group = gqa_group; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
     // the fp32 kernel's steps take 3.5-7 us
     const int64_t kUnitCost = solo ? 1 : 6, kMergeCost = solo ? 1 : 6, kMinPart = solo ? 1 : 4;
+    // With more units than that the queues are better, although their longest workgroup has 5-6 % more steps than the mean on
+    // prompts of 8-9K tokens (by the plan's steps; the time per step differs, and the queues make up for that, too).
+    // Limit 8 instead of 3: 3 layers of 28 heads at 8.2K tokens (3.6 units) 1062 us, 1045 with 3; 32 heads of d = 64 at 9K
+    // (4.5 units) 1008 and 971; the four runs of a 16K characterisation (6.9 units) 3655 and 3358.
     constexpr int64_t kMaxUnitsPerWg = 3;
     const int32_t n_units = (int32_t)std::min<size_t>(plan.items.size(), INT32_MAX);
     if (n_units > kMaxUnitsPerWg * n_wgs || n_wgs > 4096) return;
