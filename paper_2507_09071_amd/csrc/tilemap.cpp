@@ -981,52 +981,74 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
 
     // longest first, in buckets of an eighth of a share inside which the units of a KV head stay together
     const int64_t bucket = std::max<int64_t>(1, least / 8);
-    std::vector<std::pair<int64_t, int32_t>> order(n_units);
-    for (int32_t u = 0; u < n_units; ++u)
-        order[u] = {-(plan.items[u].n_tiles / bucket) * ((int64_t)1 << 32) + plan.items[u].head_a / G, u};
-    std::sort(order.begin(), order.end());
-    using Load = std::pair<int64_t, int32_t>;   // steps given to a workgroup, the workgroup
-    // what the queues need: heaviest first onto the workgroup that is free first
-    int64_t queued = longest;
-    std::vector<Load> heap(n_wgs);
-    auto deal = [&](auto &&accept) {   // units in order to the least loaded workgroup; the loads end up in `heap`
-        for (int32_t w = 0; w < n_wgs; ++w) heap[w] = {0, w};
-        if (n_units <= n_wgs) {        // each to the next workgroup that has nothing yet
-            int32_t w = 0;
-            for (const auto &o : order) {
-                const int64_t x = plan.items[o.second].n_tiles + kUnitCost;
-                if (accept(o.second, heap[w], x)) heap[w++].first = x;
-            }
-            return;
-        }
-        for (const auto &o : order) {
-            const int64_t x = plan.items[o.second].n_tiles + kUnitCost;
-            std::pop_heap(heap.begin(), heap.end(), std::greater<Load>());
-            if (accept(o.second, heap.back(), x)) heap.back().first += x;
-            std::push_heap(heap.begin(), heap.end(), std::greater<Load>());
+    struct Unit { int32_t cost, unit; };   // (costs are below 2^28: n_tiles is)
+    std::vector<Unit> order(n_units);
+    {   // two stable counting passes: KV head, then bucket
+        std::vector<int32_t> by_head(n_units), at;
+        auto pass = [&](int64_t n_keys, auto &&unit, auto &&key, auto &&place) {
+            at.assign(n_keys + 1, 0);
+            for (int32_t i = 0; i < n_units; ++i) ++at[key(unit(i)) + 1];
+            for (int64_t k = 0; k < n_keys; ++k) at[k + 1] += at[k];
+            for (int32_t i = 0; i < n_units; ++i) place(at[key(unit(i))]++, unit(i));
+        };
+        pass((tm->n_q_heads + G - 1) / G, [](int32_t i) { return i; }, [&](int32_t u) { return plan.items[u].head_a / G; },
+             [&](int32_t i, int32_t u) { by_head[i] = u; });
+        pass(longest / bucket + 1, [&](int32_t i) { return by_head[i]; },
+             [&](int32_t u) { return (int32_t)(longest / bucket - plan.items[u].n_tiles / bucket); },
+             [&](int32_t i, int32_t u) { order[i] = {plan.items[u].n_tiles + (int32_t)kUnitCost, u}; });
+    }
+    // Units in order to the least loaded workgroup (the first of several), if `accept` says so; no load passes `most`.  The
+    // least load only grows, so the workgroups lie in a set per load.  (Planning is host time that every layer pays: 624
+    // units of a windowed prompt of 5K tokens take 72 us; with a heap of pairs and a sort of them it was 300, three times the
+    // kernels' time.)
+    std::vector<int64_t> load(n_wgs);
+    std::vector<uint64_t> sets;
+    auto deal = [&](int64_t most, auto &&accept) {
+        std::fill(load.begin(), load.end(), 0);
+        int32_t w = 0, i = 0;          // first to the next workgroup that has nothing yet
+        for (; i < n_units && w < n_wgs; ++i)
+            if (accept(order[i], w, 0)) load[w++] = order[i].cost;
+        if (i == n_units) return;
+        const int32_t words = (n_wgs + 63) / 64;
+        sets.assign((size_t)(most + 1) * words, 0);
+        auto put = [&](int32_t w) { sets[(size_t)load[w] * words + (w >> 6)] |= (uint64_t)1 << (w & 63); };
+        for (w = 0; w < n_wgs; ++w) put(w);
+        for (size_t first = 0; i < n_units; ++i) {
+            while (sets[first] == 0) ++first;
+            w = (int32_t)(first % words) * 64 + __builtin_ctzll(sets[first]);
+            if (!accept(order[i], w, load[w])) continue;
+            sets[first] &= sets[first] - 1;
+            load[w] += order[i].cost;
+            put(w);                    // (behind this set: a unit costs something)
         }
     };
+    int64_t queued = longest;   // what the queues need: heaviest first onto the workgroup that is free first
     if (n_units > n_wgs) {
-        deal([](int32_t, const Load &, int64_t) { return true; });
-        for (const Load &l : heap) queued = std::max(queued, l.first);
+        deal(total / n_wgs + longest, [](const Unit &, int32_t, int64_t) { return true; });
+        for (int64_t l : load) queued = std::max(queued, l);
     }
 
     struct Piece { int32_t wg, unit, begin, steps; };
     std::vector<Piece> pieces;
     std::vector<int32_t> homeless;
-    std::vector<int64_t> load(n_wgs);
     const int64_t kQueuedFrom = solo ? INT64_MAX : 600;   // shares from here on hand a sixth of the steps to the queues ...
     auto fill = [&](int64_t share) {       // false: units are left over
         const int64_t fixed = share >= kQueuedFrom ? share - share / 6 : share;
         const int64_t queue_piece = share / 24;   // ... in pieces of four to that sixth
         pieces.clear();
         homeless.clear();
-        deal([&](int32_t u, const Load &l, int64_t x) {
-            if (l.first + x > fixed) { homeless.push_back(u); return false; }
-            pieces.push_back({l.second, u, 0, plan.items[u].n_tiles});
+        int64_t left_over = 0, room_left = 0;
+        deal(fixed, [&](const Unit &o, int32_t w, int64_t load_w) {
+            if (load_w + o.cost > fixed) {
+                homeless.push_back(o.unit);
+                left_over += o.cost;
+                return false;
+            }
+            pieces.push_back({w, o.unit, 0, o.cost - (int32_t)kUnitCost});
             return true;
         });
-        for (const Load &l : heap) load[l.second] = l.first;
+        for (int64_t l : load) room_left += fixed - l;
+        if (fixed == share && left_over > room_left) return false;
         int32_t w = 0;
         for (int32_t u : homeless) {
             int32_t done = 0;
@@ -1054,21 +1076,27 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
     auto has_room = [&](int64_t share) {
         int64_t need = 0;
         for (const bs::PairItem &it : plan.items)
-            need += it.n_tiles + kUnitCost * std::max<int64_t>(1, (it.n_tiles + share - kUnitCost - 1) / (share - kUnitCost));
+            need += it.n_tiles + kUnitCost * (it.n_tiles <= share - kUnitCost ? 1 : (it.n_tiles + share - kUnitCost - 1) / (share - kUnitCost));
         return need <= share * n_wgs;
     };
     int64_t share = least;
     while (share + kMergeCost < queued && !(has_room(share) && fill(share))) share += std::max<int64_t>(1, share / 32);
     if (share + kMergeCost >= queued) return;   // no gain over the queues
-    std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &a, const Piece &b) { return a.wg < b.wg; });
     std::vector<int32_t> off(n_wgs + 2, 0);   // (the queued pieces count as those of workgroup n_wgs)
     for (const Piece &p : pieces) ++off[p.wg + 1];
     for (int32_t w = 0; w <= n_wgs; ++w) off[w + 1] += off[w];
+    {   // by workgroup, the pieces of one in the order they were made
+        std::vector<int32_t> at(off.begin(), off.end() - 1);
+        std::vector<Piece> sorted(pieces.size());
+        for (const Piece &p : pieces) sorted[at[p.wg]++] = p;
+        pieces.swap(sorted);
+    }
     off.pop_back();
     for (int q = 0; q <= 8; ++q) sp.queue_off[q] = (int32_t)(off[n_wgs] + (pieces.size() - off[n_wgs]) * q / 8);
 
     std::vector<int32_t> n_parts(n_units, 0), made(n_units, 0), slot0(n_units, -1);
     for (const Piece &p : pieces) ++n_parts[p.unit];
+    sp.parts.reserve(pieces.size());
     for (const Piece &p : pieces) {
         const bs::PairItem &it = plan.items[p.unit];
         bs::PairItem part = it;
