@@ -989,9 +989,21 @@ size_t cut_bytes(const bs::ShareSet &shares, int head_dim)
 int take_workspace(DeviceMap *d, size_t bytes, hipStream_t st)
 {
     if (d->vt_bytes >= bytes) return BS_OK;
-    bs::pool_release(d->device, d->vt_buf, d->vt_bytes, d->last_use);
+    // (a workspace that grows takes a quarter more, so that the outgrown ones add up to a few times the last)
+    const size_t want = std::max(bytes, d->vt_bytes + d->vt_bytes / 4);
+    if (d->vt_buf) {
+        try {
+            d->outgrown.push_back({d->vt_buf, d->vt_bytes});
+        } catch (const std::bad_alloc &) {
+            return BS_ENOMEM;
+        }
+    }
     d->vt_buf = nullptr; d->vt_bytes = 0;
-    const hipError_t e = bs::pool_acquire(d->device, bytes, st, &d->vt_buf, &d->vt_bytes);
+    hipError_t e = bs::pool_acquire(d->device, want, st, &d->vt_buf, &d->vt_bytes);
+    if (e != hipSuccess && want > bytes) {
+        (void)hipGetLastError();
+        e = bs::pool_acquire(d->device, bytes, st, &d->vt_buf, &d->vt_bytes);
+    }
     if (e == hipSuccess) return BS_OK;
     d->vt_buf = nullptr; d->vt_bytes = 0;
     return bs::fail_hip(e, "hipMalloc(workspace)");

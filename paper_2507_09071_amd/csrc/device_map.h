@@ -9,6 +9,8 @@
 #include <stdint.h>
 
 #include <memory>
+#include <utility>
+#include <vector>
 
 #include "tilemap_internal.h"
 
@@ -78,6 +80,9 @@ struct DeviceMap {
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
     void *vt_buf = nullptr;
     size_t vt_bytes = 0;
+    // Workspaces that a larger one took the place of, kept as long as the map: a call of it that was captured into a graph
+    // still writes its partial results there when the graph is replayed.
+    std::vector<std::pair<void *, size_t>> outgrown;
     int32_t k_in_place = 0;               // key tiles of K that the last call read in place (see pack_k_tile)
     hipStream_t last_stream = nullptr;    // stream of the most recent upload / launch (compared, never used)
     std::shared_ptr<EventHolder> last_use;   // recorded after the most recent upload / launch

@@ -194,6 +194,7 @@ void free_device_map(DeviceMap *d)
     pool_release(d->device, d->blob, d->blob_cap, d->last_use);
     pool_release(d->device, d->bind_blob, d->bind_cap, d->last_use);
     pool_release(d->device, d->vt_buf, d->vt_bytes, d->last_use);
+    for (const auto &b : d->outgrown) pool_release(d->device, b.first, b.second, d->last_use);
     if (cur >= 0 && cur != d->device) (void)hipSetDevice(cur);
     delete d;
 }
