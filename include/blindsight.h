@@ -194,6 +194,15 @@ int bs_tilemap_key_order(const bs_tilemap *tm, int32_t *keys, int32_t *n_prompt_
 int bs_tilemap_tile_states(const bs_tilemap *tm, int32_t cls, int32_t q_tile_begin,
                            int32_t q_tile_count, uint8_t *states);
 
+/* The same decision as the kernels walk it, for one query tile: they may take keys from compact tiles of their own
+ * behind the map's n_k_tiles (the text keys once more, without the sinks, for Intra-Image heads), where that means fewer
+ * tiles.  *n_tiles = how many key tiles they know; states[*n_tiles] as above; keys[*n_tiles * block_n] the position of the
+ * key in every slot, -1 where there is none; *compact = the tile's image rows take the keys outside their own image from
+ * compact tiles, and only their own image's (classes with the intra bit) from the prompt's tiles.  Every allowed pair is
+ * in exactly one tile.  Any output pointer may be NULL.  Host only, for tests and accounting. */
+int bs_tilemap_walked(const bs_tilemap *tm, int32_t cls, int32_t q_tile, int32_t *n_tiles, uint8_t *states,
+                      int32_t *keys, int32_t *compact);
+
 /* Per-class accounting behind the FLOP figures (the paper counts attention FLOPs per unmasked pair, App.
  * "FLOPs Reduction"; Sec. 3.2 defines which pairs a class keeps).  Any output pointer may be NULL:
  *   visited = full + partial tiles over all query tiles; allowed_pairs = number of allowed

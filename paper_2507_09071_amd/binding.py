@@ -17,7 +17,7 @@ from . import build as _build
 BS_BF16, BS_F32 = 0, 1
 DENSE, SINK, INTRA, INTRA_SINK = 0, 1, 2, 3
 
-EXPORTS = ("bs_build_tilemap", "bs_build_tilemap_ex", "bs_build_tilemap_model", "bs_build_tilemap_suffix", "bs_tilemap_destroy", "bs_tilemap_dims", "bs_tilemap_row_order", "bs_tilemap_layout", "bs_tilemap_key_order", "bs_tilemap_tile_states",
+EXPORTS = ("bs_build_tilemap", "bs_build_tilemap_ex", "bs_build_tilemap_model", "bs_build_tilemap_suffix", "bs_tilemap_destroy", "bs_tilemap_dims", "bs_tilemap_row_order", "bs_tilemap_layout", "bs_tilemap_key_order", "bs_tilemap_tile_states", "bs_tilemap_walked",
            "bs_tilemap_stats", "bs_tilemap_pair_plan", "bs_tilemap_share_plan", "bs_tilemap_upload", "bs_tilemap_rebind", "bs_tilemap_prepare",
            "bs_attn_prefill", "bs_attn_prefill_ex", "bs_attn_prefill_static", "bs_static_scratch_bytes",
            "bs_characterize_prompt", "bs_head_sq_error", "bs_aggregate_head_type", "bs_aggregate_layer", "bs_alpha_layer", "bs_strerror",
@@ -90,6 +90,8 @@ def load_library():
     lib.bs_tilemap_dims.restype = ctypes.c_int
     lib.bs_tilemap_tile_states.argtypes = [vp, i32, i32, i32, u8p]
     lib.bs_tilemap_tile_states.restype = ctypes.c_int
+    lib.bs_tilemap_walked.argtypes = [vp, i32, i32, i32p, u8p, i32p, i32p]
+    lib.bs_tilemap_walked.restype = ctypes.c_int
     lib.bs_tilemap_stats.argtypes = [vp, i32, i64p, i64p, i64p, i64p, i64p, i64p]
     lib.bs_tilemap_stats.restype = ctypes.c_int
     lib.bs_tilemap_pair_plan.argtypes = [vp, i32, i64p, i64p, i64p]
@@ -162,6 +164,16 @@ class TileMap:
             self._h, cls, q_tile_begin, q_tile_count,
             out.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8))), "bs_tilemap_tile_states")
         return out
+
+    def walked(self, cls: int, q_tile: int, block_n: int = 64):
+        """(uint8 [n] state of every key tile that the kernels know, int32 [n, block_n] position of the key in every slot,
+        -1 = none; whether the tile's image rows take the keys outside their own image from compact tiles)."""
+        lib, n, compact = load_library(), ctypes.c_int32(), ctypes.c_int32()
+        _check(lib.bs_tilemap_walked(self._h, cls, q_tile, ctypes.byref(n), None, None, ctypes.byref(compact)), "bs_tilemap_walked")
+        states, keys = np.empty(n.value, dtype=np.uint8), np.empty((n.value, block_n), dtype=np.int32)
+        _check(lib.bs_tilemap_walked(self._h, cls, q_tile, None, states.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8)),
+                                     keys.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), None), "bs_tilemap_walked")
+        return states, keys, bool(compact.value)
 
     def row_order(self, block_m: int = 128) -> np.ndarray:
         """int32 [n_q_tiles, block_m]: position of every row of every query tile, -1 = no row."""

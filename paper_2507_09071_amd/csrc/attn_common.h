@@ -35,68 +35,69 @@ struct KernelArgs {
     void *out;
     int32_t L, G;
     float scale_log2e;  // scale * log2(e): softmax runs in the exp2 domain
-    int32_t n_prompt_tiles;   // key tiles that are the prompt in position order (compact tiles follow)
-    int32_t packed, intra_compact;
+    int32_t n_prompt_tiles;   // key tiles that are the prompt in position order; compact tiles of free keys follow, ...
+    int32_t text_tile0;       // ... and from here on compact tiles of text keys (n_tiles: none)
+    int32_t n_tiles;
+    int32_t window, bidir;
     int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
 };
-// What the lane's query may see (paper Sec. 3.2), in a form that is cheap to apply per tile.
-// With packed keys (see the tile-map builder) an image query of a sparse class reads the free
-// keys -- text and sink keys -- from compact tiles and only own-image keys from the prompt's
-// tiles, so that every allowed pair is counted once.
+// What the lane's query may see (paper Sec. 3.2), in a form that is cheap to apply per tile: intervals of positions and of
+// compact slots.  With compact tiles (see the tile-map builder) an image query of a sparse class reads the free keys --
+// text and sink keys -- from there and only own-image keys from the prompt's tiles, so that every allowed pair is
+// counted once; such queries, text queries and those of Dense heads see one interval of a tile, whatever its keys are, and
+// a mask of it is all there is to form (15 instead of 55 vector instructions on a tile with a partial mask: 32 heads of d = 64 at
+// 9K tokens 982 -> 967 us for three layers).
 struct QueryView {
-    int32_t row;       // last visible position: the query's own (causal), the end of its image (bidirectional images)
-    int32_t first;     // first visible position: 0, or the start of the query's sliding window
-    int32_t own_lo;    // own image [own_lo, own_hi) if the class attends inside images, else empty
-    int32_t own_hi;
-    int32_t free_bound;  // packed: free keys at positions <= i (the visible compact slots are [0, free_bound))
-    int32_t cfree_lo;    // packed, Intra-Image+Sink: compact slots of the free keys inside the own image
-    int32_t cfree_hi;
-    bool sees_all;     // text query or Dense head: every earlier key
-    bool own_only;     // packed: in the prompt's tiles only own-image keys count for this query
+    int32_t lo, hi;             // positions seen: all up to the query, or those of the own image
+    int32_t free_lo, free_hi;   // positions of which the free keys are seen, too (image query of a sparse class, no compact tiles)
+    int32_t slot_lo, slot_hi;   // slots seen of the compact tiles that the class walks
     // From the row's record in the map's device copy (two int4, see RowRecord).
-    __device__ void init(const int4 &r0, const int4 &r1, int cls, bool packed, bool intra_compact)
+    __device__ void init(const int4 &r0, const int4 &r1, int cls, bool compact, const KernelArgs &a)
     {
-        first = r0.y;
-        row = r0.z;
-        const bool image = r1.x > r0.w;
-        sees_all = !image || cls == BS_DENSE;
-        own_lo = own_hi = 0;
-        free_bound = cfree_lo = cfree_hi = 0;
-        own_only = false;
-        if (!sees_all && (cls & 2)) { own_lo = r0.w; own_hi = r1.x; }
-        if (packed && !sees_all && (cls != BS_INTRA || intra_compact)) {
-            free_bound = r1.y;
-            own_only = true;
-            if (cls == BS_INTRA_SINK) { cfree_lo = r1.z; cfree_hi = r1.w; }
-        }
+        // (values first, then choices: a choice of fields would put the records into scratch memory)
+        const int pos = r0.x, img_lo = r0.y, img_hi = r0.z, row_free_lo = r0.w, row_free_hi = r1.x, free_before = r1.y, text_lo = r1.z, text_hi = r1.w;
+        const bool image = img_hi > img_lo, sees_all = !image || cls == BS_DENSE, own = (cls & 2) != 0;
+        // an image query that sees its whole image behaves, for every class, like the image's last query under the causal
+        // mask; its image stays visible beyond a window
+        const bool whole = image && a.bidir;
+        int first = a.window > 0 ? max(0, pos - a.window + 1) : 0;
+        first = whole ? min(first, img_lo) : first;
+        const int end = whole ? img_hi : pos + 1;
+        lo = sees_all ? first : (own ? max(first, img_lo) : 0);
+        hi = sees_all || own ? end : 0;
+        const bool pattern = !sees_all && !compact;
+        free_lo = pattern ? first : 0;
+        free_hi = pattern ? end : 0;
+        const bool text_slots = cls == BS_INTRA && a.text_tile0 < a.n_tiles;
+        const int slot_end = text_slots ? text_hi : (cls == BS_SINK ? row_free_hi : free_before);   // (the own image's are not counted again)
+        slot_lo = text_slots ? text_lo : row_free_lo;
+        slot_hi = sees_all || !compact ? 0 : slot_end;
     }
 };
 
-__device__ inline uint64_t bits_below(int x)  // bits [0, x), x in [0, 64]
+// Bits [lo, hi) of 64; either may lie outside.
+__device__ inline uint64_t bits_between(int lo, int hi)
 {
-    return x >= 64 ? ~0ull : ((1ull << x) - 1ull);
-}
-__device__ inline uint64_t bits_between(int lo, int hi)  // bits [lo, hi) clipped to [0, 64)
-{
-    return bits_below(min(max(hi, 0), 64)) & ~bits_below(min(max(lo, 0), 64));
+    lo = min(max(lo, 0), 64);
+    hi = min(max(hi, 0), 64);
+    const uint64_t mask = (~0ull << (lo & 63)) & (~0ull >> ((64 - hi) & 63));   // (lo = 64 or hi = 0: an empty interval)
+    return lo < hi ? mask : 0ull;
 }
 
-// Bit b set <=> the key in slot b of key tile n is allowed for this lane's query.  tbits / sbits:
-// text keys and sink keys of the tile; n_prompt: number of key tiles that are the prompt in
-// position order (the tiles after them are compact tiles of free keys).
-__device__ inline uint64_t allowed_keys(const QueryView &qv, int cls, uint64_t tbits, uint64_t sbits, int n, int n_prompt)
+// Bit b set <=> the key in slot b of key tile n is allowed for this lane's query.  item_class: see PairItem::classes;
+// tbits / sbits: text keys and sink keys of the tile.
+__device__ inline uint64_t allowed_keys(const QueryView &qv, int item_class, uint64_t tbits, uint64_t sbits, int n, const KernelArgs &a)
 {
-    if (n < n_prompt) {
+    if (n < a.n_prompt_tiles) {
         const int n0 = n * kBlockN;
-        const uint64_t base = qv.sees_all ? ~0ull : (qv.own_only ? 0ull : (tbits | ((cls & 1) ? sbits : 0ull)));
-        const uint64_t own = bits_between(qv.own_lo - n0, qv.own_hi - n0);
-        return (base | own) & bits_between(qv.first - n0, qv.row - n0 + 1);   // keys first .. row
+        uint64_t allowed = bits_between(qv.lo - n0, qv.hi - n0);
+        if (item_class == BS_SINK || item_class == BS_INTRA || item_class == BS_INTRA_SINK)   // (sparse, no compact tiles)
+            allowed |= (tbits | ((item_class & 1) ? sbits : 0ull)) & bits_between(qv.free_lo - n0, qv.free_hi - n0);
+        return allowed;
     }
-    // compact tile: slots are free keys in position order, visible up to the row's bound
-    const int s0 = (n - n_prompt) * kBlockN;
-    const uint64_t base = qv.sees_all ? 0ull : ((cls & 1) ? ~0ull : tbits);   // Intra-Image: text keys only
-    const uint64_t excl = bits_between(qv.cfree_lo - s0, qv.cfree_hi - s0);   // counted with the own image
-    return base & ~excl & bits_below(min(max(qv.free_bound - s0, 0), 64));
+    // compact tile: slots are free keys, or text keys, in position order
+    const int s0 = (n - (n < a.text_tile0 ? a.n_prompt_tiles : a.text_tile0)) * kBlockN;
+    return ((item_class & 1) ? ~0ull : tbits) & bits_between(qv.slot_lo - s0, qv.slot_hi - s0);   // Intra-Image: text keys only
 }
 
 // A load from memory that no kernel in flight writes, at a wave-uniform address: through the scalar cache, whatever the

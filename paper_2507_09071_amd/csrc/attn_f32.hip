@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
     for (int u = u_begin; u < u_end; ++u) {
         const int4 it0 = items[2 * u], it1 = items[2 * u + 1];
         const int head = __builtin_amdgcn_readfirstlane(it0.x), m = __builtin_amdgcn_readfirstlane(it0.y);
-        const int T = __builtin_amdgcn_readfirstlane(it1.z), cls = __builtin_amdgcn_readfirstlane(it1.w) & 3;
+        const int T = __builtin_amdgcn_readfirstlane(it1.z), item_class = __builtin_amdgcn_readfirstlane(it1.w) & 7;
         const int slot_id = __builtin_amdgcn_readfirstlane(it1.w >> 16);   // > 0: a part of a cut item
         const int kvh = head / a.G;
         const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * L * ROWB;
@@ -146,12 +146,12 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
             for (int j = 0; j < D / 8; ++j) q[j] = *reinterpret_cast<const floatx4 *>(qr + 8 * j + 4 * hl);
         }
         QueryView qv;
-        qv.init(r0, r1, cls, a.packed != 0, a.intra_compact != 0);
+        qv.init(r0, r1, item_class & 3, (item_class & 4) != 0, a);
         // What was loaded for the rows must be here before the loop: the compiler would wait for it inside, and with it
         // for the LDS-direct loads, which it does not know.
 #pragma unroll
         for (int j = 0; j < D / 8; ++j) asm volatile("" : "+v"(q[j]));
-        asm volatile("" : "+v"(qv.row), "+v"(qv.first), "+v"(qv.own_lo), "+v"(qv.own_hi), "+v"(qv.free_bound), "+v"(qv.cfree_lo), "+v"(qv.cfree_hi));
+        asm volatile("" : "+v"(qv.lo), "+v"(qv.hi), "+v"(qv.free_lo), "+v"(qv.free_hi), "+v"(qv.slot_lo), "+v"(qv.slot_hi));
         floatx16 o[NDB];
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
             if (w.state(0) == 2) {
                 softmax_block<false>(s, m_run, l_run, alpha, a.scale_log2e);
             } else {
-                apply_mask(s, allowed_keys(qv, cls, map_text_bits[n], map_sink_bits[n], n, a.n_prompt_tiles), hl);
+                apply_mask(s, allowed_keys(qv, item_class, map_text_bits[n], map_sink_bits[n], n, a), hl);
                 softmax_block<true>(s, m_run, l_run, alpha, a.scale_log2e);
             }
             if (__any(alpha != 1.f)) {

@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // ---- state of the work unit in progress (a workgroup takes units from its XCD's queue until
     // ---- the queues are empty; see the unit loop below)
-    int head = 0, m = 0, T = 0, cls = 0;
+    int head = 0, m = 0, T = 0, item_class = 0;
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
     int row = 0;                    // the query position of this lane's row
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         list_end = __builtin_amdgcn_readfirstlane(it1.y);
         const int hsafe = max(head, 0);
         slot_id = __builtin_amdgcn_readfirstlane(it1.w >> 16);
-        cls = __builtin_amdgcn_readfirstlane((grp ? it1.w >> 8 : it1.w) & 3);   // head classes travel with the unit
+        item_class = __builtin_amdgcn_readfirstlane(grp ? it1.w >> 8 : it1.w) & 7;   // head classes travel with the unit
         const int kvh = __builtin_amdgcn_readfirstlane(it0.x / a.G);            // both items share it
         // a tile slot without a row behaves like a row past the end of the prompt (computed on a
         // copy of the last row, never stored)
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             qreg[t] = *reinterpret_cast<const bf16x8 *>(qh + (size_t)qrow * D + 16 * t + 8 * hl);
-        qv.init(r0, r1, cls, a.packed != 0, a.intra_compact != 0);
+        qv.init(r0, r1, item_class & 3, (item_class & 4) != 0, a);
     };
 
     // LDS byte address of this lane's MFMA operand fragments inside a K / V^T tile (see the
@@ -625,7 +625,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             rescale = softmax_pack<0>(s, pf, m_run, l_run, alpha, a.scale_log2e, false);
         } else {
             const int nu = __builtin_amdgcn_readfirstlane(w0.n);
-            uint64_t allowed = allowed_keys(qv, cls, tb_cur, sb_cur, nu, a.n_prompt_tiles);
+            uint64_t allowed = allowed_keys(qv, item_class, tb_cur, sb_cur, nu, a);
             if (st == 0) allowed = 0ull;
             if (__all(allowed == 0ull || allowed == ~0ull)) {
                 // every query of the wave sees all 64 keys or none (e.g. a text row and an
@@ -938,30 +938,33 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
     a.L = tm->L; a.G = gqa_group;
     a.scale_log2e = scale * 1.4426950408889634f;
     a.n_prompt_tiles = tm->N0;
-    a.packed = tm->packed;
-    a.intra_compact = tm->intra_compact;
+    a.text_tile0 = tm->text_tile0;
+    a.n_tiles = tm->n_tiles;
+    a.window = tm->window;
+    a.bidir = tm->bidir;
     a.q_begin = tm->q_begin;
     return a;
 }
 
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
-// holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.
+// holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
+// what the packed K tiles take, in front of the V^T tiles.
 template <int D>
-void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t pack_bytes,
+void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t k_bytes,
                  float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
 {
     __bf16 *kp = static_cast<__bf16 *>(workspace);
-    __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + pack_bytes);
+    __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
     const int32_t in_place = d->k_in_place;
-    const dim3 tgrid((unsigned)(2 * tm->N - in_place), (unsigned)n_kv_heads);
+    const dim3 tgrid((unsigned)(2 * tm->n_tiles - in_place), (unsigned)n_kv_heads);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     if (!kv_packed)
         hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->N, tm->N0, in_place, d->queue_ctr);
+                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, d->queue_ctr);
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                       d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->N, in_place,
+                       d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
                        d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
     if (sh && sh->n_cut > 0)
         hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
@@ -976,7 +979,7 @@ void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap 
 int32_t tiles_in_place(const bs_tilemap *tm, const DeviceMap *d, int n_kv_heads, int32_t head_dim)
 {
     const int64_t fetches = head_dim == 128 ? 48 : 32;   // (a tile of d = 64 is half as much to pack)
-    return d->n_steps < fetches * n_kv_heads * tm->N ? tm->L / bs::kBlockN : 0;
+    return d->n_steps < fetches * n_kv_heads * tm->n_tiles ? tm->L / bs::kBlockN : 0;
 }
 
 // Bytes of the results of cut units (0 without equal shares).
@@ -1009,9 +1012,9 @@ int take_workspace(DeviceMap *d, size_t bytes, hipStream_t st)
     return bs::fail_hip(e, "hipMalloc(workspace)");
 }
 
-size_t bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
+size_t bf16_pack_bytes(int32_t n_tiles, int n_kv_heads, int head_dim)
 {
-    return (size_t)n_kv_heads * tm->N * (size_t)head_dim * bs::kBlockN * 2;   // one of the two halves (K, V^T)
+    return (size_t)n_kv_heads * n_tiles * (size_t)head_dim * bs::kBlockN * 2;   // one of the two halves (K, V^T)
 }
 
 }  // namespace
@@ -1048,8 +1051,8 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
         if (rc == BS_OK) {   // results of cut units that have no room in the static scratch (the head dimension is not known yet)
             const int n_kv_heads = tm->n_q_heads / gqa_group;
             const size_t cut = cut_bytes(*d->shares_for(n_cus), 128);
-            if (2 * bf16_pack_bytes(tm, n_kv_heads, 64) <= kStaticScratchBytes &&
-                2 * bf16_pack_bytes(tm, n_kv_heads, 128) + cut > kStaticScratchBytes) rc = take_workspace(d, cut, st);
+            if (2 * bf16_pack_bytes(tm->N, n_kv_heads, 64) <= kStaticScratchBytes &&
+                2 * bf16_pack_bytes(tm->n_tiles, n_kv_heads, 128) + cut > kStaticScratchBytes) rc = take_workspace(d, cut, st);
         }
     } else {   // for either head dimension, and the workspace of the larger plan
         const int32_t wgs128 = n_cus * bs::f32_wgs_per_cu(128), wgs64 = n_cus * bs::f32_wgs_per_cu(64);
@@ -1110,7 +1113,7 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
     } else if (dtype == BS_BF16) {
         // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
-        const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
+        const size_t pack_bytes = bf16_pack_bytes(tm->n_tiles, n_kv_heads, head_dim);
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         const bs::ShareSet *const sh = shares.n_shares > 0 ? &shares : nullptr;
         const void *const old_workspace = d->vt_buf;
@@ -1152,7 +1155,7 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     const bool rows_bound = d->rows_G == gqa_group && d->rows_epoch == tm->class_epoch;
     if (!units_bound && !rows_bound) return not_prepared();
     const int n_kv_heads = n_q_heads / gqa_group;
-    const size_t pack_bytes = bf16_pack_bytes(tm, n_kv_heads, head_dim);
+    const size_t pack_bytes = bf16_pack_bytes(tm->n_tiles, n_kv_heads, head_dim);
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return bs::fail_hip(e, "hipGetDevice");
@@ -1162,11 +1165,19 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     if ((rc = device_setup(dev, &ws, &n_cus)) != BS_OK) return rc;   // looks the address up on the first call per device
     const bs::RowsPlan rows = bs::plan_rows(tm, BS_BF16, gqa_group, head_dim, n_cus);
     if (!units_bound && !rows.use) return not_prepared();
-    // (one limit for all calls, although the few-row kernel would need less)
-    if (std::max(rows.workspace, 2 * pack_bytes) > kStaticScratchBytes) {
+    // (one limit for all calls and maps: the few-row kernel would need less, and a map whose kernels know more tiles than it
+    // publishes has room for those if K is read in place)
+    const size_t limit_bytes = 2 * bf16_pack_bytes(tm->N, n_kv_heads, head_dim);
+    int32_t in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
+    size_t k_bytes = pack_bytes;
+    if (2 * pack_bytes > kStaticScratchBytes) {
+        in_place = tm->L / bs::kBlockN;
+        k_bytes = bf16_pack_bytes(tm->n_tiles - in_place, n_kv_heads, head_dim);
+    }
+    if (std::max(rows.workspace, limit_bytes) > kStaticScratchBytes || k_bytes + pack_bytes > kStaticScratchBytes) {
         snprintf(bs::g_last_error, sizeof bs::g_last_error,
                  "bs_attn_prefill_static: packed K / V^T tiles need %zu bytes, the static scratch holds %zu "
-                 "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", 2 * pack_bytes, kStaticScratchBytes);
+                 "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", limit_bytes, kStaticScratchBytes);
         return BS_EUNSUPPORTED;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1176,17 +1187,17 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // bs_tilemap_prepare took (too small only if a call at head dimension 64 made the binding: then nothing is cut)
     const bs::ShareSet *sh = d->shares_for(n_cus);
     if (sh && sh->n_shares == 0) sh = nullptr;
-    float *cut = reinterpret_cast<float *>(static_cast<char *>(ws) + 2 * pack_bytes);
-    if (sh && 2 * pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes) {
+    float *cut = reinterpret_cast<float *>(static_cast<char *>(ws) + k_bytes + pack_bytes);
+    if (sh && k_bytes + pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes) {
         cut = static_cast<float *>(d->vt_buf);
         if (cut_bytes(*sh, head_dim) > d->vt_bytes) sh = nullptr;
     }
-    d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
+    d->k_in_place = in_place;
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, pack_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, pack_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else launch_bf16<64>(a, tm, d, ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

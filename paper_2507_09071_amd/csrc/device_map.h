@@ -32,13 +32,13 @@ struct EventHolder {
 
 enum BindingKind : int32_t { kBindNone = 0, kBindSolo = 1, kBindPairPlan = 2 };
 
-// A query-tile slot: two int4.  pos = first = last = L-like values for a slot without a row (see expand_map).
+// A query-tile slot: two int4.  pos = L: a slot without a row.  The slots of compact tiles that a row sees, apart from those
+// of its own image: free keys [free_lo, free_before), with the own image's sinks [free_lo, free_hi), text keys [text_lo, text_hi).
 struct RowRecord {
     int32_t pos;                  // position of the row; L: no row
-    int32_t first, last;          // first and last visible position (window, own image under bidirectional images)
     int32_t img_lo, img_hi;       // own image; empty for a text row
-    int32_t free_bound;           // free keys at positions <= last
-    int32_t cfree_lo, cfree_hi;   // compact slots of the free keys inside the own image
+    int32_t free_lo, free_hi, free_before;
+    int32_t text_lo, text_hi;
 };
 
 // Equal shares of the bound units for `n_wgs` workgroups, instead of the queues.
@@ -59,9 +59,9 @@ struct DeviceMap {
     void *blob = nullptr;
     size_t blob_cap = 0;
     const int4 *rows = nullptr;           // [M * 128][2] what the query in each query-tile slot may see (RowRecord)
-    const int32_t *compact_keys = nullptr;   // packed: [(N - N0) * 64] position of each compact slot, -1 = none
-    const uint64_t *text_bits = nullptr;  // [N] text keys of each key tile
-    const uint64_t *sink_bits = nullptr;  // [N] sink keys of each key tile
+    const int32_t *compact_keys = nullptr;   // [(n_tiles - N0) * 64] position of each compact slot, -1 = none
+    const uint64_t *text_bits = nullptr;  // [n_tiles] text keys of each key tile
+    const uint64_t *sink_bits = nullptr;  // [n_tiles] sink keys of each key tile
     // ---- binding part: one block, uploaded again after a rebind / for another kind or group size
     void *bind_blob = nullptr;
     size_t bind_cap = 0;

@@ -215,8 +215,8 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct ExpandArgs {
     const SpanInfo *spans;     // n_spans + 1, the last one a sentinel that starts at L
     const int32_t *offsets;
-    int32_t n_offsets, n_spans, L, N0, Nc, M, n_free, q_begin, window, sink_len;
-    int32_t bidir, packed, regrouped, n_img_rows, m_img;
+    int32_t n_offsets, n_spans, L, N0, text_tile0, n_tiles, M, n_free, q_begin, window, sink_len;
+    int32_t bidir, regrouped, n_img_rows, m_img;
     int32_t text0;             // text tokens before q_begin
     int4 *rows;
     int32_t *compact_keys;
@@ -271,34 +271,27 @@ __global__ __launch_bounds__(256) void expand_map(const ExpandArgs a)
                 pos = sp[g].start - (sp[g].text_before - x);
             }
         }
-        RowRecord r{a.L, 0, a.L, 0, 0, 0, 0, 0};   // no row
+        RowRecord r{a.L, 0, 0, 0, 0, 0, 0, 0};   // no row
         if (pos >= 0) {
-            r.pos = r.last = pos;
-            r.first = a.window > 0 ? max(0, pos - a.window + 1) : 0;
+            r.pos = pos;
             const SpanInfo s = sp[span_at(pos)];
             if (s.start <= pos) {   // (the sentinel starts at L)
                 r.img_lo = s.start;
                 r.img_hi = s.end;
-                if (a.bidir) {
-                    // an image query that sees its whole image behaves, for every class, like the image's last
-                    // query under the causal mask; its image stays visible beyond a window
-                    r.last = s.end - 1;
-                    r.first = min(r.first, s.start);
-                }
-                if (a.packed) {
-                    r.free_bound = s.free_before + sinks_in(s, r.last + 1 - s.start);
-                    r.cfree_lo = s.free_before;
-                    r.cfree_hi = s.free_before + sinks_in(s, s.end - s.start);
+                if (a.n_tiles > a.N0) {   // the free keys up to the last one the row sees; the text keys before its image
+                    r.free_before = s.free_before;
+                    r.free_hi = s.free_before + sinks_in(s, (a.bidir ? s.end : pos + 1) - s.start);
+                    r.text_hi = s.text_before;
                 }
             }
         }
         int4 *out = a.rows + 2 * (size_t)slot;
-        out[0] = make_int4(r.pos, r.first, r.last, r.img_lo);
-        out[1] = make_int4(r.img_hi, r.free_bound, r.cfree_lo, r.cfree_hi);
+        out[0] = make_int4(r.pos, r.img_lo, r.img_hi, r.free_lo);
+        out[1] = make_int4(r.free_hi, r.free_before, r.text_lo, r.text_hi);
         return;
     }
     const int32_t n = wave - 2 * a.M;   // ---- a key tile
-    if (n >= a.N0 + a.Nc) return;
+    if (n >= a.n_tiles) return;
     bool text = false, sink = false;
     if (n < a.N0) {
         const int32_t t = n * 64 + lane;
@@ -309,9 +302,16 @@ __global__ __launch_bounds__(256) void expand_map(const ExpandArgs a)
             sink = text ? t < a.sink_len : (o < s.prefix || offsets_below(o + 1) > offsets_below(o));
         }
     } else {
-        const int32_t slot = (n - a.N0) * 64 + lane;
+        const int32_t slot = (n - (n < a.text_tile0 ? a.N0 : a.text_tile0)) * 64 + lane;
         int32_t pos = -1;
-        if (slot < a.n_free) {   // free token number `slot`: a sink of the last image that begins before it, or text behind that
+        if (n >= a.text_tile0) {   // text token number `slot`
+            if (slot < sp[a.n_spans].text_before) {
+                const int32_t g = partition(a.n_spans + 1, [&](int32_t i) { return sp[i].text_before <= slot; });
+                pos = sp[g].start - (sp[g].text_before - slot);
+                text = true;
+                sink = pos < a.sink_len;
+            }
+        } else if (slot < a.n_free) {   // free token number `slot`: a sink of the last image that begins before it, or text behind that
             const int32_t g = partition(a.n_spans, [&](int32_t i) { return sp[i].free_before <= slot; }) - 1;
             if (g < 0) {
                 pos = slot;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256) void expand_map(const ExpandArgs a)
             }
             sink = text ? pos < a.sink_len : true;
         }
-        a.compact_keys[slot] = pos;
+        a.compact_keys[(n - a.N0) * 64 + lane] = pos;
     }
     const uint64_t tb = __ballot(text), sb = __ballot(sink);
     if (lane == 0) {
@@ -379,11 +379,10 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     const size_t off_offsets = section(std::max<size_t>(P.offsets.size(), 1) * 4);
     const size_t up_bytes = bytes;
     const bool device_tiles = tm->bm == 128 && tm->bn == 64;   // the kernels' tile sizes: other maps have no device arrays
-    const int32_t Nc = tm->N - tm->N0;
     const size_t off_rows = section(device_tiles ? (size_t)tm->M * 128 * sizeof(RowRecord) : 0);
-    const size_t off_keys = section((size_t)Nc * 64 * 4);
-    const size_t off_tbits = section((size_t)tm->N * 8);
-    const size_t off_sbits = section((size_t)tm->N * 8);
+    const size_t off_keys = section((size_t)(tm->n_tiles - tm->N0) * 64 * 4);
+    const size_t off_tbits = section((size_t)tm->n_tiles * 8);
+    const size_t off_sbits = section((size_t)tm->n_tiles * 8);
 
     Staging sg;
     e = staging_begin(up_bytes, &sg);
@@ -406,17 +405,17 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
         a.spans = reinterpret_cast<const SpanInfo *>(b + off_spans);
         a.offsets = reinterpret_cast<const int32_t *>(b + off_offsets);
         a.n_offsets = (int32_t)P.offsets.size();
-        a.n_spans = P.n_spans; a.L = tm->L; a.N0 = tm->N0; a.Nc = Nc; a.M = tm->M;
-        a.n_free = tm->packed ? P.n_free(tm->L) : 0;
+        a.n_spans = P.n_spans; a.L = tm->L; a.N0 = tm->N0; a.text_tile0 = tm->text_tile0; a.n_tiles = tm->n_tiles; a.M = tm->M;
+        a.n_free = P.n_free(tm->L);
         a.q_begin = tm->q_begin; a.window = tm->window; a.sink_len = P.sink_len;
-        a.bidir = tm->bidir; a.packed = tm->packed; a.regrouped = P.regrouped;
+        a.bidir = tm->bidir; a.regrouped = P.regrouped;
         a.n_img_rows = P.n_img_rows; a.m_img = P.m_img;
         a.text0 = P.n_text(tm->q_begin);
         a.rows = reinterpret_cast<int4 *>(b + off_rows);
         a.compact_keys = reinterpret_cast<int32_t *>(b + off_keys);
         a.text_bits = reinterpret_cast<uint64_t *>(b + off_tbits);
         a.sink_bits = reinterpret_cast<uint64_t *>(b + off_sbits);
-        const int64_t waves = 2 * (int64_t)tm->M + tm->N;
+        const int64_t waves = 2 * (int64_t)tm->M + tm->n_tiles;
         hipLaunchKernelGGL(expand_map, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a);
         e = hipGetLastError();
     }

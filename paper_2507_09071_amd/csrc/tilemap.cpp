@@ -40,9 +40,10 @@ struct Geometry : PromptGeometry {
     };
     mutable FreeTiles free_tiles[2];
     bool packed = false, intra_compact = false;
-    int32_t Nc = 0;
+    int32_t Nc = 0, text_tile0 = 0;        // text_tile0 > 0: Intra-Image walks the text tiles
     std::vector<int32_t> ctext;            // packed: text keys in the compact tiles before tile c (Nc + 1)
     std::vector<TileRange> ctext_runs;     // runs of complete compact tiles by their text keys: FULL all, PARTIAL some
+    std::vector<int32_t> text_tiles_before;   // text_tile0 > 0: prompt tiles before n that hold a text key (N0 + 1)
 
     int32_t lo(int32_t i) const { return window > 0 ? first_visible(i) : 0; }
     const FreeTiles &tiles_of_free(int cls) const
@@ -246,18 +247,15 @@ void build_run(const Geometry &G, int cls, const QueryTile &qt, std::vector<int3
     flush();
 }
 
-// Packed keys: range list of rows [a, b), all inside image g (0-based span index), for a sparse
-// class.  Two parts, disjoint by construction:
-// [a, b) are the rows by the last key position they may see (Segment::ea, eb).
-//   own-image keys (classes with the intra bit): the prompt's own tiles over [start_g, b);
-//     a pair (i, j) counts there iff start_g <= j <= i;
-//   free keys: compact tiles; row i sees compact slot s iff s < free_before[i + 1] (the free
-//     keys at positions <= i) and
-//       Sink:             every such slot
-//       Intra-Image:      the text slots
-//       Intra-Image+Sink: every slot outside the image's own free keys (those are counted above).
-void build_run_packed(const Geometry &G, int cls, int32_t g, int32_t a, int32_t b, bool ragged,
-                      std::vector<TileRange> &out)
+// Range list of a sparse class for the rows of a segment, all inside one image, that take the keys outside their own
+// image from compact tiles.  Two parts, disjoint by construction:
+//   own-image keys (classes with the intra bit): the prompt's own tiles; a pair (i, j) counts there iff
+//     j is in the image and visible to i;
+//   the others: compact tiles, of which row i sees the slots
+//       Sink:             of the free keys up to its last visible position
+//       Intra-Image:      of the text keys before its image (in the text tiles, or mixed with sinks in the free tiles)
+//       Intra-Image+Sink: of the free keys before its image (the image's own are counted above).
+void build_run_packed(const Geometry &G, int cls, const Segment &s, bool ragged, std::vector<TileRange> &out)
 {
     out.clear();
     int32_t run_begin = -1, run_end = -1, run_state = 0;
@@ -274,39 +272,33 @@ void build_run_packed(const Geometry &G, int cls, int32_t g, int32_t a, int32_t 
             run_begin = bg; run_end = en; run_state = st;
         }
     };
-    const bs::SpanInfo &own = G.spans[g];
-    if (cls & 2) {
-        const int32_t s0 = own.start, n0 = s0 / G.bn, n1 = (b - 1) / G.bn + 1;
-        // FULL: tiles inside the image, visible to the first row
-        const int32_t f0 = std::min(n1, (s0 + G.bn - 1) / G.bn);
-        const int32_t f1 = ragged ? f0 : std::max(f0, std::min((a + 1) / G.bn, G.L / G.bn));
-        emit(n0, f0, 1);
-        emit(f0, f1, 2);
-        emit(f1, n1, 1);
-    }
-    const int32_t fb_min = G.n_free(a + 1), fb_max = G.n_free(b);   // visible free keys of the first / last row
-    const int32_t c_end = (fb_max + G.bn - 1) / G.bn;
-    const int32_t c_all = ragged ? 0 : fb_min / G.bn;               // tiles before it: every slot visible to every row
+    // tiles of consecutive keys of which the rows together see [lo, hi), all of them [all_lo, all_hi)
+    auto emit_keys = [&](int32_t tile0, int32_t lo, int32_t all_lo, int32_t all_hi, int32_t hi) {
+        if (hi <= lo) return;
+        const int32_t n0 = lo / G.bn, n1 = (hi - 1) / G.bn + 1;
+        const int32_t f0 = std::min(n1, (all_lo + G.bn - 1) / G.bn);
+        const int32_t f1 = ragged ? f0 : std::max(f0, std::min(n1, all_hi / G.bn));
+        emit(tile0 + n0, tile0 + f0, 1);
+        emit(tile0 + f0, tile0 + f1, 2);
+        emit(tile0 + f1, tile0 + n1, 1);
+    };
+    const bs::SpanInfo &own = G.spans[s.g];
+    if (cls & 2) emit_keys(0, own.start, own.start, s.ea + 1, s.eb);
     if (cls == BS_SINK) {
-        emit(G.N0, G.N0 + c_all, 2);
-        emit(G.N0 + c_all, G.N0 + c_end, 1);
-    } else if (cls == BS_INTRA) {
+        emit_keys(G.N0, 0, 0, G.n_free(s.ea + 1), G.n_free(s.eb));
+    } else if (cls == BS_INTRA_SINK) {
+        emit_keys(G.N0, 0, 0, own.free_before, own.free_before);
+    } else if (G.text_tile0 > 0) {
+        emit_keys(G.text_tile0, 0, 0, own.text_before, own.text_before);
+    } else {
+        const int32_t fb = own.free_before, c_all = ragged ? 0 : fb / G.bn;
         for (const TileRange &r : G.ctext_runs) {
             if (r.begin >= c_all) break;
             emit(G.N0 + r.begin, G.N0 + std::min(r.end(), c_all), r.full() ? 2 : 1);
         }
-        for (int32_t c = c_all; c < c_end; ++c) {   // (the free keys before row b's bound: the text before it counts)
-            const int32_t text = ((c + 1) * G.bn <= fb_max ? G.ctext[c + 1] : G.n_text(b)) - G.ctext[c];
+        for (int32_t c = c_all; c * G.bn < fb; ++c) {   // (the free keys before the image: the text before it counts)
+            const int32_t text = ((c + 1) * G.bn <= fb ? G.ctext[c + 1] : own.text_before) - G.ctext[c];
             emit(G.N0 + c, G.N0 + c + 1, text > 0 ? 1 : 0);
-        }
-    } else {
-        const int32_t own_lo = own.free_before, own_hi = own_lo + G.sinks_in(g, own.end - own.start);
-        const int32_t c_own = std::min(c_all, own_lo / G.bn);
-        emit(G.N0, G.N0 + c_own, 2);
-        for (int32_t c = c_own; c < c_end; ++c) {
-            const int32_t s0 = c * G.bn, vis = std::min(s0 + G.bn, fb_max);   // slots [s0, vis) are visible to the last row
-            const int32_t own_slots = std::max(0, std::min(vis, own_hi) - std::max(s0, own_lo));
-            emit(G.N0 + c, G.N0 + c + 1, own_slots == vis - s0 ? 0 : (c < c_all && own_slots == 0 ? 2 : 1));
         }
     }
     flush();
@@ -345,10 +337,19 @@ void combine_runs(const std::vector<TileRange> &a, const std::vector<TileRange> 
     }
 }
 
+// Do the text tiles hold the text keys that these image rows of Intra-Image heads see in no more tiles than the prompt's own,
+// not counting those of their own images?  (Text tiles are FULL but for the last, so they win a tie.)
+bool text_tiles_pay(const Geometry &G, const std::vector<std::pair<int32_t, int32_t>> &runs)
+{
+    const bs::SpanInfo &last = G.spans[G.span_at(runs.back().second - 1)];
+    return (last.text_before + G.bn - 1) / G.bn <= G.text_tiles_before[last.start / G.bn];
+}
+
 void build_class(const Geometry &G, int cls, ClassLists &out)
 {
     out.row_ptr.assign(G.M + 1, 0);
     out.row_tiles.assign(G.M, 0);
+    out.compact.assign(G.M, 0);
     out.ranges.clear();
     QueryTile qt;
     std::vector<int32_t> cand;
@@ -359,14 +360,17 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
         const bool ragged = G.tile_runs(m, runs) < G.bm;
         acc.clear();
         bool first = true;
+        // (the rows of a packed map are regrouped: all of a tile are image rows, or none)
+        const bool compact = G.packed && cls != BS_DENSE && (cls != BS_INTRA || (G.text_tile0 > 0 ? text_tiles_pay(G, runs) : G.intra_compact));
+        out.compact[m] = compact;
         for (const auto &rr : runs) {
             describe_query_rows(G, rr.first, rr.second, ragged, qt);
-            if (G.packed && cls != BS_DENSE && (cls != BS_INTRA || G.intra_compact) && qt.last_text < 0 && !qt.segs.empty()) {
+            if (compact && qt.last_text < 0 && !qt.segs.empty()) {
                 // image rows of a sparse class: one packed list per image the run touches
                 // (two images can be adjacent without a text token between them)
                 bool first_seg = true;
                 for (const Segment &sg : qt.segs) {
-                    build_run_packed(G, cls, sg.g, sg.ea, sg.eb, ragged, first_seg ? run : seg_run);
+                    build_run_packed(G, cls, sg, ragged, first_seg ? run : seg_run);
                     if (!first_seg) {
                         combine_runs(run, seg_run, tmp);
                         run.swap(tmp);
@@ -396,7 +400,7 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
 }
 
 // Allowed pairs and empty rows per class, from prefix counts (no pair enumeration).
-void count_pairs(const PromptGeometry &G, ClassLists lists[4])
+void count_pairs(const PromptGeometry &G, int64_t allowed_pairs[4], int64_t empty_rows[4])
 {
     int64_t pairs[4] = {0, 0, 0, 0}, empty[4] = {0, 0, 0, 0};
     for (int32_t i = G.q_begin, g = G.span_at(i); i < G.L; ++i) {
@@ -420,7 +424,112 @@ void count_pairs(const PromptGeometry &G, ClassLists lists[4])
             if (row[c] == 0) ++empty[c];
         }
     }
-    for (int c = 0; c < 4; ++c) { lists[c].allowed_pairs = pairs[c]; lists[c].empty_rows = empty[c]; }
+    for (int c = 0; c < 4; ++c) { allowed_pairs[c] = pairs[c]; empty_rows[c] = empty[c]; }
+}
+
+// The lists that the map publishes for class c (lists_mutex held, or the map not handed out yet).
+void build_published(const bs_tilemap *tm, int c)
+{
+    const PromptGeometry &P = tm->geo;
+    Geometry G(P);
+    const int32_t block_n = P.bn, L = P.L, n_spans = P.n_spans;
+    G.packed = tm->packed;
+    if (!tm->packed || c != BS_INTRA) {
+        build_class(G, c, tm->cls[c]);
+        return;
+    }
+    G.Nc = tm->N - tm->N0;
+    // text keys before every compact tile
+    G.ctext.assign(G.Nc + 1, 0);
+    for (int32_t t = 0; t < G.Nc; ++t) G.ctext[t] = P.n_text(P.free_position(t * block_n));
+    G.ctext[G.Nc] = P.n_text(L);
+    for (int32_t t = 0; t < G.Nc; ++t) {
+        const int32_t text = G.ctext[t + 1] - G.ctext[t];
+        const bool full = text == block_n;
+        if (text == 0) continue;
+        if (!G.ctext_runs.empty() && G.ctext_runs.back().end() == t && G.ctext_runs.back().full() == full)
+            G.ctext_runs.back().end_state = ((t + 1) << 1) | (int32_t)full;
+        else
+            G.ctext_runs.push_back({t, ((t + 1) << 1) | (int32_t)full});
+    }
+    // Intra-Image rows need the text keys only.  Among the compact tiles they are mixed
+    // with the sink keys; where text is rare (a few long images) the prompt's own tiles
+    // hold it in fewer tiles.  Both lists are exact, so the choice is a matter of cost
+    // only: count, for the last row of every image, the tiles with a text key either
+    // way (prefix counts over the two tile spaces) and take the smaller total; a close
+    // call is settled below by building both.
+    std::vector<int32_t> compact_tiles(G.Nc + 1, 0);
+    for (int32_t t = 0; t < G.Nc; ++t) compact_tiles[t + 1] = compact_tiles[t] + (G.ctext[t + 1] > G.ctext[t]);
+    int64_t cost_prompt = 0, cost_compact = 0;
+    int32_t text_tiles = 0, counted = 0, text_from = 0;   // prompt tiles with a text key before tile `counted`
+    for (int32_t g = 0; g < n_spans; ++g) {
+        const bs::SpanInfo &s = P.spans[g];
+        if (s.start > text_from) {                         // the text before image g
+            const int32_t n0 = std::max(counted, text_from / block_n), n1 = (s.start - 1) / block_n + 1;
+            text_tiles += std::max(0, n1 - n0);
+            counted = std::max(counted, n1);
+        }
+        text_from = s.end;
+        // (the tile of the image's last token counts if it holds a text key behind the image)
+        const int32_t n_last = (s.end - 1) / block_n;
+        const bool tail = n_last >= counted && P.n_text(std::min((n_last + 1) * block_n, L)) > P.n_text(s.end);
+        const int64_t rows = s.end - s.start;
+        cost_prompt += rows * (text_tiles + tail);
+        cost_compact += rows * compact_tiles[(s.free_before + P.sinks_in(g, s.end - s.start) + block_n - 1) / block_n];
+    }
+    G.intra_compact = cost_compact < cost_prompt;
+    build_class(G, c, tm->cls[c]);
+    if (cost_compact * 4 >= cost_prompt * 3 && cost_prompt * 4 >= cost_compact * 3) {
+        // the estimate is within a quarter: build the other variant as well and keep the shorter list
+        ClassLists alt;
+        G.intra_compact = !G.intra_compact;
+        build_class(G, c, alt);
+        if (alt.visited < tm->cls[c].visited) tm->cls[c] = std::move(alt);
+        else G.intra_compact = !G.intra_compact;
+    }
+    tm->intra_compact = G.intra_compact;
+}
+
+// The published lists of class c; made now if nobody has asked for them yet.
+const ClassLists &published(const bs_tilemap *tm, int c)
+{
+    std::lock_guard<std::mutex> lock(tm->lists_mutex);
+    if (tm->cls[c].row_ptr.empty()) {
+        try {
+            build_published(tm, c);
+        } catch (...) {
+            tm->cls[c] = ClassLists();
+            throw;
+        }
+    }
+    return tm->cls[c];
+}
+
+// Lists of the kernels' own, where further compact tiles make them shorter than the published ones.
+// Intra-Image rows see the text keys and their own image.  The map's compact tiles mix the text with the sinks, which are more
+// (a tenth of every image): in tiles of their own the text keys of a long prompt are a fraction of that, and all but the
+// last of them FULL.  302K tokens, 1100 images of 256, 26 sinks and 18 text tokens each: 155 text tiles instead of 380
+// mixed ones on average, a layer takes 185.9 ms (208.1 with the mixed ones); 16K tokens characterised, images of 1-4K: 3253 us
+// (3319, from the prompt's own tiles).  The kernels' tiles number at most half of the prompt's more than the published ones, so that the
+// static scratch, sized by these, holds all if K is read in place; with more text than that the class is nearly dense.
+void build_run_lists(bs_tilemap *tm)
+{
+    const PromptGeometry &P = tm->geo;
+    Geometry G(P);
+    G.packed = true;
+    G.text_tile0 = tm->text_tile0;
+    const std::vector<int32_t> &before = G.tiles_of_free(BS_INTRA).before;
+    G.text_tiles_before.assign(P.N0 + 1, 0);
+    for (int32_t n = 0; n < P.N0; ++n) G.text_tiles_before[n + 1] = G.text_tiles_before[n] + (before[n + 1] > before[n]);
+    build_class(G, BS_INTRA, tm->run[BS_INTRA]);
+}
+
+// The state of every key tile for query tile m: 0 skip, 1 partial, 2 full.
+void expand_states(const ClassLists &cl, int32_t m, std::vector<uint8_t> &states)
+{
+    std::fill(states.begin(), states.end(), 0);
+    for (int64_t p = cl.row_ptr[m]; p < cl.row_ptr[m + 1]; ++p)
+        for (int32_t n = cl.ranges[p].begin; n < cl.ranges[p].end(); ++n) states[n] = cl.ranges[p].full() ? 2 : 1;
 }
 
 bool spans_valid(const bs_span *spans, int32_t n, int32_t L)
@@ -534,63 +643,12 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
         }
 
         P.M = tm->M;
-        Geometry G(P);
-        bool intra_close_call = false;
-        if (tm->packed) {
-            G.packed = true;
-            G.Nc = tm->N - tm->N0;
-            // text keys before every compact tile
-            G.ctext.assign(G.Nc + 1, 0);
-            for (int32_t c = 0; c < G.Nc; ++c) G.ctext[c] = P.n_text(P.free_position(c * block_n));
-            G.ctext[G.Nc] = P.n_text(L);
-            for (int32_t c = 0; c < G.Nc; ++c) {
-                const int32_t text = G.ctext[c + 1] - G.ctext[c];
-                const bool full = text == block_n;
-                if (text == 0) continue;
-                if (!G.ctext_runs.empty() && G.ctext_runs.back().end() == c && G.ctext_runs.back().full() == full)
-                    G.ctext_runs.back().end_state = ((c + 1) << 1) | (int32_t)full;
-                else
-                    G.ctext_runs.push_back({c, ((c + 1) << 1) | (int32_t)full});
-            }
-            // Intra-Image rows need the text keys only.  Among the compact tiles they are mixed
-            // with the sink keys; where text is rare (a few long images) the prompt's own tiles
-            // hold it in fewer tiles.  Both lists are exact, so the choice is a matter of cost
-            // only: count, for the last row of every image, the tiles with a text key either
-            // way (prefix counts over the two tile spaces) and take the smaller total; a close
-            // call is settled below by building both.
-            std::vector<int32_t> compact_tiles(G.Nc + 1, 0);
-            for (int32_t c = 0; c < G.Nc; ++c) compact_tiles[c + 1] = compact_tiles[c] + (G.ctext[c + 1] > G.ctext[c]);
-            int64_t cost_prompt = 0, cost_compact = 0;
-            int32_t text_tiles = 0, counted = 0, text_from = 0;   // prompt tiles with a text key before tile `counted`
-            for (int32_t g = 0; g < n_spans; ++g) {
-                const bs::SpanInfo &s = P.spans[g];
-                if (s.start > text_from) {                         // the text before image g
-                    const int32_t n0 = std::max(counted, text_from / block_n), n1 = (s.start - 1) / block_n + 1;
-                    text_tiles += std::max(0, n1 - n0);
-                    counted = std::max(counted, n1);
-                }
-                text_from = s.end;
-                // (the tile of the image's last token counts if it holds a text key behind the image)
-                const int32_t n_last = (s.end - 1) / block_n;
-                const bool tail = n_last >= counted && P.n_text(std::min((n_last + 1) * block_n, L)) > P.n_text(s.end);
-                const int64_t rows = s.end - s.start;
-                cost_prompt += rows * (text_tiles + tail);
-                cost_compact += rows * compact_tiles[(s.free_before + P.sinks_in(g, s.end - s.start) + block_n - 1) / block_n];
-            }
-            G.intra_compact = tm->intra_compact = cost_compact < cost_prompt;
-            intra_close_call = cost_compact * 4 >= cost_prompt * 3 && cost_prompt * 4 >= cost_compact * 3;
-        }
-        for (int c = 0; c < 4; ++c) build_class(G, c, tm->cls[c]);
-        if (intra_close_call) {
-            // the estimate is within a quarter: build the other variant as well and keep the shorter list
-            ClassLists alt;
-            G.intra_compact = !G.intra_compact;
-            build_class(G, BS_INTRA, alt);
-            if (alt.visited < tm->cls[BS_INTRA].visited) {
-                tm->cls[BS_INTRA] = std::move(alt);
-                tm->intra_compact = G.intra_compact;
-            }
-        }
+        tm->n_tiles = tm->text_tile0 = tm->N;
+        const int64_t n_text_tiles = ((int64_t)P.n_text(L) + block_n - 1) / block_n;
+        if (tm->packed && n_text_tiles > 0 && 2 * n_text_tiles + 1 <= tm->N0) tm->n_tiles += (int32_t)n_text_tiles;
+        if (tm->text_tile0 < tm->n_tiles) build_run_lists(tm);
+        for (int c = 0; c < 4; ++c)
+            if (tm->run[c].row_ptr.empty()) build_published(tm, c);
     } catch (const std::bad_alloc &) {
         delete tm;
         return BS_ENOMEM;
@@ -653,6 +711,13 @@ int32_t bs::PromptGeometry::free_position(int32_t slot) const
     const int32_t r = slot - s.free_before, sinks = sinks_in((int32_t)(it - 1 - spans.begin()), s.end - s.start);
     if (r >= sinks) return s.end + (r - sinks);
     return s.start + (r < s.prefix ? r : offsets[offsets_below(s.prefix) + (r - s.prefix)]);
+}
+
+int32_t bs::PromptGeometry::text_position(int32_t slot) const
+{
+    // the span that the text token lies in front of
+    const auto it = std::upper_bound(spans.begin(), spans.end(), slot, [](int32_t t, const SpanInfo &s) { return t < s.text_before; });
+    return it->start - (it->text_before - slot);
 }
 
 int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, int32_t>> &runs) const
@@ -720,14 +785,14 @@ void bs_plan_solo(bs_tilemap *tm)
         base[c] = -1;
         if (std::find(tm->head_class.begin(), tm->head_class.end(), (uint8_t)c) == tm->head_class.end()) continue;
         base[c] = (int32_t)plan.ranges.size();
-        for (const TileRange &r : tm->cls[c].ranges) plan.ranges.push_back({r.begin, (r.end() << 4) | ((r.full() ? 2 : 1) << 2)});
+        for (const TileRange &r : tm->walked(c).ranges) plan.ranges.push_back({r.begin, (r.end() << 4) | ((r.full() ? 2 : 1) << 2)});
     }
     plan.items.reserve((size_t)H * M);
     for (int32_t h = 0; h < H; ++h) {
         const int c = tm->head_class[h];
-        const ClassLists &cl = tm->cls[c];
+        const ClassLists &cl = tm->walked(c);
         for (int32_t m = 0; m < M; ++m)
-            plan.items.push_back({h, m, -1, 0, base[c] + (int32_t)cl.row_ptr[m], base[c] + (int32_t)cl.row_ptr[m + 1], cl.row_tiles[m], c});
+            plan.items.push_back({h, m, -1, 0, base[c] + (int32_t)cl.row_ptr[m], base[c] + (int32_t)cl.row_ptr[m + 1], cl.row_tiles[m], c | cl.compact[m] << 2});
     }
     std::sort(plan.items.begin(), plan.items.end(), [](const bs::PairItem &a, const bs::PairItem &b) {
         if (a.n_tiles != b.n_tiles) return a.n_tiles > b.n_tiles;
@@ -776,8 +841,8 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     struct Span2 { int32_t begin, end, tiles; };
     bool count_only = false;
     auto merged = [&](int ca, int32_t ma, int cb, int32_t mb) {
-        const ClassLists &la = tm->cls[ca];
-        const ClassLists &lb = tm->cls[cb < 0 ? ca : cb];
+        const ClassLists &la = tm->walked(ca);
+        const ClassLists &lb = tm->walked(cb < 0 ? ca : cb);
         int64_t pa = la.row_ptr[ma], ea = la.row_ptr[ma + 1];
         int64_t pb = cb < 0 ? 0 : lb.row_ptr[mb], eb = cb < 0 ? 0 : lb.row_ptr[mb + 1];
         Span2 out{(int32_t)plan.ranges.size(), 0, 0};
@@ -932,8 +997,9 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         }
         plan.queue_off[kXcds] = (int32_t)plan.items.size();
     }
+    auto item_class = [&](int32_t head, int32_t tile) { return tm->head_class[head] | tm->walked(tm->head_class[head]).compact[tile] << 2; };
     for (bs::PairItem &it : plan.items)
-        it.classes = tm->head_class[it.head_a] | (it.head_b >= 0 ? tm->head_class[it.head_b] << 8 : 0);
+        it.classes = item_class(it.head_a, it.tile_a) | (it.head_b >= 0 ? item_class(it.head_b, it.tile_b) << 8 : 0);
     plan.gqa_group = G;
     plan.epoch = tm->class_epoch;
 }
@@ -1141,7 +1207,7 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
         bs_plan_pairs(tm, gqa_group);
         // check the plan against the per-class lists it was derived from
         const bs::PairPlan &plan = tm->pairs;
-        std::vector<uint8_t> want_a(tm->N), want_b(tm->N), got_a(tm->N), got_b(tm->N);
+        std::vector<uint8_t> want(tm->n_tiles), got_a(tm->n_tiles), got_b(tm->n_tiles);
         std::vector<int32_t> seen((size_t)tm->n_q_heads * tm->M, 0);
         int64_t tiles = 0, skips = 0;
         for (const bs::PairItem &it : plan.items) {
@@ -1156,7 +1222,7 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             for (int32_t p = it.list_begin; p < it.list_end; ++p) {
                 const bs::PairRange &r = plan.ranges[p];
                 const int32_t e = r.end_states >> 4, sa = (r.end_states >> 2) & 3, sb = r.end_states & 3;
-                if (r.begin < prev_end || e <= r.begin || e > tm->N || (sa == 0 && sb == 0) || sa == 3 || sb == 3) return BS_EINVAL;
+                if (r.begin < prev_end || e <= r.begin || e > tm->n_tiles || (sa == 0 && sb == 0) || sa == 3 || sb == 3) return BS_EINVAL;
                 for (int32_t n = r.begin; n < e; ++n) { got_a[n] = (uint8_t)sa; got_b[n] = (uint8_t)sb; }
                 skips += (int64_t)(e - r.begin) * ((sa == 0) + (sb == 0 && it.head_b >= 0));
                 n_tiles += e - r.begin;
@@ -1164,11 +1230,11 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             }
             if (n_tiles != it.n_tiles) return BS_EINVAL;
             tiles += n_tiles;
-            if (bs_tilemap_tile_states(tm, tm->head_class[it.head_a], it.tile_a, 1, want_a.data()) != BS_OK) return BS_EINVAL;
-            if (want_a != got_a) return BS_EINVAL;
+            expand_states(tm->walked(tm->head_class[it.head_a]), it.tile_a, want);
+            if (want != got_a) return BS_EINVAL;
             if (it.head_b >= 0) {
-                if (bs_tilemap_tile_states(tm, tm->head_class[it.head_b], it.tile_b, 1, want_b.data()) != BS_OK) return BS_EINVAL;
-                if (want_b != got_b) return BS_EINVAL;
+                expand_states(tm->walked(tm->head_class[it.head_b]), it.tile_b, want);
+                if (want != got_b) return BS_EINVAL;
             }
         }
         for (int32_t v : seen)
@@ -1216,7 +1282,7 @@ extern "C" int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t 
                 if (p.head_b != it.head_b || p.tile_b != it.tile_b || (p.classes & 0xffff) != it.classes) return BS_EINVAL;
                 parts_of[u].push_back((int32_t)i);
             }
-            std::vector<uint8_t> want(tm->N), got(tm->N), slot_used(sp.n_slots, 0);
+            std::vector<uint8_t> want(tm->n_tiles), got(tm->n_tiles), slot_used(sp.n_slots, 0);
             std::vector<bs::CutItem> cut;
             for (size_t u = 0; u < n_units; ++u) {
                 const bs::PairItem &it = plan.items[u];
@@ -1235,7 +1301,7 @@ extern "C" int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t 
                     if (p.list_begin < 0 || p.list_end < p.list_begin || (size_t)p.list_end > sp.ranges.size()) return BS_EINVAL;
                     for (int32_t r = p.list_begin; r < p.list_end; ++r) {
                         const int32_t b = sp.ranges[r].begin, e = sp.ranges[r].end_states >> 4;
-                        if (b < 0 || e <= b || e > tm->N) return BS_EINVAL;
+                        if (b < 0 || e <= b || e > tm->n_tiles) return BS_EINVAL;
                         for (int32_t t = b; t < e; ++t) {
                             if (got[t] != 0) return BS_EINVAL;
                             got[t] = (uint8_t)(sp.ranges[r].end_states & 15);
@@ -1319,7 +1385,14 @@ extern "C" int bs_tilemap_layout(const bs_tilemap *tm, int32_t *regrouped, int32
     if (!tm) return BS_EINVAL;
     if (regrouped) *regrouped = tm->regrouped;
     if (packed) *packed = tm->packed;
-    if (intra_compact) *intra_compact = tm->intra_compact;
+    if (intra_compact) {
+        try {
+            published(tm, BS_INTRA);
+        } catch (const std::bad_alloc &) {
+            return BS_ENOMEM;
+        }
+        *intra_compact = tm->intra_compact;
+    }
     return BS_OK;
 }
 
@@ -1342,14 +1415,44 @@ extern "C" int bs_tilemap_tile_states(const bs_tilemap *tm, int32_t cls, int32_t
     if (!tm || !states || cls < 0 || cls > 3 || q_tile_begin < 0 || q_tile_count < 0 ||
         (int64_t)q_tile_begin + q_tile_count > tm->M)
         return BS_EINVAL;
-    const ClassLists &cl = tm->cls[cls];
-    std::memset(states, 0, (size_t)q_tile_count * tm->N);
-    for (int32_t r = 0; r < q_tile_count; ++r) {
-        uint8_t *row = states + (size_t)r * tm->N;
-        for (int64_t p = cl.row_ptr[q_tile_begin + r]; p < cl.row_ptr[q_tile_begin + r + 1]; ++p) {
-            const TileRange &rg = cl.ranges[p];
-            for (int32_t n = rg.begin; n < rg.end(); ++n) row[n] = rg.full() ? 2 : 1;
+    try {
+        const ClassLists &cl = published(tm, cls);
+        std::vector<uint8_t> row(tm->N);
+        for (int32_t r = 0; r < q_tile_count; ++r) {
+            expand_states(cl, q_tile_begin + r, row);
+            std::memcpy(states + (size_t)r * tm->N, row.data(), row.size());
         }
+    } catch (const std::bad_alloc &) {
+        return BS_ENOMEM;
+    }
+    return BS_OK;
+}
+
+extern "C" int bs_tilemap_walked(const bs_tilemap *tm, int32_t cls, int32_t q_tile, int32_t *n_tiles, uint8_t *states,
+                                 int32_t *keys, int32_t *compact)
+{
+    if (!tm || cls < 0 || cls > 3 || q_tile < 0 || q_tile >= tm->M) return BS_EINVAL;
+    const ClassLists &cl = tm->walked(cls);
+    if (n_tiles) *n_tiles = tm->n_tiles;
+    if (compact) *compact = cl.compact[q_tile];
+    try {
+        if (states) {
+            std::vector<uint8_t> row(tm->n_tiles);
+            expand_states(cl, q_tile, row);
+            std::memcpy(states, row.data(), row.size());
+        }
+        if (keys) {
+            const bs::PromptGeometry &P = tm->geo;
+            const int64_t bn = tm->bn, n_free = P.n_free(tm->L), n_text = P.n_text(tm->L);
+            for (int64_t s = 0; s < tm->n_tiles * bn; ++s) {
+                const int64_t f = s - tm->N0 * bn, t = s - tm->text_tile0 * bn;
+                if (f < 0) keys[s] = s < tm->L ? (int32_t)s : -1;
+                else if (t < 0) keys[s] = f < n_free ? P.free_position((int32_t)f) : -1;
+                else keys[s] = t < n_text ? P.text_position((int32_t)t) : -1;
+            }
+        }
+    } catch (const std::bad_alloc &) {
+        return BS_ENOMEM;
     }
     return BS_OK;
 }
@@ -1359,18 +1462,23 @@ extern "C" int bs_tilemap_stats(const bs_tilemap *tm, int32_t cls, int64_t *visi
                                 int64_t *n_ranges)
 {
     if (!tm || cls < 0 || cls > 3) return BS_EINVAL;
-    const ClassLists &cl = tm->cls[cls];
     if (allowed_pairs || empty_rows) {   // counted when first asked for; the lists do not need them
-        std::lock_guard<std::mutex> lock(tm->count_mutex);
-        if (!tm->counted) count_pairs(tm->geo, tm->cls);
+        std::lock_guard<std::mutex> lock(tm->lists_mutex);
+        if (!tm->counted) count_pairs(tm->geo, tm->allowed_pairs, tm->empty_rows);
         tm->counted = true;
     }
-    if (visited) *visited = cl.visited;
-    if (full) *full = cl.full;
-    if (partial) *partial = cl.partial;
-    if (allowed_pairs) *allowed_pairs = cl.allowed_pairs;
-    if (empty_rows) *empty_rows = cl.empty_rows;
-    if (n_ranges) *n_ranges = (int64_t)cl.ranges.size();
+    if (allowed_pairs) *allowed_pairs = tm->allowed_pairs[cls];
+    if (empty_rows) *empty_rows = tm->empty_rows[cls];
+    if (!visited && !full && !partial && !n_ranges) return BS_OK;
+    try {
+        const ClassLists &cl = published(tm, cls);
+        if (visited) *visited = cl.visited;
+        if (full) *full = cl.full;
+        if (partial) *partial = cl.partial;
+        if (n_ranges) *n_ranges = (int64_t)cl.ranges.size();
+    } catch (const std::bad_alloc &) {
+        return BS_ENOMEM;
+    }
     return BS_OK;
 }
 

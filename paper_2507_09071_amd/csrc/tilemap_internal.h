@@ -83,6 +83,7 @@ struct PromptGeometry {
     }
     int32_t next_free(int cls, int32_t t) const;       // smallest free position >= t, or L
     int32_t free_position(int32_t slot) const;         // position of the slot-th free token
+    int32_t text_position(int32_t slot) const;         // position of the slot-th text token
     int32_t first_visible(int32_t i) const             // first position a query at i may see (window > 0)
     {
         const int32_t w = i >= window ? i - window + 1 : 0;
@@ -103,10 +104,11 @@ struct TileRange {
 };
 
 struct ClassLists {
-    std::vector<int64_t> row_ptr;     // M + 1 offsets into ranges
+    std::vector<int64_t> row_ptr;     // M + 1 offsets into ranges; empty: not built
     std::vector<TileRange> ranges;
     std::vector<int32_t> row_tiles;   // visited tiles per query tile (scheduling weight)
-    int64_t visited = 0, full = 0, partial = 0, allowed_pairs = 0, empty_rows = 0;
+    std::vector<uint8_t> compact;     // per query tile: its image rows take the keys outside their own image from compact tiles
+    int64_t visited = 0, full = 0, partial = 0;
 };
 
 // Work unit of the bf16 kernel: two (head, query tile) items that read the SAME KV head and walk
@@ -116,7 +118,7 @@ struct PairItem {
     int32_t head_a, tile_a, head_b, tile_b;
     int32_t list_begin, list_end;  // entries of PairPlan::ranges
     int32_t n_tiles;               // key tiles in the merged list (scheduling weight)
-    int32_t classes;               // head class of item A | head class of item B << 8
+    int32_t classes;               // item A | item B << 8; an item: its head's class | ClassLists::compact of its tile << 2
 };
 
 // Run of key tiles [begin, end) with one state per item: 0 skip, 1 partial, 2 full.
@@ -167,19 +169,24 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs);
 struct bs_tilemap {
     int32_t L = 0, bm = 0, bn = 0, M = 0, N = 0, n_q_heads = 0;
     // Key tiles: ids [0, N0) are the prompt's keys in position order; with packed keys, ids
-    // [N0, N) are compact tiles holding the free keys (text and sink keys) in position order.
-    int32_t N0 = 0;
+    // [N0, N) are compact tiles holding the free keys (text and sink keys) in position order.  The kernels know further
+    // compact tiles, ids [text_tile0, n_tiles), with the text keys alone (text_tile0 = n_tiles: none), see build_run_lists.
+    int32_t N0 = 0, text_tile0 = 0, n_tiles = 0;
     bool packed = false;
     bool bidir = false;                    // image tokens also attend to the later tokens of their own image
     int32_t window = 0;                    // > 0: sliding window, keys with i - j >= window are masked
     int32_t q_begin = 0;                   // the query rows are positions q_begin .. L - 1 (q / out hold L - q_begin rows per head)
-    bool intra_compact = false;            // packed: Intra-Image rows take their text keys from the compact tiles
     bool regrouped = false;                // the query rows are not in the natural order
     bs::PromptGeometry geo;
     std::vector<uint8_t> head_class;
-    mutable std::mutex count_mutex;        // allowed_pairs, empty_rows of cls: counted when first asked for
+    // The published lists and what is counted, made when first asked for (mutex) where the kernels walk lists of their own.
+    mutable std::mutex lists_mutex;
     mutable bool counted = false;
+    mutable int64_t allowed_pairs[4] = {0, 0, 0, 0}, empty_rows[4] = {0, 0, 0, 0};
+    mutable bool intra_compact = false;    // packed: the published lists of Intra-Image take the text keys from the compact tiles
     mutable bs::ClassLists cls[4];
+    bs::ClassLists run[4];                 // what the kernels walk instead of cls, if built
+    const bs::ClassLists &walked(int c) const { return run[c].row_ptr.empty() ? cls[c] : run[c]; }
     uint64_t class_epoch = 1;              // bumped by bs_tilemap_rebind: work units and their device copies are stale
     bs::PairPlan pairs;                    // built on first use for a given gqa_group and class vector
     bs::PairPlan solo;                     // one item per unit; built on first use
