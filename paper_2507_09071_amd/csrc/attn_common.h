@@ -38,6 +38,7 @@ struct KernelArgs {
     int32_t n_prompt_tiles;   // key tiles that are the prompt in position order; compact tiles of free keys follow, ...
     int32_t text_tile0;       // ... and from here on compact tiles of text keys (n_tiles: none)
     int32_t n_tiles;
+    int32_t first_tile;       // a tile that is there for a list without any (bf16: packed)
     int32_t window, bidir;
     int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
 };
@@ -124,18 +125,22 @@ struct PairWalker {
             states = __builtin_amdgcn_readfirstlane(r.y) & 15;
         }
     }
-    __device__ void init(const int2 *__restrict__ ranges, int begin, int end)
+    __device__ void init(const int2 *__restrict__ ranges, int begin, int end, int first_tile)
     {
         rg = ranges;
-        n = 0; n_end = 0; states = 0;
+        n = first_tile; n_end = 0; states = 0;
         p = __builtin_amdgcn_readfirstlane(begin);
         p_end = __builtin_amdgcn_readfirstlane(end);
         load();
     }
     __device__ bool valid() const { return p < p_end; }
+    // Behind its last tile the walker stays on it: what is fetched ahead there is never used, but it has to be a tile that
+    // was written (a NaN times a probability of zero is a NaN), and one that is still in the caches.
     __device__ void next()
     {
-        if (++n == n_end) { ++p; load(); }
+        if (n + 1 < n_end) ++n;
+        else if (++p < p_end) load();
+        else p = p_end;
     }
     __device__ int state(int grp) const { return grp ? (states & 3) : (states >> 2); }  // 0 skip 1 partial 2 full
 };

@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kF32Threads, D == 64 ? 2 : 1) void attn_prefill_f32
         const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * L * ROWB;
         const char *vh = static_cast<const char *>(a.v) + (size_t)kvh * L * ROWB;
         PairWalker w, w_next;   // the tile in work, and the one that is fetched
-        w.init(item_ranges, it1.x, it1.y);
+        w.init(item_ranges, it1.x, it1.y, 0);
         w_next = w;
         if (T > 0) issue_tile(kh, vh, w.n, 0);
 

@@ -209,10 +209,10 @@ __device__ inline int slot_key(const int32_t *__restrict__ compact_keys, int n, 
 
 template <int D>
 __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__restrict__ vt,
-                                    const int32_t *__restrict__ compact_keys, int L, int N, int N0, __bf16 *tile)
+                                    const int32_t *__restrict__ compact_keys, int L, int n, int N, int N0, __bf16 *tile)
 {
     constexpr int PAD = D + 2;  // odd word stride: the column gathers below spread over banks
-    const int n = blockIdx.x, kvh = blockIdx.y, tid = threadIdx.x;
+    const int kvh = blockIdx.y, tid = threadIdx.x;
     const __bf16 *src = v + (size_t)kvh * L * D;
     for (int idx = tid; idx < kBlockN * (D / 8); idx += 256) {
         const int key = idx / (D / 8), ch = idx % (D / 8);
@@ -259,18 +259,32 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     }
 }
 
-// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place; KV heads).
+// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place; KV heads), of the
+// tiles that the units of the launch walk.  Bound: HBM, so what counts is what is not packed: a chunk of 300 rows in a window
+// of 1024 needs 21 of a 27K prompt's 429 tiles (three layers: 153 us, 253 with all of them), an all-Dense layer no compact
+// ones (2048 rows behind 141K keys 9089 -> 8824 us, with the text tiles of Intra-Image).
+struct PackTiles {
+    int32_t first[6], count[6];   // runs of V^T tiles (prompt, free keys, text keys), then of K tiles
+};
 template <int D>
 __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                                      __bf16 *__restrict__ kp, __bf16 *__restrict__ vt,
                                                      const int32_t *__restrict__ compact_keys, int L, int N, int N0, int in_place,
-                                                     int32_t *__restrict__ queue_ctr)
+                                                     PackTiles todo, int32_t *__restrict__ queue_ctr)
 {
     __shared__ __bf16 tile[kBlockN * (D + 2)];
     // the attention kernel that follows starts on fresh unit queues
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
-    if ((int)blockIdx.x >= N) pack_k_tile<D>(k, kp, compact_keys, L, in_place + (int)blockIdx.x - N, N, N0, in_place);
-    else pack_vt_tile<D>(v, vt, compact_keys, L, N, N0, tile);
+    int x = blockIdx.x, run = 0;
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+        if (run == i && x >= todo.count[i]) { x -= todo.count[i]; run = i + 1; }
+    int n = todo.first[0];
+#pragma unroll
+    for (int i = 1; i < 6; ++i) n = run == i ? todo.first[i] : n;
+    n += x;
+    if (run >= 3) pack_k_tile<D>(k, kp, compact_keys, L, n, N, N0, in_place);
+    else pack_vt_tile<D>(v, vt, compact_keys, L, n, N, N0, tile);
 }
 
 constexpr int kPingPongThreads = 512;
@@ -389,7 +403,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             for (int e = 0; e < 8; ++e) pf[i >> 1][i & 1][e] = (__bf16)0.f;
         m_run = -INFINITY;
         l_run = 0.f;
-        w0.init(pair_ranges, list_begin, list_end);
+        w0.init(pair_ranges, list_begin, list_end, a.first_tile);
         w1 = w0; if (w1.valid()) w1.next();
         wt1 = w1;                                              // tile 1 (prologue)
         if (ahead && w1.valid()) w1.next();
@@ -940,28 +954,62 @@ bs::KernelArgs kernel_args(const void *q, const void *k, const void *v, void *ou
     a.n_prompt_tiles = tm->N0;
     a.text_tile0 = tm->text_tile0;
     a.n_tiles = tm->n_tiles;
+    a.first_tile = 0;
     a.window = tm->window;
     a.bidir = tm->bidir;
     a.q_begin = tm->q_begin;
     return a;
 }
 
+// The key tiles that a launch of the bf16 kernel reads, at least one: runs of the prompt's, of free keys, of text keys.
+struct TileRuns { int32_t first[3], end[3]; };
+
+// Those of the classes that the map is bound to, or of all that the kernels know.
+TileRuns tiles_read(const bs_tilemap *tm, bool all)
+{
+    TileRuns t = {{0, tm->N0, tm->text_tile0}, {tm->N0, tm->text_tile0, tm->n_tiles}};
+    if (all) return t;
+    bool bound[4] = {false, false, false, false};
+    for (uint8_t c : tm->head_class) bound[c] = true;
+    for (int kind = 0; kind < 3; ++kind) {
+        int32_t first = INT32_MAX, end = 0;
+        for (int c = 0; c < 4; ++c) {
+            if (!bound[c] || tm->walked(c).span[kind].end == 0) continue;
+            first = std::min(first, tm->walked(c).span[kind].first);
+            end = std::max(end, tm->walked(c).span[kind].end);
+        }
+        t.first[kind] = end == 0 ? t.first[kind] : first;
+        t.end[kind] = end == 0 ? t.first[kind] : end;
+    }
+    if (t.end[0] == t.first[0]) t.end[0] = t.first[0] + 1;   // (an empty list's walker names it)
+    return t;
+}
+
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
 // what the packed K tiles take, in front of the V^T tiles.
 template <int D>
-void launch_bf16(const bs::KernelArgs &a, const bs_tilemap *tm, const DeviceMap *d, void *workspace, size_t k_bytes,
+void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
                  float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
 {
+    a.first_tile = todo_tiles.first[0];
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
     const int32_t in_place = d->k_in_place;
-    const dim3 tgrid((unsigned)(2 * tm->n_tiles - in_place), (unsigned)n_kv_heads);
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
-    if (!kv_packed)
-        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, tgrid, dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, d->queue_ctr);
+    if (!kv_packed) {
+        bs::PackTiles todo;
+        int32_t n_todo = 0;
+        for (int i = 0; i < 6; ++i) {
+            const int32_t first = std::max(todo_tiles.first[i % 3], i < 3 ? 0 : in_place);
+            todo.first[i] = first;
+            todo.count[i] = std::max(0, todo_tiles.end[i % 3] - first);
+            n_todo += todo.count[i];
+        }
+        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, dim3((unsigned)n_todo, (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
+                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr);
+    }
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
                        d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
@@ -1121,8 +1169,10 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
         if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
         float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        // (a caller with several bindings of the map packs for all of them)
+        const TileRuns todo = tiles_read(tm, kv_packed != nullptr);
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
@@ -1196,8 +1246,8 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
-    else launch_bf16<64>(a, tm, d, ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

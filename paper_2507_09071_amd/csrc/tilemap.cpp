@@ -351,6 +351,7 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
     out.row_tiles.assign(G.M, 0);
     out.compact.assign(G.M, 0);
     out.ranges.clear();
+    for (auto &s : out.span) s = {};
     QueryTile qt;
     std::vector<int32_t> cand;
     std::vector<TileRange> run, seg_run, acc, tmp;
@@ -393,6 +394,16 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
             out.row_tiles[m] += len;
             if (r.full()) out.full += len; else out.partial += len;
             out.ranges.push_back(r);
+            // (a run of tiles may go on from one kind into the next)
+            const int32_t edge[4] = {0, G.N0, G.text_tile0 > 0 ? G.text_tile0 : INT32_MAX, INT32_MAX};
+            for (int kind = 0; kind < 3; ++kind) {
+                const int32_t b = std::max(r.begin, edge[kind]), e = std::min(r.end(), edge[kind + 1]);
+                if (e <= b) continue;
+                auto &s = out.span[kind];
+                if (s.end == 0) s.first = b;
+                s.first = std::min(s.first, b);
+                s.end = std::max(s.end, e);
+            }
         }
         out.row_ptr[m + 1] = (int64_t)out.ranges.size();
     }

@@ -109,6 +109,8 @@ struct ClassLists {
     std::vector<int32_t> row_tiles;   // visited tiles per query tile (scheduling weight)
     std::vector<uint8_t> compact;     // per query tile: its image rows take the keys outside their own image from compact tiles
     int64_t visited = 0, full = 0, partial = 0;
+    // Per kind of key tile (prompt, free keys, text keys): the visited ones lie in [first, end); both 0: none.
+    struct { int32_t first = 0, end = 0; } span[3];
 };
 
 // Work unit of the bf16 kernel: two (head, query tile) items that read the SAME KV head and walk
