@@ -127,8 +127,8 @@ int bs_build_tilemap_ex(const bs_span *spans, int32_t n_spans, int32_t seq_len,
  * (text queries too) and every class, only the keys with i - j < window (paper App. kernel, "Dense
  * Attention Subroutine": text queries follow the model's own dense mask, which is causal or a sliding
  * window depending on the model; the sparse masks live inside the dense mask).  0 = no window; a window of seq_len or
- * more is no window.  With a window BS_MAP_PACK_KEYS acts as BS_MAP_REGROUP_ROWS (packed lists are not built
- * for windows).  Together with BS_MAP_BIDIR_IMAGES the keys of
+ * more is no window.  With a window BS_MAP_PACK_KEYS acts as BS_MAP_REGROUP_ROWS in everything that the map
+ * reports (the kernels then have compact tiles of their own, bs_tilemap_walked).  Together with BS_MAP_BIDIR_IMAGES the keys of
  * the query's own image stay visible at any distance, also for images longer than the window: an image
  * query then sees its class pattern inside [min(window start, image start), image end).
  * Errors: as bs_build_tilemap_ex; BS_EINVAL for a negative offset, count or window.
@@ -195,8 +195,8 @@ int bs_tilemap_tile_states(const bs_tilemap *tm, int32_t cls, int32_t q_tile_beg
                            int32_t q_tile_count, uint8_t *states);
 
 /* The same decision as the kernels walk it, for one query tile: they may take keys from compact tiles of their own
- * behind the map's n_k_tiles (the text keys once more, without the sinks, for Intra-Image heads), where that means fewer
- * tiles.  *n_tiles = how many key tiles they know; states[*n_tiles] as above; keys[*n_tiles * block_n] the position of the
+ * behind the map's n_k_tiles (the text keys once more, without the sinks, for Intra-Image heads; with a window free keys and
+ * text keys), where that means fewer tiles.  *n_tiles = how many key tiles they know; states[*n_tiles] as above; keys[*n_tiles * block_n] the position of the
  * key in every slot, -1 where there is none; *compact = the tile's image rows take the keys outside their own image from
  * compact tiles, and only their own image's (classes with the intra bit) from the prompt's tiles.  Every allowed pair is
  * in exactly one tile.  Any output pointer may be NULL.  Host only, for tests and accounting. */

@@ -282,6 +282,13 @@ __global__ __launch_bounds__(256) void expand_map(const ExpandArgs a)
                     r.free_before = s.free_before;
                     r.free_hi = s.free_before + sinks_in(s, (a.bidir ? s.end : pos + 1) - s.start);
                     r.text_hi = s.text_before;
+                    if (a.window > 0) {   // those before the first one it sees (see QueryView)
+                        const int32_t first = a.bidir ? min(max(0, pos - a.window + 1), s.start) : max(0, pos - a.window + 1);
+                        const SpanInfo f = sp[span_at(first)];
+                        const int32_t x = first - f.start;
+                        r.free_lo = f.free_before + (x > 0 ? sinks_in(f, x) : x);
+                        r.text_lo = f.text_before + min(x, 0);
+                    }
                 }
             }
         }

@@ -254,7 +254,8 @@ void build_run(const Geometry &G, int cls, const QueryTile &qt, std::vector<int3
 //   the others: compact tiles, of which row i sees the slots
 //       Sink:             of the free keys up to its last visible position
 //       Intra-Image:      of the text keys before its image (in the text tiles, or mixed with sinks in the free tiles)
-//       Intra-Image+Sink: of the free keys before its image (the image's own are counted above).
+//       Intra-Image+Sink: of the free keys before its image (the image's own are counted above)
+//     from the first position in its window on.
 void build_run_packed(const Geometry &G, int cls, const Segment &s, bool ragged, std::vector<TileRange> &out)
 {
     out.clear();
@@ -283,13 +284,14 @@ void build_run_packed(const Geometry &G, int cls, const Segment &s, bool ragged,
         emit(tile0 + f1, tile0 + n1, 1);
     };
     const bs::SpanInfo &own = G.spans[s.g];
-    if (cls & 2) emit_keys(0, own.start, own.start, s.ea + 1, s.eb);
+    const int32_t lo = G.lo(s.a), all_lo = G.lo(s.b - 1);   // first visible position of the first / last row
+    if (cls & 2) emit_keys(0, std::max(own.start, lo), std::max(own.start, all_lo), s.ea + 1, s.eb);
     if (cls == BS_SINK) {
-        emit_keys(G.N0, 0, 0, G.n_free(s.ea + 1), G.n_free(s.eb));
+        emit_keys(G.N0, G.n_free(lo), G.n_free(all_lo), G.n_free(s.ea + 1), G.n_free(s.eb));
     } else if (cls == BS_INTRA_SINK) {
-        emit_keys(G.N0, 0, 0, own.free_before, own.free_before);
+        emit_keys(G.N0, G.n_free(lo), G.n_free(all_lo), own.free_before, own.free_before);
     } else if (G.text_tile0 > 0) {
-        emit_keys(G.text_tile0, 0, 0, own.text_before, own.text_before);
+        emit_keys(G.text_tile0, G.n_text(lo), G.n_text(all_lo), own.text_before, own.text_before);
     } else {
         const int32_t fb = own.free_before, c_all = ragged ? 0 : fb / G.bn;
         for (const TileRange &r : G.ctext_runs) {
@@ -345,7 +347,8 @@ bool text_tiles_pay(const Geometry &G, const std::vector<std::pair<int32_t, int3
     return (last.text_before + G.bn - 1) / G.bn <= G.text_tiles_before[last.start / G.bn];
 }
 
-void build_class(const Geometry &G, int cls, ClassLists &out)
+// `costs`: of the lists without compact tiles and as they were made, where both are compared (a window).
+void build_class(const Geometry &G, int cls, ClassLists &out, int64_t *costs = nullptr)
 {
     out.row_ptr.assign(G.M + 1, 0);
     out.row_tiles.assign(G.M, 0);
@@ -354,16 +357,12 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
     for (auto &s : out.span) s = {};
     QueryTile qt;
     std::vector<int32_t> cand;
-    std::vector<TileRange> run, seg_run, acc, tmp;
+    std::vector<TileRange> run, seg_run, acc, tmp, plain;
     std::vector<std::pair<int32_t, int32_t>> runs;
-    for (int32_t m = 0; m < G.M; ++m) {
-        // the tile's rows as runs of consecutive positions (one run in the natural order)
-        const bool ragged = G.tile_runs(m, runs) < G.bm;
+    // the list of a query tile whose rows are `runs`, to `acc`
+    auto build_tile = [&](bool ragged, bool compact) {
         acc.clear();
         bool first = true;
-        // (the rows of a packed map are regrouped: all of a tile are image rows, or none)
-        const bool compact = G.packed && cls != BS_DENSE && (cls != BS_INTRA || (G.text_tile0 > 0 ? text_tiles_pay(G, runs) : G.intra_compact));
-        out.compact[m] = compact;
         for (const auto &rr : runs) {
             describe_query_rows(G, rr.first, rr.second, ragged, qt);
             if (compact && qt.last_text < 0 && !qt.segs.empty()) {
@@ -389,6 +388,35 @@ void build_class(const Geometry &G, int cls, ClassLists &out)
                 acc.swap(tmp);
             }
         }
+    };
+    // (a PARTIAL tile takes an eighth longer than a FULL one)
+    auto cost = [](const std::vector<TileRange> &list) {
+        int64_t c = 0;
+        for (const TileRange &r : list) c += (int64_t)(r.end() - r.begin) * (r.full() ? 8 : 9);
+        return c;
+    };
+    for (int32_t m = 0; m < G.M; ++m) {
+        // the tile's rows as runs of consecutive positions (one run in the natural order)
+        const bool ragged = G.tile_runs(m, runs) < G.bm;
+        // (the rows of a map with compact tiles are regrouped: all of a tile are image rows, or none)
+        bool compact = G.packed && cls != BS_DENSE;
+        if (compact && G.window > 0 && costs) {   // both lists are short, so both are made
+            compact = m < G.m_img || !G.regrouped;
+            build_tile(ragged, false);
+            if (compact) {
+                acc.swap(plain);
+                build_tile(ragged, true);
+                const int64_t cost_compact = cost(acc), cost_plain = cost(plain);
+                compact = cost_compact < cost_plain;
+                if (!compact) acc.swap(plain);
+                costs[0] += cost_plain;
+                costs[1] += std::min(cost_compact, cost_plain);
+            }
+        } else {
+            if (cls == BS_INTRA) compact = compact && (G.text_tile0 > 0 ? text_tiles_pay(G, runs) : G.intra_compact);
+            build_tile(ragged, compact);
+        }
+        out.compact[m] = compact;
         for (const TileRange &r : acc) {
             const int32_t len = r.end() - r.begin;
             out.row_tiles[m] += len;
@@ -523,12 +551,28 @@ const ClassLists &published(const bs_tilemap *tm, int c)
 // mixed ones on average, a layer takes 185.9 ms (208.1 with the mixed ones); 16K tokens characterised, images of 1-4K: 3253 us
 // (3319, from the prompt's own tiles).  The kernels' tiles number at most half of the prompt's more than the published ones, so that the
 // static scratch, sized by these, holds all if K is read in place; with more text than that the class is nearly dense.
+//
+// In a window the map publishes no compact tiles, but a row of a sparse class sees as small a part of the window's tiles as it
+// does of a prompt's (a sixth of the pairs under Sink, a third under Intra-Image+Sink with images of 256), so the kernels know
+// both kinds, each query tile takes them where that is cheaper, and its list is cut at both ends.  A class that saves less
+// than a thirtieth that way keeps the published lists: packing the compact tiles costs about that (images of 1-5K, window
+// of 512: 1036 us with them, 1032 without).  Three layers, 27K tokens, images of 256: window of 512 1487 -> 1373 us, 1024
+// 1979 -> 1679, 4096 4667 -> 3289; d = 64, 1024: 1342 -> 1097; fp32, 6K tokens: 2998 -> 2339.
 void build_run_lists(bs_tilemap *tm)
 {
     const PromptGeometry &P = tm->geo;
     Geometry G(P);
     G.packed = true;
-    G.text_tile0 = tm->text_tile0;
+    G.text_tile0 = tm->text_tile0 < tm->n_tiles ? tm->text_tile0 : 0;
+    if (P.window > 0) {
+        for (int c : {BS_SINK, BS_INTRA, BS_INTRA_SINK}) {
+            if (c == BS_INTRA && G.text_tile0 == 0) continue;
+            int64_t costs[2] = {0, 0};
+            build_class(G, c, tm->run[c], costs);
+            if (costs[1] > costs[0] - costs[0] / 30) tm->run[c] = ClassLists();
+        }
+        return;
+    }
     const std::vector<int32_t> &before = G.tiles_of_free(BS_INTRA).before;
     G.text_tiles_before.assign(P.N0 + 1, 0);
     for (int32_t n = 0; n < P.N0; ++n) G.text_tiles_before[n + 1] = G.text_tiles_before[n] + (before[n + 1] > before[n]);
@@ -592,10 +636,9 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
     if (flags & ~(uint32_t)(BS_MAP_REGROUP_ROWS | BS_MAP_PACK_KEYS | BS_MAP_BIDIR_IMAGES)) return BS_EINVAL;
     if (window < 0) return BS_EINVAL;
     if (window >= seq_len) window = 0;   // every earlier key is inside the window
-    if (window > 0 && (flags & BS_MAP_PACK_KEYS)) {
-        // packed lists are not built for windows (they would have to be cut at both ends); the rows stay regrouped
-        flags = (flags & ~(uint32_t)BS_MAP_PACK_KEYS) | BS_MAP_REGROUP_ROWS;
-    }
+    const bool pack_window = window > 0 && (flags & BS_MAP_PACK_KEYS);
+    // a map with a window publishes no compact tiles, the kernels know some (build_run_lists); the rows are regrouped
+    if (pack_window) flags = (flags & ~(uint32_t)BS_MAP_PACK_KEYS) | BS_MAP_REGROUP_ROWS;
     if (n_sink_offsets < 0 || (n_sink_offsets > 0 && !sink_offsets)) return BS_EINVAL;
     for (int32_t o = 0; o < n_sink_offsets; ++o)
         if (sink_offsets[o] < 0) return BS_EINVAL;
@@ -655,9 +698,13 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
 
         P.M = tm->M;
         tm->n_tiles = tm->text_tile0 = tm->N;
-        const int64_t n_text_tiles = ((int64_t)P.n_text(L) + block_n - 1) / block_n;
-        if (tm->packed && n_text_tiles > 0 && 2 * n_text_tiles + 1 <= tm->N0) tm->n_tiles += (int32_t)n_text_tiles;
-        if (tm->text_tile0 < tm->n_tiles) build_run_lists(tm);
+        // compact tiles that the map does not publish, at most half of the prompt's (see build_run_lists)
+        const int64_t n_text_tiles = ((int64_t)P.n_text(L) + block_n - 1) / block_n, n_free_tiles = ((int64_t)n_free + block_n - 1) / block_n;
+        if (pack_window && n_spans > 0 && n_free > 0 && n_free < L && 2 * n_free_tiles + 1 <= tm->N0)
+            tm->n_tiles = tm->text_tile0 = tm->N0 + (int32_t)n_free_tiles;
+        if (tm->N0 < tm->n_tiles && n_text_tiles > 0 && 2 * (n_text_tiles + tm->n_tiles - tm->N) + 1 <= tm->N0)
+            tm->n_tiles += (int32_t)n_text_tiles;
+        if (tm->N < tm->n_tiles) build_run_lists(tm);
         for (int c = 0; c < 4; ++c)
             if (tm->run[c].row_ptr.empty()) build_published(tm, c);
     } catch (const std::bad_alloc &) {

@@ -1,4 +1,4 @@
-"""Intra-Image heads over text tiles: totals of text keys around multiples of the 64-key tile, both kernels, chunks, and the
+"""Compact tiles that only the kernels know: totals of text keys around multiples of the 64-key tile, windows, both kernels, chunks, and the
 static entry where the tiles that a map publishes fit its scratch and those that the kernels know only with K read in place."""
 import numpy as np
 import pytest
@@ -36,6 +36,23 @@ def test_text_keys(text, dtype, d):
 def test_chunk(rows):
     p = prompt(65, "bf16", 128, img_bidir=True, sink_offsets=(0, 5, 64, 130))
     suffix_parity(p, p.seq_len - rows, 92, bs.BS_MAP_PACK_KEYS)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("window,bidir", [(64, False), (129, True), (700, False), (1500, True)])
+def test_window(window, bidir, dtype, d):
+    """Images of 256 with sinks all over them: compact tiles cut at both ends."""
+    runs = [("T", 20)]
+    for i in range(9):
+        runs += [("I", 256), ("T", 12 + 5 * (i % 3))]
+    p = W.custom_prompt(runs, [I, S, S, I, IS, D, IS, IS], 2, d, dtype=dtype, sink_len=3, name=f"window{window}-{bidir}-{dtype}",
+                        span_sink=0, img_bidir=bidir, sink_offsets=tuple(range(3, 256, 13)), window=window,
+                        value_recipe={"std": 1.0, "first_key_scale": 4.0})
+    tm = bs.bs_build_tilemap(p.spans, p.seq_len, p.head_class, p.sink_len, flags=bs.BS_MAP_PACK_KEYS | (bs.BS_MAP_BIDIR_IMAGES if bidir else 0),
+                             window=window, sink_offsets=p.sink_offsets)
+    compact = sum(tm.walked(c, m)[2] for c in (S, I, IS) for m in range(tm.n_q_tiles))
+    assert compact > 0
+    full_parity(p, seed=94, flags=bs.BS_MAP_PACK_KEYS)
 
 
 def test_static_entry_with_more_tiles_than_published():

@@ -1,5 +1,5 @@
-"""The lists that the kernels walk where they differ from the published ones (text keys in compact tiles of their own): every
-allowed pair of the oracle's mask in exactly one tile, every state exact."""
+"""The lists that the kernels walk where they differ from the published ones (text keys in compact tiles of their own, compact
+tiles in a window): every allowed pair of the oracle's mask in exactly one tile, every state exact."""
 import numpy as np
 import pytest
 
@@ -10,34 +10,34 @@ from test_tilemap import packed_expectation
 from test_tilemap_model import random_layout
 
 
-def check_walked(tm, spans, L, sink_len, bm, bn, bidir, offsets, q_tiles=None, window=0):
+def check_walked(tm, spans, L, sink_len, bm, bn, bidir, offsets, window=0):
     """Returns how many of the query tiles walk key tiles that the map does not publish."""
     imgid, issink = oracle.token_arrays(spans, L, sink_len, offsets)
     rows = tm.row_order(bm)
+    n0, text, free = -(-L // bn), np.flatnonzero(imgid == 0), np.flatnonzero((imgid == 0) | (issink == 1))
     own_tiles = 0
     for c in range(4):
-        for m in range(tm.n_q_tiles) if q_tiles is None else q_tiles:
-            states, keys, compact = tm.walked(c, int(m), bn)
-            n0 = -(-L // bn)
+        full = oracle.mask(c, imgid, issink, bidir, window).astype(bool)
+        for m in range(tm.n_q_tiles):
+            states, keys, compact = tm.walked(c, m, bn)
             assert np.array_equal(keys[:n0].ravel()[:L], np.arange(L)) and (keys[:n0].ravel()[L:] < 0).all()
-            valid = rows[m][rows[m] >= 0]
-            allowed = oracle.mask_rows(c, imgid, issink, valid, bidir, window)
-            mask = np.zeros((L, L), dtype=bool) if L <= 4000 else None
-            if mask is not None:
-                mask[valid] = allowed
+            # the tiles behind the prompt's: free keys, then (if they are there) text keys
+            text0 = n0 + (-(-len(free) // bn) if len(states) > n0 else 0)
+            assert len(states) in (text0, text0 + -(-len(text) // bn))
+            assert np.array_equal(keys[n0:text0].ravel()[:len(free)], free[:bn * (text0 - n0)])
+            assert np.array_equal(keys[text0:].ravel()[:len(text)], text[:bn * (len(states) - text0)])
+            spaces = np.zeros(len(states), dtype=int)
+            spaces[n0:text0], spaces[text0:] = 1, 2
+            walks = {0} | ({2 if c == bs.INTRA and text0 < len(states) else 1} if compact else set())
             total = 0
             for n in range(len(states)):
-                if states[n] == 0 and n >= n0 and not compact:
+                if spaces[n] not in walks:
+                    assert states[n] == 0, (c, m, n)
                     continue
-                if states[n] == 0 and n >= tm.n_k_tiles and c != bs.INTRA:
-                    continue   # (tiles of the text keys alone, which only Intra-Image walks)
-                if c == bs.INTRA and len(states) > tm.n_k_tiles and n0 <= n < tm.n_k_tiles:
-                    assert states[n] == 0   # (its text keys are in the tiles behind)
-                    continue
-                cnt = int(packed_expectation(c, rows[m], keys[n], n < n0, mask, imgid, compact, compact).sum())
+                cnt = int(packed_expectation(c, rows[m], keys[n], n < n0, full, imgid, compact, compact).sum())
                 total += cnt
                 assert states[n] == (0 if cnt == 0 else (2 if cnt == bm * bn else 1)), (c, m, n, states[n], cnt)
-            assert total == int(allowed.sum()), (c, m)
+            assert total == int(full[rows[m][rows[m] >= 0]].sum()), (c, m)
             own_tiles += int((states[tm.n_k_tiles:] > 0).any())
     return own_tiles
 
@@ -54,6 +54,12 @@ def test_random_prompts(seed):
             tm = bs.bs_build_tilemap(spans, L, classes, sink_len, bm, bn, sink_offsets=offsets, q_begin=q_begin,
                                      flags=bs.BS_MAP_PACK_KEYS | (bs.BS_MAP_BIDIR_IMAGES if bidir else 0))
             check_walked(tm, spans, L, sink_len, bm, bn, bidir, offsets)
+            for window in (1, int(rng.integers(1, 20)), int(rng.integers(20, 90))):
+                if window < L:
+                    tw = bs.bs_build_tilemap(spans, L, classes, sink_len, bm, bn, sink_offsets=offsets, q_begin=q_begin, window=window,
+                                             flags=bs.BS_MAP_PACK_KEYS | (bs.BS_MAP_BIDIR_IMAGES if bidir else 0))
+                    check_walked(tw, spans, L, sink_len, bm, bn, bidir, offsets, window)
+                    tw.pair_plan(2)
             for group in (1, 2, 3):
                 tm.pair_plan(group)
             tm.share_plan(2, 7)
@@ -70,3 +76,16 @@ def test_kernel_tile_size(text):
     own = check_walked(tm, spans, L, 3, 128, 64, False, None)
     n_text = -(-text * 10 // 64)
     assert (own > 0) == (2 * n_text + 1 <= -(-L // 64)) and len(tm.walked(0, 0)[0]) == tm.n_k_tiles + (n_text if own else 0)
+
+
+@pytest.mark.parametrize("bidir", [False, True])
+@pytest.mark.parametrize("window", [100, 512, 1500])
+def test_kernel_tile_size_window(window, bidir):
+    runs = [("T", 9)]
+    for i in range(14):
+        runs += [("I", [64, 256, 333][i % 3]), ("T", 7 + i)]
+    L, spans = W.layout_from_runs(runs, "prefix")
+    offsets = [0, 3, 17, 64, 100, 200]
+    tm = bs.bs_build_tilemap(spans, L, np.arange(8) % 4, 3, flags=bs.BS_MAP_PACK_KEYS | (bs.BS_MAP_BIDIR_IMAGES if bidir else 0),
+                             window=window, sink_offsets=offsets)
+    assert check_walked(tm, spans, L, 3, 128, 64, bidir, offsets, window) > 0
