@@ -45,69 +45,44 @@
 
 namespace bs {
 
-// The same masking in two instructions per score, kept together so that the scheduler cannot
-// hoist the 32 bit tests in front of the 32 selects (32 registers of pressure in a kernel that
-// has none to spare): the allowed bit is spread over a word (0 / all ones) and a bit-field
-// insert then keeps the score or takes -inf.
-__device__ inline void apply_mask_tight(const floatx16 (&s)[2], floatx16 (&ms)[2], uint64_t allowed, int hl)
+// Scores of keys that the lane's query may not see become -inf, in place, two instructions per score: the allowed bit is
+// spread over a word (0 / all ones) and a bit-field insert then keeps the score or takes -inf.  One statement, so that
+// the scheduler cannot hoist the 32 bit tests in front of the 32 selects (32 registers of pressure in a kernel that has none
+// to spare).
+__device__ inline void apply_mask(floatx16 (&s)[2], uint64_t allowed, int hl)
 {
     const uint32_t w[2] = {(uint32_t)allowed >> (4 * hl), (uint32_t)(allowed >> 32) >> (4 * hl)};
-    const float ninf = -INFINITY;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            // out of place: the masked scores go to registers of their own, so the scores (in/out
-            // operands of the matrix phase) are not copied first
             uint32_t t;
-            float r;
+            float x = s[kb][v];
             asm("v_bfe_i32 %1, %2, %3, 1\n\t"
-                "v_bfi_b32 %0, %1, %4, %5"
-                : "=v"(r), "=&v"(t)
-                : "v"(w[kb]), "n"(8 * (v / 4) + (v % 4)), "v"(s[kb][v]), "v"(ninf));
-            ms[kb][v] = r;
+                "v_bfi_b32 %0, %1, %0, %4"
+                : "+v"(x), "=&v"(t)
+                : "v"(w[kb]), "n"(8 * (v / 4) + (v % 4)), "v"(-INFINITY));
+            s[kb][v] = x;
         }
 }
 
-// Same update as softmax_block, but the scores are only read and the probabilities go straight
-// into the bf16 B operands of the P.V MFMAs: contraction slot e of MFMA group (kb, t) is score
-// v = 8t + e of block kb, i.e. key 32kb + 16t + {4hl..4hl+3, 8+4hl..8+4hl+3}[e].
-//   MODE 0  FULL tile: every score counts.
-//   MODE 1  row-uniform PARTIAL tile: a lane's query sees either all 64 keys or none (`drop`).
-//           A dropped row keeps its running max and gets p = 0 through an infinite offset.
-//   MODE 2  general PARTIAL tile: `s` already holds -inf at the masked positions.
-// Fast path (FULL tiles): the probabilities are first formed against the reference point the row already
+// Online softmax of one tile: the scores are only read and the probabilities go straight into the bf16 B operands of
+// the P.V MFMAs: contraction slot e of MFMA group (kb, t) is score
+// v = 8t + e of block kb, i.e. key 32kb + 16t + {4hl..4hl+3, 8+4hl..8+4hl+3}[e].  Masked scores are -inf; a row with `drop`
+// sees none of the tile's keys: it keeps its running maximum and gets p = 0 through an infinite offset.
+// Fast path: the probabilities are first formed against the reference point the row already
 // has, without looking for the tile maximum.  Any reference gives the same quotient O / l as long as
 // nothing overflows, so this is exact whenever the row sums of the tile stay below kFastLimit -- which
 // they do on almost every tile after a row's first (scores of neighbouring tiles differ by a few units in
-// the exp2 domain, not by 16).  A wave in which some lane's sum is too large, infinite or NaN (no reference
-// yet: m = -inf) repeats the tile on the general path below, which moves the reference.  Returns whether
-// alpha may differ from 1.
-template <int MODE>
-__device__ inline bool softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float &m_run, float &l_run,
-                                    float &alpha, float c, bool drop)
+// the exp2 domain, not by 16).  A wave in which some lane's sum is too large, infinite or NaN repeats the tile on the general
+// path, which moves the reference; one with a row that has no reference yet (m = -inf) goes there at once.  alpha: what the
+// output tile is multiplied by.  PARTIAL tiles take the fast path as FULL ones do: 220 vector instructions instead of 255,
+// 120 instead of 155 where the wave's queries see all keys or none (chat_8k of the timed calls 1052 -> 1035 us, prompt_36k
+// 15777 -> 15650, window_27k 1711 -> 1698).  Two copies of the general path: with one that both branches reach, the compiler
+// straightens the branches and spills 80 registers.
+__device__ __forceinline__ void softmax_general(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float &m_run, float &l_run,
+                                                float &alpha, float c, bool drop)
 {
-    constexpr float kFastLimit = 65536.f;
-    if constexpr (MODE == 0) {   // PARTIAL tiles keep the one path (no registers to spare for two)
-        const float off = -(m_run * c);   // m = -inf: +inf, caught below
-        float sum[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + e], c, off));
-                    sum[e & 3] += pv;
-                    pf[kb][t][e] = (__bf16)pv;
-                }
-        const float tile_sum = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-        if (!__any(!(tile_sum <= kFastLimit))) {
-            l_run += tile_sum;
-            alpha = 1.f;
-            return false;
-        }
-    }
     // four independent max chains
     float mx[4];
 #pragma unroll
@@ -117,7 +92,7 @@ __device__ inline bool softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], 
 #pragma unroll
         for (int i = 0; i < 4; ++i) mx[i] = fmaxf(fmaxf(mx[i], s[i >> 1][8 * (i & 1) + v]), s[i >> 1][8 * (i & 1) + v + 1]);
     float mxl = max_across_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
-    if (MODE == 1) mxl = drop ? -INFINITY : mxl;
+    mxl = drop ? -INFINITY : mxl;
     // Lazy reference point: the running reference m only moves when the tile maximum exceeds it
     // by more than kLazyLog2 (in the exp2 domain), so p <= 2^kLazyLog2 instead of p <= 1.  The
     // result is the same quotient O / l; what changes is that alpha is exactly 1 on almost every
@@ -125,10 +100,10 @@ __device__ inline bool softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], 
     constexpr float kLazyLog2 = 8.f;
     const bool grow = fmaf(mxl, c, -(m_run * c)) > kLazyLog2;   // m_run = -inf, mxl finite: +inf > 8
     const float m_new = grow ? mxl : m_run;                     // both -inf: NaN > 8 is false
-    const float m_use = (MODE != 0 && m_new == -INFINITY) ? 0.f : m_new;  // no key seen so far: p = 0
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;       // no key seen so far: p = 0
     const float mc = m_use * c;
     alpha = grow ? __builtin_amdgcn_exp2f(fmaf(m_run, c, -mc)) : 1.f;     // m_run = -inf -> 0
-    const float off = (MODE == 1 && drop) ? -INFINITY : -mc;
+    const float off = drop ? -INFINITY : -mc;
     float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -142,7 +117,35 @@ __device__ inline bool softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], 
             }
     l_run = fmaf(l_run, alpha, (sum[0] + sum[1]) + (sum[2] + sum[3]));
     m_run = m_new;
-    return true;
+}
+
+__device__ __forceinline__ void softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float &m_run, float &l_run,
+                                             float &alpha, float c, bool drop)
+{
+    constexpr float kFastLimit = 65536.f;
+    const float off = drop ? -INFINITY : -(m_run * c);   // m = -inf: +inf, no reference yet
+    if (__any(off == INFINITY)) {
+        softmax_general(s, pf, m_run, l_run, alpha, c, drop);
+    } else {
+        float sum[4];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + e], c, off));
+                    sum[e & 3] = kb + t == 0 && e < 4 ? pv : sum[e & 3] + pv;
+                    pf[kb][t][e] = (__bf16)pv;
+                }
+        const float tile_sum = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        if (!__any(!(tile_sum <= kFastLimit))) {
+            l_run += tile_sum;
+            alpha = 1.f;
+        } else {
+            softmax_general(s, pf, m_run, l_run, alpha, c, drop);
+        }
+    }
 }
 
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
@@ -632,26 +635,23 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // tile), 1 partial, 2 full.  A skipped tile goes through the row-uniform path with
         // every row dropped (P = 0, running max and sum unchanged): rare, and one straight
         // code path keeps the register allocation of the loop simple.
-        const int st = have_item ? w0.state(grp) : 0;
-        float alpha;
-        bool rescale;
-        if (st == 2) {
-            rescale = softmax_pack<0>(s, pf, m_run, l_run, alpha, a.scale_log2e, false);
-        } else {
+        // (what stays the same for a unit is hidden from the compiler here: it made loops of their own for its values)
+        int hd = head, cls = item_class;
+        asm("" : "+s"(hd), "+s"(cls));
+        const int st = hd >= 0 ? w0.state(grp) : 0;
+        bool drop = false;
+        if (st != 2) {
             const int nu = __builtin_amdgcn_readfirstlane(w0.n);
-            uint64_t allowed = allowed_keys(qv, item_class, tb_cur, sb_cur, nu, a);
-            if (st == 0) allowed = 0ull;
-            if (__all(allowed == 0ull || allowed == ~0ull)) {
-                // every query of the wave sees all 64 keys or none (e.g. a text row and an
-                // image row over keys of another image): no per-score work
-                rescale = softmax_pack<1>(s, pf, m_run, l_run, alpha, a.scale_log2e, allowed == 0ull);
-            } else {
-                floatx16 ms[2];
-                apply_mask_tight(s, ms, allowed, hl);
-                rescale = softmax_pack<2>(ms, pf, m_run, l_run, alpha, a.scale_log2e, false);
-            }
+            const uint64_t allowed = st == 0 ? 0ull : allowed_keys(qv, cls, tb_cur, sb_cur, nu, a);
+            drop = allowed == 0ull;
+            // where every query of the wave sees all 64 keys or none (e.g. a text row and an
+            // image row over keys of another image) there is no per-score work
+            if (!__all(drop || allowed == ~0ull)) apply_mask(s, allowed, hl);
         }
-        if (rescale && __any(alpha != 1.f)) {
+        float alpha;
+        softmax_pack(s, pf, m_run, l_run, alpha, a.scale_log2e, drop);
+        asm volatile("" : "+v"(alpha));   // one place where the output tile may change, reached by every path: two cost 64 register copies
+        if (__any(alpha != 1.f)) {
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -790,6 +790,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // workgroup of 20 tiles each, takes 2058 instead of 2093 us a pass.
         int slot = 0;
         if (grp == 0) {
+            // (no first iteration of its own: the compiler puts the zeroing of the accumulators and fragments right in front of
+            // the MFMAs that read them, too close for the hardware, and does not know; tests/isa_check.py looks for that)
+#pragma nounroll
             for (int k = 0; k < T; ++k) {
                 if (wave8 == 0 && k == T - 1 && share_next >= share_end) next_ticket = take_ticket_async();   // consumed after the loop
                 phase_x(slot, k > 0, std::false_type{});
@@ -802,6 +805,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             phase_last(slot);
             __builtin_amdgcn_s_barrier();
         } else {
+#pragma nounroll
             for (int k = 0; k < T; ++k) {
                 __builtin_amdgcn_s_barrier();
                 phase_x(slot, k > 0, std::true_type{});

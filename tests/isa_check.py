@@ -20,6 +20,7 @@ import tempfile
 from paper_2507_09071_amd import build as _build
 
 WAIT_STATES = 12
+OPERAND_WAIT_STATES = 2   # vector write of a register, MFMA that reads it
 KERNELS = ("_ZN2bs17attn_prefill_bf16ILi128EEE", "_ZN2bs17attn_prefill_bf16ILi64EEE")
 
 
@@ -107,6 +108,27 @@ def lds_read_hazards(ins: list) -> list:
     return found
 
 
+def operand_hazards(ins: list) -> list:
+    """List of (vector instruction, mfma): an operand of an MFMA written by a vector instruction less than
+    OPERAND_WAIT_STATES wait states before it.  The hardware does not interlock that and the compiler, which sees no
+    matrix instruction, does not keep the distance."""
+    found = []
+    for a, t in enumerate(ins):
+        if not t.startswith("v_") or t.startswith(("v_mfma", "v_cmp", "v_readlane", "v_readfirstlane")):
+            continue
+        dst, ws = _regs(t.split(",")[0]), 0
+        for u in ins[a + 1:a + 1 + 2 * OPERAND_WAIT_STATES]:
+            if u.startswith(("s_cbranch", "s_branch", "s_endpgm")) or ws >= OPERAND_WAIT_STATES:
+                break
+            if u.startswith("v_mfma"):
+                if _regs(u.split(",", 1)[1]) & dst:
+                    found.append((t, u))
+                break
+            m = re.match(r"s_nop (\d+)", u)
+            ws += int(m.group(1)) + 1 if m else 1
+    return found
+
+
 def check(isa_path: str | None = None) -> dict:
     """Compile (unless a listing is given) and return {kernel symbol prefix: [hazards]}."""
     if isa_path is None:
@@ -119,7 +141,7 @@ def check(isa_path: str | None = None) -> dict:
     out = {}
     for k in KERNELS:
         ins = kernel_instructions(isa, k)
-        out[k] = mfma_hazards(ins) + lds_read_hazards(ins)
+        out[k] = mfma_hazards(ins) + lds_read_hazards(ins) + operand_hazards(ins)
     return out
 
 

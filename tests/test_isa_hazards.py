@@ -38,6 +38,15 @@ def test_checker_tracks_lds_reads_in_flight():
     assert len(isa_check.lds_read_hazards(overwritten)) == 1
 
 
+def test_checker_flags_an_operand_written_right_before_an_mfma():
+    mfma = "v_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], v[0:15]"
+    write = "v_mov_b64_e32 v[20:21], 0"
+    assert len(isa_check.operand_hazards([write, mfma])) == 1
+    assert len(isa_check.operand_hazards([write, "s_waitcnt lgkmcnt(0)", mfma])) == 1
+    assert isa_check.operand_hazards([write, "s_nop 1", mfma]) == []
+    assert isa_check.operand_hazards(["v_mov_b32_e32 v40, v20", mfma]) == []
+
+
 @pytest.mark.skipif(shutil.which(bs_build.hipcc()) is None, reason="hipcc not available")
 def test_compiled_bf16_kernels_have_no_mfma_hazard():
     res = isa_check.check()
