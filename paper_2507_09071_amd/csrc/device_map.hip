@@ -49,6 +49,11 @@ struct StagingBuffer {
     bool queued = false;         // a copy out of this buffer has been queued (done is recorded)
     bool in_use = false;         // a host thread is filling it
 };
+// The events order kernels of one device after each other, or tell the host that a kernel has read a pinned buffer: nobody
+// looks at memory that a kernel wrote from outside the device on their word, so they need no system-wide fence.  With one
+// the next kernel on the stream starts some 3 us later, twice or three times a call: six decoded layers 145 -> 135 us,
+// 517 rows behind 36K keys 743 -> 730.
+constexpr unsigned kEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 constexpr size_t kCacheMaxBlocks = 24;
 constexpr int kStagingBuffers = 8;
 std::mutex g_mem_mutex;
@@ -139,7 +144,7 @@ hipError_t staging_begin(size_t bytes, Staging *out)
         }
     }
     if (e == hipSuccess && !sb->done) {
-        e = hipEventCreateWithFlags(&sb->done, hipEventDisableTiming);
+        e = hipEventCreateWithFlags(&sb->done, kEventFlags);
         if (e != hipSuccess) sb->done = nullptr;
     }
     if (e != hipSuccess) {
@@ -356,7 +361,7 @@ int ensure_device_map(bs_tilemap *tm, hipStream_t st)
     } catch (const std::bad_alloc &) {
     }
     if (!d || !holder) { delete d; return BS_ENOMEM; }
-    e = hipEventCreateWithFlags(&holder->ev, hipEventDisableTiming);
+    e = hipEventCreateWithFlags(&holder->ev, kEventFlags);
     if (e != hipSuccess) { delete d; return fail_hip(e, "hipEventCreate"); }
     d->device = dev;
     d->last_stream = st;
