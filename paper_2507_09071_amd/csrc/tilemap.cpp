@@ -43,7 +43,7 @@ struct Geometry : PromptGeometry {
     int32_t Nc = 0, text_tile0 = 0;        // text_tile0 > 0: Intra-Image walks the text tiles
     std::vector<int32_t> ctext;            // packed: text keys in the compact tiles before tile c (Nc + 1)
     std::vector<TileRange> ctext_runs;     // runs of complete compact tiles by their text keys: FULL all, PARTIAL some
-    std::vector<int32_t> text_tiles_before;   // text_tile0 > 0: prompt tiles before n that hold a text key (N0 + 1)
+    std::vector<int32_t> text_tiles_before;   // text_tile0 > 0: prompt tiles with a text key before the first tile of each span
 
     int32_t lo(int32_t i) const { return window > 0 ? first_visible(i) : 0; }
     const FreeTiles &tiles_of_free(int cls) const
@@ -343,13 +343,15 @@ void combine_runs(const std::vector<TileRange> &a, const std::vector<TileRange> 
 // not counting those of their own images?  (Text tiles are FULL but for the last, so they win a tie.)
 bool text_tiles_pay(const Geometry &G, const std::vector<std::pair<int32_t, int32_t>> &runs)
 {
-    const bs::SpanInfo &last = G.spans[G.span_at(runs.back().second - 1)];
-    return (last.text_before + G.bn - 1) / G.bn <= G.text_tiles_before[last.start / G.bn];
+    const int32_t last = G.span_at(runs.back().second - 1);
+    return (G.spans[last].text_before + G.bn - 1) / G.bn <= G.text_tiles_before[last];
 }
 
-// `costs`: of the lists without compact tiles and as they were made, where both are compared (a window).
-void build_class(const Geometry &G, int cls, ClassLists &out, int64_t *costs = nullptr)
+// `sample`: only every so many query tiles, for what they cost: returns (cost) of them, without and with compact tiles.
+struct ListCosts { int64_t plain = 0, compact = 0; };
+ListCosts build_class(const Geometry &G, int cls, ClassLists &out, int32_t sample = 0)
 {
+    ListCosts costs;
     out.row_ptr.assign(G.M + 1, 0);
     out.row_tiles.assign(G.M, 0);
     out.compact.assign(G.M, 0);
@@ -400,21 +402,14 @@ void build_class(const Geometry &G, int cls, ClassLists &out, int64_t *costs = n
         const bool ragged = G.tile_runs(m, runs) < G.bm;
         // (the rows of a map with compact tiles are regrouped: all of a tile are image rows, or none)
         bool compact = G.packed && cls != BS_DENSE;
-        if (compact && G.window > 0 && costs) {   // both lists are short, so both are made
-            compact = m < G.m_img || !G.regrouped;
-            build_tile(ragged, false);
-            if (compact) {
-                acc.swap(plain);
-                build_tile(ragged, true);
-                const int64_t cost_compact = cost(acc), cost_plain = cost(plain);
-                compact = cost_compact < cost_plain;
-                if (!compact) acc.swap(plain);
-                costs[0] += cost_plain;
-                costs[1] += std::min(cost_compact, cost_plain);
-            }
-        } else {
-            if (cls == BS_INTRA) compact = compact && (G.text_tile0 > 0 ? text_tiles_pay(G, runs) : G.intra_compact);
-            build_tile(ragged, compact);
+        if (cls == BS_INTRA && G.window == 0) compact = compact && (G.text_tile0 > 0 ? text_tiles_pay(G, runs) : G.intra_compact);
+        for (int pass = sample > 0 ? 0 : 1; pass < 2; ++pass) {
+            build_tile(ragged, pass == 1 && compact);
+            if (sample > 0) (pass == 0 ? costs.plain : costs.compact) += cost(acc);
+        }
+        if (sample > 0) {
+            m += sample - 1;
+            continue;
         }
         out.compact[m] = compact;
         for (const TileRange &r : acc) {
@@ -422,20 +417,27 @@ void build_class(const Geometry &G, int cls, ClassLists &out, int64_t *costs = n
             out.row_tiles[m] += len;
             if (r.full()) out.full += len; else out.partial += len;
             out.ranges.push_back(r);
-            // (a run of tiles may go on from one kind into the next)
-            const int32_t edge[4] = {0, G.N0, G.text_tile0 > 0 ? G.text_tile0 : INT32_MAX, INT32_MAX};
-            for (int kind = 0; kind < 3; ++kind) {
-                const int32_t b = std::max(r.begin, edge[kind]), e = std::min(r.end(), edge[kind + 1]);
-                if (e <= b) continue;
+        }
+        if (!acc.empty()) {
+            auto add = [&](int kind, int32_t b, int32_t e) {
                 auto &s = out.span[kind];
-                if (s.end == 0) s.first = b;
-                s.first = std::min(s.first, b);
+                s.first = s.end == 0 ? b : std::min(s.first, b);
                 s.end = std::max(s.end, e);
+            };
+            if (acc.back().end() <= G.N0) {
+                add(0, acc.front().begin, acc.back().end());
+            } else {   // (a run of tiles may go on from one kind into the next)
+                const int32_t edge[4] = {0, G.N0, G.text_tile0 > 0 ? G.text_tile0 : INT32_MAX, INT32_MAX};
+                for (const TileRange &r : acc)
+                    for (int kind = 0; kind < 3; ++kind)
+                        if (std::max(r.begin, edge[kind]) < std::min(r.end(), edge[kind + 1]))
+                            add(kind, std::max(r.begin, edge[kind]), std::min(r.end(), edge[kind + 1]));
             }
         }
         out.row_ptr[m + 1] = (int64_t)out.ranges.size();
     }
     out.visited = out.full + out.partial;
+    return costs;
 }
 
 // Allowed pairs and empty rows per class, from prefix counts (no pair enumeration).
@@ -466,11 +468,10 @@ void count_pairs(const PromptGeometry &G, int64_t allowed_pairs[4], int64_t empt
     for (int c = 0; c < 4; ++c) { allowed_pairs[c] = pairs[c]; empty_rows[c] = empty[c]; }
 }
 
-// The lists that the map publishes for class c (lists_mutex held, or the map not handed out yet).
-void build_published(const bs_tilemap *tm, int c)
+// The lists that the map publishes for class c (lists_mutex held, or the map not handed out yet).  G: of the map's prompt.
+void build_published(const bs_tilemap *tm, Geometry &G, int c)
 {
-    const PromptGeometry &P = tm->geo;
-    Geometry G(P);
+    const PromptGeometry &P = G;
     const int32_t block_n = P.bn, L = P.L, n_spans = P.n_spans;
     G.packed = tm->packed;
     if (!tm->packed || c != BS_INTRA) {
@@ -535,7 +536,8 @@ const ClassLists &published(const bs_tilemap *tm, int c)
     std::lock_guard<std::mutex> lock(tm->lists_mutex);
     if (tm->cls[c].row_ptr.empty()) {
         try {
-            build_published(tm, c);
+            Geometry G(tm->geo);
+            build_published(tm, G, c);
         } catch (...) {
             tm->cls[c] = ClassLists();
             throw;
@@ -554,28 +556,38 @@ const ClassLists &published(const bs_tilemap *tm, int c)
 //
 // In a window the map publishes no compact tiles, but a row of a sparse class sees as small a part of the window's tiles as it
 // does of a prompt's (a sixth of the pairs under Sink, a third under Intra-Image+Sink with images of 256), so the kernels know
-// both kinds, each query tile takes them where that is cheaper, and its list is cut at both ends.  A class that saves less
-// than a thirtieth that way keeps the published lists: packing the compact tiles costs about that (images of 1-5K, window
-// of 512: 1036 us with them, 1032 without).  Three layers, 27K tokens, images of 256: window of 512 1487 -> 1373 us, 1024
-// 1979 -> 1679, 4096 4667 -> 3289; d = 64, 1024: 1342 -> 1097; fp32, 6K tokens: 2998 -> 2339.
-void build_run_lists(bs_tilemap *tm)
+// both kinds, and the lists are cut at both ends.  A class that saves less than a thirtieth of its steps that way, by some
+// four of its query tiles, keeps the published lists: packing the compact tiles costs about that (images of 1-5K, window
+// of 512: 1036 us with them, 1032 without).  Images of more than twice the window are not looked at: their rows see
+// little but their own image, and looking costs host time (10 us of a call of 127 us).
+// Three layers, 27K tokens, images of 256: window of 512 1487 -> 1373 us, 1024 1979 -> 1679, 4096 4667 -> 3289; d = 64, 1024:
+// 1342 -> 1097; fp32, 6K tokens: 2998 -> 2339.
+void build_run_lists(bs_tilemap *tm, Geometry &G)
 {
-    const PromptGeometry &P = tm->geo;
-    Geometry G(P);
+    const PromptGeometry &P = G;
     G.packed = true;
     G.text_tile0 = tm->text_tile0 < tm->n_tiles ? tm->text_tile0 : 0;
     if (P.window > 0) {
         for (int c : {BS_SINK, BS_INTRA, BS_INTRA_SINK}) {
             if (c == BS_INTRA && G.text_tile0 == 0) continue;
-            int64_t costs[2] = {0, 0};
-            build_class(G, c, tm->run[c], costs);
-            if (costs[1] > costs[0] - costs[0] / 30) tm->run[c] = ClassLists();
+            const ListCosts costs = build_class(G, c, tm->run[c], std::max(1, (P.regrouped ? P.m_img : P.M) / 4));
+            tm->run[c] = ClassLists();
+            if (costs.compact < costs.plain - costs.plain / 30) build_class(G, c, tm->run[c]);
         }
         return;
     }
-    const std::vector<int32_t> &before = G.tiles_of_free(BS_INTRA).before;
-    G.text_tiles_before.assign(P.N0 + 1, 0);
-    for (int32_t n = 0; n < P.N0; ++n) G.text_tiles_before[n + 1] = G.text_tiles_before[n] + (before[n + 1] > before[n]);
+    G.text_tiles_before.resize((size_t)P.n_spans + 1);
+    int32_t text_tiles = 0, counted = 0, text_from = 0;   // prompt tiles with a text key before tile `counted`
+    for (int32_t g = 0; g <= P.n_spans; ++g) {
+        const bs::SpanInfo &s = P.spans[g];
+        if (s.start > text_from) {
+            const int32_t n0 = std::max(counted, text_from / P.bn), n1 = (s.start - 1) / P.bn + 1;
+            text_tiles += std::max(0, n1 - n0);
+            counted = std::max(counted, n1);
+        }
+        text_from = s.end;
+        G.text_tiles_before[g] = text_tiles - (counted > s.start / P.bn);
+    }
     build_class(G, BS_INTRA, tm->run[BS_INTRA]);
 }
 
@@ -700,13 +712,16 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
         tm->n_tiles = tm->text_tile0 = tm->N;
         // compact tiles that the map does not publish, at most half of the prompt's (see build_run_lists)
         const int64_t n_text_tiles = ((int64_t)P.n_text(L) + block_n - 1) / block_n, n_free_tiles = ((int64_t)n_free + block_n - 1) / block_n;
-        if (pack_window && n_spans > 0 && n_free > 0 && n_free < L && 2 * n_free_tiles + 1 <= tm->N0)
+        const bool long_images = (int64_t)(L - P.n_text(L)) > (int64_t)2 * window * n_spans;
+        if (pack_window && !long_images && n_spans > 0 && n_free > 0 && n_free < L && 2 * n_free_tiles + 1 <= tm->N0)
             tm->n_tiles = tm->text_tile0 = tm->N0 + (int32_t)n_free_tiles;
         if (tm->N0 < tm->n_tiles && n_text_tiles > 0 && 2 * (n_text_tiles + tm->n_tiles - tm->N) + 1 <= tm->N0)
             tm->n_tiles += (int32_t)n_text_tiles;
-        if (tm->N < tm->n_tiles) build_run_lists(tm);
+        Geometry G(P);   // (one for all lists: they share its tables)
+        if (tm->N < tm->n_tiles) build_run_lists(tm, G);
+        G.text_tile0 = 0;
         for (int c = 0; c < 4; ++c)
-            if (tm->run[c].row_ptr.empty()) build_published(tm, c);
+            if (tm->run[c].row_ptr.empty()) build_published(tm, G, c);
     } catch (const std::bad_alloc &) {
         delete tm;
         return BS_ENOMEM;
