@@ -262,22 +262,30 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     }
 }
 
-// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place; KV heads), of the
+// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place, then workgroups that
+// bring the work units from a pinned buffer; KV heads), of the
 // tiles that the units of the launch walk.  Bound: HBM, so what counts is what is not packed: a chunk of 300 rows in a window
 // of 1024 needs 21 of a 27K prompt's 429 tiles (three layers: 153 us, 253 with all of them), an all-Dense layer no compact
 // ones (2048 rows behind 141K keys 9089 -> 8824 us, with the text tiles of Intra-Image).
 struct PackTiles {
     int32_t first[6], count[6];   // runs of V^T tiles (prompt, free keys, text keys), then of K tiles
+    int32_t n_tiles;              // all of them
 };
 template <int D>
 __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                                      __bf16 *__restrict__ kp, __bf16 *__restrict__ vt,
                                                      const int32_t *__restrict__ compact_keys, int L, int N, int N0, int in_place,
-                                                     PackTiles todo, int32_t *__restrict__ queue_ctr)
+                                                     PackTiles todo, int32_t *__restrict__ queue_ctr,
+                                                     const uint4 *__restrict__ copy_src, uint4 *__restrict__ copy_dst, size_t n_copy)
 {
     __shared__ __bf16 tile[kBlockN * (D + 2)];
+    if ((int)blockIdx.x >= todo.n_tiles) {   // (with it come the unit queues, at their beginning)
+        const size_t stride = (size_t)(gridDim.x - todo.n_tiles) * gridDim.y * 256;
+        for (size_t i = ((size_t)(blockIdx.x - todo.n_tiles) * gridDim.y + blockIdx.y) * 256 + threadIdx.x; i < n_copy; i += stride) copy_dst[i] = copy_src[i];
+        return;
+    }
     // the attention kernel that follows starts on fresh unit queues
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
+    if (n_copy == 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
     int x = blockIdx.x, run = 0;
 #pragma unroll
     for (int i = 0; i < 5; ++i)
@@ -991,10 +999,11 @@ TileRuns tiles_read(const bs_tilemap *tm, bool all)
 
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
-// what the packed K tiles take, in front of the V^T tiles.
+// what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do (units->n
+// stays: the caller says staging_queued).
 template <int D>
 void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
-                 float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, hipStream_t st, void *ev_main_start)
+                 float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
 {
     a.first_tile = todo_tiles.first[0];
     __bf16 *kp = static_cast<__bf16 *>(workspace);
@@ -1002,6 +1011,9 @@ void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, con
     const int32_t in_place = d->k_in_place;
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
+    if (kv_packed && units) {
+        if (bs::copy_pending(units, st) != hipSuccess) return;   // (reported by the caller's look at the last error)
+    }
     if (!kv_packed) {
         bs::PackTiles todo;
         int32_t n_todo = 0;
@@ -1011,8 +1023,14 @@ void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, con
             todo.count[i] = std::max(0, todo_tiles.end[i % 3] - first);
             n_todo += todo.count[i];
         }
-        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, dim3((unsigned)n_todo, (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr);
+        // the copy of the units: one load a thread, as the latency of the bus is all there is to it, up to 4 MB
+        const size_t n_copy = units ? units->n : 0;
+        const size_t copy_wgs = std::min<size_t>((n_copy + 255) / 256, 1024);
+        const size_t copy_x = (copy_wgs + n_kv_heads - 1) / n_kv_heads;
+        todo.n_tiles = n_todo;
+        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, dim3((unsigned)(n_todo + copy_x), (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
+                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr,
+                           n_copy ? units->src : nullptr, n_copy ? units->dst : nullptr, n_copy);
     }
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
@@ -1099,7 +1117,7 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
     if ((rc = device_setup(dev, &unused, &n_cus)) != BS_OK) return rc;
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     if (dtype == BS_BF16) {
-        rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_cus, 0, st);
+        rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_cus, 0, st, nullptr);
         if (rc == BS_OK) {   // results of cut units that have no room in the static scratch (the head dimension is not known yet)
             const int n_kv_heads = tm->n_q_heads / gqa_group;
             const size_t cut = cut_bytes(*d->shares_for(n_cus), 128);
@@ -1108,7 +1126,7 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
         }
     } else {   // for either head dimension, and the workspace of the larger plan
         const int32_t wgs128 = n_cus * bs::f32_wgs_per_cu(128), wgs64 = n_cus * bs::f32_wgs_per_cu(64);
-        rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, wgs128, wgs64, st);
+        rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, wgs128, wgs64, st, nullptr);
         if (rc == BS_OK)
             rc = take_workspace(d, std::max(bs::f32_workspace(*d->shares_for(wgs128), 128), bs::f32_workspace(*d->shares_for(wgs64), 64)), st);
     }
@@ -1149,11 +1167,13 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::RowsPlan rows = bs::plan_rows(tm, dtype, gqa_group, head_dim, n_cus);
     const uint64_t bound = d->bind_epoch;
+    bs::PendingCopy units;   // the work units on their way: the bf16 pre-pass brings them
     if (!rows.use || rows.need_bits)
         if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
     const int32_t n_wgs = dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim);
     if (!rows.use)
-        if ((rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_wgs, 0, st)) != BS_OK) return rc;
+        if ((rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_wgs, 0, st,
+                                     dtype == BS_BF16 ? &units : nullptr)) != BS_OK) return rc;
 
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
     if (rows.use) {
@@ -1169,14 +1189,23 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         const bs::ShareSet *const sh = shares.n_shares > 0 ? &shares : nullptr;
         const void *const old_workspace = d->vt_buf;
-        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) return rc;
+        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) {
+            if (bs::copy_pending(&units, st) != hipSuccess) d->bind_kind = bs::kBindNone;
+            return rc;
+        }
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
         if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
         float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
         // (a caller with several bindings of the map packs for all of them)
         const TileRuns todo = tiles_read(tm, kv_packed != nullptr);
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, st, ev_main_start);
+        if (head_dim == 128) launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        else launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        if (units.n > 0) {
+            e = hipPeekAtLastError();
+            if (e == hipSuccess) e = bs::staging_queued(units.staging, st);
+            else bs::staging_abandon(units.staging);
+            if (e != hipSuccess) d->bind_kind = bs::kBindNone;
+        }
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
@@ -1250,8 +1279,8 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
-    else launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, st, nullptr);
+    else if (head_dim == 128) launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    else launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

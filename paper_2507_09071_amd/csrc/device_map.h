@@ -112,12 +112,24 @@ hipError_t staging_begin(size_t bytes, Staging *out);
 hipError_t staging_commit(const Staging &s, void *dst, size_t bytes, hipStream_t st);
 void staging_abandon(const Staging &s);
 
+// A copy that is left to a kernel which the caller launches anyway: `n` pieces of 16 bytes from the pinned buffer.  The caller
+// launches that kernel and calls staging_queued, or has the copy done on its own (copy_pending).
+struct PendingCopy {
+    Staging staging;
+    const uint4 *src = nullptr;
+    uint4 *dst = nullptr;
+    size_t n = 0;                  // 0: nothing to do
+};
+hipError_t staging_queued(const Staging &s, hipStream_t st);   // the kernel that reads the buffer is on the stream
+hipError_t copy_pending(PendingCopy *copy, hipStream_t st);    // a kernel of its own; no-op if there is nothing to do
+
 // The map's device side without any upload: the device it lives on, its last-use event (once per map).
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Make the prompt part (once per map) / upload the binding part (when stale) on `st`; no host-side wait.
 int upload_prompt_part(bs_tilemap *tm, hipStream_t st);
 // The shares are cut for n_wgs workgroups, and for n_wgs_too if that is not 0.
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st);
+// `later` (may be null): leaves the copy to the caller.
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st, PendingCopy *later);
 // Order work queued on `st` after the map's previous use if that was on another stream.
 int order_after_last_use(DeviceMap *d, hipStream_t st);
 

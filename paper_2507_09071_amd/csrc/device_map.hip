@@ -166,21 +166,34 @@ __global__ __launch_bounds__(256) void copy_from_host(const uint4 *__restrict__ 
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) dst[i] = src[i];
 }
 
-hipError_t staging_commit(const Staging &s, void *dst, size_t bytes, hipStream_t st)
+hipError_t staging_queued(const Staging &s, hipStream_t st)
 {
     StagingBuffer &sb = g_staging[s.slot];
-    const size_t n = (bytes + 15) / 16;   // both blocks are longer than that: their sizes are multiples of 1 MiB
-    hipError_t e = hipSuccess;
-    if (n) {
-        hipLaunchKernelGGL(copy_from_host, dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024)), dim3(256), 0, st,
-                           static_cast<const uint4 *>(sb.host), static_cast<uint4 *>(dst), n);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipEventRecord(sb.done, st);
+    const hipError_t e = hipEventRecord(sb.done, st);
     std::lock_guard<std::mutex> lock(g_mem_mutex);
     sb.queued = (e == hipSuccess);
     sb.in_use = false;
     return e;
+}
+
+hipError_t copy_pending(PendingCopy *copy, hipStream_t st)
+{
+    if (copy->n == 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_from_host, dim3((unsigned)std::min<size_t>((copy->n + 255) / 256, 1024)), dim3(256), 0, st,
+                       copy->src, copy->dst, copy->n);
+    copy->n = 0;
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) return staging_queued(copy->staging, st);
+    staging_abandon(copy->staging);
+    return e;
+}
+
+hipError_t staging_commit(const Staging &s, void *dst, size_t bytes, hipStream_t st)
+{
+    // (whole pieces of 16 bytes: the sizes of both blocks are multiples of 1 MiB)
+    PendingCopy copy{s, static_cast<const uint4 *>(s.host), static_cast<uint4 *>(dst), (bytes + 15) / 16};
+    if (copy.n == 0) staging_abandon(s);
+    return copy_pending(&copy, st);
 }
 
 void staging_abandon(const Staging &s)
@@ -445,7 +458,7 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st)
+int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st, PendingCopy *later)
 {
     DeviceMap *d = tm->dev;
     if (!d) return BS_EINVAL;
@@ -509,8 +522,9 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
         staging_abandon(sg);
         return fail_hip(e, "hipMalloc(work units)");
     }
-    e = staging_commit(sg, blob, bytes, st);
-    if (e != hipSuccess) {
+    if (later) {
+        *later = {sg, static_cast<const uint4 *>(sg.host), static_cast<uint4 *>(blob), (bytes + 15) / 16};
+    } else if ((e = staging_commit(sg, blob, bytes, st)) != hipSuccess) {
         (void)hipFree(blob);
         return fail_hip(e, "copy of the work units");
     }
