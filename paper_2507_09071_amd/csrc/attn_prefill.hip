@@ -1167,13 +1167,20 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
     if ((rc = bs::order_after_last_use(d, st)) != BS_OK) return rc;
     const bs::RowsPlan rows = bs::plan_rows(tm, dtype, gqa_group, head_dim, n_cus);
     const uint64_t bound = d->bind_epoch;
-    bs::PendingCopy units;   // the work units on their way: the bf16 pre-pass brings them
-    if (!rows.use || rows.need_bits)
-        if ((rc = bs::upload_prompt_part(tm, st)) != BS_OK) return rc;
+    // The work units on their way: the bf16 pre-pass brings them, for fp32 the kernel that makes the prompt part (which for
+    // bf16 is launched before the units are planned: the two then run side by side).
+    bs::PendingCopy units;
+    const auto give_up = [&](int code) {
+        if (bs::copy_pending(&units, st) != hipSuccess) d->bind_kind = bs::kBindNone;
+        return code;
+    };
     const int32_t n_wgs = dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim);
-    if (!rows.use)
-        if ((rc = bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_wgs, 0, st,
-                                     dtype == BS_BF16 ? &units : nullptr)) != BS_OK) return rc;
+    if (dtype == BS_F32)
+        if ((rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, n_wgs, 0, st, &units)) != BS_OK) return rc;
+    if (!rows.use || rows.need_bits)
+        if ((rc = bs::upload_prompt_part(tm, st, &units)) != BS_OK) return give_up(rc);
+    if (dtype == BS_BF16 && !rows.use)
+        if ((rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_wgs, 0, st, &units)) != BS_OK) return rc;
 
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
     if (rows.use) {
@@ -1189,10 +1196,7 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         const bs::ShareSet *const sh = shares.n_shares > 0 ? &shares : nullptr;
         const void *const old_workspace = d->vt_buf;
-        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) {
-            if (bs::copy_pending(&units, st) != hipSuccess) d->bind_kind = bs::kBindNone;
-            return rc;
-        }
+        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) return give_up(rc);
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
         if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
         float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
@@ -1208,6 +1212,10 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         }
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
+        if ((e = bs::copy_pending(&units, st)) != hipSuccess) {
+            d->bind_kind = bs::kBindNone;
+            return bs::fail_hip(e, "copy of the work units");
+        }
         if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         bs::launch_f32(a, d, shares, d->vt_buf, head_dim, st);

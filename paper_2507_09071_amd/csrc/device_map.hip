@@ -239,6 +239,10 @@ struct ExpandArgs {
     int4 *rows;
     int32_t *compact_keys;
     uint64_t *text_bits, *sink_bits;
+    int32_t n_workgroups;      // behind these, workgroups that bring the work units from a pinned buffer
+    const uint4 *copy_src;
+    uint4 *copy_dst;
+    size_t n_copy;
 };
 
 // Number of the first n table entries for which `before` holds (it holds for a prefix of them).
@@ -260,6 +264,11 @@ __device__ inline int32_t partition(int32_t n, F before)
 // microseconds, and a kernel that works on a query tile finds all it has to know about a row in one record.)
 __global__ __launch_bounds__(256) void expand_map(const ExpandArgs a)
 {
+    if ((int32_t)blockIdx.x >= a.n_workgroups) {
+        const size_t stride = (size_t)(gridDim.x - a.n_workgroups) * 256;
+        for (size_t i = (size_t)(blockIdx.x - a.n_workgroups) * 256 + threadIdx.x; i < a.n_copy; i += stride) a.copy_dst[i] = a.copy_src[i];
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int32_t wave = (int32_t)(blockIdx.x * 4 + (threadIdx.x >> 6));
     const SpanInfo *sp = a.spans;
@@ -384,7 +393,7 @@ int ensure_device_map(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
+int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units)
 {
     if (!tm) return BS_EINVAL;
     if (tm->dev && tm->dev->blob) return BS_OK;
@@ -441,8 +450,18 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st)
         a.text_bits = reinterpret_cast<uint64_t *>(b + off_tbits);
         a.sink_bits = reinterpret_cast<uint64_t *>(b + off_sbits);
         const int64_t waves = 2 * (int64_t)tm->M + tm->n_tiles;
-        hipLaunchKernelGGL(expand_map, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a);
+        a.n_workgroups = (int32_t)((waves + 3) / 4);
+        int32_t copy_wgs = 0;
+        if (units && units->n > 0) {
+            a.copy_src = units->src; a.copy_dst = units->dst; a.n_copy = units->n;
+            copy_wgs = (int32_t)std::min<size_t>((units->n + 255) / 256, 1024);
+        }
+        hipLaunchKernelGGL(expand_map, dim3((unsigned)(a.n_workgroups + copy_wgs)), dim3(256), 0, st, a);
         e = hipGetLastError();
+        if (e == hipSuccess && copy_wgs > 0) {
+            units->n = 0;
+            e = staging_queued(units->staging, st);
+        }
     }
     if (e == hipSuccess) e = hipEventRecord(d->last_use->ev, st);
     if (e != hipSuccess) {
