@@ -90,3 +90,20 @@ def test_kernel_tile_size_window(window, bidir):
                              window=window, sink_offsets=offsets)
     own = check_walked(tm, spans, L, 3, 128, 64, bidir, offsets, window)
     assert (own > 0) == (window > 100)   # (images of more than twice the window keep the published lists)
+
+
+def test_units_of_two_heads_take_the_shorter_rule_block_by_block():
+    """A Dense and a Sink head of one KV group in a window: image rows pair tiles of one head, text rows the two heads."""
+    runs = [("T", 40)]
+    for _ in range(40):
+        runs += [("I", 256), ("T", 30)]
+    L, spans = W.layout_from_runs(runs, "prefix")
+    tm = bs.bs_build_tilemap(spans, L, [bs.DENSE, bs.SINK], 3, flags=bs.BS_MAP_PACK_KEYS | bs.BS_MAP_BIDIR_IMAGES, window=1024,
+                             sink_offsets=list(range(0, 256, 9)))
+    M = tm.n_q_tiles
+    visited = [[tm.walked(c, m)[0] > 0 for m in range(M)] for c in (bs.DENSE, bs.SINK)]
+    blocks = [range(m, min(m + 2, M)) for m in range(0, M, 2)]
+    rows = [sum(int(np.any([v[m] for m in b], axis=0).sum()) for v in visited) for b in blocks]
+    cross = [sum(int((visited[0][m] | visited[1][m]).sum()) for m in b) for b in blocks]
+    steps = tm.pair_plan(2)["unit_tiles"]
+    assert sum(np.minimum(rows, cross)) <= steps < 0.95 * min(sum(rows), sum(cross))
