@@ -31,6 +31,7 @@ using bs::PromptGeometry;
 // What the list builders need on top of the prompt's geometry (per-tile tables, no per-token ones).
 struct Geometry : PromptGeometry {
     explicit Geometry(const PromptGeometry &g) : PromptGeometry(g) {}
+    explicit Geometry(PromptGeometry &&g) : PromptGeometry(std::move(g)) {}
     // Per key tile, for classes without / with the sink bit; filled on first use.  The lists ask for every (query tile, key
     // tile): from the closed forms alone, a list of 36K tokens with sinks at fixed offsets took 14 ms instead of 4.
     struct FreeTiles {                     // N0 + 1 entries each
@@ -359,7 +360,7 @@ ListCosts build_class(const Geometry &G, int cls, ClassLists &out, int32_t sampl
     for (auto &s : out.span) s = {};
     QueryTile qt;
     std::vector<int32_t> cand;
-    std::vector<TileRange> run, seg_run, acc, tmp, plain;
+    std::vector<TileRange> run, seg_run, acc, tmp;
     std::vector<std::pair<int32_t, int32_t>> runs;
     // the list of a query tile whose rows are `runs`, to `acc`
     auto build_tile = [&](bool ragged, bool compact) {
@@ -717,11 +718,12 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
             tm->n_tiles = tm->text_tile0 = tm->N0 + (int32_t)n_free_tiles;
         if (tm->N0 < tm->n_tiles && n_text_tiles > 0 && 2 * (n_text_tiles + tm->n_tiles - tm->N) + 1 <= tm->N0)
             tm->n_tiles += (int32_t)n_text_tiles;
-        Geometry G(P);   // (one for all lists: they share its tables)
+        Geometry G(std::move(P));   // (one for all lists: they share its tables; the prompt's geometry goes back to the map below)
         if (tm->N < tm->n_tiles) build_run_lists(tm, G);
         G.text_tile0 = 0;
         for (int c = 0; c < 4; ++c)
             if (tm->run[c].row_ptr.empty()) build_published(tm, G, c);
+        P = std::move(static_cast<PromptGeometry &>(G));
     } catch (const std::bad_alloc &) {
         delete tm;
         return BS_ENOMEM;
