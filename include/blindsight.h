@@ -218,7 +218,7 @@ int bs_tilemap_stats(const bs_tilemap *tm, int32_t cls, int64_t *visited, int64_
  * pairs of (head, query tile) items that read the same KV head and walk one merged key-tile
  * list, so a workgroup streams every K / V tile once for two items.  Returns BS_OK only if
  * every (head, query tile) appears in exactly one unit and each unit's merged list reproduces
- * both items' tile states.  Outputs (may be NULL): number of units, key tiles summed over the
+ * both items' tile states as the kernel walks them (bs_tilemap_walked).  Outputs (may be NULL): number of units, key tiles summed over the
  * units' merged lists, and steps on which one of a unit's items has nothing to do.
  * Host only.  bs_attn_prefill plans by itself; this entry point is for tests and accounting.
  */

@@ -22,8 +22,8 @@
 //  * K and V^T tiles travel global -> LDS with 16-byte LDS-direct loads (no VGPR staging) into a
 //    ring of 4 K + 4 V^T slots shared by the two groups; ONE barrier per key tile, placed so that
 //    on every SIMD one wave runs its matrix phase while the other runs its vector phase;
-//  * PARTIAL tiles build one 64-bit allowed-key word per lane from per-tile text/sink bit
-//    masks, the query's own image range and the causal bound, then test one bit per score.
+//  * PARTIAL tiles build one 64-bit allowed-key word per lane from the intervals that the query sees (and, for sparse
+//    classes without compact tiles, per-tile text/sink bit masks), then test one bit per score.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
