@@ -946,6 +946,19 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
             cur = nxt;
         }
         if (rb >= 0) plan.ranges.push_back({rb, (re << 4) | rs});
+        // Compact tiles first.  They begin with the prompt's first key, which takes most of the weight in many a row, and the
+        // probabilities of the largest key of a row's first tile are 1 exactly: it is not rounded to bf16.  (Error of bf16
+        // results against fp64 with the image's own tiles first: 4-8 % larger.)
+        if (!count_only && tm->n_tiles > tm->N0) {
+            size_t i = out.begin;
+            while (i < plan.ranges.size() && plan.ranges[i].end_states >> 4 <= tm->N0) ++i;
+            if (i < plan.ranges.size() && plan.ranges[i].begin < tm->N0) {   // a run that goes on from the prompt's tiles
+                const bs::PairRange whole = plan.ranges[i];
+                plan.ranges[i].end_states = (tm->N0 << 4) | (whole.end_states & 15);
+                plan.ranges.insert(plan.ranges.begin() + ++i, {tm->N0, whole.end_states});
+            }
+            std::rotate(plan.ranges.begin() + out.begin, plan.ranges.begin() + i, plan.ranges.end());
+        }
         out.end = (int32_t)plan.ranges.size();
         return out;
     };
@@ -1328,14 +1341,16 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             if (it.head_b >= 0) ++seen[(size_t)it.head_b * tm->M + it.tile_b];
             std::fill(got_a.begin(), got_a.end(), 0);
             std::fill(got_b.begin(), got_b.end(), 0);
-            int32_t prev_end = 0, n_tiles = 0;
+            int32_t prev_begin = 0, prev_end = 0, n_tiles = 0;
             for (int32_t p = it.list_begin; p < it.list_end; ++p) {
                 const bs::PairRange &r = plan.ranges[p];
                 const int32_t e = r.end_states >> 4, sa = (r.end_states >> 2) & 3, sb = r.end_states & 3;
+                if (r.begin < tm->N0 && prev_begin >= tm->N0) prev_end = 0;   // (compact tiles come first)
                 if (r.begin < prev_end || e <= r.begin || e > tm->n_tiles || (sa == 0 && sb == 0) || sa == 3 || sb == 3) return BS_EINVAL;
                 for (int32_t n = r.begin; n < e; ++n) { got_a[n] = (uint8_t)sa; got_b[n] = (uint8_t)sb; }
                 skips += (int64_t)(e - r.begin) * ((sa == 0) + (sb == 0 && it.head_b >= 0));
                 n_tiles += e - r.begin;
+                prev_begin = r.begin;
                 prev_end = e;
             }
             if (n_tiles != it.n_tiles) return BS_EINVAL;
