@@ -1000,10 +1000,10 @@ TileRuns tiles_read(const bs_tilemap *tm, bool all)
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
 // what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do (units->n
-// stays: the caller says staging_queued).
+// stays: the caller says staging_queued).  On an error nothing is launched behind what failed.
 template <int D>
-void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
-                 float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
+hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
+                       float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
 {
     a.first_tile = todo_tiles.first[0];
     __bf16 *kp = static_cast<__bf16 *>(workspace);
@@ -1012,7 +1012,8 @@ void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, con
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     if (kv_packed && units) {
-        if (bs::copy_pending(units, st) != hipSuccess) return;   // (reported by the caller's look at the last error)
+        const hipError_t e = bs::copy_pending(units, st);
+        if (e != hipSuccess) return e;
     }
     if (!kv_packed) {
         bs::PackTiles todo;
@@ -1039,6 +1040,7 @@ void launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, con
     if (sh && sh->n_cut > 0)
         hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
                            d->rows, cut_results);
+    return hipSuccess;
 }
 
 // How many key tiles of K the attention kernel reads where the caller has them.  Packing one costs a read and a write of the
@@ -1202,8 +1204,13 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
         // (a caller with several bindings of the map packs for all of them)
         const TileRuns todo = tiles_read(tm, kv_packed != nullptr);
-        if (head_dim == 128) launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
-        else launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start)
+                            : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        if (e != hipSuccess) {
+            d->bind_kind = bs::kBindNone;   // the units did not arrive
+            if (kv_packed) *kv_packed = false;
+            return bs::fail_hip(e, "copy of the work units");
+        }
         if (units.n > 0) {
             e = hipPeekAtLastError();
             if (e == hipSuccess) e = bs::staging_queued(units.staging, st);
@@ -1286,10 +1293,11 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     d->k_in_place = in_place;
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
+    e = hipSuccess;
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
-    else launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
-    e = hipGetLastError();
+    else if (head_dim == 128) e = launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    else e = launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);
     if (e != hipSuccess) return bs::fail_hip(e, "hipEventRecord");

@@ -1,0 +1,89 @@
+"""What the library's host side does when a launch fails, with a stand-in for the HIP runtime (host_runtime.cpp) that runs no kernel:
+no GPU is involved."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2507_09071_amd as bs
+from paper_2507_09071_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+#include "blindsight.h"
+#include "host_runtime.h"
+
+static void expect(bool ok, const char *what) { if (!ok) { std::fprintf(stderr, "%s\n", what); std::exit(1); } }
+
+static const bs_span kSpans[3] = {{40, 540, 20}, {552, 852, 20}, {900, 1500, 20}};
+static const uint8_t kClasses[4] = {0, 1, 2, 3};
+alignas(16) static char kData[16];   // no kernel runs, so nothing is read or written
+
+static bs_tilemap *map(uint32_t flags = BS_MAP_PACK_KEYS)
+{
+    bs_tilemap *tm = nullptr;
+    expect(bs_build_tilemap_ex(kSpans, 3, 1600, kClasses, 4, 8, 128, 64, flags, &tm) == BS_OK, "build");
+    return tm;
+}
+
+static int call(bs_tilemap *tm, int dtype = BS_BF16)
+{
+    return bs_attn_prefill(kData, kData, kData, kData, tm, dtype, 4, 2, 128, 0.1f, nullptr);
+}
+
+// The units of a run over tiles that the run before packed come with a kernel of their own: the second copy, behind the prompt's.
+static void copy_of_units()
+{
+    uint8_t types[4] = {9, 9, 9, 9};
+    double nmse[12];
+    host_fail_launch("copy_from_host", 1);
+    const int rc = bs_characterize_prompt(kData, kData, kData, kSpans, 3, 1600, 8, BS_BF16, 4, 2, 128, 0.1f, 0.1, BS_MAP_PACK_KEYS, nullptr, 0,
+                                          0, types, nmse, nullptr);
+    expect(rc == BS_EHIP, "a run whose work units did not arrive is reported");
+    expect(std::strstr(bs_last_error(), "an error") != nullptr, "with the runtime's words");
+    for (uint8_t t : types) expect(t == 9, "no head type");
+    expect(host_launches("attn_prefill_bf16") == 1, "and not launched");
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "copy of the units") copy_of_units();
+    else return 2;
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    d = tmp_path_factory.mktemp("host_side")
+    bs.load_library()
+    lib = bs.library_path()
+    needs = open(lib, "rb").read()
+    soname = re.search(rb"libamdhip64\.so\.\d+", needs).group().decode()
+    versions = sorted({v.decode() for v in re.findall(rb"\0(hip_\d+\.\d+)\0", needs)})
+    (d / "versions").write_text("".join(v + " { global: *; };\n" for v in versions))
+    (d / "driver.cpp").write_text(DRIVER)
+    rocm = os.path.dirname(os.path.dirname(shutil.which(build.hipcc()) or "/opt/rocm/bin/hipcc"))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I", HERE,
+                    os.path.join(HERE, "host_runtime.cpp"), f"-Wl,-soname,{soname}", f"-Wl,--version-script={d / 'versions'}",
+                    "-o", str(d / soname)], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", os.path.join(build.ROOT, "include"), "-I", HERE, str(d / "driver.cpp"), lib,
+                    str(d / soname), f"-Wl,-rpath,{d}", "-Wl,--disable-new-dtags", "-Wl,--allow-shlib-undefined", "-o", str(d / "driver")], check=True)
+    return str(d / "driver")
+
+
+@pytest.mark.parametrize("what", ["copy of the units"])
+def test_host_side(driver, what):
+    done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
+    assert done.returncode == 0, done.stderr
