@@ -999,8 +999,8 @@ TileRuns tiles_read(const bs_tilemap *tm, bool all)
 
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
-// what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do (units->n
-// stays: the caller says staging_queued).  On an error nothing is launched behind what failed.
+// what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do.  A launch that
+// fails is the last one: the kernels behind it would read what it did not write.
 template <int D>
 hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
                        float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
@@ -1011,11 +1011,11 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     const int32_t in_place = d->k_in_place;
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
-    if (kv_packed && units) {
-        const hipError_t e = bs::copy_pending(units, st);
-        if (e != hipSuccess) return e;
-    }
-    if (!kv_packed) {
+    const size_t n_copy = units && !kv_packed ? units->n : 0;   // comes with the pre-pass
+    hipError_t e = hipSuccess;
+    if (kv_packed) {
+        if (units) e = bs::copy_pending(units, st);
+    } else {
         bs::PackTiles todo;
         int32_t n_todo = 0;
         for (int i = 0; i < 6; ++i) {
@@ -1025,22 +1025,27 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
             n_todo += todo.count[i];
         }
         // the copy of the units: one load a thread, as the latency of the bus is all there is to it, up to 4 MB
-        const size_t n_copy = units ? units->n : 0;
         const size_t copy_wgs = std::min<size_t>((n_copy + 255) / 256, 1024);
         const size_t copy_x = (copy_wgs + n_kv_heads - 1) / n_kv_heads;
         todo.n_tiles = n_todo;
-        hipLaunchKernelGGL(bs::pack_kv_tiles<D>, dim3((unsigned)(n_todo + copy_x), (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                           static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr,
-                           n_copy ? units->src : nullptr, n_copy ? units->dst : nullptr, n_copy);
+        e = bs::launch_kernel(bs::pack_kv_tiles<D>, dim3((unsigned)(n_todo + copy_x), (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
+                              static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr,
+                              n_copy ? units->src : nullptr, n_copy ? units->dst : nullptr, n_copy);
+        if (e != hipSuccess && n_copy) bs::staging_abandon(units->staging);
     }
+    if (e != hipSuccess) return e;
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
-    hipLaunchKernelGGL(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                       d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
-                       d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
-    if (sh && sh->n_cut > 0)
-        hipLaunchKernelGGL((bs::merge_cut_items<D, 2, __bf16>), dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
-                           d->rows, cut_results);
-    return hipSuccess;
+    e = bs::launch_kernel(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
+                          d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
+                          d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
+    if (e == hipSuccess && sh && sh->n_cut > 0)
+        e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
+                              d->rows, cut_results);
+    if (n_copy) {   // (an event between the two kernels would hold the second one up)
+        const hipError_t queued = bs::staging_queued(units->staging, st);
+        if (e == hipSuccess) e = queued;
+    }
+    return e;
 }
 
 // How many key tiles of K the attention kernel reads where the caller has them.  Packing one costs a read and a write of the
@@ -1207,15 +1212,10 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start)
                             : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
         if (e != hipSuccess) {
-            d->bind_kind = bs::kBindNone;   // the units did not arrive
+            d->bind_kind = bs::kBindNone;   // the units may not have arrived
             if (kv_packed) *kv_packed = false;
-            return bs::fail_hip(e, "copy of the work units");
-        }
-        if (units.n > 0) {
-            e = hipPeekAtLastError();
-            if (e == hipSuccess) e = bs::staging_queued(units.staging, st);
-            else bs::staging_abandon(units.staging);
-            if (e != hipSuccess) d->bind_kind = bs::kBindNone;
+            (void)hipEventRecord(d->last_use->ev, st);   // what was launched uses the map's blocks
+            return bs::fail_hip(e, "kernel launch");
         }
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);

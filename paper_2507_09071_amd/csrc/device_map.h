@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include <memory>
+#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -23,6 +24,19 @@ extern thread_local char g_last_error[256];
 int fail_hip(hipError_t e, const char *what);
 // Records a plain message for bs_last_error() and returns `code`.
 int fail_msg(int code, const char *what);
+
+// Queues a kernel and returns the status of that launch alone.
+template <typename... P, typename... A>
+hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t st, const A &...args)
+{
+    std::tuple<P...> values(args...);
+    const hipError_t e = std::apply([&](auto &...v) {
+        void *pointers[] = {const_cast<void *>(static_cast<const void *>(&v))...};
+        return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, pointers, lds_bytes, st);
+    }, values);
+    if (e != hipSuccess) (void)hipGetLastError();   // reported here
+    return e;
+}
 
 // An event that dies with its last owner (a map, or cached blocks that wait to be reused).
 struct EventHolder {

@@ -1,5 +1,5 @@
 // A stand-in for the HIP runtime in tests of the library's host side without a GPU: memory is host memory, kernels are counted by
-// name and not run (copy_from_host excepted, which is a memcpy), and a test says which launch fails.  Built as a shared object
+// name and not run (but for the copies out of pinned buffers, which are a memcpy), and a test says which launch fails.  Built as a shared object
 // with the runtime's soname, so that the library under test loads it instead.
 #include <hip/hip_runtime_api.h>
 
@@ -21,7 +21,7 @@ std::map<const void *, std::string> names;   // kernels by the address of their 
 std::vector<std::string> launched;           // in order; failed ones are not among them
 std::string fail_name;
 int fail_after = -1;
-int64_t malloc_bytes = 0;
+int64_t malloc_bytes = 0, copied_bytes = 0;
 std::atomic<int> malloc_ms{0};
 int event_records = 0;
 thread_local hipError_t last_error = hipSuccess;
@@ -36,6 +36,7 @@ void host_fail_launch(const char *kernel, int after) { std::lock_guard<std::mute
 void host_set_last_error(int e) { last_error = (hipError_t)e; }
 void host_malloc_takes(int ms) { malloc_ms = ms; }
 int64_t host_malloc_bytes() { std::lock_guard<std::mutex> l(mutex); return malloc_bytes; }
+int64_t host_copied_bytes() { std::lock_guard<std::mutex> l(mutex); return copied_bytes; }
 int host_event_records() { std::lock_guard<std::mutex> l(mutex); return event_records; }
 int host_launches(const char *kernel)
 {
@@ -66,7 +67,13 @@ hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipSt
     const std::string &name = names[f];
     if (!fail_name.empty() && name.find(fail_name) != std::string::npos && fail_after-- == 0) return last_error = hipErrorLaunchFailure;
     launched.push_back(name);
-    if (name.find("copy_from_host") != std::string::npos) std::memcpy(*(void **)args[1], *(void **)args[0], *(size_t *)args[2] * 16);
+    auto copy = [&](int first) {   // the arguments src, dst, pieces of 16 bytes
+        const size_t bytes = *(size_t *)args[first + 2] * 16;
+        if (bytes) std::memcpy(*(void **)args[first + 1], *(void **)args[first], bytes);
+        copied_bytes += (int64_t)bytes;
+    };
+    if (name.find("copy_from_host") != std::string::npos) copy(0);
+    if (name.find("pack_kv_tiles") != std::string::npos) copy(11);
     return hipSuccess;
 }
 hipError_t hipMalloc(void **out, size_t bytes)

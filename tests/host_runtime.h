@@ -8,5 +8,6 @@ void host_set_last_error(int e);                        // the calling thread's 
 void host_malloc_takes(int ms);                         // each hipMalloc, from now on
 int64_t host_malloc_bytes();                            // by hipMalloc so far
 int host_event_records();                               // hipEventRecord calls so far
+int64_t host_copied_bytes();                            // brought from pinned buffers so far, by whichever kernel
 int host_launches(const char *kernel);                  // launches so far whose name holds `kernel`
 }

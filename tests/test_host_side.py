@@ -52,10 +52,30 @@ static void copy_of_units()
     expect(host_launches("attn_prefill_bf16") == 1, "and not launched");
 }
 
+// The pre-pass brings the tiles and the work units that the attention kernel reads.
+static void pre_pass()
+{
+    bs_tilemap *tm = map();
+    host_fail_launch("pack_kv_tiles", 0);
+    expect(call(tm) == BS_EHIP, "a call without its pre-pass is reported");
+    expect(host_launches("attn_prefill_bf16") == 0 && host_launches("merge_cut_items") == 0, "nothing is launched behind it");
+    const int64_t copied = host_copied_bytes();
+    expect(call(tm) == BS_OK && host_launches("attn_prefill_bf16") == 1, "the next call runs");
+    expect(host_copied_bytes() > copied, "and brings the units again");
+    expect(call(tm) == BS_OK, "once more");
+    const int64_t bound = host_copied_bytes();
+    expect(bs_tilemap_prepare(tm, BS_BF16, 2, nullptr) == BS_OK && host_copied_bytes() == bound, "which are then bound");
+    host_fail_launch("pack_kv_tiles", 0);
+    expect(bs_attn_prefill_static(kData, kData, kData, kData, tm, 4, 2, 128, 0.1f, nullptr) == BS_EHIP, "the static entry as well");
+    expect(host_launches("attn_prefill_bf16") == 2, "nothing is launched behind it");
+    bs_tilemap_destroy(tm);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "copy of the units") copy_of_units();
+    else if (what == "pre-pass") pre_pass();
     else return 2;
     return 0;
 }
@@ -83,7 +103,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
