@@ -25,7 +25,7 @@ int fail_hip(hipError_t e, const char *what);
 // Records a plain message for bs_last_error() and returns `code`.
 int fail_msg(int code, const char *what);
 
-// Queues a kernel and returns the status of that launch alone.
+// Queues a kernel and returns the status of that launch alone; hipGetLastError may tell of a call before, of anybody's on the thread.
 template <typename... P, typename... A>
 hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds_bytes, hipStream_t st, const A &...args)
 {

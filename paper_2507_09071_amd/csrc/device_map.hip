@@ -179,10 +179,9 @@ hipError_t staging_queued(const Staging &s, hipStream_t st)
 hipError_t copy_pending(PendingCopy *copy, hipStream_t st)
 {
     if (copy->n == 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_from_host, dim3((unsigned)std::min<size_t>((copy->n + 255) / 256, 1024)), dim3(256), 0, st,
-                       copy->src, copy->dst, copy->n);
+    const hipError_t e = launch_kernel(copy_from_host, dim3((unsigned)std::min<size_t>((copy->n + 255) / 256, 1024)), dim3(256), 0, st,
+                                       copy->src, copy->dst, copy->n);
     copy->n = 0;
-    const hipError_t e = hipGetLastError();
     if (e == hipSuccess) return staging_queued(copy->staging, st);
     staging_abandon(copy->staging);
     return e;
@@ -456,8 +455,7 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units)
             a.copy_src = units->src; a.copy_dst = units->dst; a.n_copy = units->n;
             copy_wgs = (int32_t)std::min<size_t>((units->n + 255) / 256, 1024);
         }
-        hipLaunchKernelGGL(expand_map, dim3((unsigned)(a.n_workgroups + copy_wgs)), dim3(256), 0, st, a);
-        e = hipGetLastError();
+        e = launch_kernel(expand_map, dim3((unsigned)(a.n_workgroups + copy_wgs)), dim3(256), 0, st, a);
         if (e == hipSuccess && copy_wgs > 0) {
             units->n = 0;
             e = staging_queued(units->staging, st);

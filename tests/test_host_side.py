@@ -71,11 +71,27 @@ static void pre_pass()
     bs_tilemap_destroy(tm);
 }
 
+// An error that somebody else's call left behind says nothing about a launch: a pinned buffer is not handed on while a kernel reads it.
+static void last_error()
+{
+    bs_tilemap *tm = map(0);
+    expect(call(tm, BS_F32) == BS_OK, "call");
+    const uint8_t other[4] = {3, 2, 1, 0};
+    expect(bs_tilemap_rebind(tm, other, 4) == BS_OK, "rebind");
+    const int copies = host_launches("copy_from_host"), events = host_event_records();
+    host_set_last_error(1);
+    (void)call(tm, BS_F32);
+    expect(host_launches("copy_from_host") == copies + 1, "the units are copied");
+    expect(host_event_records() > events, "and an event behind the copy says when their buffer is free");
+    bs_tilemap_destroy(tm);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "copy of the units") copy_of_units();
     else if (what == "pre-pass") pre_pass();
+    else if (what == "last error") last_error();
     else return 2;
     return 0;
 }
@@ -103,7 +119,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units", "pre-pass"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
