@@ -1182,12 +1182,13 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         return code;
     };
     const int32_t n_wgs = dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim);
-    if (dtype == BS_F32)
-        if ((rc = bs::upload_binding(tm, bs::kBindSolo, gqa_group, n_wgs, 0, st, &units)) != BS_OK) return rc;
-    if (!rows.use || rows.need_bits)
-        if ((rc = bs::upload_prompt_part(tm, st, &units)) != BS_OK) return give_up(rc);
-    if (dtype == BS_BF16 && !rows.use)
-        if ((rc = bs::upload_binding(tm, bs::kBindPairPlan, gqa_group, n_wgs, 0, st, &units)) != BS_OK) return rc;
+    const auto bind = [&] { return bs::upload_binding(tm, dtype == BS_BF16 ? bs::kBindPairPlan : bs::kBindSolo, gqa_group, n_wgs, 0, st, &units); };
+    if (!rows.use || rows.need_bits) {
+        rc = dtype == BS_F32 ? bs::upload_prompt_part(tm, st, &units, bind) : bs::upload_prompt_part(tm, st);
+        if (rc != BS_OK) return give_up(rc);
+    }
+    if (!rows.use)
+        if ((rc = bind()) != BS_OK) return rc;
 
     const bs::KernelArgs a = kernel_args(q, k, v, out, tm, gqa_group, scale);
     if (rows.use) {

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <functional>
 #include <memory>
 #include <tuple>
 #include <utility>
@@ -140,8 +141,9 @@ hipError_t copy_pending(PendingCopy *copy, hipStream_t st);    // a kernel of it
 // The map's device side without any upload: the device it lives on, its last-use event (once per map).
 int ensure_device_map(bs_tilemap *tm, hipStream_t st);
 // Make the prompt part (once per map) / upload the binding part (when stale) on `st`; no host-side wait.
-// `units` (may be null): a copy that goes with it, if the prompt part is made now.
-int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units = nullptr);
+// `stage` (may be empty), if the prompt part is made now: leaves a copy in *units that goes with the kernel that makes it.  Called
+// when the span table's pinned buffer has been handed on: a thread holds one at a time, or eight threads could wait for each other.
+int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units = nullptr, const std::function<int()> &stage = nullptr);
 // The shares are cut for n_wgs workgroups, and for n_wgs_too if that is not 0.
 // `later` (may be null): leaves the copy to the caller.
 int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wgs, int32_t n_wgs_too, hipStream_t st, PendingCopy *later);

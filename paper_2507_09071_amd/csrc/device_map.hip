@@ -392,7 +392,7 @@ int ensure_device_map(bs_tilemap *tm, hipStream_t st)
     return BS_OK;
 }
 
-int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units)
+int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units, const std::function<int()> &stage)
 {
     if (!tm) return BS_EINVAL;
     if (tm->dev && tm->dev->blob) return BS_OK;
@@ -432,6 +432,10 @@ int upload_prompt_part(bs_tilemap *tm, hipStream_t st, PendingCopy *units)
         return fail_hip(e, "hipMalloc(tile map)");
     }
     e = staging_commit(sg, blob, up_bytes, st);
+    if (e == hipSuccess && stage && (rc = stage()) != BS_OK) {
+        (void)hipFree(blob);
+        return rc;
+    }
     unsigned char *b = static_cast<unsigned char *>(blob);
     if (e == hipSuccess && device_tiles) {
         ExpandArgs a{};

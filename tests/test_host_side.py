@@ -1,4 +1,4 @@
-"""What the library's host side does when a launch fails, with a stand-in for the HIP runtime (host_runtime.cpp) that runs no kernel:
+"""What the library's host side does when a launch fails and when several threads call it, with a stand-in for the HIP runtime (host_runtime.cpp) that runs no kernel:
 no GPU is involved."""
 import os
 import re
@@ -12,10 +12,12 @@ from paper_2507_09071_amd import build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 DRIVER = r"""
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 #include "blindsight.h"
 #include "host_runtime.h"
@@ -86,12 +88,34 @@ static void last_error()
     bs_tilemap_destroy(tm);
 }
 
+// First calls of as many threads as there are pinned buffers, each with a map of its own: all are inside an upload at once.
+static void threads(int n, int dtype)
+{
+    host_malloc_takes(20);
+    std::vector<int> rc(n, 1);
+    std::vector<std::thread> ts;
+    std::atomic<int> ready{0};
+    for (int i = 0; i < n; ++i)
+        ts.emplace_back([&, i] {
+            bs_tilemap *tm = map();
+            ++ready;
+            while (ready < n) std::this_thread::yield();
+            rc[i] = call(tm, dtype);
+            if (rc[i] != BS_OK) std::fprintf(stderr, "%d: %s\n", rc[i], bs_last_error());
+            bs_tilemap_destroy(tm);
+        });
+    for (std::thread &t : ts) t.join();
+    for (int r : rc) expect(r == BS_OK, "a thread's call");
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "copy of the units") copy_of_units();
     else if (what == "pre-pass") pre_pass();
     else if (what == "last error") last_error();
+    else if (what == "eight threads, fp32") threads(8, BS_F32);
+    else if (what == "eight threads, bf16") threads(8, BS_BF16);
     else return 2;
     return 0;
 }
@@ -119,7 +143,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
