@@ -11,6 +11,7 @@
 #include "device_map.h"
 
 #include <algorithm>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -61,6 +62,7 @@ std::mutex g_mem_mutex;
 std::vector<CachedBlock> &g_cache = *new std::vector<CachedBlock>();
 StagingBuffer g_staging[kStagingBuffers];
 int g_staging_next = 0;
+std::condition_variable g_staging_freed;   // a buffer is not in use any more
 std::vector<void *> &g_outgrown = *new std::vector<void *>();   // pinned buffers replaced by larger ones
 
 constexpr size_t kGranule = (size_t)1 << 20;
@@ -113,12 +115,16 @@ hipError_t staging_begin(size_t bytes, Staging *out)
     int slot = -1;
     hipEvent_t wait_for = nullptr;
     {
-        std::lock_guard<std::mutex> lock(g_mem_mutex);
-        for (int i = 0; i < kStagingBuffers && !sb; ++i) {
-            const int c = (g_staging_next + i) % kStagingBuffers;
-            if (!g_staging[c].in_use) { sb = &g_staging[c]; slot = c; }
-        }
-        if (!sb) return hipErrorNotReady;   // more than kStagingBuffers host threads inside an upload
+        // With more than kStagingBuffers host threads inside an upload the next one waits for its turn.  A thread holds one
+        // buffer at a time, until the kernel that reads it is queued, so a buffer comes free.
+        std::unique_lock<std::mutex> lock(g_mem_mutex);
+        g_staging_freed.wait(lock, [&] {
+            for (int i = 0; i < kStagingBuffers && !sb; ++i) {
+                const int c = (g_staging_next + i) % kStagingBuffers;
+                if (!g_staging[c].in_use) { sb = &g_staging[c]; slot = c; }
+            }
+            return sb != nullptr;
+        });
         g_staging_next = (slot + 1) % kStagingBuffers;
         sb->in_use = true;
         if (sb->queued) wait_for = sb->done;
@@ -148,8 +154,7 @@ hipError_t staging_begin(size_t bytes, Staging *out)
         if (e != hipSuccess) sb->done = nullptr;
     }
     if (e != hipSuccess) {
-        std::lock_guard<std::mutex> lock(g_mem_mutex);
-        sb->in_use = false;
+        staging_abandon({nullptr, slot});
         return e;
     }
     out->host = sb->host;
@@ -173,6 +178,7 @@ hipError_t staging_queued(const Staging &s, hipStream_t st)
     std::lock_guard<std::mutex> lock(g_mem_mutex);
     sb.queued = (e == hipSuccess);
     sb.in_use = false;
+    g_staging_freed.notify_one();
     return e;
 }
 
@@ -200,6 +206,7 @@ void staging_abandon(const Staging &s)
     if (s.slot < 0) return;
     std::lock_guard<std::mutex> lock(g_mem_mutex);
     g_staging[s.slot].in_use = false;
+    g_staging_freed.notify_one();
 }
 
 void free_device_map(DeviceMap *d)

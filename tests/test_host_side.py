@@ -88,7 +88,7 @@ static void last_error()
     bs_tilemap_destroy(tm);
 }
 
-// First calls of as many threads as there are pinned buffers, each with a map of its own: all are inside an upload at once.
+// First calls of as many threads as there are pinned buffers, or more, each with a map of its own: all are inside an upload at once.
 static void threads(int n, int dtype)
 {
     host_malloc_takes(20);
@@ -116,6 +116,7 @@ int main(int argc, char **argv)
     else if (what == "last error") last_error();
     else if (what == "eight threads, fp32") threads(8, BS_F32);
     else if (what == "eight threads, bf16") threads(8, BS_BF16);
+    else if (what == "twelve threads, bf16") threads(12, BS_BF16);
     else return 2;
     return 0;
 }
@@ -143,7 +144,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16", "twelve threads, bf16"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
