@@ -1178,7 +1178,9 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
     // bf16 is launched before the units are planned: the two then run side by side).
     bs::PendingCopy units;
     const auto give_up = [&](int code) {
+        if (units.n == 0) return code;
         if (bs::copy_pending(&units, st) != hipSuccess) d->bind_kind = bs::kBindNone;
+        (void)hipEventRecord(d->last_use->ev, st);   // the copy uses the map's block
         return code;
     };
     const int32_t n_wgs = dtype == BS_BF16 ? n_cus : n_cus * bs::f32_wgs_per_cu(head_dim);

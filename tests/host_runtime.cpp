@@ -20,7 +20,7 @@ std::mutex mutex;
 std::map<const void *, std::string> names;   // kernels by the address of their host stub
 std::vector<std::string> launched;           // in order; failed ones are not among them
 std::string fail_name;
-int fail_after = -1;
+int fail_after = -1, fail_malloc_after = -1;
 int64_t malloc_bytes = 0, copied_bytes = 0;
 std::atomic<int> malloc_ms{0};
 int event_records = 0;
@@ -33,6 +33,7 @@ extern "C" {
 
 // ---- what tests use
 void host_fail_launch(const char *kernel, int after) { std::lock_guard<std::mutex> l(mutex); fail_name = kernel; fail_after = after; }
+void host_fail_malloc(int after) { std::lock_guard<std::mutex> l(mutex); fail_malloc_after = after; }
 void host_set_last_error(int e) { last_error = (hipError_t)e; }
 void host_malloc_takes(int ms) { malloc_ms = ms; }
 int64_t host_malloc_bytes() { std::lock_guard<std::mutex> l(mutex); return malloc_bytes; }
@@ -80,6 +81,7 @@ hipError_t hipMalloc(void **out, size_t bytes)
 {
     std::this_thread::sleep_for(std::chrono::milliseconds(malloc_ms));
     std::lock_guard<std::mutex> l(mutex);
+    if (fail_malloc_after-- == 0) return last_error = hipErrorOutOfMemory;
     malloc_bytes += (int64_t)bytes;
     return (*out = std::malloc(bytes)) ? hipSuccess : (last_error = hipErrorOutOfMemory);
 }

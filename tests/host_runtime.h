@@ -4,6 +4,7 @@
 
 extern "C" {
 void host_fail_launch(const char *kernel, int after);   // of the launches whose name holds `kernel`, the one after `after` others fails
+void host_fail_malloc(int after);                       // the hipMalloc after `after` others
 void host_set_last_error(int e);                        // the calling thread's last error, as a failed call before left it
 void host_malloc_takes(int ms);                         // each hipMalloc, from now on
 int64_t host_malloc_bytes();                            // by hipMalloc so far

@@ -108,6 +108,20 @@ static void threads(int n, int dtype)
     for (int r : rc) expect(r == BS_OK, "a thread's call");
 }
 
+// A call that gets no workspace has its units copied all the same: the map's last use is behind that copy.
+static void no_workspace()
+{
+    bs_tilemap *tm = map();
+    host_fail_malloc(2);   // its prompt part and work units, then the workspace
+    const int events = host_event_records();
+    expect(call(tm) == BS_ENOMEM, "no workspace");
+    expect(host_launches("attn_prefill_bf16") == 0, "nothing launched");
+    // the span table's buffer, the prompt part, the units' buffer, the units
+    expect(host_event_records() == events + 4, "events behind both uploads");
+    expect(call(tm) == BS_OK && host_launches("attn_prefill_bf16") == 1, "the next call runs");
+    bs_tilemap_destroy(tm);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -117,6 +131,7 @@ int main(int argc, char **argv)
     else if (what == "eight threads, fp32") threads(8, BS_F32);
     else if (what == "eight threads, bf16") threads(8, BS_BF16);
     else if (what == "twelve threads, bf16") threads(12, BS_BF16);
+    else if (what == "no workspace") no_workspace();
     else return 2;
     return 0;
 }
@@ -144,7 +159,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16", "twelve threads, bf16"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16", "twelve threads, bf16", "no workspace"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
