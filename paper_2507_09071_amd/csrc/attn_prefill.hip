@@ -1137,8 +1137,8 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
         if (rc == BS_OK)
             rc = take_workspace(d, std::max(bs::f32_workspace(*d->shares_for(wgs128), 128), bs::f32_workspace(*d->shares_for(wgs64), 64)), st);
     }
+    e = hipEventRecord(d->last_use->ev, st);   // (also without a workspace: the units are on their way)
     if (rc != BS_OK) return rc;
-    e = hipEventRecord(d->last_use->ev, st);
     return e == hipSuccess ? BS_OK : bs::fail_hip(e, "hipEventRecord");
 }
 
@@ -1222,11 +1222,11 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         }
     } else {
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
+        if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return give_up(rc);
         if ((e = bs::copy_pending(&units, st)) != hipSuccess) {
             d->bind_kind = bs::kBindNone;
             return bs::fail_hip(e, "copy of the work units");
         }
-        if ((rc = take_workspace(d, bs::f32_workspace(shares, head_dim), st)) != BS_OK) return rc;
         if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
         bs::launch_f32(a, d, shares, d->vt_buf, head_dim, st);
     }

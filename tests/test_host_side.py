@@ -122,6 +122,28 @@ static void no_workspace()
     bs_tilemap_destroy(tm);
 }
 
+// The same in fp32, for a map whose prompt part is made, and in a preparation.
+static void no_workspace_f32()
+{
+    bs_tilemap *tm = map(0);
+    host_fail_malloc(2);
+    expect(call(tm, BS_F32) == BS_ENOMEM, "no workspace");
+    const uint8_t other[4] = {3, 2, 1, 0};
+    expect(bs_tilemap_rebind(tm, other, 4) == BS_OK, "rebind");
+    host_fail_malloc(1);
+    int events = host_event_records();
+    expect(call(tm, BS_F32) == BS_ENOMEM, "no workspace after a rebind");
+    expect(host_event_records() == events + 2, "events behind the units");   // their buffer's, the map's
+    expect(call(tm, BS_F32) == BS_OK, "the next call runs");
+    bs_tilemap *tm2 = map(0);
+    host_fail_malloc(1);   // (the block of the units before the rebind is free)
+    events = host_event_records();
+    expect(bs_tilemap_prepare(tm2, BS_F32, 2, nullptr) == BS_ENOMEM, "no workspace to prepare");
+    expect(host_event_records() == events + 4, "events behind both uploads of a preparation");
+    bs_tilemap_destroy(tm2);
+    bs_tilemap_destroy(tm);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -132,6 +154,7 @@ int main(int argc, char **argv)
     else if (what == "eight threads, bf16") threads(8, BS_BF16);
     else if (what == "twelve threads, bf16") threads(12, BS_BF16);
     else if (what == "no workspace") no_workspace();
+    else if (what == "no workspace, fp32") no_workspace_f32();
     else return 2;
     return 0;
 }
@@ -159,7 +182,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16", "twelve threads, bf16", "no workspace"])
+@pytest.mark.parametrize("what", ["copy of the units", "pre-pass", "last error", "eight threads, fp32", "eight threads, bf16", "twelve threads, bf16", "no workspace", "no workspace, fp32"])
 def test_host_side(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert done.returncode == 0, done.stderr
