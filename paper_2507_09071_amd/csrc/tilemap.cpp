@@ -1341,16 +1341,19 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             if (it.head_b >= 0) ++seen[(size_t)it.head_b * tm->M + it.tile_b];
             std::fill(got_a.begin(), got_a.end(), 0);
             std::fill(got_b.begin(), got_b.end(), 0);
-            int32_t prev_begin = 0, prev_end = 0, n_tiles = 0;
+            bool in_prompt = false;   // the compact tiles come first, then the prompt's, both in order
+            int32_t prev_end = 0, n_tiles = 0;
             for (int32_t p = it.list_begin; p < it.list_end; ++p) {
                 const bs::PairRange &r = plan.ranges[p];
                 const int32_t e = r.end_states >> 4, sa = (r.end_states >> 2) & 3, sb = r.end_states & 3;
-                if (r.begin < tm->N0 && prev_begin >= tm->N0) prev_end = 0;   // (compact tiles come first)
-                if (r.begin < prev_end || e <= r.begin || e > tm->n_tiles || (sa == 0 && sb == 0) || sa == 3 || sb == 3) return BS_EINVAL;
+                if (r.begin < tm->N0 && !in_prompt) {
+                    in_prompt = true;
+                    prev_end = 0;
+                }
+                if (r.begin < prev_end || e <= r.begin || e > (in_prompt ? tm->N0 : tm->n_tiles) || (sa == 0 && sb == 0) || sa == 3 || sb == 3) return BS_EINVAL;
                 for (int32_t n = r.begin; n < e; ++n) { got_a[n] = (uint8_t)sa; got_b[n] = (uint8_t)sb; }
                 skips += (int64_t)(e - r.begin) * ((sa == 0) + (sb == 0 && it.head_b >= 0));
                 n_tiles += e - r.begin;
-                prev_begin = r.begin;
                 prev_end = e;
             }
             if (n_tiles != it.n_tiles) return BS_EINVAL;
