@@ -111,14 +111,18 @@ def lds_read_hazards(ins: list) -> list:
 def operand_hazards(ins: list) -> list:
     """List of (vector instruction, mfma): an operand of an MFMA written by a vector instruction less than
     OPERAND_WAIT_STATES wait states before it.  The hardware does not interlock that and the compiler, which sees no
-    matrix instruction, does not keep the distance."""
+    matrix instruction, does not keep the distance.  A conditional branch is a wait state like any instruction: the code
+    behind it follows if it is not taken."""
     found = []
     for a, t in enumerate(ins):
         if not t.startswith("v_") or t.startswith(("v_mfma", "v_cmp", "v_readlane", "v_readfirstlane")):
             continue
-        dst, ws = _regs(t.split(",")[0]), 0
+        operands = t.split(",")
+        dst, ws = _regs(operands[0]), 0
+        if "swap" in t.split()[0]:
+            dst |= _regs(operands[1])   # writes both
         for u in ins[a + 1:a + 1 + 2 * OPERAND_WAIT_STATES]:
-            if u.startswith(("s_cbranch", "s_branch", "s_endpgm")) or ws >= OPERAND_WAIT_STATES:
+            if u.startswith(("s_branch", "s_endpgm")) or ws >= OPERAND_WAIT_STATES:
                 break
             if u.startswith("v_mfma"):
                 if _regs(u.split(",", 1)[1]) & dst:

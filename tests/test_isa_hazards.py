@@ -45,6 +45,15 @@ def test_checker_flags_an_operand_written_right_before_an_mfma():
     assert len(isa_check.operand_hazards([write, "s_waitcnt lgkmcnt(0)", mfma])) == 1
     assert isa_check.operand_hazards([write, "s_nop 1", mfma]) == []
     assert isa_check.operand_hazards(["v_mov_b32_e32 v40, v20", mfma]) == []
+    # a branch that is not taken is one wait state, and the code behind it follows
+    guard = "s_cbranch_scc1 .LBB0_7"
+    assert len(isa_check.operand_hazards([write, guard, mfma])) == 1
+    assert isa_check.operand_hazards([write, guard, "s_nop 0", mfma]) == []
+    assert isa_check.operand_hazards([write, "s_branch .LBB0_7", mfma]) == []   # (code that does not follow)
+    # a swap writes both its operands
+    assert len(isa_check.operand_hazards(["v_permlane32_swap_b32_e32 v40, v21", mfma])) == 1
+    assert len(isa_check.operand_hazards(["v_swap_b32 v20, v40", mfma])) == 1
+    assert isa_check.operand_hazards(["v_swap_b32 v41, v40", mfma]) == []
 
 
 @pytest.mark.skipif(shutil.which(bs_build.hipcc()) is None, reason="hipcc not available")
