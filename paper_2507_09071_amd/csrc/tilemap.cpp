@@ -719,7 +719,15 @@ extern "C" int bs_build_tilemap_suffix(const bs_span *spans, int32_t n_spans, in
         if (tm->N0 < tm->n_tiles && n_text_tiles > 0 && 2 * (n_text_tiles + tm->n_tiles - tm->N) + 1 <= tm->N0)
             tm->n_tiles += (int32_t)n_text_tiles;
         Geometry G(std::move(P));   // (one for all lists: they share its tables; the prompt's geometry goes back to the map below)
-        if (tm->N < tm->n_tiles) build_run_lists(tm, G);
+        if (tm->N < tm->n_tiles) {
+            build_run_lists(tm, G);
+            // tiles that none of them walks are not there: every one that is has its room in the workspace of a call
+            bool walked[3] = {false, false, false};
+            for (const ClassLists &cl : tm->run)
+                for (int kind = 1; kind < 3; ++kind) walked[kind] |= cl.span[kind].end > 0;
+            if (!walked[2]) tm->n_tiles = tm->text_tile0;
+            if (!walked[1] && !walked[2]) tm->n_tiles = tm->text_tile0 = tm->N;
+        }
         G.text_tile0 = 0;
         for (int c = 0; c < 4; ++c)
             if (tm->run[c].row_ptr.empty()) build_published(tm, G, c);

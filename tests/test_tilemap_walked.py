@@ -107,3 +107,27 @@ def test_units_of_two_heads_take_the_shorter_rule_block_by_block():
     cross = [sum(int((visited[0][m] | visited[1][m]).sum()) for m in b) for b in blocks]
     steps = tm.pair_plan(2)["unit_tiles"]
     assert sum(np.minimum(rows, cross)) <= steps < 0.95 * min(sum(rows), sum(cross))
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_tiles_that_no_list_walks_are_not_there(seed):
+    """The workspace of a call has room for every tile that the kernels know."""
+    rng = np.random.default_rng([5, seed])
+    spans, pos, L = [], 9, 9000
+    while pos + 1500 < L:
+        n = int(rng.integers(64, [200, 600, 1500][seed % 3]))
+        spans.append((pos, pos + n, max(1, n // 10)))
+        pos += n + int(rng.integers(4, 64))
+    for window in (0, 256, 1024):
+        for bidir in (False, True):
+            tm = bs.bs_build_tilemap(spans, L, np.arange(4), 5, window=window, q_begin=int(rng.choice([0, L - 300])),
+                                     flags=bs.BS_MAP_PACK_KEYS | (bs.BS_MAP_BIDIR_IMAGES if bidir else 0))
+            states = {c: np.array([tm.walked(c, m)[0] for m in range(tm.n_q_tiles)]) for c in (bs.SINK, bs.INTRA, bs.INTRA_SINK)}
+            known, n_text = states[bs.SINK].shape[1], -(-(L - sum(e - s for s, e, _ in spans)) // 64)
+            more = {c: bool((states[c][:, tm.n_k_tiles:] > 0).any()) for c in states}
+            assert (known > tm.n_k_tiles) == any(more.values())
+            if window and known > tm.n_k_tiles and not more[bs.INTRA]:   # free keys alone
+                n_free = L - sum(e - s - k for s, e, k in spans)
+                assert known == tm.n_k_tiles + -(-n_free // 64)
+            elif not window and known > tm.n_k_tiles:
+                assert known == tm.n_k_tiles + n_text
