@@ -437,13 +437,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
                      : "v"(dma_lane_off), "s"(src), "s"(dst)
                      : "memory", "m0");
     };
-    auto tile_ptr = [&](const char *base, int n) {
-        return base + (size_t)min(n, n_k_tiles - 1) * TILE;  // a walker past its end names no tile
-    };
-    auto k_ptr = [&](int n) {
-        n = min(n, n_k_tiles - 1);
-        return (n < in_place ? kph : kpackh) + (size_t)n * TILE;
-    };
+    // (a walker always names a tile that this launch's pre-pass wrote, behind its list the last one)
+    auto tile_ptr = [&](const char *base, int n) { return base + (size_t)n * TILE; };
+    auto k_ptr = [&](int n) { return (n < in_place ? kph : kpackh) + (size_t)n * TILE; };
     // The same for a K tile.  If some are read in place their rows lie one behind the other: a lane picks the 16 bytes
     // that belong at its place, 32 bytes of 32 rows per instruction (the other waves read the rest of the 128-byte
     // lines at the same time), and the next instruction's slices are 128 bytes further.
@@ -505,7 +501,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     auto advance_tile = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
         w0.next();
-        const int nn = min(__builtin_amdgcn_readfirstlane(w0.n), n_k_tiles - 1);
+        const int nn = __builtin_amdgcn_readfirstlane(w0.n);
         tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
         sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
         __builtin_amdgcn_sched_barrier(0);
@@ -758,11 +754,11 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         load_unit(unit);
         reset_unit_state();
         {
-            const int nn = min(__builtin_amdgcn_readfirstlane(w0.n), n_k_tiles - 1);
+            const int nn = __builtin_amdgcn_readfirstlane(w0.n);
             tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
             sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
         }
-        // prologue: K(0) -> K slot 0, K(1) -> K slot 1, V^T(0) -> V^T slot 0 (unconditional, clamped)
+        // prologue: K(0) -> K slot 0, K(1) -> K slot 1, V^T(0) -> V^T slot 0 (unconditional)
         {
             const char *k0 = k_ptr(w0.n), *k1 = k_ptr(wt1.n), *v0 = tile_ptr(vth, w0.n);
 #pragma unroll
