@@ -104,9 +104,9 @@ MEASURED_TRAFFIC = {
 
 
 def class_totals(tm, head_class):
-    """Sum the per-class tile-map statistics over the heads."""
+    """Sum over the heads: key tiles as the kernels walk them (which may be fewer than the map publishes) and allowed pairs."""
     tot = {"visited": 0, "full": 0, "partial": 0, "allowed_pairs": 0}
-    per_class = [tm.stats(c) for c in range(4)]
+    per_class = [{**tm.walked_stats(c), "allowed_pairs": tm.stats(c)["allowed_pairs"]} if c in head_class else None for c in range(4)]
     for c in head_class:
         for k in tot:
             tot[k] += per_class[int(c)][k]

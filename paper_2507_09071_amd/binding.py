@@ -175,6 +175,22 @@ class TileMap:
                                      keys.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), None), "bs_tilemap_walked")
         return states, keys, bool(compact.value)
 
+    def walked_stats(self, cls: int) -> dict:
+        """Key tiles that the kernels walk for a head of the class, summed over the query tiles."""
+        lib, n = load_library(), ctypes.c_int32()
+        full = partial = 0
+        states = None
+        for m in range(self.n_q_tiles):
+            if states is None:
+                _check(lib.bs_tilemap_walked(self._h, cls, m, ctypes.byref(n), None, None, None), "bs_tilemap_walked")
+                states = np.empty(n.value, dtype=np.uint8)
+            _check(lib.bs_tilemap_walked(self._h, cls, m, None, states.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8)), None, None),
+                   "bs_tilemap_walked")
+            count = np.bincount(states, minlength=3)
+            partial += int(count[1])
+            full += int(count[2])
+        return {"visited": full + partial, "full": full, "partial": partial}
+
     def row_order(self, block_m: int = 128) -> np.ndarray:
         """int32 [n_q_tiles, block_m]: position of every row of every query tile, -1 = no row."""
         out = np.empty((self.n_q_tiles, block_m), dtype=np.int32)
