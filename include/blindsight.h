@@ -282,7 +282,8 @@ int bs_tilemap_upload(bs_tilemap *tm);
  *   stream   hipStream_t (NULL = default stream).  The call only enqueues work; the caller
  *            owns q/k/v/out and keeps them alive until the stream has drained.
  * bf16 path: a pre-pass first packs V (transposed) and, where a launch fetches it often, K into per-key-tile
- * blocks in a workspace the map owns (2 x the size of K, and the partial results of work units that are
+ * blocks in a workspace the map owns (n_kv_heads * n_tiles * head_dim * 256 bytes, n_tiles from bs_tilemap_walked: 2 x the
+ * size of K, and as much more as there are compact tiles; and the partial results of work units that are
  * cut; taken from the library's block cache or hipMalloc on first use).  Calls with a few rows that see the
  * whole cache read K and V where they are; they and the fp32 path use the workspace for partial results.
  * Calls that share a map share that workspace: the library orders a call after

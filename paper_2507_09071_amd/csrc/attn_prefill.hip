@@ -1047,8 +1047,13 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
 // How many key tiles of K the attention kernel reads where the caller has them.  Packing one costs a read and a write of the
 // tile, reading it in place 32-byte pieces on every fetch: 1-1.6 % of the kernel's time on long prompts, which fetch a
 // tile hundreds of times, against 3-10 % of a launch that fetches it ten times (a window, a chunk behind a long cache).
-// Fetches per tile and time saved, d = 128: window of 1024: 11, 3 %; 517-row chunk of 36K: 9-18, 3.5 %; 2048 of 141K:
-// 10-43, 2.2 %; 8K tokens: 59-108, -0.9 to 0.3; 36K: 182-492, -0.2 %; 302K: 377, -1.6 %; d = 64, 9K tokens: 34-66, -0.5 to 0.2.
+// The line is drawn at steps per known key tile, not per tile that the pre-pass would pack: that differs where few rows walk
+// a part of the prompt, in a window, and there reading in place is no slower at several times the line.  d = 128, three layers, one of
+// them all-Dense, steps per known tile (per tile walked) of a sparse / Dense layer, in place against packed: 2.5K tokens 30 / 35
+// (36 / 43), 2 % faster; 4K 29 / 52, 0; 6K 41 / 78, -0.8 %; 9K 54 / 114, 0; two heads a group, 12K 15 / 39, 1.6 %, 24K 27 / 78, 0.9 %, 40K
+// 42 / 129, 0.4 %; rows behind 60K-100K keys in windows of 4-8K: 2K rows 1.3 / 2.7 (15 / 30), 1.8 %, 5K 4.3 / 9 (32 / 67), 0.3 %, 8K
+// 7 / 17 (48 / 118), 0.6 %; 5K rows behind 50K 41 / 118, 0.3 %.  36K tokens 182-492: -0.2 %; 302K 377: -1.6 %; d = 64, 5K tokens
+// 20 / 37 (24 / 45), 1.1 %, 9K 34-66, -0.5 to 0.2 %.
 int32_t tiles_in_place(const bs_tilemap *tm, const DeviceMap *d, int n_kv_heads, int32_t head_dim)
 {
     const int64_t fetches = head_dim == 128 ? 48 : 32;   // (a tile of d = 64 is half as much to pack)
