@@ -133,6 +133,30 @@ struct PairWalker {
         p_end = __builtin_amdgcn_readfirstlane(end);
         load();
     }
+    // The same with the list's first range at hand (two scalars; not looked at if the list is empty).
+    __device__ void init(const int2 *__restrict__ ranges, int begin, int end, int r_begin, int r_end_states, int first_tile)
+    {
+        rg = ranges;
+        p = begin;
+        p_end = end;
+        n = begin < end ? r_begin : first_tile;
+        n_end = begin < end ? r_end_states >> 4 : 0;
+        states = begin < end ? r_end_states & 15 : 0;
+    }
+    // next() for the first steps of a list whose first four ranges are at hand (eight scalars).
+    __device__ void next_of(int begin, const int *first)
+    {
+        const bool same = n + 1 < n_end;
+        const int q = min(p + 1, p_end), i = q - begin;   // (the list's end: stay on the last tile)
+        const bool move = !same && p < p_end && q < p_end;
+        // (values first, then choices: a choice of elements would put the array into scratch memory)
+        const int b1 = first[2], e1 = first[3], b2 = first[4], e2 = first[5], b3 = first[6], e3 = first[7];
+        const int b = i == 1 ? b1 : (i == 2 ? b2 : b3), e = i == 1 ? e1 : (i == 2 ? e2 : e3);
+        n = same ? n + 1 : (move ? b : n);
+        n_end = move ? e >> 4 : n_end;
+        states = move ? e & 15 : states;
+        p = same ? p : q;
+    }
     __device__ bool valid() const { return p < p_end; }
     // Behind its last tile the walker stays on it: what is fetched ahead there is never used, but it has to be a tile that
     // was written (a NaN times a probability of zero is a NaN), and one that is still in the caches.

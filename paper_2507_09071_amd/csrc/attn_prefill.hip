@@ -306,8 +306,14 @@ template <int B, bool FIRST> struct ScBatch { static constexpr int kind = 2, idx
 struct NoBatch { static constexpr int kind = 0, idx = 0; static constexpr bool first = false; };
 
 constexpr int kRing = 4;   // K slots = V^T slots of the LDS ring
+constexpr int kMailboxBytes = 128;                  // the record of a workgroup's next unit, then the unit's number
+constexpr int kPatchRow = 128 + 16;                 // a row of an output patch: 64 channels, where the row goes, the next unit's query row
+constexpr int kPatchBytes = 32 * kPatchRow;         // of one wave
+// LDS: ring, mailbox, output patches.  The patches lie beside the ring slots of a unit's first tiles and query rows, which are
+// on their way while the patches are in use; at d = 128 seven of them fill the CU's LDS, the eighth is in V^T slot 3, which is
+// written in the second step.
 template <int D>
-constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + 64; }   // ring, then the unit mailbox
+constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + kMailboxBytes + (D == 128 ? 7 : 8) * kPatchBytes; }
 
 // One workgroup = two groups of four waves = one work unit: two (head, query tile) items that
 // read the same KV head and walk one merged key-tile list (heads of a GQA group with the same
@@ -323,7 +329,7 @@ constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + 64; }   //
 template <int D>
 __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
-    const int4 *__restrict__ map_rows, const int4 *__restrict__ pair_items,
+    const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
     int32_t n_k_tiles, int32_t in_place, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
@@ -345,43 +351,13 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // ---- state of the work unit in progress (a workgroup takes units from its XCD's queue until
     // ---- the queues are empty; see the unit loop below)
-    int head = 0, m = 0, T = 0, item_class = 0;
+    int head = 0, T = 0, item_class = 0;
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
-    int row = 0;                    // the query position of this lane's row
     const char *kph = nullptr, *vth = nullptr;   // K / packed V^T tiles of the unit's KV head
     const char *kpackh = nullptr;                // its packed K tiles, as if those before `in_place` were, too
     bf16x8 qreg[NT];                // Q^T operand: Q[row][16t + 8hl .. +8] for every 16-wide slice t
     QueryView qv;
-    int list_begin = 0, list_end = 0;
-    auto load_unit = [&](int unit) __attribute__((always_inline)) {
-        const intx4 it0 = scalar_load<intx4>(pair_items + 2 * unit), it1 = scalar_load<intx4>(pair_items + 2 * unit + 1);
-        head = __builtin_amdgcn_readfirstlane(grp ? it0.z : it0.x);
-        m = __builtin_amdgcn_readfirstlane(grp ? it0.w : it0.y);
-        have_item = head >= 0;
-        T = __builtin_amdgcn_readfirstlane(it1.z);            // key tiles in the merged list
-        list_begin = __builtin_amdgcn_readfirstlane(it1.x);
-        list_end = __builtin_amdgcn_readfirstlane(it1.y);
-        const int hsafe = max(head, 0);
-        slot_id = __builtin_amdgcn_readfirstlane(it1.w >> 16);
-        item_class = __builtin_amdgcn_readfirstlane(grp ? it1.w >> 8 : it1.w) & 7;   // head classes travel with the unit
-        const int kvh = __builtin_amdgcn_readfirstlane(it0.x / a.G);            // both items share it
-        // a tile slot without a row behaves like a row past the end of the prompt (computed on a
-        // copy of the last row, never stored)
-        const int slot = max(m, 0) * kBlockM + wave * 32 + col;
-        const int4 r0 = map_rows[2 * slot], r1 = map_rows[2 * slot + 1];
-        row = r0.x;
-        const __bf16 *qh = reinterpret_cast<const __bf16 *>(a.q) + (size_t)hsafe * R * D;
-        // one TILE-byte block per key tile
-        kph = reinterpret_cast<const char *>(a.k) + (size_t)kvh * L * ROW;
-        kpackh = reinterpret_cast<const char *>(kp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
-        vth = reinterpret_cast<const char *>(vt + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
-        const int qrow = min(row, L - 1) - a.q_begin;  // rows past the end compute on a copy and are not stored
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-            qreg[t] = *reinterpret_cast<const bf16x8 *>(qh + (size_t)qrow * D + 16 * t + 8 * hl);
-        qv.init(r0, r1, item_class & 3, (item_class & 4) != 0, a);
-    };
 
     // LDS byte address of this lane's MFMA operand fragments inside a K / V^T tile (see the
     // tile layouts above): key or channel `col`, half hl; slices, blocks and groups are
@@ -393,9 +369,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     floatx16 s[2];
     bf16x8 pf[2][2];   // P^T of the previous tile as MFMA B operands
     float m_run = -INFINITY, l_run = 0.f;
+    int out_row = -1;               // where this lane's row goes in `out`; -1: nowhere
     // three walkers over the merged tile list: w0 names the tile of the current step (state),
     // w1 the next tile (V^T refill), w2 the one after (K refill)
-    PairWalker w0, w1, w2, wt1, wt2;
+    PairWalker w0, w1, w2;
     // Both groups fetch, in the barrier interval k, their shares of K(k+3) and V^T(k+2): the second group
     // at the end of its matrix phase k, the first group right behind barrier k, before its vector phase.
     constexpr int ahead = 1;
@@ -414,12 +391,6 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             for (int e = 0; e < 8; ++e) pf[i >> 1][i & 1][e] = (__bf16)0.f;
         m_run = -INFINITY;
         l_run = 0.f;
-        w0.init(pair_ranges, list_begin, list_end, a.first_tile);
-        w1 = w0; if (w1.valid()) w1.next();
-        wt1 = w1;                                              // tile 1 (prologue)
-        if (ahead && w1.valid()) w1.next();
-        w2 = w1; if (w2.valid()) w2.next();
-        wt2 = wt1; if (wt2.valid()) wt2.next();                // tile 2 (prologue of the second group)
     };
 
     // LDS-direct loads of packed tiles into ring slots: straight TILE-byte copies.  Each wave
@@ -516,9 +487,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * TILE);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto phase_x = [&](int S, bool advance, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4; advance: k > 0
+    auto phase_x = [&](int S, int Sv, bool advance, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4, Sv: slot of V^T(k-1); advance: k > 0
         auto ring = [](int x) { return x >= kRing ? x - kRing : x; };
-        const int Sv = ring(S + kRing - 1);                          // V^T(k-1)
         Sk_dst = ring(ring(S + 2) + ahead); Sv_dst = ring(S + 1 + ahead);
         kbase = kaddr0 + S * TILE;
         vbase = kaddr0 + (kRing + Sv) * TILE;
@@ -607,8 +577,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     };
 
     // The last step: O += P(T-1) V(T-1), nothing else.
-    auto phase_last = [&](int S) __attribute__((always_inline)) {
-        vbase = kaddr0 + (kRing + (S == 0 ? kRing - 1 : S - 1)) * TILE;
+    auto phase_last = [&](int Sv) __attribute__((always_inline)) {
+        vbase = kaddr0 + (kRing + Sv) * TILE;
         bf16x8 fa[4], fb[4], fc[4];
         if constexpr (NDB < 4) {
 #pragma unroll
@@ -663,34 +633,27 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         }
     };
 
-    // Zero the ring once per workgroup: phase X reads every slot from its first step on, and stale LDS
-    // bits could be NaN patterns (0 * NaN would poison the accumulators).  Between units the slots hold
-    // tiles of the previous unit: finite values, which P = 0 wipes out just as well.
-    {
-        const uint4 z4 = make_uint4(0, 0, 0, 0);
-        for (int i = tid * 16; i < 2 * kRing * TILE; i += kPingPongThreads * 16) *reinterpret_cast<uint4 *>(lds + i) = z4;
-    }
-
     // ---- Work distribution.  The host deals the units (heaviest first) to eight queues, one per XCD,
     // so that units walking the same K / V^T tiles at about the same time share an L2.  A workgroup
     // reads the id of the XCD it runs on from the hardware register (it does not depend on the launch
     // order, which other streams can perturb) and claims the next unit of that queue with an atomic
     // counter; when the queue is empty it helps out on the next one.  The first wave takes the ticket
-    // for the next unit two steps before the current one ends -- late, so that the units of a queue
+    // for the next unit three steps before the current one ends -- late, so that the units of a queue
     // start in queue order (units that start together walk the same tiles together and share them in
     // L2; a ticket taken a whole unit ahead was measured to cost half of that sharing), early enough
-    // for the atomic to return under the last steps -- and passes the unit on through a mailbox behind
-    // the ring.  Every wave reads the same mailbox entry, so the workgroup leaves the loop together.
+    // for the atomic to return under the last steps -- and requests the unit's record into a mailbox behind
+    // the ring in the last one.  Every wave reads the same mailbox entry, so the workgroup leaves the loop together.
     typedef volatile __attribute__((address_space(3))) int32_t *lds_int_ptr;
-    const lds_int_ptr mailbox = (lds_int_ptr)(uintptr_t)(ring + 2 * kRing * TILE);
+    const uint32_t mailbox_addr = ring + 2 * kRing * TILE;
+    const lds_int_ptr mailbox = (lds_int_ptr)(uintptr_t)mailbox_addr;
     int xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
     xcc &= 7;
     // The unit of a ticket of the own queue; if that is empty, a claim on the next one that is not, or -1.  One look
     // at all counters says which queues to ask (a counter only grows: what is empty stays empty); asking seven
     // empty queues one after the other took 10 us at the end of every launch.
+    const int own_begin = scalar_load<int>(queue_off + xcc), own_len = scalar_load<int>(queue_off + xcc + 1) - own_begin;
     auto claim_from = [&](int ticket) {
-        const int own_begin = scalar_load<int>(queue_off + xcc), own_len = scalar_load<int>(queue_off + xcc + 1) - own_begin;
         if (ticket < own_len) return own_begin + ticket;
         const int q = lane & 7, begin = queue_off[q], len = queue_off[q + 1] - begin;
         const bool left = __hip_atomic_load(&queue_ctr[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < len;
@@ -741,46 +704,184 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         share_next = share_off[share];
         share_end = share_off[share + 1];
     }
+    // The record of a unit goes to the mailbox by itself (64 bytes: four lanes of an LDS-direct load).
+    static_assert(sizeof(UnitRecord) == 64, "four lanes of 16 bytes");
+    auto fetch_record = [&](int u) __attribute__((always_inline)) {
+        const char *src = reinterpret_cast<const char *>(units) + (size_t)u * sizeof(UnitRecord);
+        const uint32_t off = lane * 16;
+        unsigned long long save;
+        asm volatile("s_mov_b64 %[save], exec\n\t"
+                     "s_mov_b64 exec, 15\n\t"
+                     "s_mov_b32 m0, %[dst]\n\t"
+                     "s_nop 0\n\t"
+                     "global_load_lds_dwordx4 %[off], %[src]\n\t"
+                     "s_mov_b64 exec, %[save]"
+                     : [save] "=&s"(save)
+                     : [off] "v"(off), [src] "s"(src), [dst] "s"(mailbox_addr)
+                     : "memory", "m0");
+    };
+    constexpr int kUnknown = -2;
+    int next_unit = -1;                            // first wave: the unit that the mailbox is filled for
     if (wave8 == 0) {
-        const int first = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(take_ticket()));
-        if (lane == 0) mailbox[0] = first;
+        next_unit = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(take_ticket()));
+        if (next_unit >= 0) fetch_record(next_unit);
+        if (lane == 0) mailbox[16] = next_unit;
     }
     ++share_next;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    int unit = __builtin_amdgcn_readfirstlane(mailbox[0]);
 
-    while (unit >= 0) {
-        int next_ticket = 0;
-        load_unit(unit);
-        reset_unit_state();
-        {
-            const int nn = __builtin_amdgcn_readfirstlane(w0.n);
-            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
-            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
+    // ---- the loop over units.  The end of one and the beginning of the next overlap: with the barrier behind the last step
+    // everybody knows the next unit's record, its row records are requested before the first half of the epilogue and its
+    // query rows and first tiles between the two halves, so that their latencies run side by side and under the stores.
+    // The query rows come through LDS, whole rows per load (into the slots of K(2), K(3) and V^T(1), V^T(2), which are
+    // requested when every wave has its rows): as operands straight from memory every lane would take 16 bytes of another
+    // row, 64 lines per instruction, and the 64 instructions of a workgroup kept the vector cache busy for 4,000 cycles.
+    // From the last step to the first one (time stamps): 13,500 -> 9,500 cycles on long prompts, 19,000 -> 13,000 on a windowed
+    // one; passes 1590 -> 1554 us (27K tokens, window of 1024, 13 units a workgroup), 1029 -> 1008 (8K tokens, 4 units), d = 64 910 ->
+    // 894 (9K).  Overlapping alone, with the operands straight from memory, gained nothing.
+    constexpr int kRowsPerLoad = 1024 / ROW, kChunks = ROW / 16, kQueryLoads = 32 / kRowsPerLoad;
+    auto swizzle = [](int r) { return D == 128 ? r & 15 : (r >> 1) & 7; };   // the 16-byte chunks of row r change places: column reads without conflicts
+    bool first_unit = true;
+    for (;;) {
+        const int unit = __builtin_amdgcn_readfirstlane(mailbox[16]);
+        const bool more = unit >= 0;
+        // (hidden from the compiler, or addresses that only this part needs would stay in registers through the step loops)
+        int ln = lane, w8 = wave8;
+        asm volatile("" : "+v"(ln), "+s"(w8));
+        const int hl = ln >> 5, col = ln & 31;
+        unsigned char *const stage = lds + (D == 128 && w8 == 7 ? (2 * kRing - 1) * TILE : 2 * kRing * TILE + kMailboxBytes + w8 * kPatchBytes);
+        const int query_at = (w8 >= 4 ? kRing + 1 : 2) * TILE + (w8 & 3) * 32 * ROW;
+        // of the previous unit, for its epilogue
+        const int done_head = head, done_slot = slot_id;
+        const bool done_item = have_item && !first_unit;
+        int4 r0, r1;
+        int rec[16];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const intx4 x = *(const __attribute__((address_space(3))) intx4 *)(uintptr_t)(mailbox_addr + 16 * i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) rec[4 * i + j] = __builtin_amdgcn_readfirstlane(x[j]);
         }
-        // prologue: K(0) -> K slot 0, K(1) -> K slot 1, V^T(0) -> V^T slot 0 (unconditional)
-        {
-            const char *k0 = k_ptr(w0.n), *k1 = k_ptr(wt1.n), *v0 = tile_ptr(vth, w0.n);
+        if (more) {
+            head = grp ? rec[2] : rec[0];
+            have_item = head >= 0;
+            T = rec[6];                                           // key tiles in the merged list
+            slot_id = rec[7] >> 16;
+            item_class = (grp ? rec[7] >> 8 : rec[7]) & 7;        // head classes travel with the unit
+            const int kvh = __builtin_amdgcn_readfirstlane(rec[0] / a.G);                       // both items share it
+            // a tile slot without a row behaves like a row past the end of the prompt (computed on a
+            // copy of the last row, never stored)
+            const int row_slot = max(grp ? rec[3] : rec[1], 0) * kBlockM + (w8 & 3) * 32 + col;
+            r0 = map_rows[2 * row_slot];
+            r1 = map_rows[2 * row_slot + 1];
+            // one TILE-byte block per key tile
+            kph = reinterpret_cast<const char *>(a.k) + (size_t)kvh * L * ROW;
+            kpackh = reinterpret_cast<const char *>(kp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
+            vth = reinterpret_cast<const char *>(vt + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
+        }
+
+        // epilogue of the previous unit: divide by the running sum, round, store.  Empty rows (l = 0) give zeros.  A lane holds
+        // four channels of one row at a time (O^T accumulators), which would make every store instruction
+        // touch 64 rows with 8 bytes each; the tile goes through LDS instead, 64 channels at a time in a wave-private patch, and
+        // leaves as 16-byte pieces of 128-byte row segments.
+        const float l_tot = sum_across_halves(l_run);
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 128) = out_row;
+        auto store_half = [&](int half) __attribute__((always_inline)) {
+#pragma unroll
+            for (int dbl = 0; dbl < 2; ++dbl)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    bf16x4 w;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) w[r] = (__bf16)(o[2 * half + dbl][4 * g + r] * inv);
+                    *reinterpret_cast<bf16x4 *>(stage + col * kPatchRow + (32 * dbl + 8 * g + 4 * hl) * 2) = w;
+                }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = 8 * j + (ln >> 3), chunk = ln & 7;
+                const uint4 piece = *reinterpret_cast<const uint4 *>(stage + r * kPatchRow + chunk * 16);
+                const int32_t to = *reinterpret_cast<const int32_t *>(stage + r * kPatchRow + 128);
+                if (to >= 0) *reinterpret_cast<uint4 *>(reinterpret_cast<__bf16 *>(a.out) + (size_t)to * D + 64 * half + chunk * 8) = piece;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        if (done_item) {
+            // a part of a cut unit: accumulators, reference point and row sum as they are
+            if (done_slot > 0) store_cut_item<D>(cut_results + ((size_t)(done_slot - 1) * 2 + grp) * kCutItemFloats<D>, o, m_run, l_tot, w8 & 3, ln);
+            else store_half(0);
+        }
+        if (more) {
+            const int row = r0.x;
+            out_row = row < L ? max(head, 0) * R + (row - a.q_begin) : -1;
+            // rows past the end compute on a copy and are not stored
+            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 132) = min(row, L - 1) - a.q_begin;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const char *qh = static_cast<const char *>(a.q) + (size_t)max(head, 0) * R * ROW;
+#pragma unroll
+            for (int j = 0; j < kQueryLoads; ++j) {
+                const int r = j * kRowsPerLoad + ln / kChunks;
+                const uint32_t off = *reinterpret_cast<const uint32_t *>(stage + r * kPatchRow + 132) * ROW + (((ln % kChunks) ^ swizzle(r)) << 4);
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                             :
+                             : "v"(off), "s"(qh), "s"(ring + query_at + j * 1024)
+                             : "memory", "m0");
+            }
+            // the walkers of the first four tiles, from the record's copy of the list's first ranges
+            w0.init(pair_ranges, rec[4], rec[5], rec[8], rec[9], a.first_tile);
+            auto step = [&](PairWalker &w) { w.next_of(rec[4], &rec[8]); };
+            PairWalker wt1 = w0; step(wt1);                                  // tile 1
+            w1 = wt1; step(w1);                                   // tile 2
+            w2 = w1; step(w2);                                    // tile 3
+            // K(0), K(1) and V^T(0) to the slots of these numbers (unconditional)
+            const int n0 = __builtin_amdgcn_readfirstlane(w0.n), n1 = __builtin_amdgcn_readfirstlane(wt1.n);
+            const char *k0 = k_ptr(n0), *k1 = k_ptr(n1), *v0 = tile_ptr(vth, n0);
+            ksrc = k_ptr(w1.n);
+            vsrc = tile_ptr(vth, n1);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k0, 0);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k1, TILE);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v0, kRing * TILE);
-            {
-                const char *k2 = k_ptr(wt2.n), *v1 = tile_ptr(vth, wt1.n);
-#pragma unroll
-                for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k2, 2 * TILE);
-#pragma unroll
-                for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v1, (kRing + 1) * TILE);
-            }
         }
+        if constexpr (NDB == 4) {
+            if (done_item && done_slot == 0) store_half(1);
+        }
+        if (!more) break;
+        first_unit = false;
+        reset_unit_state();
+        qv.init(r0, r1, item_class & 3, (item_class & 4) != 0, a);
+        {
+            const int nn = __builtin_amdgcn_readfirstlane(w0.n);
+            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
+            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
+        }
+        int next_ticket = 0;
+        if (wave8 == 0) next_unit = kUnknown;
+        const int k_late = wave8 == 0 && T >= 3 ? T - 3 : INT32_MAX;   // the first wave's steps with something to do for the next unit
         // Raw barriers: every LDS access of the loop is an LDS-direct load (drained with vmcnt
         // at the end of phase X) or an asm read (drained with lgkmcnt inside phase X), so no fence
         // is wanted there -- a fence would drain loads that are meant to stay in flight.
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the first tiles
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the unit's scalar loads (none stays pending into the loop)
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): query rows and first tiles
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            qreg[t] = *(const __attribute__((address_space(3))) bf16x8 *)(uintptr_t)((ring + query_at + col * ROW + ((hl ^ swizzle(col)) << 4)) ^ (t << 5));
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the query rows, the unit's scalar loads (none stays pending into the loop)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(qreg[t]));
         __builtin_amdgcn_s_barrier();
+        Sk_dst = 2; Sv_dst = 1;
+        issue_refill();                      // K(2) and V^T(1), as a step before the first one would
         // ONE barrier per step.  Group 0 runs  X(k) | barrier | refill Y(k),  group 1  barrier | X(k) refill Y(k):
         // between two barriers group 0 does Y(k) then X(k+1) while group 1 does X(k) then Y(k), so
         // the waves of a SIMD are in opposite phases by program order but nothing holds them to a
@@ -792,93 +893,60 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // The last step only adds P(T-1) V(T-1) and stands behind the loop: half a matrix phase, no refill.
         // With the look at all queues at once (claim_from) a windowed prompt of 27K tokens, 13 units per
         // workgroup of 20 tiles each, takes 2058 instead of 2093 us a pass.
-        int slot = 0;
+        int slot = 0, v_slot = 0;   // (before the first step P is zero, and any finite tile will do for V^T(-1): V^T(0))
         if (grp == 0) {
             // (no first iteration of its own: the compiler puts the zeroing of the accumulators and fragments right in front of
             // the MFMAs that read them, too close for the hardware, and does not know; tests/isa_check.py looks for that)
 #pragma nounroll
             for (int k = 0; k < T; ++k) {
-                if (wave8 == 0 && k == T - 1 && share_next >= share_end) next_ticket = take_ticket_async();   // consumed after the loop
-                phase_x(slot, k > 0, std::false_type{});
+                if (k >= k_late) {
+                    if (k == T - 3) {
+                        if (share_next >= share_end) next_ticket = take_ticket_async();
+                    } else if (k == T - 1) {
+                        // (the ticket is there: the phases since have waited for all but the newest loads)
+                        int ticket = next_ticket;
+                        asm volatile("" : "+v"(ticket));
+                        ticket = __builtin_amdgcn_readfirstlane(ticket);
+                        if (share_next < share_end) next_unit = share_next;
+                        else if (ticket < own_len) next_unit = own_begin + ticket;
+                        if (next_unit >= 0) fetch_record(next_unit);
+                    }
+                }
+                phase_x(slot, v_slot, k > 0, std::false_type{});
                 __builtin_amdgcn_s_barrier();
                 issue_refill();   // under the second group's head reads, before its chain starts
                 phase_y();
+                v_slot = slot;
                 slot = slot == kRing - 1 ? 0 : slot + 1;
             }
-            if (wave8 == 0 && T == 0 && share_next >= share_end) next_ticket = take_ticket_async();
-            phase_last(slot);
-            __builtin_amdgcn_s_barrier();
+            if (T > 0) phase_last(v_slot);
         } else {
 #pragma nounroll
             for (int k = 0; k < T; ++k) {
                 __builtin_amdgcn_s_barrier();
-                phase_x(slot, k > 0, std::true_type{});
+                phase_x(slot, v_slot, k > 0, std::true_type{});
                 phase_y();
+                v_slot = slot;
                 slot = slot == kRing - 1 ? 0 : slot + 1;
             }
-            __builtin_amdgcn_s_barrier();
-            phase_last(slot);
+            if (T > 0) phase_last(v_slot);
         }
         // End of the unit: the refills of its last steps (tiles nobody needs) must have landed
         // before the next unit's first tiles go into the same slots, and every wave must be done
-        // reading the ring.  The ticket has returned by then as well.
+        // reading the ring.  The next unit's record has arrived by then as well.
         ticket_wait(next_ticket);            // vmcnt(0)
         if (wave8 == 0) {
-            const int nxt = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(next_ticket));
-            if (lane == 0) mailbox[0] = nxt;
+            if (next_unit == kUnknown) {     // a unit of less than three steps, or an empty queue
+                if (share_next < share_end) next_unit = share_next;
+                else next_unit = claim_from(T >= 3 ? __builtin_amdgcn_readfirstlane(next_ticket) : __builtin_amdgcn_readfirstlane(take_ticket()));
+                if (next_unit >= 0) fetch_record(next_unit);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            if (lane == 0) mailbox[16] = next_unit;
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the mailbox write is in LDS before the barrier
         }
         __builtin_amdgcn_s_barrier();
-        const int next_unit = __builtin_amdgcn_readfirstlane(mailbox[0]);
         ++share_next;
-
-        // epilogue: divide by the running sum, round, store.  Empty rows (l = 0) give zeros.  A lane holds
-        // four channels of one row at a time (O^T accumulators), which would make every store instruction
-        // touch 64 rows with 8 bytes each; the tile goes through LDS instead (the ring is free: every wave is
-        // past the barrier above), 64 channels at a time in a wave-private patch, and leaves as 16-byte pieces
-        // of 128-byte row segments.
-        const float l_tot = sum_across_halves(l_run);
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        if (slot_id > 0) {
-            // a part of a cut unit: accumulators, reference point and row sum as they are
-            if (have_item) store_cut_item<D>(cut_results + ((size_t)(slot_id - 1) * 2 + grp) * kCutItemFloats<D>, o, m_run, l_tot, wave, lane);
-        } else {
-            constexpr int kStageRow = 128 + 16;                 // 64 channels, then the row's position
-            unsigned char *stage = lds + wave8 * (32 * kStageRow);
-            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kStageRow + 128) = row;
-#pragma unroll
-            for (int half = 0; half < NDB / 2; ++half) {
-#pragma unroll
-                for (int dbl = 0; dbl < 2; ++dbl)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        bf16x4 w;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) w[r] = (__bf16)(o[2 * half + dbl][4 * g + r] * inv);
-                        *reinterpret_cast<bf16x4 *>(stage + col * kStageRow + (32 * dbl + 8 * g + 4 * hl) * 2) = w;
-                    }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = 8 * j + (lane >> 3), chunk = lane & 7;
-                    const uint4 piece = *reinterpret_cast<const uint4 *>(stage + r * kStageRow + chunk * 16);
-                    const int32_t pos = *reinterpret_cast<const int32_t *>(stage + r * kStageRow + 128);
-                    if (have_item && pos < L) {
-                        __bf16 *orow = reinterpret_cast<__bf16 *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D;
-                        *reinterpret_cast<uint4 *>(orow + 64 * half + chunk * 8) = piece;
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-        }
-        // the patches lie in the ring: nobody loads the next unit's first tiles before every wave is done with its own
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        unit = next_unit;
     }
 }
 
@@ -1032,7 +1100,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     if (e != hipSuccess) return e;
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     e = bs::launch_kernel(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                          d->sink_bits, d->rows, sh ? sh->items : d->pair_items, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
+                          d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
                           d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
     if (e == hipSuccess && sh && sh->n_cut > 0)
         e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,

@@ -61,7 +61,8 @@ struct ShareSet {
     int32_t n_wgs = 0;                    // 0: not made
     int32_t n_shares = 0;                 // 0: not worth it
     int32_t n_cut = 0, n_slots = 0;
-    const int4 *items = nullptr;          // the parts, ...
+    const int4 *items = nullptr;          // the parts (fp32), ...
+    const UnitRecord *units = nullptr;    // ... or (bf16) their records
     const int2 *ranges = nullptr;
     const int32_t *off = nullptr;         // ... [n_shares + 1] the parts of each workgroup, ...
     const int32_t *queue_off = nullptr;   // ... [9] the parts for whoever is done first, ...
@@ -83,7 +84,8 @@ struct DeviceMap {
     int32_t bind_kind = kBindNone;
     int32_t bind_G = 0;
     uint64_t bind_epoch = 0;              // class_epoch of the map the binding was made for
-    const int4 *pair_items = nullptr;     // work units, two int4 each
+    const int4 *pair_items = nullptr;     // fp32: work units, two int4 each
+    const UnitRecord *units = nullptr;    // bf16: their records
     const int2 *pair_ranges = nullptr;
     int32_t n_pairs = 0;
     const int32_t *queue_off = nullptr;   // [9] the units of XCD x are pair_items[queue_off[x] .. queue_off[x + 1])

@@ -510,13 +510,15 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     // equal shares: parts, their ranges, share offsets, queue offsets, cut items
     size_t bytes = 0;
     auto section = [&](size_t n) { const size_t at = bytes; bytes = align256(bytes + n); return at; };
-    const size_t off_a = section(plan.items.size() * sizeof(PairItem));
+    const bool records = kind == kBindPairPlan;
+    const size_t unit_bytes = records ? sizeof(UnitRecord) : sizeof(PairItem);
+    const size_t off_a = section(plan.items.size() * unit_bytes);
     const size_t off_b = section(std::max<size_t>(plan.ranges.size(), 1) * sizeof(PairRange));
     const size_t off_q = section(256);
     size_t off_s[2][5];
     for (int i = 0; i < 2; ++i) {
         const SharePlan &s = *share_plans[i];
-        off_s[i][0] = section(s.parts.size() * sizeof(PairItem));
+        off_s[i][0] = section(s.parts.size() * unit_bytes);
         off_s[i][1] = section(s.ranges.size() * sizeof(PairRange));
         off_s[i][2] = section(s.share_off.size() * 4);
         off_s[i][3] = section(s.share_off.empty() ? 0 : sizeof s.queue_off);
@@ -529,13 +531,22 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     unsigned char *host = static_cast<unsigned char *>(sg.host);
     static_assert(sizeof(PairItem) == 2 * sizeof(int4) && sizeof(PairRange) == sizeof(int2) && sizeof(CutItem) == sizeof(int4), "copied as they are");
     auto put = [&](size_t at, const auto &v) { if (!v.empty()) std::memcpy(host + at, v.data(), v.size() * sizeof(v[0])); };
-    put(off_a, plan.items);
+    auto put_units = [&](size_t at, const std::vector<PairItem> &items, const std::vector<PairRange> &ranges) {
+        if (!records) return put(at, items);
+        UnitRecord *to = reinterpret_cast<UnitRecord *>(host + at);   // (written once, in order: the pinned buffer is not read)
+        for (const PairItem &it : items) {
+            UnitRecord r{it, {}};
+            for (int32_t i = 0; i < 4 && it.list_begin + i < it.list_end; ++i) r.first[i] = ranges[it.list_begin + i];
+            *to++ = r;
+        }
+    };
+    put_units(off_a, plan.items, plan.ranges);
     put(off_b, plan.ranges);
     std::memset(host + off_q, 0, 256);
     std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
     for (int i = 0; i < 2; ++i) {
         const SharePlan &s = *share_plans[i];
-        put(off_s[i][0], s.parts);
+        put_units(off_s[i][0], s.parts, s.ranges);
         put(off_s[i][1], s.ranges);
         put(off_s[i][2], s.share_off);
         if (!s.share_off.empty()) std::memcpy(host + off_s[i][3], s.queue_off, sizeof s.queue_off);
@@ -567,7 +578,8 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     d->bind_kind = kind;
     d->bind_G = gqa_group;
     d->bind_epoch = tm->class_epoch;
-    d->pair_items = reinterpret_cast<const int4 *>(b + off_a);
+    d->pair_items = records ? nullptr : reinterpret_cast<const int4 *>(b + off_a);
+    d->units = records ? reinterpret_cast<const UnitRecord *>(b + off_a) : nullptr;
     d->pair_ranges = reinterpret_cast<const int2 *>(b + off_b);
     d->n_pairs = (int32_t)plan.items.size();
     d->n_steps = 0;
@@ -581,7 +593,8 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
         to.n_shares = s.share_off.empty() ? 0 : (int32_t)s.share_off.size() - 1;
         to.n_cut = (int32_t)s.cut.size();
         to.n_slots = s.n_slots;
-        to.items = reinterpret_cast<const int4 *>(b + off_s[i][0]);
+        to.items = records ? nullptr : reinterpret_cast<const int4 *>(b + off_s[i][0]);
+        to.units = records ? reinterpret_cast<const UnitRecord *>(b + off_s[i][0]) : nullptr;
         to.ranges = reinterpret_cast<const int2 *>(b + off_s[i][1]);
         to.off = reinterpret_cast<const int32_t *>(b + off_s[i][2]);
         to.queue_off = reinterpret_cast<const int32_t *>(b + off_s[i][3]);

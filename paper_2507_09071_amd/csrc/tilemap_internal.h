@@ -129,6 +129,13 @@ struct PairRange {
     int32_t end_states;  // (end << 4) | (state_a << 2) | state_b
 };
 
+// A unit of the bf16 kernel in the device copy: with the first ranges of its list, so that a workgroup that takes it up asks for
+// its first tiles without waiting for the list.
+struct UnitRecord {
+    PairItem item;
+    PairRange first[4];   // as many as the list has
+};
+
 struct PairPlan {
     int32_t gqa_group = 0;  // the plan depends on which heads share a KV head ...
     uint64_t epoch = 0;     // ... and on the class vector (bs_tilemap::class_epoch when it was made)
