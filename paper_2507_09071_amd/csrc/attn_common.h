@@ -112,7 +112,31 @@ __device__ inline T scalar_load(const U *p)
 typedef int intx2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
-// Walks the merged key-tile list of a work unit: runs of [begin, end) with a state per item.
+// Walks the merged key-tile list of a work unit from its record on (bf16).  The run behind the present one is there before it
+// is needed: a walk that asked for it at its turn would wait for the scalar cache, and with it for the operand reads in flight.
+struct TileWalker {
+    const int2 *__restrict__ rg;
+    int cur, end;                     // the tile, with its states; where its run ends
+    int next_begin, next_end;         // the next run, if p <= p_end
+    int p, p_end;
+    // Behind its last tile the walker stays on it (see PairWalker).
+    __device__ void next()
+    {
+        const int t = cur + 16;
+        if (t != end) {
+            cur = t;
+        } else if (p <= p_end) {
+            cur = (next_begin << 4) | (next_end & 15);
+            end = next_end;
+            const intx2 r = scalar_load<intx2>(rg + min(p, p_end - 1));
+            next_begin = r.x;
+            next_end = r.y;
+            ++p;
+        }
+    }
+};
+
+// The same from the list alone, a run at a time (fp32).
 struct PairWalker {
     const int2 *__restrict__ rg;
     int p, p_end, n, n_end, states;
@@ -132,30 +156,6 @@ struct PairWalker {
         p = __builtin_amdgcn_readfirstlane(begin);
         p_end = __builtin_amdgcn_readfirstlane(end);
         load();
-    }
-    // The same with the list's first range at hand (two scalars; not looked at if the list is empty).
-    __device__ void init(const int2 *__restrict__ ranges, int begin, int end, int r_begin, int r_end_states, int first_tile)
-    {
-        rg = ranges;
-        p = begin;
-        p_end = end;
-        n = begin < end ? r_begin : first_tile;
-        n_end = begin < end ? r_end_states >> 4 : 0;
-        states = begin < end ? r_end_states & 15 : 0;
-    }
-    // next() for the first steps of a list whose first four ranges are at hand (eight scalars).
-    __device__ void next_of(int begin, const int *first)
-    {
-        const bool same = n + 1 < n_end;
-        const int q = min(p + 1, p_end), i = q - begin;   // (the list's end: stay on the last tile)
-        const bool move = !same && p < p_end && q < p_end;
-        // (values first, then choices: a choice of elements would put the array into scratch memory)
-        const int b1 = first[2], e1 = first[3], b2 = first[4], e2 = first[5], b3 = first[6], e3 = first[7];
-        const int b = i == 1 ? b1 : (i == 2 ? b2 : b3), e = i == 1 ? e1 : (i == 2 ? e2 : e3);
-        n = same ? n + 1 : (move ? b : n);
-        n_end = move ? e >> 4 : n_end;
-        states = move ? e & 15 : states;
-        p = same ? p : q;
     }
     __device__ bool valid() const { return p < p_end; }
     // Behind its last tile the walker stays on it: what is fetched ahead there is never used, but it has to be a tile that

@@ -370,9 +370,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     bf16x8 pf[2][2];   // P^T of the previous tile as MFMA B operands
     float m_run = -INFINITY, l_run = 0.f;
     int out_row = -1;               // where this lane's row goes in `out`; -1: nowhere
-    // three walkers over the merged tile list: w0 names the tile of the current step (state),
-    // w1 the next tile (V^T refill), w2 the one after (K refill)
-    PairWalker w0, w1, w2;
+    // The tile of the vector phase and those behind it, with their states: step k of a unit refills K with the tile that
+    // the walker stands on, k + 3, and V^T with the one before.
+    TileWalker walk;
+    int tile_y = 0, tile_1 = 0, tile_2 = 0, tile_3 = 0;
     // Both groups fetch, in the barrier interval k, their shares of K(k+3) and V^T(k+2): the second group
     // at the end of its matrix phase k, the first group right behind barrier k, before its vector phase.
     constexpr int ahead = 1;
@@ -457,28 +458,34 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     using I3 = std::integral_constant<int, 3>;
 
     // Phase X of step k: O += P(k-1) V(k-1) and S(k) = K(k) Q^T.  Always the same straight-line
-    // chain of asm statements: before the first tile P is zero (the ring was zero-filled), after
-    // the last tile -- and on tiles this item skips -- P is zero again and the scores it
-    // produces are ignored.  Operand reads run three batches ahead of the MFMAs that consume
+    // chain of asm statements: before the first tile -- and behind tiles this item skips -- P is zero,
+    // and the scores of a tile it skips are ignored.  Operand reads run three batches ahead of the MFMAs that consume
     // them, in three rotating register sets; each lds_wait<N> count is the number of reads
     // issued after the batch waited for.  A register is refilled right after the MFMA that
     // read it has issued (operands are read at issue, LDS data returns later), so the reads
     // issue in the shadow of the MFMAs.
-    // text / sink key bits of the tile w0 names (scalar registers, fetched one step ahead)
+    // text / sink key bits of the tile of the coming phase Y (scalar registers)
     uint64_t tb_cur = 0, sb_cur = 0;
-    // Scalar bookkeeping between two vector phases: w0 moves on to the tile of the coming phase Y and
-    // the key bit masks of that tile are requested.  It runs inside phase X, between two MFMA batches,
-    // where the wave has issue slots to spare (every MFMA keeps the matrix pipe busy for 32 cycles).
-    auto advance_tile = [&]() __attribute__((always_inline)) {
+    const char *ksrc = nullptr, *vsrc = nullptr;   // tiles of the coming refill ...
+    // The scalar work of a step -- tiles of the refill, the walk, the key bit masks of the coming phase Y -- stands inside
+    // phase X, between two MFMA batches, where the wave has issue slots to spare (every MFMA keeps the matrix pipe busy for
+    // 32 cycles).  Anything in front of the first MFMA costs its full length: with the walk there the same kernel takes 2 % longer
+    // (36K tokens 15573 us, 15220 with it here), with three walkers instead of the one and a look-ahead 3 % on windows.
+    auto advance_walk = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
-        w0.next();
-        const int nn = __builtin_amdgcn_readfirstlane(w0.n);
+        ksrc = k_ptr(walk.cur >> 4);
+        vsrc = tile_ptr(vth, tile_3 >> 4);
+        tile_y = tile_1;
+        tile_1 = tile_2;
+        tile_2 = tile_3;
+        tile_3 = walk.cur;
+        walk.next();
+        const int nn = tile_y >> 4;
         tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
         sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
         __builtin_amdgcn_sched_barrier(0);
     };
-    const char *ksrc = nullptr, *vsrc = nullptr;   // tiles of the coming refill
-    int Sk_dst = 0, Sv_dst = 0;                    // and their ring slots
+    int Sk_dst = 0, Sv_dst = 0;                    // ... and their ring slots
     auto issue_refill = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -487,7 +494,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * TILE);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto phase_x = [&](int S, int Sv, bool advance, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4, Sv: slot of V^T(k-1); advance: k > 0
+    auto phase_x = [&](int S, int Sv, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4, Sv: slot of V^T(k-1)
         auto ring = [](int x) { return x >= kRing ? x - kRing : x; };
         Sk_dst = ring(ring(S + 2) + ahead); Sv_dst = ring(S + 1 + ahead);
         kbase = kaddr0 + S * TILE;
@@ -520,27 +527,17 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             mul_one(cur, I2{}, f[2]); read_one(mid, I2{}, g[2]); read_one(nxt, I2{}, f[2]);
             mul_one(cur, I3{}, f[3]); read_one(mid, I3{}, g[3]); read_one(nxt, I3{}, f[3]);
         };
-        // Refill addresses: computed while the first operand reads are in flight.
-        auto refill_prepare = [&]() __attribute__((always_inline)) {
-            __builtin_amdgcn_sched_barrier(0);
-            ksrc = k_ptr(w2.n);
-            vsrc = tile_ptr(vth, w1.n);
-            w1.next();
-            w2.next();
-            __builtin_amdgcn_sched_barrier(0);
-        };
         if constexpr (D == 128) {
             // batch order: PV0 S0 PV1 S1 PV2 S2 PV3 S3, four reads / MFMAs each
             // Only two batches are read ahead of the first MFMA (the burst of all four waves of a group
             // costs every wave its share of the LDS time); the third goes out behind the first four
             // MFMAs together with their refills.
             read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb);
-            refill_prepare();
             lds_wait<4>(fa); batch2(PvBatch<0>{}, PvBatch<1>{}, fc, ScBatch<1, false>{}, fa);
             lds_wait<8>(fb); batch(ScBatch<0, true>{}, PvBatch<2>{}, fb);
             lds_wait<5>(fc); batch(PvBatch<1>{}, ScBatch<2, false>{}, fc);   // behind the last PV1 read: one S1 read, four PV2
             lds_wait<8>(fa); batch(ScBatch<1, false>{}, PvBatch<3>{}, fa);
-            if (advance) advance_tile();
+            advance_walk();
             lds_wait<8>(fb); batch(PvBatch<2>{}, ScBatch<3, false>{}, fb);
             lds_wait<8>(fc); batch(ScBatch<2, false>{}, NoBatch{}, fc);
             lds_wait<4>(fa); batch(PvBatch<3>{}, NoBatch{}, fa);
@@ -549,11 +546,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         } else {
             // D == 64: PV batches hold two reads / MFMAs, S has two batches of four
             read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb); read_batch(PvBatch<1>{}, fc);   // 2 + 4 + 2
-            refill_prepare();
             lds_wait<6>(fa); batch(PvBatch<0>{}, PvBatch<2>{}, fa);                     // 4 2 | 2
             lds_wait<4>(fb); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fb);        // 2 2 | 4
             lds_wait<6>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);                     // 2 4 | 2
-            if (advance) advance_tile();
+            advance_walk();
             lds_wait<6>(fa); batch(PvBatch<2>{}, NoBatch{}, fa);
             lds_wait<2>(fb); batch(ScBatch<1, false>{}, NoBatch{}, fb);
             lds_wait<0>(fc); batch(PvBatch<3>{}, NoBatch{}, fc);
@@ -612,10 +608,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // (what stays the same for a unit is hidden from the compiler here: it made loops of their own for its values)
         int hd = head, cls = item_class;
         asm("" : "+s"(hd), "+s"(cls));
-        const int st = hd >= 0 ? w0.state(grp) : 0;
+        const int st = hd >= 0 ? (grp ? tile_y : tile_y >> 2) & 3 : 0;
         bool drop = false;
         if (st != 2) {
-            const int nu = __builtin_amdgcn_readfirstlane(w0.n);
+            const int nu = tile_y >> 4;
             const uint64_t allowed = st == 0 ? 0ull : allowed_keys(qv, cls, tb_cur, sb_cur, nu, a);
             drop = allowed == 0ull;
             // where every query of the wave sees all 64 keys or none (e.g. a text row and an
@@ -705,7 +701,6 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         share_end = share_off[share + 1];
     }
     // The record of a unit goes to the mailbox by itself (64 bytes: four lanes of an LDS-direct load).
-    static_assert(sizeof(UnitRecord) == 64, "four lanes of 16 bytes");
     auto fetch_record = [&](int u) __attribute__((always_inline)) {
         const char *src = reinterpret_cast<const char *>(units) + (size_t)u * sizeof(UnitRecord);
         const uint32_t off = lane * 16;
@@ -766,10 +761,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         if (more) {
             head = grp ? rec[2] : rec[0];
             have_item = head >= 0;
-            T = rec[6];                                           // key tiles in the merged list
-            slot_id = rec[7] >> 16;
-            item_class = (grp ? rec[7] >> 8 : rec[7]) & 7;        // head classes travel with the unit
-            const int kvh = __builtin_amdgcn_readfirstlane(rec[0] / a.G);                       // both items share it
+            T = rec[4];                                           // key tiles in the merged list
+            slot_id = rec[5] >> 16;
+            item_class = (grp ? rec[5] >> 8 : rec[5]) & 7;        // head classes travel with the unit
+            const int kvh = rec[6];                               // both items share it
             // a tile slot without a row behaves like a row past the end of the prompt (computed on a
             // copy of the last row, never stored)
             const int row_slot = max(grp ? rec[3] : rec[1], 0) * kBlockM + (w8 & 3) * 32 + col;
@@ -835,17 +830,16 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
                              : "v"(off), "s"(qh), "s"(ring + query_at + j * 1024)
                              : "memory", "m0");
             }
-            // the walkers of the first four tiles, from the record's copy of the list's first ranges
-            w0.init(pair_ranges, rec[4], rec[5], rec[8], rec[9], a.first_tile);
-            auto step = [&](PairWalker &w) { w.next_of(rec[4], &rec[8]); };
-            PairWalker wt1 = w0; step(wt1);                                  // tile 1
-            w1 = wt1; step(w1);                                   // tile 2
-            w2 = w1; step(w2);                                    // tile 3
+            // (the walkers name tiles that this launch's pre-pass wrote, also those of an empty list)
+            const int none = a.first_tile << 4;
+            tile_1 = T > 0 ? rec[8] : none;
+            tile_2 = T > 0 ? rec[9] : none;
+            tile_3 = T > 0 ? rec[10] : none;
+            walk = {pair_ranges, T > 0 ? rec[11] : none, T > 0 ? rec[12] : none + 16, rec[13], rec[14], rec[15], rec[7]};
             // K(0), K(1) and V^T(0) to the slots of these numbers (unconditional)
-            const int n0 = __builtin_amdgcn_readfirstlane(w0.n), n1 = __builtin_amdgcn_readfirstlane(wt1.n);
-            const char *k0 = k_ptr(n0), *k1 = k_ptr(n1), *v0 = tile_ptr(vth, n0);
-            ksrc = k_ptr(w1.n);
-            vsrc = tile_ptr(vth, n1);
+            const char *k0 = k_ptr(tile_1 >> 4), *k1 = k_ptr(tile_2 >> 4), *v0 = tile_ptr(vth, tile_1 >> 4);
+            ksrc = k_ptr(tile_3 >> 4);
+            vsrc = tile_ptr(vth, tile_2 >> 4);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k0, 0);
 #pragma unroll
@@ -860,11 +854,6 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         first_unit = false;
         reset_unit_state();
         qv.init(r0, r1, item_class & 3, (item_class & 4) != 0, a);
-        {
-            const int nn = __builtin_amdgcn_readfirstlane(w0.n);
-            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
-            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
-        }
         int next_ticket = 0;
         if (wave8 == 0) next_unit = kUnknown;
         const int k_late = wave8 == 0 && T >= 3 ? T - 3 : INT32_MAX;   // the first wave's steps with something to do for the next unit
@@ -912,7 +901,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
                         if (next_unit >= 0) fetch_record(next_unit);
                     }
                 }
-                phase_x(slot, v_slot, k > 0, std::false_type{});
+                phase_x(slot, v_slot, std::false_type{});
                 __builtin_amdgcn_s_barrier();
                 issue_refill();   // under the second group's head reads, before its chain starts
                 phase_y();
@@ -924,7 +913,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 #pragma nounroll
             for (int k = 0; k < T; ++k) {
                 __builtin_amdgcn_s_barrier();
-                phase_x(slot, v_slot, k > 0, std::true_type{});
+                phase_x(slot, v_slot, std::true_type{});
                 phase_y();
                 v_slot = slot;
                 slot = slot == kRing - 1 ? 0 : slot + 1;

@@ -535,8 +535,29 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
         if (!records) return put(at, items);
         UnitRecord *to = reinterpret_cast<UnitRecord *>(host + at);   // (written once, in order: the pinned buffer is not read)
         for (const PairItem &it : items) {
-            UnitRecord r{it, {}};
-            for (int32_t i = 0; i < 4 && it.list_begin + i < it.list_end; ++i) r.first[i] = ranges[it.list_begin + i];
+            UnitRecord r{it.head_a, it.tile_a, it.head_b, it.tile_b, it.n_tiles, it.classes, it.head_a / gqa_group, it.list_end, {}, 0, 0, 0, 0};
+            int32_t p = it.list_begin, code = 0, end = 0;   // the run, the tile in it
+            if (p < it.list_end) {
+                end = ranges[p].end_states;
+                code = (ranges[p].begin << 4) | (end & 15);
+            }
+            for (int32_t i = 0; i < 4; ++i) {
+                r.tile[i] = code;
+                if (i == 3) break;
+                if (code + 16 < end) {
+                    code += 16;
+                } else if (p + 1 < it.list_end) {
+                    end = ranges[++p].end_states;
+                    code = (ranges[p].begin << 4) | (end & 15);
+                }
+            }
+            r.run_end = end;
+            r.next = p + 2;
+            if (p + 1 < it.list_end) {
+                r.next_begin = ranges[p + 1].begin;
+                r.next_end_states = ranges[p + 1].end_states;
+            }
+            // (a list of less than four tiles: the walker stands at its end, and stays there)
             *to++ = r;
         }
     };

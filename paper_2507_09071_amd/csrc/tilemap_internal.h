@@ -129,12 +129,19 @@ struct PairRange {
     int32_t end_states;  // (end << 4) | (state_a << 2) | state_b
 };
 
-// A unit of the bf16 kernel in the device copy: with the first ranges of its list, so that a workgroup that takes it up asks for
-// its first tiles without waiting for the list.
+// A unit of the bf16 kernel in the device copy, with the beginning of its walk: its first tiles and what follows them are known as
+// soon as the record is.  A tile is named with its states, (n << 4) | states.
 struct UnitRecord {
-    PairItem item;
-    PairRange first[4];   // as many as the list has
+    int32_t head_a, tile_a, head_b, tile_b;
+    int32_t n_tiles, classes;                 // as in PairItem
+    int32_t kv_head;
+    int32_t list_end;                         // of its runs
+    int32_t tile[4];                          // the first four; of a shorter list the last one again
+    int32_t run_end;                          // end_states of the run that tile[3] is in
+    int32_t next_begin, next_end_states;      // the run behind that, if next <= list_end
+    int32_t next;                             // the run behind that one
 };
+static_assert(sizeof(UnitRecord) == 64, "one line; fetched by four lanes");
 
 struct PairPlan {
     int32_t gqa_group = 0;  // the plan depends on which heads share a KV head ...
