@@ -281,9 +281,9 @@ int bs_tilemap_upload(bs_tilemap *tm);
  *   scale    finite and > 0 (1/sqrt(d_k) in the paper)
  *   stream   hipStream_t (NULL = default stream).  The call only enqueues work; the caller
  *            owns q/k/v/out and keeps them alive until the stream has drained.
- * bf16 path: a pre-pass first packs V (transposed) and, where a launch fetches it often, K into per-key-tile
- * blocks in a workspace the map owns (n_kv_heads * n_tiles * head_dim * 256 bytes, n_tiles from bs_tilemap_walked: 2 x the
- * size of K, and as much more as there are compact tiles; and the partial results of work units that are
+ * bf16 path: a pre-pass first packs V (transposed), and the keys of compact tiles, into per-key-tile
+ * blocks in a workspace the map owns (n_kv_heads * (2 n_tiles - seq_len / 64) * head_dim * 128 bytes, n_tiles from
+ * bs_tilemap_walked: the size of V, and twice as much more as there are compact tiles; and the partial results of work units that are
  * cut; taken from the library's block cache or hipMalloc on first use).  Calls with a few rows that see the
  * whole cache read K and V where they are; they and the fp32 path use the workspace for partial results.
  * Calls that share a map share that workspace: the library orders a call after
@@ -317,7 +317,7 @@ int bs_attn_prefill_ex(const void *q, const void *k, const void *v, void *out, b
  * map.  Calls no hipMalloc / hipFree, creates no events, uploads nothing.
  *   tm       must have been prepared: bs_tilemap_prepare(tm, BS_BF16, gqa_group, stream) after the build and
  *            after every bs_tilemap_rebind; BS_EINVAL otherwise (bs_last_error says so)
- *   limit    n_kv_heads * n_k_tiles * head_dim * 256 bytes (packed K plus packed V^T) must fit the scratch:
+ *   limit    n_kv_heads * n_k_tiles * head_dim * 256 bytes (K plus V^T, as if both were packed) must fit the scratch:
  *            BS_EUNSUPPORTED otherwise, nothing launched (96 MiB hold 4 KV heads x 768 key tiles of d = 128:
  *            a 40K-token prompt with its compact tiles).  Partial results of work units that are cut (few rows
  *            behind many keys) go behind the packed tiles or, if there is no room, to a workspace that

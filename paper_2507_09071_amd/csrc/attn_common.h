@@ -98,7 +98,7 @@ __device__ inline uint64_t allowed_keys(const QueryView &qv, int item_class, uin
     }
     // compact tile: slots are free keys, or text keys, in position order
     const int s0 = (n - (n < a.text_tile0 ? a.n_prompt_tiles : a.text_tile0)) * kBlockN;
-    return ((item_class & 1) ? ~0ull : tbits) & bits_between(qv.slot_lo - s0, qv.slot_hi - s0);   // Intra-Image: text keys only
+    return ((item_class & 1) || n >= a.text_tile0 ? ~0ull : tbits) & bits_between(qv.slot_lo - s0, qv.slot_hi - s0);   // Intra-Image: text keys only
 }
 
 // A load from memory that no kernel in flight writes, at a wave-uniform address: through the scalar cache, whatever the

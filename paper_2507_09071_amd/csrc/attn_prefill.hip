@@ -18,7 +18,7 @@
 //    holds 16 keys of ONE query per 32-key block: row max / row sum are in-lane reductions plus
 //    one exchange with the lane 32 apart (v_permlane32_swap);
 //  * O^T = V^T P^T reuses the probabilities, rounded to bf16, as the B operand; V^T comes from a
-//    pre-pass that writes K (where it is fetched often) and V^T per key tile in exactly the layout the LDS reads want;
+//    pre-pass that writes it per key tile in exactly the layout the LDS reads want, K from where the caller has it;
 //  * K and V^T tiles travel global -> LDS with 16-byte LDS-direct loads (no VGPR staging) into a
 //    ring of 4 K + 4 V^T slots shared by the two groups; ONE barrier per key tile, placed so that
 //    on every SIMD one wave runs its matrix phase while the other runs its vector phase;
@@ -192,18 +192,24 @@ __device__ inline void mfma_drain(floatx16 &c0, floatx16 &c1)
 }
 
 
-// LDS tile layouts of the bf16 kernel (written by the pre-pass below and copied verbatim by the
-// kernel's LDS-direct loads; a K tile read in place gets there piece by piece).  Both are "slice-major": everything an MFMA operand read selects
-// at compile time (head-dim slice, key block, key group, channel block) is an immediate offset,
-// and one per-lane base address serves all reads of a tile.
-//   K tile   [D/16 slices t][64 keys][32 B]   32 B = channels 16t..16t+15 of one key, as two
-//            16-byte halves h (channels 16t+8h..+7) stored at half h ^ ((key >> 3) & 1)
+// LDS tile layouts of the bf16 kernel.  V^T is written like that by the pre-pass below and copied verbatim by the kernel's
+// LDS-direct loads; those of K pick it from rows of keys.  Everything an MFMA operand read selects
+// at compile time (head-dim slice, key block, key group, channel block) is an immediate offset
+// from a per-lane base address (two for K).
+//   K tile   [D/32 pairs of slices u][64 keys][64 B]   64 B = channels 32u..32u+31 of one key, as four 16-byte chunks c, stored at
+//            c ^ ((key >> 2) & 3): slices 2u and 2u + 1 lie 32 bytes apart, which of them first alternates, so the odd slices
+//            take a base address of their own
 //   V^T tile [4 key groups g][D channels][32 B]   32 B = the 16 keys of group g of one channel,
 //            as two halves h holding keys 16g + {4h..4h+3, 8+4h..8+4h+3} (the contraction slots
 //            of lane half h), stored at half h ^ ((channel >> 3) & 1)
 // A 128-bit read of 16 consecutive keys (channels) then touches every bank exactly once.
 // The prompt's tiles hold its keys in position order, the compact tiles of a packed map the keys their slots
 // name; slots without a key are zero-filled.
+// Query rows lie in LDS as in memory but for their 16-byte chunks: chunk c of row r is at c ^ chunk_swap(r), rows that share their
+// banks get different ones.
+template <int D>
+__device__ inline int chunk_swap(int r) { return D == 128 ? r & 15 : (r >> 1) & 7; }
+
 __device__ inline int slot_key(const int32_t *__restrict__ compact_keys, int n, int key, int L, int N0)   // -1: no key
 {
     const int s = n * kBlockN + key;
@@ -239,9 +245,8 @@ __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__rest
     }
 }
 
-// K tiles before `in_place` are not packed: the attention kernel reads them where the caller has them.  The others -- the
-// ragged last tile of the prompt and the compact tiles -- then hold their rows one behind the other as well; without
-// tiles read in place (in_place = 0) all are packed in the layout above.
+// The prompt's complete K tiles are not packed: the attention kernel reads them where the caller has them.  The others -- the
+// ragged last tile and the compact tiles, from tile `in_place` = L / 64 on -- hold their rows one behind the other as well.
 template <int D>
 __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restrict__ kp,
                                    const int32_t *__restrict__ compact_keys, int L, int n, int N, int N0, int in_place)
@@ -250,11 +255,7 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     const __bf16 *src = k + (size_t)kvh * L * D;
     __bf16 *dst = kp + ((size_t)kvh * (N - in_place) + n - in_place) * (size_t)(D * kBlockN);
     for (int idx = threadIdx.x; idx < kBlockN * (D / 8); idx += 256) {   // 16 bytes per iteration
-        int key = idx / (D / 8), ch = idx % (D / 8);
-        if (in_place == 0) {
-            key = (idx >> 1) % kBlockN;
-            ch = idx / (2 * kBlockN) * 2 + ((idx & 1) ^ ((key >> 3) & 1));
-        }
+        const int key = idx / (D / 8), ch = idx % (D / 8);
         const int pos = slot_key(compact_keys, n, key, L, N0);
         uint4 val = make_uint4(0, 0, 0, 0);
         if (pos >= 0) val = *reinterpret_cast<const uint4 *>(src + (size_t)pos * D + ch * 8);
@@ -262,7 +263,7 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     }
 }
 
-// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that are not read in place, then workgroups that
+// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that lie nowhere else, then workgroups that
 // bring the work units from a pinned buffer; KV heads), of the
 // tiles that the units of the launch walk.  Bound: HBM, so what counts is what is not packed: a chunk of 300 rows in a window
 // of 1024 needs 21 of a 27K prompt's 429 tiles (three layers: 153 us, 253 with all of them), an all-Dense layer no compact
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
-    int32_t n_k_tiles, int32_t in_place, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
 {
     constexpr int ROW = D * 2;            // bytes per K row in LDS
@@ -348,6 +349,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     const int L = a.L;
 
     const int R = L - a.q_begin;   // query rows per head
+    const int in_place = L / kBlockN;   // complete K tiles of the prompt, read where the caller has them
 
     // ---- state of the work unit in progress (a workgroup takes units from its XCD's queue until
     // ---- the queues are empty; see the unit loop below)
@@ -355,7 +357,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
     const char *kph = nullptr, *vth = nullptr;   // K / packed V^T tiles of the unit's KV head
-    const char *kpackh = nullptr;                // its packed K tiles, as if those before `in_place` were, too
+    const char *kpackh = nullptr;                // its other K tiles (packed), by the same numbers
     bf16x8 qreg[NT];                // Q^T operand: Q[row][16t + 8hl .. +8] for every 16-wide slice t
     QueryView qv;
 
@@ -363,7 +365,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // tile layouts above): key or channel `col`, half hl; slices, blocks and groups are
     // immediate offsets, the ring slot is added per step.
     const uint32_t ring = (uint32_t)(uintptr_t)(lds_void_ptr)lds;
-    const uint32_t kaddr0 = ring + col * 32 + ((hl ^ ((col >> 3) & 1)) << 4);
+    const uint32_t vaddr0 = ring + col * 32 + ((hl ^ ((col >> 3) & 1)) << 4);
+    const uint32_t kaddr0 = ring + col * 64 + ((hl ^ ((col >> 2) & 3)) << 4);   // odd slices: ^ 32
 
     floatx16 o[NDB];
     floatx16 s[2];
@@ -412,15 +415,16 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // (a walker always names a tile that this launch's pre-pass wrote, behind its list the last one)
     auto tile_ptr = [&](const char *base, int n) { return base + (size_t)n * TILE; };
     auto k_ptr = [&](int n) { return (n < in_place ? kph : kpackh) + (size_t)n * TILE; };
-    // The same for a K tile.  If some are read in place their rows lie one behind the other: a lane picks the 16 bytes
-    // that belong at its place, 32 bytes of 32 rows per instruction (the other waves read the rest of the 128-byte
-    // lines at the same time), and the next instruction's slices are 128 bytes further.
-    const uint32_t kdma_key = (wave8 & 1) * 32 + (lane >> 1);
-    const uint32_t kdma_lane_off = in_place ? kdma_key * ROW + (wave8 >> 1) * 32 + (((lane & 1) ^ ((kdma_key >> 3) & 1)) << 4) : dma_lane_off;
-    const int kdma_stride = in_place ? 128 : 8 * 1024;
+    // The same for a K tile, whose rows lie one behind the other: 64 bytes of 16 rows per instruction, as many lookups in the vector
+    // cache as for a copy (the other waves read the rest of the lines at the same time).  A lane picks the 16 bytes that belong
+    // at its place.  So the caller's K is as good as a packed copy at any length; with 32 bytes of 32 rows it was 1-1.6 % slower
+    // where a tile is fetched hundreds of times, and calls of that kind packed K.  (Whole rows per instruction, with chunks
+    // exchanged by key: eight base addresses for the operand reads instead of two, 36K tokens 1.5 % slower.)
+    const uint32_t kdma_key = (wave8 & 3) * 16 + (lane >> 2);
+    const uint32_t kdma_lane_off = kdma_key * ROW + (wave8 >> 2) * 64 + (((lane & 3) ^ ((kdma_key >> 2) & 3)) << 4);
     auto kdma = [&](int r, const char *tile, int slot_byte) __attribute__((always_inline)) {
         const uint32_t dst = ring + slot_byte + wave8 * 1024 + r * 8 * 1024;
-        const char *src = tile + r * kdma_stride;
+        const char *src = tile + r * 128;
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :
                      : "v"(kdma_lane_off), "s"(src), "s"(dst)
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // A batch is four 128-bit operand reads feeding four MFMAs:
     //   PV batch g (D = 128): O^T block db += V^T(db, group g) . P^T(group g), db = 0..3
     //   S  batch b          : head-dim slices 2b, 2b+1 for both 32-key blocks
-    uint32_t kbase = 0, vbase = 0;  // fragment base addresses inside the ring slots of this step
+    uint32_t kbase = 0, kbase_odd = 0, vbase = 0;  // fragment base addresses inside the ring slots of this step
     // one operand read / one MFMA of a batch (element i = 0..3)
     auto read_one = [&](auto tag, auto ic, bf16x8 &dst) __attribute__((always_inline)) {
         using T = decltype(tag);
@@ -439,7 +443,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         if constexpr (T::kind == 1) {
             if constexpr (i < NDB) lds_read_b128<T::idx * (D * 32) + i * 1024>(dst, vbase);   // channel block i
         } else if constexpr (T::kind == 2) {
-            lds_read_b128<(2 * T::idx + (i >> 1)) * 2048 + (i & 1) * 1024>(dst, kbase);        // slice, key block
+            lds_read_b128<T::idx * 4096 + (i & 1) * 2048>(dst, (i >> 1) ? kbase_odd : kbase);   // slice 2 idx + (i >> 1), key block
         }
     };
     auto mul_one = [&](auto tag, auto ic, const bf16x8 &f) __attribute__((always_inline)) {
@@ -467,10 +471,14 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // text / sink key bits of the tile of the coming phase Y (scalar registers)
     uint64_t tb_cur = 0, sb_cur = 0;
     const char *ksrc = nullptr, *vsrc = nullptr;   // tiles of the coming refill ...
-    // The scalar work of a step -- tiles of the refill, the walk, the key bit masks of the coming phase Y -- stands inside
+    // The scalar work of a step -- tiles of the refill, the walk, key bit masks for the coming phase Y -- stands inside
     // phase X, between two MFMA batches, where the wave has issue slots to spare (every MFMA keeps the matrix pipe busy for
     // 32 cycles).  Anything in front of the first MFMA costs its full length: with the walk there the same kernel takes 2 % longer
     // (36K tokens 15573 us, 15220 with it here), with three walkers instead of the one and a look-ahead 3 % on windows.
+    // The masks are asked for only where the item needs them (a sparse class without compact tiles, Intra-Image with mixed ones): a
+    // scalar load in flight is counted together with the operand reads, which are then waited for early.  302K tokens 188.2 ->
+    // 186.5 ms, 36K 15560 -> 15450 us.
+    bool need_bits = false;
     auto advance_walk = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
         ksrc = k_ptr(walk.cur >> 4);
@@ -481,8 +489,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         tile_3 = walk.cur;
         walk.next();
         const int nn = tile_y >> 4;
-        tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
-        sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
+        if (need_bits) {
+            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
+            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     int Sk_dst = 0, Sv_dst = 0;                    // ... and their ring slots
@@ -498,7 +508,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         auto ring = [](int x) { return x >= kRing ? x - kRing : x; };
         Sk_dst = ring(ring(S + 2) + ahead); Sv_dst = ring(S + 1 + ahead);
         kbase = kaddr0 + S * TILE;
-        vbase = kaddr0 + (kRing + Sv) * TILE;
+        kbase_odd = kbase ^ 32;
+        vbase = vaddr0 + (kRing + Sv) * TILE;
         bf16x8 fa[4], fb[4], fc[4];
         if constexpr (NDB < 4) {
 #pragma unroll
@@ -574,7 +585,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // The last step: O += P(T-1) V(T-1), nothing else.
     auto phase_last = [&](int Sv) __attribute__((always_inline)) {
-        vbase = kaddr0 + (kRing + Sv) * TILE;
+        vbase = vaddr0 + (kRing + Sv) * TILE;
         bf16x8 fa[4], fb[4], fc[4];
         if constexpr (NDB < 4) {
 #pragma unroll
@@ -736,7 +747,6 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // one; passes 1590 -> 1554 us (27K tokens, window of 1024, 13 units a workgroup), 1029 -> 1008 (8K tokens, 4 units), d = 64 910 ->
     // 894 (9K).  Overlapping alone, with the operands straight from memory, gained nothing.
     constexpr int kRowsPerLoad = 1024 / ROW, kChunks = ROW / 16, kQueryLoads = 32 / kRowsPerLoad;
-    auto swizzle = [](int r) { return D == 128 ? r & 15 : (r >> 1) & 7; };   // the 16-byte chunks of row r change places: column reads without conflicts
     bool first_unit = true;
     for (;;) {
         const int unit = __builtin_amdgcn_readfirstlane(mailbox[16]);
@@ -764,6 +774,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             T = rec[4];                                           // key tiles in the merged list
             slot_id = rec[5] >> 16;
             item_class = (grp ? rec[5] >> 8 : rec[5]) & 7;        // head classes travel with the unit
+            need_bits = (item_class & 3) != 0 && !((item_class & 4) && ((item_class & 1) || a.text_tile0 < a.n_tiles));
             const int kvh = rec[6];                               // both items share it
             // a tile slot without a row behaves like a row past the end of the prompt (computed on a
             // copy of the last row, never stored)
@@ -824,7 +835,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 #pragma unroll
             for (int j = 0; j < kQueryLoads; ++j) {
                 const int r = j * kRowsPerLoad + ln / kChunks;
-                const uint32_t off = *reinterpret_cast<const uint32_t *>(stage + r * kPatchRow + 132) * ROW + (((ln % kChunks) ^ swizzle(r)) << 4);
+                const uint32_t off = *reinterpret_cast<const uint32_t *>(stage + r * kPatchRow + 132) * ROW + (((ln % kChunks) ^ chunk_swap<D>(r)) << 4);
                 asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                              :
                              : "v"(off), "s"(qh), "s"(ring + query_at + j * 1024)
@@ -864,7 +875,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-            qreg[t] = *(const __attribute__((address_space(3))) bf16x8 *)(uintptr_t)((ring + query_at + col * ROW + ((hl ^ swizzle(col)) << 4)) ^ (t << 5));
+            qreg[t] = *(const __attribute__((address_space(3))) bf16x8 *)(uintptr_t)((ring + query_at + col * ROW + ((hl ^ chunk_swap<D>(col)) << 4)) ^ (t << 5));
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the query rows, the unit's scalar loads (none stays pending into the loop)
 #pragma unroll
         for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(qreg[t]));
@@ -1061,7 +1072,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     a.first_tile = todo_tiles.first[0];
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
-    const int32_t in_place = d->k_in_place;
+    const int32_t in_place = tm->L / bs::kBlockN;
     // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     const size_t n_copy = units && !kv_packed ? units->n : 0;   // comes with the pre-pass
@@ -1089,7 +1100,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     if (e != hipSuccess) return e;
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     e = bs::launch_kernel(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                          d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles, in_place,
+                          d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles,
                           d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
     if (e == hipSuccess && sh && sh->n_cut > 0)
         e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
@@ -1099,22 +1110,6 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
         if (e == hipSuccess) e = queued;
     }
     return e;
-}
-
-// How many key tiles of K the attention kernel reads where the caller has them.  Packing one costs a read and a write of the
-// tile, reading it in place 32-byte pieces on every fetch: 1-1.6 % of the kernel's time on long prompts, which fetch a
-// tile hundreds of times, against 3-10 % of a launch that fetches it ten times (a window, a chunk behind a long cache).
-// The line is drawn at steps per known key tile, not per tile that the pre-pass would pack: that differs where few rows walk
-// a part of the prompt, in a window, and there reading in place is no slower at several times the line.  d = 128, three layers, one of
-// them all-Dense, steps per known tile (per tile walked) of a sparse / Dense layer, in place against packed: 2.5K tokens 30 / 35
-// (36 / 43), 2 % faster; 4K 29 / 52, 0; 6K 41 / 78, -0.8 %; 9K 54 / 114, 0; two heads a group, 12K 15 / 39, 1.6 %, 24K 27 / 78, 0.9 %, 40K
-// 42 / 129, 0.4 %; rows behind 60K-100K keys in windows of 4-8K: 2K rows 1.3 / 2.7 (15 / 30), 1.8 %, 5K 4.3 / 9 (32 / 67), 0.3 %, 8K
-// 7 / 17 (48 / 118), 0.6 %; 5K rows behind 50K 41 / 118, 0.3 %.  36K tokens 182-492: -0.2 %; 302K 377: -1.6 %; d = 64, 5K tokens
-// 20 / 37 (24 / 45), 1.1 %, 9K 34-66, -0.5 to 0.2 %.
-int32_t tiles_in_place(const bs_tilemap *tm, const DeviceMap *d, int n_kv_heads, int32_t head_dim)
-{
-    const int64_t fetches = head_dim == 128 ? 48 : 32;   // (a tile of d = 64 is half as much to pack)
-    return d->n_steps < fetches * n_kv_heads * tm->n_tiles ? tm->L / bs::kBlockN : 0;
 }
 
 // Bytes of the results of cut units (0 without equal shares).
@@ -1149,7 +1144,15 @@ int take_workspace(DeviceMap *d, size_t bytes, hipStream_t st)
 
 size_t bf16_pack_bytes(int32_t n_tiles, int n_kv_heads, int head_dim)
 {
-    return (size_t)n_kv_heads * n_tiles * (size_t)head_dim * bs::kBlockN * 2;   // one of the two halves (K, V^T)
+    return (size_t)n_kv_heads * n_tiles * (size_t)head_dim * bs::kBlockN * 2;   // of K or V^T
+}
+
+// What the pre-pass writes: the K tiles that are not read in place, then all V^T tiles.
+struct PackBytes { size_t k, all; };
+PackBytes bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
+{
+    const size_t k = bf16_pack_bytes(tm->n_tiles - tm->L / bs::kBlockN, n_kv_heads, head_dim);
+    return {k, k + bf16_pack_bytes(tm->n_tiles, n_kv_heads, head_dim)};
 }
 
 }  // namespace
@@ -1187,7 +1190,7 @@ extern "C" int bs_tilemap_prepare(bs_tilemap *tm, int32_t dtype, int32_t gqa_gro
             const int n_kv_heads = tm->n_q_heads / gqa_group;
             const size_t cut = cut_bytes(*d->shares_for(n_cus), 128);
             if (2 * bf16_pack_bytes(tm->N, n_kv_heads, 64) <= kStaticScratchBytes &&
-                2 * bf16_pack_bytes(tm->n_tiles, n_kv_heads, 128) + cut > kStaticScratchBytes) rc = take_workspace(d, cut, st);
+                bf16_pack_bytes(tm, n_kv_heads, 128).all + cut > kStaticScratchBytes) rc = take_workspace(d, cut, st);
         }
     } else {   // for either head dimension, and the workspace of the larger plan
         const int32_t wgs128 = n_cus * bs::f32_wgs_per_cu(128), wgs64 = n_cus * bs::f32_wgs_per_cu(64);
@@ -1258,20 +1261,18 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         d->rows_epoch = tm->class_epoch;
         d->rows_G = gqa_group;
     } else if (dtype == BS_BF16) {
-        // packed K tiles, then packed V^T tiles
         const int n_kv_heads = n_q_heads / gqa_group;
-        const size_t pack_bytes = bf16_pack_bytes(tm->n_tiles, n_kv_heads, head_dim);
+        const PackBytes pack = bf16_pack_bytes(tm, n_kv_heads, head_dim);
         const bs::ShareSet &shares = *d->shares_for(n_wgs);
         const bs::ShareSet *const sh = shares.n_shares > 0 ? &shares : nullptr;
         const void *const old_workspace = d->vt_buf;
-        if ((rc = take_workspace(d, 2 * pack_bytes + cut_bytes(shares, head_dim), st)) != BS_OK) return give_up(rc);
+        if ((rc = take_workspace(d, pack.all + cut_bytes(shares, head_dim), st)) != BS_OK) return give_up(rc);
         const bool packed = kv_packed && *kv_packed && d->vt_buf == old_workspace && d->bind_epoch != bound;
-        if (!packed) d->k_in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
-        float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + 2 * pack_bytes);
+        float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + pack.all);
         // (a caller with several bindings of the map packs for all of them)
         const TileRuns todo = tiles_read(tm, kv_packed != nullptr);
-        e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start)
-                            : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack_bytes, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start)
+                            : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
         if (e != hipSuccess) {
             d->bind_kind = bs::kBindNone;   // the units may not have arrived
             if (kv_packed) *kv_packed = false;
@@ -1314,7 +1315,7 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     const bool rows_bound = d->rows_G == gqa_group && d->rows_epoch == tm->class_epoch;
     if (!units_bound && !rows_bound) return not_prepared();
     const int n_kv_heads = n_q_heads / gqa_group;
-    const size_t pack_bytes = bf16_pack_bytes(tm->n_tiles, n_kv_heads, head_dim);
+    const PackBytes pack = bf16_pack_bytes(tm, n_kv_heads, head_dim);
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return bs::fail_hip(e, "hipGetDevice");
@@ -1324,16 +1325,10 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     if ((rc = device_setup(dev, &ws, &n_cus)) != BS_OK) return rc;   // looks the address up on the first call per device
     const bs::RowsPlan rows = bs::plan_rows(tm, BS_BF16, gqa_group, head_dim, n_cus);
     if (!units_bound && !rows.use) return not_prepared();
-    // (one limit for all calls and maps: the few-row kernel would need less, and a map whose kernels know more tiles than it
-    // publishes has room for those if K is read in place)
+    // (one limit for all calls and maps, on the published tiles, K and V^T: the call needs less -- the few-row kernel, K tiles read
+    // in place -- and with at most half as many more tiles that only the kernels know it fits all the same)
     const size_t limit_bytes = 2 * bf16_pack_bytes(tm->N, n_kv_heads, head_dim);
-    int32_t in_place = tiles_in_place(tm, d, n_kv_heads, head_dim);
-    size_t k_bytes = pack_bytes;
-    if (2 * pack_bytes > kStaticScratchBytes) {
-        in_place = tm->L / bs::kBlockN;
-        k_bytes = bf16_pack_bytes(tm->n_tiles - in_place, n_kv_heads, head_dim);
-    }
-    if (std::max(rows.workspace, limit_bytes) > kStaticScratchBytes || k_bytes + pack_bytes > kStaticScratchBytes) {
+    if (std::max(rows.workspace, limit_bytes) > kStaticScratchBytes || pack.all > kStaticScratchBytes) {
         snprintf(bs::g_last_error, sizeof bs::g_last_error,
                  "bs_attn_prefill_static: packed K / V^T tiles need %zu bytes, the static scratch holds %zu "
                  "(n_kv_heads * key tiles * head_dim * 256 bytes); use bs_attn_prefill", limit_bytes, kStaticScratchBytes);
@@ -1346,18 +1341,17 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // bs_tilemap_prepare took (too small only if a call at head dimension 64 made the binding: then nothing is cut)
     const bs::ShareSet *sh = d->shares_for(n_cus);
     if (sh && sh->n_shares == 0) sh = nullptr;
-    float *cut = reinterpret_cast<float *>(static_cast<char *>(ws) + k_bytes + pack_bytes);
-    if (sh && k_bytes + pack_bytes + cut_bytes(*sh, head_dim) > kStaticScratchBytes) {
+    float *cut = reinterpret_cast<float *>(static_cast<char *>(ws) + pack.all);
+    if (sh && pack.all + cut_bytes(*sh, head_dim) > kStaticScratchBytes) {
         cut = static_cast<float *>(d->vt_buf);
         if (cut_bytes(*sh, head_dim) > d->vt_bytes) sh = nullptr;
     }
-    d->k_in_place = in_place;
     // the pre-pass (the few-row kernel) writes all of the scratch that is read after it: nothing of the previous
     // call's contents is
     e = hipSuccess;
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) e = launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
-    else e = launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, k_bytes, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    else if (head_dim == 128) e = launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    else e = launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);

@@ -100,7 +100,6 @@ struct DeviceMap {
     // Workspaces that a larger one took the place of, kept as long as the map: a call of it that was captured into a graph
     // still writes its partial results there when the graph is replayed.
     std::vector<std::pair<void *, size_t>> outgrown;
-    int32_t k_in_place = 0;               // key tiles of K that the last call read in place (see pack_k_tile)
     hipStream_t last_stream = nullptr;    // stream of the most recent upload / launch (compared, never used)
     std::shared_ptr<EventHolder> last_use;   // recorded after the most recent upload / launch
 
