@@ -42,6 +42,7 @@ struct KernelArgs {
     int32_t window, bidir;
     int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
 };
+
 // What the lane's query may see (paper Sec. 3.2), in a form that is cheap to apply per tile: intervals of positions and of
 // compact slots.  With compact tiles (see the tile-map builder) an image query of a sparse class reads the free keys --
 // text and sink keys -- from there and only own-image keys from the prompt's tiles, so that every allowed pair is
@@ -111,6 +112,18 @@ __device__ inline T scalar_load(const U *p)
 }
 typedef int intx2 __attribute__((ext_vector_type(2)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
+
+// The row in slot j of query tile m of `head`: its record, its head, whether there is one (the record of a head's own tile says
+// so as well).  A stacked tile holds the rows of a group's heads, `head` being the first of them.
+struct RowRef { int32_t record, head; bool there; };
+__device__ inline RowRef row_of(const StackedRows *rows, bool stacked, int G, int head, int m, int j)
+{
+    if (!stacked) return {m * kBlockM + j, head, true};
+    const intx4 r = scalar_load<intx4>(reinterpret_cast<const intx4 *>(rows));   // first_tile, n_text_tiles, n_text_rows, n_other_rows
+    const bool text = m - r.x < r.y;
+    const int s = (m - r.x - (text ? 0 : r.y)) * kBlockM + j, t = s / G, n = text ? r.z : r.w;
+    return {(text ? scalar_load<int>(&rows->text_slot0) : 0) + min(t, n - 1), head + s - t * G, t < n};
+}
 
 // Walks the merged key-tile list of a work unit from its record on (bf16).  The run behind the present one is there before it
 // is needed: a walk that asked for it at its turn would wait for the scalar cache, and with it for the operand reads in flight.

@@ -250,7 +250,7 @@ static void launch_f32_dim(const KernelArgs &a, const DeviceMap *d, const ShareS
                        shares ? sh.off : nullptr, cut_results);
     if (shares && sh.n_cut > 0)
         hipLaunchKernelGGL((merge_cut_items<D, 1, float>), dim3((unsigned)sh.n_cut, 4, D / 32), dim3(64), 0, st, a, sh.cut_items,
-                           d->rows, cut_results);
+                           d->rows, static_cast<const StackedRows *>(nullptr), cut_results);
 }
 
 void launch_f32(const KernelArgs &a, const DeviceMap *d, const ShareSet &shares, void *workspace, int32_t head_dim, hipStream_t st)

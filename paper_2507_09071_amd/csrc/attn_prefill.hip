@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
     int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
-    const int32_t *__restrict__ share_off, float *__restrict__ cut_results)
+    const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
 {
     constexpr int ROW = D * 2;            // bytes per K row in LDS
     constexpr int TILE = kBlockN * ROW;   // bytes per K or V^T tile
@@ -761,6 +761,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         const int done_head = head, done_slot = slot_id;
         const bool done_item = have_item && !first_unit;
         int4 r0, r1;
+        RowRef ref;
         int rec[16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -778,9 +779,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             const int kvh = rec[6];                               // both items share it
             // a tile slot without a row behaves like a row past the end of the prompt (computed on a
             // copy of the last row, never stored)
-            const int row_slot = max(grp ? rec[3] : rec[1], 0) * kBlockM + (w8 & 3) * 32 + col;
-            r0 = map_rows[2 * row_slot];
-            r1 = map_rows[2 * row_slot + 1];
+            ref = row_of(stacked, ((grp ? rec[5] >> 8 : rec[5]) & 8) != 0, a.G, max(head, 0), max(grp ? rec[3] : rec[1], 0), (w8 & 3) * 32 + col);
+            r0 = map_rows[2 * ref.record];
+            r1 = map_rows[2 * ref.record + 1];
             // one TILE-byte block per key tile
             kph = reinterpret_cast<const char *>(a.k) + (size_t)kvh * L * ROW;
             kpackh = reinterpret_cast<const char *>(kp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
@@ -824,10 +825,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             else store_half(0);
         }
         if (more) {
-            const int row = r0.x;
-            out_row = row < L ? max(head, 0) * R + (row - a.q_begin) : -1;
+            const int row = ref.there ? r0.x : L;
+            out_row = row < L ? ref.head * R + (row - a.q_begin) : -1;
             // rows past the end compute on a copy and are not stored
-            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 132) = min(row, L - 1) - a.q_begin;
+            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 132) = (ref.head - max(head, 0)) * R + min(row, L - 1) - a.q_begin;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1101,10 +1102,10 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     e = bs::launch_kernel(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
                           d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles,
-                          d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, cut_results);
+                          d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, d->stacked, cut_results);
     if (e == hipSuccess && sh && sh->n_cut > 0)
         e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
-                              d->rows, cut_results);
+                              d->rows, d->stacked, cut_results);
     if (n_copy) {   // (an event between the two kernels would hold the second one up)
         const hipError_t queued = bs::staging_queued(units->staging, st);
         if (e == hipSuccess) e = queued;

@@ -30,7 +30,7 @@ __device__ inline void store_cut_item(float *item, const floatx16 (&o)[D / 32], 
 // keep a thousand waves reading; bf16 rows leave through LDS as 16-byte pieces.
 template <int D, int ITEMS, typename OUT>
 __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *__restrict__ cut_items,
-                                                      const int4 *__restrict__ map_rows,
+                                                      const int4 *__restrict__ map_rows, const StackedRows *__restrict__ stacked,
                                                       const float *__restrict__ cut_results)
 {
     constexpr int NDB = D / 32, kStageRow = 64 + 16;   // 32 channels, then the row's position
@@ -43,9 +43,12 @@ __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *
     const float2 *ml = reinterpret_cast<const float2 *>(slot + kBlockM * D) + wave * 32 + col;
     const floatx4 *src = reinterpret_cast<const floatx4 *>(slot) + (wave * NDB + db) * 256 + lane;
     constexpr size_t kNext = (size_t)ITEMS * kCutItemFloats<D>;
-    if constexpr (std::is_same<OUT, __bf16>::value) if (hl == 0) {
-        *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = map_rows[2 * (m * kBlockM + wave * 32 + col)].x;
-    }
+    auto out_row = [&] {   // where the lane's row goes; -1: nowhere
+        const RowRef ref = row_of(stacked, stacked && m >= stacked->first_tile, a.G, head, m, wave * 32 + col);
+        const int pos = map_rows[2 * ref.record].x;
+        return ref.there && pos < a.L ? ref.head * R + (pos - a.q_begin) : -1;
+    };
+    if constexpr (std::is_same<OUT, __bf16>::value) if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kStageRow + 64) = out_row();
 
     // one pass over the parts, with the reference point moving as in the attention loop
     float mx = -INFINITY, l = 0.f;
@@ -70,11 +73,11 @@ __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if constexpr (!std::is_same<OUT, __bf16>::value) {
-        const int pos = map_rows[2 * (m * kBlockM + wave * 32 + col)].x;
-        if (pos < a.L)
+        const int to = out_row();
+        if (to >= 0)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<floatx4 *>(static_cast<float *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D + 32 * db + 8 * g + 4 * hl) = acc[g] * inv;
+                *reinterpret_cast<floatx4 *>(static_cast<float *>(a.out) + (size_t)to * D + 32 * db + 8 * g + 4 * hl) = acc[g] * inv;
         return;
     }
 #pragma unroll
@@ -89,11 +92,8 @@ __global__ __launch_bounds__(64) void merge_cut_items(KernelArgs a, const int4 *
     for (int j = 0; j < 2; ++j) {
         const int r = 16 * j + (lane >> 2), chunk = lane & 3;
         const uint4 piece = *reinterpret_cast<const uint4 *>(stage + r * kStageRow + chunk * 16);
-        const int32_t pos = *reinterpret_cast<const int32_t *>(stage + r * kStageRow + 64);
-        if (pos < a.L) {
-            __bf16 *orow = reinterpret_cast<__bf16 *>(a.out) + ((size_t)head * R + (pos - a.q_begin)) * D;
-            *reinterpret_cast<uint4 *>(orow + 32 * db + chunk * 8) = piece;
-        }
+        const int32_t to = *reinterpret_cast<const int32_t *>(stage + r * kStageRow + 64);
+        if (to >= 0) *reinterpret_cast<uint4 *>(reinterpret_cast<__bf16 *>(a.out) + (size_t)to * D + 32 * db + chunk * 8) = piece;
     }
 }
 

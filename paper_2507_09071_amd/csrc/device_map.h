@@ -93,6 +93,7 @@ struct DeviceMap {
     uint64_t rows_epoch = 0;              // class_epoch and group size of the last call that the few-row kernel took: it needs
     int32_t rows_G = 0;                   // no units, and prepares the map for the static entry as the upload of units does
     int64_t n_steps = 0;                  // key-tile steps of the work units
+    const StackedRows *stacked = nullptr; // which rows the stacked tiles among the units hold (bf16)
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
     // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
     void *vt_buf = nullptr;

@@ -506,7 +506,8 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     const PairPlan &plan = kind == kBindPairPlan ? tm->pairs : tm->solo;
     if (plan.ranges.size() >= (size_t)INT32_MAX) return BS_EUNSUPPORTED;
     const SharePlan *const share_plans[2] = {&tm->shares, &too};
-    // the parts of the block, one after the other: units, their ranges, queue offsets [9] and counters [8 at + 64 B]; then
+    // the parts of the block, one after the other: units, their ranges, queue offsets [9], counters [8 at + 64 B] and the rows of
+    // stacked tiles [at + 128 B]; then
     // equal shares: parts, their ranges, share offsets, queue offsets, cut items
     size_t bytes = 0;
     auto section = [&](size_t n) { const size_t at = bytes; bytes = align256(bytes + n); return at; };
@@ -565,6 +566,8 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     put(off_b, plan.ranges);
     std::memset(host + off_q, 0, 256);
     std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
+    const StackedRows stacked = {tm->M, tm->stacked.n_text(), tm->geo.n_text_rows(), tm->geo.n_other_rows(), tm->geo.m_img * 128};
+    std::memcpy(host + off_q + 128, &stacked, sizeof stacked);
     for (int i = 0; i < 2; ++i) {
         const SharePlan &s = *share_plans[i];
         put_units(off_s[i][0], s.parts, s.ranges);
@@ -607,6 +610,7 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     for (const PairItem &it : plan.items) d->n_steps += it.n_tiles;
     d->queue_off = reinterpret_cast<const int32_t *>(b + off_q);
     d->queue_ctr = reinterpret_cast<int32_t *>(b + off_q + 64);
+    d->stacked = reinterpret_cast<const StackedRows *>(b + off_q + 128);
     for (int i = 0; i < 2; ++i) {
         const SharePlan &s = *share_plans[i];
         ShareSet &to = d->shares[i];

@@ -811,23 +811,33 @@ int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, 
         runs.push_back({(int32_t)r0, (int32_t)r1});
         return (int32_t)(r1 - r0);
     }
+    const bool text = m >= m_img;
+    const int32_t first = (text ? m - m_img : m) * bm;
+    const int32_t last = (int32_t)std::min<int64_t>((int64_t)first + bm, text ? n_text_rows() : n_img_rows);
+    row_runs(text, first, last, runs);
+    return last - first;
+}
+
+void bs::PromptGeometry::row_runs(bool text, int32_t first, int32_t last, std::vector<std::pair<int32_t, int32_t>> &runs) const
+{
     auto add = [&](int32_t a, int32_t b) {
         if (b <= a) return;
         if (!runs.empty() && runs.back().second == a) runs.back().second = b;
         else runs.push_back({a, b});
     };
+    if (!regrouped) return add(q_begin + first, q_begin + last);
     const int32_t text0 = n_text(q_begin), img0 = q_begin - text0;   // text / image tokens before the first row
-    if (m < m_img) {   // image rows j0 .. j1 - 1 of all image tokens
-        const int32_t j0 = img0 + m * bm, j1 = img0 + (int32_t)std::min<int64_t>((int64_t)(m + 1) * bm, n_img_rows);
+    if (!text) {   // image rows j0 .. j1 - 1 of all image tokens
+        const int32_t j0 = img0 + first, j1 = img0 + last;
         auto it = std::upper_bound(spans.begin(), spans.begin() + n_spans, j0, [](int32_t j, const SpanInfo &s) { return j < s.start - s.text_before; }) - 1;
         for (int32_t j = j0; j < j1; ++it) {
             const int32_t a = it->start + (j - (it->start - it->text_before)), b = std::min(it->end, a + (j1 - j));
             add(a, b);
             j += b - a;
         }
-        return j1 - j0;
+        return;
     }
-    const int32_t t0 = text0 + (m - m_img) * bm, t1 = (int32_t)std::min<int64_t>((int64_t)t0 + bm, spans[n_spans].text_before);
+    const int32_t t0 = text0 + first, t1 = text0 + last;
     auto it = std::upper_bound(spans.begin(), spans.end(), t0, [](int32_t t, const SpanInfo &s) { return t < s.text_before; });
     for (int32_t t = t0; t < t1; ++it) {   // the text before *it
         if (it->text_before <= t) continue;
@@ -835,7 +845,6 @@ int32_t bs::PromptGeometry::tile_runs(int32_t m, std::vector<std::pair<int32_t, 
         add(a, b);
         t += b - a;
     }
-    return t1 - t0;
 }
 
 void bs::row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, int32_t *img_lo, int32_t *img_hi)
@@ -885,6 +894,91 @@ void bs_plan_solo(bs_tilemap *tm)
     plan.epoch = tm->class_epoch;
 }
 
+// The lists of the stacked tiles (see StackedTiles) of the text rows or of the others: a row sees the keys [lo(i), e(i)] of the dense
+// mask, both ends grow with the position, so the rows of a tile share [lo(last), e(first)] and see [lo, e] of every run.
+static void build_stacked(const bs_tilemap *tm, int32_t G, bool text, ClassLists &out)
+{
+    const PromptGeometry &P = tm->geo;
+    const int64_t n_rows = text ? P.n_text_rows() : P.n_other_rows(), n_slots = n_rows * G;
+    const int32_t n_tiles = (int32_t)((n_slots + P.bm - 1) / P.bm);
+    out.row_ptr.assign(n_tiles + 1, 0);
+    out.row_tiles.assign(n_tiles, 0);
+    out.compact.assign(n_tiles, 0);
+    std::vector<std::pair<int32_t, int32_t>> runs;
+    int32_t first, last, unused_lo, unused_hi;
+    for (int32_t j = 0; j < n_tiles; ++j) {
+        const int32_t t0 = (int32_t)((int64_t)j * P.bm / G), t1 = (int32_t)(std::min<int64_t>((int64_t)(j + 1) * P.bm, n_slots) - 1) / G;
+        runs.clear();
+        P.row_runs(text, t0, t1 + 1, runs);
+        bs::row_bounds(tm, runs.back().second - 1, &first, &last, &unused_lo, &unused_hi);
+        const int32_t full_from = (first + P.bn - 1) / P.bn;
+        bs::row_bounds(tm, runs.front().first, &first, &last, &unused_lo, &unused_hi);
+        const int32_t full_end = std::max(full_from, (last + 1) / P.bn);
+        auto emit = [&](int32_t b, int32_t e, bool full) {
+            if (e <= b) return;
+            out.row_tiles[j] += e - b;
+            if ((int64_t)out.ranges.size() > out.row_ptr[j] && out.ranges.back().end() == b && out.ranges.back().full() == full) out.ranges.back().end_state = (e << 1) | (int32_t)full;
+            else out.ranges.push_back({b, (e << 1) | (int32_t)full});
+        };
+        int32_t done = 0;   // tiles before this one are decided
+        for (const auto &r : runs) {
+            bs::row_bounds(tm, r.first, &first, &last, &unused_lo, &unused_hi);
+            const int32_t b = std::max(done, first / P.bn);
+            bs::row_bounds(tm, r.second - 1, &first, &last, &unused_lo, &unused_hi);
+            const int32_t e = last / P.bn + 1;
+            if (e <= b) continue;
+            const int32_t f0 = std::min(std::max(full_from, b), e), f1 = std::min(std::max(full_end, f0), e);
+            emit(b, f0, false);
+            emit(f0, f1, true);
+            emit(f1, e, false);
+            done = e;
+        }
+        out.row_ptr[j + 1] = (int64_t)out.ranges.size();
+    }
+}
+
+// Steps of units of two neighbouring tiles.
+static int64_t unit_steps(const ClassLists &lists)
+{
+    int64_t steps = 0;
+    std::vector<TileRange> both;
+    for (size_t j = 0; j < lists.row_tiles.size(); j += 2) {
+        const bool pair = j + 1 < lists.row_tiles.size();
+        const auto at = [&](size_t i) { return std::vector<TileRange>(lists.ranges.begin() + lists.row_ptr[i], lists.ranges.begin() + lists.row_ptr[i + 1]); };
+        if (pair) combine_runs(at(j), at(j + 1), both);
+        else both = at(j);
+        for (const TileRange &r : both) steps += r.end() - r.begin;
+    }
+    return steps;
+}
+
+// Decides which rows are stacked in groups of G heads.  Without it two heads share a unit at the same 128 rows, and what is lost is
+// the last, partly filled tile of every head and the keys that only some of the 128 rows see.  Text rows are few: 37 rows at the
+// end of a 36K prompt are a tile of 577 steps for every pair of heads, stacked in groups of seven 1 unit instead of 3.5.
+// A unit holds 256 rows either way, so groups of two gain nothing.  Stacked where that saves a thirtieth of the steps of these rows:
+// below, units of two kinds side by side share fewer tiles.  (The rows' distance from the first head's has to fit an offset
+// of 32 bits in the kernel.)
+static void plan_stacked(bs_tilemap *tm, int32_t G)
+{
+    bs::StackedTiles &st = tm->stacked;
+    if (st.gqa_group == G) return;
+    st = bs::StackedTiles();
+    const PromptGeometry &P = tm->geo;
+    if (G >= 3 && (int64_t)G * (tm->L - tm->q_begin) * 256 < INT32_MAX) {
+        const int32_t m_other = P.regrouped ? P.m_img : tm->M;
+        const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
+        for (bool text : {true, false}) {
+            if (text && !P.regrouped) continue;
+            int64_t apart = 0;   // steps of one head; two heads walk them together
+            for (int32_t m = text ? m_other : 0; m < (text ? tm->M : m_other); ++m) apart += dense[m];
+            ClassLists &lists = text ? st.text : st.other;
+            build_stacked(tm, G, text, lists);
+            if (unit_steps(lists) * 60 > apart * G * 29) lists = ClassLists();
+        }
+    }
+    st.gqa_group = G;
+}
+
 extern "C" int bs_tilemap_rebind(bs_tilemap *tm, const uint8_t *head_class, int32_t n_q_heads)
 {
     if (!tm || !head_class || n_q_heads <= 0) return BS_EINVAL;
@@ -920,14 +1014,19 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     if (plan.gqa_group == G && plan.epoch == tm->class_epoch) return;
     plan.ranges.clear();
     plan.items.clear();
-    const int32_t M = tm->M, H = tm->n_q_heads;
+    plan_stacked(tm, G);
+    const bs::StackedTiles &st = tm->stacked;
+    const int32_t n_text_tiles = st.n_text(), H = tm->n_q_heads;
+    const int32_t M = n_text_tiles > 0 ? tm->geo.m_img : tm->M;   // tiles that are walked head by head
+    constexpr int kText = 4, kOther = 5;                          // stacked tiles, next to the classes
+    auto lists_of = [&](int c) -> const ClassLists & { return c == kText ? st.text : (c == kOther ? st.other : tm->walked(c)); };
 
     // merged list of (class ca, row ma) and (class cb, row mb); cb < 0: item A alone
     struct Span2 { int32_t begin, end, tiles; };
     bool count_only = false;
     auto merged = [&](int ca, int32_t ma, int cb, int32_t mb) {
-        const ClassLists &la = tm->walked(ca);
-        const ClassLists &lb = tm->walked(cb < 0 ? ca : cb);
+        const ClassLists &la = lists_of(ca);
+        const ClassLists &lb = lists_of(cb < 0 ? ca : cb);
         int64_t pa = la.row_ptr[ma], ea = la.row_ptr[ma + 1];
         int64_t pb = cb < 0 ? 0 : lb.row_ptr[mb], eb = cb < 0 ? 0 : lb.row_ptr[mb + 1];
         Span2 out{(int32_t)plan.ranges.size(), 0, 0};
@@ -1026,8 +1125,24 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         return p;
     };
 
+    std::vector<Span2> cache_stacked[6];
+    auto push_stacked = [&](int32_t kv, int c, int32_t first_id) {   // neighbouring tiles in pairs
+        const int32_t n = (int32_t)lists_of(c).row_tiles.size();
+        for (int32_t j = 0; j < n; j += 2) {
+            const bool pair = j + 1 < n;
+            const Span2 &sp = cached(cache_stacked[c], j / 2, (n + 1) / 2, [&] { return pair ? merged(c, j, c, j + 1) : merged(c, j, -1, 0); });
+            plan.items.push_back({kv * G, first_id + j, pair ? kv * G : -1, pair ? first_id + j + 1 : 0, sp.begin, sp.end, sp.tiles, 0});
+        }
+    };
     std::vector<int32_t> byclass[4], rest;
     for (int32_t kv = 0; kv < H / G; ++kv) {
+        if (n_text_tiles > 0) push_stacked(kv, kText, tm->M);
+        // (without stacked text rows these are among the tiles of every head)
+        const bool all_dense = std::all_of(tm->head_class.begin() + kv * G, tm->head_class.begin() + (kv + 1) * G, [](uint8_t c) { return c == BS_DENSE; });
+        if (all_dense && st.n_other() > 0 && (n_text_tiles > 0 || !tm->geo.regrouped)) {
+            push_stacked(kv, kOther, tm->M + n_text_tiles);
+            continue;
+        }
         for (int c = 0; c < 4; ++c) byclass[c].clear();
         for (int32_t h = kv * G; h < (kv + 1) * G; ++h) byclass[tm->head_class[h]].push_back(h);
         rest.clear();
@@ -1128,7 +1243,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         }
         plan.queue_off[kXcds] = (int32_t)plan.items.size();
     }
-    auto item_class = [&](int32_t head, int32_t tile) { return tm->head_class[head] | tm->walked(tm->head_class[head]).compact[tile] << 2; };
+    auto item_class = [&](int32_t head, int32_t tile) { return tile >= tm->M ? BS_DENSE | 8 : tm->head_class[head] | tm->walked(tm->head_class[head]).compact[tile] << 2; };
     for (bs::PairItem &it : plan.items)
         it.classes = item_class(it.head_a, it.tile_a) | (it.head_b >= 0 ? item_class(it.head_b, it.tile_b) << 8 : 0);
     plan.gqa_group = G;
@@ -1339,14 +1454,51 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
         // check the plan against the per-class lists it was derived from
         const bs::PairPlan &plan = tm->pairs;
         std::vector<uint8_t> want(tm->n_tiles), got_a(tm->n_tiles), got_b(tm->n_tiles);
-        std::vector<int32_t> seen((size_t)tm->n_q_heads * tm->M, 0);
+        const bs::StackedTiles &st = tm->stacked;
+        const int32_t M = tm->M + st.n_text() + st.n_other();   // ids of query tiles
+        std::vector<int32_t> seen((size_t)tm->n_q_heads * M, 0);
+        // the states of an item: from the lists of its class, of a stacked tile from what its rows see one by one
+        std::vector<std::vector<uint8_t>> stacked_states(M - tm->M);
+        auto expected = [&](int32_t head, int32_t tile) {
+            if (tile < tm->M) return expand_states(tm->walked(tm->head_class[head]), tile, want);
+            std::vector<uint8_t> &states = stacked_states[tile - tm->M];
+            if (states.empty()) {
+                const bool text = tile - tm->M < st.n_text();
+                const int32_t n_rows = text ? tm->geo.n_text_rows() : tm->geo.n_other_rows();
+                const int64_t s0 = (int64_t)(tile - tm->M - (text ? 0 : st.n_text())) * tm->bm;
+                std::vector<std::pair<int32_t, int32_t>> runs;
+                tm->geo.row_runs(text, (int32_t)(s0 / gqa_group), (int32_t)std::min<int64_t>(n_rows, (s0 + tm->bm - 1) / gqa_group + 1), runs);
+                states.assign(tm->n_tiles, 2);
+                std::vector<uint8_t> any(tm->n_tiles, 0);
+                for (const auto &r : runs)
+                    for (int32_t i = r.first; i < r.second; ++i) {
+                        int32_t lo, hi, unused_lo, unused_hi;
+                        bs::row_bounds(tm, i, &lo, &hi, &unused_lo, &unused_hi);
+                        for (int32_t n = 0; n < tm->n_tiles; ++n) {
+                            const bool seen_some = n < tm->N0 && lo < (n + 1) * tm->bn && hi >= n * tm->bn;
+                            any[n] |= (uint8_t)seen_some;
+                            if (!seen_some || lo > n * tm->bn || hi < (n + 1) * tm->bn - 1) states[n] = 1;
+                        }
+                    }
+                for (int32_t n = 0; n < tm->n_tiles; ++n) states[n] = any[n] ? states[n] : 0;
+            }
+            want = states;
+        };
         int64_t tiles = 0, skips = 0;
         for (const bs::PairItem &it : plan.items) {
-            if (it.head_a < 0 || it.head_a >= tm->n_q_heads || it.tile_a < 0 || it.tile_a >= tm->M) return BS_EINVAL;
-            if (it.head_b >= tm->n_q_heads || (it.head_b >= 0 && (it.tile_b < 0 || it.tile_b >= tm->M))) return BS_EINVAL;
+            if (it.head_a < 0 || it.head_a >= tm->n_q_heads || it.tile_a < 0 || it.tile_a >= M) return BS_EINVAL;
+            if (it.head_b >= tm->n_q_heads || (it.head_b >= 0 && (it.tile_b < 0 || it.tile_b >= M))) return BS_EINVAL;
             if (it.head_b >= 0 && it.head_b / gqa_group != it.head_a / gqa_group) return BS_EINVAL;
-            ++seen[(size_t)it.head_a * tm->M + it.tile_a];
-            if (it.head_b >= 0) ++seen[(size_t)it.head_b * tm->M + it.tile_b];
+            // (a stacked tile stands under the first head of its group; those of the other rows only if all its heads are Dense)
+            for (int i = 0; i < 2; ++i) {
+                const int32_t head = i ? it.head_b : it.head_a, tile = i ? it.tile_b : it.tile_a;
+                if (head < 0 || tile < tm->M) continue;
+                if (head % gqa_group != 0) return BS_EINVAL;
+                for (int32_t h = head; h < head + gqa_group; ++h)
+                    if (tile >= tm->M + st.n_text() && tm->head_class[h] != BS_DENSE) return BS_EINVAL;
+            }
+            ++seen[(size_t)it.head_a * M + it.tile_a];
+            if (it.head_b >= 0) ++seen[(size_t)it.head_b * M + it.tile_b];
             std::fill(got_a.begin(), got_a.end(), 0);
             std::fill(got_b.begin(), got_b.end(), 0);
             bool in_prompt = false;   // the compact tiles come first, then the prompt's, both in order
@@ -1366,15 +1518,27 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             }
             if (n_tiles != it.n_tiles) return BS_EINVAL;
             tiles += n_tiles;
-            expand_states(tm->walked(tm->head_class[it.head_a]), it.tile_a, want);
+            expected(it.head_a, it.tile_a);
             if (want != got_a) return BS_EINVAL;
             if (it.head_b >= 0) {
-                expand_states(tm->walked(tm->head_class[it.head_b]), it.tile_b, want);
+                expected(it.head_b, it.tile_b);
                 if (want != got_b) return BS_EINVAL;
             }
         }
-        for (int32_t v : seen)
-            if (v != 1) return BS_EINVAL;  // every (head, query tile) exactly once
+        // every row of every head exactly once: in its head's tile or in a stacked one of its group
+        const int32_t m_text = tm->geo.regrouped ? tm->geo.m_img : tm->M;
+        for (int32_t h = 0; h < tm->n_q_heads; ++h) {
+            const int32_t *own = seen.data() + (size_t)h * M, *group = seen.data() + (size_t)(h - h % gqa_group) * M;
+            auto once = [&](int32_t begin, int32_t end, int32_t stacked_begin, int32_t stacked_end) {
+                const bool stacked = stacked_end > stacked_begin && group[stacked_begin] > 0;
+                for (int32_t m = begin; m < end; ++m)
+                    if (own[m] != (stacked ? 0 : 1)) return false;
+                for (int32_t m = stacked_begin; m < stacked_end; ++m)
+                    if (group[m] != (stacked ? 1 : 0) || (own != group && own[m] != 0)) return false;
+                return true;
+            };
+            if (!once(m_text, tm->M, tm->M, tm->M + st.n_text()) || !once(0, m_text, tm->M + st.n_text(), M)) return BS_EINVAL;
+        }
         if (n_units) *n_units = (int64_t)plan.items.size();
         if (unit_tiles) *unit_tiles = tiles;
         if (skip_steps) *skip_steps = skips;
@@ -1406,13 +1570,14 @@ extern "C" int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t 
             if ((size_t)sp.queue_off[8] != sp.parts.size()) return BS_EINVAL;
 
             // the parts of every unit
-            std::vector<int32_t> unit_of((size_t)tm->n_q_heads * tm->M, -1);
-            for (size_t u = 0; u < n_units; ++u) unit_of[(size_t)plan.items[u].head_a * tm->M + plan.items[u].tile_a] = (int32_t)u;
+            const int32_t M = tm->M + (gqa_group > 0 ? tm->stacked.n_text() + tm->stacked.n_other() : 0);   // ids of query tiles
+            std::vector<int32_t> unit_of((size_t)tm->n_q_heads * M, -1);
+            for (size_t u = 0; u < n_units; ++u) unit_of[(size_t)plan.items[u].head_a * M + plan.items[u].tile_a] = (int32_t)u;
             std::vector<std::vector<int32_t>> parts_of(n_units);
             for (size_t i = 0; i < sp.parts.size(); ++i) {
                 const bs::PairItem &p = sp.parts[i];
-                if (p.head_a < 0 || p.head_a >= tm->n_q_heads || p.tile_a < 0 || p.tile_a >= tm->M) return BS_EINVAL;
-                const int32_t u = unit_of[(size_t)p.head_a * tm->M + p.tile_a];
+                if (p.head_a < 0 || p.head_a >= tm->n_q_heads || p.tile_a < 0 || p.tile_a >= M) return BS_EINVAL;
+                const int32_t u = unit_of[(size_t)p.head_a * M + p.tile_a];
                 if (u < 0) return BS_EINVAL;
                 const bs::PairItem &it = plan.items[u];
                 if (p.head_b != it.head_b || p.tile_b != it.tile_b || (p.classes & 0xffff) != it.classes) return BS_EINVAL;

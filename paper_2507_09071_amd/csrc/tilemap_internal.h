@@ -91,7 +91,12 @@ struct PromptGeometry {
         const SpanInfo &s = spans[span_at(i)];
         return i >= s.start && s.start < w ? s.start : w;
     }
-    // the rows of query tile m as runs [first, second) of positions; returns how many rows
+    int32_t n_text_rows() const { return regrouped ? L - q_begin - n_img_rows : 0; }
+    int32_t n_other_rows() const { return L - q_begin - n_text_rows(); }
+    // rows number first .. last - 1 of the text rows, or of the others (the image rows of a regrouped map, else all), as runs
+    // [first, second) of positions, behind those in `runs`
+    void row_runs(bool text, int32_t first, int32_t last, std::vector<std::pair<int32_t, int32_t>> &runs) const;
+    // the rows of query tile m as such runs; returns how many rows
     int32_t tile_runs(int32_t m, std::vector<std::pair<int32_t, int32_t>> &runs) const;
 };
 
@@ -120,7 +125,7 @@ struct PairItem {
     int32_t head_a, tile_a, head_b, tile_b;
     int32_t list_begin, list_end;  // entries of PairPlan::ranges
     int32_t n_tiles;               // key tiles in the merged list (scheduling weight)
-    int32_t classes;               // item A | item B << 8; an item: its head's class | ClassLists::compact of its tile << 2
+    int32_t classes;               // item A | item B << 8; an item: its head's class | ClassLists::compact of its tile << 2 | stacked << 3
 };
 
 // Run of key tiles [begin, end) with one state per item: 0 skip, 1 partial, 2 full.
@@ -142,6 +147,23 @@ struct UnitRecord {
     int32_t next;                             // the run behind that one
 };
 static_assert(sizeof(UnitRecord) == 64, "one line; fetched by four lanes");
+
+// Stacked query tiles: 128 rows of ALL heads of a KV group, ordered by row and then by head, of rows that see the same keys under
+// every head of the group -- text rows, and the other rows of a group whose heads are all Dense.  Their ids follow the M
+// tiles of a head: first those of the text rows, then those of the others.
+struct StackedTiles {
+    int32_t gqa_group = 0;                // made for groups of this size; 0: not yet
+    ClassLists text, other;               // no entries: not worth it
+    int32_t n_text() const { return (int32_t)text.row_tiles.size(); }
+    int32_t n_other() const { return (int32_t)other.row_tiles.size(); }
+};
+
+// The same for the kernels.
+struct alignas(16) StackedRows {
+    int32_t first_tile, n_text_tiles;     // the ids are first_tile + ...
+    int32_t n_text_rows, n_other_rows;
+    int32_t text_slot0;                   // row records: the others from 0 on, text rows from here on
+};
 
 struct PairPlan {
     int32_t gqa_group = 0;  // the plan depends on which heads share a KV head ...
@@ -203,6 +225,7 @@ struct bs_tilemap {
     mutable bs::ClassLists cls[4];
     bs::ClassLists run[4];                 // what the kernels walk instead of cls, if built
     const bs::ClassLists &walked(int c) const { return run[c].row_ptr.empty() ? cls[c] : run[c]; }
+    bs::StackedTiles stacked;              // of the bf16 kernel's units; made for a group size when first planned
     uint64_t class_epoch = 1;              // bumped by bs_tilemap_rebind: work units and their device copies are stale
     bs::PairPlan pairs;                    // built on first use for a given gqa_group and class vector
     bs::PairPlan solo;                     // one item per unit; built on first use
