@@ -828,18 +828,19 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             const int row = ref.there ? r0.x : L;
             out_row = row < L ? ref.head * R + (row - a.q_begin) : -1;
             // rows past the end compute on a copy and are not stored
-            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 132) = (ref.head - max(head, 0)) * R + min(row, L - 1) - a.q_begin;
+            if (hl == 0) *reinterpret_cast<int32_t *>(stage + col * kPatchRow + 132) = ref.head * R + min(row, L - 1) - a.q_begin;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const char *qh = static_cast<const char *>(a.q) + (size_t)max(head, 0) * R * ROW;
 #pragma unroll
             for (int j = 0; j < kQueryLoads; ++j) {
                 const int r = j * kRowsPerLoad + ln / kChunks;
-                const uint32_t off = *reinterpret_cast<const uint32_t *>(stage + r * kPatchRow + 132) * ROW + (((ln % kChunks) ^ chunk_swap<D>(r)) << 4);
-                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                // (a whole address per lane: the rows of a head alone may take more than 4 GiB)
+                const char *src = static_cast<const char *>(a.q) + (size_t)*reinterpret_cast<const uint32_t *>(stage + r * kPatchRow + 132) * ROW +
+                                  (((ln % kChunks) ^ chunk_swap<D>(r)) << 4);
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                              :
-                             : "v"(off), "s"(qh), "s"(ring + query_at + j * 1024)
+                             : "v"(src), "s"(ring + query_at + j * 1024)
                              : "memory", "m0");
             }
             // (the walkers name tiles that this launch's pre-pass wrote, also those of an empty list)

@@ -956,15 +956,14 @@ static int64_t unit_steps(const ClassLists &lists)
 // the last, partly filled tile of every head and the keys that only some of the 128 rows see.  Text rows are few: 37 rows at the
 // end of a 36K prompt are a tile of 577 steps for every pair of heads, stacked in groups of seven 1 unit instead of 3.5.
 // A unit holds 256 rows either way, so groups of two gain nothing.  Stacked where that saves a thirtieth of the steps of these rows:
-// below, units of two kinds side by side share fewer tiles.  (The rows' distance from the first head's has to fit an offset
-// of 32 bits in the kernel.)
+// below, units of two kinds side by side share fewer tiles.  (The kernel counts the rows of a group in 32 bits.)
 static void plan_stacked(bs_tilemap *tm, int32_t G)
 {
     bs::StackedTiles &st = tm->stacked;
     if (st.gqa_group == G) return;
     st = bs::StackedTiles();
     const PromptGeometry &P = tm->geo;
-    if (G >= 3 && (int64_t)G * (tm->L - tm->q_begin) * 256 < INT32_MAX) {
+    if (G >= 3 && (int64_t)G * (tm->L - tm->q_begin) < INT32_MAX - P.bm) {
         const int32_t m_other = P.regrouped ? P.m_img : tm->M;
         const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
         for (bool text : {true, false}) {
