@@ -127,12 +127,13 @@ __device__ inline RowRef row_of(const StackedRows *rows, bool stacked, int G, in
 
 // Walks the merged key-tile list of a work unit from its record on (bf16).  The run behind the present one is there before it
 // is needed: a walk that asked for it at its turn would wait for the scalar cache, and with it for the operand reads in flight.
+// Behind its last tile the walker stays on it (see PairWalker); with more than one tile a step both items skip it there.
+template <int KT>
 struct TileWalker {
     const int2 *__restrict__ rg;
     int cur, end;                     // the tile, with its states; where its run ends
     int next_begin, next_end;         // the next run, if p <= p_end
     int p, p_end;
-    // Behind its last tile the walker stays on it (see PairWalker).
     __device__ void next()
     {
         const int t = cur + 16;
@@ -145,6 +146,9 @@ struct TileWalker {
             next_begin = r.x;
             next_end = r.y;
             ++p;
+        } else if (KT > 1) {
+            cur &= ~15;
+            end = cur + 16;
         }
     }
 };

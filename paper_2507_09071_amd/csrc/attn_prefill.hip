@@ -49,7 +49,7 @@ namespace bs {
 // spread over a word (0 / all ones) and a bit-field insert then keeps the score or takes -inf.  One statement, so that
 // the scheduler cannot hoist the 32 bit tests in front of the 32 selects (32 registers of pressure in a kernel that has none
 // to spare).
-__device__ inline void apply_mask(floatx16 (&s)[2], uint64_t allowed, int hl)
+__device__ inline void apply_mask(floatx16 &s0, floatx16 &s1, uint64_t allowed, int hl)
 {
     const uint32_t w[2] = {(uint32_t)allowed >> (4 * hl), (uint32_t)(allowed >> 32) >> (4 * hl)};
 #pragma unroll
@@ -57,12 +57,12 @@ __device__ inline void apply_mask(floatx16 (&s)[2], uint64_t allowed, int hl)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             uint32_t t;
-            float x = s[kb][v];
+            float x = kb ? s1[v] : s0[v];
             asm("v_bfe_i32 %1, %2, %3, 1\n\t"
                 "v_bfi_b32 %0, %1, %0, %4"
                 : "+v"(x), "=&v"(t)
                 : "v"(w[kb]), "n"(8 * (v / 4) + (v % 4)), "v"(-INFINITY));
-            s[kb][v] = x;
+            (kb ? s1 : s0)[v] = x;
         }
 }
 
@@ -80,19 +80,25 @@ __device__ inline void apply_mask(floatx16 (&s)[2], uint64_t allowed, int hl)
 // 120 instead of 155 where the wave's queries see all keys or none (chat_8k of the timed calls 1052 -> 1035 us, prompt_36k
 // 15777 -> 15650, window_27k 1711 -> 1698).  Two copies of the general path: with one that both branches reach, the compiler
 // straightens the branches and spills 80 registers.
-__device__ __forceinline__ void softmax_general(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float &m_run, float &l_run,
-                                                float &alpha, float c, bool drop)
+template <int KT>   // tiles of 64 keys, each with a `drop` of its own
+__device__ __forceinline__ void softmax_general(const floatx16 (&s)[2 * KT], bf16x8 (&pf)[2 * KT][2], float &m_run, float &l_run,
+                                                float &alpha, float c, const bool (&drop)[KT])
 {
-    // four independent max chains
-    float mx[4];
+    float mxl = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) mx[i] = fmaxf(s[i >> 1][8 * (i & 1)], s[i >> 1][8 * (i & 1) + 1]);
+    for (int t = 0; t < KT; ++t) {
+        // four independent max chains
+        float mx[4];
 #pragma unroll
-    for (int v = 2; v < 8; v += 2)
+        for (int i = 0; i < 4; ++i) mx[i] = fmaxf(s[2 * t + (i >> 1)][8 * (i & 1)], s[2 * t + (i >> 1)][8 * (i & 1) + 1]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mx[i] = fmaxf(fmaxf(mx[i], s[i >> 1][8 * (i & 1) + v]), s[i >> 1][8 * (i & 1) + v + 1]);
-    float mxl = max_across_halves(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
-    mxl = drop ? -INFINITY : mxl;
+        for (int v = 2; v < 8; v += 2)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx[i] = fmaxf(fmaxf(mx[i], s[2 * t + (i >> 1)][8 * (i & 1) + v]), s[2 * t + (i >> 1)][8 * (i & 1) + v + 1]);
+        const float mxt = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
+        mxl = t == 0 ? (drop[t] ? -INFINITY : mxt) : fmaxf(mxl, drop[t] ? -INFINITY : mxt);
+    }
+    mxl = max_across_halves(mxl);   // (the two halves hold keys of one query and drop alike)
     // Lazy reference point: the running reference m only moves when the tile maximum exceeds it
     // by more than kLazyLog2 (in the exp2 domain), so p <= 2^kLazyLog2 instead of p <= 1.  The
     // result is the same quotient O / l; what changes is that alpha is exactly 1 on almost every
@@ -103,10 +109,10 @@ __device__ __forceinline__ void softmax_general(const floatx16 (&s)[2], bf16x8 (
     const float m_use = m_new == -INFINITY ? 0.f : m_new;       // no key seen so far: p = 0
     const float mc = m_use * c;
     alpha = grow ? __builtin_amdgcn_exp2f(fmaf(m_run, c, -mc)) : 1.f;     // m_run = -inf -> 0
-    const float off = drop ? -INFINITY : -mc;
     float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < 2 * KT; ++kb) {
+        const float off = drop[kb / 2] ? -INFINITY : -mc;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -115,26 +121,34 @@ __device__ __forceinline__ void softmax_general(const floatx16 (&s)[2], bf16x8 (
                 sum[e & 3] += pv;
                 pf[kb][t][e] = (__bf16)pv;
             }
+    }
     l_run = fmaf(l_run, alpha, (sum[0] + sum[1]) + (sum[2] + sum[3]));
     m_run = m_new;
 }
 
-__device__ __forceinline__ void softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf)[2][2], float &m_run, float &l_run,
-                                             float &alpha, float c, bool drop)
+template <int KT>
+__device__ __forceinline__ void softmax_pack(const floatx16 (&s)[2 * KT], bf16x8 (&pf)[2 * KT][2], float &m_run, float &l_run,
+                                             float &alpha, float c, const bool (&drop)[KT])
 {
     constexpr float kFastLimit = 65536.f;
-    const float off = drop ? -INFINITY : -(m_run * c);   // m = -inf: +inf, no reference yet
-    if (__any(off == INFINITY)) {
-        softmax_general(s, pf, m_run, l_run, alpha, c, drop);
+    float off[KT];   // m = -inf: +inf, no reference yet
+    bool all_dropped = true;
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+        off[t] = drop[t] ? -INFINITY : -(m_run * c);
+        all_dropped = all_dropped && drop[t];
+    }
+    if (__any(KT == 1 ? off[0] == INFINITY : !all_dropped && m_run == -INFINITY)) {
+        softmax_general<KT>(s, pf, m_run, l_run, alpha, c, drop);
     } else {
         float sum[4];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2 * KT; ++kb)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + e], c, off));
+                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[kb][8 * t + e], c, off[kb / 2]));
                     sum[e & 3] = kb + t == 0 && e < 4 ? pv : sum[e & 3] + pv;
                     pf[kb][t][e] = (__bf16)pv;
                 }
@@ -143,7 +157,7 @@ __device__ __forceinline__ void softmax_pack(const floatx16 (&s)[2], bf16x8 (&pf
             l_run += tile_sum;
             alpha = 1.f;
         } else {
-            softmax_general(s, pf, m_run, l_run, alpha, c, drop);
+            softmax_general<KT>(s, pf, m_run, l_run, alpha, c, drop);
         }
     }
 }
@@ -311,10 +325,12 @@ constexpr int kMailboxBytes = 128;                  // the record of a workgroup
 constexpr int kPatchRow = 128 + 16;                 // a row of an output patch: 64 channels, where the row goes, the next unit's query row
 constexpr int kPatchBytes = 32 * kPatchRow;         // of one wave
 // LDS: ring, mailbox, output patches.  The patches lie beside the ring slots of a unit's first tiles and query rows, which are
-// on their way while the patches are in use; at d = 128 seven of them fill the CU's LDS, the eighth is in V^T slot 3, which is
+// on their way while the patches are in use; seven of them fill the CU's LDS beside 16 KB slots, the eighth is in V^T slot 3, which is
 // written in the second step.
-template <int D>
-constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + kMailboxBytes + (D == 128 ? 7 : 8) * kPatchBytes; }
+template <int D, int KT>
+constexpr int bf16_slot_bytes() { return KT * kBlockN * D * 2; }   // of the ring: the K or V^T tiles of a step
+template <int D, int KT>
+constexpr int bf16_lds_bytes() { return 2 * kRing * bf16_slot_bytes<D, KT>() + kMailboxBytes + 7 * kPatchBytes; }
 
 // One workgroup = two groups of four waves = one work unit: two (head, query tile) items that
 // read the same KV head and walk one merged key-tile list (heads of a GQA group with the same
@@ -327,8 +343,9 @@ constexpr int bf16_lds_bytes() { return 2 * kRing * kBlockN * D * 2 + kMailboxBy
 // in opposite order between two barriers (X then Y / Y then X): on every SIMD one wave is in X
 // while the other is in Y, and the matrix pipe and the vector ALU stay busy together instead
 // of the two waves queueing for the same unit.
-template <int D>
-__global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
+// A step takes KT key tiles: one, and at d = 64 two where the lists are long (see steps_of_two).
+template <int D, int KT>
+__device__ __forceinline__ void walk_units(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
     const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
@@ -337,8 +354,10 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 {
     constexpr int ROW = D * 2;            // bytes per K row in LDS
     constexpr int TILE = kBlockN * ROW;   // bytes per K or V^T tile
-    constexpr int DMA_PER_WAVE = D / 64;  // LDS-direct loads per wave per matrix per tile (8 waves)
+    constexpr int kSlotBytes = bf16_slot_bytes<D, KT>();   // of the ring: the tiles of a step
+    constexpr int DMA_PER_WAVE = kSlotBytes / 8192;        // LDS-direct loads per wave per matrix per step (8 waves)
     constexpr int NDB = D / 32;           // 32-channel blocks of the output
+    constexpr int NPV = KT == 2 ? 4 : NDB;   // operand reads of a PV batch
     constexpr int NT = D / 16;            // 16-wide slices of the head dim
     extern __shared__ __align__(1024) unsigned char lds[];   // K slots 0..3, then V^T slots 0..3
 
@@ -369,14 +388,14 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     const uint32_t kaddr0 = ring + col * 64 + ((hl ^ ((col >> 2) & 3)) << 4);   // odd slices: ^ 32
 
     floatx16 o[NDB];
-    floatx16 s[2];
-    bf16x8 pf[2][2];   // P^T of the previous tile as MFMA B operands
+    floatx16 s[2 * KT];
+    bf16x8 pf[2 * KT][2];   // P^T of the previous step as MFMA B operands
     float m_run = -INFINITY, l_run = 0.f;
     int out_row = -1;               // where this lane's row goes in `out`; -1: nowhere
-    // The tile of the vector phase and those behind it, with their states: step k of a unit refills K with the tile that
-    // the walker stands on, k + 3, and V^T with the one before.
-    TileWalker walk;
-    int tile_y = 0, tile_1 = 0, tile_2 = 0, tile_3 = 0;
+    // The tiles of the vector phase and of the steps behind it, with their states: step k of a unit refills K with the tiles from
+    // the one on that the walker stands on, those of step k + 3, and V^T with the ones before.
+    TileWalker<KT> walk;
+    int tile_y[KT] = {}, tile_1[KT] = {}, tile_2[KT] = {}, tile_3[KT] = {};
     // Both groups fetch, in the barrier interval k, their shares of K(k+3) and V^T(k+2): the second group
     // at the end of its matrix phase k, the first group right behind barrier k, before its vector phase.
     constexpr int ahead = 1;
@@ -386,11 +405,11 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2 * KT; ++kb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4 * KT; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e) pf[i >> 1][i & 1][e] = (__bf16)0.f;
         m_run = -INFINITY;
@@ -404,9 +423,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // its LDS destination in M0: nothing of it goes through the vector ALU, which the other wave of the
     // SIMD keeps busy (asm: the compiler forms a 64-bit vector address with a vector add per load instead).
     const uint32_t dma_lane_off = wave8 * 1024 + lane * 16;
-    auto dma = [&](int r, const char *tile, int slot_byte) __attribute__((always_inline)) {
+    auto dma = [&](int r, const char *const (&tiles)[KT], int slot_byte) __attribute__((always_inline)) {
         const uint32_t dst = ring + slot_byte + wave8 * 1024 + r * 8 * 1024;   // lane 0's 16 bytes
-        const char *src = tile + r * 8 * 1024;
+        const char *src = KT == 1 ? tiles[0] + r * 8 * 1024 : tiles[r % KT];
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :
                      : "v"(dma_lane_off), "s"(src), "s"(dst)
@@ -422,9 +441,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // exchanged by key: eight base addresses for the operand reads instead of two, 36K tokens 1.5 % slower.)
     const uint32_t kdma_key = (wave8 & 3) * 16 + (lane >> 2);
     const uint32_t kdma_lane_off = kdma_key * ROW + (wave8 >> 2) * 64 + (((lane & 3) ^ ((kdma_key >> 2) & 3)) << 4);
-    auto kdma = [&](int r, const char *tile, int slot_byte) __attribute__((always_inline)) {
+    auto kdma = [&](int r, const char *const (&tiles)[KT], int slot_byte) __attribute__((always_inline)) {
         const uint32_t dst = ring + slot_byte + wave8 * 1024 + r * 8 * 1024;
-        const char *src = tile + r * 128;
+        const char *src = KT == 1 ? tiles[0] + r * 128 : tiles[r % KT];
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :
                      : "v"(kdma_lane_off), "s"(src), "s"(dst)
@@ -433,27 +452,30 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // ---- phase X building blocks (step k reads K slot k mod 4 and V^T slot (k - 1) mod 4) ----
     // A batch is four 128-bit operand reads feeding four MFMAs:
-    //   PV batch g (D = 128): O^T block db += V^T(db, group g) . P^T(group g), db = 0..3
-    //   S  batch b          : head-dim slices 2b, 2b+1 for both 32-key blocks
+    //   PV batch g: O^T block db += V^T(db, group g) . P^T(group g); two tiles a step: key groups 2g and 2g + 1, db = 0, 1
+    //   S  batch b: head-dim slices 2b, 2b+1 for both 32-key blocks; two tiles a step: slice b for the four of them
     uint32_t kbase = 0, kbase_odd = 0, vbase = 0;  // fragment base addresses inside the ring slots of this step
     // one operand read / one MFMA of a batch (element i = 0..3)
     auto read_one = [&](auto tag, auto ic, bf16x8 &dst) __attribute__((always_inline)) {
         using T = decltype(tag);
         constexpr int i = decltype(ic)::value;
         if constexpr (T::kind == 1) {
-            if constexpr (i < NDB) lds_read_b128<T::idx * (D * 32) + i * 1024>(dst, vbase);   // channel block i
+            if constexpr (i < NPV) lds_read_b128<T::idx * NPV * 1024 + i * 1024>(dst, vbase);   // channel block i (two tiles: i & 1 of group 2 idx + (i >> 1))
         } else if constexpr (T::kind == 2) {
-            lds_read_b128<T::idx * 4096 + (i & 1) * 2048>(dst, (i >> 1) ? kbase_odd : kbase);   // slice 2 idx + (i >> 1), key block
+            if constexpr (KT == 1) lds_read_b128<T::idx * 4096 + (i & 1) * 2048>(dst, (i >> 1) ? kbase_odd : kbase);   // slice 2 idx + (i >> 1), key block
+            else lds_read_b128<(T::idx >> 1) * 4096 + (i >> 1) * TILE + (i & 1) * 2048>(dst, (T::idx & 1) ? kbase_odd : kbase);   // slice idx, key block i
         }
     };
     auto mul_one = [&](auto tag, auto ic, const bf16x8 &f) __attribute__((always_inline)) {
         using T = decltype(tag);
         constexpr int i = decltype(ic)::value;
         if constexpr (T::kind == 1) {
-            if constexpr (i < NDB) mfma_acc(o[i], f, pf[T::idx >> 1][T::idx & 1]);
+            constexpr int group = KT == 1 ? T::idx : 2 * T::idx + (i >> 1);
+            if constexpr (i < NPV) mfma_acc(o[i % NDB], f, pf[group >> 1][group & 1]);
         } else if constexpr (T::kind == 2) {
-            if constexpr (T::first && i < 2) mfma_set(s[i & 1], f, qreg[2 * T::idx + (i >> 1)]);
-            else mfma_acc(s[i & 1], f, qreg[2 * T::idx + (i >> 1)]);
+            constexpr int block = KT == 1 ? i & 1 : i, slice = KT == 1 ? 2 * T::idx + (i >> 1) : T::idx;
+            if constexpr (T::first && (KT == 2 || i < 2)) mfma_set(s[block], f, qreg[slice]);
+            else mfma_acc(s[block], f, qreg[slice]);
         }
     };
     using I0 = std::integral_constant<int, 0>;
@@ -469,8 +491,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // read it has issued (operands are read at issue, LDS data returns later), so the reads
     // issue in the shadow of the MFMAs.
     // text / sink key bits of the tile of the coming phase Y (scalar registers)
-    uint64_t tb_cur = 0, sb_cur = 0;
-    const char *ksrc = nullptr, *vsrc = nullptr;   // tiles of the coming refill ...
+    uint64_t tb_cur[KT] = {}, sb_cur[KT] = {};
+    const char *ksrc[KT] = {}, *vsrc[KT] = {};   // tiles of the coming refill ...
     // The scalar work of a step -- tiles of the refill, the walk, key bit masks for the coming phase Y -- stands inside
     // phase X, between two MFMA batches, where the wave has issue slots to spare (every MFMA keeps the matrix pipe busy for
     // 32 cycles).  Anything in front of the first MFMA costs its full length: with the walk there the same kernel takes 2 % longer
@@ -481,17 +503,22 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     bool need_bits = false;
     auto advance_walk = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
-        ksrc = k_ptr(walk.cur >> 4);
-        vsrc = tile_ptr(vth, tile_3 >> 4);
-        tile_y = tile_1;
-        tile_1 = tile_2;
-        tile_2 = tile_3;
-        tile_3 = walk.cur;
-        walk.next();
-        const int nn = tile_y >> 4;
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            ksrc[t] = k_ptr(walk.cur >> 4);
+            vsrc[t] = tile_ptr(vth, tile_3[t] >> 4);
+            tile_y[t] = tile_1[t];
+            tile_1[t] = tile_2[t];
+            tile_2[t] = tile_3[t];
+            tile_3[t] = walk.cur;
+            walk.next();
+        }
         if (need_bits) {
-            tb_cur = scalar_load<uint64_t>(map_text_bits + nn);
-            sb_cur = scalar_load<uint64_t>(map_sink_bits + nn);
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                tb_cur[t] = scalar_load<uint64_t>(map_text_bits + (tile_y[t] >> 4));
+                sb_cur[t] = scalar_load<uint64_t>(map_sink_bits + (tile_y[t] >> 4));
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -499,21 +526,21 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     auto issue_refill = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, ksrc, Sk_dst * TILE);
+        for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, ksrc, Sk_dst * kSlotBytes);
 #pragma unroll
-        for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * TILE);
+        for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * kSlotBytes);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto phase_x = [&](int S, int Sv, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4, Sv: slot of V^T(k-1)
         auto ring = [](int x) { return x >= kRing ? x - kRing : x; };
         Sk_dst = ring(ring(S + 2) + ahead); Sv_dst = ring(S + 1 + ahead);
-        kbase = kaddr0 + S * TILE;
+        kbase = kaddr0 + S * kSlotBytes;
         kbase_odd = kbase ^ 32;
-        vbase = vaddr0 + (kRing + Sv) * TILE;
+        vbase = vaddr0 + (kRing + Sv) * kSlotBytes;
         bf16x8 fa[4], fb[4], fc[4];
-        if constexpr (NDB < 4) {
+        if constexpr (NPV < 4) {
 #pragma unroll
-            for (int i = NDB; i < 4; ++i)
+            for (int i = NPV; i < 4; ++i)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { fa[i][e] = (__bf16)0.f; fb[i][e] = (__bf16)0.f; fc[i][e] = (__bf16)0.f; }
         }
@@ -538,7 +565,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             mul_one(cur, I2{}, f[2]); read_one(mid, I2{}, g[2]); read_one(nxt, I2{}, f[2]);
             mul_one(cur, I3{}, f[3]); read_one(mid, I3{}, g[3]); read_one(nxt, I3{}, f[3]);
         };
-        if constexpr (D == 128) {
+        if constexpr (NPV == 4) {
             // batch order: PV0 S0 PV1 S1 PV2 S2 PV3 S3, four reads / MFMAs each
             // Only two batches are read ahead of the first MFMA (the burst of all four waves of a group
             // costs every wave its share of the LDS time); the third goes out behind the first four
@@ -554,8 +581,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             lds_wait<4>(fa); batch(PvBatch<3>{}, NoBatch{}, fa);
             lds_wait<0>(fb); batch(ScBatch<3, false>{}, NoBatch{}, fb);
             mfma_drain(s[0], s[1]);   // the PV accumulators finished four MFMAs earlier
+            if constexpr (KT == 2) asm volatile("" : "+v"(s[2]), "+v"(s[3]));
         } else {
-            // D == 64: PV batches hold two reads / MFMAs, S has two batches of four
+            // PV batches hold two reads / MFMAs, S has two batches of four
             read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb); read_batch(PvBatch<1>{}, fc);   // 2 + 4 + 2
             lds_wait<6>(fa); batch(PvBatch<0>{}, PvBatch<2>{}, fa);                     // 4 2 | 2
             lds_wait<4>(fb); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fb);        // 2 2 | 4
@@ -585,11 +613,11 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
 
     // The last step: O += P(T-1) V(T-1), nothing else.
     auto phase_last = [&](int Sv) __attribute__((always_inline)) {
-        vbase = vaddr0 + (kRing + Sv) * TILE;
+        vbase = vaddr0 + (kRing + Sv) * kSlotBytes;
         bf16x8 fa[4], fb[4], fc[4];
-        if constexpr (NDB < 4) {
+        if constexpr (NPV < 4) {
 #pragma unroll
-            for (int i = NDB; i < 4; ++i)
+            for (int i = NPV; i < 4; ++i)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { fa[i][e] = (__bf16)0.f; fb[i][e] = (__bf16)0.f; fc[i][e] = (__bf16)0.f; }
         }
@@ -602,9 +630,9 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             mul_one(tag, I2{}, f[2]); mul_one(tag, I3{}, f[3]);
         };
         read_batch(PvBatch<0>{}, fa); read_batch(PvBatch<1>{}, fb); read_batch(PvBatch<2>{}, fc);
-        lds_wait<2 * NDB>(fa); mul_batch(PvBatch<0>{}, fa); read_batch(PvBatch<3>{}, fa);
-        lds_wait<2 * NDB>(fb); mul_batch(PvBatch<1>{}, fb);
-        lds_wait<NDB>(fc); mul_batch(PvBatch<2>{}, fc);
+        lds_wait<2 * NPV>(fa); mul_batch(PvBatch<0>{}, fa); read_batch(PvBatch<3>{}, fa);
+        lds_wait<2 * NPV>(fb); mul_batch(PvBatch<1>{}, fb);
+        lds_wait<NPV>(fc); mul_batch(PvBatch<2>{}, fc);
         lds_wait<0>(fa); mul_batch(PvBatch<3>{}, fa);
         mfma_drain(o[0], o[1]);
         if constexpr (NDB > 2) asm volatile("" : "+v"(o[2]), "+v"(o[3]));
@@ -619,18 +647,24 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         // (what stays the same for a unit is hidden from the compiler here: it made loops of their own for its values)
         int hd = head, cls = item_class;
         asm("" : "+s"(hd), "+s"(cls));
-        const int st = hd >= 0 ? (grp ? tile_y : tile_y >> 2) & 3 : 0;
-        bool drop = false;
-        if (st != 2) {
-            const int nu = tile_y >> 4;
-            const uint64_t allowed = st == 0 ? 0ull : allowed_keys(qv, cls, tb_cur, sb_cur, nu, a);
-            drop = allowed == 0ull;
-            // where every query of the wave sees all 64 keys or none (e.g. a text row and an
-            // image row over keys of another image) there is no per-score work
-            if (!__all(drop || allowed == ~0ull)) apply_mask(s, allowed, hl);
+        bool drop[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            const int st = hd >= 0 ? (grp ? tile_y[t] : tile_y[t] >> 2) & 3 : 0;
+            drop[t] = false;
+            if (st != 2) {
+                const int nu = tile_y[t] >> 4;
+                const uint64_t allowed = st == 0 ? 0ull : allowed_keys(qv, cls, tb_cur[t], sb_cur[t], nu, a);
+                drop[t] = allowed == 0ull;
+                // where every query of the wave sees all 64 keys or none (e.g. a text row and an
+                // image row over keys of another image) there is no per-score work.  (Behind a list of an odd length its last tile
+                // comes again: scores that were masked the first time, whatever they are, may not reach anything now.)
+                const bool again = t > 0 && nu == tile_y[0] >> 4;
+                if (again || !__all(drop[t] || allowed == ~0ull)) apply_mask(s[2 * t], s[2 * t + 1], allowed, hl);
+            }
         }
         float alpha;
-        softmax_pack(s, pf, m_run, l_run, alpha, a.scale_log2e, drop);
+        softmax_pack<KT>(s, pf, m_run, l_run, alpha, a.scale_log2e, drop);
         asm volatile("" : "+v"(alpha));   // one place where the output tile may change, reached by every path: two cost 64 register copies
         if (__any(alpha != 1.f)) {
 #pragma unroll
@@ -651,7 +685,8 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     // for the atomic to return under the last steps -- and requests the unit's record into a mailbox behind
     // the ring in the last one.  Every wave reads the same mailbox entry, so the workgroup leaves the loop together.
     typedef volatile __attribute__((address_space(3))) int32_t *lds_int_ptr;
-    const uint32_t mailbox_addr = ring + 2 * kRing * TILE;
+    const uint32_t mailbox_addr = ring + 2 * kRing * kSlotBytes;
+    constexpr int kRecordInts = sizeof(UnitRecord) / 4;
     const lds_int_ptr mailbox = (lds_int_ptr)(uintptr_t)mailbox_addr;
     int xcc;
     asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID, 0, 4)" : "=s"(xcc));
@@ -731,7 +766,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     if (wave8 == 0) {
         next_unit = share_next < share_end ? share_next : claim_from(__builtin_amdgcn_readfirstlane(take_ticket()));
         if (next_unit >= 0) fetch_record(next_unit);
-        if (lane == 0) mailbox[16] = next_unit;
+        if (lane == 0) mailbox[kRecordInts] = next_unit;
     }
     ++share_next;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -749,22 +784,22 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     constexpr int kRowsPerLoad = 1024 / ROW, kChunks = ROW / 16, kQueryLoads = 32 / kRowsPerLoad;
     bool first_unit = true;
     for (;;) {
-        const int unit = __builtin_amdgcn_readfirstlane(mailbox[16]);
+        const int unit = __builtin_amdgcn_readfirstlane(mailbox[kRecordInts]);
         const bool more = unit >= 0;
         // (hidden from the compiler, or addresses that only this part needs would stay in registers through the step loops)
         int ln = lane, w8 = wave8;
         asm volatile("" : "+v"(ln), "+s"(w8));
         const int hl = ln >> 5, col = ln & 31;
-        unsigned char *const stage = lds + (D == 128 && w8 == 7 ? (2 * kRing - 1) * TILE : 2 * kRing * TILE + kMailboxBytes + w8 * kPatchBytes);
-        const int query_at = (w8 >= 4 ? kRing + 1 : 2) * TILE + (w8 & 3) * 32 * ROW;
+        unsigned char *const stage = lds + (w8 == 7 ? (2 * kRing - 1) * kSlotBytes : 2 * kRing * kSlotBytes + kMailboxBytes + w8 * kPatchBytes);
+        const int query_at = (w8 >= 4 ? kRing + 1 : 2) * kSlotBytes + (w8 & 3) * 32 * ROW;
         // of the previous unit, for its epilogue
         const int done_head = head, done_slot = slot_id;
         const bool done_item = have_item && !first_unit;
         int4 r0, r1;
         RowRef ref;
-        int rec[16];
+        int rec[kRecordInts];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kRecordInts / 4; ++i) {
             const intx4 x = *(const __attribute__((address_space(3))) intx4 *)(uintptr_t)(mailbox_addr + 16 * i);
 #pragma unroll
             for (int j = 0; j < 4; ++j) rec[4 * i + j] = __builtin_amdgcn_readfirstlane(x[j]);
@@ -772,7 +807,7 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
         if (more) {
             head = grp ? rec[2] : rec[0];
             have_item = head >= 0;
-            T = rec[4];                                           // key tiles in the merged list
+            T = (rec[4] + KT - 1) / KT;                           // steps: key tiles in the merged list, or pairs of them
             slot_id = rec[5] >> 16;
             item_class = (grp ? rec[5] >> 8 : rec[5]) & 7;        // head classes travel with the unit
             need_bits = (item_class & 3) != 0 && !((item_class & 4) && ((item_class & 1) || a.text_tile0 < a.n_tiles));
@@ -845,20 +880,37 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
             }
             // (the walkers name tiles that this launch's pre-pass wrote, also those of an empty list)
             const int none = a.first_tile << 4;
-            tile_1 = T > 0 ? rec[8] : none;
-            tile_2 = T > 0 ? rec[9] : none;
-            tile_3 = T > 0 ? rec[10] : none;
-            walk = {pair_ranges, T > 0 ? rec[11] : none, T > 0 ? rec[12] : none + 16, rec[13], rec[14], rec[15], rec[7]};
+            const char *k0[KT], *k1[KT], *v0[KT];
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                tile_1[t] = T > 0 ? rec[8 + t] : none;
+                tile_2[t] = T > 0 ? rec[8 + KT + t] : none;
+                k0[t] = k_ptr(tile_1[t] >> 4); k1[t] = k_ptr(tile_2[t] >> 4); v0[t] = tile_ptr(vth, tile_1[t] >> 4);
+            }
             // K(0), K(1) and V^T(0) to the slots of these numbers (unconditional)
-            const char *k0 = k_ptr(tile_1 >> 4), *k1 = k_ptr(tile_2 >> 4), *v0 = tile_ptr(vth, tile_1 >> 4);
-            ksrc = k_ptr(tile_3 >> 4);
-            vsrc = tile_ptr(vth, tile_2 >> 4);
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k0, 0);
 #pragma unroll
-            for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k1, TILE);
+            for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k1, kSlotBytes);
 #pragma unroll
-            for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v0, kRing * TILE);
+            for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v0, kRing * kSlotBytes);
+            // (the walker stands on the fourth tile; with two tiles a step it walks on while the loads are on their way)
+            walk = {pair_ranges, T > 0 ? rec[11] : none, T > 0 ? rec[12] : none + 16, rec[13], rec[14], rec[15], rec[7]};
+            if constexpr (KT == 1) {
+                tile_3[0] = T > 0 ? rec[10] : none;
+            } else {
+                walk.next();
+#pragma unroll
+                for (int t = 0; t < KT; ++t) {
+                    tile_3[t] = walk.cur;
+                    walk.next();
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                ksrc[t] = k_ptr(tile_3[t] >> 4);
+                vsrc[t] = tile_ptr(vth, tile_2[t] >> 4);
+            }
         }
         if constexpr (NDB == 4) {
             if (done_item && done_slot == 0) store_half(1);
@@ -944,12 +996,34 @@ __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
                 if (next_unit >= 0) fetch_record(next_unit);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             }
-            if (lane == 0) mailbox[16] = next_unit;
+            if (lane == 0) mailbox[kRecordInts] = next_unit;
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the mailbox write is in LDS before the barrier
         }
         __builtin_amdgcn_s_barrier();
         ++share_next;
     }
+}
+
+template <int D>
+__global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
+{
+    walk_units<D, 1>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vt, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
+}
+
+template <int D>
+__global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16_two(
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
+{
+    walk_units<D, 2>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vt, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
 }
 
 }  // namespace bs
@@ -981,11 +1055,11 @@ int device_setup(int dev, void **scratch_out, int *n_cus_out)
     std::lock_guard<std::mutex> lock(g_device_mutex);
     hipError_t e;
     if (!g_attr_set[dev]) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs::attn_prefill_bf16<128>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, bs::bf16_lds_bytes<128>());
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(bs::attn_prefill_bf16<64>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, bs::bf16_lds_bytes<64>());
+        const auto lds_limit = [&](const void *kernel, int bytes) { if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); };
+        e = hipSuccess;
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16<128>), bs::bf16_lds_bytes<128, 1>());
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16<64>), bs::bf16_lds_bytes<64, 1>());
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16_two<64>), bs::bf16_lds_bytes<64, 2>());
         if (e == hipSuccess) e = bs::f32_device_setup();
         if (e == hipSuccess) e = bs::rows_device_setup();
         if (e != hipSuccess) return bs::fail_hip(e, "hipFuncSetAttribute");
@@ -1063,6 +1137,18 @@ TileRuns tiles_read(const bs_tilemap *tm, bool all)
     return t;
 }
 
+// Whether the bf16 kernel walks two key tiles a step at d = 64.  A step of one tile is 16 MFMAs and the softmax of 64 keys, behind the
+// same barrier, head reads and walk as the 32 MFMAs at d = 128; two tiles share them: 32 heads, all Dense, 36K tokens 5.72 -> 5.18 ms
+// (1.10 -> 1.00 us a tile; the vector ALU is busy for some 0.75 of that).  A list of an odd length costs one tile more, and in front of
+// a unit's first step lie twice the bytes.  Passes with one / two, by tiles per unit or share: 7 (700 tokens) 65.9 / 68.5 us, 8 (100
+// rows behind 9K) 84.9 / 87.6, 8-10 (window of 512) 291 / 300, 11-20 (window of 1024 on 27K) 972 / 973, 16 (4K) 107.4 / 107.1,
+// 30-72 (9K) 885 / 836, 126 (40K) 2833 / 2596.
+bool steps_of_two(const DeviceMap *d, const bs::ShareSet *sh)
+{
+    constexpr int64_t kTilesPerUnit = 12;
+    return d->n_steps >= kTilesPerUnit * std::max(d->n_pairs, sh ? sh->n_shares : 0);
+}
+
 // Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
 // holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
 // what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do.  A launch that
@@ -1101,9 +1187,14 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     }
     if (e != hipSuccess) return e;
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
-    e = bs::launch_kernel(bs::attn_prefill_bf16<D>, pgrid, pblock, bs::bf16_lds_bytes<D>(), st, a, d->text_bits,
-                          d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles,
-                          d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, d->stacked, cut_results);
+    const auto launch = [&](auto *kernel, int lds_bytes) {
+        return bs::launch_kernel(kernel, pgrid, pblock, lds_bytes, st, a, d->text_bits,
+                                 d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles,
+                                 d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, d->stacked, cut_results);
+    };
+    if constexpr (D == 128) e = launch(&bs::attn_prefill_bf16<128>, bs::bf16_lds_bytes<128, 1>());
+    else if (steps_of_two(d, sh)) e = launch(&bs::attn_prefill_bf16_two<64>, bs::bf16_lds_bytes<64, 2>());
+    else e = launch(&bs::attn_prefill_bf16<64>, bs::bf16_lds_bytes<64, 1>());
     if (e == hipSuccess && sh && sh->n_cut > 0)
         e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
                               d->rows, d->stacked, cut_results);

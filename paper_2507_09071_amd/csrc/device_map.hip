@@ -542,7 +542,7 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
                 end = ranges[p].end_states;
                 code = (ranges[p].begin << 4) | (end & 15);
             }
-            for (int32_t i = 0; i < 4; ++i) {
+            for (int32_t i = 0; i < 4; ++i) {   // (as TileWalker<2> goes)
                 r.tile[i] = code;
                 if (i == 3) break;
                 if (code + 16 < end) {
@@ -550,6 +550,9 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
                 } else if (p + 1 < it.list_end) {
                     end = ranges[++p].end_states;
                     code = (ranges[p].begin << 4) | (end & 15);
+                } else {
+                    code &= ~15;
+                    end = code + 16;
                 }
             }
             r.run_end = end;
@@ -558,7 +561,6 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
                 r.next_begin = ranges[p + 1].begin;
                 r.next_end_states = ranges[p + 1].end_states;
             }
-            // (a list of less than four tiles: the walker stands at its end, and stays there)
             *to++ = r;
         }
     };

@@ -141,7 +141,7 @@ struct UnitRecord {
     int32_t n_tiles, classes;                 // as in PairItem
     int32_t kv_head;
     int32_t list_end;                         // of its runs
-    int32_t tile[4];                          // the first four; of a shorter list the last one again
+    int32_t tile[4];                          // the first four; of a shorter list the last one again, skipped by both items
     int32_t run_end;                          // end_states of the run that tile[3] is in
     int32_t next_begin, next_end_states;      // the run behind that, if next <= list_end
     int32_t next;                             // the run behind that one
