@@ -505,8 +505,10 @@ __device__ __forceinline__ void walk_units(
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
-            ksrc[t] = k_ptr(walk.cur >> 4);
-            vsrc[t] = tile_ptr(vth, tile_3[t] >> 4);
+            if constexpr (KT == 1) {
+                ksrc[t] = k_ptr(walk.cur >> 4);
+                vsrc[t] = tile_ptr(vth, tile_3[t] >> 4);
+            }
             tile_y[t] = tile_1[t];
             tile_1[t] = tile_2[t];
             tile_2[t] = tile_3[t];
@@ -525,6 +527,15 @@ __device__ __forceinline__ void walk_units(
     int Sk_dst = 0, Sv_dst = 0;                    // ... and their ring slots
     auto issue_refill = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
+        // (two tiles a step: eight scalar registers from the walk to here were eight too many, and the step loop of the first group moved
+        // others to vector lanes and back; 9K tokens 843 -> 833 us, window of 4096 on 40K 1752 -> 1722)
+        if constexpr (KT > 1) {
+#pragma unroll
+            for (int t = 0; t < KT; ++t) {
+                ksrc[t] = k_ptr(tile_3[t] >> 4);
+                vsrc[t] = tile_ptr(vth, tile_2[t] >> 4);
+            }
+        }
 #pragma unroll
         for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, ksrc, Sk_dst * kSlotBytes);
 #pragma unroll
@@ -1142,7 +1153,7 @@ TileRuns tiles_read(const bs_tilemap *tm, bool all)
 // (1.10 -> 1.00 us a tile; the vector ALU is busy for some 0.75 of that).  A list of an odd length costs one tile more, and in front of
 // a unit's first step lie twice the bytes.  Passes with one / two, by tiles per unit or share: 7 (700 tokens) 65.9 / 68.5 us, 8 (100
 // rows behind 9K) 84.9 / 87.6, 8-10 (window of 512) 291 / 300, 11-20 (window of 1024 on 27K) 972 / 973, 16 (4K) 107.4 / 107.1,
-// 30-72 (9K) 885 / 836, 126 (40K) 2833 / 2596.
+// 30-72 (9K) 885 / 834, 126 (40K) 2833 / 2596.
 bool steps_of_two(const DeviceMap *d, const bs::ShareSet *sh)
 {
     constexpr int64_t kTilesPerUnit = 12;
