@@ -1257,8 +1257,9 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
 // (unnormalised output, reference point, row sum) that a second kernel merges.  The time per step differs by up to
 // 15 % between workgroups (which tiles they find in L2, partial tiles), so long shares keep back a part of the steps
 // as short pieces that go to the queues, for whoever is done first.
-// Costs are in key-tile steps: a unit or part costs its steps and kUnitCost around them (prologue and epilogue,
-// 8 us against 1.3-1.7 us per step by time stamps), the merge kMergeCost for the launch.
+// Costs are in key-tile steps: a unit or part costs its steps and kUnitCost around them, the merge kMergeCost for the launch.
+// (By time stamps what lies around a unit takes 5 us against 1.7 us per step; 4 instead of 6: 4000 rows behind 30K 1426 -> 1410 us,
+// 517 rows behind 36K 576 -> 572, but 300 rows behind 20K of d = 64 220 -> 225; 3 and 2: mixed, or slower.)
 void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
 {
     bs::SharePlan &sp = tm->shares;
