@@ -363,7 +363,6 @@ __device__ __forceinline__ void walk_units(
 
     const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, col = lane & 31;
     const int grp = __builtin_amdgcn_readfirstlane(tid >> 8);          // wave group 0 / 1
-    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave within the group
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);        // wave within the workgroup
     const int L = a.L;
 
@@ -804,7 +803,7 @@ __device__ __forceinline__ void walk_units(
         unsigned char *const stage = lds + (w8 == 7 ? (2 * kRing - 1) * kSlotBytes : 2 * kRing * kSlotBytes + kMailboxBytes + w8 * kPatchBytes);
         const int query_at = (w8 >= 4 ? kRing + 1 : 2) * kSlotBytes + (w8 & 3) * 32 * ROW;
         // of the previous unit, for its epilogue
-        const int done_head = head, done_slot = slot_id;
+        const int done_slot = slot_id;
         const bool done_item = have_item && !first_unit;
         int4 r0, r1;
         RowRef ref;

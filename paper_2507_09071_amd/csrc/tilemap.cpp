@@ -937,17 +937,20 @@ static void build_stacked(const bs_tilemap *tm, int32_t G, bool text, ClassLists
     }
 }
 
-// Steps of units of two neighbouring tiles.
+// Steps of units of two neighbouring tiles: key tiles that either of them walks.
 static int64_t unit_steps(const ClassLists &lists)
 {
     int64_t steps = 0;
-    std::vector<TileRange> both;
-    for (size_t j = 0; j < lists.row_tiles.size(); j += 2) {
-        const bool pair = j + 1 < lists.row_tiles.size();
-        const auto at = [&](size_t i) { return std::vector<TileRange>(lists.ranges.begin() + lists.row_ptr[i], lists.ranges.begin() + lists.row_ptr[i + 1]); };
-        if (pair) combine_runs(at(j), at(j + 1), both);
-        else both = at(j);
-        for (const TileRange &r : both) steps += r.end() - r.begin;
+    const int32_t n = (int32_t)lists.row_tiles.size();
+    for (int32_t j = 0; j < n; j += 2) {
+        int64_t a = lists.row_ptr[j], b = lists.row_ptr[j + 1];
+        const int64_t a_end = b, b_end = j + 1 < n ? lists.row_ptr[j + 2] : b;
+        int32_t done = 0;   // tiles before this one are counted
+        while (a < a_end || b < b_end) {
+            const TileRange &r = b >= b_end || (a < a_end && lists.ranges[a].begin <= lists.ranges[b].begin) ? lists.ranges[a++] : lists.ranges[b++];
+            steps += std::max(0, r.end() - std::max(done, r.begin));
+            done = std::max(done, r.end());
+        }
     }
     return steps;
 }
@@ -957,25 +960,26 @@ static int64_t unit_steps(const ClassLists &lists)
 // end of a 36K prompt are a tile of 577 steps for every pair of heads, stacked in groups of seven 1 unit instead of 3.5.
 // A unit holds 256 rows either way, so groups of two gain nothing.  Stacked where that saves a thirtieth of the steps of these rows:
 // below, units of two kinds side by side share fewer tiles.  (The kernel counts the rows of a group in 32 bits.)
-static void plan_stacked(bs_tilemap *tm, int32_t G)
+static void plan_stacked(bs_tilemap *tm, int32_t G, bool any_all_dense)
 {
     bs::StackedTiles &st = tm->stacked;
-    if (st.gqa_group == G) return;
-    st = bs::StackedTiles();
-    const PromptGeometry &P = tm->geo;
-    if (G >= 3 && (int64_t)G * (tm->L - tm->q_begin) < INT32_MAX - P.bm) {
-        const int32_t m_other = P.regrouped ? P.m_img : tm->M;
-        const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
-        for (bool text : {true, false}) {
-            if (text && !P.regrouped) continue;
-            int64_t apart = 0;   // steps of one head; two heads walk them together
-            for (int32_t m = text ? m_other : 0; m < (text ? tm->M : m_other); ++m) apart += dense[m];
-            ClassLists &lists = text ? st.text : st.other;
-            build_stacked(tm, G, text, lists);
-            if (unit_steps(lists) * 60 > apart * G * 29) lists = ClassLists();
-        }
-    }
+    if (st.gqa_group != G) st = bs::StackedTiles();
     st.gqa_group = G;
+    const PromptGeometry &P = tm->geo;
+    if (G < 3 || (int64_t)G * (tm->L - tm->q_begin) >= INT32_MAX - P.bm) return;
+    const int32_t m_other = P.regrouped ? P.m_img : tm->M;
+    const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
+    auto decide = [&](bool text, bool &decided) {   // once per map; of the other rows when a group is all Dense for the first time
+        if (decided) return;
+        decided = true;
+        int64_t apart = 0;   // steps of one head; two heads walk them together
+        for (int32_t m = text ? m_other : 0; m < (text ? tm->M : m_other); ++m) apart += dense[m];
+        ClassLists &lists = text ? st.text : st.other;
+        build_stacked(tm, G, text, lists);
+        if (unit_steps(lists) * 60 > apart * G * 29) lists = ClassLists();
+    };
+    if (P.regrouped) decide(true, st.text_decided);
+    if (any_all_dense) decide(false, st.other_decided);
 }
 
 extern "C" int bs_tilemap_rebind(bs_tilemap *tm, const uint8_t *head_class, int32_t n_q_heads)
@@ -1013,7 +1017,12 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     if (plan.gqa_group == G && plan.epoch == tm->class_epoch) return;
     plan.ranges.clear();
     plan.items.clear();
-    plan_stacked(tm, G);
+    auto all_dense_group = [&](int32_t kv) {
+        return std::all_of(tm->head_class.begin() + kv * G, tm->head_class.begin() + (kv + 1) * G, [](uint8_t c) { return c == BS_DENSE; });
+    };
+    bool any_all_dense = false;
+    for (int32_t kv = 0; kv < tm->n_q_heads / G && !any_all_dense; ++kv) any_all_dense = all_dense_group(kv);
+    plan_stacked(tm, G, any_all_dense);
     const bs::StackedTiles &st = tm->stacked;
     const int32_t n_text_tiles = st.n_text(), H = tm->n_q_heads;
     const int32_t M = n_text_tiles > 0 ? tm->geo.m_img : tm->M;   // tiles that are walked head by head
@@ -1137,7 +1146,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     for (int32_t kv = 0; kv < H / G; ++kv) {
         if (n_text_tiles > 0) push_stacked(kv, kText, tm->M);
         // (without stacked text rows these are among the tiles of every head)
-        const bool all_dense = std::all_of(tm->head_class.begin() + kv * G, tm->head_class.begin() + (kv + 1) * G, [](uint8_t c) { return c == BS_DENSE; });
+        const bool all_dense = any_all_dense && all_dense_group(kv);
         if (all_dense && st.n_other() > 0 && (n_text_tiles > 0 || !tm->geo.regrouped)) {
             push_stacked(kv, kOther, tm->M + n_text_tiles);
             continue;

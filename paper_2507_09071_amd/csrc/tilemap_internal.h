@@ -153,6 +153,7 @@ static_assert(sizeof(UnitRecord) == 64, "one line; fetched by four lanes");
 // tiles of a head: first those of the text rows, then those of the others.
 struct StackedTiles {
     int32_t gqa_group = 0;                // made for groups of this size; 0: not yet
+    bool text_decided = false, other_decided = false;
     ClassLists text, other;               // no entries: not worth it
     int32_t n_text() const { return (int32_t)text.row_tiles.size(); }
     int32_t n_other() const { return (int32_t)other.row_tiles.size(); }
