@@ -971,12 +971,12 @@ static void plan_stacked(bs_tilemap *tm, int32_t G, bool any_all_dense)
     const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
     auto decide = [&](bool text, bool &decided) {   // once per map; of the other rows when a group is all Dense for the first time
         if (decided) return;
-        decided = true;
         int64_t apart = 0;   // steps of one head; two heads walk them together
         for (int32_t m = text ? m_other : 0; m < (text ? tm->M : m_other); ++m) apart += dense[m];
-        ClassLists &lists = text ? st.text : st.other;
+        ClassLists lists;   // (the map's own stay empty until these are whole: an allocation may fail)
         build_stacked(tm, G, text, lists);
-        if (unit_steps(lists) * 60 > apart * G * 29) lists = ClassLists();
+        if (unit_steps(lists) * 60 <= apart * G * 29) (text ? st.text : st.other) = std::move(lists);
+        decided = true;
     };
     if (P.regrouped) decide(true, st.text_decided);
     if (any_all_dense) decide(false, st.other_decided);
