@@ -1015,6 +1015,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
 {
     bs::PairPlan &plan = tm->pairs;
     if (plan.gqa_group == G && plan.epoch == tm->class_epoch) return;
+    plan.epoch = 0;   // (nobody's until it is whole: an allocation may fail)
     plan.ranges.clear();
     plan.items.clear();
     auto all_dense_group = [&](int32_t kv) {
@@ -1271,19 +1272,11 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
 // Dense, was cut to save 8 steps and took 68 us instead of 62.)
 // (By time stamps what lies around a unit takes 5 us against 1.7 us per step; 4 instead of 6: 4000 rows behind 30K 1426 -> 1410 us,
 // 517 rows behind 36K 576 -> 572, but 300 rows behind 20K of d = 64 220 -> 225; 3 and 2: mixed, or slower.)
-void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
+static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool solo, int32_t G, int32_t n_wgs, bs::SharePlan &sp)
 {
-    bs::SharePlan &sp = tm->shares;
-    if (sp.gqa_group == gqa_group && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
-    const bool solo = gqa_group == 0;
-    if (solo) bs_plan_solo(tm);
-    else bs_plan_pairs(tm, gqa_group);
-    const bs::PairPlan &plan = solo ? tm->solo : tm->pairs;
-    const int32_t G = std::max(gqa_group, 1);
     sp.parts.clear(); sp.ranges.clear(); sp.share_off.clear(); sp.cut.clear();
     sp.n_slots = 0;
     std::fill(sp.queue_off, sp.queue_off + 9, 0);
-    sp.gqa_group = gqa_group; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
     // the fp32 kernel's steps take 3.5-7 us
     const int64_t kUnitCost = solo ? 1 : 6, kMergeCost = solo ? 1 : 8, kMinPart = solo ? 1 : 4;
     // With more units than that the queues are better, although their longest workgroup has 5-6 % more steps than the mean on
@@ -1454,6 +1447,18 @@ void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
         sp.parts.clear(); sp.ranges.clear(); sp.share_off.clear(); sp.cut.clear();
         sp.n_slots = 0;
     }
+}
+
+void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
+{
+    bs::SharePlan &sp = tm->shares;
+    if (sp.gqa_group == gqa_group && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
+    const bool solo = gqa_group == 0;
+    if (solo) bs_plan_solo(tm);
+    else bs_plan_pairs(tm, gqa_group);
+    sp.epoch = 0;   // (as for a plan of units)
+    make_shares(tm, solo ? tm->solo : tm->pairs, solo, std::max(gqa_group, 1), n_wgs, sp);
+    sp.gqa_group = gqa_group; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;
 }
 
 extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *n_units, int64_t *unit_tiles,

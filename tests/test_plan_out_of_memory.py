@@ -1,5 +1,5 @@
 """A plan that ran out of memory half-way leaves nothing behind: a driver of its own, compiled with the builder's source, lets the
-allocation behind k others fail, for every k, and plans again.  The units that a call uses are then those of a map that never failed."""
+allocation behind k others fail, for every k, and plans again.  The plans that a call uses are then those of a map that never failed."""
 import os
 import shutil
 import subprocess
@@ -34,7 +34,7 @@ static bool same(const std::vector<T> &a, const std::vector<T> &b)
 }
 
 static const uint8_t kSparse[8] = {3, 2, 1, 3, 3, 3, 2, 2}, kDense[8] = {0, 0, 0, 0, 3, 2, 1, 0};
-static int plan(bs_tilemap *tm, int G) { return bs_tilemap_pair_plan(tm, G, nullptr, nullptr, nullptr); }
+static int plan(bs_tilemap *tm, int G) { return bs_tilemap_share_plan(tm, G, 256, nullptr, nullptr, nullptr); }
 
 static bs_tilemap *map(const char *what)   // up to the plan that fails
 {
@@ -49,18 +49,22 @@ static bs_tilemap *map(const char *what)   // up to the plan that fails
 
 int main(int, char **argv)
 {
+    const int fails_at = !std::strcmp(argv[1], "other group size") ? 8 : (!std::strcmp(argv[1], "one head a unit") ? 0 : 4);
     bs_tilemap *right = map(argv[1]);
     expect(plan(right, 4) == BS_OK, "plan", -1);
     expect(right->stacked.n_text() > 0, "stacked tiles", -1);
     for (long k = 0;; ++k) {
         bs_tilemap *tm = map(argv[1]);
         fail_after = k;
-        const int rc = plan(tm, 4);
+        const int rc = plan(tm, fails_at);
         const bool failed = fail_after < 0;
         fail_after = -1;
         expect(rc == BS_OK || (failed && rc == BS_ENOMEM), "what the call says", k);   // (a sort does without its buffer)
-        expect(plan(tm, 4) == BS_OK, "plan again", k);
+        expect(bs_tilemap_pair_plan(tm, 4, nullptr, nullptr, nullptr) == BS_OK && plan(tm, 4) == BS_OK, "plan again", k);
         expect(same(tm->pairs.items, right->pairs.items) && same(tm->pairs.ranges, right->pairs.ranges), "units", k);
+        expect(same(tm->shares.parts, right->shares.parts) && same(tm->shares.ranges, right->shares.ranges) &&
+               same(tm->shares.share_off, right->shares.share_off) && same(tm->shares.cut, right->shares.cut) &&
+               !std::memcmp(tm->shares.queue_off, right->shares.queue_off, sizeof right->shares.queue_off), "shares", k);
         bs_tilemap_destroy(tm);
         if (!failed) break;
     }
@@ -80,7 +84,7 @@ def driver(tmp_path_factory):
     return str(d / "driver")
 
 
-@pytest.mark.parametrize("what", ["first plan", "all Dense for the first time"])
+@pytest.mark.parametrize("what", ["first plan", "all Dense for the first time", "other group size", "one head a unit"])
 def test_allocation_fails(driver, what):
     done = subprocess.run([driver, what], capture_output=True, text=True)
     assert done.returncode == 0, done.stderr
