@@ -1452,10 +1452,10 @@ static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool sol
 void bs_plan_shares(bs_tilemap *tm, int32_t gqa_group, int32_t n_wgs)
 {
     bs::SharePlan &sp = tm->shares;
-    if (sp.gqa_group == gqa_group && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
     const bool solo = gqa_group == 0;
     if (solo) bs_plan_solo(tm);
-    else bs_plan_pairs(tm, gqa_group);
+    else bs_plan_pairs(tm, gqa_group);   // (also where the shares are there: the units may be those of another group size by now)
+    if (sp.gqa_group == gqa_group && sp.epoch == tm->class_epoch && sp.n_wgs == n_wgs) return;
     sp.epoch = 0;   // (as for a plan of units)
     make_shares(tm, solo ? tm->solo : tm->pairs, solo, std::max(gqa_group, 1), n_wgs, sp);
     sp.gqa_group = gqa_group; sp.n_wgs = n_wgs; sp.epoch = tm->class_epoch;

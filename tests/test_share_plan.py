@@ -61,3 +61,13 @@ def test_refuses_what_it_cannot_plan():
     for group, wgs in ((3, CUS), (-1, CUS), (2, 0)):
         with pytest.raises(bs.BlindsightError):
             tm.share_plan(group, wgs)
+
+
+def test_units_of_another_group_size_in_between():
+    """The shares are there already, but the units that they are cut from have been planned for other groups since."""
+    spans = [(p, p + 1000, 100) for p in range(20, 36000, 1018)]
+    tm = bs.bs_build_tilemap(spans, 36660, np.arange(16) % 4, 5, 128, 64, flags=bs.BS_MAP_PACK_KEYS, q_begin=36660 - 517)
+    plan = tm.share_plan(4, CUS)
+    assert plan["n_parts"] > 0
+    tm.pair_plan(8)
+    assert tm.share_plan(4, CUS) == plan
