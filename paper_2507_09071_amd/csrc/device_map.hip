@@ -568,7 +568,7 @@ int upload_binding(bs_tilemap *tm, int32_t kind, int32_t gqa_group, int32_t n_wg
     put(off_b, plan.ranges);
     std::memset(host + off_q, 0, 256);
     std::memcpy(host + off_q, plan.queue_off, sizeof plan.queue_off);
-    const StackedRows stacked = {tm->M, tm->stacked.n_text(), tm->geo.n_text_rows(), tm->geo.n_other_rows(), tm->geo.m_img * 128};
+    const StackedRows stacked = {tm->M, tm->stacked.text.n_tiles, tm->geo.n_text_rows(), tm->geo.n_other_rows(), tm->geo.m_img * 128};
     std::memcpy(host + off_q + 128, &stacked, sizeof stacked);
     for (int i = 0; i < 2; ++i) {
         const SharePlan &s = *share_plans[i];

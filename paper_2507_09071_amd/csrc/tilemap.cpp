@@ -894,63 +894,84 @@ void bs_plan_solo(bs_tilemap *tm)
     plan.epoch = tm->class_epoch;
 }
 
-// The lists of the stacked tiles (see StackedTiles) of the text rows or of the others: a row sees the keys [lo(i), e(i)] of the dense
-// mask, both ends grow with the position, so the rows of a tile share [lo(last), e(first)] and see [lo, e] of every run.
-static void build_stacked(const bs_tilemap *tm, int32_t G, bool text, ClassLists &out)
+// The units of the stacked tiles (see StackedTiles) of the text rows or of the others: a row sees the keys [lo(i), e(i)] of the dense
+// mask, both ends grow with the position, so the rows of a tile share [lo(last), e(first)] and see [lo, e] of every run.  One walk
+// over all rows, which makes the merged lists at once: this is host time of every new map (28K tokens in a window of 512, 883 units of a group
+// of eight: the plan of a new map 275 -> 174 us, 158 without stacking).  Returns the steps of the units.
+static int64_t build_stacked(const bs_tilemap *tm, int32_t G, bool text, bs::StackedTiles::Kind &out)
 {
     const PromptGeometry &P = tm->geo;
     const int64_t n_rows = text ? P.n_text_rows() : P.n_other_rows(), n_slots = n_rows * G;
-    const int32_t n_tiles = (int32_t)((n_slots + P.bm - 1) / P.bm);
-    out.row_ptr.assign(n_tiles + 1, 0);
-    out.row_tiles.assign(n_tiles, 0);
-    out.compact.assign(n_tiles, 0);
-    std::vector<std::pair<int32_t, int32_t>> runs;
-    int32_t first, last, unused_lo, unused_hi;
-    for (int32_t j = 0; j < n_tiles; ++j) {
-        const int32_t t0 = (int32_t)((int64_t)j * P.bm / G), t1 = (int32_t)(std::min<int64_t>((int64_t)(j + 1) * P.bm, n_slots) - 1) / G;
-        runs.clear();
-        P.row_runs(text, t0, t1 + 1, runs);
-        bs::row_bounds(tm, runs.back().second - 1, &first, &last, &unused_lo, &unused_hi);
+    out.n_tiles = (int32_t)((n_slots + P.bm - 1) / P.bm);
+    if (out.n_tiles == 0) return 0;
+    auto bounds = [&, window = tm->window, in_images = tm->bidir && !text](int32_t i, int32_t &first, int32_t &last) {
+        int32_t unused_lo, unused_hi;
+        if (in_images) return bs::row_bounds(tm, i, &first, &last, &unused_lo, &unused_hi);
+        first = window > 0 ? std::max(0, i - window + 1) : 0;
+        last = i;
+    };
+    std::vector<std::pair<int32_t, int32_t>> runs;   // of all rows
+    P.row_runs(text, 0, (int32_t)n_rows, runs);
+    size_t run = 0;        // the run that row t0 is in, ...
+    int32_t before = 0;    // ... and the rows in front of it
+    struct Piece { int32_t begin, end, state; };
+    std::vector<Piece> lists[2];
+    auto list_of = [&](int32_t j, std::vector<Piece> &list) {
+        const int32_t t0 = (int32_t)((int64_t)j * P.bm / G), t1 = (int32_t)((std::min<int64_t>((int64_t)(j + 1) * P.bm, n_slots) - 1) / G);
+        while (t0 - before >= runs[run].second - runs[run].first) before += runs[run].second - runs[run].first, ++run;
+        size_t r = run;
+        int32_t at = before;   // rows in front of run r
+        while (t1 - at >= runs[r].second - runs[r].first) at += runs[r].second - runs[r].first, ++r;
+        int32_t first, last;
+        const size_t r_last = r;
+        const int32_t p0 = runs[run].first + (t0 - before), p1 = runs[r_last].first + (t1 - at);
+        bounds(p1, first, last);
         const int32_t full_from = (first + P.bn - 1) / P.bn;
-        bs::row_bounds(tm, runs.front().first, &first, &last, &unused_lo, &unused_hi);
+        bounds(p0, first, last);
         const int32_t full_end = std::max(full_from, (last + 1) / P.bn);
-        auto emit = [&](int32_t b, int32_t e, bool full) {
-            if (e <= b) return;
-            out.row_tiles[j] += e - b;
-            if ((int64_t)out.ranges.size() > out.row_ptr[j] && out.ranges.back().end() == b && out.ranges.back().full() == full) out.ranges.back().end_state = (e << 1) | (int32_t)full;
-            else out.ranges.push_back({b, (e << 1) | (int32_t)full});
-        };
+        list.clear();
+        auto emit = [&](int32_t b, int32_t e, int32_t state) { if (e > b) list.push_back({b, e, state}); };
         int32_t done = 0;   // tiles before this one are decided
-        for (const auto &r : runs) {
-            bs::row_bounds(tm, r.first, &first, &last, &unused_lo, &unused_hi);
+        for (r = run; r <= r_last; ++r) {
+            bounds(r == run ? p0 : runs[r].first, first, last);
             const int32_t b = std::max(done, first / P.bn);
-            bs::row_bounds(tm, r.second - 1, &first, &last, &unused_lo, &unused_hi);
+            bounds(r == r_last ? p1 : runs[r].second - 1, first, last);
             const int32_t e = last / P.bn + 1;
             if (e <= b) continue;
             const int32_t f0 = std::min(std::max(full_from, b), e), f1 = std::min(std::max(full_end, f0), e);
-            emit(b, f0, false);
-            emit(f0, f1, true);
-            emit(f1, e, false);
+            emit(b, f0, 1);
+            emit(f0, f1, 2);
+            emit(f1, e, 1);
             done = e;
         }
-        out.row_ptr[j + 1] = (int64_t)out.ranges.size();
-    }
-}
-
-// Steps of units of two neighbouring tiles: key tiles that either of them walks.
-static int64_t unit_steps(const ClassLists &lists)
-{
+    };
     int64_t steps = 0;
-    const int32_t n = (int32_t)lists.row_tiles.size();
-    for (int32_t j = 0; j < n; j += 2) {
-        int64_t a = lists.row_ptr[j], b = lists.row_ptr[j + 1];
-        const int64_t a_end = b, b_end = j + 1 < n ? lists.row_ptr[j + 2] : b;
-        int32_t done = 0;   // tiles before this one are counted
-        while (a < a_end || b < b_end) {
-            const TileRange &r = b >= b_end || (a < a_end && lists.ranges[a].begin <= lists.ranges[b].begin) ? lists.ranges[a++] : lists.ranges[b++];
-            steps += std::max(0, r.end() - std::max(done, r.begin));
-            done = std::max(done, r.end());
+    out.units.reserve((out.n_tiles + 1) / 2);
+    for (int32_t j = 0; j < out.n_tiles; j += 2) {
+        list_of(j, lists[0]);
+        if (j + 1 < out.n_tiles) list_of(j + 1, lists[1]);
+        else lists[1].clear();
+        const Piece *a = lists[0].data(), *const a_end = a + lists[0].size(), *b = lists[1].data(), *const b_end = b + lists[1].size();
+        const int32_t list_begin = (int32_t)out.ranges.size();
+        int32_t tiles = 0;
+        for (int32_t cur = 0; a < a_end || b < b_end;) {
+            const bool in_a = a < a_end && a->begin <= cur, in_b = b < b_end && b->begin <= cur;
+            int32_t next = INT32_MAX;   // boundary behind cur
+            if (a < a_end) next = std::min(next, in_a ? a->end : a->begin);
+            if (b < b_end) next = std::min(next, in_b ? b->end : b->begin);
+            const int32_t states = (in_a ? a->state << 2 : 0) | (in_b ? b->state : 0);
+            if (states != 0) {
+                tiles += next - cur;
+                const bool goes_on = (int32_t)out.ranges.size() > list_begin && out.ranges.back().end_states == (cur << 4 | states);
+                if (goes_on) out.ranges.back().end_states = next << 4 | states;
+                else out.ranges.push_back({cur, next << 4 | states});
+            }
+            cur = next;
+            if (in_a && a->end == cur) ++a;
+            if (in_b && b->end == cur) ++b;
         }
+        out.units.push_back({list_begin, (int32_t)out.ranges.size(), tiles});
+        steps += tiles;
     }
     return steps;
 }
@@ -969,17 +990,16 @@ static void plan_stacked(bs_tilemap *tm, int32_t G, bool any_all_dense)
     if (G < 3 || (int64_t)G * (tm->L - tm->q_begin) >= INT32_MAX - P.bm) return;
     const int32_t m_other = P.regrouped ? P.m_img : tm->M;
     const std::vector<int32_t> &dense = tm->walked(BS_DENSE).row_tiles;
-    auto decide = [&](bool text, bool &decided) {   // once per map; of the other rows when a group is all Dense for the first time
-        if (decided) return;
+    auto decide = [&](bool text, bs::StackedTiles::Kind &kind) {   // once per map; of the other rows when a group is all Dense for the first time
+        if (kind.decided) return;
         int64_t apart = 0;   // steps of one head; two heads walk them together
         for (int32_t m = text ? m_other : 0; m < (text ? tm->M : m_other); ++m) apart += dense[m];
-        ClassLists lists;   // (the map's own stay empty until these are whole: an allocation may fail)
-        build_stacked(tm, G, text, lists);
-        if (unit_steps(lists) * 60 <= apart * G * 29) (text ? st.text : st.other) = std::move(lists);
-        decided = true;
+        bs::StackedTiles::Kind made;   // (the map's own stays empty until this is whole: an allocation may fail)
+        if (build_stacked(tm, G, text, made) * 60 <= apart * G * 29) kind = std::move(made);
+        kind.decided = true;
     };
-    if (P.regrouped) decide(true, st.text_decided);
-    if (any_all_dense) decide(false, st.other_decided);
+    if (P.regrouped) decide(true, st.text);
+    if (any_all_dense) decide(false, st.other);
 }
 
 extern "C" int bs_tilemap_rebind(bs_tilemap *tm, const uint8_t *head_class, int32_t n_q_heads)
@@ -1025,17 +1045,15 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     for (int32_t kv = 0; kv < tm->n_q_heads / G && !any_all_dense; ++kv) any_all_dense = all_dense_group(kv);
     plan_stacked(tm, G, any_all_dense);
     const bs::StackedTiles &st = tm->stacked;
-    const int32_t n_text_tiles = st.n_text(), H = tm->n_q_heads;
+    const int32_t n_text_tiles = st.text.n_tiles, H = tm->n_q_heads;
     const int32_t M = n_text_tiles > 0 ? tm->geo.m_img : tm->M;   // tiles that are walked head by head
-    constexpr int kText = 4, kOther = 5;                          // stacked tiles, next to the classes
-    auto lists_of = [&](int c) -> const ClassLists & { return c == kText ? st.text : (c == kOther ? st.other : tm->walked(c)); };
 
     // merged list of (class ca, row ma) and (class cb, row mb); cb < 0: item A alone
     struct Span2 { int32_t begin, end, tiles; };
     bool count_only = false;
     auto merged = [&](int ca, int32_t ma, int cb, int32_t mb) {
-        const ClassLists &la = lists_of(ca);
-        const ClassLists &lb = lists_of(cb < 0 ? ca : cb);
+        const ClassLists &la = tm->walked(ca);
+        const ClassLists &lb = tm->walked(cb < 0 ? ca : cb);
         int64_t pa = la.row_ptr[ma], ea = la.row_ptr[ma + 1];
         int64_t pb = cb < 0 ? 0 : lb.row_ptr[mb], eb = cb < 0 ? 0 : lb.row_ptr[mb + 1];
         Span2 out{(int32_t)plan.ranges.size(), 0, 0};
@@ -1134,22 +1152,25 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         return p;
     };
 
-    std::vector<Span2> cache_stacked[6];
-    auto push_stacked = [&](int32_t kv, int c, int32_t first_id) {   // neighbouring tiles in pairs
-        const int32_t n = (int32_t)lists_of(c).row_tiles.size();
-        for (int32_t j = 0; j < n; j += 2) {
-            const bool pair = j + 1 < n;
-            const Span2 &sp = cached(cache_stacked[c], j / 2, (n + 1) / 2, [&] { return pair ? merged(c, j, c, j + 1) : merged(c, j, -1, 0); });
-            plan.items.push_back({kv * G, first_id + j, pair ? kv * G : -1, pair ? first_id + j + 1 : 0, sp.begin, sp.end, sp.tiles, 0});
+    int32_t text_lists = -1, other_lists = -1;   // where the lists of stacked tiles begin
+    auto push_stacked = [&](int32_t kv, const bs::StackedTiles::Kind &kind, int32_t first_id, int32_t &base) {
+        if (base < 0) {
+            base = (int32_t)plan.ranges.size();
+            plan.ranges.insert(plan.ranges.end(), kind.ranges.begin(), kind.ranges.end());
+        }
+        for (int32_t j = 0; j < kind.n_tiles; j += 2) {   // neighbouring tiles in pairs
+            const bs::StackedTiles::Unit &u = kind.units[j / 2];
+            const bool pair = j + 1 < kind.n_tiles;
+            plan.items.push_back({kv * G, first_id + j, pair ? kv * G : -1, pair ? first_id + j + 1 : 0, base + u.list_begin, base + u.list_end, u.n_tiles, 0});
         }
     };
     std::vector<int32_t> byclass[4], rest;
     for (int32_t kv = 0; kv < H / G; ++kv) {
-        if (n_text_tiles > 0) push_stacked(kv, kText, tm->M);
+        if (n_text_tiles > 0) push_stacked(kv, st.text, tm->M, text_lists);
         // (without stacked text rows these are among the tiles of every head)
         const bool all_dense = any_all_dense && all_dense_group(kv);
-        if (all_dense && st.n_other() > 0 && (n_text_tiles > 0 || !tm->geo.regrouped)) {
-            push_stacked(kv, kOther, tm->M + n_text_tiles);
+        if (all_dense && st.other.n_tiles > 0 && (n_text_tiles > 0 || !tm->geo.regrouped)) {
+            push_stacked(kv, st.other, tm->M + n_text_tiles, other_lists);
             continue;
         }
         for (int c = 0; c < 4; ++c) byclass[c].clear();
@@ -1471,7 +1492,7 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
         const bs::PairPlan &plan = tm->pairs;
         std::vector<uint8_t> want(tm->n_tiles), got_a(tm->n_tiles), got_b(tm->n_tiles);
         const bs::StackedTiles &st = tm->stacked;
-        const int32_t M = tm->M + st.n_text() + st.n_other();   // ids of query tiles
+        const int32_t M = tm->M + st.text.n_tiles + st.other.n_tiles;   // ids of query tiles
         std::vector<int32_t> seen((size_t)tm->n_q_heads * M, 0);
         // the states of an item: from the lists of its class, of a stacked tile from what its rows see one by one
         std::vector<std::vector<uint8_t>> stacked_states(M - tm->M);
@@ -1479,9 +1500,9 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
             if (tile < tm->M) return expand_states(tm->walked(tm->head_class[head]), tile, want);
             std::vector<uint8_t> &states = stacked_states[tile - tm->M];
             if (states.empty()) {
-                const bool text = tile - tm->M < st.n_text();
+                const bool text = tile - tm->M < st.text.n_tiles;
                 const int32_t n_rows = text ? tm->geo.n_text_rows() : tm->geo.n_other_rows();
-                const int64_t s0 = (int64_t)(tile - tm->M - (text ? 0 : st.n_text())) * tm->bm;
+                const int64_t s0 = (int64_t)(tile - tm->M - (text ? 0 : st.text.n_tiles)) * tm->bm;
                 std::vector<std::pair<int32_t, int32_t>> runs;
                 tm->geo.row_runs(text, (int32_t)(s0 / gqa_group), (int32_t)std::min<int64_t>(n_rows, (s0 + tm->bm - 1) / gqa_group + 1), runs);
                 states.assign(tm->n_tiles, 2);
@@ -1511,7 +1532,7 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
                 if (head < 0 || tile < tm->M) continue;
                 if (head % gqa_group != 0) return BS_EINVAL;
                 for (int32_t h = head; h < head + gqa_group; ++h)
-                    if (tile >= tm->M + st.n_text() && tm->head_class[h] != BS_DENSE) return BS_EINVAL;
+                    if (tile >= tm->M + st.text.n_tiles && tm->head_class[h] != BS_DENSE) return BS_EINVAL;
             }
             ++seen[(size_t)it.head_a * M + it.tile_a];
             if (it.head_b >= 0) ++seen[(size_t)it.head_b * M + it.tile_b];
@@ -1553,7 +1574,7 @@ extern "C" int bs_tilemap_pair_plan(bs_tilemap *tm, int32_t gqa_group, int64_t *
                     if (group[m] != (stacked ? 1 : 0) || (own != group && own[m] != 0)) return false;
                 return true;
             };
-            if (!once(m_text, tm->M, tm->M, tm->M + st.n_text()) || !once(0, m_text, tm->M + st.n_text(), M)) return BS_EINVAL;
+            if (!once(m_text, tm->M, tm->M, tm->M + st.text.n_tiles) || !once(0, m_text, tm->M + st.text.n_tiles, M)) return BS_EINVAL;
         }
         if (n_units) *n_units = (int64_t)plan.items.size();
         if (unit_tiles) *unit_tiles = tiles;
@@ -1586,7 +1607,7 @@ extern "C" int bs_tilemap_share_plan(bs_tilemap *tm, int32_t gqa_group, int32_t 
             if ((size_t)sp.queue_off[8] != sp.parts.size()) return BS_EINVAL;
 
             // the parts of every unit
-            const int32_t M = tm->M + (gqa_group > 0 ? tm->stacked.n_text() + tm->stacked.n_other() : 0);   // ids of query tiles
+            const int32_t M = tm->M + (gqa_group > 0 ? tm->stacked.text.n_tiles + tm->stacked.other.n_tiles : 0);   // ids of query tiles
             std::vector<int32_t> unit_of((size_t)tm->n_q_heads * M, -1);
             for (size_t u = 0; u < n_units; ++u) unit_of[(size_t)plan.items[u].head_a * M + plan.items[u].tile_a] = (int32_t)u;
             std::vector<std::vector<int32_t>> parts_of(n_units);

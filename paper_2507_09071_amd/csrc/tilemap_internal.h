@@ -152,11 +152,15 @@ static_assert(sizeof(UnitRecord) == 64, "one line; fetched by four lanes");
 // every head of the group -- text rows, and the other rows of a group whose heads are all Dense.  Their ids follow the M
 // tiles of a head: first those of the text rows, then those of the others.
 struct StackedTiles {
+    struct Unit { int32_t list_begin, list_end, n_tiles; };   // of `ranges`
+    struct Kind {
+        bool decided = false;
+        int32_t n_tiles = 0;              // query tiles; 0: not worth it
+        std::vector<Unit> units;          // of two neighbouring tiles, the last one of an odd number alone
+        std::vector<PairRange> ranges;
+    };
     int32_t gqa_group = 0;                // made for groups of this size; 0: not yet
-    bool text_decided = false, other_decided = false;
-    ClassLists text, other;               // no entries: not worth it
-    int32_t n_text() const { return (int32_t)text.row_tiles.size(); }
-    int32_t n_other() const { return (int32_t)other.row_tiles.size(); }
+    Kind text, other;
 };
 
 // The same for the kernels.

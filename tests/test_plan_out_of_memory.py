@@ -52,7 +52,7 @@ int main(int, char **argv)
     const int fails_at = !std::strcmp(argv[1], "other group size") ? 8 : (!std::strcmp(argv[1], "one head a unit") ? 0 : 4);
     bs_tilemap *right = map(argv[1]);
     expect(plan(right, 4) == BS_OK, "plan", -1);
-    expect(right->stacked.n_text() > 0, "stacked tiles", -1);
+    expect(right->stacked.text.n_tiles > 0, "stacked tiles", -1);
     for (long k = 0;; ++k) {
         bs_tilemap *tm = map(argv[1]);
         fail_after = k;

@@ -1,0 +1,46 @@
+"""Time of planning stacked query tiles: host time of every new map, next to the same number of units of two heads each."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2507_09071_amd import build
+
+DRIVER = r"""
+#include <algorithm>
+#include <chrono>
+#include <cstdio>
+#include "blindsight.h"
+#include "tilemap_internal.h"
+
+int main()
+{
+    std::vector<bs_span> spans;
+    for (int p = 30; p + 2000 < 28000; p += 2030) spans.push_back({p, p + 2000, 200});
+    const uint8_t dense[16] = {};
+    double best[2] = {1e9, 1e9};
+    for (int i = 0; i < 150; ++i)
+        for (int k = 0; k < 2; ++k) {   // groups of two heads are never stacked
+            bs_tilemap *tm = nullptr;
+            if (bs_build_tilemap_suffix(spans.data(), (int32_t)spans.size(), 28000, dense, 16, 5, 128, 64, 0, nullptr, 0, 512, 0, &tm) != BS_OK) return 1;
+            const auto begin = std::chrono::steady_clock::now();
+            bs_plan_pairs(tm, k ? 8 : 2);
+            best[k] = std::min(best[k], std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - begin).count());
+            if ((tm->stacked.other.n_tiles > 0) != (k == 1)) return 2;
+            bs_tilemap_destroy(tm);
+        }
+    std::printf("%.1f %.1f\n", best[0], best[1]);
+    return 0;
+}
+"""
+
+
+def test_about_what_units_of_two_heads_cost(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    (tmp_path / "driver.cpp").write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O3", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    os.path.join(build.CSRC, "tilemap.cpp"), str(tmp_path / "driver.cpp"), "-o", str(tmp_path / "driver")], check=True)
+    heads, stacked = map(float, subprocess.run([tmp_path / "driver"], check=True, capture_output=True, text=True).stdout.split())
+    assert stacked < 1.5 * heads, (heads, stacked)   # 1.2 times; 1.75 with lists per tile that are merged afterwards
