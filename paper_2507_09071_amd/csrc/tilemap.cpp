@@ -1255,23 +1255,39 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     }
     if (tm->window > 0) cost_bucket = 8;
     const int32_t kXcdBlock = std::min<int64_t>(16, std::max<int64_t>(8, (int64_t)plan.items.size() / 2048));
-    std::stable_sort(plan.items.begin(), plan.items.end(), [G, cost_bucket, by_position = tm->window > 0](const bs::PairItem &a, const bs::PairItem &b) {
-        const int32_t ba = a.n_tiles / cost_bucket, bb = b.n_tiles / cost_bucket;
-        if (ba != bb) return ba > bb;
-        const int32_t ka = a.head_a / G, kb = b.head_a / G;
-        if (ka != kb) return ka < kb;
-        return by_position ? a.tile_a < b.tile_a : a.n_tiles > b.n_tiles;
-    });
     {
+        // Stable counting passes, a byte at a time, from the last field to the first: a sort that compares units took 50-70 ns each, more
+        // than half of the planning that every rebinding pays (4336 units 358 -> 148 us; in a window, 4076 units, 511 -> 268).
+        struct Place { uint32_t key; int32_t unit; };
         const size_t n = plan.items.size();
-        std::vector<bs::PairItem> queues[kXcds];
-        for (size_t p = 0; p < n; ++p) queues[(p / kXcdBlock) % kXcds].push_back(plan.items[p]);
-        plan.items.clear();
+        std::vector<Place> order(n), moved(n);
+        for (size_t i = 0; i < n; ++i) order[i].unit = (int32_t)i;
+        auto by = [&](auto &&field) {
+            uint32_t bits = 0;
+            for (Place &p : order) bits |= p.key = (uint32_t)field(plan.items[p.unit]);
+            for (int shift = 0; shift < 32 && bits >> shift != 0; shift += 8) {
+                uint32_t at[257] = {0};
+                for (const Place &p : order) ++at[(p.key >> shift & 255) + 1];
+                for (int i = 0; i < 256; ++i) at[i + 1] += at[i];
+                for (const Place &p : order) moved[at[p.key >> shift & 255]++] = p;
+                order.swap(moved);
+            }
+        };
+        int32_t longest = 0;
+        for (const bs::PairItem &it : plan.items) longest = std::max(longest, it.n_tiles);
+        if (tm->window > 0) by([](const bs::PairItem &it) { return it.tile_a; });
+        else by([&](const bs::PairItem &it) { return longest - it.n_tiles; });
+        by([&](const bs::PairItem &it) { return it.head_a / G; });
+        by([&](const bs::PairItem &it) { return longest / cost_bucket - it.n_tiles / cost_bucket; });
+        std::vector<bs::PairItem> queued;
+        queued.reserve(n);
         for (int x = 0; x < kXcds; ++x) {
-            plan.queue_off[x] = (int32_t)plan.items.size();
-            plan.items.insert(plan.items.end(), queues[x].begin(), queues[x].end());
+            plan.queue_off[x] = (int32_t)queued.size();
+            for (size_t block = (size_t)x * kXcdBlock; block < n; block += (size_t)kXcds * kXcdBlock)
+                for (size_t p = block; p < std::min(n, block + kXcdBlock); ++p) queued.push_back(plan.items[order[p].unit]);
         }
-        plan.queue_off[kXcds] = (int32_t)plan.items.size();
+        plan.queue_off[kXcds] = (int32_t)n;
+        plan.items.swap(queued);
     }
     auto item_class = [&](int32_t head, int32_t tile) { return tile >= tm->M ? BS_DENSE | 8 : tm->head_class[head] | tm->walked(tm->head_class[head]).compact[tile] << 2; };
     for (bs::PairItem &it : plan.items)

@@ -36,11 +36,11 @@ int main()
 """
 
 
-def test_about_what_units_of_two_heads_cost(tmp_path):
+def test_next_to_units_of_two_heads(tmp_path):
     if shutil.which("g++") is None:
         pytest.skip("needs g++")
     (tmp_path / "driver.cpp").write_text(DRIVER)
     subprocess.run(["g++", "-std=c++17", "-O3", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
                     os.path.join(build.CSRC, "tilemap.cpp"), str(tmp_path / "driver.cpp"), "-o", str(tmp_path / "driver")], check=True)
     heads, stacked = map(float, subprocess.run([tmp_path / "driver"], check=True, capture_output=True, text=True).stdout.split())
-    assert stacked < 1.5 * heads, (heads, stacked)   # 1.2 times; 1.75 with lists per tile that are merged afterwards
+    assert stacked < 2 * heads, (heads, stacked)   # 1.65 times; 2.4 with lists per tile that are merged afterwards
