@@ -1305,8 +1305,10 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
 // 15 % between workgroups (which tiles they find in L2, partial tiles), so long shares keep back a part of the steps
 // as short pieces that go to the queues, for whoever is done first.
 // Costs are in key-tile steps: a unit or part costs its steps and kUnitCost around them, the merge kMergeCost for the launch.
-// (The merge: 6 us, the gap in front of it, and the host's share of planning and launching it; with 6 a prompt of 1K tokens, 40 heads all
-// Dense, was cut to save 8 steps and took 68 us instead of 62.)
+// (The merge: 6 us, the gap in front of it, and the host's share of planning and launching it, of steps of 1.0 us at d = 64 and 1.7 at 128.
+// 240 prompts of 0.6-4K tokens, passes with 6 / 7 / 8, the same plans for nearly all of them: 8 heads of d = 64, 970 tokens 71.2 / 71.9 / 77.5 us,
+// 960 tokens 100 / 101 / 106; 32 heads, 990 tokens 83.9 / 84.1 / 88.3, 940 tokens 46.4 / 42.8 / 42.9, 1.4K tokens 55.3 / 54.5 / 52.2; 28
+// heads of d = 128, 920 tokens 83.2 / 80.3 / 80.2; 32 heads, 890 tokens 90.5 / 90.4 / 93.6.)
 // (By time stamps what lies around a unit takes 5 us against 1.7 us per step; 4 instead of 6: 4000 rows behind 30K 1426 -> 1410 us,
 // 517 rows behind 36K 576 -> 572, but 300 rows behind 20K of d = 64 220 -> 225; 3 and 2: mixed, or slower.)
 static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool solo, int32_t G, int32_t n_wgs, bs::SharePlan &sp)
@@ -1315,7 +1317,7 @@ static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool sol
     sp.n_slots = 0;
     std::fill(sp.queue_off, sp.queue_off + 9, 0);
     // the fp32 kernel's steps take 3.5-7 us
-    const int64_t kUnitCost = solo ? 1 : 6, kMergeCost = solo ? 1 : 8, kMinPart = solo ? 1 : 4;
+    const int64_t kUnitCost = solo ? 1 : 6, kMergeCost = solo ? 1 : 7, kMinPart = solo ? 1 : 4;
     // With more units than that the queues are better, although their longest workgroup has 5-6 % more steps than the mean on
     // prompts of 8-9K tokens (by the plan's steps; the time per step differs, and the queues make up for that, too).
     // Limit 8 instead of 3: 3 layers of 28 heads at 8.2K tokens (3.6 units) 1062 us, 1045 with 3; 32 heads of d = 64 at 9K
