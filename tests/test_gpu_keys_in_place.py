@@ -1,5 +1,5 @@
-"""K tiles read where the caller has them (few fetches per tile) and packed ones (many), at prompt lengths around multiples of
-the 64-key tile, with and without compact tiles, in windows and for chunks."""
+"""The prompt's complete K tiles are read where the caller has them, a ragged last one and the compact tiles from packed copies: prompt
+lengths around multiples of the 64-key tile, with and without compact tiles, tiles fetched a few times and often, in windows and for chunks."""
 import numpy as np
 import pytest
 
@@ -31,7 +31,7 @@ def test_few_fetches(L, flags, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("G", [6, 8, 10, 12])   # some 32, 40, 50 and 60 fetches per tile: both sides of the rule
+@pytest.mark.parametrize("G", [6, 8, 10, 12])   # some 32 to 60 fetches per tile, 40 complete ones and one of 40 keys
 def test_many_fetches(G, d):
     full_parity(prompt(2600, 1, G, d), seed=72, flags=bs.BS_MAP_PACK_KEYS)
 
