@@ -331,6 +331,7 @@ template <int D, int KT>
 constexpr int bf16_slot_bytes() { return KT * kBlockN * D * 2; }   // of the ring: the K or V^T tiles of a step
 template <int D, int KT>
 constexpr int bf16_lds_bytes() { return 2 * kRing * bf16_slot_bytes<D, KT>() + kMailboxBytes + 7 * kPatchBytes; }
+static_assert(bf16_lds_bytes<128, 1>() <= 160 * 1024 && bf16_lds_bytes<64, 1>() <= 160 * 1024 && bf16_lds_bytes<64, 2>() <= 160 * 1024, "the CU's LDS");
 
 // One workgroup = two groups of four waves = one work unit: two (head, query tile) items that
 // read the same KV head and walk one merged key-tile list (heads of a GQA group with the same
@@ -1171,7 +1172,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     __bf16 *kp = static_cast<__bf16 *>(workspace);
     __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
     const int32_t in_place = tm->L / bs::kBlockN;
-    // one workgroup per CU (128 KB of LDS each), which take the units from the queues until they are empty
+    // one workgroup per CU (160 KB of LDS each; 96 KB for steps of one tile at d = 64), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     const size_t n_copy = units && !kv_packed ? units->n : 0;   // comes with the pre-pass
     hipError_t e = hipSuccess;
