@@ -97,9 +97,9 @@ class HipEvents:
 # Keyed by workload and row order of the map -> (bytes, summary under profiles/).
 MEASURED_TRAFFIC = {
     ("cfg2-qwen2vl7b-36k/paper10/seed0", "packed"): (4.64e9, "profiles/attn_prefill_bf16_d128_cfg2_36k.md"),
-    ("cfg3-qwen25vl32b-128k/paper10/seed0", "packed"): (50.6e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
-    ("cfg4-gemma3-27b-300k/paper10/seed0", "packed"): (314.7e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
-    ("cfg5-stress-307200/paper10/seed0", "packed"): (120.8e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
+    ("cfg3-qwen25vl32b-128k/paper10/seed0", "packed"): (49.6e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
+    ("cfg4-gemma3-27b-300k/paper10/seed0", "packed"): (317.1e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
+    ("cfg5-stress-307200/paper10/seed0", "packed"): (123.5e9, "profiles/attn_prefill_bf16_d128_128k_300k.md"),
 }
 
 

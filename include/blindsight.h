@@ -289,6 +289,8 @@ int bs_tilemap_upload(bs_tilemap *tm);
  * Calls that share a map share that workspace: the library orders a call after
  * the map's previous call when the stream changes, but two threads must not call with one map
  * at the same time.
+ * Values of k and v have to be finite: one that is not makes the rows that see its key not finite, and may reach
+ * rows that do not see the key but stand in one work unit with rows that do (calls with a few rows excepted).
  * The first call on a map uploads it: the arrays are staged through pinned host buffers and
  * copied on `stream`; the host does not wait for the device (it may wait for an upload queued
  * eight uploads earlier, whose staging buffer it reuses).

@@ -498,8 +498,8 @@ __device__ __forceinline__ void walk_units(
     // 32 cycles).  Anything in front of the first MFMA costs its full length: with the walk there the same kernel takes 2 % longer
     // (36K tokens 15573 us, 15220 with it here), with three walkers instead of the one and a look-ahead 3 % on windows.
     // The masks are asked for only where the item needs them (a sparse class without compact tiles, Intra-Image with mixed ones): a
-    // scalar load in flight is counted together with the operand reads, which are then waited for early.  302K tokens 188.2 ->
-    // 186.5 ms, 36K 15560 -> 15450 us.
+    // scalar load in flight is counted together with the operand reads, which are then waited for early.  This kernel asking for
+    // them at every step and as it is, one box: 302K tokens 185.1 / 182.8 ms, 36K 15599 / 15471 us, window of 1024 on 27K 1529 / 1517.
     bool need_bits = false;
     auto advance_walk = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);

@@ -981,6 +981,10 @@ static int64_t build_stacked(const bs_tilemap *tm, int32_t G, bool text, bs::Sta
 // end of a 36K prompt are a tile of 577 steps for every pair of heads, stacked in groups of seven 1 unit instead of 3.5.
 // A unit holds 256 rows either way, so groups of two gain nothing.  Stacked where that saves a thirtieth of the steps of these rows:
 // below, units of two kinds side by side share fewer tiles.  (The kernel counts the rows of a group in 32 bits.)
+// What lies around a unit is dearer with stacked rows, and in a short window a unit is ten steps long, but it has fewer of them: passes of
+// three all-Dense layers, stacked / not: window of 512, 28 / 4 heads, 2.8K tokens 159 / 184 us, 40 / 8, 3.2K 209 / 240, 32 / 8 of d = 64, 2.8K
+// 139 / 148, 16 / 2 (groups of eight, less than a unit a workgroup) 2.8K 126 / 129, 3.2K 134 / 130; window of 1024, 2.3K, 166 / 176, 218 / 225,
+// 144 / 144, 134 / 139; none, 1.5K, 139 / 145, 157 / 165, 117 / 121, 121 / 123.
 static void plan_stacked(bs_tilemap *tm, int32_t G, bool any_all_dense)
 {
     bs::StackedTiles &st = tm->stacked;
