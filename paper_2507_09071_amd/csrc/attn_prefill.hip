@@ -189,8 +189,8 @@ __device__ inline void lds_wait(bf16x8 (&a)[4])
 // form one chain of volatile statements, which the compiler keeps in program order, and the
 // accumulator is an in/out operand, so it is updated in place (no copies of the 64 output
 // registers).  The compiler does not see a matrix instruction here, so the wait states between
-// the last MFMA writing an accumulator and the first vector instruction reading it are
-// inserted by hand (mfma_drain) at the end of the chain.
+// the last MFMA writing an accumulator and the first vector instruction reading it are seen to
+// by hand: other work of at least that length at the end of the chain, mfma_drain behind a unit's last step.
 __device__ inline void mfma_acc(floatx16 &c, const bf16x8 &a, const bf16x8 &b)
 {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
@@ -577,34 +577,37 @@ __device__ __forceinline__ void walk_units(
             mul_one(cur, I3{}, f[3]); read_one(mid, I3{}, g[3]); read_one(nxt, I3{}, f[3]);
         };
         if constexpr (NPV == 4) {
-            // batch order: PV0 S0 PV1 S1 PV2 S2 PV3 S3, four reads / MFMAs each
+            // batch order: S0 PV0 S1 PV1 S2 PV2 S3 PV3, four reads / MFMAs each.  The scores are there four MFMAs before the end of
+            // the chain, so the vector phase starts under the last ones: with the scores last, and a wait for them, 36K tokens 16327 us,
+            // 16179 so, 2048 rows behind 141K keys 8489 -> 8406, 16K tokens characterised 3214 -> 3183.
             // Only two batches are read ahead of the first MFMA (the burst of all four waves of a group
             // costs every wave its share of the LDS time); the third goes out behind the first four
             // MFMAs together with their refills.
-            read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb);
-            lds_wait<4>(fa); batch2(PvBatch<0>{}, PvBatch<1>{}, fc, ScBatch<1, false>{}, fa);
-            lds_wait<8>(fb); batch(ScBatch<0, true>{}, PvBatch<2>{}, fb);
-            lds_wait<5>(fc); batch(PvBatch<1>{}, ScBatch<2, false>{}, fc);   // behind the last PV1 read: one S1 read, four PV2
-            lds_wait<8>(fa); batch(ScBatch<1, false>{}, PvBatch<3>{}, fa);
+            read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb);
+            lds_wait<4>(fa); batch2(ScBatch<0, true>{}, ScBatch<1, false>{}, fc, PvBatch<1>{}, fa);
+            lds_wait<8>(fb); batch(PvBatch<0>{}, ScBatch<2, false>{}, fb);
+            lds_wait<5>(fc); batch(ScBatch<1, false>{}, PvBatch<2>{}, fc);   // behind the last S1 read: one PV1 read, four S2
+            lds_wait<8>(fa); batch(PvBatch<1>{}, ScBatch<3, false>{}, fa);
             advance_walk();
-            lds_wait<8>(fb); batch(PvBatch<2>{}, ScBatch<3, false>{}, fb);
-            lds_wait<8>(fc); batch(ScBatch<2, false>{}, NoBatch{}, fc);
-            lds_wait<4>(fa); batch(PvBatch<3>{}, NoBatch{}, fa);
-            lds_wait<0>(fb); batch(ScBatch<3, false>{}, NoBatch{}, fb);
-            mfma_drain(s[0], s[1]);   // the PV accumulators finished four MFMAs earlier
-            if constexpr (KT == 2) asm volatile("" : "+v"(s[2]), "+v"(s[3]));
+            lds_wait<8>(fb); batch(ScBatch<2, false>{}, PvBatch<3>{}, fb);
+            lds_wait<8>(fc); batch(PvBatch<2>{}, NoBatch{}, fc);
+            lds_wait<4>(fa); batch(ScBatch<3, false>{}, NoBatch{}, fa);
+            lds_wait<0>(fb); batch(PvBatch<3>{}, NoBatch{}, fb);
         } else {
             // PV batches hold two reads / MFMAs, S has two batches of four
-            read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb); read_batch(PvBatch<1>{}, fc);   // 2 + 4 + 2
-            lds_wait<6>(fa); batch(PvBatch<0>{}, PvBatch<2>{}, fa);                     // 4 2 | 2
-            lds_wait<4>(fb); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fb);        // 2 2 | 4
-            lds_wait<6>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);                     // 2 4 | 2
+            read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb); read_batch(PvBatch<1>{}, fc);   // 4 + 2 + 2
+            lds_wait<4>(fa); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fa);        // 2 2 | 4
+            lds_wait<6>(fb); batch(PvBatch<0>{}, PvBatch<2>{}, fb);                     // 2 4 | 2
+            lds_wait<6>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);                     // 4 2 | 2
             advance_walk();
-            lds_wait<6>(fa); batch(PvBatch<2>{}, NoBatch{}, fa);
-            lds_wait<2>(fb); batch(ScBatch<1, false>{}, NoBatch{}, fb);
+            lds_wait<4>(fa); batch(ScBatch<1, false>{}, NoBatch{}, fa);
+            lds_wait<2>(fb); batch(PvBatch<2>{}, NoBatch{}, fb);
             lds_wait<0>(fc); batch(PvBatch<3>{}, NoBatch{}, fc);
-            mfma_drain(o[0], o[1]);   // the scores finished two MFMAs earlier
         }
+        // No wait for the accumulators: the last scores were finished by the MFMAs behind them, and the output tile is next
+        // touched at the end of the vector phase.  (The statement keeps the vector phase behind the chain.)
+        asm volatile("" : "+v"(s[0]), "+v"(s[1]));
+        if constexpr (KT == 2) asm volatile("" : "+v"(s[2]), "+v"(s[3]));
         // Every LDS read and scalar load of the phase has returned (the last lds_wait was for zero): say so
         // in a form the compiler sees, or it waits for its own scalar loads in the middle of the next chain.
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
