@@ -17,8 +17,9 @@
 //  * scores are produced transposed, S^T = K Q^T, with 32x32x16 bf16 MFMA tiles, so every lane
 //    holds 16 keys of ONE query per 32-key block: row max / row sum are in-lane reductions plus
 //    one exchange with the lane 32 apart (v_permlane32_swap);
-//  * O^T = V^T P^T reuses the probabilities, rounded to bf16, as the B operand; V^T comes from a
-//    pre-pass that writes it per key tile in exactly the layout the LDS reads want, K from where the caller has it;
+//  * O^T = V^T P^T reuses the probabilities, rounded to bf16, as the B operand; K comes from where the caller has it, V where
+//    its tiles are walked a few times and the operand reads transpose; where they are walked often, V^T comes from a
+//    pre-pass that writes it per key tile in exactly the layout the LDS reads want (see transposed_values);
 //  * K and V^T tiles travel global -> LDS with 16-byte LDS-direct loads (no VGPR staging) into a
 //    ring of 4 K + 4 V^T slots shared by the two groups; ONE barrier per key tile, placed so that
 //    on every SIMD one wave runs its matrix phase while the other runs its vector phase;
@@ -177,6 +178,13 @@ __device__ inline void lds_read_b128(bf16x8 &dst, uint32_t addr)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFFSET));
 }
 
+// The transposing read of four keys: a lane gets the values that these keys have in one channel.
+template <int OFFSET>
+__device__ inline void lds_read_tr_b64(bf16x4 &dst, uint32_t addr)
+{
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFFSET));
+}
+
 // Wait until at most N LDS operations are outstanding.  The operands tie the wait to the
 // registers it protects, so their consumers cannot be scheduled above it.
 template <int N>
@@ -207,7 +215,7 @@ __device__ inline void mfma_drain(floatx16 &c0, floatx16 &c1)
 
 
 // LDS tile layouts of the bf16 kernel.  V^T is written like that by the pre-pass below and copied verbatim by the kernel's
-// LDS-direct loads; those of K pick it from rows of keys.  Everything an MFMA operand read selects
+// LDS-direct loads; those of K, and of V where it is not transposed, pick it from rows of keys.  Everything an MFMA operand read selects
 // at compile time (head-dim slice, key block, key group, channel block) is an immediate offset
 // from a per-lane base address (two for K).
 //   K tile   [D/32 pairs of slices u][64 keys][64 B]   64 B = channels 32u..32u+31 of one key, as four 16-byte chunks c, stored at
@@ -217,6 +225,8 @@ __device__ inline void mfma_drain(floatx16 &c0, floatx16 &c1)
 //            as two halves h holding keys 16g + {4h..4h+3, 8+4h..8+4h+3} (the contraction slots
 //            of lane half h), stored at half h ^ ((channel >> 3) & 1)
 // A 128-bit read of 16 consecutive keys (channels) then touches every bank exactly once.
+//   V tile   as a K tile.  A transposing 64-bit read of a V operand takes, per lane half, 64 bytes of four neighbouring keys: every
+//            bank once.  An operand is two of them, eight keys apart, whose chunks are stored at ^ 2 of each other: two base addresses
 // The prompt's tiles hold its keys in position order, the compact tiles of a packed map the keys their slots
 // name; slots without a key are zero-filled.
 // Query rows lie in LDS as in memory but for their 16-byte chunks: chunk c of row r is at c ^ chunk_swap(r), rows that share their
@@ -260,14 +270,15 @@ __device__ inline void pack_vt_tile(const __bf16 *__restrict__ v, __bf16 *__rest
 }
 
 // The prompt's complete K tiles are not packed: the attention kernel reads them where the caller has them.  The others -- the
-// ragged last tile and the compact tiles, from tile `in_place` = L / 64 on -- hold their rows one behind the other as well.
+// ragged last tile and the compact tiles, from tile `in_place` = L / 64 on -- hold their rows one behind the other as well.  So do the
+// V tiles of a launch that reads V where the caller has it.
 template <int D>
-__device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restrict__ kp,
-                                   const int32_t *__restrict__ compact_keys, int L, int n, int N, int N0, int in_place)
+__device__ inline void pack_rows(const __bf16 *__restrict__ rows, __bf16 *__restrict__ packed,
+                                 const int32_t *__restrict__ compact_keys, int L, int n, int N, int N0, int in_place)
 {
     const int kvh = blockIdx.y;
-    const __bf16 *src = k + (size_t)kvh * L * D;
-    __bf16 *dst = kp + ((size_t)kvh * (N - in_place) + n - in_place) * (size_t)(D * kBlockN);
+    const __bf16 *src = rows + (size_t)kvh * L * D;
+    __bf16 *dst = packed + ((size_t)kvh * (N - in_place) + n - in_place) * (size_t)(D * kBlockN);
     for (int idx = threadIdx.x; idx < kBlockN * (D / 8); idx += 256) {   // 16 bytes per iteration
         const int key = idx / (D / 8), ch = idx % (D / 8);
         const int pos = slot_key(compact_keys, n, key, L, N0);
@@ -277,30 +288,32 @@ __device__ inline void pack_k_tile(const __bf16 *__restrict__ k, __bf16 *__restr
     }
 }
 
-// The pre-pass of a bf16 call, one launch: grid (V^T tiles, then the K tiles that lie nowhere else, then workgroups that
+// The pre-pass of a bf16 call, one launch: grid (V^T tiles or the V tiles that lie nowhere else, then such K tiles, then workgroups that
 // bring the work units from a pinned buffer; KV heads), of the
 // tiles that the units of the launch walk.  Bound: HBM, so what counts is what is not packed: a chunk of 300 rows in a window
 // of 1024 needs 21 of a 27K prompt's 429 tiles (three layers: 153 us, 253 with all of them), an all-Dense layer no compact
 // ones (2048 rows behind 141K keys 9089 -> 8824 us, with the text tiles of Intra-Image).
 struct PackTiles {
-    int32_t first[6], count[6];   // runs of V^T tiles (prompt, free keys, text keys), then of K tiles
+    int32_t first[6], count[6];   // runs of V tiles (prompt, free keys, text keys), then of K tiles
     int32_t n_tiles;              // all of them
+    int32_t transpose;            // V tiles: all of the prompt's, as V^T; else like the K tiles
 };
 template <int D>
 __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
-                                                     __bf16 *__restrict__ kp, __bf16 *__restrict__ vt,
+                                                     __bf16 *__restrict__ kp, __bf16 *__restrict__ vp,
                                                      const int32_t *__restrict__ compact_keys, int L, int N, int N0, int in_place,
                                                      PackTiles todo, int32_t *__restrict__ queue_ctr,
                                                      const uint4 *__restrict__ copy_src, uint4 *__restrict__ copy_dst, size_t n_copy)
 {
     __shared__ __bf16 tile[kBlockN * (D + 2)];
-    if ((int)blockIdx.x >= todo.n_tiles) {   // (with it come the unit queues, at their beginning)
+    if ((int)blockIdx.x >= todo.n_tiles && n_copy > 0) {   // (with it come the unit queues, at their beginning)
         const size_t stride = (size_t)(gridDim.x - todo.n_tiles) * gridDim.y * 256;
         for (size_t i = ((size_t)(blockIdx.x - todo.n_tiles) * gridDim.y + blockIdx.y) * 256 + threadIdx.x; i < n_copy; i += stride) copy_dst[i] = copy_src[i];
         return;
     }
     // the attention kernel that follows starts on fresh unit queues
     if (n_copy == 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 8) queue_ctr[threadIdx.x] = 0;
+    if ((int)blockIdx.x >= todo.n_tiles) return;
     int x = blockIdx.x, run = 0;
 #pragma unroll
     for (int i = 0; i < 5; ++i)
@@ -309,8 +322,8 @@ __global__ __launch_bounds__(256) void pack_kv_tiles(const __bf16 *__restrict__ 
 #pragma unroll
     for (int i = 1; i < 6; ++i) n = run == i ? todo.first[i] : n;
     n += x;
-    if (run >= 3) pack_k_tile<D>(k, kp, compact_keys, L, n, N, N0, in_place);
-    else pack_vt_tile<D>(v, vt, compact_keys, L, n, N, N0, tile);
+    if (run < 3 && todo.transpose) pack_vt_tile<D>(v, vp, compact_keys, L, n, N, N0, tile);
+    else pack_rows<D>(run < 3 ? v : k, run < 3 ? vp : kp, compact_keys, L, n, N, N0, in_place);
 }
 
 constexpr int kPingPongThreads = 512;
@@ -345,11 +358,13 @@ static_assert(bf16_lds_bytes<128, 1>() <= 160 * 1024 && bf16_lds_bytes<64, 1>() 
 // while the other is in Y, and the matrix pipe and the vector ALU stay busy together instead
 // of the two waves queueing for the same unit.
 // A step takes KT key tiles: one, and at d = 64 two where the lists are long (see steps_of_two).
-template <int D, int KT>
+// VT: V^T tiles, packed by the pre-pass; else V tiles lie as K tiles do, the complete ones of the prompt where the caller has them, and
+// the operand reads transpose.
+template <int D, int KT, bool VT>
 __device__ __forceinline__ void walk_units(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
-    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp,
     int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
 {
@@ -358,7 +373,8 @@ __device__ __forceinline__ void walk_units(
     constexpr int kSlotBytes = bf16_slot_bytes<D, KT>();   // of the ring: the tiles of a step
     constexpr int DMA_PER_WAVE = kSlotBytes / 8192;        // LDS-direct loads per wave per matrix per step (8 waves)
     constexpr int NDB = D / 32;           // 32-channel blocks of the output
-    constexpr int NPV = KT == 2 ? 4 : NDB;   // operand reads of a PV batch
+    constexpr int NPV = KT == 2 ? 4 : NDB;   // operands of a PV batch
+    constexpr int RPV = VT ? 1 : 2;          // reads of such an operand
     constexpr int NT = D / 16;            // 16-wide slices of the head dim
     extern __shared__ __align__(1024) unsigned char lds[];   // K slots 0..3, then V^T slots 0..3
 
@@ -375,8 +391,8 @@ __device__ __forceinline__ void walk_units(
     int head = 0, T = 0, item_class = 0;
     int slot_id = 0;                // > 0: a part of a cut unit, its results go to slot slot_id - 1
     bool have_item = false;
-    const char *kph = nullptr, *vth = nullptr;   // K / packed V^T tiles of the unit's KV head
-    const char *kpackh = nullptr;                // its other K tiles (packed), by the same numbers
+    const char *kph = nullptr, *vph = nullptr;            // K and V of the unit's KV head (VT: its V^T tiles)
+    const char *kpackh = nullptr, *vpackh = nullptr;      // its other tiles (packed), by the same numbers
     bf16x8 qreg[NT];                // Q^T operand: Q[row][16t + 8hl .. +8] for every 16-wide slice t
     QueryView qv;
 
@@ -384,7 +400,10 @@ __device__ __forceinline__ void walk_units(
     // tile layouts above): key or channel `col`, half hl; slices, blocks and groups are
     // immediate offsets, the ring slot is added per step.
     const uint32_t ring = (uint32_t)(uintptr_t)(lds_void_ptr)lds;
-    const uint32_t vaddr0 = ring + col * 32 + ((hl ^ ((col >> 3) & 1)) << 4);
+    // (a transposing read: 16 lanes name the 8-byte pieces of 32 bytes of four keys, a lane gets its channel; the operand's upper
+    // four keys lie eight rows further, at ^ 32)
+    const uint32_t vaddr0 = VT ? ring + col * 32 + ((hl ^ ((col >> 3) & 1)) << 4)
+                               : ring + (4 * hl + ((lane & 15) >> 2)) * 64 + (((2 * ((lane >> 4) & 1) + ((lane >> 1) & 1)) ^ hl) << 4) + (lane & 1) * 8;
     const uint32_t kaddr0 = ring + col * 64 + ((hl ^ ((col >> 2) & 3)) << 4);   // odd slices: ^ 32
 
     floatx16 o[NDB];
@@ -431,8 +450,8 @@ __device__ __forceinline__ void walk_units(
                      : "v"(dma_lane_off), "s"(src), "s"(dst)
                      : "memory", "m0");
     };
-    // (a walker always names a tile that this launch's pre-pass wrote, behind its list the last one)
-    auto tile_ptr = [&](const char *base, int n) { return base + (size_t)n * TILE; };
+    // (a walker always names a tile that is there, behind its list the last one)
+    auto v_ptr = [&](int n) { return (VT || n < in_place ? vph : vpackh) + (size_t)n * TILE; };
     auto k_ptr = [&](int n) { return (n < in_place ? kph : kpackh) + (size_t)n * TILE; };
     // The same for a K tile, whose rows lie one behind the other: 64 bytes of 16 rows per instruction, as many lookups in the vector
     // cache as for a copy (the other waves read the rest of the lines at the same time).  A lane picks the 16 bytes that belong
@@ -449,18 +468,32 @@ __device__ __forceinline__ void walk_units(
                      : "v"(kdma_lane_off), "s"(src), "s"(dst)
                      : "memory", "m0");
     };
+    auto vdma = [&](int r, const char *const (&tiles)[KT], int slot_byte) __attribute__((always_inline)) {
+        if constexpr (VT) dma(r, tiles, slot_byte);
+        else kdma(r, tiles, slot_byte);
+    };
 
     // ---- phase X building blocks (step k reads K slot k mod 4 and V^T slot (k - 1) mod 4) ----
     // A batch is four 128-bit operand reads feeding four MFMAs:
     //   PV batch g: O^T block db += V^T(db, group g) . P^T(group g); two tiles a step: key groups 2g and 2g + 1, db = 0, 1
     //   S  batch b: head-dim slices 2b, 2b+1 for both 32-key blocks; two tiles a step: slice b for the four of them
-    uint32_t kbase = 0, kbase_odd = 0, vbase = 0;  // fragment base addresses inside the ring slots of this step
+    uint32_t kbase = 0, kbase_odd = 0, vbase = 0, vbase_upper = 0;  // fragment base addresses inside the ring slots of this step
     // one operand read / one MFMA of a batch (element i = 0..3)
     auto read_one = [&](auto tag, auto ic, bf16x8 &dst) __attribute__((always_inline)) {
         using T = decltype(tag);
         constexpr int i = decltype(ic)::value;
         if constexpr (T::kind == 1) {
-            if constexpr (i < NPV) lds_read_b128<T::idx * NPV * 1024 + i * 1024>(dst, vbase);   // channel block i (two tiles: i & 1 of group 2 idx + (i >> 1))
+            // channel block i (two tiles: i & 1 of group 2 idx + (i >> 1))
+            if constexpr (i < NPV && VT) {
+                lds_read_b128<T::idx * NPV * 1024 + i * 1024>(dst, vbase);
+            } else if constexpr (i < NPV) {
+                constexpr int group = KT == 1 ? T::idx : 2 * T::idx + (i >> 1);
+                constexpr int at = (group >> 2) * TILE + (i % NDB) * 4096 + (group & 3) * 1024;
+                bf16x4 lower, upper;
+                lds_read_tr_b64<at>(lower, vbase);
+                lds_read_tr_b64<at + 512>(upper, vbase_upper);
+                dst = __builtin_shufflevector(lower, upper, 0, 1, 2, 3, 4, 5, 6, 7);
+            }
         } else if constexpr (T::kind == 2) {
             if constexpr (KT == 1) lds_read_b128<T::idx * 4096 + (i & 1) * 2048>(dst, (i >> 1) ? kbase_odd : kbase);   // slice 2 idx + (i >> 1), key block
             else lds_read_b128<(T::idx >> 1) * 4096 + (i >> 1) * TILE + (i & 1) * 2048>(dst, (T::idx & 1) ? kbase_odd : kbase);   // slice idx, key block i
@@ -507,7 +540,7 @@ __device__ __forceinline__ void walk_units(
         for (int t = 0; t < KT; ++t) {
             if constexpr (KT == 1) {
                 ksrc[t] = k_ptr(walk.cur >> 4);
-                vsrc[t] = tile_ptr(vth, tile_3[t] >> 4);
+                vsrc[t] = v_ptr(tile_3[t] >> 4);
             }
             tile_y[t] = tile_1[t];
             tile_1[t] = tile_2[t];
@@ -533,13 +566,13 @@ __device__ __forceinline__ void walk_units(
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 ksrc[t] = k_ptr(tile_3[t] >> 4);
-                vsrc[t] = tile_ptr(vth, tile_2[t] >> 4);
+                vsrc[t] = v_ptr(tile_2[t] >> 4);
             }
         }
 #pragma unroll
         for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, ksrc, Sk_dst * kSlotBytes);
 #pragma unroll
-        for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, vsrc, (kRing + Sv_dst) * kSlotBytes);
+        for (int r = 0; r < DMA_PER_WAVE; ++r) vdma(r, vsrc, (kRing + Sv_dst) * kSlotBytes);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto phase_x = [&](int S, int Sv, auto refill_here) __attribute__((always_inline)) {  // S = k mod 4, Sv: slot of V^T(k-1)
@@ -548,6 +581,7 @@ __device__ __forceinline__ void walk_units(
         kbase = kaddr0 + S * kSlotBytes;
         kbase_odd = kbase ^ 32;
         vbase = vaddr0 + (kRing + Sv) * kSlotBytes;
+        vbase_upper = vbase ^ 32;
         bf16x8 fa[4], fb[4], fc[4];
         if constexpr (NPV < 4) {
 #pragma unroll
@@ -577,31 +611,32 @@ __device__ __forceinline__ void walk_units(
             mul_one(cur, I3{}, f[3]); read_one(mid, I3{}, g[3]); read_one(nxt, I3{}, f[3]);
         };
         if constexpr (NPV == 4) {
-            // batch order: S0 PV0 S1 PV1 S2 PV2 S3 PV3, four reads / MFMAs each.  The scores are there four MFMAs before the end of
+            // batch order: S0 PV0 S1 PV1 S2 PV2 S3 PV3, four MFMAs each, with four reads (eight for a PV batch that transposes).  The
+            // scores are there four MFMAs before the end of
             // the chain, so the vector phase starts under the last ones: with the scores last, and a wait for them, 36K tokens 16327 us,
             // 16179 so, 2048 rows behind 141K keys 8489 -> 8406, 16K tokens characterised 3214 -> 3183.
             // Only two batches are read ahead of the first MFMA (the burst of all four waves of a group
             // costs every wave its share of the LDS time); the third goes out behind the first four
             // MFMAs together with their refills.
             read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb);
-            lds_wait<4>(fa); batch2(ScBatch<0, true>{}, ScBatch<1, false>{}, fc, PvBatch<1>{}, fa);
-            lds_wait<8>(fb); batch(PvBatch<0>{}, ScBatch<2, false>{}, fb);
-            lds_wait<5>(fc); batch(ScBatch<1, false>{}, PvBatch<2>{}, fc);   // behind the last S1 read: one PV1 read, four S2
-            lds_wait<8>(fa); batch(PvBatch<1>{}, ScBatch<3, false>{}, fa);
+            lds_wait<4 * RPV>(fa); batch2(ScBatch<0, true>{}, ScBatch<1, false>{}, fc, PvBatch<1>{}, fa);
+            lds_wait<4 + 4 * RPV>(fb); batch(PvBatch<0>{}, ScBatch<2, false>{}, fb);
+            lds_wait<4 + RPV>(fc); batch(ScBatch<1, false>{}, PvBatch<2>{}, fc);   // behind the last S1 read: the last of PV1, four S2
+            lds_wait<4 + 4 * RPV>(fa); batch(PvBatch<1>{}, ScBatch<3, false>{}, fa);
             advance_walk();
-            lds_wait<8>(fb); batch(ScBatch<2, false>{}, PvBatch<3>{}, fb);
-            lds_wait<8>(fc); batch(PvBatch<2>{}, NoBatch{}, fc);
-            lds_wait<4>(fa); batch(ScBatch<3, false>{}, NoBatch{}, fa);
+            lds_wait<4 + 4 * RPV>(fb); batch(ScBatch<2, false>{}, PvBatch<3>{}, fb);
+            lds_wait<4 + 4 * RPV>(fc); batch(PvBatch<2>{}, NoBatch{}, fc);
+            lds_wait<4 * RPV>(fa); batch(ScBatch<3, false>{}, NoBatch{}, fa);
             lds_wait<0>(fb); batch(PvBatch<3>{}, NoBatch{}, fb);
         } else {
-            // PV batches hold two reads / MFMAs, S has two batches of four
-            read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb); read_batch(PvBatch<1>{}, fc);   // 4 + 2 + 2
-            lds_wait<4>(fa); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fa);        // 2 2 | 4
-            lds_wait<6>(fb); batch(PvBatch<0>{}, PvBatch<2>{}, fb);                     // 2 4 | 2
-            lds_wait<6>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);                     // 4 2 | 2
+            // PV batches are half as large, S has two batches of four
+            read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb); read_batch(PvBatch<1>{}, fc);
+            lds_wait<4 * RPV>(fa); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fa);
+            lds_wait<4 + 2 * RPV>(fb); batch(PvBatch<0>{}, PvBatch<2>{}, fb);
+            lds_wait<4 + 2 * RPV>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);
             advance_walk();
-            lds_wait<4>(fa); batch(ScBatch<1, false>{}, NoBatch{}, fa);
-            lds_wait<2>(fb); batch(PvBatch<2>{}, NoBatch{}, fb);
+            lds_wait<4 * RPV>(fa); batch(ScBatch<1, false>{}, NoBatch{}, fa);
+            lds_wait<2 * RPV>(fb); batch(PvBatch<2>{}, NoBatch{}, fb);
             lds_wait<0>(fc); batch(PvBatch<3>{}, NoBatch{}, fc);
         }
         // No wait for the accumulators: the last scores were finished by the MFMAs behind them, and the output tile is next
@@ -628,6 +663,7 @@ __device__ __forceinline__ void walk_units(
     // The last step: O += P(T-1) V(T-1), nothing else.
     auto phase_last = [&](int Sv) __attribute__((always_inline)) {
         vbase = vaddr0 + (kRing + Sv) * kSlotBytes;
+        vbase_upper = vbase ^ 32;
         bf16x8 fa[4], fb[4], fc[4];
         if constexpr (NPV < 4) {
 #pragma unroll
@@ -643,10 +679,11 @@ __device__ __forceinline__ void walk_units(
             mul_one(tag, I0{}, f[0]); mul_one(tag, I1{}, f[1]);
             mul_one(tag, I2{}, f[2]); mul_one(tag, I3{}, f[3]);
         };
-        read_batch(PvBatch<0>{}, fa); read_batch(PvBatch<1>{}, fb); read_batch(PvBatch<2>{}, fc);
-        lds_wait<2 * NPV>(fa); mul_batch(PvBatch<0>{}, fa); read_batch(PvBatch<3>{}, fa);
-        lds_wait<2 * NPV>(fb); mul_batch(PvBatch<1>{}, fb);
-        lds_wait<NPV>(fc); mul_batch(PvBatch<2>{}, fc);
+        constexpr int kReads = NPV * RPV;   // of a batch
+        read_batch(PvBatch<0>{}, fa); read_batch(PvBatch<1>{}, fb);
+        lds_wait<kReads>(fa); mul_batch(PvBatch<0>{}, fa); read_batch(PvBatch<2>{}, fc);
+        lds_wait<kReads>(fb); mul_batch(PvBatch<1>{}, fb); read_batch(PvBatch<3>{}, fa);
+        lds_wait<kReads>(fc); mul_batch(PvBatch<2>{}, fc);
         lds_wait<0>(fa); mul_batch(PvBatch<3>{}, fa);
         mfma_drain(o[0], o[1]);
         if constexpr (NDB > 2) asm volatile("" : "+v"(o[2]), "+v"(o[3]));
@@ -834,7 +871,12 @@ __device__ __forceinline__ void walk_units(
             // one TILE-byte block per key tile
             kph = reinterpret_cast<const char *>(a.k) + (size_t)kvh * L * ROW;
             kpackh = reinterpret_cast<const char *>(kp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
-            vth = reinterpret_cast<const char *>(vt + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
+            if constexpr (VT) {
+                vph = reinterpret_cast<const char *>(vp + (size_t)kvh * n_k_tiles * (size_t)(D * kBlockN));
+            } else {
+                vph = reinterpret_cast<const char *>(a.v) + (size_t)kvh * L * ROW;
+                vpackh = reinterpret_cast<const char *>(vp) + ((int64_t)kvh * (n_k_tiles - in_place) - in_place) * (int64_t)TILE;
+            }
         }
 
         // epilogue of the previous unit: divide by the running sum, round, store.  Empty rows (l = 0) give zeros.  A lane holds
@@ -899,7 +941,7 @@ __device__ __forceinline__ void walk_units(
             for (int t = 0; t < KT; ++t) {
                 tile_1[t] = T > 0 ? rec[8 + t] : none;
                 tile_2[t] = T > 0 ? rec[8 + KT + t] : none;
-                k0[t] = k_ptr(tile_1[t] >> 4); k1[t] = k_ptr(tile_2[t] >> 4); v0[t] = tile_ptr(vth, tile_1[t] >> 4);
+                k0[t] = k_ptr(tile_1[t] >> 4); k1[t] = k_ptr(tile_2[t] >> 4); v0[t] = v_ptr(tile_1[t] >> 4);
             }
             // K(0), K(1) and V^T(0) to the slots of these numbers (unconditional)
 #pragma unroll
@@ -907,7 +949,7 @@ __device__ __forceinline__ void walk_units(
 #pragma unroll
             for (int r = 0; r < DMA_PER_WAVE; ++r) kdma(r, k1, kSlotBytes);
 #pragma unroll
-            for (int r = 0; r < DMA_PER_WAVE; ++r) dma(r, v0, kRing * kSlotBytes);
+            for (int r = 0; r < DMA_PER_WAVE; ++r) vdma(r, v0, kRing * kSlotBytes);
             // (the walker stands on the fourth tile; with two tiles a step it walks on while the loads are on their way)
             walk = {pair_ranges, T > 0 ? rec[11] : none, T > 0 ? rec[12] : none + 16, rec[13], rec[14], rec[15], rec[7]};
             if constexpr (KT == 1) {
@@ -923,7 +965,7 @@ __device__ __forceinline__ void walk_units(
 #pragma unroll
             for (int t = 0; t < KT; ++t) {
                 ksrc[t] = k_ptr(tile_3[t] >> 4);
-                vsrc[t] = tile_ptr(vth, tile_2[t] >> 4);
+                vsrc[t] = v_ptr(tile_2[t] >> 4);
             }
         }
         if constexpr (NDB == 4) {
@@ -1022,22 +1064,44 @@ template <int D>
 __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
-    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp,
     int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
 {
-    walk_units<D, 1>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vt, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
+    walk_units<D, 1, true>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vp, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
 }
 
 template <int D>
 __global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16_two(
     KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
     const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
-    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vt,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp,
     int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
     const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
 {
-    walk_units<D, 2>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vt, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
+    walk_units<D, 2, true>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vp, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
+}
+
+template <int D>
+__global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16_v(
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp,
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
+{
+    walk_units<D, 1, false>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vp, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
+}
+
+template <int D>
+__global__ __launch_bounds__(kPingPongThreads, 2) void attn_prefill_bf16_two_v(
+    KernelArgs a, const uint64_t *__restrict__ map_text_bits, const uint64_t *__restrict__ map_sink_bits,
+    const int4 *__restrict__ map_rows, const UnitRecord *__restrict__ units,
+    const int2 *__restrict__ pair_ranges, const __bf16 *__restrict__ kp, const __bf16 *__restrict__ vp,
+    int32_t n_k_tiles, int32_t *__restrict__ queue_ctr, const int32_t *__restrict__ queue_off,
+    const int32_t *__restrict__ share_off, const StackedRows *__restrict__ stacked, float *__restrict__ cut_results)
+{
+    walk_units<D, 2, false>(a, map_text_bits, map_sink_bits, map_rows, units, pair_ranges, kp, vp, n_k_tiles, queue_ctr, queue_off, share_off, stacked, cut_results);
 }
 
 }  // namespace bs
@@ -1074,6 +1138,9 @@ int device_setup(int dev, void **scratch_out, int *n_cus_out)
         lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16<128>), bs::bf16_lds_bytes<128, 1>());
         lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16<64>), bs::bf16_lds_bytes<64, 1>());
         lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16_two<64>), bs::bf16_lds_bytes<64, 2>());
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16_v<128>), bs::bf16_lds_bytes<128, 1>());
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16_v<64>), bs::bf16_lds_bytes<64, 1>());
+        lds_limit(reinterpret_cast<const void *>(bs::attn_prefill_bf16_two_v<64>), bs::bf16_lds_bytes<64, 2>());
         if (e == hipSuccess) e = bs::f32_device_setup();
         if (e == hipSuccess) e = bs::rows_device_setup();
         if (e != hipSuccess) return bs::fail_hip(e, "hipFuncSetAttribute");
@@ -1163,18 +1230,43 @@ bool steps_of_two(const DeviceMap *d, const bs::ShareSet *sh)
     return d->n_steps >= kTilesPerUnit * std::max(d->n_pairs, sh ? sh->n_shares : 0);
 }
 
-// Pre-pass (K and V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
-// holds these tiles already and the binding was just uploaded, its queue counters at zero.  sh: null, the queues.  k_bytes:
+// Whether the pre-pass transposes V for a launch of the bf16 kernel.  If not, V tiles come from where the caller has them and the
+// operand reads transpose: two reads of 64 bits for one of 128, at half the rate, so a step takes 0.04-0.055 us longer (2.3 % on 36K
+// tokens at d = 128, 4-5 % at d = 64), 0.15-0.2 ns a step with 256 workgroups; V^T costs 32 KB of traffic a tile at d = 128, 6 ns.
+// The line lies at the tiles' quotient.  Passes with V^T / V, by steps a tile: 6-11 (window of 1024 on 27K) 1613 / 1553 us, 6-15 (517
+// rows behind 36K) 612 / 580, 10 and 43 (2048 rows behind 141K) 8406 / 8307; 36 and 74 (d = 64, 9K) 847 / 862, 55 and 115 (8K) 1029 /
+// 1036, 167 and 546 (36K) 16179 / 16459.
+template <int D>
+bool transposed_values(const DeviceMap *d, const TileRuns &read, int n_kv_heads)
+{
+    constexpr int64_t kStepsPerTile = D == 128 ? 32 : 14;
+    int64_t tiles = 0;
+    for (int i = 0; i < 3; ++i) tiles += read.end[i] - read.first[i];
+    return d->n_steps >= kStepsPerTile * tiles * n_kv_heads;
+}
+
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
+// Pre-pass (K and V or V^T into per-key-tile blocks of `workspace`) and the attention kernel.  kv_packed: the workspace
+// holds these tiles already and the binding was just uploaded, its queue counters at zero; shared_pack: they are for calls with several
+// bindings.  sh: null, the queues.  k_bytes:
 // what the packed K tiles take, in front of the V^T tiles.  units: the copy of the work units, if it is still to do.  A launch that
 // fails is the last one: the kernels behind it would read what it did not write.
 template <int D>
 hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *d, const TileRuns &todo_tiles, void *workspace, size_t k_bytes,
-                       float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
+                       float *cut_results, int n_kv_heads, int n_cus, const bs::ShareSet *sh, bool shared_pack, bool kv_packed, bs::PendingCopy *units, hipStream_t st, void *ev_main_start)
 {
     a.first_tile = todo_tiles.first[0];
     __bf16 *kp = static_cast<__bf16 *>(workspace);
-    __bf16 *vt = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
+    __bf16 *vp = reinterpret_cast<__bf16 *>(static_cast<char *>(workspace) + k_bytes);
     const int32_t in_place = tm->L / bs::kBlockN;
+    // (a result that is written over V needs the copy, and the calls that share a pre-pass take what it made)
+    const size_t row_bytes = (size_t)D * 2;
+    const bool transpose = shared_pack || transposed_values<D>(d, todo_tiles, n_kv_heads) ||
+                           overlap(a.out, row_bytes * tm->n_q_heads * (tm->L - tm->q_begin), a.v, row_bytes * n_kv_heads * tm->L);
     // one workgroup per CU (160 KB of LDS each; 96 KB for steps of one tile at d = 64), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);
     const size_t n_copy = units && !kv_packed ? units->n : 0;   // comes with the pre-pass
@@ -1185,7 +1277,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
         bs::PackTiles todo;
         int32_t n_todo = 0;
         for (int i = 0; i < 6; ++i) {
-            const int32_t first = std::max(todo_tiles.first[i % 3], i < 3 ? 0 : in_place);
+            const int32_t first = std::max(todo_tiles.first[i % 3], i < 3 && transpose ? 0 : in_place);
             todo.first[i] = first;
             todo.count[i] = std::max(0, todo_tiles.end[i % 3] - first);
             n_todo += todo.count[i];
@@ -1194,8 +1286,9 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
         const size_t copy_wgs = std::min<size_t>((n_copy + 255) / 256, 1024);
         const size_t copy_x = (copy_wgs + n_kv_heads - 1) / n_kv_heads;
         todo.n_tiles = n_todo;
-        e = bs::launch_kernel(bs::pack_kv_tiles<D>, dim3((unsigned)(n_todo + copy_x), (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
-                              static_cast<const __bf16 *>(a.v), kp, vt, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr,
+        todo.transpose = transpose;
+        e = bs::launch_kernel(bs::pack_kv_tiles<D>, dim3((unsigned)std::max<size_t>(n_todo + copy_x, 1), (unsigned)n_kv_heads), dim3(256), 0, st, static_cast<const __bf16 *>(a.k),
+                              static_cast<const __bf16 *>(a.v), kp, vp, d->compact_keys, tm->L, tm->n_tiles, tm->N0, in_place, todo, d->queue_ctr,
                               n_copy ? units->src : nullptr, n_copy ? units->dst : nullptr, n_copy);
         if (e != hipSuccess && n_copy) bs::staging_abandon(units->staging);
     }
@@ -1203,12 +1296,15 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     if (ev_main_start) (void)hipEventRecord(static_cast<hipEvent_t>(ev_main_start), st);
     const auto launch = [&](auto *kernel, int lds_bytes) {
         return bs::launch_kernel(kernel, pgrid, pblock, lds_bytes, st, a, d->text_bits,
-                                 d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vt, tm->n_tiles,
+                                 d->sink_bits, d->rows, sh ? sh->units : d->units, sh ? sh->ranges : d->pair_ranges, kp, vp, tm->n_tiles,
                                  d->queue_ctr, sh ? sh->queue_off : d->queue_off, sh ? sh->off : nullptr, d->stacked, cut_results);
     };
-    if constexpr (D == 128) e = launch(&bs::attn_prefill_bf16<128>, bs::bf16_lds_bytes<128, 1>());
-    else if (steps_of_two(d, sh)) e = launch(&bs::attn_prefill_bf16_two<64>, bs::bf16_lds_bytes<64, 2>());
-    else e = launch(&bs::attn_prefill_bf16<64>, bs::bf16_lds_bytes<64, 1>());
+    if constexpr (D == 64) {
+        if (steps_of_two(d, sh)) e = launch(transpose ? &bs::attn_prefill_bf16_two<64> : &bs::attn_prefill_bf16_two_v<64>, bs::bf16_lds_bytes<64, 2>());
+        else e = launch(transpose ? &bs::attn_prefill_bf16<64> : &bs::attn_prefill_bf16_v<64>, bs::bf16_lds_bytes<64, 1>());
+    } else {
+        e = launch(transpose ? &bs::attn_prefill_bf16<128> : &bs::attn_prefill_bf16_v<128>, bs::bf16_lds_bytes<128, 1>());
+    }
     if (e == hipSuccess && sh && sh->n_cut > 0)
         e = bs::launch_kernel(bs::merge_cut_items<D, 2, __bf16>, dim3((unsigned)sh->n_cut, 4, D / 32), dim3(64), 0, st, a, sh->cut_items,
                               d->rows, d->stacked, cut_results);
@@ -1254,7 +1350,7 @@ size_t bf16_pack_bytes(int32_t n_tiles, int n_kv_heads, int head_dim)
     return (size_t)n_kv_heads * n_tiles * (size_t)head_dim * bs::kBlockN * 2;   // of K or V^T
 }
 
-// What the pre-pass writes: the K tiles that are not read in place, then all V^T tiles.
+// What the pre-pass writes at most: the K tiles that are not read in place, then all V^T tiles.
 struct PackBytes { size_t k, all; };
 PackBytes bf16_pack_bytes(const bs_tilemap *tm, int n_kv_heads, int head_dim)
 {
@@ -1378,8 +1474,8 @@ int bs::attn_prefill(const void *q, const void *k, const void *v, void *out, bs_
         float *const cut = reinterpret_cast<float *>(static_cast<char *>(d->vt_buf) + pack.all);
         // (a caller with several bindings of the map packs for all of them)
         const TileRuns todo = tiles_read(tm, kv_packed != nullptr);
-        e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start)
-                            : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, packed, &units, st, ev_main_start);
+        e = head_dim == 128 ? launch_bf16<128>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, kv_packed != nullptr, packed, &units, st, ev_main_start)
+                            : launch_bf16<64>(a, tm, d, todo, d->vt_buf, pack.k, cut, n_kv_heads, n_cus, sh, kv_packed != nullptr, packed, &units, st, ev_main_start);
         if (e != hipSuccess) {
             d->bind_kind = bs::kBindNone;   // the units may not have arrived
             if (kv_packed) *kv_packed = false;
@@ -1457,8 +1553,8 @@ extern "C" int bs_attn_prefill_static(const void *q, const void *k, const void *
     // call's contents is
     e = hipSuccess;
     if (rows.use) bs::launch_rows(rows, q, k, v, out, tm, d, ws, gqa_group, head_dim, scale, st);
-    else if (head_dim == 128) e = launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
-    else e = launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, nullptr, st, nullptr);
+    else if (head_dim == 128) e = launch_bf16<128>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, false, nullptr, st, nullptr);
+    else e = launch_bf16<64>(a, tm, d, tiles_read(tm, false), ws, pack.k, cut, n_kv_heads, n_cus, sh, false, false, nullptr, st, nullptr);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return bs::fail_hip(e, "kernel launch");
     e = hipEventRecord(d->last_use->ev, st);
