@@ -3,9 +3,9 @@
 // The 128-row query tiles of the prefill kernel are the wrong shape here.  The work is reading K and V once,
 // so the bound is HBM, and what the prefill path does around it (a packed copy of V, a K and V tile per two heads, units
 // cut over the chip and merged) costs a multiple of the read.  Measured, one row: 28 heads over 39.5K keys of
-// 4 KV heads (81 MB) 103 us there, 17.4 + 4.1 us here (4.7 TB/s in the first kernel, a kernel that only reads reaches 5.3
-// on so little; 18.5 + 5 with the query rows and the rows' bounds loaded before the first keys were requested, and the
-// merge waiting for memory twice); 32 heads over 302K keys of 16 KV heads (2.5 GB) 1060 us there, 413 + 4 us here (6.0
+// 4 KV heads (81 MB) 103 us there, 21.0 us a call here, two kernels (by time stamps: 1.3 us until the first keys are requested,
+// 7.2 TB/s from there until the last ones have arrived at 14 us; 1.2 us to the end of the first kernel; the merge; a kernel that only
+// reads takes 15.3 us for so little); 32 heads over 302K keys of 16 KV heads (2.5 GB) 1060 us there, 412 + 4 us here (6.0
 // TB/s; a kernel that only reads reaches 6.2).  How:
 //  * the query rows of ALL heads of a GQA group are stacked (head-major) into blocks of 32 rows, the free
 //    dimension of a 32x32x16 MFMA, so K and V of a KV head are read once for the whole group;
@@ -84,6 +84,48 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     const int part = blockIdx.x, kvh = blockIdx.y, grp = blockIdx.z, n_parts = gridDim.x;
     const int S = a.G * a.R;   // stacked rows of a KV head
 
+    // ---- key blocks of this wave
+    const int b_begin = part * a.blocks_each + min(part, a.blocks_more);
+    const int b_end = b_begin + a.blocks_each + (part < a.blocks_more ? 1 : 0);
+    const int n_steps = b_end - b_begin > wave ? (b_end - b_begin - wave + kRowsWaves - 1) / kRowsWaves : 0;
+    const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * a.L * ROWB;
+    const char *vh = static_cast<const char *>(a.v) + (size_t)kvh * a.L * ROWB;
+    auto block_of = [&](int i) { return a.k0 + b_begin + wave + kRowsWaves * i; };
+
+    // LDS-direct loads of a block: instruction j moves 1 KB, i.e. 1024 / ROWB whole rows; a lane picks the chunk
+    // of its row that belongs at its place.
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const uint32_t ring = (uint32_t)(uintptr_t)(lds_ptr)lds + wave * TR::kWave;
+    uint32_t voff[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int r = j * (1024 / ROWB) + lane / (ROWB / 16), p = lane % (ROWB / 16);
+        voff[j] = r * ROWB + ((p ^ TR::swizzle(r)) << 4);
+    }
+    auto issue = [&](const char *base, int blk, uint32_t dst) __attribute__((always_inline)) {
+        const char *src = base + (size_t)blk * BLK;
+        const int rows_left = a.L - blk * kRowsKeys;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            uint32_t off = voff[j];
+            if (rows_left < kRowsKeys) {   // the last block of the cache: rows past its end repeat the last one (masked)
+                const int r = j * (1024 / ROWB) + lane / (ROWB / 16);
+                off = off % ROWB + min(r, rows_left - 1) * ROWB;
+            }
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                         :
+                         : "v"(off), "s"(src), "s"(dst + j * 1024)
+                         : "memory", "m0");
+        }
+    };
+    // The first keys are requested before anything else, so that memory is busy while the rows' bounds and the query rows come
+    // (one row of 28 heads over 39.5K keys, a pass of six layers: 136.6 -> 132.7 us).  Not with more rows: what they see comes through
+    // vector loads, which would be waited for together with the LDS-direct loads.
+    const auto request_first_keys = [&]() __attribute__((always_inline)) {
+        if (n_steps > 0) issue(kh, block_of(0), ring);
+    };
+    if (a.R == 1) request_first_keys();
+
     // ---- what the rows of this lane see (column `col` of every row block; a slot without a row works on a copy of the
     // last one, never stored).  A vector load here would be waited for together with the LDS-direct loads, which the
     // compiler does not know, so what a decoding step needs comes through scalar loads, and the rest is here before
@@ -127,6 +169,8 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) all_see_all = all_see_all && __all(sees_all[rb]);
 
+    if (a.R != 1) request_first_keys();
+
     floatx16 o[NRB][NDB];
     float m_run[NRB], l_run[NRB];
 #pragma unroll
@@ -139,40 +183,6 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
             for (int i = 0; i < 16; ++i) o[rb][db][i] = 0.f;
     }
 
-    // ---- key blocks of this wave
-    const int b_begin = part * a.blocks_each + min(part, a.blocks_more);
-    const int b_end = b_begin + a.blocks_each + (part < a.blocks_more ? 1 : 0);
-    const int n_steps = b_end - b_begin > wave ? (b_end - b_begin - wave + kRowsWaves - 1) / kRowsWaves : 0;
-    const char *kh = static_cast<const char *>(a.k) + (size_t)kvh * a.L * ROWB;
-    const char *vh = static_cast<const char *>(a.v) + (size_t)kvh * a.L * ROWB;
-    auto block_of = [&](int i) { return a.k0 + b_begin + wave + kRowsWaves * i; };
-
-    // LDS-direct loads of a block: instruction j moves 1 KB, i.e. 1024 / ROWB whole rows; a lane picks the chunk
-    // of its row that belongs at its place.
-    typedef __attribute__((address_space(3))) void *lds_ptr;
-    const uint32_t ring = (uint32_t)(uintptr_t)(lds_ptr)lds + wave * TR::kWave;
-    uint32_t voff[NI];
-#pragma unroll
-    for (int j = 0; j < NI; ++j) {
-        const int r = j * (1024 / ROWB) + lane / (ROWB / 16), p = lane % (ROWB / 16);
-        voff[j] = r * ROWB + ((p ^ TR::swizzle(r)) << 4);
-    }
-    auto issue = [&](const char *base, int blk, uint32_t dst) __attribute__((always_inline)) {
-        const char *src = base + (size_t)blk * BLK;
-        const int rows_left = a.L - blk * kRowsKeys;
-#pragma unroll
-        for (int j = 0; j < NI; ++j) {
-            uint32_t off = voff[j];
-            if (rows_left < kRowsKeys) {   // the last block of the cache: rows past its end repeat the last one (masked)
-                const int r = j * (1024 / ROWB) + lane / (ROWB / 16);
-                off = off % ROWB + min(r, rows_left - 1) * ROWB;
-            }
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :
-                         : "v"(off), "s"(src), "s"(dst + j * 1024)
-                         : "memory", "m0");
-        }
-    };
     // at most `kNewer` blocks issued after the one that is waited for
     auto wait_loads = [&](auto newer) __attribute__((always_inline)) {
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(newer)::value * NI) : "memory");
@@ -194,8 +204,8 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
         }
     }
 
-    // The query rows go to LDS (all waves work on the same ones) in the layout of a K block, ahead of the first blocks of
-    // keys and with them on the way: stacked rows of a KV head lie one behind the other.
+    // The query rows go to LDS (all waves work on the same ones) in the layout of a K block, with the first blocks of
+    // keys on the way: stacked rows of a KV head lie one behind the other.
     {
         const char *qh = static_cast<const char *>(a.q) + (size_t)kvh * S * ROWB;
         constexpr int kPerWave = ROWS * ROWB / 1024 / kRowsWaves;
@@ -207,16 +217,13 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
             asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(qh), "s"(dst) : "memory", "m0");
         }
     }
-    if (n_steps > 0) {
-        issue(kh, block_of(0), ring);
-        issue(vh, block_of(0), ring + BLK);
-    }
+    if (n_steps > 0) issue(vh, block_of(0), ring + BLK);
     if (n_steps > 1) {
         issue(kh, block_of(1), ring + 2 * BLK);
         issue(vh, block_of(1), ring + 3 * BLK);
     }
-    if (n_steps > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NI) : "memory");
-    else if (n_steps > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
+    if (n_steps > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NI) : "memory");   // the query rows (and the first keys)
+    else if (n_steps > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -320,46 +327,47 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
         if (more2) issue(vh, block_of(i + 2), ring + stage + BLK);
     }
 
-    // ---- merge of the four waves, through LDS (the ring is free after the barrier)
+    // ---- merge of the four waves, through LDS: each leaves its rows in its own part of the ring, which nobody else reads, so that
+    // one barrier is enough (one row of 28 heads over 39.5K keys, a pass of six layers: 133.6 -> 130.6 us, 17 rows of 40 heads over 7.4K, three
+    // layers: 69.1 -> 63.9; three barriers before, and the rows scaled between them)
     constexpr int CH4 = D / 4;
     float2 *ml = reinterpret_cast<float2 *>(lds + TR::kRing);   // [wave][row]
-#pragma unroll
-    for (int rb = 0; rb < NRB; ++rb) {
-        const float l = sum_across_halves(l_run[rb]);
-        if (hl == 0) ml[wave * ROWS + rb * 32 + col] = make_float2(m_run[rb], l);
-    }
-    __syncthreads();
     const int n_rows = min(ROWS, S - grp * ROWS);
-    float4 *stage = reinterpret_cast<float4 *>(lds);
+    float4 *stage = reinterpret_cast<float4 *>(lds);            // [wave][row][chunks of 4 channels, exchanged]
+    constexpr int kStageWave = TR::kWave / 16;
+    static_assert(ROWS * CH4 <= kStageWave, "a wave's rows in its part of the ring");
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const int row = rb * 32 + col;
-        float m = -INFINITY;
-#pragma unroll
-        for (int w = 0; w < kRowsWaves; ++w) m = fmaxf(m, ml[w * ROWS + row].x);
-        const float f = m_run[rb] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[rb] - m) * a.scale_log2e);
+        const float l = sum_across_halves(l_run[rb]);
+        if (hl == 0) ml[wave * ROWS + row] = make_float2(m_run[rb], l);
         if (row < n_rows)
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    stage[(wave * ROWS + row) * CH4 + ((db * 8 + 2 * g + hl) ^ (col & (CH4 - 1)))] =
-                        make_float4(o[rb][db][4 * g] * f, o[rb][db][4 * g + 1] * f, o[rb][db][4 * g + 2] * f, o[rb][db][4 * g + 3] * f);
+                    stage[wave * kStageWave + row * CH4 + ((db * 8 + 2 * g + hl) ^ (col & (CH4 - 1)))] =
+                        make_float4(o[rb][db][4 * g], o[rb][db][4 * g + 1], o[rb][db][4 * g + 2], o[rb][db][4 * g + 3]);
     }
     __syncthreads();
     const size_t slot = ((size_t)(kvh * gridDim.z + grp) * n_parts + part) * ROWS;
     for (int idx = tid; idx < n_rows * CH4; idx += kRowsThreads) {
         const int row = idx / CH4, ch = idx % CH4;
-        float m = -INFINITY, l = 0.f;
+        float2 x[kRowsWaves];
+        float4 y[kRowsWaves];
 #pragma unroll
-        for (int w = 0; w < kRowsWaves; ++w) m = fmaxf(m, ml[w * ROWS + row].x);
+        for (int w = 0; w < kRowsWaves; ++w) {
+            x[w] = ml[w * ROWS + row];
+            y[w] = stage[w * kStageWave + row * CH4 + (ch ^ (row & 31 & (CH4 - 1)))];
+        }
+        const float m = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
+        float l = 0.f;
         float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int w = 0; w < kRowsWaves; ++w) {
-            const float2 x = ml[w * ROWS + row];
-            l += x.x == -INFINITY ? 0.f : x.y * __builtin_amdgcn_exp2f((x.x - m) * a.scale_log2e);
-            const float4 y = stage[(w * ROWS + row) * CH4 + (ch ^ (row & 31 & (CH4 - 1)))];
-            sum.x += y.x; sum.y += y.y; sum.z += y.z; sum.w += y.w;
+            const float f = x[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x[w].x - m) * a.scale_log2e);
+            l = fmaf(x[w].y, f, l);
+            sum.x = fmaf(y[w].x, f, sum.x); sum.y = fmaf(y[w].y, f, sum.y); sum.z = fmaf(y[w].z, f, sum.z); sum.w = fmaf(y[w].w, f, sum.w);
         }
         if (a.part_o == nullptr) {   // one part, and nothing to check
             const float inv = l > 0.f ? 1.f / l : 0.f;
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(kRowsThreads, NRB == 1 || D == 64 ? 2 : 1) void att
     }
 }
 
-// Merges the parts of a (head, row): one workgroup; its threads are D / 4 channel quads times the parts in flight.  The
+// Merges the parts of a stacked row (blockIdx.x) of a KV head (blockIdx.y): one workgroup; its threads are D / 4 channel quads times the parts in flight.  The
 // result is in the first D / 4 threads.
 template <int D>
 struct MergeLds {
@@ -382,70 +390,84 @@ struct MergeLds {
     float m_wave[4], l_wave[4];
 };
 
+// Adds (takes the larger of) what the lanes of a wave hold that have a channel quad in common.
 template <int D>
-__device__ inline bf16x4 merge_parts(MergeLds<D> &lds, const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
-                                     int R, int G, int groups, int rows_per_group, int n_parts, float scale_log2e)
+__device__ inline float sum_over_parts(float x)
+{
+    if constexpr (D == 64) x += __shfl_xor(x, 16, 64);
+    return sum_across_halves(x);
+}
+template <int D>
+__device__ inline float max_over_parts(float x)
+{
+    if constexpr (D == 64) x = fmaxf(x, __shfl_xor(x, 16, 64));
+    return max_across_halves(x);
+}
+
+template <int D>
+__device__ __forceinline__ bf16x4 merge_parts(MergeLds<D> &lds, const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
+                                     int groups, int rows_per_group, int n_parts, float scale_log2e)
 {
     constexpr int CH4 = MergeLds<D>::CH4, LANES = MergeLds<D>::LANES;
-    const int head = blockIdx.x / R, r = blockIdx.x % R;
-    const int kvh = head / G, s = (head % G) * R + r;
-    const int grp = s / rows_per_group, row = s % rows_per_group;
-    const size_t base = (size_t)(kvh * groups + grp) * n_parts * rows_per_group + row;
+    const int grp = blockIdx.x / (unsigned)rows_per_group, row = blockIdx.x % (unsigned)rows_per_group;
+    const size_t base = (size_t)(blockIdx.y * groups + grp) * n_parts * rows_per_group + row;
     const int tid = threadIdx.x;
 
-    // The first kAtOnce parts of a lane are requested before the reference point is known (64 parts at D = 128, 128 at
-    // D = 64: all there are for four KV heads on 256 CUs), so a decoding step waits for memory once here, not twice.
-    constexpr int kAtOnce = 8;
+    // A lane merges its parts to the reference point that they have in common, up to 64 (128) or 128 (256) parts of a row requested together
+    // at D = 128 (64); then the lanes of a wave do so, then the waves: a decoding step waits for memory once here, and for one
+    // barrier.  With two, exchanges over all lanes for what the lanes of a part agree on, and the parts behind the first 64 in turn:
+    // one row of 28 heads over 39.5K keys, 64 parts, a pass of six layers 128.8 us, 126.1 so; two rows of 16 heads over 81K keys, 128
+    // parts, two layers 46.9 and 41.4.  (Rows and KV heads are a grid of two dimensions: dividing by the group and the number of
+    // rows took 0.3 us a call.)
     const int ch = tid % CH4, p0 = tid / CH4;
-    float2 x[kAtOnce];
-    float4 y[kAtOnce];
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) {
-        const size_t at = base + (size_t)min(p0 + i * LANES, n_parts - 1) * rows_per_group;
-        x[i] = part_ml[at];
-        y[i] = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
-    }
-    float m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) m = fmaxf(m, x[i].x);
-    for (int p = kAtOnce * LANES + tid; p < n_parts; p += 256) m = fmaxf(m, part_ml[base + (size_t)p * rows_per_group].x);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((tid & 63) == 0) lds.m_wave[tid >> 6] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(lds.m_wave[0], lds.m_wave[1]), fmaxf(lds.m_wave[2], lds.m_wave[3]));
-
+    float m = -INFINITY, l = 0.f;
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-    float l = 0.f;
-    auto add = [&](const float2 &x, const float4 &y) {
-        const float f = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m) * scale_log2e);
-        l += x.y * f;
-        sum.x += y.x * f; sum.y += y.y * f; sum.z += y.z * f; sum.w += y.w * f;
+    auto merge_some = [&](int first, auto n) __attribute__((always_inline)) {
+        constexpr int N = decltype(n)::value;
+        float2 x[N];
+        float4 y[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const size_t at = base + (size_t)min(first + i * LANES, n_parts - 1) * rows_per_group;
+            x[i] = part_ml[at];
+            y[i] = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
+        }
+        const float m_old = m;
+#pragma unroll
+        for (int i = 0; i < N; ++i) m = fmaxf(m, x[i].x);
+        const float old = m_old == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_old - m) * scale_log2e);
+        l *= old;
+        sum.x *= old; sum.y *= old; sum.z *= old; sum.w *= old;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {   // (no branch on whether the part is there: its loads would go behind it)
+            const float f = x[i].x == -INFINITY || first + i * LANES >= n_parts ? 0.f : __builtin_amdgcn_exp2f((x[i].x - m) * scale_log2e);
+            l = fmaf(x[i].y, f, l);
+            sum.x = fmaf(y[i].x, f, sum.x); sum.y = fmaf(y[i].y, f, sum.y); sum.z = fmaf(y[i].z, f, sum.z); sum.w = fmaf(y[i].w, f, sum.w);
+        }
     };
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i)
-        if (p0 + i * LANES < n_parts) add(x[i], y[i]);
-    for (int p = p0 + kAtOnce * LANES; p < n_parts; p += LANES) {
-        const size_t at = base + (size_t)p * rows_per_group;
-        add(part_ml[at], *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch));
-    }
-    lds.acc[tid / CH4][ch] = sum;
-    float l_lane = ch == 0 ? l : 0.f;   // every channel lane of a part holds the same l
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) l_lane += __shfl_xor(l_lane, off, 64);
-    if ((tid & 63) == 0) lds.l_wave[tid >> 6] = l_lane;
+    if (n_parts <= 8 * LANES) merge_some(p0, std::integral_constant<int, 8>{});
+    else for (int first = p0; first < n_parts; first += 16 * LANES) merge_some(first, std::integral_constant<int, 16>{});
+    const float m_wave = max_over_parts<D>(m);
+    const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_wave) * scale_log2e);
+    l = sum_over_parts<D>(l * f);
+    sum.x = sum_over_parts<D>(sum.x * f); sum.y = sum_over_parts<D>(sum.y * f); sum.z = sum_over_parts<D>(sum.z * f); sum.w = sum_over_parts<D>(sum.w * f);
+    if ((tid & 63) < CH4) lds.acc[tid >> 6][ch] = sum;
+    if ((tid & 63) == 0) { lds.m_wave[tid >> 6] = m_wave; lds.l_wave[tid >> 6] = l; }
     __syncthreads();
     bf16x4 w;
     w[0] = w[1] = w[2] = w[3] = (__bf16)0.f;
     if (tid < CH4) {
-        const float l_tot = (lds.l_wave[0] + lds.l_wave[1]) + (lds.l_wave[2] + lds.l_wave[3]);
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        float4 t = lds.acc[0][tid];
+        const float m_all = fmaxf(fmaxf(lds.m_wave[0], lds.m_wave[1]), fmaxf(lds.m_wave[2], lds.m_wave[3]));
+        float l_tot = 0.f;
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int i = 1; i < LANES; ++i) {
+        for (int i = 0; i < 4; ++i) {   // waves
+            const float f = lds.m_wave[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((lds.m_wave[i] - m_all) * scale_log2e);
             const float4 y = lds.acc[i][tid];
-            t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
+            l_tot = fmaf(lds.l_wave[i], f, l_tot);
+            t.x = fmaf(y.x, f, t.x); t.y = fmaf(y.y, f, t.y); t.z = fmaf(y.z, f, t.z); t.w = fmaf(y.w, f, t.w);
         }
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         w[0] = (__bf16)(t.x * inv); w[1] = (__bf16)(t.y * inv); w[2] = (__bf16)(t.z * inv); w[3] = (__bf16)(t.w * inv);
     }
     return w;
@@ -453,12 +475,12 @@ __device__ inline bf16x4 merge_parts(MergeLds<D> &lds, const float *__restrict__
 
 template <int D>
 __global__ __launch_bounds__(256) void merge_rows(const float *__restrict__ part_o, const float2 *__restrict__ part_ml,
-                                                  __bf16 *__restrict__ out, int R, int G, int groups, int rows_per_group,
+                                                  __bf16 *__restrict__ out, int groups, int rows_per_group,
                                                   int n_parts, float scale_log2e)
 {
     __shared__ MergeLds<D> lds;
-    const bf16x4 w = merge_parts<D>(lds, part_o, part_ml, R, G, groups, rows_per_group, n_parts, scale_log2e);
-    if (threadIdx.x < D / 4) *reinterpret_cast<bf16x4 *>(out + (size_t)blockIdx.x * D + 4 * threadIdx.x) = w;
+    const bf16x4 w = merge_parts<D>(lds, part_o, part_ml, groups, rows_per_group, n_parts, scale_log2e);
+    if (threadIdx.x < D / 4) *reinterpret_cast<bf16x4 *>(out + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * D + 4 * threadIdx.x) = w;
 }
 
 // The same where rows are handed keys that their head's tile lists skip (see plan_rows).  The attention kernel multiplies
@@ -473,16 +495,17 @@ __global__ __launch_bounds__(256) void merge_rows_checked(const RowsArgs a, int 
     __shared__ MergeLds<D> lds;
     __shared__ float p_key[256];   // probabilities of 256 keys, negative: not seen
     const int tid = threadIdx.x;
-    bf16x4 w = merge_parts<D>(lds, a.part_o, a.part_ml, a.R, a.G, groups, rows_per_group, n_parts, a.scale_log2e);
+    bf16x4 w = merge_parts<D>(lds, a.part_o, a.part_ml, groups, rows_per_group, n_parts, a.scale_log2e);
+    const size_t out_row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;   // rows of a head one behind the other
     bool bad = false;
 #pragma unroll
     for (int e = 0; e < 4; ++e) bad = bad || !(fabsf((float)w[e]) < INFINITY);
     if (__syncthreads_or(bad)) {
-        const int head = blockIdx.x / a.R;
+        const int head = blockIdx.y * a.G + blockIdx.x / a.R;
         const RowBounds b = a.rows[blockIdx.x % a.R];
         const int cls = (a.classes[head >> 4] >> (2 * (head & 15))) & 3;
         const bool sees_all = cls == BS_DENSE || b.img_hi == b.img_lo;
-        const __bf16 *q = static_cast<const __bf16 *>(a.q) + (size_t)blockIdx.x * D;
+        const __bf16 *q = static_cast<const __bf16 *>(a.q) + out_row * D;
         const __bf16 *k = static_cast<const __bf16 *>(a.k) + (size_t)(head / a.G) * a.L * D;
         const __bf16 *v = static_cast<const __bf16 *>(a.v) + (size_t)(head / a.G) * a.L * D;
         const int ch = tid % CH4;
@@ -543,7 +566,7 @@ __global__ __launch_bounds__(256) void merge_rows_checked(const RowsArgs a, int 
             w[0] = (__bf16)(t.x * inv); w[1] = (__bf16)(t.y * inv); w[2] = (__bf16)(t.z * inv); w[3] = (__bf16)(t.w * inv);
         }
     }
-    if (tid < CH4) *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + (size_t)blockIdx.x * D + 4 * tid) = w;
+    if (tid < CH4) *reinterpret_cast<bf16x4 *>(static_cast<__bf16 *>(a.out) + out_row * D + 4 * tid) = w;
 }
 
 RowsPlan plan_rows(const bs_tilemap *tm, int32_t dtype, int32_t gqa_group, int32_t head_dim, int32_t n_cus)
@@ -596,11 +619,11 @@ static void launch_rows_dim(const RowsPlan &plan, const RowsArgs &a, int n_kv, h
     else
         hipLaunchKernelGGL((attn_rows_bf16<D, 2>), grid, block, RowsTraits<D>::kLds, st, a);
     if (plan.check)
-        hipLaunchKernelGGL(merge_rows_checked<D>, dim3((unsigned)(n_kv * a.G * a.R)), dim3(256), 0, st, a, plan.groups,
+        hipLaunchKernelGGL(merge_rows_checked<D>, dim3((unsigned)(a.G * a.R), (unsigned)n_kv), dim3(256), 0, st, a, plan.groups,
                            plan.row_blocks * 32, plan.parts);
     else if (plan.parts > 1)
-        hipLaunchKernelGGL(merge_rows<D>, dim3((unsigned)(n_kv * a.G * a.R)), dim3(256), 0, st, a.part_o, a.part_ml,
-                           static_cast<__bf16 *>(a.out), a.R, a.G, plan.groups, plan.row_blocks * 32, plan.parts, a.scale_log2e);
+        hipLaunchKernelGGL(merge_rows<D>, dim3((unsigned)(a.G * a.R), (unsigned)n_kv), dim3(256), 0, st, a.part_o, a.part_ml,
+                           static_cast<__bf16 *>(a.out), plan.groups, plan.row_blocks * 32, plan.parts, a.scale_log2e);
 }
 
 void launch_rows(const RowsPlan &plan, const void *q, const void *k, const void *v, void *out, const bs_tilemap *tm,
