@@ -66,17 +66,14 @@ def load_library():
     lib = ctypes.CDLL(_build.LIB)
     i32, i64p = ctypes.c_int32, ctypes.POINTER(ctypes.c_int64)
     i32p, u8p, vp = ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_uint8), ctypes.c_void_p
-    lib.bs_build_tilemap.argtypes = [ctypes.POINTER(_Span), i32, i32, u8p, i32, i32, i32, i32,
-                                     ctypes.POINTER(vp)]
+    # (the calls of every prompt and layer take plain addresses: bytes, integers, byref)
+    lib.bs_build_tilemap.argtypes = [vp, i32, i32, vp, i32, i32, i32, i32, vp]
     lib.bs_build_tilemap.restype = ctypes.c_int
-    lib.bs_build_tilemap_ex.argtypes = [ctypes.POINTER(_Span), i32, i32, u8p, i32, i32, i32, i32, ctypes.c_uint32,
-                                        ctypes.POINTER(ctypes.c_void_p)]
+    lib.bs_build_tilemap_ex.argtypes = [vp, i32, i32, vp, i32, i32, i32, i32, ctypes.c_uint32, vp]
     lib.bs_build_tilemap_ex.restype = ctypes.c_int
-    lib.bs_build_tilemap_model.argtypes = [ctypes.POINTER(_Span), i32, i32, u8p, i32, i32, i32, i32, ctypes.c_uint32,
-                                           i32p, i32, i32, ctypes.POINTER(ctypes.c_void_p)]
+    lib.bs_build_tilemap_model.argtypes = [vp, i32, i32, vp, i32, i32, i32, i32, ctypes.c_uint32, vp, i32, i32, vp]
     lib.bs_build_tilemap_model.restype = ctypes.c_int
-    lib.bs_build_tilemap_suffix.argtypes = [ctypes.POINTER(_Span), i32, i32, u8p, i32, i32, i32, i32, ctypes.c_uint32,
-                                            i32p, i32, i32, i32, ctypes.POINTER(ctypes.c_void_p)]
+    lib.bs_build_tilemap_suffix.argtypes = [vp, i32, i32, vp, i32, i32, i32, i32, ctypes.c_uint32, vp, i32, i32, i32, vp]
     lib.bs_build_tilemap_suffix.restype = ctypes.c_int
     lib.bs_tilemap_row_order.argtypes = [vp, i32p]
     lib.bs_tilemap_row_order.restype = ctypes.c_int
@@ -86,7 +83,7 @@ def load_library():
     lib.bs_tilemap_key_order.restype = ctypes.c_int
     lib.bs_tilemap_destroy.argtypes = [vp]
     lib.bs_tilemap_destroy.restype = None
-    lib.bs_tilemap_dims.argtypes = [vp, i32p, i32p, i32p, i32p]
+    lib.bs_tilemap_dims.argtypes = [vp, vp, vp, vp, vp]
     lib.bs_tilemap_dims.restype = ctypes.c_int
     lib.bs_tilemap_tile_states.argtypes = [vp, i32, i32, i32, u8p]
     lib.bs_tilemap_tile_states.restype = ctypes.c_int
@@ -100,7 +97,7 @@ def load_library():
     lib.bs_tilemap_share_plan.restype = ctypes.c_int
     lib.bs_tilemap_upload.argtypes = [vp]
     lib.bs_tilemap_upload.restype = ctypes.c_int
-    lib.bs_tilemap_rebind.argtypes = [vp, u8p, i32]
+    lib.bs_tilemap_rebind.argtypes = [vp, vp, i32]
     lib.bs_tilemap_rebind.restype = ctypes.c_int
     lib.bs_tilemap_prepare.argtypes = [vp, i32, i32, vp]
     lib.bs_tilemap_prepare.restype = ctypes.c_int
@@ -141,16 +138,19 @@ def _check(code: int, where: str):
         raise BlindsightError(code, where)
 
 
+_FourInts = ctypes.c_int32 * 4
+
+
 class TileMap:
     """Owner of one bs_tilemap*.  Immutable after construction; reusable for every call on
     the same prompt and class vector."""
 
     def __init__(self, handle: int):
         self._h = ctypes.c_void_p(handle)
-        lib = load_library()
-        vals = [ctypes.c_int32() for _ in range(4)]
-        _check(lib.bs_tilemap_dims(self._h, *[ctypes.byref(v) for v in vals]), "bs_tilemap_dims")
-        self.seq_len, self.n_q_tiles, self.n_k_tiles, self.n_q_heads = (int(v.value) for v in vals)
+        dims = _FourInts()
+        at = ctypes.addressof(dims)
+        _check(load_library().bs_tilemap_dims(self._h, at, at + 4, at + 8, at + 12), "bs_tilemap_dims")
+        self.seq_len, self.n_q_tiles, self.n_k_tiles, self.n_q_heads = dims
 
     @property
     def handle(self):
@@ -237,14 +237,12 @@ class TileMap:
     def rebind(self, head_class):
         """Bind the map to another class vector (one per layer); the per-class lists are kept."""
         hc = np.ascontiguousarray(head_class, dtype=np.uint8)
-        _check(load_library().bs_tilemap_rebind(self._h, hc.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8)), len(hc)),
-               "bs_tilemap_rebind")
+        _check(load_library().bs_tilemap_rebind(self._h, hc.tobytes(), len(hc)), "bs_tilemap_rebind")
         self.n_q_heads = len(hc)
 
     def prepare(self, dtype: int, gqa_group: int, stream=None):
         """Upload and plan ahead of time, so that bs_attn_prefill_static allocates nothing."""
-        _check(load_library().bs_tilemap_prepare(self._h, int(dtype), int(gqa_group),
-                                                 ctypes.c_void_p(int(stream) if stream else 0)), "bs_tilemap_prepare")
+        _check(load_library().bs_tilemap_prepare(self._h, int(dtype), int(gqa_group), int(stream) if stream else None), "bs_tilemap_prepare")
 
     def close(self):
         if self._h is not None and self._h.value:
@@ -271,34 +269,26 @@ def bs_build_tilemap(spans, seq_len: int, head_class, sink_len: int = 0,
     are sink keys in every image, window: sliding window of the layer (both go through
     bs_build_tilemap_model); q_begin: the query rows are positions q_begin .. seq_len - 1 only
     (bs_build_tilemap_suffix)."""
+    # Arrays go down as bytes: a small copy, where numpy's typed ctypes pointers cost some 2 us each, half of what a decoding step's
+    # map takes on the host (a pass of 24 us: build, rebind, call).
     lib = load_library()
-    sp = np.ascontiguousarray(np.asarray(spans, dtype=np.int32).reshape(-1, 3))
+    sp = np.asarray(spans, dtype=np.int32).reshape(-1, 3)
     hc = np.ascontiguousarray(head_class, dtype=np.uint8)
     handle = ctypes.c_void_p()
-    sp_ptr = sp.ctypes.data_as(ctypes.POINTER(_Span)) if len(sp) else None
-    hc_ptr = hc.ctypes.data_as(ctypes.POINTER(ctypes.c_uint8))
-    if q_begin:
+    common = (sp.tobytes() if len(sp) else None, len(sp), int(seq_len), hc.tobytes(), len(hc), int(sink_len), int(block_m), int(block_n))
+    out = ctypes.byref(handle)
+    if q_begin or window or (sink_offsets is not None and len(sink_offsets)):
         so = np.ascontiguousarray([] if sink_offsets is None else sink_offsets, dtype=np.int32).reshape(-1)
-        rc = lib.bs_build_tilemap_suffix(sp_ptr, len(sp), int(seq_len), hc_ptr, len(hc), int(sink_len),
-                                         int(block_m), int(block_n), int(flags),
-                                         so.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)) if len(so) else None, len(so),
-                                         int(window), int(q_begin), ctypes.byref(handle))
-        _check(rc, "bs_build_tilemap_suffix")
-    elif (sink_offsets is not None and len(sink_offsets)) or window:
-        so = np.ascontiguousarray([] if sink_offsets is None else sink_offsets, dtype=np.int32).reshape(-1)
-        rc = lib.bs_build_tilemap_model(sp_ptr, len(sp), int(seq_len), hc_ptr, len(hc), int(sink_len),
-                                        int(block_m), int(block_n), int(flags),
-                                        so.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)) if len(so) else None, len(so),
-                                        int(window), ctypes.byref(handle))
-        _check(rc, "bs_build_tilemap_model")
+        offsets = (so.tobytes() if len(so) else None, len(so))
+        if q_begin:
+            rc, name = lib.bs_build_tilemap_suffix(*common, int(flags), *offsets, int(window), int(q_begin), out), "bs_build_tilemap_suffix"
+        else:
+            rc, name = lib.bs_build_tilemap_model(*common, int(flags), *offsets, int(window), out), "bs_build_tilemap_model"
     elif flags:
-        rc = lib.bs_build_tilemap_ex(sp_ptr, len(sp), int(seq_len), hc_ptr, len(hc), int(sink_len),
-                                     int(block_m), int(block_n), int(flags), ctypes.byref(handle))
-        _check(rc, "bs_build_tilemap_ex")
+        rc, name = lib.bs_build_tilemap_ex(*common, int(flags), out), "bs_build_tilemap_ex"
     else:
-        rc = lib.bs_build_tilemap(sp_ptr, len(sp), int(seq_len), hc_ptr, len(hc), int(sink_len),
-                                  int(block_m), int(block_n), ctypes.byref(handle))
-        _check(rc, "bs_build_tilemap")
+        rc, name = lib.bs_build_tilemap(*common, out), "bs_build_tilemap"
+    _check(rc, name)
     return TileMap(handle.value)
 
 
@@ -325,7 +315,7 @@ def bs_attn_prefill(q, k, v, out, tilemap: TileMap, dtype: int, n_q_heads: int, 
     Enqueues only."""
     rc = load_library().bs_attn_prefill(_ptr(q), _ptr(k), _ptr(v), _ptr(out), tilemap.handle,
                                         int(dtype), int(n_q_heads), int(gqa_group), int(head_dim),
-                                        float(scale), ctypes.c_void_p(int(stream) if stream else 0))
+                                        float(scale), int(stream) if stream else None)
     _check(rc, "bs_attn_prefill")
 
 
@@ -334,8 +324,7 @@ def bs_attn_prefill_static(q, k, v, out, tilemap: TileMap, n_q_heads: int, gqa_g
     """bf16 prefill that allocates nothing (static scratch inside the library); the map must have been
     prepared with TileMap.prepare(BS_BF16, gqa_group)."""
     rc = load_library().bs_attn_prefill_static(_ptr(q), _ptr(k), _ptr(v), _ptr(out), tilemap.handle, int(n_q_heads),
-                                               int(gqa_group), int(head_dim), float(scale),
-                                               ctypes.c_void_p(int(stream) if stream else 0))
+                                               int(gqa_group), int(head_dim), float(scale), int(stream) if stream else None)
     _check(rc, "bs_attn_prefill_static")
 
 
