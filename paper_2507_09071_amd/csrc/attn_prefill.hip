@@ -628,21 +628,23 @@ __device__ __forceinline__ void walk_units(
             lds_wait<4 + 4 * RPV>(fc); batch(PvBatch<2>{}, NoBatch{}, fc);
             lds_wait<4 * RPV>(fa); batch(ScBatch<3, false>{}, NoBatch{}, fa);
             lds_wait<0>(fb); batch(PvBatch<3>{}, NoBatch{}, fb);
+            // No wait for the accumulators: the last scores were finished by the MFMAs behind them, and the output tile is next
+            // touched at the end of the vector phase.  (The statement keeps the vector phase behind the chain.)
+            asm volatile("" : "+v"(s[0]), "+v"(s[1]));
+            if constexpr (KT == 2) asm volatile("" : "+v"(s[2]), "+v"(s[3]));
         } else {
-            // PV batches are half as large, S has two batches of four
-            read_batch(ScBatch<0, true>{}, fa); read_batch(PvBatch<0>{}, fb); read_batch(PvBatch<1>{}, fc);
-            lds_wait<4 * RPV>(fa); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fa);
-            lds_wait<4 + 2 * RPV>(fb); batch(PvBatch<0>{}, PvBatch<2>{}, fb);
+            // PV batches are half as large, S has two batches of four.  The chain is half as long, and scores first gain nothing (window of
+            // 512 on 30K tokens 540 us, 536 with values first, 1.4K tokens 49.4 and 48.4)
+            read_batch(PvBatch<0>{}, fa); read_batch(ScBatch<0, true>{}, fb); read_batch(PvBatch<1>{}, fc);
+            lds_wait<4 + 2 * RPV>(fa); batch(PvBatch<0>{}, PvBatch<2>{}, fa);
+            lds_wait<4 * RPV>(fb); batch(ScBatch<0, true>{}, ScBatch<1, false>{}, fb);
             lds_wait<4 + 2 * RPV>(fc); batch(PvBatch<1>{}, PvBatch<3>{}, fc);
             advance_walk();
-            lds_wait<4 * RPV>(fa); batch(ScBatch<1, false>{}, NoBatch{}, fa);
-            lds_wait<2 * RPV>(fb); batch(PvBatch<2>{}, NoBatch{}, fb);
+            lds_wait<4 + 2 * RPV>(fa); batch(PvBatch<2>{}, NoBatch{}, fa);
+            lds_wait<2 * RPV>(fb); batch(ScBatch<1, false>{}, NoBatch{}, fb);
             lds_wait<0>(fc); batch(PvBatch<3>{}, NoBatch{}, fc);
+            mfma_drain(o[0], o[1]);   // the scores finished two MFMAs earlier
         }
-        // No wait for the accumulators: the last scores were finished by the MFMAs behind them, and the output tile is next
-        // touched at the end of the vector phase.  (The statement keeps the vector phase behind the chain.)
-        asm volatile("" : "+v"(s[0]), "+v"(s[1]));
-        if constexpr (KT == 2) asm volatile("" : "+v"(s[2]), "+v"(s[3]));
         // Every LDS read and scalar load of the phase has returned (the last lds_wait was for zero): say so
         // in a form the compiler sees, or it waits for its own scalar loads in the middle of the next chain.
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
@@ -1231,18 +1233,23 @@ bool steps_of_two(const DeviceMap *d, const bs::ShareSet *sh)
 }
 
 // Whether the pre-pass transposes V for a launch of the bf16 kernel.  If not, V tiles come from where the caller has them and the
-// operand reads transpose: two reads of 64 bits for one of 128, at half the rate, so a step takes 0.04-0.055 us longer (2.3 % on 36K
-// tokens at d = 128, 4-5 % at d = 64), 0.15-0.2 ns a step with 256 workgroups; V^T costs 32 KB of traffic a tile at d = 128, 6 ns.
-// The line lies at the tiles' quotient.  Passes with V^T / V, by steps a tile: 6-11 (window of 1024 on 27K) 1613 / 1553 us, 6-15 (517
-// rows behind 36K) 612 / 580, 10 and 43 (2048 rows behind 141K) 8406 / 8307; 36 and 74 (d = 64, 9K) 847 / 862, 55 and 115 (8K) 1029 /
-// 1036, 167 and 546 (36K) 16179 / 16459.
+// operand reads transpose: two reads of 64 bits for one of 128, at half the rate, so a step takes 0.04-0.055 us longer at d = 128 (2.3 % on
+// 36K tokens), 0.15-0.2 ns with 256 workgroups; V^T costs 32 KB of traffic a tile, 6 ns.  The line lies at the tiles' quotient.  Passes
+// with V^T / V, by steps a tile: 6-11 (window of 1024 on 27K) 1613 / 1553 us, 6-15 (517 rows behind 36K) 612 / 580, 10 and 43 (2048 rows
+// behind 141K) 8406 / 8307, 25 (1278 rows behind 29K) 1545 / 1526, 27 (1167 rows behind 20K) 291 / 285, 27 (6.5K) 1044 / 1054, 30 (16K)
+// 1843 / 1843, 34 (window of 1024 on 54K) 946 / 949, 55 and 115 (8K) 1029 / 1036, 167 and 546 (36K) 16179 / 16459.
+// At d = 64 a step, which is bound by the vector ALU and by what stands around it, loses more (4-5 %), and V^T, half as large, is still in
+// the caches where it is up to some 32 MB: 1.1 (307 rows behind 18K, 2688 tiles) 103 / 94, 2 (68 rows behind 4K) 43.9 / 42.2; 4 (window on
+// 24K, 2976 tiles) 219 / 228, 4 (442 rows behind 10K) 114 / 125, 5.5 (window on 20K) 212 / 216, 10 (14K) 475 / 486, 17 (9K) 381 / 393, 14
+// (window on 34K, 4192 tiles) 696 / 712; but 6 (515 rows behind 35K, 4368 tiles) 513 / 498, 8 (1258 rows behind 85K) 950 / 913.
 template <int D>
 bool transposed_values(const DeviceMap *d, const TileRuns &read, int n_kv_heads)
 {
-    constexpr int64_t kStepsPerTile = D == 128 ? 32 : 14;
     int64_t tiles = 0;
     for (int i = 0; i < 3; ++i) tiles += read.end[i] - read.first[i];
-    return d->n_steps >= kStepsPerTile * tiles * n_kv_heads;
+    tiles *= n_kv_heads;
+    const int64_t steps_per_tile = D == 128 ? 32 : tiles <= 4096 ? 4 : 10;
+    return d->n_steps >= steps_per_tile * tiles;
 }
 
 bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)

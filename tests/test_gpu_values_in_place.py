@@ -30,15 +30,15 @@ def test_kernels_that_transpose_have_no_mfma_hazard(monkeypatch):
 @pytest.mark.parametrize("flags", [0, bs.BS_MAP_PACK_KEYS])
 @pytest.mark.parametrize("d,G,L", [(128, 2, 1537), (128, 2, 1600),             # steps per tile: some 6
                                    (128, 24, 1471), (128, 24, 1472), (128, 24, 1473),   # around 32
-                                   (64, 2, 1665), (64, 2, 1600),               # some 6, two tiles a step
-                                   (64, 16, 1023), (64, 16, 1024), (64, 8, 1601)])      # around 14
+                                   (64, 1, 1665), (64, 1, 1600), (64, 1, 700),  # some 3, steps of two tiles and of one
+                                   (64, 2, 1023), (64, 2, 1024), (64, 2, 1025), (64, 16, 1023)])   # from 4 on
 def test_both_sides_of_the_line(d, G, L, flags):
     full_parity(prompt(L, 1, G, d), seed=81, flags=flags)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("rows,window", [(70, 0), (300, 200), (1, 64)])
+@pytest.mark.parametrize("rows,window", [(70, 0), (300, 200), (700, 0), (1, 64)])
 def test_chunks(rows, window, d):
     p = prompt(2111, 2, 2, d, **({"window": window} if window else {}))
     suffix_parity(p, p.seq_len - rows, 82, bs.BS_MAP_REGROUP_ROWS if window else bs.BS_MAP_PACK_KEYS, row_step=5)
