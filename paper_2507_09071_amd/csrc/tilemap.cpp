@@ -1244,9 +1244,11 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     // 32), but never so wide that the heaviest-first order loses its grip on the tail (a workgroup's
     // share of the steps / 64; below 32 tiles on prompts of less than some 20K tokens, whose K and V the caches
     // hold anyway).
-    // Blocks are dealt there and back, so that every queue gets heavy and light ones alike: dealt in turn, the first queue had 6-14 % more
-    // steps than the last with four blocks a queue and more (d = 64, 9K tokens: 86 and 75 steps a workgroup; passes 779 -> 767 us, 8K
-    // tokens 936 -> 931, long prompts the same).  In a window the blocks of a bucket are alike (1430 / 1432).
+    // With up to some thirty rounds of blocks these are dealt there and back, so that every queue gets heavy and light ones alike: dealt in turn, the
+    // first queue had 6-14 % more steps than the last (d = 64, 9K tokens, 1144 units: 86 and 75 steps a workgroup; passes 779 -> 767
+    // us, 8K tokens, 912 units, 936 -> 931).  With more rounds the queues are even enough, and neighbours in a queue meet less in L2
+    // (281K tokens of d = 64, 8 KV heads, 8800 units: 29.9 ms in turn, 30.2 there and back).  In a window the blocks of a bucket
+    // are alike (1430 / 1432).
     // In a window the cost says nothing about where a unit's keys lie: inside a bucket the units of a KV head stand in order
     // of their rows, and the buckets are 8 tiles wide (27K tokens, images of 256, window of 1024: 1624 -> 1603 us for three
     // layers, 4096: 3216 -> 3192, images of 1-5K 1388 -> 1364; 16 tiles the same, 64 tiles 2 % slower: the tail).
@@ -1261,7 +1263,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
         cost_bucket = (int32_t)std::max<int64_t>(1, for_balance < 32 ? for_balance : std::min(for_locality, for_balance) / 32 * 32);
     }
     if (tm->window > 0) cost_bucket = 8;
-    const bool there_and_back = tm->window == 0;
+    const bool there_and_back = tm->window == 0 && plan.items.size() <= 2048;
     const int32_t kXcdBlock = std::min<int64_t>(16, std::max<int64_t>(8, (int64_t)plan.items.size() / 2048));
     {
         // Stable counting passes, a byte at a time, from the last field to the first: a sort that compares units took 50-70 ns each, more

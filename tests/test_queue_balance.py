@@ -1,4 +1,4 @@
-"""Without a window the blocks of units are dealt to the eight queues there and back: every unit once, in order, and with full turns
+"""Without a window the blocks of up to 2048 units are dealt to the eight queues there and back (of more, in turn): every unit once, in order, and with full turns
 no queue has more steps than another by more than its heaviest block and the width of the cost buckets allow."""
 import os
 import shutil
@@ -32,7 +32,7 @@ int main()
             int at[8], heaviest = 0, last = 1 << 30;
             std::copy(plan.queue_off, plan.queue_off + 8, at);
             for (int p = 0; p < n; ++p) {
-                const int round = p / block / 8, x = p / block % 8, q = round & 1 ? 7 - x : x;
+                const int round = p / block / 8, x = p / block % 8, q = n <= 2048 && (round & 1) ? 7 - x : x;
                 if (at[q] >= plan.queue_off[q + 1]) return 3;
                 const int tiles = plan.items[at[q]++].n_tiles;
                 heaviest = std::max(heaviest, tiles);
@@ -50,7 +50,7 @@ int main()
                 most = std::max(most, sum);
                 least = std::min(least, sum);
             }
-            if (turns > 0 && most - least > (long)block * heaviest + 2L * turns * block * 32 * 32) return 6;
+            if (n <= 2048 && turns > 0 && most - least > (long)block * heaviest + 2L * turns * block * 32 * 32) return 6;
             bs_tilemap_destroy(tm);
         }
     return 0;
