@@ -1299,6 +1299,7 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
             }
         }
         plan.queue_off[kXcds] = (int32_t)n;
+        plan.back_block = there_and_back ? kXcdBlock : 0;
         plan.items.swap(queued);
     }
     auto item_class = [&](int32_t head, int32_t tile) { return tile >= tm->M ? BS_DENSE | 8 : tm->head_class[head] | tm->walked(tm->head_class[head]).compact[tile] << 2; };
@@ -1346,7 +1347,17 @@ static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool sol
     const int64_t least = std::max<int64_t>((total + n_wgs - 1) / n_wgs, 2 * kMinPart + kUnitCost);
     if (n_units <= n_wgs && longest <= least + kMergeCost) return;
 
-    // longest first, in buckets of an eighth of a share inside which the units of a KV head stay together
+    // Longest first, in buckets of an eighth of a share inside which the units of a KV head stay together, in the order of the queues
+    // as dealing in turn fills them: which units are cut, and so how the results are rounded, does not hang on how the queues are dealt.
+    std::vector<int32_t> in_turn;
+    if (plan.back_block > 0) {
+        in_turn.reserve(n_units);
+        for (int32_t x = 0; x < 8; ++x)
+            for (int32_t round = 0; (round * 8 + x) * plan.back_block < n_units; ++round) {
+                const int32_t first = plan.queue_off[round & 1 ? 7 - x : x] + round * plan.back_block;
+                for (int32_t i = 0; i < std::min(plan.back_block, n_units - (round * 8 + x) * plan.back_block); ++i) in_turn.push_back(first + i);
+            }
+    }
     const int64_t bucket = std::max<int64_t>(1, least / 8);
     struct Unit { int32_t cost, unit; };   // (costs are below 2^28: n_tiles is)
     std::vector<Unit> order(n_units);
@@ -1358,7 +1369,7 @@ static void make_shares(const bs_tilemap *tm, const bs::PairPlan &plan, bool sol
             for (int64_t k = 0; k < n_keys; ++k) at[k + 1] += at[k];
             for (int32_t i = 0; i < n_units; ++i) place(at[key(unit(i))]++, unit(i));
         };
-        pass((tm->n_q_heads + G - 1) / G, [](int32_t i) { return i; }, [&](int32_t u) { return plan.items[u].head_a / G; },
+        pass((tm->n_q_heads + G - 1) / G, [&](int32_t i) { return in_turn.empty() ? i : in_turn[i]; }, [&](int32_t u) { return plan.items[u].head_a / G; },
              [&](int32_t i, int32_t u) { by_head[i] = u; });
         pass(longest / bucket + 1, [&](int32_t i) { return by_head[i]; },
              [&](int32_t u) { return (int32_t)(longest / bucket - plan.items[u].n_tiles / bucket); },

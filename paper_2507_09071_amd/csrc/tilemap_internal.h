@@ -176,6 +176,7 @@ struct PairPlan {
     std::vector<PairRange> ranges;
     std::vector<PairItem> items;  // eight queues, one per XCD, each heaviest first
     int32_t queue_off[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};   // queue x = items[queue_off[x] .. queue_off[x + 1])
+    int32_t back_block = 0;       // dealt there and back in blocks of so many units; 0: in turn
 };
 
 // One item of a unit that was cut: its partial results lie in slots first_slot .. first_slot + n_parts - 1.
