@@ -422,13 +422,17 @@ __device__ __forceinline__ bf16x4 merge_parts(MergeLds<D> &lds, const float *__r
     const int ch = tid % CH4, p0 = tid / CH4;
     float m = -INFINITY, l = 0.f;
     float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-    auto merge_some = [&](int first, auto n) __attribute__((always_inline)) {
+    // (all: every lane has N parts from `first` on.  A lane behind the last part holds a copy of it, which is replaced: times zero, an
+    // infinity in it would be a NaN.  Values, not a branch on whether the part is there: its loads would go behind it.  Replacing them also
+    // where all are there: 64 parts 125.7 -> 126.2 us, 128 parts 41.2 -> 42.3.)
+    auto merge_some = [&](int first, auto n, auto all) __attribute__((always_inline)) {
         constexpr int N = decltype(n)::value;
+        const auto there = [&](int i) { return decltype(all)::value || first + i * LANES < n_parts; };
         float2 x[N];
         float4 y[N];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const size_t at = base + (size_t)min(first + i * LANES, n_parts - 1) * rows_per_group;
+            const size_t at = base + (size_t)(there(i) ? first + i * LANES : n_parts - 1) * rows_per_group;
             x[i] = part_ml[at];
             y[i] = *reinterpret_cast<const float4 *>(part_o + at * D + 4 * ch);
         }
@@ -439,14 +443,24 @@ __device__ __forceinline__ bf16x4 merge_parts(MergeLds<D> &lds, const float *__r
         l *= old;
         sum.x *= old; sum.y *= old; sum.z *= old; sum.w *= old;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {   // (no branch on whether the part is there: its loads would go behind it)
-            const float f = x[i].x == -INFINITY || first + i * LANES >= n_parts ? 0.f : __builtin_amdgcn_exp2f((x[i].x - m) * scale_log2e);
+        for (int i = 0; i < N; ++i) {
+            const float f = x[i].x == -INFINITY || !there(i) ? 0.f : __builtin_amdgcn_exp2f((x[i].x - m) * scale_log2e);
             l = fmaf(x[i].y, f, l);
-            sum.x = fmaf(y[i].x, f, sum.x); sum.y = fmaf(y[i].y, f, sum.y); sum.z = fmaf(y[i].z, f, sum.z); sum.w = fmaf(y[i].w, f, sum.w);
+            sum.x = fmaf(there(i) ? y[i].x : 0.f, f, sum.x); sum.y = fmaf(there(i) ? y[i].y : 0.f, f, sum.y);
+            sum.z = fmaf(there(i) ? y[i].z : 0.f, f, sum.z); sum.w = fmaf(there(i) ? y[i].w : 0.f, f, sum.w);
         }
     };
-    if (n_parts <= 8 * LANES) merge_some(p0, std::integral_constant<int, 8>{});
-    else for (int first = p0; first < n_parts; first += 16 * LANES) merge_some(first, std::integral_constant<int, 16>{});
+    using N8 = std::integral_constant<int, 8>;
+    using N16 = std::integral_constant<int, 16>;
+    if (n_parts == 8 * LANES) {
+        merge_some(p0, N8{}, std::true_type{});
+    } else if (n_parts < 8 * LANES) {
+        merge_some(p0, N8{}, std::false_type{});
+    } else {
+        int begin = 0;
+        for (; begin + 16 * LANES <= n_parts; begin += 16 * LANES) merge_some(begin + p0, N16{}, std::true_type{});
+        if (begin < n_parts) merge_some(begin + p0, N16{}, std::false_type{});
+    }
     const float m_wave = max_over_parts<D>(m);
     const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_wave) * scale_log2e);
     l = sum_over_parts<D>(l * f);
