@@ -1232,24 +1232,12 @@ bool steps_of_two(const DeviceMap *d, const bs::ShareSet *sh)
     return d->n_steps >= kTilesPerUnit * std::max(d->n_pairs, sh ? sh->n_shares : 0);
 }
 
-// Whether the pre-pass transposes V for a launch of the bf16 kernel.  If not, V tiles come from where the caller has them and the
-// operand reads transpose: two reads of 64 bits for one of 128, at half the rate, so a step takes 0.04-0.055 us longer at d = 128 (2.3 % on
-// 36K tokens), 0.15-0.2 ns with 256 workgroups; V^T costs 32 KB of traffic a tile, 6 ns.  The line lies at the tiles' quotient.  Passes
-// with V^T / V, by steps a tile: 6-11 (window of 1024 on 27K) 1613 / 1553 us, 6-15 (517 rows behind 36K) 612 / 580, 10 and 43 (2048 rows
-// behind 141K) 8406 / 8307, 25 (1278 rows behind 29K) 1545 / 1526, 27 (1167 rows behind 20K) 291 / 285, 27 (6.5K) 1044 / 1054, 30 (16K)
-// 1843 / 1843, 34 (window of 1024 on 54K) 946 / 949, 55 and 115 (8K) 1029 / 1036, 167 and 546 (36K) 16179 / 16459.
-// At d = 64 a step, which is bound by the vector ALU and by what stands around it, loses more (4-5 %), and V^T, half as large, is still in
-// the caches where it is up to some 32 MB: 1.1 (307 rows behind 18K, 2688 tiles) 103 / 94, 2 (68 rows behind 4K) 43.9 / 42.2; 4 (window on
-// 24K, 2976 tiles) 219 / 228, 4 (442 rows behind 10K) 114 / 125, 5.5 (window on 20K) 212 / 216, 10 (14K) 475 / 486, 17 (9K) 381 / 393, 14
-// (window on 34K, 4192 tiles) 696 / 712; but 6 (515 rows behind 35K, 4368 tiles) 513 / 498, 8 (1258 rows behind 85K) 950 / 913.
-template <int D>
-bool transposed_values(const DeviceMap *d, const TileRuns &read, int n_kv_heads)
+// Key tiles that the runs name, of all KV heads.
+int64_t tiles_of(const TileRuns &read, int n_kv_heads)
 {
     int64_t tiles = 0;
     for (int i = 0; i < 3; ++i) tiles += read.end[i] - read.first[i];
-    tiles *= n_kv_heads;
-    const int64_t steps_per_tile = D == 128 ? 32 : tiles <= 4096 ? 4 : 10;
-    return d->n_steps >= steps_per_tile * tiles;
+    return tiles * n_kv_heads;
 }
 
 bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
@@ -1272,7 +1260,7 @@ hipError_t launch_bf16(bs::KernelArgs a, const bs_tilemap *tm, const DeviceMap *
     const int32_t in_place = tm->L / bs::kBlockN;
     // (a result that is written over V needs the copy, and the calls that share a pre-pass take what it made)
     const size_t row_bytes = (size_t)D * 2;
-    const bool transpose = shared_pack || transposed_values<D>(d, todo_tiles, n_kv_heads) ||
+    const bool transpose = shared_pack || bs::transposed_values(D, d->n_steps, tiles_of(todo_tiles, n_kv_heads)) ||
                            overlap(a.out, row_bytes * tm->n_q_heads * (tm->L - tm->q_begin), a.v, row_bytes * n_kv_heads * tm->L);
     // one workgroup per CU (160 KB of LDS each; 96 KB for steps of one tile at d = 64), which take the units from the queues until they are empty
     const dim3 pgrid((unsigned)(sh ? sh->n_shares : std::min(d->n_pairs, n_cus))), pblock(bs::kPingPongThreads);

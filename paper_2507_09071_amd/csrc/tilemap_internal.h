@@ -197,6 +197,29 @@ struct SharePlan {
 
 struct DeviceMap;  // defined by the HIP side
 
+// Whether the pre-pass transposes V for a launch of the bf16 kernel of so many steps, whose units read so many key tiles (of all KV heads).
+// If not, V tiles come from where the caller has them and the operand reads transpose: two reads of 64 bits for one of 128, at half the
+// rate, so a step takes 0.04-0.055 us longer at d = 128 (2.3 % on 36K tokens), 0.15-0.2 ns with 256 workgroups; V^T costs 32 KB of traffic
+// a tile, 6 ns.  The line lies at the tiles' quotient.  Passes of two sparse layers with V^T / V, by steps a tile: 7 (1000 rows behind 99K)
+// 1746 / 1654 us, 10 (4.2K tokens, 16 KV heads) 264 / 260, 11 (window of 1024 on 27K) 962 / 947, 12 (1300 rows behind 28K) 436 / 427, 18 (2000
+// behind 58K) 1172 / 1149, 25 (3000 behind 37K) 1091 / 1078, 25 (16K, 16 KV heads) 1666 / 1664, 26 (3000 behind 17K) 602 / 602, 27 (window of
+// 4096 on 20K) 1359 / 1364, 27 (6K) 407 / 404, 29 (5.3K) 387 / 388, 33 (4000 behind 36K) 1412 / 1396, 34 (6.5K) 527 / 530, 39 (window of 4096 on
+// 27K) 1317 / 1329, 60 (11K) 737 / 743, 83 (16K) 1387 / 1408.
+// Up to 256 tiles (4 MB of V^T at d = 128) the copy is still in the L2s and costs little beside its launch, which is there either way: 20
+// (1.7K, 120 tiles) 107 / 106, 24 (1.7K, 60) 87.3 / 88.3, 24 (2.1K, 148) 122 / 124, 26 (2.6K, 188) 145 / 147, 27 (2.1K, 37) 100.5 / 101.4; but 11 (1.3K,
+// 192) 108 / 104, 15 (1.7K, 240) 125 / 119.
+// At d = 64 a step, which is bound by the vector ALU and by what stands around it, loses more (4-5 %), and V^T, half as large, is still in
+// the caches where it is up to some 32 MB: 1.2 (0.5K, 88 tiles) 69.7 / 70.4, 2.9 (1K, 144) 83.9 / 84.8, 3.6 (2K, 148) 82.9 / 84.1; 1.2 (300 rows
+// behind 18K, 2576) 110 / 105, 2.9 (1K, 576) 93.8 / 92.6, 3.0 (2000 rows behind 24K, 3688) 177 / 169; 4.6 (4K, 2336) 178.3 / 180.2, 8.8 (9K,
+// 1280) 170 / 173, 30 (9K) 406 / 413; above 4096 tiles 5.6 (1000 rows behind 29K, 4264) 309 / 297, 8.8 (9K, 5120) 475 / 468, 8.7-8.8
+// (window of 1024, 4304, 5248 and 7648) 551 / 554, 664 / 664 and 959 / 956, 10.7 (2000 behind 32K, 4808) 557 / 547, 12 (2500 behind 77K)
+// 1378 / 1357, 12.5 (16K, 9088) 1128 / 1137, 20 (30K, 17056) 3089 / 3111.
+inline bool transposed_values(int32_t head_dim, int64_t steps, int64_t tiles)
+{
+    const int64_t steps_per_tile = tiles <= 256 ? (head_dim == 128 ? 22 : 0) : head_dim == 128 ? 32 : tiles <= 4096 ? 4 : 10;
+    return steps >= steps_per_tile * tiles;
+}
+
 // What the query at position i sees apart from its head's class: keys *first .. *last; its image (empty for text).
 void row_bounds(const bs_tilemap *tm, int32_t i, int32_t *first, int32_t *last, int32_t *img_lo, int32_t *img_hi);
 
