@@ -1244,11 +1244,14 @@ void bs_plan_pairs(bs_tilemap *tm, int32_t G)
     // 32), but never so wide that the heaviest-first order loses its grip on the tail (a workgroup's
     // share of the steps / 64; below 32 tiles on prompts of less than some 20K tokens, whose K and V the caches
     // hold anyway).
-    // With up to some thirty rounds of blocks these are dealt there and back, so that every queue gets heavy and light ones alike: dealt in turn, the
-    // first queue had 6-14 % more steps than the last (d = 64, 9K tokens, 1144 units: 86 and 75 steps a workgroup; passes 779 -> 767
-    // us, 8K tokens, 912 units, 936 -> 931).  With more rounds the queues are even enough, and neighbours in a queue meet less in L2
-    // (281K tokens of d = 64, 8 KV heads, 8800 units: 29.9 ms in turn, 30.2 there and back).  In a window the blocks of a bucket
-    // are alike (1430 / 1432).
+    // Blocks are dealt there and back, so that every queue gets heavy and light ones alike.  Dealt in turn, the first queue of a launch with
+    // 16 / 28 rounds of blocks has 11-24 / 7-14 % more steps than the last, there and back 1-2 %: d = 64, 9K tokens, 1144 units, 779 -> 767 us, 8K
+    // tokens, 912 units, 936 -> 931; single layers in turn / there and back, 16K of d = 64, 2021 units, 480.2 / 472.5, 11K, 1745 units,
+    // 489.8 / 485.2, 16K, 1760, 660.5 / 659.2.  With more units the first queue still has 2-11 % more (41 rounds 1.04 and 1.11, 68 rounds 1.02 and
+    // 1.06), but whoever has emptied its own helps on the next one, and neighbours in a queue meet less in L2 if it is dealt there and back: 16K,
+    // 2520 units, 941.3 / 935.1, 24K, 2632, 1296 / 1296 and, all Dense, 3248 / 3243, 24K of d = 64, 3008, 918.9 / 917.5 and 2232 / 2249, 39.5K, 4333,
+    // 3144 / 3147 and 8566 / 8561, 60K, 6572, 6917 / 6925; 281K of d = 64, 8 KV heads, 8800, 29.9 / 30.2 ms.  So the line lies where
+    // the gain ends.  In a window the blocks of a bucket are alike (1430 / 1432).
     // In a window the cost says nothing about where a unit's keys lie: inside a bucket the units of a KV head stand in order
     // of their rows, and the buckets are 8 tiles wide (27K tokens, images of 256, window of 1024: 1624 -> 1603 us for three
     // layers, 4096: 3216 -> 3192, images of 1-5K 1388 -> 1364; 16 tiles the same, 64 tiles 2 % slower: the tail).
