@@ -3,12 +3,15 @@
 The matrix phase of the kernel issues its MFMAs through inline asm, so the compiler does not know
 that the registers those statements write are matrix-pipe results: it inserts no wait states if
 it decides to read, copy or overwrite one of them with a vector instruction right behind the
-MFMA.  The kernel inserts the wait states it needs by hand; this check makes sure the compiler
+MFMA.  Behind the last step of a unit the kernel waits by hand; behind the chains of the others it relies on
+what follows being long enough: the scores are finished by the MFMAs behind them, the output tile is next touched
+at the end of the vector phase, with a barrier and branches in between.  This check makes sure that it is, and that the compiler
 did not add an access of its own.
 
 Rule checked: a vector register written by a `v_mfma` is not named by any non-MFMA instruction
-within WAIT_STATES wait states (one per issued instruction, N + 1 for `s_nop N`) in straight-line
-code after it.  (An MFMA that accumulates into the same registers is interlocked by hardware.)
+within WAIT_STATES wait states (one per issued instruction, N + 1 for `s_nop N`) after it, in straight-line
+code (mfma_hazards) and on every path through branches, loops and barriers (flow_hazards).  (An MFMA that accumulates into
+the same registers is interlocked by hardware.)
 The 32x32x16 bf16 MFMA has 8 passes; the compiler's own rule for it is 11 wait states."""
 from __future__ import annotations
 
@@ -82,8 +85,8 @@ def lds_read_hazards(ins: list) -> list:
     the asm statement is over; check that nothing names a destination register while its read
     may still be in flight.  LDS reads complete in order: after `lgkmcnt(N)` all but the N
     youngest are done (scalar loads share the counter and only make the wait stricter).
-    Straight-line code only: the list of reads in flight is dropped at branches and labels,
-    which the kernel never crosses with a read outstanding.  Returns (read, offending
+    Straight-line code only: the list of reads in flight is dropped at branches and barriers; flow_hazards
+    follows those that cross one (the walk's branches stand between two batches).  Returns (read, offending
     instruction) pairs."""
     found = []
     inflight = []   # (instruction, destination registers), oldest first
@@ -133,6 +136,96 @@ def operand_hazards(ins: list) -> list:
     return found
 
 
+def kernel_blocks(isa: str, symbol_prefix: str) -> list:
+    """The kernel's basic blocks: [(instructions, indices of the blocks that may follow)].  An instruction of an inline asm statement
+    has a leading "asm "."""
+    start = isa.index("\n" + symbol_prefix) + 1
+    end = isa.index(".Lfunc_end", start)
+    blocks, label_at, in_asm = [[]], {}, False
+    for line in isa[start:end].split("\n"):
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            in_asm = "#ASMSTART" in line
+            continue
+        t = line.split(";")[0].strip()
+        if t.endswith(":"):
+            if blocks[-1]:
+                blocks.append([])
+            label_at[t[:-1]] = len(blocks) - 1
+        elif t and not t.startswith("."):
+            blocks[-1].append(("asm " if in_asm else "") + t)
+            if t.startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                blocks.append([])
+    out = []
+    for i, ins in enumerate(blocks):
+        last = ins[-1] if ins else ""
+        follow = [label_at[last.split()[1]]] if last.startswith(("s_cbranch", "s_branch")) else []
+        if not last.startswith(("s_branch", "s_endpgm")) and i + 1 < len(blocks):
+            follow.append(i + 1)
+        out.append((ins, follow))
+    return out
+
+
+def _wait_states(t: str) -> int:
+    m = re.match(r"s_nop (\d+)", t)
+    return int(m.group(1)) + 1 if m else 1
+
+
+def flow_hazards(blocks: list) -> list:
+    """The rules for MFMA results, their operands and asm LDS reads on every path through the kernel.  Along a path every register that an
+    MFMA (a vector instruction) has written has so many wait states left in which no other instruction may name it (no MFMA may read it);
+    LDS operations in flight are known by how many were issued behind them, as they complete in order.  Where paths meet, the longer wait
+    and the reads of both count.  Returns (rule, instruction, register)."""
+    found = set()
+
+    def run(ins, state):
+        result, operand, reads = dict(state[0]), dict(state[1]), dict(state[2])
+        for t in ins:
+            from_asm, u = t.startswith("asm "), t[4:] if t.startswith("asm ") else t
+            operands = u.split(None, 1)[1].split(", ") if " " in u else []
+            is_mfma, named = u.startswith("v_mfma"), _regs(u)
+            if is_mfma:
+                sources = _regs(", ".join(operands[1:3]))   # (the accumulator is interlocked)
+                found.update(("result as operand", u, r) for r in sources & result.keys())
+                found.update(("operand", u, r) for r in _regs(", ".join(operands[1:])) & operand.keys())
+            else:
+                found.update(("result", u, r) for r in named & result.keys())
+            found.update(("LDS read in flight", u, r) for r in named & reads.keys())
+            m = re.match(r"s_waitcnt .*lgkmcnt\((\d+)\)", u)
+            if m:
+                reads = {r: behind for r, behind in reads.items() if behind < int(m.group(1))}
+            if u.startswith("ds_"):
+                reads = {r: behind + 1 for r, behind in reads.items()}
+                if from_asm and u.startswith("ds_read"):
+                    reads.update((r, 0) for r in _regs(operands[0]))   # (a read of the compiler's own is waited for by the compiler)
+            ws = _wait_states(u)
+            for left in (result, operand):
+                for r in [r for r in left if left[r] <= ws]:
+                    del left[r]
+                for r in left:
+                    left[r] -= ws
+            if is_mfma:
+                result.update((r, WAIT_STATES) for r in _regs(operands[0]))
+                for r in _regs(operands[0]):
+                    operand.pop(r, None)
+            elif u.startswith("v_") and not u.startswith(("v_cmp", "v_readlane", "v_readfirstlane")):
+                operand.update((r, OPERAND_WAIT_STATES) for r in _regs(operands[0]) | (_regs(operands[1]) if "swap" in u.split()[0] else set()))
+        return result, operand, reads
+
+    meet = (max, max, min)   # (fewer operations behind a read: a wait for a given number of them ends later)
+    entry = [None] * len(blocks)
+    entry[0] = ({}, {}, {})
+    todo = [0]
+    while todo:
+        i = todo.pop()
+        state = run(blocks[i][0], entry[i])
+        for j in blocks[i][1]:
+            merged = entry[j] and tuple({r: f(x[r] for x in (a, b) if r in x) for r in a.keys() | b.keys()} for f, a, b in zip(meet, entry[j], state))
+            if entry[j] is None or merged != entry[j]:
+                entry[j] = merged or state
+                todo.append(j)
+    return sorted(found, key=str)
+
+
 def check(isa_path: str | None = None) -> dict:
     """Compile (unless a listing is given) and return {kernel symbol prefix: [hazards]}."""
     if isa_path is None:
@@ -145,7 +238,7 @@ def check(isa_path: str | None = None) -> dict:
     out = {}
     for k in KERNELS:
         ins = kernel_instructions(isa, k)
-        out[k] = mfma_hazards(ins) + lds_read_hazards(ins) + operand_hazards(ins)
+        out[k] = mfma_hazards(ins) + lds_read_hazards(ins) + operand_hazards(ins) + flow_hazards(kernel_blocks(isa, k))
     return out
 
 
