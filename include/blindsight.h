@@ -283,7 +283,7 @@ int bs_tilemap_upload(bs_tilemap *tm);
  *            owns q/k/v/out and keeps them alive until the stream has drained.
  * bf16 path: a pre-pass first packs the keys and values of compact tiles, and all of V (transposed) where its tiles are
  * walked often, into per-key-tile blocks in a workspace the map owns (n_kv_heads * (2 n_tiles - seq_len / 64) * head_dim * 128 bytes, n_tiles from
- * bs_tilemap_walked: the size of V, and twice as much more as there are compact tiles; and the partial results of work units that are
+ * bs_tilemap_walked: the size of V, whether or not all of it is packed, and twice as much more as there are compact tiles; and the partial results of work units that are
  * cut; taken from the library's block cache or hipMalloc on first use).  Calls with a few rows that see the
  * whole cache read K and V where they are; they and the fp32 path use the workspace for partial results.
  * Calls that share a map share that workspace: the library orders a call after

@@ -38,7 +38,7 @@ struct KernelArgs {
     int32_t n_prompt_tiles;   // key tiles that are the prompt in position order; compact tiles of free keys follow, ...
     int32_t text_tile0;       // ... and from here on compact tiles of text keys (n_tiles: none)
     int32_t n_tiles;
-    int32_t first_tile;       // a tile that is there for a list without any (bf16: packed)
+    int32_t first_tile;       // a tile that is there for a list without any
     int32_t window, bidir;
     int32_t q_begin;          // q / out hold the query positions q_begin .. L - 1, row r = position q_begin + r
 };

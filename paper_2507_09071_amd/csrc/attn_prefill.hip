@@ -376,7 +376,7 @@ __device__ __forceinline__ void walk_units(
     constexpr int NPV = KT == 2 ? 4 : NDB;   // operands of a PV batch
     constexpr int RPV = VT ? 1 : 2;          // reads of such an operand
     constexpr int NT = D / 16;            // 16-wide slices of the head dim
-    extern __shared__ __align__(1024) unsigned char lds[];   // K slots 0..3, then V^T slots 0..3
+    extern __shared__ __align__(1024) unsigned char lds[];   // K slots 0..3, then V (V^T) slots 0..3
 
     const int tid = threadIdx.x, lane = tid & 63, hl = lane >> 5, col = lane & 31;
     const int grp = __builtin_amdgcn_readfirstlane(tid >> 8);          // wave group 0 / 1
@@ -518,11 +518,11 @@ __device__ __forceinline__ void walk_units(
 
     // Phase X of step k: O += P(k-1) V(k-1) and S(k) = K(k) Q^T.  Always the same straight-line
     // chain of asm statements: before the first tile -- and behind tiles this item skips -- P is zero,
-    // and the scores of a tile it skips are ignored.  Operand reads run three batches ahead of the MFMAs that consume
-    // them, in three rotating register sets; each lds_wait<N> count is the number of reads
-    // issued after the batch waited for.  A register is refilled right after the MFMA that
-    // read it has issued (operands are read at issue, LDS data returns later), so the reads
-    // issue in the shadow of the MFMAs.
+    // and the scores of a tile it skips are ignored.  Operand reads run up to three batches ahead of the MFMAs that
+    // consume them (at the head of the chain two, three where batches are halves), in three rotating register sets; each
+    // lds_wait<N> count is the number of reads issued after the batch waited for (a transposing operand takes two).
+    // A register is refilled right after the MFMA that read it has issued (operands are read at issue, LDS data
+    // returns later), so the reads issue in the shadow of the MFMAs.
     // text / sink key bits of the tile of the coming phase Y (scalar registers)
     uint64_t tb_cur[KT] = {}, sb_cur[KT] = {};
     const char *ksrc[KT] = {}, *vsrc[KT] = {};   // tiles of the coming refill ...

@@ -3,9 +3,9 @@
 // The 128-row query tiles of the prefill kernel are the wrong shape here.  The work is reading K and V once,
 // so the bound is HBM, and what the prefill path does around it (a packed copy of V, a K and V tile per two heads, units
 // cut over the chip and merged) costs a multiple of the read.  Measured, one row: 28 heads over 39.5K keys of
-// 4 KV heads (81 MB) 103 us there, 21.0 us a call here, two kernels (by time stamps: 1.3 us until the first keys are requested,
-// 7.2 TB/s from there until the last ones have arrived at 14 us; 1.2 us to the end of the first kernel; the merge; a kernel that only
-// reads takes 15.3 us for so little); 32 heads over 302K keys of 16 KV heads (2.5 GB) 1060 us there, 412 + 4 us here (6.0
+// 4 KV heads (81 MB) 103 us there, 21.0 us a call here, two kernels (by time stamps, keys from HBM, medians of 36 launches: the waves request
+// their first keys at 0.9 us, their last ones have arrived at 13.1 us on average, 6.6 TB/s, and at 15.1 for the last of the 1024 waves, 5.7;
+// the first kernel ends at 15.8, the merge runs from 16.9 to 18.8; a kernel that only reads takes 15.3 us for so little); 32 heads over 302K keys of 16 KV heads (2.5 GB) 1060 us there, 412 + 4 us here (6.0
 // TB/s; a kernel that only reads reaches 6.2).  How:
 //  * the query rows of ALL heads of a GQA group are stacked (head-major) into blocks of 32 rows, the free
 //    dimension of a 32x32x16 MFMA, so K and V of a KV head are read once for the whole group;

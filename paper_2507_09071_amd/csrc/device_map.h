@@ -95,7 +95,7 @@ struct DeviceMap {
     int64_t n_steps = 0;                  // key-tile steps of the work units
     const StackedRows *stacked = nullptr; // which rows the stacked tiles among the units hold (bf16)
     int32_t *queue_ctr = nullptr;         // [8] next unit of each queue; cleared by the pre-pass of every call
-    // ---- bf16 workspace: packed K tiles, then packed V^T tiles, or partial results, of the last call
+    // ---- bf16 workspace: packed K tiles, then V^T tiles or packed V tiles (room for all of V^T either way), or partial results, of the last call
     void *vt_buf = nullptr;
     size_t vt_bytes = 0;
     // Workspaces that a larger one took the place of, kept as long as the map: a call of it that was captured into a graph
